@@ -8,9 +8,9 @@
 // by streaming X / Y once through HBM, not by MFMA rate; the tiling below is chosen for full-width 16-byte
 // loads and stores per lane, with the small operand (W) resident in LDS.
 //
-// MFMA shape used everywhere: v_mfma_f32_32x32x16_f16.  Operand A is 32 x 16: lane l holds row l % 32,
-// columns 8*(l / 32) .. +7.  Operand B is 16 x 32: lane l holds column l % 32, rows 8*(l / 32) .. +7.
-// The 32 x 32 result: lane l holds column l % 32; its element r (0..15) is row 8*(r / 4) + 4*(l / 32) + r % 4.
+// MFMA shape used everywhere: v_mfma_f32_16x16x32_f16.  Operand A is 16 x 32: lane l holds row l % 16,
+// columns 8*(l / 16) .. +7.  Operand B is 32 x 16: lane l holds column l % 16, rows 8*(l / 16) .. +7.
+// The 16 x 16 result: lane l holds column l % 16, rows 4*(l / 16) .. +3.
 #include <algorithm>
 #include <cstdio>
 
@@ -18,11 +18,7 @@
 
 namespace hgnn {
 
-typedef float float16_t __attribute__((ext_vector_type(16)));
-
-constexpr int kRowsPerWave = 32;                           // rows of X one wave multiplies per step
-constexpr int kRowsPerBlock = kRowsPerWave * kWavesPerBlock;
-constexpr int kLinearLdsHalves = 28 * 1024;                // LDS budget of the weight tile, in halves (56 KB)
+typedef float float4_t __attribute__((ext_vector_type(4)));
 
 struct LinearArgs {
   int64_t n;
@@ -34,134 +30,178 @@ struct LinearArgs {
   int trans;  // 0: W is [K][F]; 1: W is [F][K]
   half_t* Y;
   int64_t ldy;
-  int KC;  // columns of X (rows of W) held in LDS at a time; a multiple of 16
+  int KC;     // columns of X (rows of W) held in LDS at a time; a multiple of 32, and of the 128 columns of a group when K > KC
+  int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
+  int wvec;   // W may be read in 16-byte pieces
 };
 
-__device__ __forceinline__ unsigned pack2(float a, float b) {
-  const half2_t h = {half_t(a), half_t(b)};
-  return __builtin_bit_cast(unsigned, h);
-}
-
-// Y[r, fc0 .. fc0 + 32*NT) for the 128 rows of a workgroup pass; fc0 = blockIdx.y * 32 * NT.  The weight tile
-// sits in LDS transposed (Wt[f][k], pitch KC + 8 halves so that the 16-byte reads of 32 consecutive f are
-// spread over the banks); it is loaded once per workgroup when K fits (KC >= K) and the workgroup then walks
-// row blocks grid-stride, otherwise once per row block and chunk of K.  The product is formed transposed
-// (features x rows), which leaves every lane with values of ONE row of Y: after one exchange between the two
-// half-waves a lane stores two 16-byte pieces.
-// the four 16-byte pieces of X that one lane feeds into four consecutive MFMA steps (64 columns from k0 on)
-struct XGroup {
-  half8_t b[4];
-};
-
-__device__ __forceinline__ XGroup load_xgroup(const half_t* xrow, bool row_ok, int k0, int kn, int hf) {
-  XGroup g;
+// The weight tile W[kc .. kc+KC)[fc0 .. fc0+FC) into LDS in the order in which the products read it: fragment
+// (tile t of 16 features, step ks of 32 columns) is 64 lanes x 16 bytes, so every read of it is one conflict-free
+// kilobyte.  The features of a pair of tiles are dealt out so that a lane's 2 x 4 result values are 8 consecutive
+// features: tile 2b+o, row i of the tile <-> feature 32b + 8(i/4) + 4o + i%4.
+// W [F][K]: a thread moves one 16-byte piece of a row.  W [K][F]: a thread reads an 8 x 8 block and writes it transposed.
+__device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __restrict__ Wf, int kc, int fc0) {
+  const int KS = a.KC / 32;
+  const int kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0);
+  const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (a.trans) {
+    const int total = (a.FC / 16) * KS * kWave;
+    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+      const int lane = idx & (kWave - 1), fr = idx >> 6;
+      const int t = fr / KS, ks = fr - t * KS;
+      const int i = lane & 15, q = lane >> 4;
+      const int f = 32 * (t >> 1) + 8 * (i >> 2) + 4 * (t & 1) + (i & 3), k = 32 * ks + 8 * q;
+      half8_t v = zero;
+      if (f < fn && k < kn) {
+        const half_t* src = a.W + int64_t(fc0 + f) * a.ldw + kc + k;
+        if (a.wvec) {
+          v = *reinterpret_cast<const half8_t*>(src);
+        } else {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int kk = k0 + 16 * u + 8 * hf;
-    g.b[u] = (row_ok && kk < kn) ? *reinterpret_cast<const half8_t*>(xrow + kk) : zero;
+          for (int j = 0; j < 8; ++j) v[j] = src[j];
+        }
+      }
+      *reinterpret_cast<half8_t*>(Wf + int64_t(idx) * 8) = v;
+    }
+  } else {
+    const int F8 = a.FC / 8, total = F8 * (a.KC / 8);
+    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+      const int k8 = idx / F8, f8 = idx - k8 * F8;
+      half8_t row[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        row[j] = zero;
+        if (8 * k8 < kn) {  // K is a multiple of 8: the eight rows are inside the matrix or outside together
+          const half_t* src = a.W + int64_t(kc + 8 * k8 + j) * a.ldw + fc0 + 8 * f8;
+          if (a.wvec && 8 * f8 + 8 <= fn) {
+            row[j] = *reinterpret_cast<const half8_t*>(src);
+          } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+              if (8 * f8 + c < fn) row[j][c] = src[c];
+          }
+        }
+      }
+      const int ks = k8 >> 2, q = k8 & 3, b = f8 >> 2, i4 = 4 * (f8 & 3);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        half8_t v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = row[j][c];
+        const int t = 2 * b + (c >> 2), lane = 16 * q + i4 + (c & 3);
+        *reinterpret_cast<half8_t*>(Wf + ((int64_t(t) * KS + ks) * kWave + lane) * 8) = v;
+      }
+    }
   }
-  return g;
 }
 
-template <int NT>
-__global__ __launch_bounds__(kBlock, NT == 4 ? 3 : 4) void linear_kernel(LinearArgs a) {
+// Y[16*RT rows per wave and step] = X . W on the matrix cores, formed transposed (features x rows): a lane holds values of
+// ONE row of Y, and with the feature order of linear_load_w they are whole 16-byte pieces, four lanes to 64 consecutive
+// bytes of a row; a load of X is likewise 64 consecutive bytes of 16 rows.  NT tiles of 16 features per pass over the
+// row tile's columns (X of the row tile is read again from the caches for further passes).
+// The bound is the stream of X and Y.  What the first form of this kernel lost against it was the weight: it came in
+// by 2-byte LDS stores with a division each, once per workgroup of one to nine 128-row passes, again for every row block
+// when K > 440, and X was read once per 128 features from memory.  Now workgroups are persistent, as many as the LDS
+// and registers of the chip hold, a workgroup brings its part of W in once (16-byte pieces) and the loads of X run one
+// group (4 x 16 bytes per lane) ahead of the products across passes and row blocks.  2.4 M x 128 -> 128: 323 -> 249 us
+// (4.9 TB/s, what a copy reaches); 233 k x 608 -> 64: 232 -> 64 us; 131 k x 128 -> 128: 40 -> 17 us.  Two row tiles per
+// wave for the sake of the weight fragments were slower (2.4 M: 325 us): the kernel waits for rows, not for LDS, and the
+// registers are better spent on the loads in flight.  RT > 1 is for rows that do not fill a group: with K <= 64 (32) a group
+// takes two (four) row tiles, so that as many bytes are in flight as with long rows.
+// CHUNKED: the weights of 128 features do not fit; the columns come in chunks, a chunk of W once per row block.
+template <int NT, int RT, bool CHUNKED>
+__global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
+  constexpr int GS = 4 / RT;    // 32-column steps in a group of X loads
+  constexpr int GK = 32 * GS;   // columns of a group
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  half_t* Wt = reinterpret_cast<half_t*>(lds_raw);
-  const int pitch = a.KC + 8;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int m = lane & 31, hf = lane >> 5;
-  const int fc0 = blockIdx.y * 32 * NT;
-  const int nchunks = (a.K + a.KC - 1) / a.KC;
-  const int64_t nrb = (a.n + kRowsPerBlock - 1) / kRowsPerBlock;
-  bool loaded = false;
-  // The loads of X run one group (64 columns) ahead of the products, across chunk and row-block borders, so
-  // that a wave always has memory requests in flight while it multiplies and stores.
-  XGroup next{};
-  if (int64_t(blockIdx.x) < nrb) {
-    const int64_t row = int64_t(blockIdx.x) * kRowsPerBlock + wave * kRowsPerWave + m;
-    next = load_xgroup(a.X + (row < a.n ? row : 0) * a.ldx, row < a.n, 0, min(a.KC, a.K), hf);
+  half_t* Wf = reinterpret_cast<half_t*>(lds_raw);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, wpw = blockDim.x / kWave;
+  const int i = lane & 15, q = lane >> 4;
+  const int fc0 = blockIdx.y * a.FC;
+  const int KS = a.KC / 32;
+  const int nchunks = CHUNKED ? (a.K + a.KC - 1) / a.KC : 1;
+  const int npass = CHUNKED ? 1 : (min(a.FC, a.F - fc0) + 16 * NT - 1) / (16 * NT);
+  const bool keep = RT > 1 || a.K <= GK;  // one group holds the whole row: it serves all passes
+  const int64_t nrb = (a.n + int64_t(16 * RT) * wpw - 1) / (int64_t(16 * RT) * wpw);
+  const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  half8_t next[4];
+  auto load_group = [&](int64_t rb, int k0) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int64_t row = (rb * wpw + wave) * (16 * RT) + 16 * r + i;
+      const half_t* src = a.X + (row < a.n ? row : 0) * a.ldx + k0 + 8 * q;
+#pragma unroll
+      for (int u = 0; u < GS; ++u) {
+        next[r * GS + u] = zero;
+        if (row < a.n && k0 + 32 * u + 8 * q < a.K) next[r * GS + u] = *reinterpret_cast<const half8_t*>(src + 32 * u);
+      }
+    }
+  };
+  load_group(blockIdx.x, 0);
+  if (!CHUNKED) {
+    linear_load_w(a, Wf, 0, fc0);
+    __syncthreads();
   }
   for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
-    const int64_t row = rb * kRowsPerBlock + wave * kRowsPerWave + m;
-    const bool row_ok = row < a.n;
-    const half_t* xrow = a.X + (row_ok ? row : 0) * a.ldx;
-    float16_t acc[NT];
+    half8_t cur[4];
+    for (int pass = 0; pass < npass; ++pass) {
+      float4_t acc[RT][NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+      for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-    for (int c = 0; c < nchunks; ++c) {
-      const int kc = c * a.KC;
-      const int kn = min(a.KC, a.K - kc);  // a multiple of 8
-      if (!loaded || nchunks > 1) {
-        if (loaded) __syncthreads();  // everyone is done with the previous tile
-        const int total = 32 * NT * a.KC;
-        if (a.trans) {
-          for (int idx = threadIdx.x; idx < total; idx += kBlock) {
-            const int fl = idx / a.KC, k = idx - fl * a.KC;
-            const bool ok = k < kn && fc0 + fl < a.F;
-            Wt[fl * pitch + k] = ok ? a.W[int64_t(fc0 + fl) * a.ldw + kc + k] : half_t(0);
-          }
-        } else {
-          for (int idx = threadIdx.x; idx < total; idx += kBlock) {
-            const int k = idx / (32 * NT), fl = idx - k * (32 * NT);
-            const bool ok = k < kn && fc0 + fl < a.F;
-            Wt[fl * pitch + k] = ok ? a.W[int64_t(kc + k) * a.ldw + fc0 + fl] : half_t(0);
-          }
+        for (int t = 0; t < NT; ++t) acc[r][t] = float4_t{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < nchunks; ++c) {
+        const int kc = c * a.KC;
+        const int kn = CHUNKED ? min(a.KC, a.K - kc) : a.K;
+        if (CHUNKED) {  // trip counts are uniform over the workgroup
+          __syncthreads();
+          linear_load_w(a, Wf, kc, fc0);
+          __syncthreads();
         }
-        __syncthreads();
-        loaded = true;
-      }
-      for (int k0 = 0; k0 < kn; k0 += 64) {
-        const XGroup cur = next;
-        // what comes after this group: more of this chunk, the next chunk of the row, or the next row block
-        if (k0 + 64 < kn) {
-          next = load_xgroup(xrow + kc, row_ok, k0 + 64, kn, hf);
-        } else if (c + 1 < nchunks) {
-          next = load_xgroup(xrow + kc + a.KC, row_ok, 0, min(a.KC, a.K - kc - a.KC), hf);
-        } else if (rb + gridDim.x < nrb) {
-          const int64_t nrow = row + int64_t(gridDim.x) * kRowsPerBlock;
-          next = load_xgroup(a.X + (nrow < a.n ? nrow : 0) * a.ldx, nrow < a.n, 0, min(a.KC, a.K), hf);
-        }
+        for (int k0 = 0; k0 < kn; k0 += GK) {
+          if (!keep || pass == 0) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (k0 + 16 * u < kn) {  // uniform; keeps the LDS reads inside the tile
+            for (int u = 0; u < 4; ++u) cur[u] = next[u];
+          }
+          // what comes after this group: more of the row, the row again for the next pass, or the next row block
+          if (kc + k0 + GK < a.K) load_group(rb, kc + k0 + GK);
+          else if (pass + 1 < npass) { if (!keep) load_group(rb, 0); }
+          else if (rb + gridDim.x < nrb) load_group(rb + gridDim.x, 0);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              const half8_t w = *reinterpret_cast<const half8_t*>(Wt + (32 * t + m) * pitch + k0 + 16 * u + 8 * hf);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w, cur.b[u], acc[t], 0, 0, 0);
+          for (int u = 0; u < GS; ++u) {
+            if (k0 + 32 * u < kn) {  // uniform
+              const half_t* w = Wf + ((int64_t(pass) * NT * KS + (k0 / 32 + u)) * kWave + lane) * 8;
+#pragma unroll
+              for (int t = 0; t < NT; ++t) {
+                const half8_t wv = *reinterpret_cast<const half8_t*>(w + int64_t(t) * KS * (kWave * 8));
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+                  acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, cur[r * GS + u], acc[r][t], 0, 0, 0);
+              }
             }
           }
         }
       }
-    }
-    // acc[t][4q + i] = Y[row][fc0 + 32t + 8q + 4hf + i].  The lower half-wave keeps the groups q = 0, 1 and
-    // gets the partner's halves of them, the upper one keeps q = 2, 3.
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float16_t c = acc[t];
-      const unsigned p0 = pack2(c[0], c[1]), p1 = pack2(c[2], c[3]), p2 = pack2(c[4], c[5]), p3 = pack2(c[6], c[7]);
-      const unsigned p4 = pack2(c[8], c[9]), p5 = pack2(c[10], c[11]), p6 = pack2(c[12], c[13]), p7 = pack2(c[14], c[15]);
-      const unsigned k0 = hf ? p4 : p0, k1 = hf ? p5 : p1, k2 = hf ? p6 : p2, k3 = hf ? p7 : p3;  // kept
-      const unsigned g0 = unsigned(__shfl_xor(int(hf ? p0 : p4), 32)), g1 = unsigned(__shfl_xor(int(hf ? p1 : p5), 32));
-      const unsigned g2 = unsigned(__shfl_xor(int(hf ? p2 : p6), 32)), g3 = unsigned(__shfl_xor(int(hf ? p3 : p7), 32));
-      if (row_ok) {
-        // lower half-wave: its own values are features 0..3 of a group, the partner's 4..7; upper: the other way
-        const int4_t va = hf ? int4_t{int(g0), int(g1), int(k0), int(k1)} : int4_t{int(k0), int(k1), int(g0), int(g1)};
-        const int4_t vb = hf ? int4_t{int(g2), int(g3), int(k2), int(k3)} : int4_t{int(k2), int(k3), int(g2), int(g3)};
+      for (int r = 0; r < RT; ++r) {
+        const int64_t row = (rb * wpw + wave) * (16 * RT) + 16 * r + i;
+        if (row >= a.n) continue;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int f = fc0 + 32 * t + 8 * (2 * hf + j);
-          const int4_t v = j ? vb : va;
+        for (int b = 0; b < NT / 2; ++b) {
+          const int f = fc0 + 16 * NT * pass + 32 * b + 8 * q;
+          half8_t h;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            h[j] = half_t(acc[r][2 * b][j]);
+            h[4 + j] = half_t(acc[r][2 * b + 1][j]);
+          }
           half_t* dst = a.Y + row * a.ldy + f;
           if (f + 8 <= a.F) {
-            *reinterpret_cast<int4_t*>(dst) = v;
+            *reinterpret_cast<half8_t*>(dst) = h;
           } else if (f < a.F) {
-            const half8_t h = __builtin_bit_cast(half8_t, v);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (i < a.F - f) dst[i] = h[i];
+            for (int j = 0; j < 8; ++j)
+              if (j < a.F - f) dst[j] = h[j];
           }
         }
       }
@@ -177,99 +217,169 @@ struct WgradArgs {
   int64_t ldx;
   const half_t* dY;
   int64_t ldy;
-  float* part;  // [parts][K][F] fp32
-  int parts;    // partial results = waves along blockIdx.x
+  float* part;  // [gridDim.x][K][F] fp32
 };
 
-constexpr int kWgradRows = 16;                 // rows of X and dY per MFMA step
-constexpr int kWgradTile = 64;                 // a wave owns a 64 x 64 block of dW
-constexpr int kWgradPitch = kWgradTile + 8;    // halves; 16-byte aligned rows, half-waves on different banks
+constexpr int kWgradRows = 32;  // rows of X and dY per step
+constexpr int kWgradTile = 64;  // a wave owns a 64 x 64 block of dW
 
-// dW[kc0 .. kc0+64, fc0 .. fc0+64) = sum over rows of X[:, k] * dY[:, f].  Every wave walks groups of 16 rows
-// grid-stride, keeps a 64 x 64 fp32 block in registers and leaves it as partial number p in the workspace
-// (summed in a fixed order afterwards: no atomics, the same bits on every run).  The two operands are wanted
-// column-wise (eight consecutive ROWS of one column per lane), so a wave loads its 16 x 64 tiles with 16-byte
-// row reads, parks them in its private LDS region and picks the columns from there.
-__global__ __launch_bounds__(kBlock) void wgrad_kernel(WgradArgs a) {
-  __shared__ __align__(16) half_t lds[kWavesPerBlock][2][kWgradRows * kWgradPitch];
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) short4_t lds_short4_t;
+
+// Eight consecutive rows of one column per lane (an MFMA operand whose contraction runs over the rows) out of a
+// row-major LDS tile: ds_read_b64_tr_b16 transposes 4 rows x 16 columns among 16 lanes (lane i supplies the address
+// of row i/4, columns 4*(i%4).., and receives column i).
+__device__ __forceinline__ half8_t wgrad_column(const half_t* tile, int pitch, int c0, int lane) {
+  const int i = lane & 15, q = lane >> 4;
+  const half_t* p = tile + (8 * q + (i >> 2)) * pitch + c0 + 4 * (i & 3);
+  const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)p);
+  const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(p + 4 * pitch));
+  typedef short short8_t __attribute__((ext_vector_type(8)));
+  const short8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(half8_t, v);
+}
+
+// dW[64*WA columns of X][64*WB columns of dY] of one workgroup = sum over its rows of X[:, k] * dY[:, f].  The four waves
+// form WR = 4 / (WA*WB) row teams of WA x WB waves; a team parks its 32 x 64*WA and 32 x 64*WB tiles in LDS (whole rows,
+// 16 bytes per lane, the next step's pieces in flight meanwhile) and a wave picks its operands from there column-wise
+// with transposing reads; pitch = columns + 16 halves puts the four rows of such a read on different banks.  At the end
+// the teams are added in LDS in a fixed order and the workgroup leaves one partial result in the workspace: no
+// atomics, the same bits on every run.  WA = WB = 2 lets X and dY of up to 128 columns be read once; the form before
+// (a 64 x 64 block per wave, columns picked by 2-byte LDS reads, a partial per wave) read both twice and was bound by
+// those reads.
+template <int WA, int WB>
+__global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
+  constexpr int WT = WA * WB, WR = 4 / WT;     // waves in a team, teams
+  constexpr int NBUF = WR == 1 ? 2 : 1;        // one team: two buffers, one barrier per step
+  constexpr int PX = 64 * WA + 16, PY = 64 * WB + 16;
+  constexpr int TILE = kWgradRows * (PX + PY);
+  constexpr int NX = 4 / WB, NY = 4 / WA;      // 16-byte pieces per thread and step
+  constexpr int kTileBytes = WR * NBUF * TILE * 2, kSumBytes = WR > 1 ? WT * kWave * 64 * 4 : 0;
+  __shared__ __align__(16) unsigned char lds[kTileBytes > kSumBytes ? kTileBytes : kSumBytes];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int m = lane & 31, hf = lane >> 5;
-  const int kc0 = blockIdx.y * kWgradTile, fc0 = blockIdx.z * kWgradTile;
-  half_t* xs = lds[wave][0];
-  half_t* ys = lds[wave][1];
-  const int p = blockIdx.x * kWavesPerBlock + wave;
-  const int64_t ngroups = (a.n + kWgradRows - 1) / kWgradRows;
-  float16_t acc[2][2];
+  const int team = wave / WT, tw = wave % WT, wa = tw / WB, wb = tw % WB;
+  const int tt = tw * kWave + lane;            // thread of the team
+  const int kc0 = blockIdx.y * 64 * WA, fc0 = blockIdx.z * 64 * WB;
+  half_t* tiles = reinterpret_cast<half_t*>(lds) + team * NBUF * TILE;
+  const int64_t nsteps = (a.n + int64_t(kWgradRows) * WR - 1) / (int64_t(kWgradRows) * WR);
+  const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  half8_t vx[NX], vy[NY];
+  auto load = [&](int64_t step) {
+    const int64_t r0 = (step * WR + team) * kWgradRows;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < NX; ++u) {
+      const int p = tt + u * (WT * kWave), row = p / (8 * WA), c = 8 * (p % (8 * WA));
+      vx[u] = zero;  // K and F are multiples of 8 here, so a piece is inside the matrix or outside it as a whole
+      if (r0 + row < a.n && kc0 + c < a.K) vx[u] = *reinterpret_cast<const half8_t*>(a.X + (r0 + row) * a.ldx + kc0 + c);
+    }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  // lane -> (row of the group, 16-byte piece of the 64-column tile): 16 rows x 8 pieces = 128 pieces, 2 per lane
-  const int pr = lane >> 3, pc = (lane & 7) * 8;
-  for (int64_t g = p; g < ngroups; g += a.parts) {
-    const int64_t r0 = g * kWgradRows;
-    half8_t vx[2], vy[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t row = r0 + pr + 8 * u;
-      const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      vx[u] = zero;
+    for (int u = 0; u < NY; ++u) {
+      const int p = tt + u * (WT * kWave), row = p / (8 * WB), c = 8 * (p % (8 * WB));
       vy[u] = zero;
-      if (row < a.n) {
-        // K and F are multiples of 8 here, so a piece is inside the matrix or outside it as a whole
-        if (kc0 + pc < a.K) vx[u] = *reinterpret_cast<const half8_t*>(a.X + row * a.ldx + kc0 + pc);
-        if (fc0 + pc < a.F) vy[u] = *reinterpret_cast<const half8_t*>(a.dY + row * a.ldy + fc0 + pc);
-      }
+      if (r0 + row < a.n && fc0 + c < a.F) vy[u] = *reinterpret_cast<const half8_t*>(a.dY + (r0 + row) * a.ldy + fc0 + c);
     }
-    wave_sync();  // the previous step's column reads are done
+  };
+  auto meet = [&]() {
+    if (WT == 1) wave_sync();
+    else __syncthreads();
+  };
+  float4_t acc[4][4];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      *reinterpret_cast<half8_t*>(xs + (pr + 8 * u) * kWgradPitch + pc) = vx[u];
-      *reinterpret_cast<half8_t*>(ys + (pr + 8 * u) * kWgradPitch + pc) = vy[u];
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[x][y] = float4_t{0.f, 0.f, 0.f, 0.f};
+  int buf = 0;
+  if (int64_t(blockIdx.x) < nsteps) load(blockIdx.x);
+  for (int64_t step = blockIdx.x; step < nsteps; step += gridDim.x) {  // uniform over the workgroup
+    half_t* xs = tiles + buf * TILE;
+    half_t* ys = xs + kWgradRows * PX;
+    if (NBUF == 1) meet();  // the previous step's column reads are done
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      const int p = tt + u * (WT * kWave), row = p / (8 * WA), c = 8 * (p % (8 * WA));
+      *reinterpret_cast<half8_t*>(xs + row * PX + c) = vx[u];
     }
-    wave_sync();
-    half8_t xa[2], yb[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int u = 0; u < NY; ++u) {
+      const int p = tt + u * (WT * kWave), row = p / (8 * WB), c = 8 * (p % (8 * WB));
+      *reinterpret_cast<half8_t*>(ys + row * PY + c) = vy[u];
+    }
+    meet();
+    if (step + gridDim.x < nsteps) load(step + gridDim.x);
+    half8_t xa[4], yb[4];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        xa[t][j] = xs[(8 * hf + j) * kWgradPitch + 32 * t + m];
-        yb[t][j] = ys[(8 * hf + j) * kWgradPitch + 32 * t + m];
-      }
+    for (int t = 0; t < 4; ++t) {
+      xa[t] = wgrad_column(xs, PX, 64 * wa + 16 * t, lane);
+      yb[t] = wgrad_column(ys, PY, 64 * wb + 16 * t, lane);
+    }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[i], yb[j], acc[i][j], 0, 0, 0);
+      for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[x], yb[y], acc[x][y], 0, 0, 0);
+    if (NBUF == 2) buf ^= 1;
   }
-  float* out = a.part + int64_t(p) * a.K * a.F;
+  if (WR > 1) {
+    float4_t* sum = reinterpret_cast<float4_t*>(lds) + tw * (16 * kWave) + lane;
+    for (int w = 1; w < WR; ++w) {
+      __syncthreads();
+      if (team == w) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+          for (int y = 0; y < 4; ++y) sum[(4 * x + y) * kWave] = acc[x][y];
+      }
+      __syncthreads();
+      if (team == 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int k = kc0 + 32 * i + 8 * (r / 4) + 4 * hf + (r % 4);
-        const int f = fc0 + 32 * j + m;
-        if (k < a.K && f < a.F) out[int64_t(k) * a.F + f] = acc[i][j][r];
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) acc[x][y] += sum[(4 * x + y) * kWave];
+      }
+    }
+    if (team != 0) return;
+  }
+  float* out = a.part + int64_t(blockIdx.x) * a.K * a.F;
+  const int i = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = kc0 + 64 * wa + 16 * x + 4 * q + r, f = fc0 + 64 * wb + 16 * y + i;
+        if (k < a.K && f < a.F) out[int64_t(k) * a.F + f] = acc[x][y][r];
       }
 }
 
-// out[q][e] = sum_{j < group} in[q*group + j][e] (j ascending, partials in_stride apart), e < elems; e = k*F + f lands at
-// out + q*out_stride + k*out_ld + f.  Two rounds of this add the partial results in a fixed order.
-__global__ __launch_bounds__(kBlock) void partial_sum_kernel(const float* __restrict__ in, int64_t in_stride, int nparts, int group,
-                                                            int64_t elems, int F, float* __restrict__ out, int64_t out_stride,
-                                                            int64_t out_ld) {
-  const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  const int q = blockIdx.y;
-  if (e >= elems) return;
-  const int j0 = q * group, j1 = min(nparts, j0 + group);
+// out[k*out_ld + f] = sum over the partials j (part_stride apart) of in[j][e], e = k*F + f < elems; from element `split` on the
+// result goes to out2[e - split].  A workgroup takes 64 elements; its kSumSlices slices add a strided share of the partials
+// each and the slice sums are added in slice order: a fixed order whatever the launch, in one launch (two rounds of
+// launches cost 4-5 us each on the smallest layers, more than the addition).
+constexpr int kSumSlices = 16;
+
+__global__ __launch_bounds__(kWave * kSumSlices) void partial_sum_kernel(const float* __restrict__ in, int64_t part_stride, int nparts,
+                                                                         int64_t elems, int F, float* __restrict__ out, int64_t out_ld,
+                                                                         int64_t split, float* __restrict__ out2) {
+  __shared__ float red[kSumSlices][kWave];
+  const int x = threadIdx.x & (kWave - 1), y = threadIdx.x / kWave;
+  const int64_t e = int64_t(blockIdx.x) * kWave + x;
   float s = 0.f;
+  if (e < elems) {
 #pragma unroll 8
-  for (int j = j0; j < j1; ++j) s += in[int64_t(j) * in_stride + e];
-  const int64_t k = e / F, f = e - k * F;
-  out[int64_t(q) * out_stride + k * out_ld + f] = s;
+    for (int j = y; j < nparts; j += kSumSlices) s += in[int64_t(j) * part_stride + e];
+  }
+  red[y][x] = s;
+  __syncthreads();
+  if (y != 0 || e >= elems) return;
+  s = 0.f;
+#pragma unroll
+  for (int j = 0; j < kSumSlices; ++j) s += red[j][x];
+  if (e >= split) {
+    out2[e - split] = s;
+  } else {
+    const int64_t k = e / F;
+    out[k * out_ld + (e - k * F)] = s;
+  }
 }
 
 // ---- feature gradient of a GAT layer -------------------------------------------------------------------
@@ -339,12 +449,24 @@ __global__ __launch_bounds__(kBlock) void gat_feature_grad_kernel(FeatGradArgs a
   }
 }
 
-static int linear_chunk(int K, int NT) {
-  // largest multiple of 16 with 32*NT * (KC + 8) halves inside the LDS budget, at most K rounded up to 16
-  int kc = kLinearLdsHalves / (32 * NT) - 8;
-  kc = kc / 16 * 16;
-  const int k16 = (K + 15) / 16 * 16;
-  return kc < k16 ? kc : k16;
+constexpr int kLinearLds = 152 * 1024;  // most bytes of W a workgroup keeps (of the 160 KB of a compute unit)
+
+template <int NT, int RT, bool CHUNKED>
+static hgnn_status launch_linear(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  // beyond 64 KB of dynamic LDS the runtime wants to be told, once per kernel and device
+  static bool told[64] = {};
+  if (lds > 65536) {
+    int dev = 0;
+    HGNN_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64 || !told[dev]) {
+      HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_kernel<NT, RT, CHUNKED>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kLinearLds));
+      if (dev >= 0 && dev < 64) told[dev] = true;
+    }
+  }
+  linear_kernel<NT, RT, CHUNKED><<<grid, threads, lds, s>>>(a);
+  HGNN_LAUNCH_CHECK("linear_kernel");
+  return HGNN_OK;
 }
 
 static int wgrad_parts(int K, int F) {
@@ -356,7 +478,8 @@ static int wgrad_parts(int K, int F) {
   return q;
 }
 
-constexpr int kSumGroup = 32;
+constexpr int kSumGroup = 32;  // the workspace bounds hold parts + parts / kSumGroup results
+constexpr int kCus = 256;       // compute units of an MI355X
 constexpr int kFeatGradBlocks = 1024;
 
 }  // namespace hgnn
@@ -377,25 +500,57 @@ hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int
   HGNN_REQUIRE(K % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y), HGNN_EUNSUPPORTED,
                "%s: needs K %% 8 == 0, ldx %% 8 == 0, ldy %% 8 == 0 and 16-byte aligned X, Y (pad with zeros)", who);
   LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw, trans_w ? 1 : 0,
-               reinterpret_cast<half_t*>(Y), ldy, 0};
-  const int tiles = int(ceil_div(F, 32));
-  const int NT = tiles >= 4 ? 4 : (tiles >= 2 ? 2 : 1);
-  a.KC = linear_chunk(K, NT);
-  const size_t lds = size_t(32 * NT) * size_t(a.KC + 8) * sizeof(half_t);
-  const int64_t nrb = ceil_div(n, kRowsPerBlock);
-  const int fy = int(ceil_div(tiles, NT));
-  // when the whole weight fits in LDS a workgroup keeps it and takes several row blocks
-  const int64_t want = a.KC >= K ? std::min<int64_t>(nrb, 2048) : nrb;
+               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0};
+  a.wvec = ldw % 8 == 0 && aligned16(W) ? 1 : 0;
+  const int k32 = (K + 31) / 32 * 32, f32 = (F + 31) / 32 * 32;
+  // short rows: several row tiles per wave, where that still leaves four waves for every compute unit
+  const int RT = n < int64_t(32) * 4 * kCus || K > 64 ? 1 : (K > 32 || n < int64_t(64) * 4 * kCus ? 2 : 4);
+  // 16-feature tiles per pass: 2, 4 or 8, the fewest passes (a pass reads the row tile of X again, or keeps it where RT > 1,
+  // whose registers hold NT * RT <= 8 tiles)
+  const int most = 8 / RT;
+  const int NT = std::min(most, f32 <= 32 ? 2 : (f32 <= 64 ? 4 : 8));
+  // the whole weight in LDS where it fits, else the most features whose weights do, else 128 features in
+  // chunks of columns
+  int nt = NT;
+  a.KC = k32;
+  a.FC = int(ceil_div(F, 16 * nt)) * 16 * nt;
+  if (int64_t(k32) * a.FC * 2 > kLinearLds) {
+    const int fit = kLinearLds / (k32 * 2) / (16 * nt) * (16 * nt);
+    a.FC = std::min(fit, int(ceil_div(F, 16 * nt)) * 16 * nt);
+    if (fit == 0) {
+      a.FC = 16 * nt;
+      a.KC = kLinearLds / (a.FC * 2) / 128 * 128;
+    }
+  }
+  const size_t lds = size_t(a.KC) * size_t(a.FC) * sizeof(half_t);
+  // waves per workgroup: the more LDS a workgroup holds, the more waves share it (16 waves per compute unit in all);
+  // fewer, so that every compute unit has work, while bringing the weight in stays short
+  int wpw = lds <= 40 * 1024 ? 4 : (lds <= 80 * 1024 ? 8 : 16);
+  const int least = lds <= 16 * 1024 ? 1 : (lds <= 32 * 1024 ? 2 : 4);
+  const int64_t tiles = ceil_div(n, int64_t(16) * RT);
+  while (wpw > least && ceil_div(tiles, wpw) < kCus) wpw /= 2;
+  const int fy = int(ceil_div(F, a.FC));
+  const int64_t nrb = ceil_div(tiles, wpw);
+  // persistent workgroups, as many as fit the chip at once, each with the same number of row blocks (to one)
+  const int64_t resident = int64_t(kCus) * std::max<int64_t>(1, std::min<int64_t>(16 / wpw, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
+  const int64_t per = ceil_div(nrb, std::max<int64_t>(1, resident / fy));
+  const int64_t want = ceil_div(nrb, per);
   HGNN_REQUIRE(want <= 0x7fffffff && fy <= 65535, HGNN_EUNSUPPORTED, "%s: grid too large", who);
   const dim3 grid{unsigned(want), unsigned(fy), 1u};
   hipStream_t s = static_cast<hipStream_t>(stream);
-  switch (NT) {
-    case 1: linear_kernel<1><<<grid, kBlock, lds, s>>>(a); break;
-    case 2: linear_kernel<2><<<grid, kBlock, lds, s>>>(a); break;
-    default: linear_kernel<4><<<grid, kBlock, lds, s>>>(a); break;
+  const int threads = wpw * kWave;
+  if (a.KC < K) {
+    if (nt == 2) return launch_linear<2, 1, true>(a, grid, threads, lds, s);
+    if (nt == 4) return launch_linear<4, 1, true>(a, grid, threads, lds, s);
+    return launch_linear<8, 1, true>(a, grid, threads, lds, s);
   }
-  HGNN_LAUNCH_CHECK("linear_kernel");
-  return HGNN_OK;
+  if (nt == 2) {
+    if (RT == 4) return launch_linear<2, 4, false>(a, grid, threads, lds, s);
+    return RT == 2 ? launch_linear<2, 2, false>(a, grid, threads, lds, s) : launch_linear<2, 1, false>(a, grid, threads, lds, s);
+  }
+  if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, grid, threads, lds, s);
+  if (nt == 4) return launch_linear<4, 1, false>(a, grid, threads, lds, s);
+  return launch_linear<8, 1, false>(a, grid, threads, lds, s);
 }
 
 size_t hgnn_linear_wgrad_workspace(int32_t K, int32_t F) {
@@ -420,19 +575,25 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
                    (reinterpret_cast<uintptr_t>(workspace) & 3u) == 0,
                HGNN_EUNSUPPORTED, "%s: needs K, F, ldx, ldy %% 8 == 0 and 16-byte aligned X, dY (pad with zeros)", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int parts = wgrad_parts(K, F);
   float* part = static_cast<float*>(workspace);
-  float* part2 = part + size_t(parts) * size_t(K) * size_t(F);
-  WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part, parts};
-  const dim3 grid{unsigned(parts / kWavesPerBlock), unsigned(ceil_div(K, kWgradTile)), unsigned(ceil_div(F, kWgradTile))};
-  wgrad_kernel<<<grid, kBlock, 0, s>>>(a);
+  // up to 64 columns on a side: one wave wide; else two, so that up to 128 columns are read once
+  const int WA = K <= 64 ? 1 : 2, WB = F <= 64 ? 1 : 2;
+  const int kb = int(ceil_div(K, 64 * WA)), fb = int(ceil_div(F, 64 * WB)), WR = 4 / (WA * WB);
+  // three workgroups per compute unit over all blocks of dW, but no more than there are steps of rows and no more
+  // partial results than the workspace holds
+  int64_t parts = std::max<int64_t>(1, int64_t(3) * kCus / (int64_t(kb) * fb));
+  parts = std::min<int64_t>(parts, wgrad_parts(K, F));
+  parts = std::max<int64_t>(1, std::min<int64_t>(parts, ceil_div(n, int64_t(kWgradRows) * WR)));
+  WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
+  const dim3 grid{unsigned(parts), unsigned(kb), unsigned(fb)};
+  if (WA == 1 && WB == 1) wgrad_kernel<1, 1><<<grid, kBlock, 0, s>>>(a);
+  else if (WA == 2 && WB == 1) wgrad_kernel<2, 1><<<grid, kBlock, 0, s>>>(a);
+  else if (WA == 1) wgrad_kernel<1, 2><<<grid, kBlock, 0, s>>>(a);
+  else wgrad_kernel<2, 2><<<grid, kBlock, 0, s>>>(a);
   HGNN_LAUNCH_CHECK("wgrad_kernel");
   const int64_t elems = int64_t(K) * F;
-  const int mid = parts / kSumGroup;
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(elems, kBlock)), unsigned(mid)), kBlock, 0, s>>>(part, elems, parts, kSumGroup, elems,
-                                                                                            F, part2, elems, F);
-  HGNN_LAUNCH_CHECK("partial_sum_kernel");
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(elems, kBlock)), 1), kBlock, 0, s>>>(part2, elems, mid, mid, elems, F, dW, 0, lddw);
+  partial_sum_kernel<<<dim3(unsigned(ceil_div(elems, kWave))), kWave * kSumSlices, 0, s>>>(part, elems, int(parts), elems, F, dW, lddw,
+                                                                                         elems, nullptr);
   HGNN_LAUNCH_CHECK("partial_sum_kernel");
   return HGNN_OK;
 }
@@ -462,12 +623,13 @@ hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_ha
                HGNN_EUNSUPPORTED, "%s: needs D %% 8 == 0, ld %% 8 == 0 and 16-byte aligned dV, hfeat, dh", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* part = static_cast<float*>(workspace);
-  float* part2 = part + size_t(kFeatGradBlocks) * 2 * size_t(F);
   FeatGradArgs a{n, H, D, F, reinterpret_cast<const half_t*>(dV), lddv, reinterpret_cast<const half_t*>(d_el),
                  reinterpret_cast<const half_t*>(d_er), reinterpret_cast<const half_t*>(a_l), reinterpret_cast<const half_t*>(a_r),
                  reinterpret_cast<const half_t*>(hfeat), ldh, reinterpret_cast<half_t*>(dh), lddh, part};
   const int LP = pow2_at_least(F / 8);
-  dim3 grid(kFeatGradBlocks);
+  // enough workgroups for the chip, no more than a pass of rows each: every one leaves a partial result
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kFeatGradBlocks / 2, ceil_div(n, kBlock / LP)));
+  dim3 grid{unsigned(blocks)};
   switch (LP) {
     case 1: gat_feature_grad_kernel<1><<<grid, kBlock, 0, s>>>(a); break;
     case 2: gat_feature_grad_kernel<2><<<grid, kBlock, 0, s>>>(a); break;
@@ -478,17 +640,9 @@ hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_ha
     default: gat_feature_grad_kernel<64><<<grid, kBlock, 0, s>>>(a); break;
   }
   HGNN_LAUNCH_CHECK("gat_feature_grad_kernel");
-  // the partial of workgroup b is [2][F]: treat it as one row of 2F elements
-  const int64_t elems = 2 * int64_t(F);
-  const int mid = kFeatGradBlocks / kSumGroup;
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(elems, kBlock)), unsigned(mid)), kBlock, 0, s>>>(part, elems, kFeatGradBlocks,
-                                                                                            kSumGroup, elems, int(elems), part2, elems,
-                                                                                            elems);
-  HGNN_LAUNCH_CHECK("partial_sum_kernel");
-  // second round: the two sides go to two output arrays
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(F, kBlock)), 1), kBlock, 0, s>>>(part2, elems, mid, mid, F, F, da_l, 0, F);
-  HGNN_LAUNCH_CHECK("partial_sum_kernel");
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(F, kBlock)), 1), kBlock, 0, s>>>(part2 + F, elems, mid, mid, F, F, da_r, 0, F);
+  // the partial of workgroup b is [2][F]: one row of 2F elements, whose second half is da_r
+  partial_sum_kernel<<<dim3(unsigned(ceil_div(2 * F, kWave))), kWave * kSumSlices, 0, s>>>(part, 2 * int64_t(F), int(blocks),
+                                                                                         2 * int64_t(F), F, da_l, F, F, da_r);
   HGNN_LAUNCH_CHECK("partial_sum_kernel");
   return HGNN_OK;
 }

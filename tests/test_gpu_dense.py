@@ -54,6 +54,14 @@ def test_linear_shapes(hgnn, dev, n, K, F, trans, px, py):
     assert np.array_equal(down(Y2).view(np.uint16), got.view(np.uint16))
 
 
+# rows per wave (from 32768 / 65536 rows on with K <= 64 / 32), features split over workgroups, columns in chunks
+@pytest.mark.parametrize("n,K,F,trans", [(65537, 32, 40, False), (65551, 24, 8, True), (32769, 64, 72, True), (40001, 40, 42, False),
+                                         (333, 608, 300, False), (97, 608, 300, True), (65, 1304, 200, False), (130, 2504, 40, True),
+                                         (31, 5000, 8, False), (16385, 128, 128, False)])
+def test_linear_dispatch_edges(hgnn, dev, n, K, F, trans):
+    test_linear_shapes(hgnn, dev, n, K, F, trans, 0, 0)
+
+
 def test_linear_identity_and_zero_rows(hgnn, dev):
     n, K = 777, 96
     r = np.random.default_rng(5)
@@ -94,6 +102,12 @@ def test_linear_wgrad_shapes(hgnn, dev, n, K, F):
     dW2 = torch.empty((K, F), dtype=torch.float32, device=dev)
     hgnn.hgnn_linear_wgrad(Xd, dYd, dW2, ws)
     assert np.array_equal(down(dW2).view(np.uint32), got[:, :F].view(np.uint32))
+
+
+# one or two waves across either side of dW, partial last blocks, fewer rows than a step
+@pytest.mark.parametrize("n,K,F", [(31, 72, 64), (33, 64, 72), (4097, 128, 128), (129, 136, 8), (65, 608, 64), (20000, 104, 256)])
+def test_linear_wgrad_dispatch_edges(hgnn, dev, n, K, F):
+    test_linear_wgrad_shapes(hgnn, dev, n, K, F)
 
 
 def test_linear_wgrad_errors(hgnn, dev):
