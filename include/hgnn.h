@@ -182,7 +182,11 @@ hgnn_status hgnn_plan_block_export(const hgnn_plan* p, int32_t b, int64_t* nnz_b
  * split_seg_hi [num_split_rows].  Synchronizes. */
 hgnn_status hgnn_plan_export(const hgnn_plan* p, int32_t* seg_row_lo, int32_t* seg_row_hi, int32_t* split_row,
                              int32_t* split_seg_lo, int32_t* split_seg_hi);
+/* Waits for the device: calls that use the plan may still be in flight. */
 void hgnn_plan_destroy(hgnn_plan* p);
+/* The set-up calls keep the device memory that they and destroyed plans free for the next set-up call, at most 512 MiB per
+ * device; this gives it back to the runtime at once.  May be called at any time. */
+void hgnn_release_cached_memory(void);
 
 /* SpMM, vertex-parallel (sections 2.1.2, 4.1): for every row i
  *   Y[i,f] = s_i * sum_{k in row i} w[slot(k), f/D] * X[col[k], f],   slot(k) = eid ? eid[k] : k,

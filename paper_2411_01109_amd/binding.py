@@ -23,7 +23,7 @@ EXPORTS = (
     "hgnn_plan_num_segments", "hgnn_plan_num_split_rows", "hgnn_plan_seg_edges", "hgnn_plan_col_blocks", "hgnn_plan_col_blocks_fine",
     "hgnn_plan_cache_bytes",
     "hgnn_plan_block_export", "hgnn_plan_export",
-    "hgnn_plan_destroy", "hgnn_spmm", "hgnn_spmm_discretized", "hgnn_spmm_discretized_fused", "hgnn_sddmm", "hgnn_edge_softmax",
+    "hgnn_plan_destroy", "hgnn_release_cached_memory", "hgnn_spmm", "hgnn_spmm_discretized", "hgnn_spmm_discretized_fused", "hgnn_sddmm", "hgnn_edge_softmax",
     "hgnn_edge_softmax_bwd", "hgnn_edge_rowsum", "hgnn_spmm_discretized_variant", "hgnn_plan_add_groups",
     "hgnn_plan_num_groups", "hgnn_plan_group_edges", "hgnn_plan_groups_export", "hgnn_plan_set_vector_halves",
     "hgnn_plan_vector_halves", "hgnn_spmm_workspace", "hgnn_plan_add_slices", "hgnn_plan_num_slices", "hgnn_edge_colsum", "hgnn_spmm_static", "hgnn_spmm_static_limit", "hgnn_gat_forward_fused", "hgnn_gat_alpha", "hgnn_gat_backward_fused",
@@ -91,6 +91,8 @@ def load() -> ctypes.CDLL:
     lib.hgnn_plan_block_export.argtypes = [vp, i32, ctypes.POINTER(i64), vp, vp, vp, vp, vp]
     lib.hgnn_plan_destroy.restype = None
     lib.hgnn_plan_destroy.argtypes = [vp]
+    lib.hgnn_release_cached_memory.restype = None
+    lib.hgnn_release_cached_memory.argtypes = []
     lib.hgnn_spmm_workspace.restype = ctypes.c_size_t
     lib.hgnn_spmm_workspace.argtypes = [i32, i32, i64, i32]
     lib.hgnn_spmm.argtypes = [csr, vp, i32, vp, i64, vp, i64, i32, ctypes.c_int, vp, vp, ctypes.c_size_t, vp]
@@ -296,6 +298,11 @@ def hgnn_plan_destroy(p: Plan) -> None:
     h, p.handle = p.handle, None
     if h:
         load().hgnn_plan_destroy(h)
+
+
+def hgnn_release_cached_memory() -> None:
+    """Gives the device memory that set-up calls keep for one another (at most 512 MiB per device) back to the runtime."""
+    load().hgnn_release_cached_memory()
 
 
 def hgnn_spmm_workspace(nrows: int, ncols: int, nnz: int, F: int) -> int:

@@ -86,28 +86,28 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_
   p->block_width = width;
   p->block_eid = g->eid != nullptr;
   int *cut = nullptr, *cnt = nullptr, *goff = nullptr;
-  void* tmp = nullptr;
+  char* tmp = nullptr;
   size_t tmp_bytes = 0;
   const size_t n_flat = size_t(nb) * size_t(V);
   hgnn_status rc = HGNN_OK;
-  hipError_t e = hipMalloc(&cut, sizeof(int) * size_t(V) * size_t(nb + 1));
-  if (e == hipSuccess) e = hipMalloc(&cnt, sizeof(int) * n_flat);
-  if (e == hipSuccess) e = hipMalloc(&goff, sizeof(int) * n_flat);
-  if (e == hipSuccess) e = hipMalloc(&p->brp, sizeof(int) * size_t(nb) * (size_t(V) + 1));
-  if (e == hipSuccess) e = hipMalloc(&p->bcol, sizeof(int) * size_t(E));
-  if (e == hipSuccess) e = hipMalloc(&p->beid, sizeof(int) * size_t(E));
+  hipError_t e = dev_malloc(&cut, sizeof(int) * size_t(V) * size_t(nb + 1));
+  if (e == hipSuccess) e = dev_malloc(&cnt, sizeof(int) * n_flat);
+  if (e == hipSuccess) e = dev_malloc(&goff, sizeof(int) * n_flat);
+  if (e == hipSuccess) e = dev_malloc(&p->brp, sizeof(int) * size_t(nb) * (size_t(V) + 1));
+  if (e == hipSuccess) e = dev_malloc(&p->bcol, sizeof(int) * size_t(E));
+  if (e == hipSuccess) e = dev_malloc(&p->beid, sizeof(int) * size_t(E));
   // partial rows twice over and three scalars per row and head: the fused GAT pass that saves for its backward
   // leaves two vectors and (max, sum, masked sum) per block; row sums of edge tensors use one scalar
-  if (e == hipSuccess) e = hipMalloc(&p->bstage, sizeof(hgnn_half) * 2 * n_flat * size_t(p->max_F));
-  if (e == hipSuccess) e = hipMalloc(&p->bsum, sizeof(float) * 3 * n_flat * size_t(p->max_H));
-  if (e == hipSuccess) e = hipMalloc(&p->bdelta, sizeof(int) * n_flat);
+  if (e == hipSuccess) e = dev_malloc(&p->bstage, sizeof(hgnn_half) * 2 * n_flat * size_t(p->max_F));
+  if (e == hipSuccess) e = dev_malloc(&p->bsum, sizeof(float) * 3 * n_flat * size_t(p->max_H));
+  if (e == hipSuccess) e = dev_malloc(&p->bdelta, sizeof(int) * n_flat);
   if (e == hipSuccess) {
     block_cuts_kernel<<<dim3(unsigned(ceil_div(int64_t(V) * (nb + 1), kBlock))), kBlock, 0, s>>>(g->rowptr, g->col, V, nb,
                                                                                                  width, cut);
     block_counts_kernel<<<dim3(unsigned(ceil_div(int64_t(n_flat), kBlock))), kBlock, 0, s>>>(cut, V, nb, cnt);
     e = rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
   }
-  if (e == hipSuccess) e = hipMalloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
+  if (e == hipSuccess) e = dev_malloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
   if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
   if (e == hipSuccess) {
     block_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(nb) * (V + 1), kBlock))), kBlock, 0, s>>>(goff, V, nb, E, p->brp);
@@ -126,10 +126,10 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess)
     rc = fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "build_col_blocks: %s", hipGetErrorString(e));
-  (void)hipFree(cut);
-  (void)hipFree(cnt);
-  (void)hipFree(goff);
-  (void)hipFree(tmp);
+  dev_free(cut);
+  dev_free(cnt);
+  dev_free(goff);
+  dev_free(tmp);
   if (rc != HGNN_OK) return rc;
   // a segment plan per block, over the block's own CSR
   for (int b = 0; b < nb; ++b) {
@@ -170,7 +170,7 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_
     d.pad = 0;
     d.stage_mz = q->stage_mz;
   }
-  HGNN_HIP(hipMalloc(&p->bdesc, sizeof(hgnn_seg_block) * size_t(nb)));
+  HGNN_HIP(dev_malloc(&p->bdesc, sizeof(hgnn_seg_block) * size_t(nb)));
   HGNN_HIP(hipMemcpyAsync(p->bdesc, desc.data(), sizeof(hgnn_seg_block) * size_t(nb), hipMemcpyHostToDevice, s));
   HGNN_HIP(hipStreamSynchronize(s));
   return HGNN_OK;

@@ -67,6 +67,42 @@ inline int pow2_at_least(int v) {
 
 hgnn_status check_csr_args(const hgnn_csr* g, const char* who);
 
+// ---- memory of the set-up calls (memory.hip): device blocks that are kept for the next call when freed ----------
+// A block may be freed only when no work that uses it is in flight.
+hipError_t dev_malloc_bytes(void** out, size_t bytes);
+void dev_free(const void* p);
+template <class T>
+inline hipError_t dev_malloc(T** out, size_t bytes) {
+  void* p = nullptr;
+  const hipError_t e = dev_malloc_bytes(&p, bytes);
+  *out = static_cast<T*>(p);
+  return e;
+}
+
+// a device block that is freed when it goes out of scope
+struct DevTemp {
+  void* p = nullptr;
+  DevTemp() = default;
+  DevTemp(const DevTemp&) = delete;
+  DevTemp& operator=(const DevTemp&) = delete;
+  ~DevTemp() { dev_free(p); }
+  hipError_t alloc(size_t bytes) { return dev_malloc_bytes(&p, bytes); }
+  template <class T>
+  T* as() const { return static_cast<T*>(p); }
+};
+
+// a small piece of pinned host memory that kernels can write and the host reads after a synchronization (a copy out of
+// pageable memory costs a staging round of its own); data == nullptr when there is none left
+constexpr size_t kMailBytes = 256;
+struct HostMail {
+  char* data = nullptr;
+  int slot = -1;
+  HostMail();
+  ~HostMail();
+  HostMail(const HostMail&) = delete;
+  HostMail& operator=(const HostMail&) = delete;
+};
+
 // row that holds CSR position k: the last r with rowptr[r] <= k (an upper bound minus one, so
 // empty rows are skipped)
 __host__ __device__ inline int row_of_edge(const int* rowptr, int nrows, int64_t k) {

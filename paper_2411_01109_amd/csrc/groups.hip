@@ -47,10 +47,10 @@ __global__ void group_first_kernel(const int* __restrict__ rowptr, const int* __
 }
 
 static void free_groups(hgnn_plan* p) {
-  (void)hipFree(p->goff);
-  (void)hipFree(p->moff);
-  (void)hipFree(p->grp_row);
-  (void)hipFree(p->gstage);
+  dev_free(p->goff);
+  dev_free(p->moff);
+  dev_free(p->grp_row);
+  dev_free(p->gstage);
   p->goff = p->moff = p->grp_row = nullptr;
   p->gstage = nullptr;
   p->ng = 0;
@@ -77,36 +77,36 @@ hgnn_status hgnn_plan_add_groups(hgnn_plan* p, const hgnn_csr* g, int32_t group_
   free_groups(p);
   const int V = g->nrows;
   int *cnt = nullptr, *mcnt = nullptr;
-  void* tmp = nullptr;
+  char* tmp = nullptr;
   size_t tmp_bytes = 0;
   const size_t n1 = size_t(V) + 1;
-  hipError_t e = hipMalloc(&cnt, sizeof(int) * n1);
-  if (e == hipSuccess) e = hipMalloc(&mcnt, sizeof(int) * n1);
-  if (e == hipSuccess) e = hipMalloc(&p->goff, sizeof(int) * n1);
-  if (e == hipSuccess) e = hipMalloc(&p->moff, sizeof(int) * n1);
+  hipError_t e = dev_malloc(&cnt, sizeof(int) * n1);
+  if (e == hipSuccess) e = dev_malloc(&mcnt, sizeof(int) * n1);
+  if (e == hipSuccess) e = dev_malloc(&p->goff, sizeof(int) * n1);
+  if (e == hipSuccess) e = dev_malloc(&p->moff, sizeof(int) * n1);
   if (e == hipSuccess) {
     group_counts_kernel<<<dim3(unsigned(ceil_div(int64_t(n1), kBlock))), kBlock, 0, s>>>(g->rowptr, V, group_edges, cnt, mcnt);
     e = rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, p->goff, 0, n1, rocprim::plus<int>(), s);
   }
-  if (e == hipSuccess) e = hipMalloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
+  if (e == hipSuccess) e = dev_malloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
   if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, cnt, p->goff, 0, n1, rocprim::plus<int>(), s);
   if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, mcnt, p->moff, 0, n1, rocprim::plus<int>(), s);
   int totals[2] = {0, 0};
   if (e == hipSuccess) e = hipMemcpyAsync(&totals[0], p->goff + V, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&totals[1], p->moff + V, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess && totals[0] > 0) e = hipMalloc(&p->grp_row, sizeof(int) * size_t(totals[0]));
+  if (e == hipSuccess && totals[0] > 0) e = dev_malloc(&p->grp_row, sizeof(int) * size_t(totals[0]));
   if (e == hipSuccess && totals[1] > 0)
-    e = hipMalloc(&p->gstage, sizeof(hgnn_half) * size_t(totals[1]) * size_t(p->max_F));
+    e = dev_malloc(&p->gstage, sizeof(hgnn_half) * size_t(totals[1]) * size_t(p->max_F));
   if (e == hipSuccess && totals[0] > 0) {
     group_rows_kernel<<<dim3(unsigned(ceil_div(int64_t(totals[0]), kBlock))), kBlock, 0, s>>>(p->goff, V, totals[0],
                                                                                               p->grp_row);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
-  (void)hipFree(cnt);
-  (void)hipFree(mcnt);
-  (void)hipFree(tmp);
+  dev_free(cnt);
+  dev_free(mcnt);
+  dev_free(tmp);
   if (e != hipSuccess) {
     free_groups(p);
     return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
@@ -130,13 +130,13 @@ hgnn_status hgnn_plan_groups_export(const hgnn_plan* p, const hgnn_csr* g, int32
   if (p->n_groups == 0) return HGNN_OK;
   HGNN_REQUIRE(group_row && group_first, HGNN_EINVAL, "%s: output array is NULL", who);
   int* first = nullptr;
-  HGNN_HIP(hipMalloc(&first, sizeof(int) * size_t(p->n_groups)));
+  HGNN_HIP(dev_malloc(&first, sizeof(int) * size_t(p->n_groups)));
   group_first_kernel<<<dim3(unsigned(ceil_div(p->n_groups, kBlock))), kBlock, 0, nullptr>>>(g->rowptr, p->goff, p->grp_row,
                                                                                             p->n_groups, p->ng, first);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpy(group_first, first, sizeof(int) * size_t(p->n_groups), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemcpy(group_row, p->grp_row, sizeof(int) * size_t(p->n_groups), hipMemcpyDeviceToHost);
-  (void)hipFree(first);
+  dev_free(first);
   if (e != hipSuccess) return fail(HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
   return HGNN_OK;
 }

@@ -6,6 +6,7 @@
 
 #include <hsa/hsa.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -97,11 +98,21 @@ hgnn_status check_csr_args(const hgnn_csr* g, const char* who) {
 }
 
 // ---- validation ---------------------------------------------------------------------------------
-// err starts at kNoError and receives the smallest rule number broken.  Two passes: the offset array first
-// (rules 1-3); the per-edge rules only run on a graph that passed them, because they index the offset array
-// with values that are in range only when it is monotone and has the right end points.
-constexpr int kNoError = 0x7f7f7f7f;
-__global__ void validate_rowptr_kernel(hgnn_csr g, int* err) {
+// Results of the passes over a graph that the host waits for, zeroed before the first one.
+struct GraphFacts {
+  int bad;                        // 8 - the smallest number of the offset array's rules (1-3) that is broken, 0 = none
+  int bad_edge;                   // the same for rules 4-6
+  int n_split, n_big, n_mid;      // rows in the three lists of a plan
+  int n_chunks;                   // chunks of kHubEdges of the long rows
+  unsigned long long listed;      // non-zeros of the long and middle rows
+  unsigned long long drops;       // positions whose column is below their predecessor's
+  unsigned long long drops_ok;    // rows whose first column is below the column before it
+};
+static_assert(sizeof(GraphFacts) <= kMailBytes, "GraphFacts goes through a mail slot");
+
+// The offset array first (rules 1-3); the per-edge rules only count on a graph that passed them, because they index with
+// values that are in range only when it is monotone and has the right end points.
+__global__ void validate_rowptr_kernel(hgnn_csr g, GraphFacts* f) {
   const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   int bad = 0;
   if (i == 0) {
@@ -109,28 +120,70 @@ __global__ void validate_rowptr_kernel(hgnn_csr g, int* err) {
     else if (int64_t(g.rowptr[g.nrows]) != g.nnz) bad = 2;
   }
   if (!bad && i < g.nrows && g.rowptr[i] > g.rowptr[i + 1]) bad = 3;
-  if (bad) atomicMin(err, bad);
+  if (bad) atomicMax(&f->bad, 8 - bad);
 }
 
-__global__ void validate_edges_kernel(hgnn_csr g, int* err) {
-  const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (i >= g.nnz) return;
-  int bad = 0;
-  const int c = g.col[i];
-  if (c < 0 || c >= g.ncols) bad = 4;
-  if (!bad && g.eid) {
-    const int e = g.eid[i];
-    if (e < 0 || int64_t(e) >= g.nnz) bad = 5;
+__device__ __forceinline__ void add_block_total(int v, unsigned long long* total) {  // blockDim.x == kBlock
+  __shared__ int part[kBlock / kWave];
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int t = 0;
+    for (int w = 0; w < kBlock / kWave; ++w) t += part[w];
+    if (t) atomicAdd(total, (unsigned long long)t);
   }
-  if (!bad && g.row) {
-    const int r = g.row[i];
-    if (r < 0 || r >= g.nrows) bad = 6;
-    else if (!(int64_t(g.rowptr[r]) <= i && i < int64_t(g.rowptr[r + 1]))) bad = 6;
+}
+
+// Rules 4-7.  A column id may only drop where a new row starts (rule 7): the positions where it drops are counted over the
+// stream of column ids, the row starts among them over the rows, and the two numbers are equal exactly when no drop lies
+// inside a row (43 us with a search of the row of every drop at 5.5 M non-zeros).  Few workgroups, each adding its total
+// once: thousands of additions to one address took longer than the pass (51 us).
+constexpr int kEdgesPerThread = 8;
+constexpr int kFactBlocks = 512;  // most workgroups that add to a fact
+__global__ __launch_bounds__(kBlock) void validate_edges_kernel(hgnn_csr g, GraphFacts* f, int64_t edge_blocks) {
+  if (f->bad) return;  // written by the launch before
+  if (int64_t(blockIdx.x) >= edge_blocks) {
+    int ok = 0;
+    for (int64_t r = (int64_t(blockIdx.x) - edge_blocks) * kBlock + threadIdx.x; r < g.nrows;
+         r += (int64_t(gridDim.x) - edge_blocks) * kBlock) {
+      const int b = g.rowptr[r], e = g.rowptr[r + 1];
+      if (b < e && b > 0) ok += g.col[b - 1] > g.col[b];
+    }
+    add_block_total(ok, &f->drops_ok);
+    return;
   }
-  // a column id may only drop where a new row starts (rowptr is monotone from 0 to nnz here, so the row found is
-  // in [0, nrows))
-  if (!bad && i > 0 && g.col[i - 1] > c && int64_t(g.rowptr[row_of_edge(g.rowptr, g.nrows, i)]) != i) bad = 7;
-  if (bad) atomicMin(err, bad);
+  int bad = 0, drops = 0;
+  for (int64_t i0 = int64_t(blockIdx.x) * (kBlock * kEdgesPerThread) + threadIdx.x; i0 < g.nnz;
+       i0 += edge_blocks * (kBlock * kEdgesPerThread)) {
+    int c[kEdgesPerThread], before[kEdgesPerThread];
+#pragma unroll
+    for (int u = 0; u < kEdgesPerThread; ++u) {
+      const int64_t i = i0 + u * kBlock;
+      c[u] = i < g.nnz ? g.col[i] : 0;
+      before[u] = i < g.nnz && i > 0 ? g.col[i - 1] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kEdgesPerThread; ++u) {
+      const int64_t i = i0 + u * kBlock;
+      if (i >= g.nnz) break;
+      int b = 0;
+      if (c[u] < 0 || c[u] >= g.ncols) b = 4;
+      if (!b && g.eid) {
+        const int e = g.eid[i];
+        if (e < 0 || int64_t(e) >= g.nnz) b = 5;
+      }
+      if (!b && g.row) {
+        const int r = g.row[i];
+        if (r < 0 || r >= g.nrows) b = 6;
+        else if (!(int64_t(g.rowptr[r]) <= i && i < int64_t(g.rowptr[r + 1]))) b = 6;
+      }
+      if (i > 0) drops += before[u] > c[u];
+      if (b && (bad == 0 || b < bad)) bad = b;
+    }
+  }
+  if (bad) atomicMax(&f->bad_edge, 8 - bad);
+  add_block_total(drops, &f->drops);
 }
 
 static const char* const kRule[] = {"ok",
@@ -142,6 +195,24 @@ static const char* const kRule[] = {"ok",
                                     "a COO row id disagrees with rowptr",
                                     "column ids are not ascending inside a row"};
 
+static hipError_t launch_validate(const hgnn_csr* g, GraphFacts* facts, hipStream_t s) {
+  hipError_t e = hipMemsetAsync(facts, 0, sizeof(GraphFacts), s);
+  if (e != hipSuccess) return e;
+  validate_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) + 1, kBlock))), kBlock, 0, s>>>(*g, facts);
+  if (g->nnz > 0) {
+    const int64_t eb = std::min<int64_t>(kFactBlocks, ceil_div(g->nnz, int64_t(kBlock) * kEdgesPerThread));
+    const int64_t rb = std::min<int64_t>(kFactBlocks / 2, ceil_div(g->nrows, kBlock));
+    validate_edges_kernel<<<dim3(unsigned(eb + rb)), kBlock, 0, s>>>(*g, facts, eb);
+  }
+  return hipGetLastError();
+}
+
+static hgnn_status check_facts(const GraphFacts& f) {
+  const int rule = f.bad ? 8 - f.bad : (f.bad_edge ? 8 - f.bad_edge : (f.drops != f.drops_ok ? 7 : 0));
+  if (rule) return fail(HGNN_EINVAL, "hgnn_csr_validate: %s", kRule[rule > 0 && rule < 8 ? rule : 0]);
+  return HGNN_OK;
+}
+
 // ---- first and last row of every segment: binary searches in the offset array ------------------------
 __global__ void seg_rows_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int S, int64_t nseg,
                                 int* __restrict__ lo, int* __restrict__ hi) {
@@ -152,226 +223,207 @@ __global__ void seg_rows_kernel(const int* __restrict__ rowptr, int nrows, int64
   hi[k] = row_of_edge(rowptr, nrows, e1 - 1);
 }
 
-// ---- ordered compaction of the rows that satisfy a predicate -------------------------------------------
-struct SplitPred {  // first and last edge of the row fall in different segments
+// ---- the row lists of a plan ------------------------------------------------------------------------------
+// split: first and last edge of the row fall in different segments; big: longer than big_deg; mid: longer than mid_deg and
+// not big.  One pass counts the members of all three per workgroup (and the chunks of the long rows and the non-zeros of
+// the two length lists), one workgroup turns the counts into offsets and hands the totals to the host, one pass writes
+// the lists in row order.  A column block's sub-plan only needs the split rows (big_deg < 0).
+struct RowLists {
   const int* rowptr;
-  int S;
-  __device__ bool operator()(int r) const {
-    int b = rowptr[r], e = rowptr[r + 1];
-    return e > b && (b / S) != ((e - 1) / S);
-  }
+  int nrows, S, big_deg, mid_deg;
 };
-struct MidPred {  // row longer than lo and at most hi
-  const int* rowptr;
-  int lo, hi;
-  __device__ bool operator()(int r) const {
-    const int d = rowptr[r + 1] - rowptr[r];
-    return d > lo && d <= hi;
-  }
-};
-struct BigPred {  // row longer than a threshold
-  const int* rowptr;
-  int deg;
-  __device__ bool operator()(int r) const { return rowptr[r + 1] - rowptr[r] > deg; }
-};
-
-// total[0] += the lengths of the listed rows
-__global__ void list_length_sum_kernel(const int* __restrict__ rowptr, const int* __restrict__ list, int n,
-                                       unsigned long long* __restrict__ total) {
-  __shared__ unsigned long long part[kBlock / kWave];
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  unsigned long long v = 0;
-  if (i < n) v = (unsigned long long)(rowptr[list[i] + 1] - rowptr[list[i]]);
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
-  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    for (int w = 0; w < kBlock / kWave; ++w) t += part[w];
-    if (t) atomicAdd(total, t);
-  }
-}
 
 constexpr int kRowsPerThread = 4;
 constexpr int kRowsPerBlock = kBlock * kRowsPerThread;
+enum { kSplitList, kBigList, kMidList, kChunkList, kLists };
 
-__device__ inline int block_exclusive_scan(int v, int* total) {  // blockDim.x == kBlock
-  __shared__ int buf[2][kBlock];
-  int t = threadIdx.x, cur = 0;
-  buf[0][t] = v;
-  __syncthreads();
-  for (int d = 1; d < kBlock; d <<= 1) {
-    int x = buf[cur][t];
-    if (t >= d) x += buf[cur][t - d];
-    buf[cur ^ 1][t] = x;
-    cur ^= 1;
-    __syncthreads();
+__device__ __forceinline__ void row_memberships(const RowLists& q, int r, int (&m)[kLists], int& len) {
+  const int b = q.rowptr[r], e = q.rowptr[r + 1];
+  len = e - b;
+  m[kSplitList] = e > b && (b / q.S) != ((e - 1) / q.S);
+  m[kBigList] = q.big_deg >= 0 && len > q.big_deg;
+  m[kMidList] = q.big_deg >= 0 && len > q.mid_deg && len <= q.big_deg;
+  m[kChunkList] = m[kBigList] ? (len + kHubEdges - 1) / kHubEdges : 0;
+}
+
+// exclusive scan of one value per thread over the workgroup (blockDim.x == kBlock)
+__device__ inline int block_exclusive_scan(int v, int* total) {
+  __shared__ int wsum[kBlock / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int incl = v;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if (lane >= d) incl += t;
   }
-  int incl = buf[cur][t];
-  *total = buf[cur][kBlock - 1];
+  __syncthreads();  // a previous scan has been read
+  if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
-  return incl - v;
-}
-
-template <class Pred>
-__global__ void compact_count_kernel(Pred pred, int nrows, int* __restrict__ block_count) {
-  int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
-  int c = 0;
-  for (int u = 0; u < kRowsPerThread; ++u)
-    if (base + u < nrows && pred(base + u)) ++c;
-  int total;
-  (void)block_exclusive_scan(c, &total);
-  if (threadIdx.x == 0) block_count[blockIdx.x] = total;
-}
-
-// one workgroup: exclusive scan of n block counts in place; total[0] = sum
-__global__ void scan_counts_kernel(int* __restrict__ counts, int n, int* __restrict__ total) {
-  int carry = 0;
-  for (int base = 0; base < n; base += kBlock) {
-    int i = base + threadIdx.x;
-    int v = i < n ? counts[i] : 0;
-    int tot;
-    int ex = block_exclusive_scan(v, &tot);
-    if (i < n) counts[i] = carry + ex;
-    carry += tot;
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / kWave; ++w) {
+    if (w < wave) before += wsum[w];
+    all += wsum[w];
   }
-  if (threadIdx.x == 0) total[0] = carry;
+  *total = all;
+  return before + incl - v;
 }
 
-template <class Pred>
-__global__ void compact_write_kernel(Pred pred, int nrows, const int* __restrict__ block_offset, int* __restrict__ out) {
-  int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
-  bool f[kRowsPerThread];
-  int c = 0;
+__global__ __launch_bounds__(kBlock) void row_lists_count_kernel(RowLists q, int nblk, int* __restrict__ counts, GraphFacts* f) {
+  const int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
+  int c[kLists] = {0, 0, 0, 0}, listed = 0;
   for (int u = 0; u < kRowsPerThread; ++u) {
-    f[u] = base + u < nrows && pred(base + u);
-    c += f[u];
+    if (base + u >= q.nrows) break;
+    int m[kLists], len;
+    row_memberships(q, base + u, m, len);
+    for (int i = 0; i < kLists; ++i) c[i] += m[i];
+    if (m[kBigList] || m[kMidList]) listed += len;
   }
-  int total;
-  int pos = block_offset[blockIdx.x] + block_exclusive_scan(c, &total);
-  for (int u = 0; u < kRowsPerThread; ++u)
-    if (f[u]) out[pos++] = base + u;
+  for (int i = 0; i < kLists; ++i) {
+    int total;
+    (void)block_exclusive_scan(c[i], &total);
+    if (threadIdx.x == 0) counts[i * nblk + blockIdx.x] = total;
+  }
+  add_block_total(listed, &f->listed);
 }
 
-template <class Pred>
-static hgnn_status compact_rows(Pred pred, int nrows, int** out, int* n_out, hipStream_t s) {
-  *out = nullptr;
-  *n_out = 0;
-  if (nrows == 0) return HGNN_OK;
-  int nblk = int(ceil_div(nrows, kRowsPerBlock));
-  int* counts = nullptr;
-  HGNN_HIP(hipMalloc(&counts, sizeof(int) * (size_t(nblk) + 1)));
-  compact_count_kernel<Pred><<<nblk, kBlock, 0, s>>>(pred, nrows, counts);
-  scan_counts_kernel<<<1, kBlock, 0, s>>>(counts, nblk, counts + nblk);
-  int total = 0;
-  hipError_t e = hipMemcpyAsync(&total, counts + nblk, sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    (void)hipFree(counts);
-    return fail(HGNN_EHIP, "compact_rows: %s", hipGetErrorString(e));
-  }
-  if (total > 0) {
-    e = hipMalloc(out, sizeof(int) * size_t(total));
-    if (e != hipSuccess) {
-      (void)hipFree(counts);
-      return fail(HGNN_ENOMEM, "compact_rows: %s", hipGetErrorString(e));
+// one workgroup: exclusive scans of the n block counts of every list in place; the totals and what earlier passes left in
+// `facts` go to `out` (host memory)
+__global__ __launch_bounds__(kBlock) void row_lists_scan_kernel(int* __restrict__ counts, int n, const GraphFacts* __restrict__ facts,
+                                                                GraphFacts* out) {
+  int carry[kLists] = {0, 0, 0, 0};
+  for (int base = 0; base < n; base += kBlock) {
+    const int i = base + threadIdx.x;
+    for (int l = 0; l < kLists; ++l) {
+      const int v = i < n ? counts[l * n + i] : 0;
+      int tot;
+      const int ex = block_exclusive_scan(v, &tot);
+      if (i < n) counts[l * n + i] = carry[l] + ex;
+      carry[l] += tot;
     }
-    compact_write_kernel<Pred><<<nblk, kBlock, 0, s>>>(pred, nrows, counts, *out);
-    e = hipStreamSynchronize(s);
   }
-  (void)hipFree(counts);
-  if (e != hipSuccess) return fail(HGNN_EHIP, "compact_rows: %s", hipGetErrorString(e));
-  *n_out = total;
-  return HGNN_OK;
+  if (threadIdx.x == 0) {
+    GraphFacts r = *facts;
+    r.n_split = carry[kSplitList];
+    r.n_big = carry[kBigList];
+    r.n_mid = carry[kMidList];
+    r.n_chunks = carry[kChunkList];
+    *out = r;
+  }
 }
 
-__global__ void split_segs_kernel(const int* __restrict__ rowptr, const int* __restrict__ split_row, int n, int S,
-                                  int* __restrict__ lo, int* __restrict__ hi) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int r = split_row[i];
-  lo[i] = rowptr[r] / S;
-  hi[i] = (rowptr[r + 1] - 1) / S;
+struct RowListArrays {
+  int *split_row, *split_lo, *split_hi, *big_row, *big_first, *mid_row, *chunk_row, *chunk_first, *chunk_count;
+};
+
+__global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int nblk, const int* __restrict__ offsets, RowListArrays o) {
+  const int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
+  int m[kRowsPerThread][kLists], c[kLists] = {0, 0, 0, 0}, pos[kLists];
+  for (int u = 0; u < kRowsPerThread; ++u) {
+    for (int i = 0; i < kLists; ++i) m[u][i] = 0;
+    int len;
+    if (base + u < q.nrows) row_memberships(q, base + u, m[u], len);
+    for (int i = 0; i < kLists; ++i) c[i] += m[u][i];
+  }
+  for (int i = 0; i < kLists; ++i) {
+    int total;
+    pos[i] = offsets[i * nblk + blockIdx.x] + block_exclusive_scan(c[i], &total);
+  }
+  for (int u = 0; u < kRowsPerThread; ++u) {
+    const int r = base + u;
+    if (m[u][kSplitList]) {
+      const int k = pos[kSplitList]++;
+      o.split_row[k] = r;
+      o.split_lo[k] = q.rowptr[r] / q.S;
+      o.split_hi[k] = (q.rowptr[r + 1] - 1) / q.S;
+    }
+    if (m[u][kMidList]) o.mid_row[pos[kMidList]++] = r;
+    if (m[u][kBigList]) {
+      const int k = pos[kBigList]++, first = pos[kChunkList], nch = m[u][kChunkList];
+      o.big_row[k] = r;
+      o.big_first[k] = first;
+      for (int j = 0; j < nch; ++j) {
+        o.chunk_row[first + j] = r;
+        o.chunk_first[first + j] = first;
+        o.chunk_count[first + j] = nch;
+      }
+      pos[kChunkList] += nch;
+    }
+  }
 }
 
-// Builds the segment arrays, split-row list and staging buffer of p for the graph g (p->S, p->nseg,
-// p->max_F set by the caller).  sub = true: p is the sub-plan of one column block.
+// Builds the segment arrays, row lists and staging buffer of p for the graph g (p->S, p->nseg, p->max_F set by the
+// caller).  sub = true: p is the sub-plan of one column block; otherwise the graph is validated as well.  The host waits
+// twice: for the totals of the lists (which size the allocations) and for the arrays.
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub) {
   const int64_t E = g->nnz;
+  const int nblk = int(ceil_div(g->nrows, kRowsPerBlock));
+  DevTemp facts_buf, counts_buf;
+  HostMail mail;
+  HGNN_HIP(facts_buf.alloc(2 * sizeof(GraphFacts)));
+  HGNN_HIP(counts_buf.alloc(sizeof(int) * kLists * (size_t(nblk) + 1)));
+  GraphFacts* facts = facts_buf.as<GraphFacts>();
+  GraphFacts* totals = mail.data ? reinterpret_cast<GraphFacts*>(mail.data) : facts + 1;
+  int* counts = counts_buf.as<int>();
+  if (sub) HGNN_HIP(hipMemsetAsync(facts, 0, sizeof(GraphFacts), s));
+  else HGNN_HIP(launch_validate(g, facts, s));
+  const RowLists q{g->rowptr, g->nrows, p->S, sub ? -1 : p->big_deg, p->mid_deg};
+  if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
+  row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
+  HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
+  GraphFacts f;
+  if (mail.data) {
+    HGNN_HIP(hipStreamSynchronize(s));
+    f = *totals;
+  } else {
+    HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
+    HGNN_HIP(hipStreamSynchronize(s));
+  }
+  hgnn_status st = check_facts(f);
+  if (st != HGNN_OK) return st;
+  p->n_split = f.n_split;
+  p->n_big = f.n_big;
+  p->n_mid = f.n_mid;
+  p->n_hub_chunks = f.n_chunks;
+  p->listed_nnz = int64_t(f.listed);
   if (E > 0) {
-    HGNN_HIP(hipMalloc(&p->seg_row_lo, sizeof(int) * size_t(p->nseg)));
-    HGNN_HIP(hipMalloc(&p->seg_row_hi, sizeof(int) * size_t(p->nseg)));
+    HGNN_HIP(dev_malloc(&p->seg_row_lo, sizeof(int) * size_t(p->nseg)));
+    HGNN_HIP(dev_malloc(&p->seg_row_hi, sizeof(int) * size_t(p->nseg)));
     seg_rows_kernel<<<dim3(unsigned(ceil_div(p->nseg, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, E, p->S, p->nseg,
                                                                                   p->seg_row_lo, p->seg_row_hi);
     HGNN_LAUNCH_CHECK("seg_rows_kernel");
     // staging: two partial vectors (entering piece / leaving piece) per segment
     // (twice over, and three scalars per piece and head: the fused GAT pass that saves for its backward stages two
-    // vectors and (max, sum, masked sum) per piece)
-    HGNN_HIP(hipMalloc(&p->staging, sizeof(hgnn_half) * size_t(4) * size_t(p->nseg) * size_t(p->max_F)));
-    HGNN_HIP(hipMemsetAsync(p->staging, 0, sizeof(hgnn_half) * size_t(4) * size_t(p->nseg) * size_t(p->max_F), s));
-    HGNN_HIP(hipMalloc(&p->stage_mz, sizeof(float) * size_t(6) * size_t(p->nseg) * size_t(p->max_H)));
+    // vectors and (max, sum, masked sum) per piece); every slot that is read has been written by the same call
+    HGNN_HIP(dev_malloc(&p->staging, sizeof(hgnn_half) * size_t(4) * size_t(p->nseg) * size_t(p->max_F)));
+    HGNN_HIP(dev_malloc(&p->stage_mz, sizeof(float) * size_t(6) * size_t(p->nseg) * size_t(p->max_H)));
   }
-  hgnn_status st = compact_rows(SplitPred{g->rowptr, p->S}, g->nrows, &p->split_row, &p->n_split, s);
-  if (st != HGNN_OK) return st;
   if (p->n_split > 0) {
-    HGNN_HIP(hipMalloc(&p->split_seg_lo, sizeof(int) * size_t(p->n_split)));
-    HGNN_HIP(hipMalloc(&p->split_seg_hi, sizeof(int) * size_t(p->n_split)));
-    split_segs_kernel<<<dim3(unsigned(ceil_div(p->n_split, kBlock))), kBlock, 0, s>>>(
-        g->rowptr, p->split_row, p->n_split, p->S, p->split_seg_lo, p->split_seg_hi);
-    HGNN_LAUNCH_CHECK("split_segs_kernel");
+    HGNN_HIP(dev_malloc(&p->split_row, sizeof(int) * size_t(p->n_split)));
+    HGNN_HIP(dev_malloc(&p->split_seg_lo, sizeof(int) * size_t(p->n_split)));
+    HGNN_HIP(dev_malloc(&p->split_seg_hi, sizeof(int) * size_t(p->n_split)));
+  }
+  if (p->n_mid > 0) HGNN_HIP(dev_malloc(&p->mid_row, sizeof(int) * size_t(p->n_mid)));
+  if (p->n_big > 0) {  // the long rows and their chunk table
+    const size_t nc = size_t(p->n_hub_chunks);
+    HGNN_HIP(dev_malloc(&p->big_row, sizeof(int) * size_t(p->n_big)));
+    HGNN_HIP(dev_malloc(&p->big_first, sizeof(int) * size_t(p->n_big)));
+    HGNN_HIP(dev_malloc(&p->hub_chunk_row, sizeof(int) * nc));
+    HGNN_HIP(dev_malloc(&p->hub_chunk_first, sizeof(int) * nc));
+    HGNN_HIP(dev_malloc(&p->hub_chunk_count, sizeof(int) * nc));
+    HGNN_HIP(dev_malloc(&p->hub_part, sizeof(float) * 2 * nc * size_t(p->max_H)));
+  }
+  if (p->n_split + p->n_mid + p->n_big > 0) {
+    row_lists_write_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts,
+                                                   RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row,
+                                                                 p->big_first, p->mid_row, p->hub_chunk_row, p->hub_chunk_first,
+                                                                 p->hub_chunk_count});
+    HGNN_LAUNCH_CHECK("row_lists_write_kernel");
   }
   if (!sub) {  // a column block's sub-plan only serves the SpMM kernels
-    st = compact_rows(BigPred{g->rowptr, p->big_deg}, g->nrows, &p->big_row, &p->n_big, s);
-    if (st != HGNN_OK) return st;
-    st = compact_rows(MidPred{g->rowptr, p->mid_deg, p->big_deg}, g->nrows, &p->mid_row, &p->n_mid, s);
-    if (st != HGNN_OK) return st;
-    if (p->n_big > 0) {  // chunk table of the long rows (a short list: built on the host)
-      std::vector<int> rows(size_t(p->n_big)), rp(size_t(g->nrows) + 1);
-      HGNN_HIP(hipMemcpyAsync(rows.data(), p->big_row, sizeof(int) * rows.size(), hipMemcpyDeviceToHost, s));
-      HGNN_HIP(hipMemcpyAsync(rp.data(), g->rowptr, sizeof(int) * rp.size(), hipMemcpyDeviceToHost, s));
-      HGNN_HIP(hipStreamSynchronize(s));
-      std::vector<int> c_row, c_first, c_count, first(size_t(p->n_big));
-      for (size_t i = 0; i < rows.size(); ++i) {
-        const int deg = rp[size_t(rows[i]) + 1] - rp[size_t(rows[i])];
-        const int nch = (deg + kHubEdges - 1) / kHubEdges;
-        first[i] = int(c_row.size());
-        for (int c = 0; c < nch; ++c) {
-          c_row.push_back(rows[i]);
-          c_first.push_back(first[i]);
-          c_count.push_back(nch);
-        }
-      }
-      p->n_hub_chunks = int32_t(c_row.size());
-      const size_t nc = c_row.size();
-      HGNN_HIP(hipMalloc(&p->hub_chunk_row, sizeof(int) * nc));
-      HGNN_HIP(hipMalloc(&p->hub_chunk_first, sizeof(int) * nc));
-      HGNN_HIP(hipMalloc(&p->hub_chunk_count, sizeof(int) * nc));
-      HGNN_HIP(hipMalloc(&p->big_first, sizeof(int) * first.size()));
-      HGNN_HIP(hipMalloc(&p->hub_part, sizeof(float) * 2 * nc * size_t(p->max_H)));
-      HGNN_HIP(hipMemcpyAsync(p->hub_chunk_row, c_row.data(), sizeof(int) * nc, hipMemcpyHostToDevice, s));
-      HGNN_HIP(hipMemcpyAsync(p->hub_chunk_first, c_first.data(), sizeof(int) * nc, hipMemcpyHostToDevice, s));
-      HGNN_HIP(hipMemcpyAsync(p->hub_chunk_count, c_count.data(), sizeof(int) * nc, hipMemcpyHostToDevice, s));
-      HGNN_HIP(hipMemcpyAsync(p->big_first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, s));
-      HGNN_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
-    }
-    if (p->n_mid + p->n_big > 0) {  // how many non-zeros the two lists hold: the edge-row kernels size their teams by the rest
-      unsigned long long* total = nullptr;
-      HGNN_HIP(hipMalloc(&total, sizeof(unsigned long long)));
-      hipError_t e = hipMemsetAsync(total, 0, sizeof(unsigned long long), s);
-      if (e == hipSuccess && p->n_mid > 0)
-        list_length_sum_kernel<<<dim3(unsigned(ceil_div(p->n_mid, kBlock))), kBlock, 0, s>>>(g->rowptr, p->mid_row, p->n_mid, total);
-      if (e == hipSuccess && p->n_big > 0)
-        list_length_sum_kernel<<<dim3(unsigned(ceil_div(p->n_big, kBlock))), kBlock, 0, s>>>(g->rowptr, p->big_row, p->n_big, total);
-      unsigned long long h = 0;
-      if (e == hipSuccess) e = hipMemcpyAsync(&h, total, sizeof(h), hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = hipStreamSynchronize(s);
-      (void)hipFree(total);
-      if (e != hipSuccess) return fail(HGNN_EHIP, "hgnn_plan_create: %s", hipGetErrorString(e));
-      p->listed_nnz = int64_t(h);
-    }
-    size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
-    if (nv > 0) HGNN_HIP(hipMalloc(&p->vscratch, sizeof(float) * nv));
-    if (g->nrows > 0) HGNN_HIP(hipMalloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));
+    const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
+    if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));
+    if (g->nrows > 0) HGNN_HIP(dev_malloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));
   }
   HGNN_HIP(hipStreamSynchronize(s));
   return HGNN_OK;
@@ -412,26 +464,14 @@ hgnn_status hgnn_csr_validate(const hgnn_csr* g, void* stream) {
   hgnn_status st = check_csr_args(g, "hgnn_csr_validate");
   if (st != HGNN_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int* derr = nullptr;
-  HGNN_HIP(hipMalloc(&derr, sizeof(int)));
-  int herr = 0;
-  hipError_t e = hipMemsetAsync(derr, 0x7f, sizeof(int), s);
-  if (e == hipSuccess) {
-    validate_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) + 1, kBlock))), kBlock, 0, s>>>(*g, derr);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(&herr, derr, sizeof(int), hipMemcpyDeviceToHost, s);
+  DevTemp facts;
+  GraphFacts f;
+  HGNN_HIP(facts.alloc(sizeof(GraphFacts)));
+  hipError_t e = launch_validate(g, facts.as<GraphFacts>(), s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&f, facts.p, sizeof(f), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess && herr == kNoError && g->nnz > 0) {
-    validate_edges_kernel<<<dim3(unsigned(ceil_div(g->nnz, kBlock))), kBlock, 0, s>>>(*g, derr);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&herr, derr, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-  }
-  (void)hipFree(derr);
   if (e != hipSuccess) return fail(HGNN_EHIP, "hgnn_csr_validate: %s", hipGetErrorString(e));
-  if (herr != kNoError) return fail(HGNN_EINVAL, "hgnn_csr_validate: %s", kRule[herr > 0 && herr < 8 ? herr : 0]);
-  return HGNN_OK;
+  return check_facts(f);
 }
 
 int64_t hgnn_plan_num_segments(const hgnn_plan* p) { return p ? p->nseg : 0; }
@@ -446,42 +486,52 @@ void hgnn_plan_cache_bytes(const hgnn_plan* p, int64_t* l2_bytes, int64_t* llc_b
   if (llc_bytes) *llc_bytes = p ? p->llc_bytes : 0;
 }
 
+}  // extern "C"
+
+static void destroy_plan(hgnn_plan* p) {
+  if (!p) return;
+  for (hgnn_plan* q : p->sub) destroy_plan(q);
+  destroy_plan(p->fine);
+  dev_free(p->brp);
+  dev_free(p->bcol);
+  dev_free(p->beid);
+  dev_free(p->bdelta);
+  dev_free(p->bstage);
+  dev_free(p->bsum);
+  dev_free(p->bdesc);
+  dev_free(p->seg_row_lo);
+  dev_free(p->seg_row_hi);
+  dev_free(p->split_row);
+  dev_free(p->split_seg_lo);
+  dev_free(p->split_seg_hi);
+  dev_free(p->big_row);
+  dev_free(p->hub_chunk_row);
+  dev_free(p->hub_chunk_first);
+  dev_free(p->hub_chunk_count);
+  dev_free(p->big_first);
+  dev_free(p->hub_part);
+  dev_free(p->mid_row);
+  dev_free(p->staging);
+  dev_free(p->stage_mz);
+  dev_free(p->vscratch);
+  dev_free(p->vtab);
+  dev_free(p->goff);
+  dev_free(p->moff);
+  dev_free(p->grp_row);
+  dev_free(p->gstage);
+  dev_free(p->scut);
+  dev_free(p->chunk_row);
+  dev_free(p->col_part);
+  dev_free(p->col_poison);
+  delete p;
+}
+
+extern "C" {
+
 void hgnn_plan_destroy(hgnn_plan* p) {
   if (!p) return;
-  for (hgnn_plan* q : p->sub) hgnn_plan_destroy(q);
-  hgnn_plan_destroy(p->fine);
-  (void)hipFree(p->brp);
-  (void)hipFree(p->bcol);
-  (void)hipFree(p->beid);
-  (void)hipFree(p->bdelta);
-  (void)hipFree(p->bstage);
-  (void)hipFree(p->bsum);
-  (void)hipFree(p->bdesc);
-  (void)hipFree(p->seg_row_lo);
-  (void)hipFree(p->seg_row_hi);
-  (void)hipFree(p->split_row);
-  (void)hipFree(p->split_seg_lo);
-  (void)hipFree(p->split_seg_hi);
-  (void)hipFree(p->big_row);
-  (void)hipFree(p->hub_chunk_row);
-  (void)hipFree(p->hub_chunk_first);
-  (void)hipFree(p->hub_chunk_count);
-  (void)hipFree(p->big_first);
-  (void)hipFree(p->hub_part);
-  (void)hipFree(p->mid_row);
-  (void)hipFree(p->staging);
-  (void)hipFree(p->stage_mz);
-  (void)hipFree(p->vscratch);
-  (void)hipFree(p->vtab);
-  (void)hipFree(p->goff);
-  (void)hipFree(p->moff);
-  (void)hipFree(p->grp_row);
-  (void)hipFree(p->gstage);
-  (void)hipFree(p->scut);
-  (void)hipFree(p->chunk_row);
-  (void)hipFree(p->col_part);
-  (void)hipFree(p->col_poison);
-  delete p;
+  (void)hipDeviceSynchronize();  // calls that use the plan may be in flight, and its memory is handed to the next plan
+  destroy_plan(p);
 }
 
 hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F, int32_t max_H, int32_t col_blocks,
@@ -498,8 +548,6 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
   HGNN_REQUIRE(max_H >= 1, HGNN_EINVAL, "hgnn_plan_create: max_H = %d must be positive", max_H);
   HGNN_REQUIRE(col_blocks >= 0 && col_blocks <= 64, HGNN_EINVAL, "hgnn_plan_create: col_blocks = %d outside [0, 64]",
                col_blocks);
-  st = hgnn_csr_validate(g, stream);
-  if (st != HGNN_OK) return st;
   hgnn_plan* p = new (std::nothrow) hgnn_plan();
   HGNN_REQUIRE(p != nullptr, HGNN_ENOMEM, "hgnn_plan_create: host allocation failed");
   p->nrows = g->nrows;

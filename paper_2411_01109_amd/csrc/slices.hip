@@ -259,10 +259,10 @@ __global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int
 }
 
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s) {
-  (void)hipFree(p->scut);
-  (void)hipFree(p->chunk_row);
-  (void)hipFree(p->col_part);
-  (void)hipFree(p->col_poison);
+  dev_free(p->scut);
+  dev_free(p->chunk_row);
+  dev_free(p->col_part);
+  dev_free(p->col_poison);
   p->scut = p->chunk_row = nullptr;
   p->col_part = nullptr;
   p->col_poison = nullptr;
@@ -279,10 +279,10 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t
   int nch = 8 * std::max(1, (cus / 8) / ns);
   const int by_rows = 8 * int(ceil_div(g->nrows, 8 * 512));
   if (nch > by_rows) nch = by_rows;
-  HGNN_HIP(hipMalloc(&p->scut, sizeof(int) * size_t(ns + 1) * size_t(g->nrows)));
-  HGNN_HIP(hipMalloc(&p->chunk_row, sizeof(int) * size_t(nch + 1)));
-  HGNN_HIP(hipMalloc(&p->col_part, sizeof(unsigned long long) * size_t(nch) * size_t(g->ncols)));
-  HGNN_HIP(hipMalloc(&p->col_poison, sizeof(float) * size_t(g->ncols)));
+  HGNN_HIP(dev_malloc(&p->scut, sizeof(int) * size_t(ns + 1) * size_t(g->nrows)));
+  HGNN_HIP(dev_malloc(&p->chunk_row, sizeof(int) * size_t(nch + 1)));
+  HGNN_HIP(dev_malloc(&p->col_part, sizeof(unsigned long long) * size_t(nch) * size_t(g->ncols)));
+  HGNN_HIP(dev_malloc(&p->col_poison, sizeof(float) * size_t(g->ncols)));
   HGNN_HIP(hipMemsetAsync(p->col_poison, 0, sizeof(float) * size_t(g->ncols), s));
   slice_cuts_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) * (ns + 1), kBlock))), kBlock, 0, s>>>(g->rowptr, g->col, g->nrows,
                                                                                                     ns, W, p->scut);

@@ -10,51 +10,131 @@
 
 namespace hgnn {
 
-__global__ void iota_kernel(int* __restrict__ v, int64_t n) {
-  int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (k < n) v[k] = int(k);
-}
-
-// rowptr_T[j] = number of non-zeros whose column is < j = lower bound of j in the sorted column keys
-__global__ void offsets_kernel(const int* __restrict__ sorted_col, int64_t nnz, int ncols, int* __restrict__ rowptr_T) {
+// rowptr_T[j] = number of sorted keys whose leading field (key >> shift) is < j
+template <class Key>
+__global__ void offsets_kernel(const Key* __restrict__ sorted, int shift, int64_t nnz, int ncols, int* __restrict__ rowptr_T) {
   int64_t j = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (j > ncols) return;
   int64_t lo = 0, hi = nnz;
   while (lo < hi) {
     int64_t mid = (lo + hi) >> 1;
-    if (sorted_col[mid] < j) lo = mid + 1;
+    if (int64_t(sorted[mid] >> shift) < j) lo = mid + 1;
     else hi = mid;
   }
   rowptr_T[j] = int(lo);
 }
 
-// COO -> CSR: key = (row, col) in one 64-bit word, so that one stable sort orders the edges by row, then column,
-// then position in the list; bad receives 1 when an id is out of range (such an edge gets key 0)
-__global__ void coo_keys_kernel(const int* __restrict__ row, const int* __restrict__ col, int64_t nnz, int nrows, int ncols,
-                                uint64_t* __restrict__ keys, int* __restrict__ ids, int* __restrict__ bad) {
+// COO -> CSR: key = (row, col, list position) packed into one 64-bit word (position_bits = 0: without it), so that one
+// stable sort of the leading fields orders the edges by row, then column, then position in the list; bad receives 1 when
+// an id is out of range (such an edge gets row and column 0)
+__global__ void coo_keys_kernel(const int* __restrict__ row, const int* __restrict__ col, int64_t nnz, int nrows, int ncols, int col_bits,
+                                int position_bits, uint64_t* __restrict__ keys, int* __restrict__ ids, int* __restrict__ bad) {
   int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= nnz) return;
   const int r = row[k], c = col[k];
   const bool ok = r >= 0 && r < nrows && c >= 0 && c < ncols;
   if (!ok) atomicOr(bad, 1);
-  keys[k] = ok ? (uint64_t(uint32_t(r)) << 32) | uint64_t(uint32_t(c)) : 0;
-  ids[k] = int(k);
+  const uint64_t rc = ok ? (uint64_t(uint32_t(r)) << col_bits) | uint64_t(uint32_t(c)) : 0;
+  keys[k] = position_bits ? (rc << position_bits) | uint64_t(k) : rc;
+  if (ids) ids[k] = int(k);
 }
 
-__global__ void coo_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int* __restrict__ row_sorted,
-                                 int* __restrict__ col_out) {
+__global__ void coo_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int col_bits, int position_bits,
+                                 int* __restrict__ col_out, int* __restrict__ eid) {
   int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= nnz) return;
-  row_sorted[k] = int(keys[k] >> 32);
-  col_out[k] = int(uint32_t(keys[k]));
+  const uint64_t key = keys[k];
+  col_out[k] = int(uint32_t(key >> position_bits) & ((uint32_t(1) << col_bits) - 1u));
+  if (eid) eid[k] = int(uint32_t(key) & ((uint32_t(1) << position_bits) - 1u));
 }
 
-// col_T[k'] = row of the non-zero eid_T[k'] of A (upper bound over rowptr, minus one)
-__global__ void source_rows_kernel(const int* __restrict__ rowptr, int nrows, const int* __restrict__ eid_T, int64_t nnz,
-                                   int* __restrict__ col_T) {
+// The row of every non-zero, handed to put(k, row): a workgroup takes kExpand consecutive positions, its rows mark the slot
+// of their first non-zero in LDS and a running maximum spreads the ids (a search of the offset array per non-zero took
+// 196 us at 5.5 M non-zeros).
+constexpr int kExpandPerThread = 8;
+constexpr int kExpand = kBlock * kExpandPerThread;
+
+template <class Put>
+__device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int nrows, int64_t nnz, Put&& put) {
+  __shared__ int s_row[kExpand];
+  __shared__ int s_max[kBlock / kWave], s_lim[2];
+  const int64_t e0 = int64_t(blockIdx.x) * kExpand;
+  const int n = int(nnz - e0 < kExpand ? nnz - e0 : kExpand);
+  if (threadIdx.x < 2) s_lim[threadIdx.x] = row_of_edge(rowptr, nrows, threadIdx.x == 0 ? e0 : e0 + n - 1);
+  for (int i = threadIdx.x; i < kExpand; i += kBlock) s_row[i] = -1;
+  __syncthreads();
+  const int lo = s_lim[0], hi = s_lim[1];
+  for (int r = lo + 1 + int(threadIdx.x); r <= hi; r += kBlock) {
+    const int p = rowptr[r];
+    if (rowptr[r + 1] > p) s_row[p - int(e0)] = r;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int v[kExpandPerThread], run = lo;
+#pragma unroll
+  for (int j = 0; j < kExpandPerThread; ++j) {
+    run = max(run, s_row[threadIdx.x * kExpandPerThread + j]);
+    v[j] = run;
+  }
+  int incl = run;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if (lane >= d) incl = max(incl, t);
+  }
+  if (lane == kWave - 1) s_max[wave] = incl;
+  int excl = __shfl_up(incl, 1);
+  if (lane == 0) excl = lo;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) excl = max(excl, s_max[w]);
+#pragma unroll
+  for (int j = 0; j < kExpandPerThread; ++j) s_row[threadIdx.x * kExpandPerThread + j] = max(v[j], excl);
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kBlock) put(e0 + i, s_row[i]);
+}
+
+// transposition keys: (column, row, position) packed into one word; sorting the columns' bits brings everything along
+__global__ __launch_bounds__(kBlock) void transpose_keys_kernel(const int* __restrict__ rowptr, const int* __restrict__ col, int nrows,
+                                                                int64_t nnz, int row_bits, int position_bits,
+                                                                uint64_t* __restrict__ keys) {
+  expand_rows(rowptr, nrows, nnz, [&](int64_t k, int r) {
+    keys[k] = (((uint64_t(uint32_t(col[k])) << row_bits) | uint64_t(uint32_t(r))) << position_bits) | uint64_t(k);
+  });
+}
+
+__global__ void transpose_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int row_bits, int position_bits,
+                                       int* __restrict__ col_T, int* __restrict__ eid_T) {
   int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= nnz) return;
-  col_T[k] = row_of_edge(rowptr, nrows, eid_T[k]);
+  const uint64_t key = keys[k];
+  eid_T[k] = int(uint32_t(key) & ((uint32_t(1) << position_bits) - 1u));
+  col_T[k] = int(uint32_t(key >> position_bits) & ((uint32_t(1) << row_bits) - 1u));
+}
+
+// the same in two arrays where the three fields do not fit 64 bits: column keys with positions; rows of all positions
+__global__ __launch_bounds__(kBlock) void transpose_rows_kernel(const int* __restrict__ rowptr, const int* __restrict__ col, int nrows,
+                                                                int64_t nnz, int* __restrict__ rows, uint32_t* __restrict__ keys,
+                                                                int* __restrict__ ids) {
+  expand_rows(rowptr, nrows, nnz, [&](int64_t k, int r) {
+    rows[k] = r;
+    keys[k] = uint32_t(col[k]);
+    ids[k] = int(k);
+  });
+}
+
+__global__ void source_rows_kernel(const int* __restrict__ rows, const int* __restrict__ order, int64_t nnz, int* __restrict__ col_T,
+                                   int* __restrict__ eid_T) {
+  int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+  if (k >= nnz) return;
+  const int e = order[k];
+  eid_T[k] = e;
+  col_T[k] = rows[e];
+}
+
+static int bits_for(int64_t n) {  // bits that hold 0 .. n - 1
+  int b = 1;
+  while ((int64_t(1) << b) < n) ++b;
+  return b;
 }
 
 // out[i, f] = fp16(scale[i] * X[i, f]), 8 halves per thread
@@ -100,34 +180,51 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
     HGNN_HIP(hipStreamSynchronize(s));
     return HGNN_OK;
   }
-  int bits = 1;
-  while ((int64_t(1) << bits) < int64_t(g->ncols)) ++bits;
-  int *ids = nullptr, *keys_out = nullptr;
-  void* tmp = nullptr;
+  const int col_bits = bits_for(g->ncols), row_bits = bits_for(g->nrows), pos_bits = bits_for(E);
+  const dim3 per_edge(unsigned(ceil_div(E, kBlock))), per_tile(unsigned(ceil_div(E, kExpand)));
+  const dim3 per_col(unsigned(ceil_div(int64_t(g->ncols) + 1, kBlock)));
+  DevTemp buf[2], ids[2], rows, tmp;
   size_t tmp_bytes = 0;
-  hgnn_status rc = HGNN_OK;
-  hipError_t e = hipMalloc(&ids, sizeof(int) * size_t(E));
-  if (e == hipSuccess) e = hipMalloc(&keys_out, sizeof(int) * size_t(E));
-  if (e == hipSuccess) {
-    iota_kernel<<<dim3(unsigned(ceil_div(E, kBlock))), kBlock, 0, s>>>(ids, E);
-    e = rocprim::radix_sort_pairs(nullptr, tmp_bytes, g->col, keys_out, ids, eid_T, size_t(E), 0u, unsigned(bits), s);
+  hipError_t e = hipSuccess;
+  if (col_bits + row_bits + pos_bits <= 64) {
+    // one word per non-zero carries its row and position through a sort of the columns alone: no gather afterwards
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(8 * size_t(E));
+    rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
+    const unsigned first = unsigned(row_bits + pos_bits), last = first + unsigned(col_bits);
+    if (e == hipSuccess) e = rocprim::radix_sort_keys(nullptr, tmp_bytes, keys, unsigned(E), first, last, s);
+    if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+    if (e == hipSuccess) {
+      transpose_keys_kernel<<<per_tile, kBlock, 0, s>>>(g->rowptr, g->col, g->nrows, E, row_bits, pos_bits, keys.current());
+      e = rocprim::radix_sort_keys(tmp.p, tmp_bytes, keys, unsigned(E), first, last, s);
+    }
+    if (e == hipSuccess) {
+      transpose_split_kernel<<<per_edge, kBlock, 0, s>>>(keys.current(), E, row_bits, pos_bits, col_T, eid_T);
+      offsets_kernel<uint64_t><<<per_col, kBlock, 0, s>>>(keys.current(), int(first), E, g->ncols, rowptr_T);
+      e = hipGetLastError();
+    }
+  } else {
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(4 * size_t(E));
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = ids[i].alloc(4 * size_t(E));
+    if (e == hipSuccess) e = rows.alloc(4 * size_t(E));
+    rocprim::double_buffer<uint32_t> keys(buf[0].as<uint32_t>(), buf[1].as<uint32_t>());
+    rocprim::double_buffer<int> order(ids[0].as<int>(), ids[1].as<int>());
+    if (e == hipSuccess) e = rocprim::radix_sort_pairs(nullptr, tmp_bytes, keys, order, unsigned(E), 0u, unsigned(col_bits), s);
+    if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+    if (e == hipSuccess) {
+      transpose_rows_kernel<<<per_tile, kBlock, 0, s>>>(g->rowptr, g->col, g->nrows, E, rows.as<int>(), keys.current(), order.current());
+      e = rocprim::radix_sort_pairs(tmp.p, tmp_bytes, keys, order, unsigned(E), 0u, unsigned(col_bits), s);
+    }
+    if (e == hipSuccess) {
+      source_rows_kernel<<<per_edge, kBlock, 0, s>>>(rows.as<int>(), order.current(), E, col_T, eid_T);
+      offsets_kernel<uint32_t><<<per_col, kBlock, 0, s>>>(keys.current(), 0, E, g->ncols, rowptr_T);
+      e = hipGetLastError();
+    }
   }
-  if (e == hipSuccess) e = hipMalloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
-  if (e == hipSuccess)
-    e = rocprim::radix_sort_pairs(tmp, tmp_bytes, g->col, keys_out, ids, eid_T, size_t(E), 0u, unsigned(bits), s);
-  if (e == hipSuccess) {
-    offsets_kernel<<<dim3(unsigned(ceil_div(int64_t(g->ncols) + 1, kBlock))), kBlock, 0, s>>>(keys_out, E, g->ncols,
-                                                                                               rowptr_T);
-    source_rows_kernel<<<dim3(unsigned(ceil_div(E, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, eid_T, E, col_T);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  const hipError_t e2 = hipStreamSynchronize(s);  // also after a failure: the buffers go back
+  if (e == hipSuccess) e = e2;
   if (e != hipSuccess)
-    rc = fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "hgnn_transpose: %s", hipGetErrorString(e));
-  (void)hipFree(ids);
-  (void)hipFree(keys_out);
-  (void)hipFree(tmp);
-  return rc;
+    return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "hgnn_transpose: %s", hipGetErrorString(e));
+  return HGNN_OK;
 }
 
 extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t* row, const int32_t* col,
@@ -145,65 +242,47 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
     HGNN_HIP(hipStreamSynchronize(s));
     return HGNN_OK;
   }
-  int row_bits = 1, col_bits = 1;
-  while ((int64_t(1) << row_bits) < int64_t(nrows)) ++row_bits;
-  while ((int64_t(1) << col_bits) < int64_t(ncols)) ++col_bits;
+  const int row_bits = bits_for(nrows), col_bits = bits_for(ncols), pos_bits = bits_for(nnz);
+  const dim3 per_edge(unsigned(ceil_div(nnz, kBlock))), per_row(unsigned(ceil_div(int64_t(nrows) + 1, kBlock)));
   const size_t E = size_t(nnz);
-  uint64_t *keys = nullptr, *keys_out = nullptr;
-  int *ids = nullptr, *ids_out = nullptr, *row_sorted = nullptr, *bad = nullptr;
-  void* tmp = nullptr;
+  DevTemp buf[2], ids[2], bad, tmp;
+  HostMail mail;
   size_t tmp_bytes = 0;
   int hbad = 0;
-  hgnn_status rc = HGNN_OK;
-  hipError_t e = hipMalloc(&keys, 8 * E);
-  if (e == hipSuccess) e = hipMalloc(&keys_out, 8 * E);
-  if (e == hipSuccess) e = hipMalloc(&ids, 4 * E);
-  if (e == hipSuccess) e = hipMalloc(&row_sorted, 4 * E);
-  if (e == hipSuccess) e = hipMalloc(&bad, 4);
-  if (e == hipSuccess && !eid) e = hipMalloc(&ids_out, 4 * E);
-  int* order = eid ? eid : ids_out;
-  if (e == hipSuccess) e = hipMemsetAsync(bad, 0, 4, s);
+  // the list position rides in the key where it fits (or is not asked for), else beside it
+  const bool packed = !eid || row_bits + col_bits + pos_bits <= 64;
+  const int in_key = packed && eid ? pos_bits : 0;
+  const unsigned first = unsigned(in_key), last = first + unsigned(row_bits + col_bits);
+  hipError_t e = bad.alloc(4);
+  for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(8 * E);
+  for (int i = 0; i < 2 && e == hipSuccess && !packed; ++i) e = ids[i].alloc(4 * E);
+  rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
+  rocprim::double_buffer<int> order(ids[0].as<int>(), ids[1].as<int>());
+  auto sort = [&](void* t) {
+    return packed ? rocprim::radix_sort_keys(t, tmp_bytes, keys, unsigned(E), first, last, s)
+                  : rocprim::radix_sort_pairs(t, tmp_bytes, keys, order, unsigned(E), first, last, s);
+  };
+  if (e == hipSuccess) e = sort(nullptr);
+  if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+  if (e == hipSuccess) e = hipMemsetAsync(bad.p, 0, 4, s);
   if (e == hipSuccess) {
-    coo_keys_kernel<<<dim3(unsigned(ceil_div(nnz, kBlock))), kBlock, 0, s>>>(row, col, nnz, nrows, ncols, keys, ids, bad);
-    // the columns occupy the low word: the bits between col_bits and 32 are zero in every key and are skipped by
-    // sorting the two fields one after the other (least significant field first; the sort is stable)
-    e = rocprim::radix_sort_pairs(nullptr, tmp_bytes, keys, keys_out, ids, order, E, 0u, unsigned(col_bits), s);
+    coo_keys_kernel<<<per_edge, kBlock, 0, s>>>(row, col, nnz, nrows, ncols, col_bits, in_key, keys.current(),
+                                                packed ? nullptr : order.current(), bad.as<int>());
+    e = sort(tmp.p);
   }
-  if (e == hipSuccess) e = hipMalloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
-  if (e == hipSuccess) e = rocprim::radix_sort_pairs(tmp, tmp_bytes, keys, keys_out, ids, order, E, 0u, unsigned(col_bits), s);
   if (e == hipSuccess) {
-    size_t need = 0;
-    e = rocprim::radix_sort_pairs(nullptr, need, keys_out, keys, order, ids, E, 32u, unsigned(32 + row_bits), s);
-    if (e == hipSuccess && need > tmp_bytes) {
-      (void)hipStreamSynchronize(s);
-      (void)hipFree(tmp);
-      tmp = nullptr;
-      tmp_bytes = need;
-      e = hipMalloc(&tmp, tmp_bytes);
-    }
-  }
-  if (e == hipSuccess)
-    e = rocprim::radix_sort_pairs(tmp, tmp_bytes, keys_out, keys, order, ids, E, 32u, unsigned(32 + row_bits), s);
-  if (e == hipSuccess) {  // sorted keys are back in `keys`, the order in `ids`
-    coo_split_kernel<<<dim3(unsigned(ceil_div(nnz, kBlock))), kBlock, 0, s>>>(keys, nnz, row_sorted, col_out);
-    offsets_kernel<<<dim3(unsigned(ceil_div(int64_t(nrows) + 1, kBlock))), kBlock, 0, s>>>(row_sorted, nnz, nrows, rowptr);
+    coo_split_kernel<<<per_edge, kBlock, 0, s>>>(keys.current(), nnz, col_bits, in_key, col_out, packed ? eid : nullptr);
+    offsets_kernel<uint64_t><<<per_row, kBlock, 0, s>>>(keys.current(), in_key + col_bits, nnz, nrows, rowptr);
     e = hipGetLastError();
   }
-  if (e == hipSuccess && eid) e = hipMemcpyAsync(eid, ids, 4 * E, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess)
-    rc = fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
-  else if (hbad)
-    rc = fail(HGNN_EINVAL, "%s: a row id outside [0, nrows) or a column id outside [0, ncols)", who);
-  (void)hipFree(keys);
-  (void)hipFree(keys_out);
-  (void)hipFree(ids);
-  (void)hipFree(ids_out);
-  (void)hipFree(row_sorted);
-  (void)hipFree(bad);
-  (void)hipFree(tmp);
-  return rc;
+  if (e == hipSuccess && !packed) e = hipMemcpyAsync(eid, order.current(), 4 * E, hipMemcpyDeviceToDevice, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(mail.data ? static_cast<void*>(mail.data) : &hbad, bad.p, 4, hipMemcpyDeviceToHost, s);
+  const hipError_t e2 = hipStreamSynchronize(s);  // also after a failure: the buffers go back
+  if (e == hipSuccess) e = e2;
+  if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
+  if (mail.data) hbad = *reinterpret_cast<const int*>(mail.data);
+  if (hbad) return fail(HGNN_EINVAL, "%s: a row id outside [0, nrows) or a column id outside [0, ncols)", who);
+  return HGNN_OK;
 }
 
 extern "C" hgnn_status hgnn_edge_to_transposed(const hgnn_csr* gt, int32_t H, const hgnn_half* t, hgnn_half* t_T,

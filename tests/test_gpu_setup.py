@@ -1,0 +1,134 @@
+"""Set-up calls at the edges of their dispatch: edge lists and transposes whose fields do and do not fit one 64-bit sort key,
+row lists of every kind, graphs rejected by each rule, and the memory that set-up calls keep for one another."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+from parity import up
+
+pytestmark = pytest.mark.gpu
+
+
+def down(t):
+    return t.cpu().numpy()
+
+
+def check_lists(hgnn, dev, V, row, col):
+    E = row.size
+    g, eid = hgnn.hgnn_coo_to_csr(up(row, dev), up(col, dev), V, V)
+    order = np.lexsort((np.arange(E), col, row))
+    assert np.array_equal(down(eid), order) and np.array_equal(down(g.col), col[order])
+    rowptr = np.searchsorted(row[order], np.arange(V + 1))
+    assert np.array_equal(down(g.rowptr), rowptr)
+    h, none = hgnn.hgnn_coo_to_csr(up(row, dev), up(col, dev), V, V, want_eid=False)
+    assert none is None and torch.equal(h.col, g.col) and torch.equal(h.rowptr, g.rowptr)
+    gt = hgnn.hgnn_transpose(g)
+    t = np.argsort(col[order], kind="stable")
+    assert np.array_equal(down(gt.eid), t) and np.array_equal(down(gt.col), row[order][t])
+    assert np.array_equal(down(gt.rowptr), np.searchsorted(col[order][t], np.arange(V + 1)))
+    return g, gt
+
+
+# 2^25 vertices and 2^15 edges: 65 bits for row, column and position; with 2^24 vertices they fit
+@pytest.mark.parametrize("V,E", [(1, 1), (3, 2047), (5, 2049), (1000, 4096), (40000, 100001), (1 << 24, 1 << 14), ((1 << 24) + 1, (1 << 15) + 1)])
+def test_sort_keys(hgnn, dev, V, E):
+    print(f"setup V={V} E={E}", flush=True)
+    r = np.random.default_rng(V + E)
+    row, col = (r.integers(0, V, E).astype(np.int32) for _ in range(2))
+    row[: E // 3] = row[0]  # a hub, and duplicates
+    col[: E // 8] = col[0]
+    check_lists(hgnn, dev, V, row, col)
+
+
+def test_plan_lists(hgnn, dev):
+    """Rows shorter and longer than every threshold of a plan, empty rows between them."""
+    r = np.random.default_rng(3)
+    deg = np.concatenate([r.integers(0, 40, 3000), [31, 32, 33, 2047, 2048, 2049, 4096, 4097, 9000], np.zeros(1500, int), [1, 300, 5000]])
+    V = deg.size
+    row = np.repeat(np.arange(V, dtype=np.int32), deg)
+    col = r.integers(0, V, row.size).astype(np.int32)
+    g, gt = check_lists(hgnn, dev, V, row, col)
+    for S in (64, 256, 1000):
+        p = hgnn.hgnn_plan_create(g, S, 64, 1)
+        x = hgnn.hgnn_plan_export(p)
+        rowptr = down(g.rowptr).astype(np.int64)
+        b, e = rowptr[:-1], rowptr[1:]
+        split = np.flatnonzero((e > b) & (b // S != (e - 1) // S))
+        assert np.array_equal(x["split_row"], split)
+        assert np.array_equal(x["split_seg_lo"], b[split] // S) and np.array_equal(x["split_seg_hi"], (e[split] - 1) // S)
+
+
+@pytest.mark.parametrize("rule", range(8))
+def test_validation_rules(hgnn, dev, rule):
+    V, E = 3000, 20000
+    r = np.random.default_rng(rule)
+    rowptr = np.sort(np.concatenate([[0, E], r.integers(0, E + 1, V - 1)])).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, V, n)) for n in np.diff(rowptr)]).astype(np.int32)
+    row, eid = np.repeat(np.arange(V), np.diff(rowptr)).astype(np.int32), r.permutation(E).astype(np.int32)
+    k = int(rowptr[np.argmax(np.diff(rowptr))])  # inside the longest row
+    if rule == 1:
+        rowptr[0] = 1
+    elif rule == 2:
+        rowptr[-1] = E - 1
+    elif rule == 3:
+        rowptr[V // 2] = rowptr[V // 2 + 1] + 1
+    elif rule == 4:
+        col[k] = V
+    elif rule == 5:
+        eid[k] = -1
+    elif rule == 6:
+        row[k] += 1
+    elif rule == 7:
+        col[k], col[k + 1] = V - 1, 0
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), row=up(row, dev), eid=up(eid, dev))
+    words = [None, "rowptr[0]", "rowptr[nrows]", "decreases", "column id", "edge id", "COO row id", "ascending"]
+    for call in (lambda: hgnn.hgnn_csr_validate(g), lambda: hgnn.hgnn_plan_create(g, 256, 8, 1)):
+        if rule == 0:
+            call()
+            continue
+        with pytest.raises(hgnn.HgnnError) as err:
+            call()
+        assert err.value.status == hgnn.HGNN_EINVAL and words[rule] in str(err.value)
+
+
+def test_kept_memory(hgnn, dev):
+    """Plans made and destroyed by several threads on streams of their own get memory of earlier ones and stay correct."""
+    V, E = 2000, 30000
+    r = np.random.default_rng(9)
+    lists = [(up(r.integers(0, V, E).astype(np.int32), dev), up(r.integers(0, V, E).astype(np.int32), dev)) for _ in range(3)]
+    X = torch.randn((V, 64), device=dev).half()
+    want = []
+    for row, col in lists:
+        A = torch.zeros((V, V), device=dev)
+        A.index_put_((row.long(), col.long()), torch.ones(E, device=dev), accumulate=True)
+        want.append(A @ X.float())
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        torch.cuda.set_device(dev)
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for k in range(6):
+                row, col = lists[(i + k) % 3]
+                g = hgnn.hgnn_coo_to_csr(row, col, V, V, want_eid=False)[0]
+                p = hgnn.hgnn_plan_create(g, 64, 64, 1)
+                Y = torch.empty_like(X)
+                hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+                del p
+                s.synchronize()
+                if (Y.float() - want[(i + k) % 3]).abs().max() > 0.05:
+                    wrong.append((i, k))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    hgnn.hgnn_release_cached_memory()
+    hgnn.hgnn_release_cached_memory()
+    work(0)
+    assert not wrong
