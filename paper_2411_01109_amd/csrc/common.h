@@ -292,6 +292,30 @@ struct hgnn_seg_block {
   float* stage_mz;         // scalars of the staged pieces of the fused GAT passes
 };
 
+// ---- row tasks of a plan (tasks.hip): the rows of a graph, or of its column blocks, as pieces of work for a wave ----
+// A piece of a row is at most S consecutive non-zeros (S = the plan's segment size); a row within S is one piece.  Pieces
+// longer than a threshold take a whole wave each, shorter ones a lane group, sorted by length inside windows of rows so
+// that the groups of a wave end together; empty rows are listed on their own.
+// One piece: x = first non-zero (in the task's column array), y = length | block << 16, z = row, w = staging slot of a row
+// that has several pieces, or -1.
+struct hgnn_task_sec {  // the pieces of one column block (or of the whole graph)
+  int32_t w_off, nw;  // task[w_off ..): whole-wave pieces
+  int32_t g_off, ng;  // task[g_off ..): lane-group pieces
+  int32_t z_off, nz;  // zrow[z_off ..): empty rows
+  int32_t first;      // the block's first non-zero in the task's column array
+};
+struct hgnn_row_tasks {
+  int32_t nb = 0;
+  int4* task = nullptr;
+  int32_t* zrow = nullptr;
+  int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
+  hgnn_task_sec* sec = nullptr;  // [nb]
+  int32_t n_split = 0, n_slots = 0;
+  std::vector<hgnn_task_sec> host;  // sec on the host
+  hgnn_half* staging = nullptr;  // [2][n_slots][max_F] partial vectors (second set: masked vectors of the saving GAT pass)
+  float* stage_mz = nullptr;     // [3][n_slots][max_H] scalars of the partial vectors of the fused GAT passes
+};
+
 // The plan object behind the opaque handle of the C ABI.
 constexpr int kHubEdges = 2048;  // non-zeros per chunk of a long row in the edge-row kernels
 
@@ -341,6 +365,8 @@ struct hgnn_plan {
   std::vector<int64_t> boff;        // [nb+1] first non-zero of every block in bcol / beid
   std::vector<hgnn_plan*> sub;      // [nb] segment plans of the blocks
   hgnn_seg_block* bdesc = nullptr;  // [nb] the blocks' arrays, for kernels that walk all blocks in one launch
+  hgnn_row_tasks* tasks = nullptr;   // of the whole graph
+  hgnn_row_tasks* btasks = nullptr;  // of the column blocks (nb > 1; not where `fine` takes their place)
   hgnn_plan* fine = nullptr;        // the same graph in twice the blocks (blocked arrays only), for the SpMM that gathers edge
                                     // values through the edge-id map and for the SDDMM; only where the automatic rule
                                     // chose the blocks
@@ -384,6 +410,29 @@ size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratc
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub);
 hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_t s);
 constexpr int kSliceMaxCols = 16384;  // columns per slice: 8 bytes each fill 128 KB of the 160 KB of LDS a workgroup may hold
+// row tasks in two steps around a host wait: task_count launches the counting passes, task_build takes their result
+struct TaskSource {
+  const int32_t* rowptr;  // [nb][nrows+1], every block's offsets from 0
+  const int32_t* first;   // device, [nb] first non-zero of every block, or nullptr (one block)
+  int32_t nrows, nb, S, group_max;
+};
+// Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
+// reductions across lane groups (2.1 M non-zeros x 128: 32 is 3 % better than 64; 62 M x 128: 128 is 1 % better); the pieces of
+// column blocks come in numbers and are bound by the L2s (114 M non-zeros: 256 is 3 % better than 128).
+constexpr int kGroupMaxBlocks = 256;
+inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 : 128; }
+struct TaskTotals {
+  int32_t n_task, n_whole, n_zero, n_split, n_slots;
+};
+struct TaskCounts {
+  DevTemp counts, sec;
+  HostMail mail;
+  TaskTotals* totals = nullptr;  // valid after the stream has been waited for (host memory, or a device copy)
+};
+hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s);
+hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, hipStream_t s);
+hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s);
+void destroy_tasks(hgnn_row_tasks* t);
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s);
 hgnn_status slice_edge_score(const hgnn_plan* p, const hgnn_csr* g, const float* el, const float* er, const float* lse,
                              float slope, hgnn_half* out, hipStream_t s);

@@ -371,6 +371,15 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bo
   if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
   row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
   HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
+  const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz)};
+  TaskCounts tc;
+  if (!sub) {
+    const hgnn_status ts = task_count(tq, tc, s);
+    if (ts != HGNN_OK) {
+      (void)hipStreamSynchronize(s);  // the blocks above go back when this returns
+      return ts;
+    }
+  }
   GraphFacts f;
   if (mail.data) {
     HGNN_HIP(hipStreamSynchronize(s));
@@ -419,6 +428,13 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bo
                                                                  p->big_first, p->mid_row, p->hub_chunk_row, p->hub_chunk_first,
                                                                  p->hub_chunk_count});
     HGNN_LAUNCH_CHECK("row_lists_write_kernel");
+  }
+  if (!sub) {
+    st = task_build(tq, tc, p->max_F, p->max_H, &p->tasks, s);
+    if (st != HGNN_OK) {
+      (void)hipStreamSynchronize(s);
+      return st;
+    }
   }
   if (!sub) {  // a column block's sub-plan only serves the SpMM kernels
     const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
@@ -492,6 +508,8 @@ static void destroy_plan(hgnn_plan* p) {
   if (!p) return;
   for (hgnn_plan* q : p->sub) destroy_plan(q);
   destroy_plan(p->fine);
+  destroy_tasks(p->tasks);
+  destroy_tasks(p->btasks);
   dev_free(p->brp);
   dev_free(p->bcol);
   dev_free(p->beid);
@@ -605,6 +623,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         st = build_col_blocks(f, g, 2 * p->nb, s);
       }
     }
+    if (st == HGNN_OK && p->nb > 1) st = build_block_tasks(p->fine ? p->fine : p, s);
     // column slices for the per-edge passes over per-vertex scalars: where a row's share of a slice still is a piece
     // of 16 non-zeros or more on average
     if (st == HGNN_OK && col_blocks == 0 && g->nrows > 0 && g->nnz > 0) {

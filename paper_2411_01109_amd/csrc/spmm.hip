@@ -6,10 +6,11 @@
 // halves is covered by L = pow2 >= F/8 lanes that load 16 bytes (8 halves) each, so a wave
 // holds G = 64/L such groups and touches G different neighbour rows per load instruction.
 // Products are formed and accumulated in fp32 (v_fma_mix), fp16 only when a value is stored.
-#include "common.h"
+#include "task.h"
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 namespace hgnn {
 
@@ -38,58 +39,13 @@ struct SpmmArgs {
   int64_t ld_self;
   float self_coef, agg_coef;
   // discretized kernels
-  int S;
-  int64_t nseg;
-  const int* seg_lo;  // row of the first / last edge of every segment
-  const int* seg_hi;
-  half_t* staging;  // [2*nseg][stage_ld]
+  half_t* staging;  // [slots][stage_ld] pieces of the rows that have several
   int stage_ld;
-  const int* split_row;
-  const int* split_lo;
-  const int* split_hi;
-  int n_split;
   int atomic_y;  // 1: conflicting pieces are added to Y with packed fp16 atomics instead of being staged (comparison variant)
-  // all column blocks of a plan in one launch: workgroups are numbered block after block (they are dispatched in that
-  // order, so the compute units still gather from one slice of X at a time, without a drain between the blocks)
-  const hgnn_seg_block* blocks;  // nullptr: the arrays above describe the one graph of the launch
-  int nblocks;
-  int use_eid;             // the call's graph has an edge-id map: slots through the blocks' copy of it, else through delta
+  // all column blocks of a plan in one launch: waves are numbered block after block (they are dispatched in that order, so
+  // the compute units still gather from one slice of X at a time, without a drain between the blocks)
   int64_t block_y_stride;  // halves between the blocks' partial outputs
 };
-
-// Finds the block of workgroup `wg` when blocks are walked in one launch (per block cnt(b) workgroups, at least one
-// so that an empty block still zero-fills its partial output), rewrites `a` to that block's arrays and returns the
-// workgroup's number inside the block; wg_count receives the block's workgroup count.
-template <class Count>
-__device__ __forceinline__ int64_t enter_block(SpmmArgs& a, int64_t wg, int64_t& wg_count, Count cnt) {
-  int b = 0;
-  int64_t first = 0;
-  for (;;) {
-    const int64_t c = cnt(a.blocks[b]);
-    if (wg < first + c || b + 1 == a.nblocks) {
-      wg_count = c;
-      break;
-    }
-    first += c;
-    ++b;
-  }
-  const hgnn_seg_block& B = a.blocks[b];
-  a.rowptr = B.rowptr;
-  a.col = B.col;
-  a.eid = a.use_eid ? B.eid : nullptr;
-  a.delta = a.use_eid ? nullptr : B.delta;
-  a.seg_lo = B.seg_lo;
-  a.seg_hi = B.seg_hi;
-  a.staging = reinterpret_cast<half_t*>(B.staging);
-  a.split_row = B.split_row;
-  a.split_lo = B.split_lo;
-  a.split_hi = B.split_hi;
-  a.nnz = B.nnz;
-  a.nseg = B.nseg;
-  a.n_split = B.n_split;
-  a.Y += int64_t(b) * a.block_y_stride;
-  return wg - first;
-}
 
 __device__ __forceinline__ float scale_of(const SpmmArgs& a, int r) {
   float s = 1.f;
@@ -545,376 +501,10 @@ __global__ __launch_bounds__(kBlock) void spmm_scalar_kernel(SpmmArgs a) {
   a.Y[int64_t(row) * a.ldy + f] = half_t(acc * scale_of(a, row));
 }
 
-// ---------------------------------------------------------------------------------------------------
-// Discretized-reduction SpMM, pass 1 (section 5.2): one wave per segment of S edges.
-//  phase 1  the wave loads the segment's column ids and edge values once, coalesced, into LDS
-//           (the two-phase load of section 4.1; LDS reads broadcast to a group) and derives the
-//           row id of every edge from the offset array: the rows seg_row_lo..seg_row_hi mark
-//           their first edge in LDS and a wave-wide running maximum spreads the ids.  No per-edge
-//           row array is read from memory.
-//  phase 2  group g walks its contiguous chunk of the segment, four edges per step, with a
-//           running reduction; a row piece that starts and ends inside the chunk is scaled and
-//           stored straight to Y;
-//  merge    pieces that touch a chunk border are parked in LDS (fp32, scaled) and group 0 sews
-//           them together in order: rows that lie inside the segment are stored to Y, the piece
-//           entering from the previous segment and the piece leaving into the next go to the
-//           staging buffer as fp16 (each covers at most S edges, so it cannot overflow where
-//           S * max|w x| fits fp16).  No atomics; every Y row has exactly one writer.
-// The wave also zero-fills its share of the empty rows.
-// ---------------------------------------------------------------------------------------------------
-__host__ __device__ inline int align16i(int v) { return (v + 15) & ~15; }
+constexpr int kFinishShort = 8;  // rows of at most this many pieces are summed by one lane group, longer ones by a wave
 
-struct SegLds {
-  int per;   // LDS entries per lane (multiple of 4); the padded segment holds 64*per edges
-  int spad;
-  int col_off, row_off, blk_off, w_off, vec_off, flag_off, total;
-};
-// wm: 0 = no per-edge factor, 1 = fp16 edge values, 2 = fp32 factor (edge value times column scale)
-__host__ __device__ inline SegLds seg_lds_layout(int S, int H, int wm, int L) {
-  SegLds o;
-  const int G = kWave / L;
-  o.per = 4 * ((S + 255) / 256);  // = seg_slots_per_lane(S)
-  o.spad = kWave * o.per;
-  o.col_off = 0;
-  o.row_off = o.col_off + o.spad * 4;
-  o.blk_off = o.row_off + o.spad * 4;
-  o.w_off = o.blk_off + align16i(o.spad);  // one int per 4 edges
-  o.vec_off = o.w_off + (wm == 0 ? 0 : align16i(o.spad * H * (wm == 2 ? 4 : 2)));
-  o.flag_off = o.vec_off + G * 8 * L * 4;  // one parked vector per lane group (the piece that entered its chunk)
-  o.total = o.flag_off + align16i(3 * G * 4);
-  return o;
-}
-
-// Edge values of four staged edges (i0 + q * kWave, q = 0..3) into the LDS table: fp16 as they are (WM == 1) or
-// as fp32 factors times the column scale cs (WM == 2; no values: the scale alone).  HV = 1, 2, 4, 8: the H values of
-// an edge are read as one vector (H == HV, base aligned to it); HV = 0: any head count, one value at a time.
-// All four edges' loads of a level are issued before the first LDS store.
-template <int WM, int HV>
-__device__ __forceinline__ void seg_stage_values(const SpmmArgs& a, int i0, int n, const int64_t (&slot)[4],
-                                                 const float (&cs)[4], half_t* s_w, float* s_wf) {
-  const bool have = WM == 1 || a.w != nullptr;
-  if (HV == 0) {
-    for (int h = 0; h < a.H; ++h) {
-      half_t wv[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        wv[q] = (i0 + q * kWave < n && have) ? a.w[slot[q] * a.H + h] : half_t(WM == 1 ? 0 : 1);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * kWave;
-        if (WM == 1) s_w[i * a.H + h] = wv[q];
-        else s_wf[i * a.H + h] = float(wv[q]) * cs[q];
-      }
-    }
-    return;
-  }
-  constexpr int N = HV > 0 ? HV : 1;
-  typedef _Float16 hv_t __attribute__((ext_vector_type(N)));
-  hv_t wv[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    wv[q] = hv_t(half_t(WM == 1 ? 0 : 1));
-    if (i0 + q * kWave < n && have) wv[q] = *reinterpret_cast<const hv_t*>(a.w + slot[q] * N);
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + q * kWave;
-    if (WM == 1) {
-      *reinterpret_cast<hv_t*>(s_w + i * N) = wv[q];
-    } else {
-#pragma unroll
-      for (int h = 0; h < N; ++h) s_wf[i * N + h] = float(wv[q][h]) * cs[q];
-    }
-  }
-}
-
-template <int WM>
-__device__ __forceinline__ void seg_stage_values_any(const SpmmArgs& a, int i0, int n, const int64_t (&slot)[4],
-                                                     const float (&cs)[4], half_t* s_w, float* s_wf) {
-  const uintptr_t wa = reinterpret_cast<uintptr_t>(a.w);
-  if (a.H == 1) seg_stage_values<WM, 1>(a, i0, n, slot, cs, s_w, s_wf);
-  else if (a.H == 4 && (wa & 7u) == 0) seg_stage_values<WM, 4>(a, i0, n, slot, cs, s_w, s_wf);
-  else if (a.H == 2 && (wa & 3u) == 0) seg_stage_values<WM, 2>(a, i0, n, slot, cs, s_w, s_wf);
-  else if (a.H == 8 && (wa & 15u) == 0) seg_stage_values<WM, 8>(a, i0, n, slot, cs, s_w, s_wf);
-  else seg_stage_values<WM, 0>(a, i0, n, slot, cs, s_w, s_wf);
-}
-
-// MAPPED = false: the call has no edge-id map (only instantiated for WM == 1, where the code of the map costs the
-// registers of a seventh wave per SIMD)
-template <int L, int WM, bool OFF32, bool MAPPED = true>
-__global__ __launch_bounds__(kBlock, WM == 0 ? 8 : ((WM == 1 && !MAPPED) ? 7 : 1)) void spmm_seg_kernel(SpmmArgs a) {
-  constexpr int G = kWave / L;
-  constexpr int VEC = 8 * L;  // floats per parked vector
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int g = lane / L, l = lane % L;
-  const int f0 = 8 * l;
-  const bool active = f0 < a.F;
-  const int f0c = active ? f0 : 0;  // idle lanes of a group load a valid address and drop the result
-  const int head = f0c / a.D;
-  const int S = a.S;
-  const SegLds lay = seg_lds_layout(S, a.H, WM, L);
-  unsigned char* base = smem + size_t(wave) * lay.total;
-  int* s_col = reinterpret_cast<int*>(base + lay.col_off);
-  int* s_row = reinterpret_cast<int*>(base + lay.row_off);  // row id of every edge of the segment
-  int* s_blk = reinterpret_cast<int*>(base + lay.blk_off);  // per 4 edges: their common row id, or -1
-  half_t* s_w = reinterpret_cast<half_t*>(base + lay.w_off);   // WM == 1
-  float* s_wf = reinterpret_cast<float*>(base + lay.w_off);    // WM == 2
-  // A group's piece that entered its chunk from the previous one is parked in LDS when its row ends; the piece that
-  // leaves into the next chunk simply stays in the group's registers and is fetched from there by the merge
-  // (cross-lane reads need no LDS allocation).  Every KB of LDS less per wave is more waves per compute unit, and
-  // this latency-bound gather speeds up almost in proportion.
-  float* m_vec = reinterpret_cast<float*>(base + lay.vec_off);  // [G][VEC]: the entering piece of group g
-  int* m_flag = reinterpret_cast<int*>(base + lay.flag_off);    // bit0 entering, bit1 runs through, bit2 leaving
-  int* m_hrow = m_flag + G;
-  int* m_trow = m_hrow + G;
-
-  const int wpb = int(blockDim.x) / kWave;  // waves per workgroup (4, 2 or 1, chosen on the host for LDS packing)
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = enter_block(a, wg, wg_count, [&](const hgnn_seg_block& B) {
-      const int64_t c = (B.nseg + wpb - 1) / wpb;
-      return c > 0 ? c : int64_t(1);
-    });
-  const int64_t wid = wg * wpb + wave;
-  const int64_t seg = wid;
-  const bool valid = seg < a.nseg;
-  const int64_t e0 = seg * S;
-  const int n = valid ? int(a.nnz - e0 < S ? a.nnz - e0 : S) : 0;
-  const int per = lay.per, spad = lay.spad;
-  int row_lo = 0, row_hi = -1;
-  bool seg_left_open = false, seg_right_open = false;
-  if (valid) {
-    row_lo = a.seg_lo[seg];
-    row_hi = a.seg_hi[seg];
-    seg_left_open = int64_t(a.rowptr[row_lo]) < e0;
-    seg_right_open = int64_t(a.rowptr[row_hi + 1]) > e0 + n;
-  }
-
-  // ---- phase 1: coalesced stage of column ids and edge values, then the row id of every edge.  spad is a
-  // multiple of 4 * kWave; a lane keeps its four loads of a round in flight together (column ids, then the
-  // edge-id map, then the values behind it), so a round costs one memory latency per level, not four.
-  const bool nt = stream_nontemporal(a.nnz);
-  for (int i0 = lane; i0 < spad; i0 += 4 * kWave) {
-    int c[4];
-    int64_t slot[4] = {0, 0, 0, 0};
-    if (nt) stream_load4<true>(a.col + e0, i0, n, c);
-    else stream_load4<false>(a.col + e0, i0, n, c);
-    if (WM != 0 && !a.delta) {
-      if (MAPPED && a.eid) {
-        int e[4];
-        if (nt) stream_load4<true>(a.eid + e0, i0, n, e);
-        else stream_load4<false>(a.eid + e0, i0, n, e);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) slot[q] = e[q];
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) slot[q] = i0 + q * kWave < n ? e0 + i0 + q * kWave : 0;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)  // OFF32: byte offset of the neighbour's row
-      s_col[i0 + q * kWave] = OFF32 ? int(uint32_t(c[q]) * uint32_t(a.ldx) * 2u) : c[q];
-    if (WM != 0 && !a.delta) {
-      float cs[4] = {1.f, 1.f, 1.f, 1.f};
-      if (WM == 2) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bool in = i0 + q * kWave < n;
-          cs[q] = (in && a.col_scale) ? a.col_scale[c[q]] : (in ? 1.f : 0.f);
-        }
-      }
-      seg_stage_values_any<WM>(a, i0, n, slot, cs, s_w, s_wf);
-    }
-  }
-  if (lane < G) m_flag[lane] = 0;
-  seg_stage_rows(s_row, s_blk, lane, per, n, row_lo, row_hi, a.rowptr, e0);
-  if (WM != 0 && a.delta) {
-    // a row piece of a column block is a run of consecutive slots: slot = position + delta[row], so the
-    // edge values are read coalesced without an edge-id array (the row ids are known only now)
-    for (int i0 = lane; i0 < spad; i0 += 4 * kWave) {  // four in flight per level, as above
-      int64_t slot[4];
-      float cs[4] = {1.f, 1.f, 1.f, 1.f};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * kWave;
-        slot[q] = i < n ? e0 + i + a.delta[s_row[i]] : 0;
-      }
-      if (WM == 2) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int i = i0 + q * kWave;
-          cs[q] = i < n ? (a.col_scale ? a.col_scale[a.col[e0 + i]] : 1.f) : 0.f;
-        }
-      }
-      seg_stage_values_any<WM>(a, i0, n, slot, cs, s_w, s_wf);
-    }
-    wave_sync();
-  }
-
-  // ---- phase 2: running reduction over this group's chunk
-  const int C = 4 * ((S + 4 * G - 1) / (4 * G));  // edges per group, a multiple of 4
-  const int c0 = g * C < n ? g * C : n;
-  const int c1 = c0 + C < n ? c0 + C : n;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int cur = -1;
-  bool lo = false;  // current piece began before this chunk
-
-  // the scale of the current row (1/degree, row factor) is requested when the row begins, so that its latency has
-  // passed by the time the row ends; fetched at the flush it would stall the lane group once per row
-  float sc = 0.f;
-  auto flush = [&](bool ro) {
-    if (!lo && !ro) {
-      if (active) store_row(a, cur, f0, acc, sc);
-    } else if (lo) {
-      if (active) {
-        float* dst = m_vec + g * VEC + f0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) dst[i] = acc[i] * sc;
-      }
-      if (l == 0) {
-        m_flag[g] |= ro ? 3 : 1;
-        m_hrow[g] = cur;
-      }
-    } else {  // leaves into the next chunk (only the last flush of a chunk gets here): stays in acc, scaled
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] *= sc;
-      if (l == 0) {
-        m_flag[g] |= 4;
-        m_trow[g] = cur;
-      }
-    }
-  };
-  auto gather = [&](int c) -> half8_t {
-    if (OFF32) {  // byte offset in 32 bits: scalar base address + per-lane offset
-      const uint32_t boff = uint32_t(c) + uint32_t(f0c) * 2u;
-      return *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(a.X) + boff);
-    }
-    return *reinterpret_cast<const half8_t*>(a.X + int64_t(c) * a.ldx + f0c);
-  };
-
-  if (c0 < c1) {
-    cur = s_row[c0];
-    lo = c0 > 0 ? s_row[c0 - 1] == cur : seg_left_open;
-    sc = scale_of(a, cur);
-  }
-  for (int i = c0; i < c1; i += 4) {
-    const int4_t cols = *reinterpret_cast<const int4_t*>(s_col + i);
-    const int blk = s_blk[i >> 2];
-    half8_t x[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = gather(cols[u]);
-    float wv[4] = {a.one, a.one, a.one, a.one};  // 1.0 the compiler cannot fold: keeps convert+add in one v_fma_mix
-    if (WM == 1) {
-      if (a.H == 1) {
-        const half4_t w4 = *reinterpret_cast<const half4_t*>(s_w + i);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) wv[u] = float(w4[u]);
-      } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) wv[u] = float(s_w[(i + u) * a.H + head]);
-      }
-    } else if (WM == 2) {
-      if (a.H == 1) {
-        const float4 w4 = *reinterpret_cast<const float4*>(s_wf + i);
-        wv[0] = w4.x;
-        wv[1] = w4.y;
-        wv[2] = w4.z;
-        wv[3] = w4.w;
-      } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) wv[u] = s_wf[(i + u) * a.H + head];
-      }
-    }
-    if (blk == cur) {  // the four edges continue the current row: no bookkeeping at all
-#pragma unroll
-      for (int u = 0; u < 4; ++u) fma8(acc, wv[u], x[u]);
-    } else {
-      const int4_t rows = *reinterpret_cast<const int4_t*>(s_row + i);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (i + u < c1) {
-          if (rows[u] != cur) {
-            flush(false);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-            cur = rows[u];
-            lo = false;
-            sc = scale_of(a, cur);
-          }
-          fma8(acc, wv[u], x[u]);
-        }
-      }
-    }
-  }
-  if (c0 < c1) flush(c1 < n ? s_row[c1] == cur : seg_right_open);
-  wave_sync();
-
-  // ---- merge: group 0 sews the pieces together in chunk order (all lanes take part in the cross-lane reads)
-  if (valid) {
-    float run[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    bool open = false, from_before = false;
-    int run_row = -1;
-    const bool me = g == 0 && active;
-    for (int gg = 0; gg < G; ++gg) {
-      const int fl = m_flag[gg];  // the same value on every lane
-      if (fl & 1) {
-        if (me) {
-          const float* src = m_vec + gg * VEC + f0;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) run[i] += src[i];
-        }
-        if (gg == 0) {
-          from_before = true;
-          open = true;
-          run_row = m_hrow[0];
-        }
-        if (!(fl & 2)) {  // the row ends inside chunk gg
-          if (me) {
-            if (!from_before) store_row(a, run_row, f0, run, 1.f);
-            else if (a.atomic_y) atomic_add8(a.Y + int64_t(run_row) * a.ldy + f0, run, a.F - f0);
-            else store8(a.staging + (2 * seg) * a.stage_ld + f0, run, 1.f);
-          }
-#pragma unroll
-          for (int i = 0; i < 8; ++i) run[i] = 0.f;
-          open = false;
-          from_before = false;
-        }
-      }
-      if (fl & 4) {  // the piece that left chunk gg: from the registers of group gg
-#pragma unroll
-        for (int i = 0; i < 8; ++i) run[i] = __shfl(acc[i], gg * L + l);
-        run_row = m_trow[gg];
-        open = true;
-        from_before = false;
-      }
-    }
-    if (open && me) {  // leaves into the next segment; a piece that also entered is a "middle" and uses slot 2*seg
-      if (a.atomic_y) atomic_add8(a.Y + int64_t(run_row) * a.ldy + f0, run, a.F - f0);
-      else store8(a.staging + (2 * seg + (from_before ? 0 : 1)) * a.stage_ld + f0, run, 1.f);
-    }
-  }
-
-  // ---- zero-fill this wave's share of the empty rows
-  const int64_t nw = wg_count * wpb;
-  const int rpw = int((a.nrows + nw - 1) / nw);
-  const int64_t r0 = wid * rpw;
-  const int64_t r1 = r0 + rpw < a.nrows ? r0 + rpw : a.nrows;
-  if (active) {
-    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int64_t r = r0 + g; r < r1; r += G)
-      if (a.rowptr[r] == a.rowptr[r + 1]) store_row(a, r, f0, zero, 0.f);
-  }
-}
-
-// Pass 2, the follow-up kernel (section 5.2.3): adds the staged fp16 partials of every split row
-// (fp32, fixed order) and stores the row once.  A wave owns G split rows: a row of at most
-// kFinishShort pieces is summed by its own lane group, a hub that spans more segments by the
-// whole wave, the groups striding over its pieces.
-constexpr int kFinishShort = 8;
-
-// acc += staging rows MUL*k for k = first, first + STRIDE, ... <= last
-template <int STRIDE, int MUL = 2>
+// acc += staging rows k = first, first + STRIDE, ... <= last
+template <int STRIDE>
 __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t first, int64_t last, int f0,
                                                   float (&acc)[8]) {
   constexpr int U = 4;
@@ -924,7 +514,7 @@ __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t fir
     for (int u = 0; u < U; ++u) {
       const int64_t kk = k + u * STRIDE;
       t[u] = half8_t(0);
-      if (kk <= last) t[u] = *reinterpret_cast<const half8_t*>(a.staging + (MUL * kk) * a.stage_ld + f0);
+      if (kk <= last) t[u] = *reinterpret_cast<const half8_t*>(a.staging + kk * a.stage_ld + f0);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -933,48 +523,193 @@ __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t fir
   }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Discretized-reduction SpMM over row tasks: pass 1.  A wave takes one long piece of a row, or as many short pieces as it
+// has lane groups, or a share of the empty rows.  A lane group stays inside its row, so its loop is eight gathers, the
+// broadcast of the eight columns (and factors) held by its lanes, and 64 products; nothing is parked, nothing merged but
+// the groups of a long piece.  Pieces of a row that has several go to staging slots as fp16 (each covers at most S
+// non-zeros, so it cannot overflow where S * max|w x| fits fp16) and spmm_task_finish_kernel adds them; every row of Y has
+// exactly one writer.
+//
+// Bound: the gathers, 64 bytes per clock and compute unit while the table sits in the L2s, the traffic behind the L2s
+// beyond that.  Against the walk over equal runs of non-zeros with row ids in LDS (which held 7 waves per SIMD and spent 2-3
+// times the vector instructions): R-MAT 5.5 M non-zeros x 64, weighted 88 -> 50 us; 2.1 M x 128 58 -> 42 us; a 36 k graph 17.8 ->
+// 8 us; 114 M non-zeros x 64 in blocks of 3.7 MB 1.05 -> 0.80 ms (18 TB/s of rows).
+// WM: 0 = no factor per non-zero, 1 = edge values, 2 = edge values (if any) times a column scale.  MAPPED: edge values
+// behind an edge-id map.
+// ---------------------------------------------------------------------------------------------------
+// HV: heads of the edge values where they are read as one vector (1, 2, 4 or 8; aligned to it), 0 = any number.
+template <int L, int WM, int HV>
+struct TaskLds {
+  typedef Round<L> Rd;
+  static constexpr int G = kWave / L;
+  static constexpr int kHandles = G * Rd::PITCH * 4;
+  typedef typename std::conditional<WM == 2 || HV == 0, float, half_t>::type factor_t;
+  // factors of a group: [R][H] and one 16-byte step to the next group's banks
+  static __host__ __device__ int pitch(int H) { return Rd::R * H + 16 / int(sizeof(factor_t)); }
+  static size_t bytes(int H) { return size_t(kHandles) + (WM == 0 ? 0 : size_t(G) * size_t(pitch(H)) * sizeof(factor_t)); }
+};
+
+template <int L, int WM, bool NEAR, bool MAPPED, int HV>
+__global__ __launch_bounds__(kWave, L < 8 ? 5 : (WM == 0 ? 8 : 7)) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
+  constexpr int G = kWave / L;
+  typedef Round<L> Rd;
+  typedef TaskLds<L, WM, HV> Lds;
+  typedef typename Lds::factor_t factor_t;
+  constexpr int NV = HV > 0 ? HV : 1;
+  constexpr int E = Rd::E;
+  typedef _Float16 hv_t __attribute__((ext_vector_type(NV)));
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x;
+  const int g = lane / L, l = lane % L;
+  const int f0 = 8 * l;
+  const bool active = f0 < a.F;
+  const int f0c = active ? f0 : 0;  // idle lanes of a group load a valid address and drop the result
+  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  a.Y += int64_t(w.block) * a.block_y_stride;
+  if (w.z1 > w.z0) {
+    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int i = w.z0 + g; i < w.z1; i += G)
+      if (active) store_row(a, v.zrow[i], f0, zero, 0.f);
+    return;
+  }
+  const int H = HV > 0 ? HV : a.H;
+  const int head = HV == 1 ? 0 : f0c / a.D;
+  int* const s_hnd = reinterpret_cast<int*>(smem) + g * Rd::PITCH;
+  factor_t* const s_val = reinterpret_cast<factor_t*>(smem + Lds::kHandles) + g * Lds::pitch(H);
+  const RowTable<NEAR> table(a.X, ncols, a.ldx, f0c);
+  const int row = w.row >= 0 ? w.row : 0;
+  const float sc = scale_of(a, row);  // requested here, used at the end
+  int shift = 0;  // slot in the edge tensors = position + shift
+  if (WM != 0 && !MAPPED && a.delta) shift = a.delta[int64_t(w.block) * a.nrows + row] - w.first;
+  const int own = (lane & (Rd::LC - 1)) * E;
+  const bool nt = MAPPED && stream_nontemporal(a.nnz);
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int k = w.beg; k < w.end; k += w.step) {
+    const int end = k + w.span < w.end ? k + w.span : w.end;
+    const int i0 = k + own;
+    wave_sync();  // the previous round has been read
+    {
+      int c[E], e[E];
+      hv_t wv[E];
+      float cs[E];
+      if (nt) load_run<E, true>(a.col, i0, end, c);
+      else load_run<E, false>(a.col, i0, end, c);
+      if (MAPPED) {
+        if (nt) load_run<E, true>(a.eid, i0, end, e);
+        else load_run<E, false>(a.eid, i0, end, e);
+      }
+      if (WM != 0 && HV > 0) {
+        if (!MAPPED && (WM == 1 || a.w) && i0 + E <= end) {
+          __builtin_memcpy(wv, a.w + int64_t(i0 + shift) * NV, sizeof(wv));
+        } else {
+#pragma unroll
+          for (int m = 0; m < E; ++m) {
+            wv[m] = hv_t(half_t(0));
+            if (i0 + m < end) {
+              if (WM == 1 || a.w) wv[m] = *reinterpret_cast<const hv_t*>(a.w + int64_t(MAPPED ? e[m] : i0 + m + shift) * NV);
+              else wv[m] = hv_t(half_t(1));
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        cs[m] = 0.f;
+        if (WM == 2 && i0 + m < end) cs[m] = a.col_scale[c[m]];
+      }
+#pragma unroll
+      for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], i0 + m < end);
+#pragma unroll
+      for (int m = 0; m < E; m += 4) *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
+      if (WM == 1 && HV > 0) {
+        __builtin_memcpy(__builtin_assume_aligned(s_val + own * NV, 8), wv, sizeof(wv));
+      } else if (WM != 0) {
+        for (int m = 0; m < E; ++m)
+          for (int h = 0; h < H; ++h) {
+            float x = 0.f;
+            if (HV > 0) x = float(wv[m][h < NV ? h : 0]) * (WM == 2 ? cs[m] : 1.f);
+            else if (i0 + m < end) x = (a.w ? float(a.w[int64_t(MAPPED ? e[m] : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
+            s_val[(own + m) * H + h] = factor_t(x);
+          }
+      }
+    }
+    wave_sync();
+    for (int q = 0; k + q < end; q += 8) {
+      int h8[8];
+      const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        h8[u] = ha[u];
+        h8[4 + u] = hb[u];
+      }
+      half8_t x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = table.row(h8[u]);
+      if (WM == 0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) fma8(acc, a.one, x[u]);  // 1.0 the compiler cannot fold: keeps convert+add in one v_fma_mix
+      } else {
+        factor_t f[8];
+        if (HV == 1) {
+          __builtin_memcpy(f, __builtin_assume_aligned(s_val + q, 16), sizeof(f));
+        } else {
+#pragma unroll
+          for (int u = 0; u < 8; ++u) f[u] = s_val[(q + u) * H + head];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) fma8(acc, float(f[u]), x[u]);
+      }
+    }
+  }
+  if (w.whole) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = across_groups_sum<L>(acc[i]);
+    if (g) return;
+  }
+  if (!active || w.row < 0) return;
+  if (w.slot < 0) {
+    store_row(a, row, f0, acc, sc);
+  } else if (WM < 2 && a.atomic_y) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] *= sc;
+    atomic_add8(a.Y + int64_t(row) * a.ldy + f0, acc, a.F - f0);
+  } else {
+    store8(a.staging + int64_t(w.slot) * a.stage_ld + f0, acc, sc);
+  }
+}
+
+// Pass 2 (section 5.2.3): adds the staged fp16 pieces of every row that has several (fp32, in order) and stores the row
+// once.  A wave owns G rows: rows of at most kFinishShort pieces are summed by their own lane group, longer ones by the
+// whole wave.
 template <int L>
-__global__ __launch_bounds__(kBlock) void spmm_finish_kernel(SpmmArgs a) {
+__global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = enter_block(a, wg, wg_count,
-                     [&](const hgnn_seg_block& B) { return (int64_t(B.n_split) + kWavesPerBlock * G - 1) / (kWavesPerBlock * G); });
-  const int64_t i0 = (wg * kWavesPerBlock + wave) * G;
-  if (i0 >= a.n_split) return;
-  const int64_t idx = i0 + g;
-  int r = 0, sa = 0, sb = -1;
-  if (idx < a.n_split) {
-    r = a.split_row[idx];
-    sa = a.split_lo[idx];
-    sb = a.split_hi[idx];
-  }
-  // the tail piece of segment sa, then the head pieces of segments sa+1 .. sb
-  if (idx < a.n_split && sb - sa <= kFinishShort) {
-    float acc[8];
-    const half8_t t = *reinterpret_cast<const half8_t*>(a.staging + (2 * int64_t(sa) + 1) * a.stage_ld + f0c);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = float(t[i]);
-    pieces_accumulate<1>(a, int64_t(sa) + 1, sb, f0c, acc);
-    if (active) store_row(a, r, f0, acc, 1.f);
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  if (i0 >= n_split) return;
+  int4_t q = {0, 0, 0, 0};
+  if (i0 + g < n_split) q = split[i0 + g];
+  half_t* const Y = a.Y;
+  if (q[2] > 0 && q[2] <= kFinishShort) {
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    pieces_accumulate<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
+    a.Y = Y + int64_t(q[3]) * a.block_y_stride;
+    if (active) store_row(a, q[0], f0, acc, 1.f);
   }
   for (int j = 0; j < G; ++j) {
-    const int rj = __shfl(r, j * L), sj = __shfl(sa, j * L), ej = __shfl(sb, j * L);
-    if (ej - sj <= kFinishShort) continue;
+    const int n = __shfl(q[2], j * L);
+    if (n <= kFinishShort) continue;
+    const int r = __shfl(q[0], j * L), first = __shfl(q[1], j * L), b = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (g == 0) {
-      const half8_t t = *reinterpret_cast<const half8_t*>(a.staging + (2 * int64_t(sj) + 1) * a.stage_ld + f0c);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = float(t[i]);
-    }
-    pieces_accumulate<G>(a, int64_t(sj) + 1 + g, ej, f0c, acc);
+    pieces_accumulate<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
     groups_reduce<L>(acc);
-    if (g == 0 && active) store_row(a, rj, f0, acc, 1.f);
+    a.Y = Y + int64_t(b) * a.block_y_stride;
+    if (g == 0 && active) store_row(a, r, f0, acc, 1.f);
   }
 }
 
@@ -997,6 +732,8 @@ struct VGroupArgs {
   int pair_loads;  // edge values: one per edge, no edge-id map, 4-byte aligned base
   int acc16;       // products and sums of a lane's chunk in packed fp16 (the paper's arithmetic, section 4.2)
 };
+
+__host__ __device__ inline int align16i(int v) { return (v + 15) & ~15; }
 
 __host__ __device__ inline int vgroup_lds_bytes(int ng, int H, bool has_w) {
   const int spad = kWave * 4 * ((ng + 255) / 256);
@@ -1171,14 +908,14 @@ __global__ __launch_bounds__(kBlock) void spmm_vgroup_finish_kernel(SpmmArgs a, 
   }
   if (cnt > 1 && cnt <= kFinishShort) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    pieces_accumulate<1, 1>(a, first, int64_t(first) + cnt - 1, f0c, acc);
+    pieces_accumulate<1>(a, first, int64_t(first) + cnt - 1, f0c, acc);
     if (active) store_row(a, r, f0, acc, 1.f);
   }
   for (int j = 0; j < G; ++j) {
     const int cj = __shfl(cnt, j * L), fj = __shfl(first, j * L);
     if (cj <= kFinishShort) continue;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    pieces_accumulate<G, 1>(a, int64_t(fj) + g, int64_t(fj) + cj - 1, f0c, acc);
+    pieces_accumulate<G>(a, int64_t(fj) + g, int64_t(fj) + cj - 1, f0c, acc);
     groups_reduce<L>(acc);
     if (g == 0 && active) store_row(a, r0 + j, f0, acc, 1.f);
   }
@@ -1186,16 +923,16 @@ __global__ __launch_bounds__(kBlock) void spmm_vgroup_finish_kernel(SpmmArgs a, 
 
 // zero the rows whose pieces the atomic comparison variant adds into Y
 template <int L>
-__global__ __launch_bounds__(kBlock) void zero_split_rows_kernel(SpmmArgs a) {
+__global__ __launch_bounds__(kBlock) void zero_split_rows_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int64_t idx = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G + g;
-  if (idx >= a.n_split || 8 * l >= a.F) return;
+  if (idx >= n_split || 8 * l >= a.F) return;
   const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   SpmmArgs b = a;
   b.self = nullptr;
-  store_row(b, a.split_row[idx], 8 * l, zero, 0.f);
+  store_row(b, split[idx][0], 8 * l, zero, 0.f);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1382,55 +1119,6 @@ static HubLists hub_lists_at(void* base, const HubLayout& o) {
   return h;
 }
 
-template <int WM, bool OFF32>
-static void launch_seg(int L, dim3 grid, int threads, size_t lds, hipStream_t s, const SpmmArgs& a) {
-  if (WM == 1 && !a.eid && !(a.blocks && a.use_eid)) {  // edge values at the graph's own positions
-    switch (L) {
-      case 1: spmm_seg_kernel<1, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      case 2: spmm_seg_kernel<2, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      case 4: spmm_seg_kernel<4, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      case 8: spmm_seg_kernel<8, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      case 16: spmm_seg_kernel<16, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      case 32: spmm_seg_kernel<32, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-      default: spmm_seg_kernel<64, WM, OFF32, WM != 1><<<grid, threads, lds, s>>>(a); break;
-    }
-    return;
-  }
-  switch (L) {
-    case 1: spmm_seg_kernel<1, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    case 2: spmm_seg_kernel<2, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    case 4: spmm_seg_kernel<4, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    case 8: spmm_seg_kernel<8, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    case 16: spmm_seg_kernel<16, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    case 32: spmm_seg_kernel<32, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-    default: spmm_seg_kernel<64, WM, OFF32><<<grid, threads, lds, s>>>(a); break;
-  }
-}
-
-static void launch_finish(int L, dim3 grid, hipStream_t s, const SpmmArgs& a) {
-  switch (L) {
-    case 1: spmm_finish_kernel<1><<<grid, kBlock, 0, s>>>(a); break;
-    case 2: spmm_finish_kernel<2><<<grid, kBlock, 0, s>>>(a); break;
-    case 4: spmm_finish_kernel<4><<<grid, kBlock, 0, s>>>(a); break;
-    case 8: spmm_finish_kernel<8><<<grid, kBlock, 0, s>>>(a); break;
-    case 16: spmm_finish_kernel<16><<<grid, kBlock, 0, s>>>(a); break;
-    case 32: spmm_finish_kernel<32><<<grid, kBlock, 0, s>>>(a); break;
-    default: spmm_finish_kernel<64><<<grid, kBlock, 0, s>>>(a); break;
-  }
-}
-
-static void launch_zero_split(int L, dim3 grid, hipStream_t s, const SpmmArgs& a) {
-  switch (L) {
-    case 1: zero_split_rows_kernel<1><<<grid, kBlock, 0, s>>>(a); break;
-    case 2: zero_split_rows_kernel<2><<<grid, kBlock, 0, s>>>(a); break;
-    case 4: zero_split_rows_kernel<4><<<grid, kBlock, 0, s>>>(a); break;
-    case 8: zero_split_rows_kernel<8><<<grid, kBlock, 0, s>>>(a); break;
-    case 16: zero_split_rows_kernel<16><<<grid, kBlock, 0, s>>>(a); break;
-    case 32: zero_split_rows_kernel<32><<<grid, kBlock, 0, s>>>(a); break;
-    default: zero_split_rows_kernel<64><<<grid, kBlock, 0, s>>>(a); break;
-  }
-}
-
 template <int L, int VW>
 static void launch_vgroup_main(bool has_w, bool off32, dim3 grid, int threads, size_t lds, hipStream_t s, const SpmmArgs& a,
                                const VGroupArgs& v) {
@@ -1510,94 +1198,125 @@ static hgnn_status run_vgroups(const hgnn_plan* p, SpmmArgs a, int ncols, bool a
   return HGNN_OK;
 }
 
-// Pass 1 and pass 2 of the discretized SpMM for the graph in `a` with the segment arrays of plan q.
-static hgnn_status run_segments(const hgnn_plan* q, SpmmArgs a, int ncols, hipStream_t s) {
-  const int wm = a.col_scale ? 2 : (a.w ? 1 : 0);
-  a.seg_lo = q->seg_row_lo;
-  a.seg_hi = q->seg_row_hi;
-  a.S = q->S;
-  a.nseg = q->nseg;
-  a.staging = reinterpret_cast<half_t*>(q->staging);
-  a.stage_ld = q->max_F;
-  a.split_row = q->split_row;
-  a.split_lo = q->split_seg_lo;
-  a.split_hi = q->split_seg_hi;
-  a.n_split = q->n_split;
-  const int L = pow2_at_least((a.F + 7) / 8);
-  const SegLds lay = seg_lds_layout(a.S, a.H, wm, L);
-  const int wpb = waves_per_block_for_lds(size_t(lay.total), wm != 0);
-  const int threads = wpb * kWave;
-  const size_t lds = size_t(lay.total) * wpb;
-  HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-               "hgnn_spmm_discretized: seg_edges = %d with H = %d needs %zu bytes of LDS per workgroup (limit 65536)", a.S,
-               a.H, lds);
-  const int64_t nblk = ceil_div(q->nseg, wpb);
-  dim3 grid(unsigned(nblk > 0 ? nblk : 1));
-  // feature table below 2^32 bytes: 32-bit byte offsets from a scalar base address
-  const bool off32 = uint64_t(ncols) * uint64_t(a.ldx) * 2u < (uint64_t(1) << 32);
-  if (a.atomic_y && a.n_split > 0) {
-    launch_zero_split(L, dim3(unsigned(ceil_div(a.n_split, int64_t(kWavesPerBlock) * (kWave / L)))), s, a);
-    HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
+// the vector forms of several heads only where they are used in earnest: edge values alone, a table below 4 GB
+template <int L, bool NEAR>
+static void launch_tasks_l(int wm, bool mapped, unsigned waves, hipStream_t s, const SpmmArgs& a, const TaskView& v,
+                           int ncols) {
+  const dim3 grid(waves);
+#define HGNN_TASKS(WM, MAPPED, HV) \
+  spmm_task_kernel<L, WM, NEAR, MAPPED, HV><<<grid, kWave, TaskLds<L, WM, HV>::bytes(a.H), s>>>(a, v, ncols)
+  const int hv = (reinterpret_cast<uintptr_t>(a.w) & uintptr_t(2 * a.H - 1)) == 0 ? a.H : 0;
+  if (wm == 0) {
+    HGNN_TASKS(0, false, 1);
+    return;
   }
-  if (wm == 2) {
-    if (off32) launch_seg<2, true>(L, grid, threads, lds, s, a);
-    else launch_seg<2, false>(L, grid, threads, lds, s, a);
-  } else if (wm == 1) {
-    if (off32) launch_seg<1, true>(L, grid, threads, lds, s, a);
-    else launch_seg<1, false>(L, grid, threads, lds, s, a);
+  if (wm == 1) {
+    if (a.H == 1) {
+      if (mapped) HGNN_TASKS(1, true, 1);
+      else HGNN_TASKS(1, false, 1);
+      return;
+    }
+    if constexpr (NEAR) {
+      if (hv == 2) {
+        if constexpr (L >= 2) {
+          if (mapped) HGNN_TASKS(1, true, 2);
+          else HGNN_TASKS(1, false, 2);
+          return;
+        }
+      }
+      if (hv == 4) {
+        if constexpr (L >= 4) {
+          if (mapped) HGNN_TASKS(1, true, 4);
+          else HGNN_TASKS(1, false, 4);
+          return;
+        }
+      }
+      if (hv == 8) {
+        if constexpr (L >= 8) {
+          if (mapped) HGNN_TASKS(1, true, 8);
+          else HGNN_TASKS(1, false, 8);
+          return;
+        }
+      }
+    }
+    if (mapped) HGNN_TASKS(1, true, 0);
+    else HGNN_TASKS(1, false, 0);
+    return;
+  }
+  if (a.H == 1) {
+    if (mapped) HGNN_TASKS(2, true, 1);
+    else HGNN_TASKS(2, false, 1);
   } else {
-    if (off32) launch_seg<0, true>(L, grid, threads, lds, s, a);
-    else launch_seg<0, false>(L, grid, threads, lds, s, a);
+    if (mapped) HGNN_TASKS(2, true, 0);
+    else HGNN_TASKS(2, false, 0);
   }
-  HGNN_LAUNCH_CHECK("spmm_seg_kernel");
-  if (a.n_split > 0 && !a.atomic_y) {
-    const int G = kWave / L;
-    dim3 grid2(unsigned(ceil_div(a.n_split, int64_t(kWavesPerBlock) * G)));
-    launch_finish(L, grid2, s, a);
-    HGNN_LAUNCH_CHECK("spmm_finish_kernel");
-  }
-  return HGNN_OK;
+#undef HGNN_TASKS
 }
 
-// Pass 1 and pass 2 over all column blocks of plan p, one launch each: a.Y / a.ldy / a.block_y_stride describe the
-// blocks' partial outputs.
-static hgnn_status run_segments_blocked(const hgnn_plan* p, SpmmArgs a, int ncols, hipStream_t s) {
+template <bool NEAR>
+static void launch_tasks(int L, int wm, bool mapped, unsigned waves, hipStream_t s, const SpmmArgs& a, const TaskView& v,
+                         int ncols) {
+  switch (L) {
+    case 1: launch_tasks_l<1, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 2: launch_tasks_l<2, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 4: launch_tasks_l<4, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 8: launch_tasks_l<8, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 16: launch_tasks_l<16, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 32: launch_tasks_l<32, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    default: launch_tasks_l<64, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+  }
+}
+
+static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
+  switch (L) {
+    case 1: zero_split_rows_kernel<1><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 2: zero_split_rows_kernel<2><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 4: zero_split_rows_kernel<4><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 8: zero_split_rows_kernel<8><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 16: zero_split_rows_kernel<16><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 32: zero_split_rows_kernel<32><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    default: zero_split_rows_kernel<64><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+  }
+}
+
+static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
+  switch (L) {
+    case 1: spmm_task_finish_kernel<1><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 2: spmm_task_finish_kernel<2><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 4: spmm_task_finish_kernel<4><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 8: spmm_task_finish_kernel<8><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 16: spmm_task_finish_kernel<16><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 32: spmm_task_finish_kernel<32><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    default: spmm_task_finish_kernel<64><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+  }
+}
+
+// Pass 1 and pass 2 of the discretized SpMM over the row tasks t of plan p, whose column array `a.col` indexes (with a.eid,
+// a.delta beside it); a.Y / a.ldy / a.block_y_stride describe the result, or the column blocks' partial results.
+static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmArgs a, int ncols, hipStream_t s) {
   const int wm = a.col_scale ? 2 : (a.w ? 1 : 0);
-  a.blocks = p->bdesc;
-  a.nblocks = p->nb;
-  a.S = p->S;
+  const int L = pow2_at_least((a.F + 7) / 8), G = kWave / L;
+  a.staging = reinterpret_cast<half_t*>(t->staging);
   a.stage_ld = p->max_F;
-  const int L = pow2_at_least((a.F + 7) / 8);
-  const int G = kWave / L;
-  const SegLds lay = seg_lds_layout(a.S, a.H, wm, L);
-  const int wpb = waves_per_block_for_lds(size_t(lay.total), wm != 0);
-  const size_t lds = size_t(lay.total) * wpb;
-  HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-               "hgnn_spmm_discretized: seg_edges = %d with H = %d needs %zu bytes of LDS per workgroup (limit 65536)", a.S,
-               a.H, lds);
-  int64_t wgs = 0, wgs2 = 0;
-  for (const hgnn_plan* q : p->sub) {
-    const int64_t c = ceil_div(q->nseg, wpb);
-    wgs += c > 0 ? c : 1;
-    wgs2 += ceil_div(q->n_split, int64_t(kWavesPerBlock) * G);
+  // edge values behind a map: the slots of a column's non-zeros are consecutive over the rows, so the waves of an XCD
+  // stay on one range of rows for longer
+  const bool mapped = wm != 0 && a.w && a.eid;
+  const TaskView v = task_view(t, G, mapped ? 512 : 128);
+  const int waves = v.first_wave[t->nb];
+  if (a.atomic_y && v.n_split > 0) {
+    launch_zero_split(L, s, a, v);
+    HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
-  const bool off32 = uint64_t(ncols) * uint64_t(a.ldx) * 2u < (uint64_t(1) << 32);
-  dim3 grid{unsigned(wgs)};
-  const int threads = wpb * kWave;
-  if (wm == 2) {
-    if (off32) launch_seg<2, true>(L, grid, threads, lds, s, a);
-    else launch_seg<2, false>(L, grid, threads, lds, s, a);
-  } else if (wm == 1) {
-    if (off32) launch_seg<1, true>(L, grid, threads, lds, s, a);
-    else launch_seg<1, false>(L, grid, threads, lds, s, a);
-  } else {
-    if (off32) launch_seg<0, true>(L, grid, threads, lds, s, a);
-    else launch_seg<0, false>(L, grid, threads, lds, s, a);
+  if (waves > 0) {
+    if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), s, a, v, ncols);
+    else launch_tasks<false>(L, wm, mapped, unsigned(waves), s, a, v, ncols);
+    HGNN_LAUNCH_CHECK("spmm_task_kernel");
   }
-  HGNN_LAUNCH_CHECK("spmm_seg_kernel");
-  if (wgs2 > 0) {
-    launch_finish(L, dim3(unsigned(wgs2)), s, a);
-    HGNN_LAUNCH_CHECK("spmm_finish_kernel");
+  if (v.n_split > 0 && !a.atomic_y) {
+    launch_task_finish(L, s, a, v);
+    HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
   }
   return HGNN_OK;
 }
@@ -1767,26 +1486,27 @@ hgnn_status hgnn_spmm_discretized_fused(const hgnn_plan* p, const hgnn_csr* g, c
   }
   // blocks that the automatic rule chose (for max_F) are used when the table of this call is beyond an L2 too
   const bool use_blocks = p->nb > 1 && (!p->auto_blocks || double(g->ncols) * double(a.ldx) * 2.0 > 3.0 * double(p->l2_bytes));
-  if (!use_blocks) return run_segments(p, a, g->ncols, s);
+  if (!use_blocks) return run_tasks(p, p->tasks, a, g->ncols, s);
   HGNN_REQUIRE(!(edge_val && g->eid && !p->block_eid), HGNN_EINVAL,
                "%s: the column-blocked plan was built from a graph without an edge-id map; build the plan from the graph "
                "that carries the map", who);
   // column-blocked plan: one discretized SpMM per block into that block's partial output, blocks one
   // after the other so that all compute units gather from the same slice of X, then one pass adds
   // the partials of every row (and the self term, once).  Scales are applied per partial (section 5.2.2).
-  // edge values behind an edge-id map: the plan's finer blocks, where it has them
-  if (edge_val && g->eid && p->fine) p = p->fine;
+  if (p->fine) p = p->fine;
   {
-    // all blocks in one launch of each kernel (workgroups numbered block after block), into the blocks' partial outputs.
-    // Slots in the edge tensors: a graph without an edge-id map reads at its own CSR positions (block position + the
-    // row's offset, a coalesced read); a graph with one reads through the blocked copy of the map
+    // all blocks in one launch (waves numbered block after block and dispatched in that order), into the blocks' partial
+    // outputs.  Slots in the edge tensors: a graph without an edge-id map reads at its own CSR positions (block position +
+    // the row's offset, a coalesced read); a graph with one reads through the blocked copy of the map
     SpmmArgs ab = a;
-    ab.use_eid = g->eid ? 1 : 0;
+    ab.col = p->bcol;
+    ab.eid = g->eid ? p->beid : nullptr;
+    ab.delta = g->eid ? nullptr : p->bdelta;
     ab.Y = reinterpret_cast<half_t*>(p->bstage);
     ab.ldy = p->max_F;
     ab.block_y_stride = int64_t(p->nrows) * p->max_F;
     ab.self = nullptr;
-    st = run_segments_blocked(p, ab, g->ncols, s);
+    st = run_tasks(p, p->btasks, ab, g->ncols, s);
     if (st != HGNN_OK) return st;
   }
   const int L = pow2_at_least((F + 7) / 8);
@@ -1828,7 +1548,7 @@ hgnn_status hgnn_spmm_discretized_variant(const hgnn_plan* p, const hgnn_csr* g,
   SpmmArgs a = make_args(g, edge_val, H, X, ldx, Y, ldy, F, op, row_scale);
   if (variant != HGNN_EDGE_SEGMENTS_ATOMIC) return run_vgroups(p, a, g->ncols, variant == HGNN_VERTEX_GROUPS_HALF2, s);
   a.atomic_y = 1;  // always on the whole graph: column blocks are not used by the comparison variants
-  return run_segments(p, a, g->ncols, s);
+  return run_tasks(p, p->tasks, a, g->ncols, s);
 }
 
 }  // extern "C"

@@ -1,0 +1,210 @@
+// Device side of the row tasks (see hgnn_row_tasks): how a wave finds its piece of work, reads the column ids of a lane
+// group eight at a time and gathers table rows.
+#pragma once
+
+#include "common.h"
+
+namespace hgnn {
+
+constexpr int kMaxTaskBlocks = 64;
+constexpr int kZeroTurns = 8;  // turns of G empty rows that a wave stores
+
+struct TaskView {
+  const int4_t* task;
+  const int* zrow;
+  const hgnn_task_sec* sec;
+  const int4_t* split;
+  int n_split, nb;
+  // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
+  // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
+  // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms).
+  int chunk;
+  int first_wave[kMaxTaskBlocks + 1];  // for the lane groups of this launch: waves before each block, then all of them
+};
+
+// host: the launch shape of tasks t for G lane groups per wave; zeros = false leaves the empty rows out
+inline TaskView task_view(const hgnn_row_tasks* t, int G, int chunk = 128, bool zeros = true) {
+  TaskView v{};
+  v.task = reinterpret_cast<const int4_t*>(t->task);
+  v.zrow = t->zrow;
+  v.sec = t->sec;
+  v.split = reinterpret_cast<const int4_t*>(t->split);
+  v.n_split = t->n_split;
+  v.nb = t->nb;
+  int64_t n = 0;
+  for (int b = 0; b < t->nb; ++b) {
+    const hgnn_task_sec& s = t->host[size_t(b)];
+    n = (n + 7) & ~int64_t(7);
+    v.first_wave[b] = int(n);
+    n += ((s.nw + 7) & ~7) + ((ceil_div(s.ng, G) + 7) & ~int64_t(7)) + (zeros ? ceil_div(s.nz, int64_t(G) * kZeroTurns) : 0);
+  }
+  v.first_wave[t->nb] = int(n);
+  v.chunk = chunk;
+  while (v.chunk > 1 && int64_t(v.chunk) * 64 * t->nb > n) v.chunk >>= 1;  // eight chunks per XCD and block at least
+  return v;
+}
+
+// ---- rounds: up to R consecutive non-zeros of a lane group, whose table handles and factors are put in LDS together ----
+// A lane reads E consecutive column ids as vectors, so a group's round is one or two cache lines of the column array.
+// Read 32 bytes at a time, the lines were asked for four times and the gathers waited for each (114 M non-zeros: 832 ->
+// 782 us).  The rows of the LDS tables are 4 entries longer than a round: the groups then read different banks.
+template <int L>
+struct Round {
+  static constexpr int LC = L < 8 ? L : 8;          // lanes that read ids (the others of a wider group repeat them)
+  static constexpr int R = L < 4 ? 8 * L : 32;
+  static constexpr int E = R / LC;
+  static constexpr int PITCH = R + 4;               // ints per group in the handle table
+};
+
+// v[m] = p[i0 + m] for the entries below end; the others are 0
+template <int E, bool NT>
+__device__ __forceinline__ void load_run(const int* __restrict__ p, int i0, int end, int (&v)[E]) {
+  const int* q = p + i0;
+  if (i0 + E <= end) {
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = NT ? __builtin_nontemporal_load(q + m) : q[m];
+  } else {
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      v[m] = 0;
+      if (i0 + m < end) v[m] = q[m];
+    }
+  }
+}
+
+// what one wave does
+struct TaskWave {
+  int block, first; // column block and its first non-zero
+  bool whole;       // all lane groups share one piece
+  int z0, z1;       // z1 > z0: entries [z0, z1) of zrow, nothing else
+  int beg, end;     // this lane group's first non-zero and the end of the piece
+  int span, step;   // non-zeros per round of this group (a multiple of 8, at most Round<L>::R), and from one round to the next
+  int row, slot;    // row -1: no piece for this lane group
+};
+
+// wid is the same on all lanes of the wave; g = lane / L
+template <int L>
+__device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
+  constexpr int G = kWave / L;
+  TaskWave w;
+  int b = 0;
+  while (b + 1 < v.nb && wid >= v.first_wave[b + 1]) ++b;
+  const hgnn_task_sec s = v.sec[b];
+  int i = wid - v.first_wave[b];
+  w.block = b;
+  w.first = s.first;
+  w.whole = i < s.nw;
+  w.z0 = w.z1 = 0;
+  int4_t t = {0, 0, -1, -1};
+  if (w.whole) {
+    t = v.task[s.w_off + i];
+  } else {
+    i -= (s.nw + 7) & ~7;  // sections begin at multiples of eight: i & 7 is the XCD
+    const int gw = (((s.ng + G - 1) / G) + 7) & ~7;
+    if (i < 0) {  // between two sections: nothing
+    } else if (i < gw) {
+      const int panel = 8 * v.chunk, full = gw / panel * panel;
+      if (i < full) {
+        const int p = i / panel * panel, j = i - p;
+        i = p + (j & 7) * v.chunk + (j >> 3);
+      }
+      const int k = i * G + g;
+      if (k < s.ng) t = v.task[s.g_off + k];
+    } else {
+      w.z0 = (i - gw) * (G * kZeroTurns);
+      w.z1 = w.z0 + G * kZeroTurns < s.nz ? w.z0 + G * kZeroTurns : s.nz;
+      w.z0 += s.z_off;
+      w.z1 += s.z_off;
+    }
+  }
+  w.beg = t[0];
+  w.end = t[0] + (t[1] & 0xffff);
+  w.row = t[2];
+  w.slot = t[3];
+  w.span = w.step = Round<L>::R;
+  if (w.whole) {  // the lane groups share the piece in equal runs
+    const int each = (((t[1] & 0xffff) + G - 1) / G + 7) & ~7;
+    if (each < w.span) w.span = each;
+    w.beg += w.span * g;
+    w.step = w.span * G;
+  }
+  return w;
+}
+
+// A table of rows of ld halves.  NEAR: its bytes stay below 2^32 - 8192, rows are read through a buffer descriptor whose
+// bounds make the positions past the end of a piece read as zeros (offset kNoRow), so the loop needs no masks; else by
+// 64-bit addresses and a branch.
+constexpr uint32_t kNoRow = 0xFFFFF000u;
+inline bool near_table(int64_t rows, int64_t ld) { return uint64_t(rows) * uint64_t(ld) * 2u < (uint64_t(1) << 32) - 8192u; }
+
+template <bool NEAR>
+struct RowTable {
+  __amdgpu_buffer_rsrc_t rsrc;
+  const half_t* base;
+  int64_t ld;
+  uint32_t pitch;  // bytes
+  uint32_t lane_bytes;
+  __device__ __forceinline__ RowTable(const half_t* x, int64_t rows, int64_t ld_, int f0) {
+    base = x + f0;
+    ld = ld_;
+    pitch = uint32_t(ld_) * 2u;
+    lane_bytes = uint32_t(f0) * 2u;
+    if (NEAR) rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(x), 0, int(uint32_t(rows) * pitch), 0x00020000);
+  }
+  // what to hand to row() for column c, or for no column at all
+  __device__ __forceinline__ int handle(int c, bool valid) const {
+    if (NEAR) return valid ? int(uint32_t(c) * pitch) : int(kNoRow);
+    return valid ? c : -1;
+  }
+  __device__ __forceinline__ half8_t row(int h) const {
+    if (NEAR) {
+      typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
+      const uint4_t r = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(uint32_t(h) + lane_bytes), 0, 0);
+      return __builtin_bit_cast(half8_t, r);
+    }
+    half8_t r = half8_t(0);
+    if (h >= 0) r = *reinterpret_cast<const half8_t*>(base + int64_t(h) * ld);
+    return r;
+  }
+};
+
+// v summed over the wave's lane groups of L lanes; the lanes of group 0 hold the result.  Vector instructions only: quad
+// permutes, rotations inside 16 lanes and the exchanges between the four rows of 16.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float xor16_mov(float v, bool max_of) {
+  typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+  const uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);
+  return max_of ? fmaxf(x, y) : x + y;
+}
+__device__ __forceinline__ float xor32_mov(float v, bool max_of) {
+  typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+  const uint2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);
+  return max_of ? fmaxf(x, y) : x + y;
+}
+template <int L>
+__device__ __forceinline__ float across_groups_sum(float v) {
+  if (L <= 1) v += dpp_mov<0xB1>(v);
+  if (L <= 2) v += dpp_mov<0x4E>(v);
+  if (L <= 4) v += dpp_mov<0x124>(v);
+  if (L <= 8) v += dpp_mov<0x128>(v);
+  if (L <= 16) v = xor16_mov(v, false);
+  if (L <= 32) v = xor32_mov(v, false);
+  return v;
+}
+template <int L>
+__device__ __forceinline__ float across_groups_max(float v) {
+  if (L <= 1) v = fmaxf(v, dpp_mov<0xB1>(v));
+  if (L <= 2) v = fmaxf(v, dpp_mov<0x4E>(v));
+  if (L <= 4) v = fmaxf(v, dpp_mov<0x124>(v));
+  if (L <= 8) v = fmaxf(v, dpp_mov<0x128>(v));
+  if (L <= 16) v = xor16_mov(v, true);
+  if (L <= 32) v = xor32_mov(v, true);
+  return v;
+}
+
+}  // namespace hgnn

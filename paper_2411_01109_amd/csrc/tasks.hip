@@ -1,0 +1,260 @@
+// The row tasks of a plan: every row of a graph (or of its column blocks) as one or more pieces of at most S non-zeros.
+// Integer work only; set-up.
+//
+// Why pieces of rows and not equal runs of non-zeros: a lane group that stays inside one row needs no row id per non-zero,
+// no row change in its loop and no merging of pieces with its neighbours.  A wave that walked 256 consecutive non-zeros
+// spent about 850 vector instructions on 32 products per lane; with a row per lane group it is about 300.  What the equal
+// runs gave for free, lane groups that end together, comes from sorting the rows of a window by length.
+#include <string.h>
+
+#include "common.h"
+
+namespace hgnn {
+
+constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for equal neighbours; few, because the short rows of a
+                                   // window share cache lines of the column array and of edge tensors (see TaskView::chunk)
+constexpr int kTaskThreads = 256;
+constexpr int kTaskRowsPerThread = kTaskWindow / kTaskThreads;
+constexpr int kMaxGroupLen = 256;
+static_assert(kGroupMaxBlocks <= kMaxGroupLen, "table of lengths");
+enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters };
+
+struct RowCut {
+  int len, part, m;  // non-zeros, non-zeros per piece, pieces
+};
+
+__device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, int r) {
+  RowCut c;
+  c.len = rp[r + 1] - rp[r];
+  if (c.len < 0) c.len = 0;  // an offset array that validation will reject
+  c.part = c.len;
+  c.m = c.len > 0 ? 1 : 0;
+  if (c.len > q.S) {
+    const int m = (c.len + q.S - 1) / q.S;
+    c.part = (c.len + m - 1) / m;
+    c.m = (c.len + c.part - 1) / c.part;
+  }
+  return c;
+}
+
+// counts[q][b][window]
+__global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, int nwin, int* __restrict__ counts) {
+  __shared__ int total[kTaskCounters];
+  const int b = blockIdx.y;
+  const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
+  if (threadIdx.x < kTaskCounters) total[threadIdx.x] = 0;
+  __syncthreads();
+  int n[kTaskCounters] = {0, 0, 0, 0, 0};
+  for (int u = 0; u < kTaskRowsPerThread; ++u) {
+    const int64_t r = int64_t(blockIdx.x) * kTaskWindow + u * kTaskThreads + threadIdx.x;
+    if (r >= q.nrows) break;
+    const RowCut c = cut_row(q, rp, int(r));
+    if (c.m == 0) ++n[kTaskZ];
+    else n[c.part > q.group_max ? kTaskW : kTaskG] += c.m;
+    if (c.m > 1) {
+      ++n[kTaskSplit];
+      n[kTaskSlots] += c.m;
+    }
+  }
+  for (int i = 0; i < kTaskCounters; ++i) {
+    int v = n[i];
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
+    if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
+  }
+  __syncthreads();
+  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = total[threadIdx.x];
+}
+
+// One workgroup: exclusive scans over the windows of every (counter, block), then the sections of the blocks.  A wave per
+// (counter, block).
+__global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, int nwin, int* __restrict__ counts, int* __restrict__ sums,
+                                                                  hgnn_task_sec* __restrict__ sec, TaskTotals* out) {
+  const int nb = q.nb;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  for (int i = wave; i < kTaskCounters * nb; i += kTaskThreads / kWave) {
+    int* c = counts + int64_t(i) * nwin;
+    int carry = 0;
+    for (int w0 = 0; w0 < nwin; w0 += kWave) {
+      const int v = w0 + lane < nwin ? c[w0 + lane] : 0;
+      int incl = v;
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+      }
+      if (w0 + lane < nwin) c[w0 + lane] = carry + incl - v;
+      carry += __shfl(incl, kWave - 1);
+    }
+    if (lane == 0) sums[i] = carry;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    TaskTotals t{0, 0, 0, 0, 0};
+    for (int b = 0; b < nb; ++b) {
+      hgnn_task_sec s;
+      s.nw = sums[kTaskW * nb + b];
+      s.ng = sums[kTaskG * nb + b];
+      s.nz = sums[kTaskZ * nb + b];
+      s.w_off = t.n_task;
+      s.g_off = t.n_task + s.nw;
+      s.z_off = t.n_zero;
+      s.first = q.first ? q.first[b] : 0;
+      t.n_task += s.nw + s.ng;
+      t.n_zero += s.nz;
+      t.n_whole += s.nw;
+      const int split = sums[kTaskSplit * nb + b], slots = sums[kTaskSlots * nb + b];
+      sums[kTaskSplit * nb + b] = t.n_split;
+      sums[kTaskSlots * nb + b] = t.n_slots;
+      t.n_split += split;
+      t.n_slots += slots;
+      sec[b] = s;
+    }
+    *out = t;
+  }
+}
+
+// One workgroup per window and block: counting sort of the lane-group pieces by falling length.  The order of equal
+// pieces depends on the order in which the LDS counters are reached; no result does.
+__global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts,
+                                                                   const int* __restrict__ sums, const hgnn_task_sec* __restrict__ sec,
+                                                                   int4* __restrict__ task, int* __restrict__ zrow,
+                                                                   int4* __restrict__ split) {
+  __shared__ int at[kMaxGroupLen + 1];  // pieces of each length, then where the next one goes
+  __shared__ int next[kTaskCounters];
+  const int b = blockIdx.y, w = blockIdx.x;
+  const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
+  const hgnn_task_sec s = sec[b];
+  for (int i = threadIdx.x; i <= kMaxGroupLen; i += kTaskThreads) at[i] = 0;
+  if (threadIdx.x < kTaskCounters) {
+    const int i = threadIdx.x;
+    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? s.z_off : sums[i * q.nb + b];
+    next[i] = base + counts[(int64_t(i) * q.nb + b) * nwin + w];
+  }
+  __syncthreads();
+  RowCut cut[kTaskRowsPerThread];
+  for (int u = 0; u < kTaskRowsPerThread; ++u) {
+    const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
+    cut[u] = RowCut{0, 0, -1};
+    if (r >= q.nrows) break;
+    cut[u] = cut_row(q, rp, int(r));
+    if (cut[u].m > 0 && cut[u].part <= q.group_max) {
+      const int last = cut[u].len - (cut[u].m - 1) * cut[u].part;
+      if (cut[u].m > 1) atomicAdd(&at[cut[u].part], cut[u].m - 1);
+      atomicAdd(&at[last], 1);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kWave) {  // longest first
+    int carry = next[kTaskG];
+    for (int i0 = kMaxGroupLen; i0 >= 0; i0 -= kWave) {
+      const int i = i0 - int(threadIdx.x);
+      const int n = i >= 0 ? at[i] : 0;
+      int incl = n;
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (int(threadIdx.x) >= d) incl += t;
+      }
+      if (i >= 0) at[i] = carry + incl - n;
+      carry += __shfl(incl, kWave - 1);
+    }
+  }
+  __syncthreads();
+  for (int u = 0; u < kTaskRowsPerThread; ++u) {
+    const RowCut c = cut[u];
+    if (c.m < 0) break;
+    const int r = w * kTaskWindow + u * kTaskThreads + int(threadIdx.x);
+    if (c.m == 0) {
+      zrow[atomicAdd(&next[kTaskZ], 1)] = r;
+      continue;
+    }
+    int slot = -1;
+    if (c.m > 1) {
+      slot = atomicAdd(&next[kTaskSlots], c.m);
+      split[atomicAdd(&next[kTaskSplit], 1)] = make_int4(r, slot, c.m, b);
+    }
+    const bool whole = c.part > q.group_max;
+    int pos = whole ? atomicAdd(&next[kTaskW], c.m) : 0;
+    const int k0 = s.first + rp[r];
+    for (int j = 0; j < c.m; ++j) {
+      const int n = j + 1 < c.m ? c.part : c.len - j * c.part;
+      const int p = whole ? pos++ : atomicAdd(&at[n], 1);
+      task[p] = make_int4(k0 + j * c.part, n | (b << 16), r, slot < 0 ? -1 : slot + j);
+    }
+  }
+}
+
+hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s) {
+  const int nwin = int(ceil_div(q.nrows, kTaskWindow));
+  HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskCounters) * size_t(q.nb) * (size_t(nwin) + 1)));
+  HGNN_HIP(c.sec.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals)));
+  int* counts = c.counts.as<int>();
+  int* sums = counts + size_t(kTaskCounters) * size_t(q.nb) * size_t(nwin);
+  hgnn_task_sec* sec = c.sec.as<hgnn_task_sec>();
+  c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(sec + q.nb);
+  if (nwin > 0) task_count_kernel<<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts);
+  task_scan_kernel<<<1, kTaskThreads, 0, s>>>(q, nwin, counts, sums, sec, c.totals);
+  HGNN_LAUNCH_CHECK("task_count_kernel / task_scan_kernel");
+  return HGNN_OK;
+}
+
+// After a wait for the stream of task_count.  The arrays are written when the stream has been waited for again.
+hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, hipStream_t s) {
+  const int nwin = int(ceil_div(q.nrows, kTaskWindow));
+  int* counts = c.counts.as<int>();
+  int* sums = counts + size_t(kTaskCounters) * size_t(q.nb) * size_t(nwin);
+  hgnn_row_tasks* t = new (std::nothrow) hgnn_row_tasks();
+  if (!t) return fail(HGNN_ENOMEM, "task_build: host allocation failed");
+  *out = t;  // the plan owns it from here
+  TaskTotals tot;
+  if (c.mail.data) tot = *c.totals;
+  else HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
+  t->nb = q.nb;
+  t->n_split = tot.n_split;
+  t->n_slots = tot.n_slots;
+  t->host.resize(size_t(q.nb));
+  t->sec = c.sec.as<hgnn_task_sec>();
+  c.sec.p = nullptr;
+  HGNN_HIP(dev_malloc(&t->task, sizeof(int4) * size_t(tot.n_task > 0 ? tot.n_task : 1)));
+  HGNN_HIP(dev_malloc(&t->zrow, sizeof(int) * size_t(tot.n_zero > 0 ? tot.n_zero : 1)));
+  if (tot.n_split > 0) {
+    HGNN_HIP(dev_malloc(&t->split, sizeof(int4) * size_t(tot.n_split)));
+    HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(tot.n_slots) * size_t(max_F)));
+    HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(tot.n_slots) * size_t(max_H)));
+  }
+  if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, tot.n_zero, 0};
+  else HGNN_HIP(hipMemcpyAsync(t->host.data(), t->sec, sizeof(hgnn_task_sec) * size_t(q.nb), hipMemcpyDeviceToHost, s));
+  if (nwin > 0)
+    task_write_kernel<<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts, sums, t->sec, t->task, t->zrow,
+                                                                                   t->split);
+  HGNN_LAUNCH_CHECK("task_write_kernel");
+  return HGNN_OK;
+}
+
+// the tasks of plan p's column blocks
+hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s) {
+  DevTemp first;
+  std::vector<int32_t> host(size_t(p->nb));
+  for (int b = 0; b < p->nb; ++b) host[size_t(b)] = int32_t(p->boff[size_t(b)]);
+  HGNN_HIP(first.alloc(sizeof(int32_t) * size_t(p->nb)));
+  HGNN_HIP(hipMemcpyAsync(first.p, host.data(), sizeof(int32_t) * size_t(p->nb), hipMemcpyHostToDevice, s));
+  const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks};
+  TaskCounts c;
+  hgnn_status st = task_count(q, c, s);
+  HGNN_HIP(hipStreamSynchronize(s));
+  if (st != HGNN_OK) return st;
+  st = task_build(q, c, p->max_F, p->max_H, &p->btasks, s);
+  HGNN_HIP(hipStreamSynchronize(s));
+  return st;
+}
+
+void destroy_tasks(hgnn_row_tasks* t) {
+  if (!t) return;
+  dev_free(t->task);
+  dev_free(t->zrow);
+  dev_free(t->split);
+  dev_free(t->sec);
+  dev_free(t->staging);
+  dev_free(t->stage_mz);
+  delete t;
+}
+
+}  // namespace hgnn

@@ -1,0 +1,72 @@
+"""The discretized SpMM over row tasks at the sizes where a piece of work changes shape: row lengths around a tile (8), a round
+(32), the longest lane-group piece and the segment size; every lanes-per-row count; tables beyond 4 GiB."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity import compare, down, f16, up
+
+pytestmark = pytest.mark.gpu
+
+EDGES = (1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 2049)
+
+
+def border_graph(V, ncols, seed):
+    """Rows of every border length, scattered among short and empty ones; columns ascending."""
+    r = np.random.default_rng(seed)
+    deg = r.integers(0, 6, size=V)
+    deg[r.permutation(V)[:len(EDGES)]] = EDGES
+    deg[V - 1] = 40
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, ncols, size=d)) for d in deg]).astype(np.int32)
+    return rowptr, col
+
+
+@pytest.mark.parametrize("F,H,S,nb", [(8, 1, 256, 1), (16, 1, 256, 1), (32, 1, 100, 1), (42, 1, 256, 1), (64, 1, 256, 3), (64, 2, 64, 1),
+                                      (64, 4, 256, 3), (64, 8, 256, 1), (100, 1, 2048, 1), (128, 1, 256, 2), (128, 16, 1, 1),
+                                      (256, 8, 256, 1), (512, 1, 256, 1)])
+@pytest.mark.parametrize("what", ["plain", "w", "map"])
+def test_piece_borders(hgnn, dev, F, H, S, nb, what):
+    print(f"row tasks F={F} H={H} S={S} nb={nb} {what}", flush=True)
+    V = 2300  # more than two windows of rows
+    rowptr, col = border_graph(V, V, F + S)
+    r = np.random.default_rng(F)
+    pitch = (F + 7) // 8 * 8
+    Xh = np.zeros((V, pitch), dtype=np.float16)
+    Xh[:, :F] = f16(r.standard_normal((V, F)))
+    w = None if what == "plain" else f16(r.standard_normal((col.size, H)))
+    H = 1 if w is None else H
+    wd = None if w is None else up(w, dev)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    eid = None
+    if what == "map":
+        g = hgnn.hgnn_transpose(g)
+        rowptr, col, eid = down(g.rowptr), down(g.col), down(g.eid)
+    p = hgnn.hgnn_plan_create(g, S, pitch, H, col_blocks=nb)
+    Y = torch.full((V, pitch), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm_discretized(p, g, wd, H, up(Xh, dev), Y, F=F)
+    ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(Xh[:, :F]), w=w, H=H, want_sabs=True, **({"eid": eid} if eid is not None else {}))
+    compare("row tasks", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+
+
+@pytest.mark.parametrize("H", [1, 4])
+def test_table_beyond_4_gib(hgnn, dev, H):
+    """Rows 2.2 M halves apart: the table spans 4.8 GB, its rows are read by 64-bit addresses."""
+    V, F, ld = 1100, 64, 2200000
+    rowptr, col = border_graph(V, V, 5)
+    r = np.random.default_rng(9)
+    Xh = f16(r.standard_normal((V, F)))
+    w = f16(r.standard_normal((col.size, H)))
+    far = torch.empty((V, ld), dtype=torch.float16, device=dev)
+    X = far[:, :F]
+    X.copy_(up(Xh, dev))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    p = hgnn.hgnn_plan_create(g, 256, F, H)
+    Y = torch.empty((V, F), dtype=torch.float16, device=dev)
+    for wd, wn, h in ((up(w, dev), w, H), (None, None, 1)):
+        hgnn.hgnn_spmm_discretized(p, g, wd, h, X, Y, F=F)
+        ref, sabs = oracle.spmm(rowptr, col, Xh, w=wn, H=h, want_sabs=True)
+        compare("far table", down(Y), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
