@@ -23,7 +23,7 @@
 //   out_masked[i, h*D+d] = sum_k alpha_k * mu_k * X[col k, h*D+d],   csum[i,h] = sum_k alpha_k * mu_k
 // (then sum_k ds_k = <dOut_i, out_masked_i> - <dOut_i, out_i> * csum_i).  They ride on the same gathered rows:
 // a second accumulator and a second sum in every triple, rescaled with the first.
-#include "common.h"
+#include "task.h"
 
 namespace hgnn {
 
@@ -42,62 +42,23 @@ struct GatArgs {
   half_t* Ym;       // SAVE: [nrows][ldym] masked result (or this block's normalised partial rows)
   int64_t ldym;
   float* csum;      // SAVE: [nrows][H] masked weight sum (or, with part_mz, this block's share, relative to its z)
-  half_t* staging_m;  // SAVE: [2*nseg][stage_ld] masked counterpart of staging
-  float* stage_c;     // SAVE: [2*nseg][H] masked weight sum of a staged piece, relative to its z
-  int S;
-  int64_t nseg;
-  const int* seg_lo;
-  const int* seg_hi;
-  half_t* staging;  // [2*nseg][stage_ld] normalised vectors of the pieces that cross a segment border
-  float* stage_mz;  // [2*nseg][H][2]
+  half_t* staging_m;  // SAVE: [slots][stage_ld] masked counterpart of staging
+  float* stage_c;     // SAVE: [slots][H] masked weight sum of a staged piece, relative to its z
+  half_t* staging;  // [slots][stage_ld] normalised vectors of the pieces of rows that have several
+  float* stage_mz;  // [slots][H][2]
   int stage_ld;
-  const int* split_row;
-  const int* split_lo;
-  const int* split_hi;
-  int n_split;
-  // all column blocks of a plan in one launch (workgroups numbered block after block): the table of the blocks'
-  // arrays, or nullptr when the fields above describe the one graph of the launch.  Y, part_mz, Ym and csum then
-  // point at block 0's partial results and advance by the strides per block.
-  const hgnn_seg_block* blocks;
-  int nblocks, max_F, max_H;
+  // column blocks in one launch (waves numbered block after block): Y, part_mz, Ym and csum point at block 0's partial
+  // results and advance by the strides per block
   int64_t y_stride, mz_stride, c_stride;
+  __device__ __forceinline__ void enter_block(int b) {
+    Y += int64_t(b) * y_stride;
+    if (part_mz) part_mz += int64_t(b) * mz_stride;
+    if (Ym) {
+      Ym += int64_t(b) * y_stride;
+      csum += int64_t(b) * c_stride;
+    }
+  }
 };
-
-// Finds the block of workgroup wg (cnt(B) workgroups per block), rewrites `a` to that block and returns the
-// workgroup's number inside the block; wg_count receives the block's workgroup count.
-template <class Count>
-__device__ __forceinline__ int64_t gat_enter_block(GatArgs& a, int64_t wg, int64_t& wg_count, Count cnt) {
-  int b = 0;
-  for (;;) {
-    const int64_t c = cnt(a.blocks[b]);
-    wg_count = c;
-    if (wg < c || b + 1 == a.nblocks) break;
-    wg -= c;
-    ++b;
-  }
-  const hgnn_seg_block& B = a.blocks[b];
-  a.rowptr = B.rowptr;
-  a.col = B.col;
-  a.nnz = B.nnz;
-  a.seg_lo = B.seg_lo;
-  a.seg_hi = B.seg_hi;
-  a.nseg = B.nseg;
-  a.staging = reinterpret_cast<half_t*>(B.staging);
-  a.stage_mz = B.stage_mz;
-  a.staging_m = a.staging + size_t(2) * size_t(B.nseg) * size_t(a.max_F);
-  a.stage_c = B.stage_mz + size_t(4) * size_t(B.nseg) * size_t(a.max_H);
-  a.split_row = B.split_row;
-  a.split_lo = B.split_lo;
-  a.split_hi = B.split_hi;
-  a.n_split = B.n_split;
-  a.Y += int64_t(b) * a.y_stride;
-  a.part_mz += int64_t(b) * a.mz_stride;
-  if (a.Ym) {
-    a.Ym += int64_t(b) * a.y_stride;
-    a.csum += int64_t(b) * a.c_stride;
-  }
-  return wg;
-}
 
 // A partial result of one row and head over some of its edges, as held by one lane (8 features):
 // m = largest score met, z = sum exp(e - m), acc = sum exp(e - m) * x; SAVE adds zm = sum exp(e - m) * mu and
@@ -125,18 +86,6 @@ struct Soft {
       zm *= f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) accm[i] *= f;
-    }
-  }
-  // one more edge with weight p = exp(e - m) (relative to the current m) and features x
-  __device__ __forceinline__ void add(float p, float e, float slope, const half8_t& x) {
-    z += p;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = fmaf(p, float(x[q]), acc[q]);
-    if (SAVE) {
-      const float pm = e > 0.f ? p : p * slope;
-      zm += pm;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) accm[q] = fmaf(pm, float(x[q]), accm[q]);
     }
   }
 };
@@ -179,7 +128,11 @@ __device__ __forceinline__ void soft_merge_normalised(Soft<SAVE>& a, float mp, f
 __device__ __forceinline__ void store_vec8(half_t* p, int f0, const float (&v)[8], float s) {
   half8_t h;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) h[i] = half_t(v[i] * s);
+  for (int i = 0; i < 8; ++i) {
+    float r = v[i] * s;
+    asm("" : "+v"(r));  // rounded to fp32 first everywhere: some instantiations fused the product into the conversion
+    h[i] = half_t(r);
+  }
   *reinterpret_cast<half8_t*>(p + f0) = h;
 }
 
@@ -211,152 +164,56 @@ __device__ __forceinline__ void stage_store(const GatArgs& a, int64_t slot, int 
   }
 }
 
-struct GatLds {
-  int per, spad, col_off, row_off, blk_off, vec_off, mz_off, flag_off, total;
-};
-__host__ __device__ inline GatLds gat_lds_layout(int S, int L, bool save) {
-  GatLds o;
-  const int G = kWave / L;
-  const int nv = save ? 2 : 1, ns = save ? 3 : 2;  // vectors and scalars of a parked piece
-  o.per = 4 * ((S + 255) / 256);
-  o.spad = kWave * o.per;
-  o.col_off = 0;
-  o.row_off = o.col_off + o.spad * 4;
-  o.blk_off = o.row_off + o.spad * 4;
-  o.vec_off = o.blk_off + ((o.spad + 15) & ~15);
-  o.mz_off = o.vec_off + G * nv * 8 * L * 4;  // one parked piece per lane group: the one that entered its chunk
-  o.flag_off = o.mz_off + G * L * ns * 4;
-  o.total = o.flag_off + ((3 * G * 4 + 15) & ~15);
-  return o;
+// The running maximum of a row only has to keep the exponentials in range, so it follows the scores lazily: it is raised,
+// and the sums rescaled, when a score exceeds it by more than kSlack (weights up to e^8, far inside fp32).
+constexpr float kSlack = 8.f;
+
+template <bool SAVE, int RS, int U>
+__device__ __forceinline__ void soft_add(Soft<SAVE>& t, const float (&p)[8 / RS], const float (&pm)[8 / RS], const half8_t& x) {
+  const float w = HeadTile<RS>::template from_owner<U>(p);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) t.acc[q] = fmaf(w, float(x[q]), t.acc[q]);
+  if (SAVE) {
+    const float wm = HeadTile<RS>::template from_owner<U>(pm);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t.accm[q] = fmaf(wm, float(x[q]), t.accm[q]);
+  }
 }
 
-// The score of an edge is formed in the main loop, with no per-edge table and no per-edge scalar fetched: the
-// column-side term a_r.X[col] from the gathered row itself (four two-way dot products per lane and an exchange
-// among the lanes of a head), the row-side term el[row] from a register that is refilled when the row changes.
-// Staging finished scores per (edge, head) in LDS instead (one 4-byte gather of er[col] per edge and head) was
-// slower for every head width from 8 to 512: the table costs waves per compute unit, the gather a cache request.
-template <int L, bool OFF32, bool SAVE>
-__global__ __launch_bounds__(kBlock) void gat_seg_kernel(GatArgs a) {
+// Segment pass over row tasks (see spmm_task_kernel for how a wave is laid out).  The row-side term el[row] is constant in a
+// lane group; the column-side term a_r.X[col] is formed from the gathered row itself (four two-way dot products per lane).
+// RS = min(lanes per head, 8).
+//
+// Bound: vector instructions, then the gathers.  The walk over equal runs of edges spent about 45 instructions per edge and
+// lane (every lane of a head repeated maximum, exponential and masks, two sums were rescaled every four edges, and most
+// steps had a row change in some lane group); this one about 27 with SAVE, 19 without.  5.5 M edges, 4 heads of 16,
+// SAVE: 169 -> 109 us; 114 M edges, one head of 64: 2.12 -> 1.06 ms; 108 k edges, eight heads of 8: 26 -> 7.5 us.
+template <int L, bool NEAR, bool SAVE, int RS>
+__global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(GatArgs a, TaskView v, int ncols) {
   constexpr int G = kWave / L;
-  constexpr int VEC = 8 * L;
-  constexpr int NV = SAVE ? 2 : 1, NS = SAVE ? 3 : 2;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  typedef Round<L> Rd;
+  typedef HeadTile<RS> Ht;
+  __shared__ __align__(16) int s_handles[G * Rd::PITCH];
+  const int lane = threadIdx.x;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;  // the lane that writes its head's scalars
-  const int S = a.S;
-  const GatLds lay = gat_lds_layout(S, L, SAVE);
-  unsigned char* base = smem + size_t(wave) * lay.total;
-  int* s_col = reinterpret_cast<int*>(base + lay.col_off);
-  int* s_row = reinterpret_cast<int*>(base + lay.row_off);
-  int* s_blk = reinterpret_cast<int*>(base + lay.blk_off);
-  // The piece that entered a group's chunk is parked in LDS when its row ends; the piece that leaves the chunk stays
-  // in the group's registers and the merge reads it from there (cross-lane reads take no LDS allocation, and the
-  // kernel's speed follows the number of waves that fit a compute unit).
-  float* m_vec = reinterpret_cast<float*>(base + lay.vec_off);  // [G][NV][VEC]: the entering piece of group g
-  float* m_mz = reinterpret_cast<float*>(base + lay.mz_off);    // [G][L][NS]: its (m, z[, zm]), per lane
-  int* m_flag = reinterpret_cast<int*>(base + lay.flag_off);    // bit0 entering, bit1 runs through, bit2 leaving
-  int* m_hrow = m_flag + G;
-  int* m_trow = m_hrow + G;
-
-  const int wpb = int(blockDim.x) / kWave;  // waves per workgroup (4, 2 or 1, chosen on the host for LDS packing)
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = gat_enter_block(a, wg, wg_count, [&](const hgnn_seg_block& B) {
-      const int64_t c = (B.nseg + wpb - 1) / wpb;
-      return c > 0 ? c : int64_t(1);
-    });
-  const int64_t wid = wg * wpb + wave;
-  const int64_t seg = wid;
-  const bool valid = seg < a.nseg;
-  const int64_t e0 = seg * S;
-  const int n = valid ? int(a.nnz - e0 < S ? a.nnz - e0 : S) : 0;
-  const int per = lay.per, spad = lay.spad;
-  int row_lo = 0, row_hi = -1;
-  if (valid) {
-    row_lo = a.seg_lo[seg];
-    row_hi = a.seg_hi[seg];
+  const int LH = a.D / 8;                         // lanes per head, a power of two
+  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  a.enter_block(w.block);
+  if (w.z1 > w.z0) {
+    const Soft<SAVE> none;
+    for (int i = w.z0 + g; i < w.z1; i += G)
+      if (active) row_store<SAVE>(a, v.zrow[i], f0, head, leader, none);
+    return;
   }
-
-  // ---- phase 1: column ids (as byte offsets of the neighbour's row where they fit 32 bits) and row ids
-  seg_stage_cols(a.col, e0, lane, spad, n, stream_nontemporal(a.nnz),
-                 [&](int i, int c) { s_col[i] = OFF32 ? int(uint32_t(c) * uint32_t(a.ldx) * 2u) : c; });
-  if (lane < G) m_flag[lane] = 0;
-  bool seg_open[2];
-  seg_stage_rows(s_row, s_blk, lane, per, n, row_lo, row_hi, a.rowptr, e0, seg_open);
-  const bool seg_left_open = seg_open[0], seg_right_open = seg_open[1];
-  wave_sync();
-
-  // ---- phase 2: running (m, z, acc) over this group's chunk
-  const int C = 4 * ((S + 4 * G - 1) / (4 * G));
-  const int c0 = g * C < n ? g * C : n;
-  const int c1 = c0 + C < n ? c0 + C : n;
-  Soft<SAVE> t;
-  int cur = -1;
-  bool lo = false;  // current piece began before this chunk
-
-  auto park = [&](int slot, const Soft<SAVE>& v) {
-    if (active) {
-      float* dst = m_vec + slot * NV * VEC + f0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) dst[i] = v.acc[i];
-      if (SAVE) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) dst[VEC + i] = v.accm[i];
-      }
-    }
-    m_mz[(slot * L + l) * NS] = v.m;
-    m_mz[(slot * L + l) * NS + 1] = v.z;
-    if (SAVE) m_mz[(slot * L + l) * NS + 2] = v.zm;
-  };
-  auto unpark = [&](int slot) -> Soft<SAVE> {
-    Soft<SAVE> v;
-    const float* src = m_vec + slot * NV * VEC + f0c;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v.acc[i] = src[i];
-    if (SAVE) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v.accm[i] = src[VEC + i];
-    }
-    v.m = m_mz[(slot * L + l) * NS];
-    v.z = m_mz[(slot * L + l) * NS + 1];
-    if (SAVE) v.zm = m_mz[(slot * L + l) * NS + 2];
-    return v;
-  };
-  auto flush = [&](bool ro) {
-    if (!lo && !ro) {
-      if (active) row_store<SAVE>(a, cur, f0, head, leader, t);
-    } else if (lo) {
-      park(g, t);
-      if (l == 0) {
-        m_flag[g] |= ro ? 3 : 1;
-        m_hrow[g] = cur;
-      }
-    } else if (l == 0) {  // leaves into the next chunk (only the last flush of a chunk gets here): stays in t
-      m_flag[g] |= 4;
-      m_trow[g] = cur;
-    }
-  };
-  auto gather = [&](int c) -> half8_t {
-    if (OFF32) {
-      const uint32_t boff = uint32_t(c) + uint32_t(f0c) * 2u;
-      return *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(a.X) + boff);
-    }
-    return *reinterpret_cast<const half8_t*>(a.X + int64_t(c) * a.ldx + f0c);
-  };
-
-  float el_cur = 0.f;  // the row-side score term of the current row, fetched when the row changes
-  if (c0 < c1) {
-    cur = s_row[c0];
-    lo = c0 > 0 ? s_row[c0 - 1] == cur : seg_left_open;
-    el_cur = a.el[int64_t(cur) * a.H + head];
-  }
-  const int LH = a.D / 8;  // lanes per head (power of two)
-  typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+  int* const s_hnd = s_handles + g * Rd::PITCH;
+  const RowTable<NEAR> table(a.X, ncols, a.ldx, f0c);
+  const int row = w.row >= 0 ? w.row : 0;
+  const float el = a.el[int64_t(row) * a.H + head];
   half2_t ar2[4];
   {
     const half8_t t = *reinterpret_cast<const half8_t*>(a.a_r + f0c);
@@ -366,128 +223,119 @@ __global__ __launch_bounds__(kBlock) void gat_seg_kernel(GatArgs a) {
       ar2[q][1] = active ? t[2 * q + 1] : half_t(0);
     }
   }
-  // the lanes of a group share their chunk, so the exchanges between the lanes of a head always meet
-  for (int i = c0; i < c1; i += 4) {
-    const int4_t cols = *reinterpret_cast<const int4_t*>(s_col + i);
-    const int blk = s_blk[i >> 2];
-    half8_t x[4];
+  const int own = (lane & (Rd::LC - 1)) * Rd::E;
+  const int edge = Ht::own_edge(l);
+  Soft<SAVE> t;  // z and zm: this lane's edges only, until the end
+  for (int k = w.beg; k < w.end; k += w.step) {
+    const int end = k + w.span < w.end ? k + w.span : w.end;
+    wave_sync();  // the previous round has been read
+    {
+      int c[Rd::E];
+      load_run<Rd::E, false>(a.col, k + own, end, c);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = gather(cols[u]);
-    float sc[4];  // column-side term a_r.x from the row just gathered, summed over the lanes of the head
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float d = 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {  // two fp16 products per instruction, fp32 sum
-        half2_t xv;
-        xv[0] = x[u][2 * q];
-        xv[1] = x[u][2 * q + 1];
-        d = __builtin_amdgcn_fdot2(ar2[q], xv, d, false);
-      }
-      sc[u] = d;
+      for (int m = 0; m < Rd::E; m += 4)
+        *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
     }
-    head_sum4(sc, LH);
-    if (blk == cur) {  // four more edges of the current row: one rescale, four terms
+    wave_sync();
+    for (int q = 0; k + q < end; q += 8) {
+      int h8[8];
+      const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float v = sc[u] + el_cur;
-        sc[u] = v > 0.f ? v : a.slope * v;
+        h8[u] = ha[u];
+        h8[4 + u] = hb[u];
       }
-      const float mn = fmaxf(fmaxf(t.m, fmaxf(sc[0], sc[1])), fmaxf(sc[2], sc[3]));
-      t.scale(__expf(t.m - mn));
+      half8_t x[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) t.add(__expf(sc[u] - mn), sc[u], a.slope, x[u]);
-      t.m = mn;
-    } else {
-      const int4_t rows = *reinterpret_cast<const int4_t*>(s_row + i);
+      for (int u = 0; u < 8; ++u) x[u] = table.row(h8[u]);
+      float d[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (i + u < c1) {
-          if (rows[u] != cur) {
-            flush(false);
-            t.clear();
-            cur = rows[u];
-            lo = false;
-            el_cur = a.el[int64_t(cur) * a.H + head];
-          }
-          const float v = sc[u] + el_cur;
-          const float e = v > 0.f ? v : a.slope * v;
-          const float mn = fmaxf(t.m, e);
-          t.scale(__expf(t.m - mn));
-          t.add(__expf(e - mn), e, a.slope, x[u]);
-          t.m = mn;
+      for (int u = 0; u < 8; ++u) {
+        d[u] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // two fp16 products per instruction, fp32 sum
+          half2_t xv;
+          xv[0] = x[u][2 * j];
+          xv[1] = x[u][2 * j + 1];
+          d[u] = __builtin_amdgcn_fdot2(ar2[j], xv, d[u], false);
         }
       }
+      if (RS == 8 && LH > 8) {  // heads of more than eight lanes: the eights are added first
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          d[u] += dpp_mov<0x128>(d[u]);
+          if (LH > 16) d[u] = xor16_mov(d[u], false);
+          if (LH > 32) d[u] = xor32_mov(d[u], false);
+        }
+      }
+      float s[Ht::NS];
+      Ht::scores(d, l, s);
+      bool above = false;
+#pragma unroll
+      for (int j = 0; j < Ht::NS; ++j) {
+        const float e = s[j] + el;
+        s[j] = k + q + j * RS + edge < end ? e : -INFINITY;
+        const float lk = s[j] > 0.f ? s[j] : a.slope * s[j];
+        above |= lk > t.m + kSlack;
+      }
+      if (__any(above)) {
+        float mx = t.m;
+#pragma unroll
+        for (int j = 0; j < Ht::NS; ++j) mx = fmaxf(mx, s[j] > 0.f ? s[j] : a.slope * s[j]);
+        mx = Ht::max_of(mx);
+        // a head in which no score exceeds the slack keeps its maximum, unless it has none yet
+        const float mn = mx > t.m + kSlack ? mx : t.m;
+        t.scale(__expf(t.m - mn));  // exp(-inf) = 0 on the first tile
+        t.m = mn;
+      }
+      float p[Ht::NS], pm[Ht::NS];
+#pragma unroll
+      for (int j = 0; j < Ht::NS; ++j) {
+        p[j] = __expf((s[j] > 0.f ? s[j] : a.slope * s[j]) - t.m);
+        t.z += p[j];
+        pm[j] = s[j] > 0.f ? p[j] : p[j] * a.slope;
+        if (SAVE) t.zm += pm[j];
+      }
+      soft_add<SAVE, RS, 0>(t, p, pm, x[0]);
+      soft_add<SAVE, RS, 1>(t, p, pm, x[1]);
+      soft_add<SAVE, RS, 2>(t, p, pm, x[2]);
+      soft_add<SAVE, RS, 3>(t, p, pm, x[3]);
+      soft_add<SAVE, RS, 4>(t, p, pm, x[4]);
+      soft_add<SAVE, RS, 5>(t, p, pm, x[5]);
+      soft_add<SAVE, RS, 6>(t, p, pm, x[6]);
+      soft_add<SAVE, RS, 7>(t, p, pm, x[7]);
     }
   }
-  if (c0 < c1) flush(c1 < n ? s_row[c1] == cur : seg_right_open);
-  wave_sync();
-
-  // ---- merge: group 0 sews the parked pieces together in chunk order
-  if (valid) {  // all lanes take part in the cross-lane reads; only group 0 keeps and stores the result
-    Soft<SAVE> run;
-    bool open = false, from_before = false;
-    int run_row = -1;
-    const bool me = g == 0 && active;
-    for (int gg = 0; gg < G; ++gg) {
-      const int fl = m_flag[gg];  // the same value on every lane
-      if (fl & 1) {
-        if (g == 0) soft_merge<SAVE>(run, unpark(gg));
-        if (gg == 0) {
-          from_before = true;
-          open = true;
-          run_row = m_hrow[0];
-        }
-        if (!(fl & 2)) {  // the row ends inside chunk gg
-          if (me) {
-            if (from_before) stage_store<SAVE>(a, 2 * seg, f0, head, leader, run);
-            else row_store<SAVE>(a, run_row, f0, head, leader, run);
-          }
-          run.clear();
-          open = false;
-          from_before = false;
-        }
-      }
-      if (fl & 4) {  // the piece that left chunk gg: from the registers of group gg
-        const int src = gg * L + l;
-        run.m = __shfl(t.m, src);
-        run.z = __shfl(t.z, src);
+  t.z = Ht::sum(t.z);
+  if (SAVE) t.zm = Ht::sum(t.zm);
+  if (w.whole) {
+    const float M = across_groups_max<L>(t.m);  // finite: a piece has at least one edge
+    t.scale(__expf(t.m - M));
+    t.m = M;
+    t.z = across_groups_sum<L>(t.z);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) run.acc[i] = __shfl(t.acc[i], src);
-        if (SAVE) {
-          run.zm = __shfl(t.zm, src);
+    for (int i = 0; i < 8; ++i) t.acc[i] = across_groups_sum<L>(t.acc[i]);
+    if (SAVE) {
+      t.zm = across_groups_sum<L>(t.zm);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) run.accm[i] = __shfl(t.accm[i], src);
-        }
-        run_row = m_trow[gg];
-        open = true;
-        from_before = false;
-      }
+      for (int i = 0; i < 8; ++i) t.accm[i] = across_groups_sum<L>(t.accm[i]);
     }
-    if (open && me)  // leaves into the next segment; a piece that also entered uses slot 2*seg
-      stage_store<SAVE>(a, 2 * seg + (from_before ? 0 : 1), f0, head, leader, run);
+    if (g) return;
   }
-
-  // ---- this wave's share of the empty rows
-  const int64_t nw = wg_count * wpb;
-  const int rpw = int((a.nrows + nw - 1) / nw);
-  const int64_t r0 = wid * rpw;
-  const int64_t r1 = r0 + rpw < a.nrows ? r0 + rpw : a.nrows;
-  if (active) {
-    const Soft<SAVE> none;
-    for (int64_t r = r0 + g; r < r1; r += G)
-      if (a.rowptr[r] == a.rowptr[r + 1]) row_store<SAVE>(a, r, f0, head, leader, none);
-  }
+  if (!active || w.row < 0) return;
+  if (w.slot < 0) row_store<SAVE>(a, row, f0, head, leader, t);
+  else stage_store<SAVE>(a, w.slot, f0, head, leader, t);
 }
 
-// Follow-up kernel: merges the staged pieces of every row that crosses a segment border (the tail
-// piece of its first segment, then the head pieces of the following ones) and stores the row.
-// A wave owns G split rows; rows of up to kShortPieces pieces are merged by their own lane group,
-// hubs by the whole wave with a final merge across the groups.
+// Follow-up kernel: merges the staged pieces of every row that has several and stores the row.  A wave owns G such rows;
+// rows of up to kShortPieces pieces are merged by their own lane group, hubs by the whole wave with a final merge across
+// the groups.
 constexpr int kShortPieces = 8;
 
 template <int L, bool SAVE>
-__global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a) {
+__global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int4_t* __restrict__ split, int n_split) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -496,20 +344,10 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a) {
   const int f0c = active ? f0 : 0;
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = gat_enter_block(a, wg, wg_count, [&](const hgnn_seg_block& B) {
-      return (int64_t(B.n_split) + kWavesPerBlock * G - 1) / (kWavesPerBlock * G);
-    });
-  const int64_t i0 = (wg * kWavesPerBlock + wave) * G;
-  if (i0 >= a.n_split) return;
-  const int64_t idx = i0 + g;
-  int r = 0, sa = 0, sb = -1;
-  if (idx < a.n_split) {
-    r = a.split_row[idx];
-    sa = a.split_lo[idx];
-    sb = a.split_hi[idx];
-  }
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  if (i0 >= n_split) return;
+  int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
+  if (i0 + g < n_split) q = split[i0 + g];
   auto take = [&](Soft<SAVE>& t, int64_t slot) {
     const half8_t o = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
     half8_t om = o;
@@ -520,18 +358,19 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a) {
     }
     soft_merge_normalised<SAVE>(t, a.stage_mz[(slot * a.H + head) * 2], a.stage_mz[(slot * a.H + head) * 2 + 1], cp, o, om);
   };
-  if (idx < a.n_split && sb - sa <= kShortPieces) {
+  if (q[2] > 0 && q[2] <= kShortPieces) {
     Soft<SAVE> t;
-    take(t, 2 * int64_t(sa) + 1);
-    for (int64_t k = int64_t(sa) + 1; k <= sb; ++k) take(t, 2 * k);
-    if (active) row_store<SAVE>(a, r, f0, head, leader, t);
+    for (int k = 0; k < q[2]; ++k) take(t, int64_t(q[1]) + k);
+    GatArgs b = a;
+    b.enter_block(q[3]);
+    if (active) row_store<SAVE>(b, q[0], f0, head, leader, t);
   }
   for (int j = 0; j < G; ++j) {
-    const int rj = __shfl(r, j * L), sj = __shfl(sa, j * L), ej = __shfl(sb, j * L);
-    if (ej - sj <= kShortPieces) continue;
+    const int n = __shfl(q[2], j * L);
+    if (n <= kShortPieces) continue;
+    const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     Soft<SAVE> t;
-    if (g == 0) take(t, 2 * int64_t(sj) + 1);
-    for (int64_t k = int64_t(sj) + 1 + g; k <= ej; k += G) take(t, 2 * k);
+    for (int k = g; k < n; k += G) take(t, int64_t(first) + k);
 #pragma unroll
     for (int off = L; off < kWave; off <<= 1) {
       Soft<SAVE> o;
@@ -546,7 +385,9 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a) {
       }
       soft_merge<SAVE>(t, o);
     }
-    if (g == 0 && active) row_store<SAVE>(a, rj, f0, head, leader, t);
+    GatArgs b = a;
+    b.enter_block(bj);
+    if (g == 0 && active) row_store<SAVE>(b, rj, f0, head, leader, t);
   }
 }
 
@@ -587,40 +428,42 @@ __global__ __launch_bounds__(kBlock) void gat_block_merge_kernel(GatArgs a, GatB
   row_store<SAVE>(a, r, f0, head, (f0 % a.D) == 0, t);
 }
 
-template <int L, bool OFF32>
-static void launch_gat_seg_l(bool save, dim3 grid, int threads, size_t lds, hipStream_t s, const GatArgs& a) {
-  if (save) gat_seg_kernel<L, OFF32, true><<<grid, threads, lds, s>>>(a);
-  else gat_seg_kernel<L, OFF32, false><<<grid, threads, lds, s>>>(a);
+template <int L, bool NEAR, bool SAVE>
+static void launch_gat_tasks_l(int lh, unsigned waves, hipStream_t s, const GatArgs& a, const TaskView& v, int ncols) {
+  if (lh == 1) gat_task_kernel<L, NEAR, SAVE, 1><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else if (lh == 2) gat_task_kernel<L, NEAR, SAVE, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else if (lh == 4) gat_task_kernel<L, NEAR, SAVE, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else gat_task_kernel<L, NEAR, SAVE, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v, ncols);
 }
 
-template <bool OFF32>
-static void launch_gat_seg(int L, bool save, dim3 grid, int threads, size_t lds, hipStream_t s, const GatArgs& a) {
+template <bool NEAR, bool SAVE>
+static void launch_gat_tasks(int L, int lh, unsigned waves, hipStream_t s, const GatArgs& a, const TaskView& v, int ncols) {
   switch (L) {
-    case 1: launch_gat_seg_l<1, OFF32>(save, grid, threads, lds, s, a); break;
-    case 2: launch_gat_seg_l<2, OFF32>(save, grid, threads, lds, s, a); break;
-    case 4: launch_gat_seg_l<4, OFF32>(save, grid, threads, lds, s, a); break;
-    case 8: launch_gat_seg_l<8, OFF32>(save, grid, threads, lds, s, a); break;
-    case 16: launch_gat_seg_l<16, OFF32>(save, grid, threads, lds, s, a); break;
-    case 32: launch_gat_seg_l<32, OFF32>(save, grid, threads, lds, s, a); break;
-    default: launch_gat_seg_l<64, OFF32>(save, grid, threads, lds, s, a); break;
+    case 1: launch_gat_tasks_l<1, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    case 2: launch_gat_tasks_l<2, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    case 4: launch_gat_tasks_l<4, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    case 8: launch_gat_tasks_l<8, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    case 16: launch_gat_tasks_l<16, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    case 32: launch_gat_tasks_l<32, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
+    default: launch_gat_tasks_l<64, NEAR, SAVE>(lh, waves, s, a, v, ncols); break;
   }
 }
 
 template <int L>
-static void launch_gat_finish_l(bool save, dim3 grid, hipStream_t s, const GatArgs& a) {
-  if (save) gat_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a);
-  else gat_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a);
+static void launch_gat_finish_l(bool save, dim3 grid, hipStream_t s, const GatArgs& a, const TaskView& v) {
+  if (save) gat_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split);
+  else gat_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split);
 }
 
-static void launch_gat_finish(int L, bool save, dim3 grid, hipStream_t s, const GatArgs& a) {
+static void launch_gat_finish(int L, bool save, dim3 grid, hipStream_t s, const GatArgs& a, const TaskView& v) {
   switch (L) {
-    case 1: launch_gat_finish_l<1>(save, grid, s, a); break;
-    case 2: launch_gat_finish_l<2>(save, grid, s, a); break;
-    case 4: launch_gat_finish_l<4>(save, grid, s, a); break;
-    case 8: launch_gat_finish_l<8>(save, grid, s, a); break;
-    case 16: launch_gat_finish_l<16>(save, grid, s, a); break;
-    case 32: launch_gat_finish_l<32>(save, grid, s, a); break;
-    default: launch_gat_finish_l<64>(save, grid, s, a); break;
+    case 1: launch_gat_finish_l<1>(save, grid, s, a, v); break;
+    case 2: launch_gat_finish_l<2>(save, grid, s, a, v); break;
+    case 4: launch_gat_finish_l<4>(save, grid, s, a, v); break;
+    case 8: launch_gat_finish_l<8>(save, grid, s, a, v); break;
+    case 16: launch_gat_finish_l<16>(save, grid, s, a, v); break;
+    case 32: launch_gat_finish_l<32>(save, grid, s, a, v); break;
+    default: launch_gat_finish_l<64>(save, grid, s, a, v); break;
   }
 }
 
@@ -642,39 +485,28 @@ static void launch_gat_block_merge(int L, bool save, dim3 grid, hipStream_t s, c
   }
 }
 
-// segment pass + follow-up pass for the graph in `a` with the segment arrays of plan q
-static hgnn_status run_gat_segments(const hgnn_plan* q, GatArgs a, int ncols, hipStream_t s) {
-  a.seg_lo = q->seg_row_lo;
-  a.seg_hi = q->seg_row_hi;
-  a.S = q->S;
-  a.nseg = q->nseg;
-  a.staging = reinterpret_cast<half_t*>(q->staging);
-  a.stage_mz = q->stage_mz;
-  a.stage_ld = q->max_F;
+// pass over the row tasks t of plan p + follow-up pass
+static hgnn_status run_gat_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, GatArgs a, int ncols, hipStream_t s) {
+  a.staging = reinterpret_cast<half_t*>(t->staging);
+  a.stage_mz = t->stage_mz;
+  a.stage_ld = p->max_F;
   const bool save = a.Ym != nullptr;
-  // the plan holds a second set of staging vectors and a third scalar per staged piece behind the first
-  a.staging_m = a.staging + size_t(2) * size_t(q->nseg) * size_t(q->max_F);
-  a.stage_c = q->stage_mz + size_t(4) * size_t(q->nseg) * size_t(q->max_H);
-  a.split_row = q->split_row;
-  a.split_lo = q->split_seg_lo;
-  a.split_hi = q->split_seg_hi;
-  a.n_split = q->n_split;
-  const int L = pow2_at_least(a.F / 8);
-  const size_t per_wave = size_t(gat_lds_layout(a.S, L, save).total);
-  const int wpb = waves_per_block_for_lds(per_wave, true);
-  const size_t lds = per_wave * wpb;
-  HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-               "hgnn_gat_forward_fused: seg_edges = %d with H = %d needs %zu bytes of LDS per workgroup (limit 65536)", a.S,
-               a.H, lds);
-  const int64_t nblk = ceil_div(q->nseg, wpb);
-  dim3 grid(unsigned(nblk > 0 ? nblk : 1));
-  const int threads = wpb * kWave;
-  const bool off32 = uint64_t(ncols) * uint64_t(a.ldx) * 2u < (uint64_t(1) << 32);
-  if (off32) launch_gat_seg<true>(L, save, grid, threads, lds, s, a);
-  else launch_gat_seg<false>(L, save, grid, threads, lds, s, a);
-  HGNN_LAUNCH_CHECK("gat_seg_kernel");
-  if (a.n_split > 0) {
-    launch_gat_finish(L, save, dim3(unsigned(ceil_div(a.n_split, int64_t(kWavesPerBlock) * (kWave / L)))), s, a);
+  // a second set of staging vectors and a third scalar per staged piece lie behind the first
+  a.staging_m = a.staging + size_t(t->n_slots) * size_t(p->max_F);
+  a.stage_c = t->stage_mz + size_t(2) * size_t(t->n_slots) * size_t(p->max_H);
+  const int L = pow2_at_least(a.F / 8), G = kWave / L, lh = a.D / 8;
+  const TaskView v = task_view(t, G);
+  const int waves = v.first_wave[t->nb];
+  if (waves > 0) {
+    const bool near = near_table(ncols, a.ldx);
+    if (near && save) launch_gat_tasks<true, true>(L, lh, unsigned(waves), s, a, v, ncols);
+    else if (near) launch_gat_tasks<true, false>(L, lh, unsigned(waves), s, a, v, ncols);
+    else if (save) launch_gat_tasks<false, true>(L, lh, unsigned(waves), s, a, v, ncols);
+    else launch_gat_tasks<false, false>(L, lh, unsigned(waves), s, a, v, ncols);
+    HGNN_LAUNCH_CHECK("gat_task_kernel");
+  }
+  if (v.n_split > 0) {
+    launch_gat_finish(L, save, dim3(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * G))), s, a, v);
     HGNN_LAUNCH_CHECK("gat_finish_kernel");
   }
   return HGNN_OK;
@@ -736,8 +568,9 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   a.ldym = ldom;
   a.csum = csum;
   const bool save = out_masked != nullptr;
-  if (p->nb <= 1) return run_gat_segments(p, a, g->ncols, s);
+  if (p->nb <= 1) return run_gat_tasks(p, p->tasks, a, g->ncols, s);
   // column-blocked plan: every block leaves normalised partial rows and their (m, z[, zm/z]) per row; one pass merges them
+  if (p->fine) p = p->fine;
   const size_t V = size_t(p->nrows);
   const size_t flat = size_t(p->nb) * V;
   half_t* bstage = reinterpret_cast<half_t*>(p->bstage);
@@ -745,7 +578,7 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   float* bsum_c = p->bsum + 2 * flat * size_t(p->max_H);  // and a third scalar per partial row
   const int L = pow2_at_least(F / 8);
   {
-    // all blocks in one launch of each kernel: workgroups numbered block after block and dispatched in that order
+    // all blocks in one launch: waves numbered block after block and dispatched in that order
     GatArgs ab = a;
     ab.Y = bstage;
     ab.ldy = p->max_F;
@@ -754,34 +587,12 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
     ab.Ym = save ? bstage_m : nullptr;
     ab.ldym = p->max_F;
     ab.csum = save ? bsum_c : nullptr;
-    ab.blocks = p->bdesc;
-    ab.nblocks = p->nb;
-    ab.max_F = p->max_F;
-    ab.max_H = p->max_H;
+    ab.col = p->bcol;
     ab.y_stride = int64_t(V) * p->max_F;
     ab.mz_stride = int64_t(V) * p->max_H * 2;
     ab.c_stride = int64_t(V) * p->max_H;
-    ab.S = p->S;
-    ab.stage_ld = p->max_F;
-    const size_t per_wave = size_t(gat_lds_layout(ab.S, L, save).total);
-    const int wpb = waves_per_block_for_lds(per_wave, true);
-    const size_t lds = per_wave * wpb;
-    HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-                 "%s: seg_edges = %d with H = %d needs %zu bytes of LDS per workgroup (limit 65536)", who, ab.S, ab.H, lds);
-    int64_t wgs = 0, wgs2 = 0;
-    for (const hgnn_plan* q : p->sub) {
-      const int64_t c = ceil_div(q->nseg, wpb);
-      wgs += c > 0 ? c : 1;
-      wgs2 += ceil_div(q->n_split, int64_t(kWavesPerBlock) * (kWave / L));
-    }
-    const bool off32 = uint64_t(g->ncols) * uint64_t(ab.ldx) * 2u < (uint64_t(1) << 32);
-    if (off32) launch_gat_seg<true>(L, save, dim3(unsigned(wgs)), wpb * kWave, lds, s, ab);
-    else launch_gat_seg<false>(L, save, dim3(unsigned(wgs)), wpb * kWave, lds, s, ab);
-    HGNN_LAUNCH_CHECK("gat_seg_kernel");
-    if (wgs2 > 0) {
-      launch_gat_finish(L, save, dim3(unsigned(wgs2)), s, ab);
-      HGNN_LAUNCH_CHECK("gat_finish_kernel");
-    }
+    st = run_gat_tasks(p, p->btasks, ab, g->ncols, s);
+    if (st != HGNN_OK) return st;
   }
   const GatBlockParts parts{bstage, bstage_m, p->max_F, p->bsum, int64_t(V) * p->max_H * 2, bsum_c, int64_t(V) * p->max_H, p->nb};
   launch_gat_block_merge(L, save, dim3(unsigned(ceil_div(g->nrows, int64_t(kWavesPerBlock) * (kWave / L)))), s, a, parts);

@@ -5,16 +5,15 @@
 // the backward pass (sections 2.1.2 and 3.1.2: SDDMM for dalpha, Eq. 1 differentiated, the
 // alpha-weighted SpMM on the transpose) follows from one gathered feature row and a few scalars:
 //   dalpha_ij = <dOut_i, h_j>,   ds_ij = alpha_ij * (dalpha_ij - t_i) * LeakyReLU'(el_i + er_j)
-// Two passes over the graph, both on the segment design (no atomics, staged pieces, follow-up):
+// Two passes over the graph, both over row tasks (no atomics, staged pieces, follow-up):
 //   transposed pass (rows j, gathers dOut_i):  dV_j = sum_i alpha_ij * dOut_i,  d_er_j = sum_i ds_ij
 //   forward pass    (rows i, gathers h_j):     d_el_i = sum_j ds_ij
 // The destination vertex's scalars (el, lse, t) sit in one 16-byte entry per (vertex, head), so the
-// transposed pass fetches them with a single gather from a table that stays in L2; the weight and
-// the mask are formed once per edge and wave while the segment is staged.  Because the sum of ds over
+// transposed pass fetches them with a single gather from a table that stays in L2.  Because the sum of ds over
 // any piece of a row is linear in the gathered vectors, no dot product is formed per edge: the
 // kernels accumulate the mask-weighted vector sum and one scalar, and take the dot product with the
 // row-side vector once per piece.
-#include "common.h"
+#include "task.h"
 
 namespace hgnn {
 
@@ -29,78 +28,19 @@ struct GatBwdArgs {
   float slope;
   const float4* vtab;  // [destination vertex][H]: (el, lse, t, unused)
   const float* er;     // [source vertex][H]
-  int dst_is_col;      // 1: the destination vertex of a non-zero is its column (transposed pass), 0: its row
   half_t* dsum;        // [nrows][H] sum over the row of ds (fp16), or
   float* dsum_f32;     // column blocks: this block's partial sums in fp32
-  int S;
-  int64_t nseg;
-  const int* seg_lo;
-  const int* seg_hi;
-  half_t* staging;     // [2*nseg][stage_ld]
-  float* stage_ds;     // [2*nseg][H][2], first float = partial sum of ds
+  half_t* staging;     // [slots][stage_ld] pieces of the rows that have several
+  float* stage_ds;     // [slots][H] their partial sums of ds
   int stage_ld;
-  const int* split_row;
-  const int* split_lo;
-  const int* split_hi;
-  int n_split;
-  // all column blocks of a plan in one launch (workgroups numbered block after block): the table of the blocks'
-  // arrays, or nullptr when the fields above describe the one graph of the launch.  Y and dsum_f32 then point at
-  // block 0's partial results and advance by the strides per block.
-  const hgnn_seg_block* blocks;
-  int nblocks;
+  // column blocks in one launch (waves numbered block after block): Y and dsum_f32 point at block 0's partial results and
+  // advance by the strides per block
   int64_t y_stride, ds_stride;
-};
-
-// Finds the block of workgroup wg (cnt(B) workgroups per block), rewrites `a` to that block and returns the
-// workgroup's number inside the block; wg_count receives the block's workgroup count.
-template <class Count>
-__device__ __forceinline__ int64_t gat_bwd_enter_block(GatBwdArgs& a, int64_t wg, int64_t& wg_count, Count cnt) {
-  int b = 0;
-  for (;;) {
-    const int64_t c = cnt(a.blocks[b]);
-    wg_count = c;
-    if (wg < c || b + 1 == a.nblocks) break;
-    wg -= c;
-    ++b;
+  __device__ __forceinline__ void enter_block(int b) {
+    if (Y) Y += int64_t(b) * y_stride;
+    if (dsum_f32) dsum_f32 += int64_t(b) * ds_stride;
   }
-  const hgnn_seg_block& B = a.blocks[b];
-  a.rowptr = B.rowptr;
-  a.col = B.col;
-  a.nnz = B.nnz;
-  a.seg_lo = B.seg_lo;
-  a.seg_hi = B.seg_hi;
-  a.nseg = B.nseg;
-  a.staging = reinterpret_cast<half_t*>(B.staging);
-  a.stage_ds = B.stage_mz;
-  a.split_row = B.split_row;
-  a.split_lo = B.split_lo;
-  a.split_hi = B.split_hi;
-  a.n_split = B.n_split;
-  if (a.Y) a.Y += int64_t(b) * a.y_stride;
-  a.dsum_f32 += int64_t(b) * a.ds_stride;
-  return wg;
-}
-
-struct GatBwdLds {
-  int per, spad, col_off, row_off, blk_off, a_off, t_off, vec_off, ds_off, flag_off, total;
 };
-// fly: no per (edge, head) tables; a copy of the raw column ids instead where s_col holds byte offsets (off32)
-__host__ __device__ inline GatBwdLds gat_bwd_lds_layout(int S, int H, int L, bool vec, bool fly, bool off32) {
-  GatBwdLds o;
-  const int G = kWave / L;
-  o.per = 4 * ((S + 255) / 256);
-  o.spad = kWave * o.per;
-  o.col_off = 0;
-  o.row_off = o.col_off + o.spad * 4;
-  o.blk_off = o.row_off + o.spad * 4;
-  o.a_off = o.blk_off + ((o.spad + 15) & ~15);
-  o.t_off = o.a_off + (fly ? (off32 ? o.spad * 4 : 0) : o.spad * H * 4);
-  o.vec_off = o.t_off + (fly ? 0 : o.spad * H * 4);
-  o.ds_off = o.vec_off + (vec ? G * 8 * L * 4 : 0);  // one parked piece per lane group: the one that entered its chunk
-  o.flag_off = o.ds_off + G * L * 4;
-  o.total = o.flag_off + ((3 * G * 4 + 15) & ~15);
-  return o;
-}
 
 // one finished row: the vector (VEC) and the head's scalar
 template <bool VEC>
@@ -127,21 +67,29 @@ __device__ __forceinline__ void bwd_stage_store(const GatBwdArgs& a, int64_t slo
     for (int i = 0; i < 8; ++i) h[i] = half_t(acc[i]);
     *reinterpret_cast<half8_t*>(a.staging + slot * a.stage_ld + f0) = h;
   }
-  if (leader) a.stage_ds[(slot * a.H + head) * 2] = ds;
+  if (leader) a.stage_ds[slot * a.H + head] = ds;
 }
 
-// VEC = true is the pass over the transposed graph (the destination vertex of a non-zero is its column).
-// FLY = true: the weight of an edge is formed in the main loop from the destination's packed scalars and the
-// source's er, one of them gathered per edge and the other fetched when the row changes; no per-edge tables in
-// LDS, so more waves fit a compute unit (wins with several heads, where the tables are large, and with one head
-// of up to 64 features, whose few lanes repeat little of the scalar work).  FLY = false: formed once per
-// (edge, head) while the segment is staged.
-template <int L, bool OFF32, bool VEC, bool FLY>
-__global__ __launch_bounds__(kBlock, VEC ? 1 : 6) void gat_bwd_seg_kernel(GatBwdArgs a) {
+// VEC = true is the pass over the transposed graph (the destination vertex of a non-zero is its column).  A wave is laid out as
+// in gat_task_kernel.  The weight of a (non-zero, head) and what follows from it are formed once, by the lane that owns the
+// pair (HeadTile), from the destination's packed scalars and the source's er -- one of them fetched per non-zero, the
+// other constant in a lane group -- and handed to the other lanes of the head with the weight.
+//
+// The sum of ds over a piece of a row is linear in the gathered vectors:
+//   sum_k alpha_k m_k (<r, x_k> - t_k) = <r, sum_k alpha_k m_k x_k> - sum_k alpha_k m_k t_k
+// (r = the row-side vector, m = the LeakyReLU slope of the edge), so the loop only accumulates the mask-weighted vector
+// wacc beside acc and one scalar; the dot product with r happens once per piece.
+//
+// Bound: the L2s' requests (two per non-zero: the vector, the packed scalars) and the products.  5.5 M non-zeros, 4 heads of
+// 16: 131 -> 107 us against the walk over equal runs; 114 M, one head of 64: 1.65 -> 1.29 ms.
+template <int L, bool NEAR, bool VEC, int RS>
+__global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task_kernel(GatBwdArgs a, TaskView v, int ncols) {
   constexpr int G = kWave / L;
-  constexpr int VECF = 8 * L;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  typedef Round<L> Rd;
+  typedef HeadTile<RS> Ht;
+  __shared__ __align__(16) int s_handles[G * Rd::PITCH];
+  __shared__ __align__(16) int s_raw[NEAR ? G * Rd::PITCH : 4];
+  const int lane = threadIdx.x;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
@@ -149,292 +97,118 @@ __global__ __launch_bounds__(kBlock, VEC ? 1 : 6) void gat_bwd_seg_kernel(GatBwd
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
   const int LH = a.D / 8;
-  const int S = a.S;
-  const GatBwdLds lay = gat_bwd_lds_layout(S, a.H, L, VEC, FLY, OFF32);
-  unsigned char* base = smem + size_t(wave) * lay.total;
-  int* s_col = reinterpret_cast<int*>(base + lay.col_off);
-  int* s_row = reinterpret_cast<int*>(base + lay.row_off);
-  int* s_blk = reinterpret_cast<int*>(base + lay.blk_off);
-  float* s_a = reinterpret_cast<float*>(base + lay.a_off);    // [spad][H]: alpha, negated where the score is <= 0
-  int* s_raw = OFF32 ? reinterpret_cast<int*>(base + lay.a_off) : s_col;  // FLY: [spad] column ids (s_a's place)
-  float* s_t = reinterpret_cast<float*>(base + lay.t_off);    // [spad][H]: alpha * mask * t of the destination vertex
-  // the piece that entered a group's chunk is parked here when its row ends; the piece that leaves the chunk stays
-  // in the group's registers, from where the merge reads it (no LDS allocation: more waves per compute unit)
-  float* m_vec = reinterpret_cast<float*>(base + lay.vec_off);  // [G][VECF] parked vectors (VEC)
-  float* m_ds = reinterpret_cast<float*>(base + lay.ds_off);    // [G][L] parked ds sums, per lane
-  int* m_flag = reinterpret_cast<int*>(base + lay.flag_off);
-  int* m_hrow = m_flag + G;
-  int* m_trow = m_hrow + G;
-
-  const int wpb = int(blockDim.x) / kWave;  // 4 waves per workgroup, fewer when the heads' LDS tables are large
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = gat_bwd_enter_block(a, wg, wg_count, [&](const hgnn_seg_block& B) {
-      const int64_t c = (B.nseg + wpb - 1) / wpb;
-      return c > 0 ? c : int64_t(1);
-    });
-  const int64_t wid = wg * wpb + wave;
-  const int64_t seg = wid;
-  const bool valid = seg < a.nseg;
-  const int64_t e0 = seg * S;
-  const int n = valid ? int(a.nnz - e0 < S ? a.nnz - e0 : S) : 0;
-  const int per = lay.per, spad = lay.spad;
-  int row_lo = 0, row_hi = -1;
-  bool seg_left_open = false, seg_right_open = false;
-  if (valid) {
-    row_lo = a.seg_lo[seg];
-    row_hi = a.seg_hi[seg];
-    seg_left_open = int64_t(a.rowptr[row_lo]) < e0;
-    seg_right_open = int64_t(a.rowptr[row_hi + 1]) > e0 + n;
-  }
-
-  // ---- phase 1: column ids, row ids, then per (edge, head) the attention weight with the LeakyReLU branch in
-  // its sign, and u = alpha * mask * t of the destination vertex
-  seg_stage_cols(a.col, e0, lane, spad, n, stream_nontemporal(a.nnz), [&](int i, int c) {
-    if (FLY && OFF32) {
-      s_raw[i] = c;
-      s_col[i] = int(uint32_t(c) * uint32_t(a.ldx) * 2u);
-    } else {
-      s_col[i] = c;
-    }
-  });
-  if (lane < G) m_flag[lane] = 0;
-  seg_stage_rows(s_row, s_blk, lane, per, n, row_lo, row_hi, a.rowptr, e0);
-  if (!FLY) {
-    for (int i = lane; i < spad; i += kWave) {
-      const bool in = i < n;
-      const int c = s_col[i];
-      const int r = in ? s_row[i] : 0;
-      const int64_t dst = a.dst_is_col ? c : r, src = a.dst_is_col ? r : c;
-      for (int h = 0; h < a.H; ++h) {
-        float av = 0.f, uv = 0.f;
-        if (in) {
-          const float4 v = a.vtab[dst * a.H + h];
-          const float sc = v.x + a.er[src * a.H + h];
-          const float alpha = __expf((sc > 0.f ? sc : a.slope * sc) - v.y);
-          av = sc > 0.f ? alpha : -alpha;
-          uv = (sc > 0.f ? alpha : a.slope * alpha) * v.z;
-        }
-        s_a[i * a.H + h] = av;
-        s_t[i * a.H + h] = uv;
-      }
-      if (OFF32) s_col[i] = int(uint32_t(c) * uint32_t(a.ldx) * 2u);
-    }
-  }
-  wave_sync();
-
-  // ---- phase 2.  The sum of ds over a piece of a row is linear in the gathered vectors:
-  //   sum_k alpha_k m_k (<r, x_k> - t_k) = <r, sum_k alpha_k m_k x_k> - sum_k alpha_k m_k t_k
-  // (r = the row-side vector, m = the LeakyReLU slope of the edge), so the inner loop only accumulates the
-  // mask-weighted vector wacc beside acc and one scalar; the dot product with r and the exchange between
-  // the lanes of a head happen once per piece, when it is flushed.
-  const int C = 4 * ((S + 4 * G - 1) / (4 * G));
-  const int c0 = g * C < n ? g * C : n;
-  const int c1 = c0 + C < n ? c0 + C : n;
+  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  a.enter_block(w.block);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum alpha * x          (VEC)
+  if (w.z1 > w.z0) {
+    for (int i = w.z0 + g; i < w.z1; i += G)
+      if (active) bwd_row_store<VEC>(a, v.zrow[i], f0, head, leader, acc, 0.f);
+    return;
+  }
   float wacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // sum alpha * m * x
-  float csum = 0.f;                                           // sum alpha * m * t
-  int cur = -1;
-  bool lo = false;
-  float leave_ds = 0.f;     // ds sum of the piece that leaves this chunk (its vector stays in acc)
-  half8_t ur = half8_t(0);  // this lane's slice of the current row's row-side vector
-  float4 v_row = make_float4(0.f, 0.f, 0.f, 0.f);  // FLY, pass over the graph: the row's (el, lse, t)
-  float er_row = 0.f;                              // FLY, transposed pass: the row's er
-  auto load_row_vec = [&](int r) {
-    ur = *reinterpret_cast<const half8_t*>(a.R + int64_t(r) * a.ldr + f0c);
-    if (FLY) {
-      if (VEC) er_row = a.er[int64_t(r) * a.H + head];
-      else v_row = a.vtab[int64_t(r) * a.H + head];
-    }
-  };
-  auto flush = [&](bool ro) {
-    float d = 0.f;
-    if (active) {
+  float csum = 0.f;                                           // sum alpha * m * t over this lane's edges
+  int* const s_hnd = s_handles + g * Rd::PITCH;
+  int* const s_col = NEAR ? s_raw + g * Rd::PITCH : s_hnd;  // column ids
+  const RowTable<NEAR> table(a.X, ncols, a.ldx, f0c);
+  const int row = w.row >= 0 ? w.row : 0;
+  const half8_t ur = *reinterpret_cast<const half8_t*>(a.R + int64_t(row) * a.ldr + f0c);  // the row-side vector
+  float er_row = 0.f;                                // VEC: the row is the source vertex
+  float4 v_row = make_float4(0.f, 0.f, 0.f, 0.f);    // else the destination
+  if (VEC) er_row = a.er[int64_t(row) * a.H + head];
+  else v_row = a.vtab[int64_t(row) * a.H + head];
+  const int own = (lane & (Rd::LC - 1)) * Rd::E;
+  const int edge = Ht::own_edge(l);
+  for (int k = w.beg; k < w.end; k += w.step) {
+    const int end = k + w.span < w.end ? k + w.span : w.end;
+    wave_sync();  // the previous round has been read
+    {
+      int c[Rd::E];
+      load_run<Rd::E, false>(a.col, k + own, end, c);
+      if (NEAR) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) d = fmaf(wacc[q], float(ur[q]), d);
-    }
-    const float dsv = head_sum1(d, LH) - csum;
-    if (!lo && !ro) {
-      if (active) bwd_row_store<VEC>(a, cur, f0, head, leader, acc, dsv);
-    } else if (lo) {
-      if (VEC && active) {
-        float* dst = m_vec + g * VECF + f0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) dst[i] = acc[i];
+        for (int m = 0; m < Rd::E; m += 4)
+          *reinterpret_cast<int4_t*>(s_col + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
       }
-      m_ds[g * L + l] = dsv;
-      if (l == 0) {
-        m_flag[g] |= ro ? 3 : 1;
-        m_hrow[g] = cur;
-      }
-    } else {  // leaves into the next chunk (only the last flush of a chunk gets here)
-      leave_ds = dsv;
-      if (l == 0) {
-        m_flag[g] |= 4;
-        m_trow[g] = cur;
-      }
-    }
-  };
-  auto gather = [&](int c) -> half8_t {
-    if (OFF32) {
-      const uint32_t boff = uint32_t(c) + uint32_t(f0c) * 2u;
-      return *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(a.X) + boff);
-    }
-    return *reinterpret_cast<const half8_t*>(a.X + int64_t(c) * a.ldx + f0c);
-  };
-  // FLY: av = the destination's el, uv = the source's er, lse and t beside them; else the staged pair
-  auto add_edge = [&](float av, float uv, float lse, float tt, const half8_t& x) {
-    float alpha, am;
-    if (FLY) {
-      const float sc = av + uv;
-      alpha = __expf((sc > 0.f ? sc : a.slope * sc) - lse);
-      am = sc > 0.f ? alpha : a.slope * alpha;
-      csum = fmaf(am, tt, csum);
-    } else {
-      alpha = fabsf(av);
-      am = av > 0.f ? av : -a.slope * av;
-      csum += uv;
-    }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float xf = float(x[q]);
-      if (VEC) acc[q] = fmaf(alpha, xf, acc[q]);
-      wacc[q] = fmaf(am, xf, wacc[q]);
-    }
-  };
-
-  if (c0 < c1) {
-    cur = s_row[c0];
-    lo = c0 > 0 ? s_row[c0 - 1] == cur : seg_left_open;
-    load_row_vec(cur);
-  }
-  for (int i = c0; i < c1; i += 4) {
-    const int4_t cols = *reinterpret_cast<const int4_t*>(s_col + i);
-    const int blk = s_blk[i >> 2];
-    half8_t x[4];
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = gather(cols[u]);
-    float av[4], uv[4], ls[4], tt[4];
-    if (FLY) {
-      const int4_t raw = OFF32 ? *reinterpret_cast<const int4_t*>(s_raw + i) : cols;
+      for (int m = 0; m < Rd::E; m += 4)
+        *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
+    }
+    wave_sync();
+    for (int q = 0; k + q < end; q += 8) {
+      float4 dv[Ht::NS];
+      float es[Ht::NS];
+      bool in[Ht::NS];
+#pragma unroll
+      for (int j = 0; j < Ht::NS; ++j) {
+        in[j] = k + q + j * RS + edge < end;
+        const int c = in[j] ? s_col[q + j * RS + edge] : 0;
+        if (VEC) dv[j] = a.vtab[int64_t(c) * a.H + head];
+        else es[j] = a.er[int64_t(c) * a.H + head];
+      }
+      int h8[8];
+      const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
+        h8[u] = ha[u];
+        h8[4 + u] = hb[u];
+      }
+      half8_t x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = table.row(h8[u]);
+      float alpha[Ht::NS], am[Ht::NS];
+#pragma unroll
+      for (int j = 0; j < Ht::NS; ++j) {
+        const float sc = VEC ? dv[j].x + er_row : v_row.x + es[j];
+        const float lse = VEC ? dv[j].y : v_row.y, tt = VEC ? dv[j].z : v_row.z;
+        alpha[j] = in[j] ? __expf((sc > 0.f ? sc : a.slope * sc) - lse) : 0.f;
+        am[j] = sc > 0.f ? alpha[j] : a.slope * alpha[j];
+        csum += in[j] ? am[j] * tt : 0.f;
+      }
+      auto add = [&](auto U) {
+        constexpr int u = decltype(U)::value;
         if (VEC) {
-          const float4 v = a.vtab[int64_t(raw[u]) * a.H + head];
-          av[u] = v.x;
-          ls[u] = v.y;
-          tt[u] = v.z;
-        } else {
-          uv[u] = a.er[int64_t(raw[u]) * a.H + head];
+          const float wa = Ht::template from_owner<u>(alpha);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[i] = fmaf(wa, float(x[u][i]), acc[i]);
         }
-      }
-    } else {
+        const float wm = Ht::template from_owner<u>(am);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        av[u] = s_a[(i + u) * a.H + head];
-        uv[u] = s_t[(i + u) * a.H + head];
-        ls[u] = tt[u] = 0.f;
-      }
-    }
-    // the row-side half of a FLY edge is read when the edge is added: the row may have changed by then
-    auto add = [&](int u) {
-      if (FLY && VEC) add_edge(av[u], er_row, ls[u], tt[u], x[u]);
-      else if (FLY) add_edge(v_row.x, uv[u], v_row.y, v_row.z, x[u]);
-      else add_edge(av[u], uv[u], 0.f, 0.f, x[u]);
-    };
-    if (blk == cur) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) add(u);
-    } else {
-      const int4_t rows = *reinterpret_cast<const int4_t*>(s_row + i);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (i + u < c1) {
-          if (rows[u] != cur) {
-            flush(false);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              acc[q] = 0.f;
-              wacc[q] = 0.f;
-            }
-            csum = 0.f;
-            cur = rows[u];
-            lo = false;
-            load_row_vec(cur);
-          }
-          add(u);
-        }
-      }
+        for (int i = 0; i < 8; ++i) wacc[i] = fmaf(wm, float(x[u][i]), wacc[i]);
+      };
+      add(std::integral_constant<int, 0>{});
+      add(std::integral_constant<int, 1>{});
+      add(std::integral_constant<int, 2>{});
+      add(std::integral_constant<int, 3>{});
+      add(std::integral_constant<int, 4>{});
+      add(std::integral_constant<int, 5>{});
+      add(std::integral_constant<int, 6>{});
+      add(std::integral_constant<int, 7>{});
     }
   }
-  if (c0 < c1) flush(c1 < n ? s_row[c1] == cur : seg_right_open);
-  wave_sync();
-
-  // ---- merge: group 0 sews the pieces together in chunk order (all lanes take part in the cross-lane reads)
-  if (valid) {
-    float run[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float rds = 0.f;
-    bool open = false, from_before = false;
-    int run_row = -1;
-    const bool me = g == 0 && active;
-    for (int gg = 0; gg < G; ++gg) {
-      const int fl = m_flag[gg];  // the same value on every lane
-      if (fl & 1) {
-        if (g == 0) {
-          if (VEC) {
-            const float* src = m_vec + gg * VECF + f0c;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) run[i] += src[i];
-          }
-          rds += m_ds[gg * L + l];
-        }
-        if (gg == 0) {
-          from_before = true;
-          open = true;
-          run_row = m_hrow[0];
-        }
-        if (!(fl & 2)) {
-          if (me) {
-            if (from_before) bwd_stage_store<VEC>(a, 2 * seg, f0, head, leader, run, rds);
-            else bwd_row_store<VEC>(a, run_row, f0, head, leader, run, rds);
-          }
-#pragma unroll
-          for (int i = 0; i < 8; ++i) run[i] = 0.f;
-          rds = 0.f;
-          open = false;
-          from_before = false;
-        }
-      }
-      if (fl & 4) {  // the piece that left chunk gg: from the registers of group gg
-        const int src = gg * L + l;
-        if (VEC) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) run[i] = __shfl(acc[i], src);
-        }
-        rds = __shfl(leave_ds, src);
-        run_row = m_trow[gg];
-        open = true;
-        from_before = false;
-      }
-    }
-    if (open && me) bwd_stage_store<VEC>(a, 2 * seg + (from_before ? 0 : 1), f0, head, leader, run, rds);
-  }
-
-  // ---- this wave's share of the empty rows
-  const int64_t nw = wg_count * wpb;
-  const int rpw = int((a.nrows + nw - 1) / nw);
-  const int64_t r0 = wid * rpw;
-  const int64_t r1 = r0 + rpw < a.nrows ? r0 + rpw : a.nrows;
+  float d = 0.f;
   if (active) {
-    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int64_t r = r0 + g; r < r1; r += G)
-      if (a.rowptr[r] == a.rowptr[r + 1]) bwd_row_store<VEC>(a, r, f0, head, leader, zero, 0.f);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d = fmaf(wacc[i], float(ur[i]), d);
   }
+  float ds = head_sum1(d, LH) - Ht::sum(csum);
+  if (w.whole) {
+    ds = across_groups_sum<L>(ds);
+    if (VEC) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = across_groups_sum<L>(acc[i]);
+    }
+    if (g) return;
+  }
+  if (!active || w.row < 0) return;
+  if (w.slot < 0) bwd_row_store<VEC>(a, row, f0, head, leader, acc, ds);
+  else bwd_stage_store<VEC>(a, w.slot, f0, head, leader, acc, ds);
 }
 
-// Follow-up kernel: sums the staged pieces of every row that crosses a segment border, in segment order.
+// Follow-up kernel: sums the staged pieces of every row that has several, in order.
 template <int L, bool VEC>
-__global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a) {
+__global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, const int4_t* __restrict__ split, int n_split) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -443,42 +217,33 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a) {
   const int f0c = active ? f0 : 0;
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
-  int64_t wg = blockIdx.x, wg_count = gridDim.x;
-  if (a.blocks)
-    wg = gat_bwd_enter_block(a, wg, wg_count, [&](const hgnn_seg_block& B) {
-      return (int64_t(B.n_split) + kWavesPerBlock * G - 1) / (kWavesPerBlock * G);
-    });
-  const int64_t i0 = (wg * kWavesPerBlock + wave) * G;
-  if (i0 >= a.n_split) return;
-  const int64_t idx = i0 + g;
-  int r = 0, sa = 0, sb = -1;
-  if (idx < a.n_split) {
-    r = a.split_row[idx];
-    sa = a.split_lo[idx];
-    sb = a.split_hi[idx];
-  }
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  if (i0 >= n_split) return;
+  int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
+  if (i0 + g < n_split) q = split[i0 + g];
   auto take = [&](float (&acc)[8], float& ds, int64_t slot) {
     if (VEC) {
       const half8_t o = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] += float(o[i]);
     }
-    ds += a.stage_ds[(slot * a.H + head) * 2];
+    ds += a.stage_ds[slot * a.H + head];
   };
-  if (idx < a.n_split && sb - sa <= 8) {
+  if (q[2] > 0 && q[2] <= 8) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
-    take(acc, ds, 2 * int64_t(sa) + 1);
-    for (int64_t k = int64_t(sa) + 1; k <= sb; ++k) take(acc, ds, 2 * k);
-    if (active) bwd_row_store<VEC>(a, r, f0, head, leader, acc, ds);
+    for (int k = 0; k < q[2]; ++k) take(acc, ds, int64_t(q[1]) + k);
+    GatBwdArgs b = a;
+    b.enter_block(q[3]);
+    if (active) bwd_row_store<VEC>(b, q[0], f0, head, leader, acc, ds);
   }
   for (int j = 0; j < G; ++j) {
-    const int rj = __shfl(r, j * L), sj = __shfl(sa, j * L), ej = __shfl(sb, j * L);
-    if (ej - sj <= 8) continue;
+    const int n = __shfl(q[2], j * L);
+    if (n <= 8) continue;
+    const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
-    if (g == 0) take(acc, ds, 2 * int64_t(sj) + 1);
-    for (int64_t k = int64_t(sj) + 1 + g; k <= ej; k += G) take(acc, ds, 2 * k);
+    for (int k = g; k < n; k += G) take(acc, ds, int64_t(first) + k);
 #pragma unroll
     for (int off = L; off < kWave; off <<= 1) {
       if (VEC) {
@@ -487,7 +252,9 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a) {
       }
       ds += __shfl_xor(ds, off);
     }
-    if (g == 0 && active) bwd_row_store<VEC>(a, rj, f0, head, leader, acc, ds);
+    GatBwdArgs b = a;
+    b.enter_block(bj);
+    if (g == 0 && active) bwd_row_store<VEC>(b, rj, f0, head, leader, acc, ds);
   }
 }
 
@@ -556,29 +323,38 @@ __global__ __launch_bounds__(kBlock) void gat_vtab_kernel(const float* __restric
   }
 }
 
-template <bool OFF32, bool VEC, bool FLY>
-static void launch_bwd_seg(int L, dim3 grid, int threads, size_t lds, hipStream_t s, const GatBwdArgs& a) {
+template <int L, bool NEAR, bool VEC>
+static void launch_bwd_tasks_l(int lh, unsigned waves, hipStream_t s, const GatBwdArgs& a, const TaskView& v, int ncols) {
+  if (lh == 1) gat_bwd_task_kernel<L, NEAR, VEC, 1><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else if (lh == 2) gat_bwd_task_kernel<L, NEAR, VEC, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else if (lh == 4) gat_bwd_task_kernel<L, NEAR, VEC, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v, ncols);
+  else gat_bwd_task_kernel<L, NEAR, VEC, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v, ncols);
+}
+
+template <bool NEAR, bool VEC>
+static void launch_bwd_tasks(int L, int lh, unsigned waves, hipStream_t s, const GatBwdArgs& a, const TaskView& v, int ncols) {
   switch (L) {
-    case 1: gat_bwd_seg_kernel<1, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    case 2: gat_bwd_seg_kernel<2, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    case 4: gat_bwd_seg_kernel<4, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    case 8: gat_bwd_seg_kernel<8, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    case 16: gat_bwd_seg_kernel<16, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    case 32: gat_bwd_seg_kernel<32, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
-    default: gat_bwd_seg_kernel<64, OFF32, VEC, FLY><<<grid, threads, lds, s>>>(a); break;
+    case 1: launch_bwd_tasks_l<1, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    case 2: launch_bwd_tasks_l<2, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    case 4: launch_bwd_tasks_l<4, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    case 8: launch_bwd_tasks_l<8, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    case 16: launch_bwd_tasks_l<16, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    case 32: launch_bwd_tasks_l<32, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
+    default: launch_bwd_tasks_l<64, NEAR, VEC>(lh, waves, s, a, v, ncols); break;
   }
 }
 
 template <bool VEC>
-static void launch_bwd_finish(int L, dim3 grid, hipStream_t s, const GatBwdArgs& a) {
+static void launch_bwd_finish(int L, hipStream_t s, const GatBwdArgs& a, const TaskView& v) {
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
   switch (L) {
-    case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    case 2: gat_bwd_finish_kernel<2, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    case 4: gat_bwd_finish_kernel<4, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    case 8: gat_bwd_finish_kernel<8, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    case 16: gat_bwd_finish_kernel<16, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    case 32: gat_bwd_finish_kernel<32, VEC><<<grid, kBlock, 0, s>>>(a); break;
-    default: gat_bwd_finish_kernel<64, VEC><<<grid, kBlock, 0, s>>>(a); break;
+    case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 2: gat_bwd_finish_kernel<2, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 4: gat_bwd_finish_kernel<4, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 8: gat_bwd_finish_kernel<8, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 16: gat_bwd_finish_kernel<16, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 32: gat_bwd_finish_kernel<32, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    default: gat_bwd_finish_kernel<64, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
   }
 }
 
@@ -619,44 +395,22 @@ static void launch_vtab(int L, dim3 grid, hipStream_t s, const float* el, const 
 #undef HGNN_VTAB
 }
 
-// one pass (segment kernel + follow-up) over the graph in `a` with the segment arrays of plan q
+// one pass (row tasks t of plan q, follow-up)
 template <bool VEC>
-static hgnn_status run_bwd_segments(const hgnn_plan* q, GatBwdArgs a, int ncols, hipStream_t s) {
-  a.seg_lo = q->seg_row_lo;
-  a.seg_hi = q->seg_row_hi;
-  a.S = q->S;
-  a.nseg = q->nseg;
-  a.staging = reinterpret_cast<half_t*>(q->staging);
-  a.stage_ds = q->stage_mz;
+static hgnn_status run_bwd_tasks(const hgnn_plan* q, const hgnn_row_tasks* t, GatBwdArgs a, int ncols, hipStream_t s) {
+  a.staging = reinterpret_cast<half_t*>(t->staging);
+  a.stage_ds = t->stage_mz;
   a.stage_ld = q->max_F;
-  a.split_row = q->split_row;
-  a.split_lo = q->split_seg_lo;
-  a.split_hi = q->split_seg_hi;
-  a.n_split = q->n_split;
-  const int L = pow2_at_least(a.F / 8);
-  const bool off32 = uint64_t(ncols) * uint64_t(a.ldx) * 2u < (uint64_t(1) << 32);
-  // weights formed in the main loop: measured 0.26 -> 0.17 ms for the transposed pass with 4 heads of 16 (12 -> 20
-  // waves per compute unit); with one head 3-15 % faster up to 64 features, 1-3 % slower from 128 on (every lane of
-  // the head repeats the scalar work)
-  const bool fly = a.H >= 2 || a.D <= 64;
-  const size_t per_wave = size_t(gat_bwd_lds_layout(a.S, a.H, L, VEC, fly, off32).total);
-  const int wpb = waves_per_block_for_lds(per_wave, true);
-  const size_t lds = per_wave * wpb;
-  HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-               "hgnn_gat_backward_fused: seg_edges = %d with H = %d needs %zu bytes of LDS per wavefront (limit 65536)", a.S,
-               a.H, lds);
-  const int64_t nblk = ceil_div(q->nseg, wpb);
-  dim3 grid(unsigned(nblk > 0 ? nblk : 1));
-  if (fly) {
-    if (off32) launch_bwd_seg<true, VEC, true>(L, grid, wpb * kWave, lds, s, a);
-    else launch_bwd_seg<false, VEC, true>(L, grid, wpb * kWave, lds, s, a);
-  } else {
-    if (off32) launch_bwd_seg<true, VEC, false>(L, grid, wpb * kWave, lds, s, a);
-    else launch_bwd_seg<false, VEC, false>(L, grid, wpb * kWave, lds, s, a);
+  const int L = pow2_at_least(a.F / 8), lh = a.D / 8;
+  const TaskView v = task_view(t, kWave / L);
+  const int waves = v.first_wave[t->nb];
+  if (waves > 0) {
+    if (near_table(ncols, a.ldx)) launch_bwd_tasks<true, VEC>(L, lh, unsigned(waves), s, a, v, ncols);
+    else launch_bwd_tasks<false, VEC>(L, lh, unsigned(waves), s, a, v, ncols);
+    HGNN_LAUNCH_CHECK("gat_bwd_task_kernel");
   }
-  HGNN_LAUNCH_CHECK("gat_bwd_seg_kernel");
-  if (a.n_split > 0) {
-    launch_bwd_finish<VEC>(L, dim3(unsigned(ceil_div(a.n_split, int64_t(kWavesPerBlock) * (kWave / L)))), s, a);
+  if (v.n_split > 0) {
+    launch_bwd_finish<VEC>(L, s, a, v);
     HGNN_LAUNCH_CHECK("gat_bwd_finish_kernel");
   }
   return HGNN_OK;
@@ -665,50 +419,23 @@ static hgnn_status run_bwd_segments(const hgnn_plan* q, GatBwdArgs a, int ncols,
 // a pass over graph gg with plan q (column-blocked or not)
 template <bool VEC>
 static hgnn_status run_bwd_pass(const hgnn_plan* q, const hgnn_csr* gg, GatBwdArgs a, hipStream_t s) {
-  if (q->nb <= 1) return run_bwd_segments<VEC>(q, a, gg->ncols, s);
+  if (q->nb <= 1) return run_bwd_tasks<VEC>(q, q->tasks, a, gg->ncols, s);
+  if (q->fine) q = q->fine;
   const size_t V = size_t(q->nrows);
   const int64_t ds_stride = int64_t(V) * q->max_H * 2;
   const int L = pow2_at_least(a.F / 8);
   {
-    // all blocks in one launch of each kernel: workgroups numbered block after block and dispatched in that order
+    // all blocks in one launch: waves numbered block after block and dispatched in that order
     GatBwdArgs ab = a;
+    ab.col = q->bcol;
     ab.Y = reinterpret_cast<half_t*>(q->bstage);
     ab.ldy = q->max_F;
     ab.dsum = nullptr;
     ab.dsum_f32 = q->bsum;
-    ab.blocks = q->bdesc;
-    ab.nblocks = q->nb;
     ab.y_stride = int64_t(V) * q->max_F;
     ab.ds_stride = ds_stride;
-    ab.S = q->S;
-    ab.stage_ld = q->max_F;
-    const bool off32 = uint64_t(gg->ncols) * uint64_t(ab.ldx) * 2u < (uint64_t(1) << 32);
-    const bool fly = ab.H >= 2 || ab.D <= 64;  // as in run_bwd_segments
-    const size_t per_wave = size_t(gat_bwd_lds_layout(ab.S, ab.H, L, VEC, fly, off32).total);
-    const int wpb = waves_per_block_for_lds(per_wave, true);
-    const size_t lds = per_wave * wpb;
-    HGNN_REQUIRE(lds <= 65536, HGNN_EUNSUPPORTED,
-                 "hgnn_gat_backward_fused: seg_edges = %d with H = %d needs %zu bytes of LDS per wavefront (limit 65536)", ab.S,
-                 ab.H, lds);
-    int64_t wgs = 0, wgs2 = 0;
-    for (const hgnn_plan* sub : q->sub) {
-      const int64_t c = ceil_div(sub->nseg, wpb);
-      wgs += c > 0 ? c : 1;
-      wgs2 += ceil_div(sub->n_split, int64_t(kWavesPerBlock) * (kWave / L));
-    }
-    const dim3 grid{unsigned(wgs)};
-    if (fly) {
-      if (off32) launch_bwd_seg<true, VEC, true>(L, grid, wpb * kWave, lds, s, ab);
-      else launch_bwd_seg<false, VEC, true>(L, grid, wpb * kWave, lds, s, ab);
-    } else {
-      if (off32) launch_bwd_seg<true, VEC, false>(L, grid, wpb * kWave, lds, s, ab);
-      else launch_bwd_seg<false, VEC, false>(L, grid, wpb * kWave, lds, s, ab);
-    }
-    HGNN_LAUNCH_CHECK("gat_bwd_seg_kernel");
-    if (wgs2 > 0) {
-      launch_bwd_finish<VEC>(L, dim3(unsigned(wgs2)), s, ab);
-      HGNN_LAUNCH_CHECK("gat_bwd_finish_kernel");
-    }
+    const hgnn_status st = run_bwd_tasks<VEC>(q, q->btasks, ab, gg->ncols, s);
+    if (st != HGNN_OK) return st;
   }
   launch_bwd_block_sum<VEC>(L, dim3(unsigned(ceil_div(gg->nrows, int64_t(kWavesPerBlock) * (kWave / L)))), s, a,
                             reinterpret_cast<const half_t*>(q->bstage), q->max_F, q->bsum, ds_stride, q->nb);
@@ -791,7 +518,6 @@ static hgnn_status gat_backward_impl(const char* who, const hgnn_csr* g, const h
     t.Y = reinterpret_cast<half_t*>(dV);
     t.ldy = lddv;
     t.dsum = reinterpret_cast<half_t*>(d_er);
-    t.dst_is_col = 1;
     st = run_bwd_pass<true>(pt, gt, t, s);
     if (st != HGNN_OK) return st;
   }
@@ -807,7 +533,6 @@ static hgnn_status gat_backward_impl(const char* who, const hgnn_csr* g, const h
     f.R = reinterpret_cast<const half_t*>(dOut);
     f.ldr = lddo;
     f.dsum = reinterpret_cast<half_t*>(d_el);
-    f.dst_is_col = 0;
     st = run_bwd_pass<false>(p, g, f, s);
     if (st != HGNN_OK) return st;
   }

@@ -2,6 +2,8 @@
 // group eight at a time and gathers table rows.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace hgnn {
@@ -206,5 +208,65 @@ __device__ __forceinline__ float across_groups_max(float v) {
   if (L <= 32) v = xor32_mov(v, true);
   return v;
 }
+
+// ---- scores of a tile -------------------------------------------------------------------------------------------------
+// Every lane of a head holds its eight features' share of the scores of eight edges.  The shares are summed by halves: with
+// each exchange a lane keeps half of the edges, so a head of RS or more lanes ends with 8 / RS finished scores per
+// lane, and maximum, exponential and LeakyReLU are evaluated once per (edge, head), not once per lane.
+// Edges a lane ends up with: j * RS + own_edge(l), j = 0 .. 8 / RS - 1.
+template <int RS>
+struct HeadTile {
+  static constexpr int NS = 8 / RS;
+  static __device__ __forceinline__ int own_edge(int l) {
+    if (RS < 8) return l & (RS - 1);
+    const int b2 = (l >> 2) & 1;  // the last exchange mirrors eight lanes: the upper four keep mirrored edges
+    return b2 ? 4 | ((l & 3) ^ 3) : (l & 3);
+  }
+  static constexpr int lane_of(int e) { return RS < 8 ? e : (e & 4 ? 4 | ((e & 3) ^ 3) : e); }
+  template <int CTRL>
+  static __device__ __forceinline__ float halve(float a, float b, bool upper) {  // lower lanes keep a, upper ones b
+    const float keep = upper ? b : a, send = upper ? a : b;
+    return keep + dpp_mov<CTRL>(send);
+  }
+  static __device__ __forceinline__ void scores(const float (&d)[8], int l, float (&s)[NS]) {
+    const bool flip = RS == 8 && (l & 4);
+    const bool u0 = ((l & 1) != 0) != flip, u1 = ((l & 2) != 0) != flip, u2 = (l & 4) != 0;
+    if constexpr (RS == 1) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j] = d[j];
+    } else {
+      float r[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = halve<0xB1>(d[2 * j], d[2 * j + 1], u0);
+      if constexpr (RS == 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] = r[j];
+      } else {
+        float t[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) t[j] = halve<0x4E>(r[2 * j], r[2 * j + 1], u1);
+        if constexpr (RS == 4) {
+          s[0] = t[0];
+          s[1] = t[1];
+        } else {
+          s[0] = halve<0x141>(t[0], t[1], u2);
+        }
+      }
+    }
+  }
+  // the value of edge U of the tile, from the lane of this head that holds it
+  template <int U>
+  static __device__ __forceinline__ float from_owner(const float (&v)[NS]) {
+    if constexpr (RS == 1) return v[U];
+    else return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v[U / RS]), (0x1f & ~(RS - 1)) | (lane_of(U % RS) << 5)));
+  }
+  static __device__ __forceinline__ float sum(float v) { return head_sum1(v, RS); }  // over the RS lanes
+  static __device__ __forceinline__ float max_of(float v) {
+    if (RS >= 2) v = fmaxf(v, dpp_mov<0xB1>(v));
+    if (RS >= 4) v = fmaxf(v, dpp_mov<0x4E>(v));
+    if (RS >= 8) v = fmaxf(v, dpp_mov<0x141>(v));
+    return v;
+  }
+};
 
 }  // namespace hgnn
