@@ -191,6 +191,13 @@ __device__ __forceinline__ int seg_slots_per_lane(int S) { return 4 * ((S + 255)
 // between kernels (config 3: the next kernel's reads of the column ids 15 % slower), hence the size rule.
 __host__ __device__ inline bool stream_nontemporal(int64_t nnz) { return nnz * 4 > (int64_t(64) << 20); }
 
+__device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
+  float p = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) p = fmaf(float(a[i]), float(b[i]), p);
+  return p;
+}
+
 // four consecutive rounds of a lane's reads from an index array, in flight together: v[q] = p[i0 + q * kWave], or 0
 // from position n on.  NT is a template parameter because a run-time choice between two loads of one address is
 // folded into a single ordinary load by the compiler.
@@ -395,6 +402,8 @@ struct hgnn_plan {
 namespace hgnn {
 // el[i,h] = a_l[h].U[i,h] and er[j,h] = a_r[h].Vt[j,h] into the plan's fp32 scratch (el first, then er;
 // Vt == nullptr skips er)
+hgnn_status gat_check(const hgnn_plan* p, int H, int D, const hgnn_half* U, int64_t ldu, const hgnn_half* Vt, int64_t ldv,
+                      const hgnn_half* a_l, const hgnn_half* a_r, const char* who);  // what the projection needs of its arguments
 hgnn_status gat_project(const hgnn_plan* p, const hgnn_csr* g, int H, int D, const hgnn_half* U, int64_t ldu,
                         const hgnn_half* Vt, int64_t ldv, const hgnn_half* a_l, const hgnn_half* a_r, hipStream_t s,
                         const char* who);

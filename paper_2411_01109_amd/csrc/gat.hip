@@ -35,7 +35,10 @@ struct GatArgs {
   int64_t ldx, ldy, nnz;
   int nrows, F, H, D;
   float slope;
-  const float* el;  // [nrows][H]
+  const float* el;  // [nrows][H], or nullptr: formed per piece from the row's own features
+  const half_t* U;  // row-side features [nrows][ldu] and their attention vector [H*D] (el == nullptr)
+  int64_t ldu;
+  const half_t* a_l;
   const half_t* a_r;  // [H*D]
   float* lse;       // [nrows][H] or nullptr
   float* part_mz;   // column blocks: [nrows][H][2] (m, z) of this block's partial rows; else nullptr
@@ -79,6 +82,7 @@ struct Soft {
     }
   }
   __device__ __forceinline__ void scale(float f) {
+#pragma clang fp contract(off)
     z *= f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= f;
@@ -90,19 +94,23 @@ struct Soft {
   }
 };
 
+// The sums of a row are written out in fused and plain operations, with nothing left to contraction: the kernels with and
+// without SAVE give the same bits.
+
 // a <- a merged with b (both rescaled to the larger maximum)
 template <bool SAVE>
 __device__ __forceinline__ void soft_merge(Soft<SAVE>& a, const Soft<SAVE>& b) {
+#pragma clang fp contract(off)
   const float M = fmaxf(a.m, b.m);
   if (M == -INFINITY) return;  // both empty
   const float fa = __expf(a.m - M), fb = __expf(b.m - M);  // exp(-inf) = 0 drops an empty side
-  a.z = a.z * fa + b.z * fb;
+  a.z = fmaf(b.z, fb, a.z * fa);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc[i] = a.acc[i] * fa + b.acc[i] * fb;
+  for (int i = 0; i < 8; ++i) a.acc[i] = fmaf(b.acc[i], fb, a.acc[i] * fa);
   if (SAVE) {
-    a.zm = a.zm * fa + b.zm * fb;
+    a.zm = fmaf(b.zm, fb, a.zm * fa);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a.accm[i] = a.accm[i] * fa + b.accm[i] * fb;
+    for (int i = 0; i < 8; ++i) a.accm[i] = fmaf(b.accm[i], fb, a.accm[i] * fa);
   }
   a.m = M;
 }
@@ -111,16 +119,17 @@ __device__ __forceinline__ void soft_merge(Soft<SAVE>& a, const Soft<SAVE>& b) {
 template <bool SAVE>
 __device__ __forceinline__ void soft_merge_normalised(Soft<SAVE>& a, float mp, float zp, float cp, const half8_t& o,
                                                       const half8_t& om) {
+#pragma clang fp contract(off)
   const float M = fmaxf(a.m, mp);
   if (M == -INFINITY) return;
   const float fa = __expf(a.m - M), fb = __expf(mp - M) * zp;
-  a.z = a.z * fa + fb;
+  a.z = fmaf(a.z, fa, fb);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc[i] = a.acc[i] * fa + fb * float(o[i]);
+  for (int i = 0; i < 8; ++i) a.acc[i] = fmaf(fb, float(o[i]), a.acc[i] * fa);
   if (SAVE) {
-    a.zm = a.zm * fa + fb * cp;
+    a.zm = fmaf(fb, cp, a.zm * fa);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a.accm[i] = a.accm[i] * fa + fb * float(om[i]);
+    for (int i = 0; i < 8; ++i) a.accm[i] = fmaf(fb, float(om[i]), a.accm[i] * fa);
   }
   a.m = M;
 }
@@ -130,7 +139,7 @@ __device__ __forceinline__ void store_vec8(half_t* p, int f0, const float (&v)[8
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     float r = v[i] * s;
-    asm("" : "+v"(r));  // rounded to fp32 first everywhere: some instantiations fused the product into the conversion
+    asm("" : "+v"(r));  // rounded to fp32 first, not fused into the conversion
     h[i] = half_t(r);
   }
   *reinterpret_cast<half8_t*>(p + f0) = h;
@@ -190,6 +199,7 @@ __device__ __forceinline__ void soft_add(Soft<SAVE>& t, const float (&p)[8 / RS]
 // SAVE: 169 -> 109 us; 114 M edges, one head of 64: 2.12 -> 1.06 ms; 108 k edges, eight heads of 8: 26 -> 7.5 us.
 template <int L, bool NEAR, bool SAVE, int RS>
 __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(GatArgs a, TaskView v, int ncols) {
+#pragma clang fp contract(off)
   constexpr int G = kWave / L;
   typedef Round<L> Rd;
   typedef HeadTile<RS> Ht;
@@ -213,7 +223,13 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   int* const s_hnd = s_handles + g * Rd::PITCH;
   const RowTable<NEAR> table(a.X, ncols, a.ldx, f0c);
   const int row = w.row >= 0 ? w.row : 0;
-  const float el = a.el[int64_t(row) * a.H + head];
+  float el;
+  if (a.el) {
+    el = a.el[int64_t(row) * a.H + head];
+  } else {
+    el = dot8(*reinterpret_cast<const half8_t*>(a.a_l + f0c), *reinterpret_cast<const half8_t*>(a.U + int64_t(row) * a.ldu + f0c));
+    el = head_sum1(active ? el : 0.f, LH);
+  }
   half2_t ar2[4];
   {
     const half8_t t = *reinterpret_cast<const half8_t*>(a.a_r + f0c);
@@ -348,19 +364,29 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   if (i0 >= n_split) return;
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (i0 + g < n_split) q = split[i0 + g];
-  auto take = [&](Soft<SAVE>& t, int64_t slot) {
-    const half8_t o = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
-    half8_t om = o;
-    float cp = 0.f;
-    if (SAVE) {
-      om = *reinterpret_cast<const half8_t*>(a.staging_m + slot * a.stage_ld + f0c);
-      cp = a.stage_c[slot * a.H + head];
+  // merges the pieces first, first + stride, ... < end, four of them in flight at a time
+  auto take = [&](Soft<SAVE>& t, int first, int end, int stride) {
+    for (int k0 = first; k0 < end; k0 += 4 * stride) {
+      half8_t o[4], om[4];
+      float m[4], z[4], cp[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u * stride;
+        const int64_t slot = k < end ? k : k0;
+        o[u] = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
+        om[u] = SAVE ? *reinterpret_cast<const half8_t*>(a.staging_m + slot * a.stage_ld + f0c) : o[u];
+        m[u] = a.stage_mz[(slot * a.H + head) * 2];
+        z[u] = a.stage_mz[(slot * a.H + head) * 2 + 1];
+        cp[u] = SAVE ? a.stage_c[slot * a.H + head] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u * stride < end) soft_merge_normalised<SAVE>(t, m[u], z[u], cp[u], o[u], om[u]);
     }
-    soft_merge_normalised<SAVE>(t, a.stage_mz[(slot * a.H + head) * 2], a.stage_mz[(slot * a.H + head) * 2 + 1], cp, o, om);
   };
   if (q[2] > 0 && q[2] <= kShortPieces) {
     Soft<SAVE> t;
-    for (int k = 0; k < q[2]; ++k) take(t, int64_t(q[1]) + k);
+    take(t, q[1], q[1] + q[2], 1);
     GatArgs b = a;
     b.enter_block(q[3]);
     if (active) row_store<SAVE>(b, q[0], f0, head, leader, t);
@@ -370,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
     if (n <= kShortPieces) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     Soft<SAVE> t;
-    for (int k = g; k < n; k += G) take(t, int64_t(first) + k);
+    take(t, first + g, first + n, G);
 #pragma unroll
     for (int off = L; off < kWave; off <<= 1) {
       Soft<SAVE> o;
@@ -544,9 +570,11 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   HGNN_REQUIRE(out_masked == nullptr || (ldom % 8 == 0 && aligned16(out_masked)), HGNN_EUNSUPPORTED,
                "%s: needs ldom %% 8 == 0 and a 16-byte aligned out_masked", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // per-vertex projection into the plan's fp32 scratch: el[i,h] = a_l[h].U[i,h]; the column-side term is formed in
-  // the kernel from the gathered row
-  st = gat_project(p, g, H, D, U, ldu, nullptr, ldv, a_l, a_r, s, who);
+  // The row-side score term el[i,h] = a_l[h].U[i,h] is formed where a row's piece begins; over column blocks, which visit
+  // every row once per block, it comes from a projection of the vertices into the plan's scratch.  The column-side term is
+  // formed in the kernel from the gathered row.
+  if (p->nb > 1) st = gat_project(p, g, H, D, U, ldu, nullptr, ldv, a_l, a_r, s, who);
+  else st = gat_check(p, H, D, U, ldu, nullptr, ldv, a_l, a_r, who);
   if (st != HGNN_OK) return st;
   GatArgs a{};
   a.rowptr = g->rowptr;
@@ -561,7 +589,10 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   a.H = H;
   a.D = D;
   a.slope = neg_slope;
-  a.el = p->vscratch;
+  a.el = p->nb > 1 ? p->vscratch : nullptr;
+  a.U = reinterpret_cast<const half_t*>(U);
+  a.ldu = ldu;
+  a.a_l = reinterpret_cast<const half_t*>(a_l);
   a.a_r = reinterpret_cast<const half_t*>(a_r);
   a.lse = lse;
   a.Ym = reinterpret_cast<half_t*>(out_masked);

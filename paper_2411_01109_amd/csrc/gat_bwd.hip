@@ -221,18 +221,35 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   if (i0 >= n_split) return;
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (i0 + g < n_split) q = split[i0 + g];
-  auto take = [&](float (&acc)[8], float& ds, int64_t slot) {
-    if (VEC) {
-      const half8_t o = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
+  // adds the pieces first, first + stride, ... < end, four of them in flight at a time
+  auto take = [&](float (&acc)[8], float& ds, int first, int end, int stride) {
+    for (int k0 = first; k0 < end; k0 += 4 * stride) {
+      half8_t o[4];
+      float d[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += float(o[i]);
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u * stride;
+        o[u] = half8_t(0);
+        d[u] = 0.f;
+        if (k < end) {
+          if (VEC) o[u] = *reinterpret_cast<const half8_t*>(a.staging + int64_t(k) * a.stage_ld + f0c);
+          d[u] = a.stage_ds[int64_t(k) * a.H + head];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (VEC) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[i] += float(o[u][i]);
+        }
+        ds += d[u];
+      }
     }
-    ds += a.stage_ds[slot * a.H + head];
   };
   if (q[2] > 0 && q[2] <= 8) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
-    for (int k = 0; k < q[2]; ++k) take(acc, ds, int64_t(q[1]) + k);
+    take(acc, ds, q[1], q[1] + q[2], 1);
     GatBwdArgs b = a;
     b.enter_block(q[3]);
     if (active) bwd_row_store<VEC>(b, q[0], f0, head, leader, acc, ds);
@@ -243,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
-    for (int k = g; k < n; k += G) take(acc, ds, int64_t(first) + k);
+    take(acc, ds, first + g, first + n, G);
 #pragma unroll
     for (int off = L; off < kWave; off <<= 1) {
       if (VEC) {
@@ -283,43 +300,51 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_block_sum_kernel(GatBwdArgs a,
   bwd_row_store<VEC>(a, r, f0, head, (f0 % a.D) == 0, acc, ds);
 }
 
-// vtab[i,h] = (el[i,h], lse[i,h], t[i,h] = <dOut[i,h], out[i,h]>, 0) for every destination vertex.  With the masked
-// result and weight sum that the saving forward pass left (outm, csum), the gradient of the row-side score term is
-// a per-vertex expression and is written here: d_el[i,h] = <dOut[i,h], outm[i,h]> - t[i,h] * csum[i,h].
+// Everything the passes need of single vertices, in one launch: er[j,h] = a_r[h].Vt[j,h] for every source vertex, and for every
+// destination vertex vtab[i,h] = (a_l[h].U[i,h], lse[i,h], t[i,h] = <dOut[i,h], out[i,h]>, 0).  With the masked result and
+// weight sum that the saving forward pass left (outm, csum), the gradient of the row-side score term is a per-vertex
+// expression and is written here: d_el[i,h] = <dOut[i,h], outm[i,h]> - t[i,h] * csum[i,h].
+struct VertexArgs {
+  const half_t *U, *Vt, *a_l, *a_r, *dOut, *out, *outm;  // outm, csum, d_el: nullptr without the saved tensors
+  int64_t ldu, ldv, lddo, ldo, ldom;
+  const float *lse, *csum;
+  int nrows, ncols, F, D, H;
+  float4* vtab;
+  float* er;
+  half_t* d_el;
+};
+
 template <int L>
-__global__ __launch_bounds__(kBlock) void gat_vtab_kernel(const float* __restrict__ el, const float* __restrict__ lse,
-                                                           const half_t* __restrict__ dOut, int64_t lddo,
-                                                           const half_t* __restrict__ out, int64_t ldo, int nv, int F, int D,
-                                                           int H, float4* __restrict__ vtab, const half_t* __restrict__ outm,
-                                                           int64_t ldom, const float* __restrict__ csum,
-                                                           half_t* __restrict__ d_el) {
+__global__ __launch_bounds__(kBlock) void gat_vtab_kernel(VertexArgs a) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
-  const bool active = f0 < F;
-  const int LH = D / 8;
+  const bool active = f0 < a.F;
+  const int f0c = active ? f0 : 0;
+  const int LH = a.D / 8;
   const int64_t v = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G + g;
-  float p = 0.f, pm = 0.f;
-  if (active && v < nv) {
-    const half8_t x = *reinterpret_cast<const half8_t*>(dOut + v * lddo + f0);
-    const half8_t y = *reinterpret_cast<const half8_t*>(out + v * ldo + f0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) p = fmaf(float(x[i]), float(y[i]), p);
-    if (outm) {
-      const half8_t ym = *reinterpret_cast<const half8_t*>(outm + v * ldom + f0);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) pm = fmaf(float(x[i]), float(ym[i]), pm);
+  auto load = [&](const half_t* p, int64_t ld) { return *reinterpret_cast<const half8_t*>(p + v * ld + f0c); };
+  const bool dst = active && v < a.nrows, src = active && v < a.ncols;
+  float el = 0.f, er = 0.f, p = 0.f, pm = 0.f;
+  if (dst) {
+    const half8_t x = load(a.dOut, a.lddo);
+    el = dot8(*reinterpret_cast<const half8_t*>(a.a_l + f0c), load(a.U, a.ldu));
+    p = dot8(x, load(a.out, a.ldo));
+    if (a.outm) pm = dot8(x, load(a.outm, a.ldom));
+  }
+  if (src) er = dot8(*reinterpret_cast<const half8_t*>(a.a_r + f0c), load(a.Vt, a.ldv));
+  el = head_sum1(el, LH);
+  er = head_sum1(er, LH);
+  p = head_sum1(p, LH);
+  if (a.outm) pm = head_sum1(pm, LH);
+  if ((l % LH) == 0) {
+    const int64_t k = v * a.H + l / LH;
+    if (src) a.er[k] = er;
+    if (dst) {
+      a.vtab[k] = make_float4(el, a.lse[k], p, 0.f);
+      if (a.outm) a.d_el[k] = half_t(pm - p * a.csum[k]);
     }
-  }
-  for (int off = 1; off < LH; off <<= 1) {
-    p += __shfl_xor(p, off);
-    pm += __shfl_xor(pm, off);
-  }
-  if (active && v < nv && (l % LH) == 0) {
-    const int64_t k = v * H + l / LH;
-    vtab[k] = make_float4(el[k], lse[k], p, 0.f);
-    if (outm) d_el[k] = half_t(pm - p * csum[k]);
   }
 }
 
@@ -372,27 +397,16 @@ static void launch_bwd_block_sum(int L, dim3 grid, hipStream_t s, const GatBwdAr
   }
 }
 
-struct VtabSaved {
-  const half_t* outm;
-  int64_t ldom;
-  const float* csum;
-  half_t* d_el;
-};
-
-static void launch_vtab(int L, dim3 grid, hipStream_t s, const float* el, const float* lse, const half_t* dOut, int64_t lddo,
-                        const half_t* out, int64_t ldo, int nv, int F, int D, int H, float4* vtab, const VtabSaved& q) {
-#define HGNN_VTAB(LL) \
-  gat_vtab_kernel<LL><<<grid, kBlock, 0, s>>>(el, lse, dOut, lddo, out, ldo, nv, F, D, H, vtab, q.outm, q.ldom, q.csum, q.d_el)
+static void launch_vtab(int L, dim3 grid, hipStream_t s, const VertexArgs& a) {
   switch (L) {
-    case 1: HGNN_VTAB(1); break;
-    case 2: HGNN_VTAB(2); break;
-    case 4: HGNN_VTAB(4); break;
-    case 8: HGNN_VTAB(8); break;
-    case 16: HGNN_VTAB(16); break;
-    case 32: HGNN_VTAB(32); break;
-    default: HGNN_VTAB(64); break;
+    case 1: gat_vtab_kernel<1><<<grid, kBlock, 0, s>>>(a); break;
+    case 2: gat_vtab_kernel<2><<<grid, kBlock, 0, s>>>(a); break;
+    case 4: gat_vtab_kernel<4><<<grid, kBlock, 0, s>>>(a); break;
+    case 8: gat_vtab_kernel<8><<<grid, kBlock, 0, s>>>(a); break;
+    case 16: gat_vtab_kernel<16><<<grid, kBlock, 0, s>>>(a); break;
+    case 32: gat_vtab_kernel<32><<<grid, kBlock, 0, s>>>(a); break;
+    default: gat_vtab_kernel<64><<<grid, kBlock, 0, s>>>(a); break;
   }
-#undef HGNN_VTAB
 }
 
 // one pass (row tasks t of plan q, follow-up)
@@ -484,17 +498,22 @@ static hgnn_status gat_backward_impl(const char* who, const hgnn_csr* g, const h
   HGNN_REQUIRE(!saved || (ldom % 8 == 0 && aligned16(out_masked)), HGNN_EUNSUPPORTED,
                "%s: needs ldom %% 8 == 0 and a 16-byte aligned out_masked", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // per-vertex scalars in plan p's scratch: el, er, then (el, lse, t) packed per destination vertex
-  st = gat_project(p, g, H, D, U, ldu, Vt, ldv, a_l, a_r, s, who);
+  // per-vertex scalars in plan p's scratch: er, and (el, lse, t) packed per destination vertex
+  st = gat_check(p, H, D, U, ldu, Vt, ldv, a_l, a_r, who);
   if (st != HGNN_OK) return st;
   const int L = pow2_at_least(F / 8), G = kWave / L;
-  const float* el = p->vscratch;
-  const float* er = p->vscratch + size_t(g->nrows) * H;
+  float* er = p->vscratch + size_t(g->nrows) * H;
   float4* vtab = reinterpret_cast<float4*>(p->vtab);
-  if (g->nrows > 0) {
-    launch_vtab(L, dim3(unsigned(ceil_div(g->nrows, int64_t(kWavesPerBlock) * G))), s, el, lse,
-                reinterpret_cast<const half_t*>(dOut), lddo, reinterpret_cast<const half_t*>(out), ldo, g->nrows, F, D, H,
-                vtab, VtabSaved{reinterpret_cast<const half_t*>(out_masked), ldom, csum, reinterpret_cast<half_t*>(d_el)});
+  {
+    VertexArgs q{};
+    auto h = [](const hgnn_half* x) { return reinterpret_cast<const half_t*>(x); };
+    q.U = h(U), q.Vt = h(Vt), q.a_l = h(a_l), q.a_r = h(a_r), q.dOut = h(dOut), q.out = h(out), q.outm = h(out_masked);
+    q.ldu = ldu, q.ldv = ldv, q.lddo = lddo, q.ldo = ldo, q.ldom = ldom;
+    q.lse = lse, q.csum = csum;
+    q.nrows = g->nrows, q.ncols = g->ncols, q.F = F, q.D = D, q.H = H;
+    q.vtab = vtab, q.er = er, q.d_el = reinterpret_cast<half_t*>(d_el);
+    const int nv = g->nrows > g->ncols ? g->nrows : g->ncols;
+    launch_vtab(L, dim3(unsigned(ceil_div(nv, int64_t(kWavesPerBlock) * G))), s, q);
     HGNN_LAUNCH_CHECK("gat_vtab_kernel");
   }
   GatBwdArgs a{};

@@ -39,13 +39,6 @@ struct SddmmArgs {
 
 constexpr int kTile = 256;  // non-zeros per wave in the kernels that run without a plan
 
-__device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
-  float p = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) p = fmaf(float(a[i]), float(b[i]), p);
-  return p;
-}
-
 struct SddmmLds {
   int per, spad, col_off, row_off, blk_off, out_off, total;
 };
@@ -439,9 +432,8 @@ static hgnn_status launch_edge_score(const SddmmArgs& a, int64_t seg_blocks, hip
   return HGNN_OK;
 }
 
-hgnn_status gat_project(const hgnn_plan* p, const hgnn_csr* g, int H, int D, const hgnn_half* U, int64_t ldu,
-                        const hgnn_half* Vt, int64_t ldv, const hgnn_half* a_l, const hgnn_half* a_r, hipStream_t s,
-                        const char* who) {
+hgnn_status gat_check(const hgnn_plan* p, int H, int D, const hgnn_half* U, int64_t ldu, const hgnn_half* Vt, int64_t ldv,
+                      const hgnn_half* a_l, const hgnn_half* a_r, const char* who) {
   const int F = H * D, LH = D / 8;
   // Vt == nullptr: only the row side is wanted
   HGNN_REQUIRE(D % 8 == 0 && (LH & (LH - 1)) == 0 && F <= 512 && ldu % 8 == 0 && ldv % 8 == 0 && aligned16(U) &&
@@ -450,6 +442,15 @@ hgnn_status gat_project(const hgnn_plan* p, const hgnn_csr* g, int H, int D, con
                "%s: the per-vertex projection needs D = 8 * 2^k, H * D <= 512, ld %% 8 == 0 and 16-byte aligned U, Vt, a_l, a_r",
                who);
   HGNN_REQUIRE(H <= p->max_H, HGNN_EINVAL, "%s: H = %d exceeds the plan's max_H = %d", who, H, p->max_H);
+  return HGNN_OK;
+}
+
+hgnn_status gat_project(const hgnn_plan* p, const hgnn_csr* g, int H, int D, const hgnn_half* U, int64_t ldu,
+                        const hgnn_half* Vt, int64_t ldv, const hgnn_half* a_l, const hgnn_half* a_r, hipStream_t s,
+                        const char* who) {
+  const hgnn_status st = gat_check(p, H, D, U, ldu, Vt, ldv, a_l, a_r, who);
+  if (st != HGNN_OK) return st;
+  const int F = H * D;
   const int L = pow2_at_least(F / 8), G = kWave / L;
   float* el = p->vscratch;
   float* er = p->vscratch + size_t(g->nrows) * H;

@@ -177,12 +177,14 @@ __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 __device__ __forceinline__ float xor16_mov(float v, bool max_of) {
+#pragma clang fp contract(off)
   typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
   const uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);
   return max_of ? fmaxf(x, y) : x + y;
 }
 __device__ __forceinline__ float xor32_mov(float v, bool max_of) {
+#pragma clang fp contract(off)
   typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
   const uint2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);
@@ -190,6 +192,7 @@ __device__ __forceinline__ float xor32_mov(float v, bool max_of) {
 }
 template <int L>
 __device__ __forceinline__ float across_groups_sum(float v) {
+#pragma clang fp contract(off)
   if (L <= 1) v += dpp_mov<0xB1>(v);
   if (L <= 2) v += dpp_mov<0x4E>(v);
   if (L <= 4) v += dpp_mov<0x124>(v);
@@ -225,6 +228,7 @@ struct HeadTile {
   static constexpr int lane_of(int e) { return RS < 8 ? e : (e & 4 ? 4 | ((e & 3) ^ 3) : e); }
   template <int CTRL>
   static __device__ __forceinline__ float halve(float a, float b, bool upper) {  // lower lanes keep a, upper ones b
+#pragma clang fp contract(off)
     const float keep = upper ? b : a, send = upper ? a : b;
     return keep + dpp_mov<CTRL>(send);
   }
