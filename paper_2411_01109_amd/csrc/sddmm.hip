@@ -1,14 +1,11 @@
 // fp16 SDDMM for gfx950 (paper sections 2.1.2 and 5.1): per non-zero, a reduction along the
 // feature dimension of the row vertex's and the column vertex's vectors.
 //
-// Edge-parallel over the plan's segments: a wave owns one segment of consecutive non-zeros and
-// each group of L lanes takes a contiguous chunk of it, four non-zeros per step.  Every lane
-// loads 16 bytes (8 halves) of the column vertex's row -- the wide per-lane load of section
-// 5.1.3 -- while the row vertex's vector stays in registers for as long as the row does not
-// change.  The four partial dot products of a step are reduced across the lanes of a head with a
-// transposing butterfly (each exchange halves the number of live values), so a step costs 2+1
-// exchanges instead of 4*log2(D/8).  Results are collected in LDS and written back coalesced.
-#include "common.h"
+// Over a plan's row tasks a lane group stays inside one row: that row's vector is in registers, every lane loads 16 bytes (8
+// halves) of the column vertices' rows -- the wide per-lane load of section 5.1.3 -- eight non-zeros at a time, and the
+// eight partial dot products are summed by halves across the lanes of a head.  Results are collected in LDS and written
+// back coalesced.  The narrower loads of the vector-width study run over the plan's segments of consecutive non-zeros.
+#include "task.h"
 
 namespace hgnn {
 
@@ -18,7 +15,6 @@ struct SddmmArgs {
   const int* erow;  // COO row ids from the caller, or nullptr (then the row is searched in rowptr)
   const int* seg_lo;
   const int* seg_hi;
-  const int* eid;  // result slot of every non-zero (column-blocked plans), or nullptr: slot = position
   const half_t* U;
   const half_t* Vt;
   const half_t* a_l;
@@ -31,10 +27,7 @@ struct SddmmArgs {
   int nrows, ncols;
   int H, D, F, S;
   float slope;
-  // all column blocks of a plan in one launch (workgroups numbered block after block): the table of the blocks'
-  // arrays, or nullptr when the arrays above describe the one graph of the launch
-  const hgnn_seg_block* blocks;
-  int nblocks;
+  const int* delta;  // column blocks: slot = position in the block + delta[block][row], else nullptr: slot = position
 };
 
 constexpr int kTile = 256;  // non-zeros per wave in the kernels that run without a plan
@@ -55,11 +48,8 @@ __host__ __device__ inline SddmmLds sddmm_lds_layout(int S, int H) {
 }
 
 // DOT over one plan segment per wave:  out[k,h] = <U[row k, h], Vt[col k, h]>
-// MASK: one head whose length is not a multiple of 8 -- the group's lanes cover the padded row pitch and
-// the elements past D are forced to zero on both operands (whatever the padding columns hold).
-// VW = halves per lane and load: 8 (16 bytes), or 4 / 2 for the vector-width study of section 6.3.1 (a head
-// then spans D/VW lanes and the reduction across lanes has more rounds).
-template <int L, int VW, bool MASK>
+// VW = halves per lane and load: 4 or 2, for the vector-width study of section 6.3.1 (a head spans D/VW lanes).
+template <int L, int VW>
 __global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
   constexpr int G = kWave / L;
   typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
@@ -69,19 +59,9 @@ __global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
   const int f0 = VW * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int LH = MASK ? L : a.D / VW;  // lanes per head (power of two)
+  const int LH = a.D / VW;  // lanes per head (power of two)
   const int head = f0c / a.D;
-  const int nvalid = active ? a.F - f0 : 0;  // MASK: elements of this lane's vector that exist
-  const bool writer = MASK || active;         // MASK: every lane of the group may end up holding a result
-  auto load8 = [&](const half_t* p) -> hv_t {
-    hv_t v = *reinterpret_cast<const hv_t*>(p);
-    if (MASK && nvalid < VW) {
-#pragma unroll
-      for (int i = 0; i < VW; ++i)
-        if (i >= nvalid) v[i] = half_t(0);
-    }
-    return v;
-  };
+  auto load8 = [&](const half_t* p) -> hv_t { return *reinterpret_cast<const hv_t*>(p); };
   auto dot = [&](const hv_t& x, const hv_t& y) -> float {
     float p = 0.f;
 #pragma unroll
@@ -99,23 +79,6 @@ __global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
 
   const int wpb = int(blockDim.x) / kWave;
   int64_t wg = blockIdx.x;
-  if (a.blocks) {  // find this workgroup's block and take over its arrays
-    int b = 0;
-    for (;;) {
-      const int64_t c = (a.blocks[b].nseg + wpb - 1) / wpb;
-      if (wg < c || b + 1 == a.nblocks) break;
-      wg -= c;
-      ++b;
-    }
-    const hgnn_seg_block& B = a.blocks[b];
-    a.rowptr = B.rowptr;
-    a.col = B.col;
-    a.eid = B.eid;
-    a.seg_lo = B.seg_lo;
-    a.seg_hi = B.seg_hi;
-    a.nseg = B.nseg;
-    a.nnz = B.nnz;
-  }
   const int64_t seg = wg * wpb + wave;
   const bool valid = seg < a.nseg;
   const int64_t e0 = seg * S;
@@ -170,7 +133,7 @@ __global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
         p[0] = (b1 ? p[1] : p[0]) + r;  // edge 2*b0 + b1
         for (int off = 4; off < LH; off <<= 1) p[0] += __shfl_xor(p[0], off);
         const int e = i + 2 * int(b0) + int(b1);
-        if (writer && lh < 4 && e < c1) s_out[e * a.H + head] = half_t(p[0]);
+        if (active && lh < 4 && e < c1) s_out[e * a.H + head] = half_t(p[0]);
       } else {
         const int e = i + 2 * int(b0);
         if (active && e < c1) s_out[e * a.H + head] = half_t(p[0]);
@@ -186,18 +149,104 @@ __global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
   // coalesced write-back, 16 bytes per lane where the destination allows it
   const int tot = n * a.H;
   half_t* dst = a.out + e0 * a.H;
-  if (a.eid) {  // a column block: the non-zeros of a row piece are consecutive in the result, pieces are not
-    for (int j = lane; j < tot; j += kWave) {
-      const int k = j / a.H;
-      a.out[int64_t(a.eid[e0 + k]) * a.H + (j - k * a.H)] = s_out[j];
-    }
-  } else if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
+  if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
     const int nv = tot / 8;
     for (int j = lane; j < nv; j += kWave)
       reinterpret_cast<half8_t*>(dst)[j] = reinterpret_cast<const half8_t*>(s_out)[j];
     for (int j = nv * 8 + lane; j < tot; j += kWave) dst[j] = s_out[j];
   } else {
     for (int j = lane; j < tot; j += kWave) dst[j] = s_out[j];
+  }
+}
+
+// DOT over row tasks: out[k,h] = <U[row, h], Vt[col k, h]>.  MASK: one head whose length is not a multiple of 8 -- the group's
+// lanes cover the padded row pitch and the elements past D are forced to zero on both operands (whatever the padding
+// columns hold).  RS = min(lanes per head, 8).  Bound: the gathers (a row of 128 bytes is one request to the L2s).  Against
+// the walk over equal runs of non-zeros, whose row changes took most of its steps through a slow path: 114 M non-zeros, one
+// head of 64: 1.07 -> 0.98 ms; 5.5 M, four heads of 16: the same (62, 66 us).
+template <int L, bool NEAR, bool MASK, int RS>
+__global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(SddmmArgs a, TaskView v) {
+  constexpr int G = kWave / L;
+  typedef Round<L> Rd;
+  typedef HeadTile<RS> Ht;
+  __shared__ __align__(16) int s_handles[G * Rd::PITCH];
+  __shared__ __align__(16) half_t s_results[kWave * Rd::R];  // [G][R * H]: H is at most L
+  const int lane = threadIdx.x;
+  const int g = lane / L, l = lane % L;
+  const int f0 = 8 * l;
+  const bool active = f0 < a.F;
+  const int f0c = active ? f0 : 0;
+  const int head = MASK ? 0 : f0c / a.D;
+  const int LH = MASK ? L : a.D / 8;        // lanes per head (power of two)
+  const int nvalid = active ? a.F - f0 : 0; // MASK: elements of this lane's vector that exist
+  auto masked = [&](half8_t x) -> half8_t {
+    if (MASK) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = i < nvalid ? x[i] : half_t(0);
+    }
+    return x;
+  };
+  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  int* const s_hnd = s_handles + g * Rd::PITCH;
+  half_t* const s_out = s_results + g * (Rd::R * L);
+  const RowTable<NEAR> table(a.Vt, a.ncols, a.ldv, f0c);
+  const int row = w.row >= 0 ? w.row : 0;
+  const half8_t ur = masked(*reinterpret_cast<const half8_t*>(a.U + int64_t(row) * a.ldu + f0c));
+  const int64_t shift = a.delta ? int64_t(a.delta[int64_t(w.block) * a.nrows + row]) - w.first : 0;
+  const int own = (lane & (Rd::LC - 1)) * Rd::E;
+  const int edge = Ht::own_edge(l);
+  for (int k = w.beg; k < w.end; k += w.step) {
+    const int end = k + w.span < w.end ? k + w.span : w.end;
+    wave_sync();  // the previous round has been read
+    {
+      int c[Rd::E];
+      load_run<Rd::E, false>(a.col, k + own, end, c);
+#pragma unroll
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
+#pragma unroll
+      for (int m = 0; m < Rd::E; m += 4)
+        *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
+    }
+    wave_sync();
+    for (int q = 0; k + q < end; q += 8) {
+      int h8[8];
+      const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        h8[u] = ha[u];
+        h8[4 + u] = hb[u];
+      }
+      half8_t x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = table.row(h8[u]);
+      float d[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) d[u] = dot8(ur, masked(x[u]));
+      if (RS == 8 && LH > 8) {  // heads of more than eight lanes: the eights are added first
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          d[u] += dpp_mov<0x128>(d[u]);
+          if (LH > 16) d[u] = xor16_mov(d[u], false);
+          if (LH > 32) d[u] = xor32_mov(d[u], false);
+        }
+      }
+      float s[Ht::NS];
+      Ht::scores(d, l, s);
+      if (MASK || active) {
+#pragma unroll
+        for (int j = 0; j < Ht::NS; ++j) s_out[(q + j * RS + edge) * a.H + head] = half_t(s[j]);
+      }
+    }
+    wave_sync();
+    const int n = (end - k) * a.H;
+    half_t* dst = a.out + (int64_t(k) + shift) * a.H;
+    for (int j = 4 * l; j < n; j += 4 * L) {
+      if (j + 4 <= n) {
+        __builtin_memcpy(dst + j, __builtin_assume_aligned(s_out + j, 8), 8);
+      } else {
+        for (int i = j; i < n; ++i) dst[i] = s_out[i];
+      }
+    }
   }
 }
 
@@ -380,28 +429,38 @@ static void launch_edge(int L, dim3 grid, size_t lds, hipStream_t s, const Sddmm
 }
 
 template <int VW>
-static void launch_seg_vw(int L, bool mask, dim3 grid, int threads, size_t lds, hipStream_t s, const SddmmArgs& a) {
-#define LAUNCH_SEG(LL)                                                                   \
-  do {                                                                                  \
-    if (mask && VW == 8) sddmm_seg_kernel<LL, 8, true><<<grid, threads, lds, s>>>(a);   \
-    else sddmm_seg_kernel<LL, VW, false><<<grid, threads, lds, s>>>(a);                 \
-  } while (0)
+static void launch_seg_vw(int L, dim3 grid, int threads, size_t lds, hipStream_t s, const SddmmArgs& a) {
   switch (L) {
-    case 1: LAUNCH_SEG(1); break;
-    case 2: LAUNCH_SEG(2); break;
-    case 4: LAUNCH_SEG(4); break;
-    case 8: LAUNCH_SEG(8); break;
-    case 16: LAUNCH_SEG(16); break;
-    case 32: LAUNCH_SEG(32); break;
-    default: LAUNCH_SEG(64); break;
+    case 1: sddmm_seg_kernel<1, VW><<<grid, threads, lds, s>>>(a); break;
+    case 2: sddmm_seg_kernel<2, VW><<<grid, threads, lds, s>>>(a); break;
+    case 4: sddmm_seg_kernel<4, VW><<<grid, threads, lds, s>>>(a); break;
+    case 8: sddmm_seg_kernel<8, VW><<<grid, threads, lds, s>>>(a); break;
+    case 16: sddmm_seg_kernel<16, VW><<<grid, threads, lds, s>>>(a); break;
+    case 32: sddmm_seg_kernel<32, VW><<<grid, threads, lds, s>>>(a); break;
+    default: sddmm_seg_kernel<64, VW><<<grid, threads, lds, s>>>(a); break;
   }
-#undef LAUNCH_SEG
 }
 
-static void launch_seg(int L, int vw, bool mask, dim3 grid, int threads, size_t lds, hipStream_t s, const SddmmArgs& a) {
-  if (vw == 8) launch_seg_vw<8>(L, mask, grid, threads, lds, s, a);
-  else if (vw == 4) launch_seg_vw<4>(L, false, grid, threads, lds, s, a);
-  else launch_seg_vw<2>(L, false, grid, threads, lds, s, a);
+template <int L, bool NEAR>
+static void launch_dot_tasks_l(int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
+  if (mask) sddmm_task_kernel<L, NEAR, true, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v);
+  else if (lh == 1) sddmm_task_kernel<L, NEAR, false, 1><<<waves, kWave, 0, s>>>(a, v);
+  else if (lh == 2) sddmm_task_kernel<L, NEAR, false, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v);
+  else if (lh == 4) sddmm_task_kernel<L, NEAR, false, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v);
+  else sddmm_task_kernel<L, NEAR, false, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v);
+}
+
+template <bool NEAR>
+static void launch_dot_tasks(int L, int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
+  switch (L) {
+    case 1: launch_dot_tasks_l<1, NEAR>(lh, mask, waves, s, a, v); break;
+    case 2: launch_dot_tasks_l<2, NEAR>(lh, mask, waves, s, a, v); break;
+    case 4: launch_dot_tasks_l<4, NEAR>(lh, mask, waves, s, a, v); break;
+    case 8: launch_dot_tasks_l<8, NEAR>(lh, mask, waves, s, a, v); break;
+    case 16: launch_dot_tasks_l<16, NEAR>(lh, mask, waves, s, a, v); break;
+    case 32: launch_dot_tasks_l<32, NEAR>(lh, mask, waves, s, a, v); break;
+    default: launch_dot_tasks_l<64, NEAR>(lh, mask, waves, s, a, v); break;
+  }
 }
 
 static void launch_proj(int L, dim3 grid, hipStream_t s, const half_t* feat, int64_t ld, int nv, const half_t* avec, int F,
@@ -535,38 +594,39 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
   }
   if ((vec || masked) && !score && p) {
     // halves per lane: the plan's setting, when the shape allows a narrower load than 16 bytes
-    int vw = p->vec_halves;
-    int Ls = L;
+    const int vw = p->vec_halves;
     if (vw != 8) {
       const int lh = D / vw;
       HGNN_REQUIRE(vec && F <= kWave * vw && D % vw == 0 && (lh & (lh - 1)) == 0, HGNN_EUNSUPPORTED,
                    "hgnn_sddmm: %d halves per lane needs F <= %d and D / %d a power of two", vw, kWave * vw, vw);
-      Ls = pow2_at_least(F / vw);
-    }
-    const size_t seg_per_wave = size_t(sddmm_lds_layout(a.S, H).total);
-    const int wpb = waves_per_block_for_lds(seg_per_wave, true);
-    const size_t lds = seg_per_wave * wpb;
-    if (lds <= 65536 && p->nb > 1 && !p->block_eid) {  // (a plan built over an edge-id map maps its blocks to that map's slots)
-      // column-blocked plan: block after block, so that the gathered slice of Vt stays cache resident; on the plan's
-      // finer cut where it has one (no partial rows here, so narrower blocks cost nothing)
-      if (p->fine) p = p->fine;
-      // one launch over all blocks: workgroups numbered block after block and dispatched in that order
-      SddmmArgs ab = a;
-      ab.blocks = p->bdesc;
-      ab.nblocks = p->nb;
-      int64_t wgs = 0;
-      for (const hgnn_plan* q : p->sub) wgs += ceil_div(q->nseg, wpb);
-      if (wgs > 0) {
-        launch_seg(Ls, vw, masked, dim3(unsigned(wgs)), wpb * kWave, lds, s, ab);
+      const size_t seg_per_wave = size_t(sddmm_lds_layout(a.S, H).total);
+      const int wpb = waves_per_block_for_lds(seg_per_wave, true);
+      const size_t lds = seg_per_wave * wpb;
+      if (lds <= 65536) {
+        const dim3 grid(unsigned(ceil_div(p->nseg, wpb)));
+        if (vw == 4) launch_seg_vw<4>(pow2_at_least(F / vw), grid, wpb * kWave, lds, s, a);
+        else launch_seg_vw<2>(pow2_at_least(F / vw), grid, wpb * kWave, lds, s, a);
         HGNN_LAUNCH_CHECK("sddmm_seg_kernel");
+        return HGNN_OK;
       }
-      return HGNN_OK;
     }
-    if (lds <= 65536) {
-      launch_seg(Ls, vw, masked, dim3(unsigned(ceil_div(p->nseg, wpb))), wpb * kWave, lds, s, a);
-      HGNN_LAUNCH_CHECK("sddmm_seg_kernel");
-      return HGNN_OK;
+    // column-blocked plan: block after block, so that the gathered slice of Vt stays cache resident (a plan built over an
+    // edge-id map maps its blocks to that map's slots)
+    const hgnn_row_tasks* t = p->tasks;
+    if (p->nb > 1 && !p->block_eid) {
+      if (p->fine) p = p->fine;
+      t = p->btasks;
+      a.col = p->bcol;
+      a.delta = p->bdelta;
     }
+    const TaskView v = task_view(t, kWave / L, 128, false);
+    const int waves = v.first_wave[t->nb];
+    if (waves > 0) {
+      if (near_table(g->ncols, ldv)) launch_dot_tasks<true>(L, LH, masked, unsigned(waves), s, a, v);
+      else launch_dot_tasks<false>(L, LH, masked, unsigned(waves), s, a, v);
+      HGNN_LAUNCH_CHECK("sddmm_task_kernel");
+    }
+    return HGNN_OK;
   }
   const size_t lds_tile = size_t(kTile) * H * sizeof(hgnn_half) * kWavesPerBlock;
   if (vec && lds_tile <= 65536) {
