@@ -10,17 +10,18 @@
 // divides 8 the head of each of a lane's 8 elements is fixed.  A row that fits the lanes'
 // registers is read once.  exp, sums and the division stay in fp32; the exponent is <= 0, so
 // the numerator is in (0,1] (section 3.1.2) and alpha is rounded once.
-#include "common.h"
+#include "task.h"
+
+#include <climits>
 
 namespace hgnn {
 
 constexpr int kKeepVec = 2;     // 8-element vectors per lane held in registers
-constexpr int kTeamThreads = 64;  // workgroup size of the team kernel: its waves never meet, so one wave each
 
 struct EdgeRowArgs {
   const int* rowptr;
   const int* big_row;
-  const int* row_list;  // when set, the team kernel takes its rows from this list of n_list rows
+  const int* row_list;  // when set, the wave-per-row tier takes its rows from this list of n_list rows
   int n_list;
   const int* eid;
   const half_t* x0;  // forward: e.          backward: alpha.   rowsum: t
@@ -30,8 +31,8 @@ struct EdgeRowArgs {
   float* out_f32;    // rowsum only: when set, the sums are written here in fp32 instead of out
   int64_t total;     // nnz * H
   int nrows, H;
-  int skip_above;    // rows longer than this are left to a later tier (0 = none)
-  int skip_below;    // rows of at most this many non-zeros were done by an earlier tier (-1 = none)
+  int team_max;      // rows longer than this are left by the sub-wave teams to a wave each
+  int wave_max;      // rows longer than this go to the chunked kernels (INT_MAX: there are none)
   float slope;
 };
 
@@ -39,7 +40,7 @@ struct EdgeRowArgs {
 // One step of an all-reduce (sum or maximum) among aligned groups of lanes: with the partner inside a row of 16
 // lanes the exchange is a DPP operand of the VALU instruction (lane ^ 1, lane ^ 2, then mirrors inside 8 and 16
 // lanes, which pair a lane with one from the other half, whose partial result is the same on all its lanes);
-// across rows it goes through ds_bpermute.
+// across rows it is one of the row swaps.
 template <int OFF, bool IS_MAX>
 __device__ __forceinline__ float team_step(float v) {
   float o;
@@ -47,7 +48,7 @@ __device__ __forceinline__ float team_step(float v) {
   else if (OFF == 2) o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));
   else if (OFF == 4) o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));
   else if (OFF == 8) o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, false));
-  else o = __shfl_xor(v, OFF);
+  else return OFF == 16 ? xor16_mov(v, IS_MAX) : xor32_mov(v, IS_MAX);
   return IS_MAX ? fmaxf(v, o) : v + o;
 }
 
@@ -272,21 +273,12 @@ __device__ __forceinline__ void rowsum_row(const EdgeRowArgs& a, const Team& tea
 
 enum { kFwd = 0, kBwd = 1, kSum = 2 };
 
+// one row by the team of LR lanes that the calling lane belongs to
 template <int OP, int LR, int H>
-__global__ __launch_bounds__(kBlock) void edge_row_team_kernel(EdgeRowArgs a) {
-  constexpr int GR = kWave / LR;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  int64_t row = (int64_t(blockIdx.x) * (int(blockDim.x) / kWave) + wave) * GR + lane / LR;
-  if (a.row_list) {
-    if (row >= a.n_list) return;
-    row = a.row_list[row];
-  }
-  if (row >= a.nrows) return;
-  const int beg = a.rowptr[row], end = a.rowptr[row + 1];
-  if ((a.skip_above > 0 && end - beg > a.skip_above) || end - beg <= a.skip_below) return;
+__device__ __forceinline__ void edge_row(const EdgeRowArgs& a, int row, int beg, int end) {
   const SubWaveTeam<LR> team;
   if (OP == kSum) {
-    rowsum_row<H>(a, team, int(row), beg, end);
+    rowsum_row<H>(a, team, row, beg, end);
   } else if (end > beg) {
     if (OP == kFwd) softmax_fwd_row<H>(a, team, int64_t(beg) * H, int64_t(end) * H);
     else softmax_bwd_row<H>(a, team, int64_t(beg) * H, int64_t(end) * H);
@@ -334,9 +326,8 @@ __device__ __forceinline__ void hub_chunk_range(const EdgeRowArgs& a, const HubC
 }
 
 template <int OP, int H>
-__global__ __launch_bounds__(kHubThreads) void edge_hub_partial_kernel(EdgeRowArgs a, HubChunks c) {
+__device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const HubChunks& c, int slot) {
   __shared__ float sm[(kHubThreads / kWave) * 8];
-  const int slot = blockIdx.x;
   int beg, end;
   hub_chunk_range(a, c, slot, beg, end);
   const int64_t j0 = int64_t(beg) * H, j1 = int64_t(end) * H;
@@ -397,6 +388,36 @@ __global__ __launch_bounds__(kHubThreads) void edge_hub_partial_kernel(EdgeRowAr
     c.part[(int64_t(slot) * H + threadIdx.x) * 2] = v0;
     c.part[(int64_t(slot) * H + threadIdx.x) * 2 + 1] = v1;
   }
+}
+
+// Every row of the graph in one launch: first the chunks of the long rows (n_chunks workgroups), then the wave-per-row tier
+// (wave_wgs workgroups), then the sub-wave teams.  The three used to be launches of their own, each with a tail in which
+// the chip drained: 5.5 M non-zeros x 4 heads, forward 75 -> 63 us with the follow-up, backward 74 -> 56, sums through a map 87 -> 80 + 5.
+template <int OP, int LR, int H>
+__global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, HubChunks c, int n_chunks, int wave_wgs) {
+  constexpr int W = kHubThreads / kWave;
+  int wg = int(blockIdx.x);
+  if (wg < n_chunks) {
+    edge_hub_partial<OP, H>(a, c, wg);
+    return;
+  }
+  wg -= n_chunks;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (wg < wave_wgs) {
+    int64_t row = int64_t(wg) * W + wave;
+    if (a.row_list) {
+      if (row >= a.n_list) return;
+      row = a.row_list[row];
+    }
+    if (row >= a.nrows) return;
+    const int beg = a.rowptr[row], end = a.rowptr[row + 1];
+    if (end - beg > a.team_max && end - beg <= a.wave_max) edge_row<OP, kWave, H>(a, int(row), beg, end);
+    return;
+  }
+  const int64_t row = (int64_t(wg - wave_wgs) * W + wave) * (kWave / LR) + lane / LR;
+  if (row >= a.nrows) return;
+  const int beg = a.rowptr[row], end = a.rowptr[row + 1];
+  if (end - beg <= a.team_max && end - beg <= a.wave_max) edge_row<OP, LR, H>(a, int(row), beg, end);
 }
 
 // softmax forward / backward: the row's partials combined, then this chunk's outputs
@@ -501,17 +522,17 @@ __global__ __launch_bounds__(kBlock) void edge_row_scalar_kernel(EdgeRowArgs a) 
 }
 
 template <int OP, int H>
-static void launch_team_h(int LR, dim3 grid, hipStream_t s, const EdgeRowArgs& a) {
+static void launch_rows_h(int LR, dim3 grid, hipStream_t s, const EdgeRowArgs& a, const HubChunks& c, int n_chunks, int wave_wgs) {
   switch (LR) {
-    case 4: edge_row_team_kernel<OP, 4, H><<<grid, kTeamThreads, 0, s>>>(a); break;
-    case 8: edge_row_team_kernel<OP, 8, H><<<grid, kTeamThreads, 0, s>>>(a); break;
-    case 16: edge_row_team_kernel<OP, 16, H><<<grid, kTeamThreads, 0, s>>>(a); break;
-    case 32: edge_row_team_kernel<OP, 32, H><<<grid, kTeamThreads, 0, s>>>(a); break;
-    default: edge_row_team_kernel<OP, 64, H><<<grid, kTeamThreads, 0, s>>>(a); break;
+    case 4: edge_rows_kernel<OP, 4, H><<<grid, kHubThreads, 0, s>>>(a, c, n_chunks, wave_wgs); break;
+    case 8: edge_rows_kernel<OP, 8, H><<<grid, kHubThreads, 0, s>>>(a, c, n_chunks, wave_wgs); break;
+    case 16: edge_rows_kernel<OP, 16, H><<<grid, kHubThreads, 0, s>>>(a, c, n_chunks, wave_wgs); break;
+    case 32: edge_rows_kernel<OP, 32, H><<<grid, kHubThreads, 0, s>>>(a, c, n_chunks, wave_wgs); break;
+    default: edge_rows_kernel<OP, 64, H><<<grid, kHubThreads, 0, s>>>(a, c, n_chunks, wave_wgs); break;
   }
 }
 
-// Launches the team kernel (and the chunked kernels when a plan lists long rows) for H in {1,2,4,8}.
+// Launches the row kernel (and the follow-up of the chunks when a plan lists long rows) for H in {1,2,4,8}.
 template <int OP>
 static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeRowArgs a, hipStream_t s) {
   const int H = a.H;
@@ -543,39 +564,30 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
   // instead of starting a wave for every row of the graph only to find most of them done
   const bool mid_list = p && LR < kWave && (big == 0 || big > p->mid_deg);
   if (mid_list && t1 < p->mid_deg) t1 = p->mid_deg;  // the sub-wave tier takes what the list leaves out
-  for (int tier = 0; tier < 2; ++tier) {
-    const int lr = tier == 0 ? LR : kWave;
-    if (tier == 1 && (LR == kWave || (big > 0 && t1 >= big))) break;
-    a.skip_below = tier == 0 ? -1 : t1;
-    a.skip_above = (tier == 0 && LR < kWave) ? (big > 0 && big < t1 ? big : t1) : big;
-    int64_t nrows_tier = g->nrows;
-    a.row_list = nullptr;
-    a.n_list = 0;
-    if (tier == 1 && mid_list) {
-      if (p->n_mid == 0) break;
+  if (LR == kWave) t1 = INT_MAX;  // every row has a wave anyway
+  a.team_max = t1;
+  a.wave_max = big > 0 ? big : INT_MAX;
+  const int64_t rows_per_wg = kHubThreads / kWave;
+  int64_t wave_wgs = 0;
+  if (LR < kWave && !(big > 0 && t1 >= big)) {
+    if (mid_list) {
       a.row_list = p->mid_row;
       a.n_list = p->n_mid;
-      nrows_tier = p->n_mid;
     }
-    dim3 grid(unsigned(ceil_div(nrows_tier, int64_t(kTeamThreads / kWave) * (kWave / lr))));
-    switch (H) {
-      case 1: launch_team_h<OP, 1>(lr, grid, s, a); break;
-      case 2: launch_team_h<OP, 2>(lr, grid, s, a); break;
-      case 4: launch_team_h<OP, 4>(lr, grid, s, a); break;
-      default: launch_team_h<OP, 8>(lr, grid, s, a); break;
-    }
-    HGNN_LAUNCH_CHECK("edge_row_team_kernel");
+    wave_wgs = ceil_div(mid_list ? int64_t(p->n_mid) : int64_t(g->nrows), rows_per_wg);
   }
+  const int n_chunks = big > 0 ? p->n_hub_chunks : 0;
+  const HubChunks c = big > 0 ? HubChunks{p->hub_chunk_row, p->hub_chunk_first, p->hub_chunk_count, p->hub_part} : HubChunks{};
+  const dim3 grid(unsigned(n_chunks + wave_wgs + ceil_div(g->nrows, rows_per_wg * (kWave / LR))));
+  switch (H) {
+    case 1: launch_rows_h<OP, 1>(LR, grid, s, a, c, n_chunks, int(wave_wgs)); break;
+    case 2: launch_rows_h<OP, 2>(LR, grid, s, a, c, n_chunks, int(wave_wgs)); break;
+    case 4: launch_rows_h<OP, 4>(LR, grid, s, a, c, n_chunks, int(wave_wgs)); break;
+    default: launch_rows_h<OP, 8>(LR, grid, s, a, c, n_chunks, int(wave_wgs)); break;
+  }
+  HGNN_LAUNCH_CHECK("edge_rows_kernel");
   if (big > 0) {
-    const HubChunks c{p->hub_chunk_row, p->hub_chunk_first, p->hub_chunk_count, p->hub_part};
-    dim3 gc(unsigned(p->n_hub_chunks));
-    switch (H) {
-      case 1: edge_hub_partial_kernel<OP, 1><<<gc, kHubThreads, 0, s>>>(a, c); break;
-      case 2: edge_hub_partial_kernel<OP, 2><<<gc, kHubThreads, 0, s>>>(a, c); break;
-      case 4: edge_hub_partial_kernel<OP, 4><<<gc, kHubThreads, 0, s>>>(a, c); break;
-      default: edge_hub_partial_kernel<OP, 8><<<gc, kHubThreads, 0, s>>>(a, c); break;
-    }
-    HGNN_LAUNCH_CHECK("edge_hub_partial_kernel");
+    const dim3 gc{unsigned(p->n_hub_chunks)};
     if (OP == kSum) {
       edge_hub_rowsum_kernel<<<dim3(unsigned(ceil_div(int64_t(p->n_big) * H, kBlock))), kBlock, 0, s>>>(a, c, p->big_first,
                                                                                                        p->n_big);
