@@ -413,7 +413,7 @@ hgnn_status check_spmm_args(const char* who, const hgnn_csr* g, const hgnn_half*
                             hgnn_half* Y, int64_t ldy, int F, hgnn_reduce op);
 hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X,
                       int64_t ldx, hgnn_half* Y, int64_t ldy, int32_t F, hgnn_reduce op, const float* row_scale,
-                      void* scratch, size_t scratch_bytes, hipStream_t s);
+                      void* scratch, size_t scratch_bytes, bool one_sweep, hipStream_t s);
 void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub);
@@ -433,6 +433,20 @@ inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 :
 struct TaskTotals {
   int32_t n_task, n_whole, n_zero, n_split, n_slots;
 };
+// The same without a plan, in memory of the caller and without a host wait: the launch shape is then not known on the host, so
+// the kernels read it from `sec` and `totals` and walk the tasks with a grid stride.
+struct TaskScratch {
+  int32_t* counts;
+  hgnn_task_sec* sec;
+  TaskTotals* totals;
+  int4* task;
+  int32_t* zrow;
+  int4* split;
+  float* staging;  // [slots][F rounded up to a multiple of 8] fp32
+  size_t bytes;
+};
+TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
 struct TaskCounts {
   DevTemp counts, sec;
   HostMail mail;

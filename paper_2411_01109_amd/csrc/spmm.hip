@@ -41,6 +41,7 @@ struct SpmmArgs {
   // discretized kernels
   half_t* staging;  // [slots][stage_ld] pieces of the rows that have several
   int stage_ld;
+  int stage32;   // 1: the pieces are staged in fp32 (staging is an array of floats)
   int atomic_y;  // 1: conflicting pieces are added to Y with packed fp16 atomics instead of being staged (comparison variant)
   // all column blocks of a plan in one launch: waves are numbered block after block (they are dispatched in that order, so
   // the compute units still gather from one slice of X at a time, without a drain between the blocks)
@@ -551,7 +552,7 @@ struct TaskLds {
 };
 
 template <int L, int WM, bool NEAR, bool MAPPED, int HV>
-__global__ __launch_bounds__(kWave, L < 8 ? 5 : (WM == 0 ? 8 : 7)) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
+__device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, int wid) {
   constexpr int G = kWave / L;
   typedef Round<L> Rd;
   typedef TaskLds<L, WM, HV> Lds;
@@ -565,7 +566,7 @@ __global__ __launch_bounds__(kWave, L < 8 ? 5 : (WM == 0 ? 8 : 7)) void spmm_tas
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;  // idle lanes of a group load a valid address and drop the result
-  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  const TaskWave w = task_enter<L>(v, wid, g);
   a.Y += int64_t(w.block) * a.block_y_stride;
   if (w.z1 > w.z0) {
     const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -674,16 +675,57 @@ __global__ __launch_bounds__(kWave, L < 8 ? 5 : (WM == 0 ? 8 : 7)) void spmm_tas
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= sc;
     atomic_add8(a.Y + int64_t(row) * a.ldy + f0, acc, a.F - f0);
+  } else if (WM < 2 && a.stage32) {
+    float* out = reinterpret_cast<float*>(a.staging) + int64_t(w.slot) * a.stage_ld + f0;
+    *reinterpret_cast<float4*>(out) = make_float4(acc[0] * sc, acc[1] * sc, acc[2] * sc, acc[3] * sc);
+    *reinterpret_cast<float4*>(out + 4) = make_float4(acc[4] * sc, acc[5] * sc, acc[6] * sc, acc[7] * sc);
   } else {
     store8(a.staging + int64_t(w.slot) * a.stage_ld + f0, acc, sc);
+  }
+}
+
+// LOOP: the number of tasks is only known on the device, a wave takes several (the loop costs registers: not with a plan)
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, bool LOOP>
+__global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
+  if (LOOP) {
+    const int n = task_waves<kWave / L>(v);
+    for (int wid = blockIdx.x; wid < n; wid += gridDim.x) spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, wid);
+  } else {
+    spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, blockIdx.x);
   }
 }
 
 // Pass 2 (section 5.2.3): adds the staged fp16 pieces of every row that has several (fp32, in order) and stores the row
 // once.  A wave owns G rows: rows of at most kFinishShort pieces are summed by their own lane group, longer ones by the
 // whole wave.
-template <int L>
-__global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split) {
+template <int STRIDE>
+__device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t first, int64_t last, int f0, float (&acc)[8]) {
+  const float* p = reinterpret_cast<const float*>(a.staging) + f0;
+  constexpr int U = 4;
+  for (int64_t k = first; k <= last; k += STRIDE * U) {
+    float4 lo[U], hi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t kk = k + u * STRIDE;
+      lo[u] = hi[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (kk <= last) {
+        lo[u] = *reinterpret_cast<const float4*>(p + kk * a.stage_ld);
+        hi[u] = *reinterpret_cast<const float4*>(p + kk * a.stage_ld + 4);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc[0] += lo[u].x, acc[1] += lo[u].y, acc[2] += lo[u].z, acc[3] += lo[u].w;
+      acc[4] += hi[u].x, acc[5] += hi[u].y, acc[6] += hi[u].z, acc[7] += hi[u].w;
+    }
+  }
+}
+
+// F32: pieces staged in fp32, n_split is a bound and the number is in *totals
+template <int L, bool F32>
+__global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split,
+                                                                  const TaskTotals* __restrict__ totals) {
+  if (F32) n_split = totals->n_split;
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -697,7 +739,8 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   half_t* const Y = a.Y;
   if (q[2] > 0 && q[2] <= kFinishShort) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    pieces_accumulate<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
+    if (F32) pieces_accumulate32<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
+    else pieces_accumulate<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
     a.Y = Y + int64_t(q[3]) * a.block_y_stride;
     if (active) store_row(a, q[0], f0, acc, 1.f);
   }
@@ -706,7 +749,8 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
     if (n <= kFinishShort) continue;
     const int r = __shfl(q[0], j * L), first = __shfl(q[1], j * L), b = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    pieces_accumulate<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
+    if (F32) pieces_accumulate32<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
+    else pieces_accumulate<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
     groups_reduce<L>(acc);
     a.Y = Y + int64_t(b) * a.block_y_stride;
     if (g == 0 && active) store_row(a, r, f0, acc, 1.f);
@@ -1105,6 +1149,13 @@ static PassLayout pass_layout(int64_t nrows, int npass, int F) {
   return o;
 }
 
+// The plan-free SpMM over row tasks: what it needs of the scratch, 0 where no row can be long (then one wave per row does)
+constexpr int kFreePiece = 512;  // non-zeros per piece
+static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
+  if (hub_layout(nnz, hub_threshold(nrows, nnz), F).bytes == 0) return 0;
+  return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F).bytes;
+}
+
 static HubLists hub_lists_at(void* base, const HubLayout& o) {
   HubLists h{};
   char* p = static_cast<char*>(base);
@@ -1203,8 +1254,17 @@ template <int L, bool NEAR>
 static void launch_tasks_l(int wm, bool mapped, unsigned waves, hipStream_t s, const SpmmArgs& a, const TaskView& v,
                            int ncols) {
   const dim3 grid(waves);
-#define HGNN_TASKS(WM, MAPPED, HV) \
-  spmm_task_kernel<L, WM, NEAR, MAPPED, HV><<<grid, kWave, TaskLds<L, WM, HV>::bytes(a.H), s>>>(a, v, ncols)
+#define HGNN_TASKS(WM, MAPPED, HV)                                                                                          \
+  do {                                                                                                                      \
+    const size_t lds = TaskLds<L, WM, HV>::bytes(a.H);                                                                      \
+    if constexpr (WM < 2) {                                                                                                 \
+      if (v.totals) {                                                                                                       \
+        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, true><<<grid, kWave, lds, s>>>(a, v, ncols);                              \
+        break;                                                                                                              \
+      }                                                                                                                     \
+    }                                                                                                                       \
+    spmm_task_kernel<L, WM, NEAR, MAPPED, HV, false><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
+  } while (0)
   const int hv = (reinterpret_cast<uintptr_t>(a.w) & uintptr_t(2 * a.H - 1)) == 0 ? a.H : 0;
   if (wm == 0) {
     HGNN_TASKS(0, false, 1);
@@ -1280,16 +1340,22 @@ static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const Tas
   }
 }
 
+template <int L>
+static void launch_task_finish_l(dim3 grid, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
+  if (a.stage32) spmm_task_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, v.totals);
+  else spmm_task_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, nullptr);
+}
+
 static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
   const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
   switch (L) {
-    case 1: spmm_task_finish_kernel<1><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 2: spmm_task_finish_kernel<2><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 4: spmm_task_finish_kernel<4><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 8: spmm_task_finish_kernel<8><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 16: spmm_task_finish_kernel<16><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 32: spmm_task_finish_kernel<32><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    default: spmm_task_finish_kernel<64><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 1: launch_task_finish_l<1>(grid, s, a, v); break;
+    case 2: launch_task_finish_l<2>(grid, s, a, v); break;
+    case 4: launch_task_finish_l<4>(grid, s, a, v); break;
+    case 8: launch_task_finish_l<8>(grid, s, a, v); break;
+    case 16: launch_task_finish_l<16>(grid, s, a, v); break;
+    case 32: launch_task_finish_l<32>(grid, s, a, v); break;
+    default: launch_task_finish_l<64>(grid, s, a, v); break;
   }
 }
 
@@ -1353,11 +1419,36 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
   }
 }
 
-// The plan-free SpMM with its hub scratch at `scratch` (scratch_bytes of device memory, may be null: then no row is
+// The plan-free SpMM over row tasks that are listed in the scratch by two small launches: rows sorted by length and cut into
+// pieces, so that lane groups end together and a hub keeps many compute units busy, as with a plan.  Pieces are staged in
+// fp32, a row is rounded once.  A wave per G rows in storage order, hubs in chunks of their own, took as long as its longest
+// row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.79 -> 1.25 ms together.
+static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, hipStream_t s) {
+  const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
+  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz)};
+  const hgnn_status st = task_build_in(q, t, s);
+  if (st != HGNN_OK) return st;
+  const int L = pow2_at_least((a.F + 7) / 8);
+  const bool mapped = a.w && a.eid;
+  int64_t grid = 0;
+  const TaskView v = task_view(t, q, g->nnz, kWave / L, mapped ? 512 : 128, &grid);
+  a.staging = reinterpret_cast<half_t*>(t.staging);
+  a.stage_ld = (a.F + 7) & ~7;
+  a.stage32 = 1;
+  const int wm = a.w ? 1 : 0;
+  if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), s, a, v, g->ncols);
+  else launch_tasks<false>(L, wm, mapped, unsigned(grid), s, a, v, g->ncols);
+  HGNN_LAUNCH_CHECK("spmm_task_kernel");
+  launch_task_finish(L, s, a, v);
+  HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
+  return HGNN_OK;
+}
+
+// The plan-free SpMM with its scratch at `scratch` (scratch_bytes of device memory, may be null: then no row is
 // treated as a hub and a long row is reduced by one wave).
 hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X,
                              int64_t ldx, hgnn_half* Y, int64_t ldy, int32_t F, hgnn_reduce op, const float* row_scale,
-                             void* scratch, size_t scratch_bytes, hipStream_t s) {
+                             void* scratch, size_t scratch_bytes, bool one_sweep, hipStream_t s) {
   SpmmArgs a = make_args(g, edge_val, H, X, ldx, Y, ldy, F, op, row_scale);
   if (!vector_path_ok(edge_val, H, X, ldx, Y, ldy, F)) {
     dim3 grid(unsigned(ceil_div(int64_t(g->nrows) * F, kBlock)));
@@ -1375,7 +1466,9 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
   const bool hubs = lay.bytes > 0 && scratch != nullptr;
   const int npass = scratch ? row_passes(g->nrows, g->ncols, g->nnz, F) : 1;
   const PassLayout pl = pass_layout(g->nrows, npass, F);
-  if (npass > 1 && scratch_bytes >= size_t(lay.bytes + pl.bytes)) {
+  const size_t base_bytes = spmm_hub_scratch_bytes(g->nrows, g->nnz, F), task_bytes = free_task_bytes(g->nrows, g->nnz, F);
+  const size_t rows_bytes = std::max(base_bytes, task_bytes);
+  if (npass > 1 && !one_sweep && scratch_bytes >= rows_bytes + size_t(pl.bytes)) {
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
     a.long_row = kPassLongRow > a.long_row ? kPassLongRow : a.long_row;
     if (hubs) {
@@ -1385,7 +1478,7 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     } else {
       a.long_row = INT_MAX;
     }
-    char* base = static_cast<char*>(scratch) + lay.bytes;
+    char* base = static_cast<char*>(scratch) + rows_bytes;
     int* cuts = reinterpret_cast<int*>(base + pl.o_cuts);
     float* part = reinterpret_cast<float*>(base + pl.o_part);
     const int width = int(ceil_div(g->ncols, npass));
@@ -1397,9 +1490,11 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     return HGNN_OK;
   }
   if (hubs) {
-    HGNN_REQUIRE(scratch_bytes >= size_t(lay.bytes), HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %lld", who,
-                 scratch_bytes, (long long)lay.bytes);
+    HGNN_REQUIRE(scratch_bytes >= (one_sweep ? base_bytes : rows_bytes), HGNN_EINVAL,
+                 "%s: the workspace holds %zu bytes, this graph needs %zu", who, scratch_bytes, rows_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
+    if (scratch_bytes >= task_bytes) return spmm_free_tasks(g, a, scratch, s);
+    // (the static array can be too small for the tasks and still hold the hubs)
     h = hub_lists_at(scratch, lay);
     hub_zero_kernel<<<1, kBlock, 0, s>>>(h);
     hub_scan_kernel<<<dim3(unsigned(ceil_div(g->nrows, kBlock * kScanRows))), kBlock, 0, s>>>(a, h);
@@ -1425,7 +1520,7 @@ extern "C" {
 
 size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F) {
   if (nrows <= 0 || nnz <= 0 || F <= 0) return 0;
-  size_t need = spmm_hub_scratch_bytes(nrows, nnz, F);
+  size_t need = std::max(spmm_hub_scratch_bytes(nrows, nnz, F), free_task_bytes(nrows, nnz, F));
   const int npass = ncols > 0 ? row_passes(nrows, ncols, nnz, F) : 1;
   if (npass > 1) need += size_t(pass_layout(nrows, npass, F).bytes);
   return need;
@@ -1438,7 +1533,7 @@ hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, c
   hgnn_status st = check_spmm_args("hgnn_spmm", g, edge_val, H, X, ldx, Y, ldy, F, op);
   if (st != HGNN_OK) return st;
   if (g->nrows == 0) return HGNN_OK;
-  return spmm_rows("hgnn_spmm", g, edge_val, H, X, ldx, Y, ldy, F, op, row_scale, workspace, workspace_bytes,
+  return spmm_rows("hgnn_spmm", g, edge_val, H, X, ldx, Y, ldy, F, op, row_scale, workspace, workspace_bytes, false,
                    static_cast<hipStream_t>(stream));
 }
 

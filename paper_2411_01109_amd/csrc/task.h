@@ -16,6 +16,7 @@ struct TaskView {
   const int* zrow;
   const hgnn_task_sec* sec;
   const int4_t* split;
+  const TaskTotals* totals;  // device; set where the host does not know the numbers (then one block, n_split is a bound)
   int n_split, nb;
   // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
   // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
@@ -72,6 +73,32 @@ __device__ __forceinline__ void load_run(const int* __restrict__ p, int i0, int 
       if (i0 + m < end) v[m] = q[m];
     }
   }
+}
+
+// the same for tasks whose numbers are on the device; *grid = workgroups to launch
+inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz, int G, int chunk, int64_t* grid) {
+  TaskView v{};
+  v.task = reinterpret_cast<const int4_t*>(t.task);
+  v.zrow = t.zrow;
+  v.sec = t.sec;
+  v.split = reinterpret_cast<const int4_t*>(t.split);
+  v.totals = t.totals;
+  v.n_split = int(nnz / q.S + 1);
+  v.nb = 1;
+  const int64_t n = nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
+  v.chunk = chunk;
+  while (v.chunk > 1 && int64_t(v.chunk) * 64 > n) v.chunk >>= 1;
+  constexpr int64_t kMostWaves = 65536;  // beyond this the waves take several tasks each
+  *grid = n < kMostWaves ? (n + 7) / 8 * 8 : kMostWaves;
+  return v;
+}
+
+// waves of work behind a view (G lane groups per wave)
+template <int G>
+__device__ __forceinline__ int task_waves(const TaskView& v) {
+  if (!v.totals) return v.first_wave[v.nb];
+  const hgnn_task_sec s = v.sec[0];
+  return ((s.nw + 7) & ~7) + ((((s.ng + G - 1) / G) + 7) & ~7) + (s.nz + G * kZeroTurns - 1) / (G * kZeroTurns);
 }
 
 // what one wave does

@@ -113,29 +113,63 @@ __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, i
 }
 
 // One workgroup per window and block: counting sort of the lane-group pieces by falling length.  The order of equal
-// pieces depends on the order in which the LDS counters are reached; no result does.
+// pieces depends on the order in which the LDS counters are reached; no result does.  SELF (one block): every workgroup adds
+// up the counts of the windows before it, instead of a launch that scans them; the first leaves section and totals.
+template <bool SELF>
 __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts,
-                                                                   const int* __restrict__ sums, const hgnn_task_sec* __restrict__ sec,
-                                                                   int4* __restrict__ task, int* __restrict__ zrow,
-                                                                   int4* __restrict__ split) {
+                                                                   const int* __restrict__ sums, hgnn_task_sec* __restrict__ sec,
+                                                                   TaskTotals* __restrict__ totals, int4* __restrict__ task,
+                                                                   int* __restrict__ zrow, int4* __restrict__ split) {
   __shared__ int at[kMaxGroupLen + 1];  // pieces of each length, then where the next one goes
   __shared__ int next[kTaskCounters];
   const int b = blockIdx.y, w = blockIdx.x;
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
-  const hgnn_task_sec s = sec[b];
+  __shared__ int before[kTaskCounters], all[kTaskCounters];
+  hgnn_task_sec s;
+  if (SELF) {
+    if (threadIdx.x < kTaskCounters) before[threadIdx.x] = all[threadIdx.x] = 0;
+    __syncthreads();
+    int b4[kTaskCounters] = {0, 0, 0, 0, 0}, sum[kTaskCounters] = {0, 0, 0, 0, 0};
+    for (int j = threadIdx.x; j < nwin; j += kTaskThreads) {
+#pragma unroll
+      for (int i = 0; i < kTaskCounters; ++i) {
+        const int n = counts[int64_t(i) * nwin + j];
+        sum[i] += n;
+        b4[i] += j < w ? n : 0;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kTaskCounters; ++i) {
+      for (int off = kWave / 2; off > 0; off >>= 1) {
+        b4[i] += __shfl_down(b4[i], off);
+        sum[i] += __shfl_down(sum[i], off);
+      }
+      if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&before[i], b4[i]);
+        atomicAdd(&all[i], sum[i]);
+      }
+    }
+    __syncthreads();
+    s = hgnn_task_sec{0, all[kTaskW], all[kTaskW], all[kTaskG], 0, all[kTaskZ], 0};
+    if (w == 0 && threadIdx.x == 0) {
+      *sec = s;
+      *totals = TaskTotals{all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskZ], all[kTaskSplit], all[kTaskSlots]};
+    }
+  } else {
+    s = sec[b];
+  }
   for (int i = threadIdx.x; i <= kMaxGroupLen; i += kTaskThreads) at[i] = 0;
   if (threadIdx.x < kTaskCounters) {
     const int i = threadIdx.x;
-    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? s.z_off : sums[i * q.nb + b];
-    next[i] = base + counts[(int64_t(i) * q.nb + b) * nwin + w];
+    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? s.z_off : (SELF ? 0 : sums[i * q.nb + b]);
+    next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
   }
   __syncthreads();
   RowCut cut[kTaskRowsPerThread];
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
-    cut[u] = RowCut{0, 0, -1};
-    if (r >= q.nrows) break;
-    cut[u] = cut_row(q, rp, int(r));
+    cut[u] = RowCut{0, 0, -1};  // no row
+    if (r < q.nrows) cut[u] = cut_row(q, rp, int(r));
     if (cut[u].m > 0 && cut[u].part <= q.group_max) {
       const int last = cut[u].len - (cut[u].m - 1) * cut[u].part;
       if (cut[u].m > 1) atomicAdd(&at[cut[u].part], cut[u].m - 1);
@@ -158,26 +192,36 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
     }
   }
   __syncthreads();
+  const int lane = threadIdx.x & (kWave - 1);
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const RowCut c = cut[u];
-    if (c.m < 0) break;
     const int r = w * kTaskWindow + u * kTaskThreads + int(threadIdx.x);
-    if (c.m == 0) {
-      zrow[atomicAdd(&next[kTaskZ], 1)] = r;
-      continue;
-    }
-    int slot = -1;
+    int slot = -1, pos = 0, k0 = 0;
+    if (c.m == 0) zrow[atomicAdd(&next[kTaskZ], 1)] = r;
     if (c.m > 1) {
       slot = atomicAdd(&next[kTaskSlots], c.m);
       split[atomicAdd(&next[kTaskSplit], 1)] = make_int4(r, slot, c.m, b);
     }
     const bool whole = c.part > q.group_max;
-    int pos = whole ? atomicAdd(&next[kTaskW], c.m) : 0;
-    const int k0 = s.first + rp[r];
-    for (int j = 0; j < c.m; ++j) {
-      const int n = j + 1 < c.m ? c.part : c.len - j * c.part;
-      const int p = whole ? pos++ : atomicAdd(&at[n], 1);
-      task[p] = make_int4(k0 + j * c.part, n | (b << 16), r, slot < 0 ? -1 : slot + j);
+    if (c.m > 0) {
+      if (whole) pos = atomicAdd(&next[kTaskW], c.m);
+      k0 = s.first + rp[r];
+    }
+    auto piece = [&](int j, int k, int part, int m, int len, bool wh, int at_w, int row, int sl) {
+      const int n = j + 1 < m ? part : len - j * part;
+      const int p = wh ? at_w + j : atomicAdd(&at[n], 1);
+      task[p] = make_int4(k + j * part, n | (b << 16), row, sl < 0 ? -1 : sl + j);
+    };
+    constexpr int kFew = 4;
+    if (c.m <= kFew)
+      for (int j = 0; j < c.m; ++j) piece(j, k0, c.part, c.m, c.len, whole, pos, r, slot);
+    // a row of many pieces: the whole wave writes them (its own lane took 20 us for the longest row of a power-law graph)
+    for (unsigned long long many = __ballot(c.m > kFew); many; many &= many - 1) {
+      const int src = __ffsll((long long)many) - 1;
+      const int m = __shfl(c.m, src), k = __shfl(k0, src), part = __shfl(c.part, src), len = __shfl(c.len, src);
+      const int at_w = __shfl(pos, src), row = __shfl(r, src), sl = __shfl(slot, src);
+      const bool wh = part > q.group_max;
+      for (int j = lane; j < m; j += kWave) piece(j, k, part, m, len, wh, at_w, row, sl);
     }
   }
 }
@@ -223,8 +267,8 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
   if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, tot.n_zero, 0};
   else HGNN_HIP(hipMemcpyAsync(t->host.data(), t->sec, sizeof(hgnn_task_sec) * size_t(q.nb), hipMemcpyDeviceToHost, s));
   if (nwin > 0)
-    task_write_kernel<<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts, sums, t->sec, t->task, t->zrow,
-                                                                                   t->split);
+    task_write_kernel<false><<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts, sums, t->sec, nullptr,
+                                                                                          t->task, t->zrow, t->split);
   HGNN_LAUNCH_CHECK("task_write_kernel");
   return HGNN_OK;
 }
@@ -244,6 +288,38 @@ hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s) {
   st = task_build(q, c, p->max_F, p->max_H, &p->btasks, s);
   HGNN_HIP(hipStreamSynchronize(s));
   return st;
+}
+
+TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F) {
+  // bounds from the sizes alone: a row of more than S non-zeros has at most len / S + 1 pieces, and there are fewer than
+  // nnz / S such rows
+  const int64_t nwin = ceil_div(nrows, kTaskWindow), over = nnz / S + 1;
+  TaskScratch t{};
+  char* const p = static_cast<char*>(base);
+  int64_t at = 0;
+  auto take = [&](int64_t bytes) {
+    char* r = p ? p + at : nullptr;
+    at += (bytes + 255) / 256 * 256;
+    return r;
+  };
+  t.sec = reinterpret_cast<hgnn_task_sec*>(take(sizeof(hgnn_task_sec)));
+  t.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
+  t.counts = reinterpret_cast<int32_t*>(take(nwin * kTaskCounters * 4));
+  t.task = reinterpret_cast<int4*>(take((nrows + over) * 16));
+  t.zrow = reinterpret_cast<int32_t*>(take(nrows * 4));
+  t.split = reinterpret_cast<int4*>(take(over * 16));
+  t.staging = reinterpret_cast<float*>(take(2 * over * int64_t((F + 7) & ~7) * 4));
+  t.bytes = size_t(at);
+  return t;
+}
+
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s) {
+  const int nwin = int(ceil_div(q.nrows, kTaskWindow));
+  task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
+  task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow,
+                                                                            t.split);
+  HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
+  return HGNN_OK;
 }
 
 void destroy_tasks(hgnn_row_tasks* t) {
