@@ -359,6 +359,11 @@ hgnn_status hgnn_scale_rows(int64_t n, int32_t F, const hgnn_half* X, int64_t ld
 hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* W, int64_t ldw,
                         int32_t trans_w, hgnn_half* Y, int64_t ldy, void* stream);
 
+/* hgnn_linear (trans_w = 0) for a weight of KW <= K rows: columns KW .. K-1 of X are padding and must hold zeros (any finite
+ * values give the same result); W is read up to its row KW - 1 only. */
+hgnn_status hgnn_linear_padded(int64_t n, int32_t K, int32_t KW, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* W,
+                               int64_t ldw, hgnn_half* Y, int64_t ldy, void* stream);
+
 /* dW[k, f] = sum_i X[i, k] * dY[i, f], fp32 [K][lddw >= F]: the gradient of the weight of hgnn_linear
  * (trans_w = 0) given the gradient dY of its output.  Partial sums of fixed row sets are written to the
  * workspace and added in a fixed order: no atomics, the same bits on every run.  workspace is device

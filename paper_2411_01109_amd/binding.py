@@ -27,7 +27,7 @@ EXPORTS = (
     "hgnn_edge_softmax_bwd", "hgnn_edge_rowsum", "hgnn_spmm_discretized_variant", "hgnn_plan_add_groups",
     "hgnn_plan_num_groups", "hgnn_plan_group_edges", "hgnn_plan_groups_export", "hgnn_plan_set_vector_halves",
     "hgnn_plan_vector_halves", "hgnn_spmm_workspace", "hgnn_plan_add_slices", "hgnn_plan_num_slices", "hgnn_edge_colsum", "hgnn_spmm_static", "hgnn_spmm_static_limit", "hgnn_gat_forward_fused", "hgnn_gat_alpha", "hgnn_gat_backward_fused",
-    "hgnn_edge_to_transposed", "hgnn_scale_rows", "hgnn_linear", "hgnn_linear_wgrad", "hgnn_linear_wgrad_workspace",
+    "hgnn_edge_to_transposed", "hgnn_scale_rows", "hgnn_linear", "hgnn_linear_padded", "hgnn_linear_wgrad", "hgnn_linear_wgrad_workspace",
     "hgnn_gat_feature_grad", "hgnn_gat_feature_grad_workspace", "hgnn_gat_forward_fused_save",
     "hgnn_gat_backward_fused_saved",
 )
@@ -130,6 +130,7 @@ def load() -> ctypes.CDLL:
     lib.hgnn_gat_backward_fused_saved.argtypes = [csr, vp, csr, vp, i32, i32, vp, i64, vp, i64, vp, vp, f32, vp, i64, vp, vp, i64,
                                                   vp, vp, i64, vp, i64, vp, vp, vp]
     lib.hgnn_linear.argtypes = [i64, i32, i32, vp, i64, vp, i64, i32, vp, i64, vp]
+    lib.hgnn_linear_padded.argtypes = [i64, i32, i32, i32, vp, i64, vp, i64, vp, i64, vp]
     lib.hgnn_linear_wgrad_workspace.argtypes = [i32, i32]
     lib.hgnn_linear_wgrad_workspace.restype = ctypes.c_size_t
     lib.hgnn_linear_wgrad.argtypes = [i64, i32, i32, vp, i64, vp, i64, vp, i64, vp, ctypes.c_size_t, vp]
@@ -150,6 +151,12 @@ def _check(status: int) -> None:
         raise HgnnError(status, f"{lib.hgnn_status_str(status).decode()}: {detail}")
 
 
+# A call's host time counts on small graphs (one of these calls is two to five kernels of 3 to 8 us): the current stream is
+# asked for as a number (0.15 us; a torch.cuda.Stream object costs 2.7 us), strides are fetched once.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _ptr(t: Optional[torch.Tensor], dtype=None) -> Optional[int]:
     if t is None:
         return None
@@ -162,14 +169,17 @@ def _ptr(t: Optional[torch.Tensor], dtype=None) -> Optional[int]:
 
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None:
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2 or t.stride(1) != 1:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1:
         raise ValueError("vertex-level tensors must be 2-D with unit stride along features")
-    return t.stride(0)
+    return st[0]
 
 
 class Csr:
@@ -438,10 +448,15 @@ def hgnn_scale_rows(X: torch.Tensor, scale: torch.Tensor, out: torch.Tensor, F: 
 
 def hgnn_linear(X: torch.Tensor, W: torch.Tensor, Y: torch.Tensor, trans_w: bool = False, K: Optional[int] = None,
                 F: Optional[int] = None, stream=None) -> None:
-    """Y = X.W (W is [K][F]) or X.W^T (trans_w, W is [F][K])."""
+    """Y = X.W (W is [K][F]) or X.W^T (trans_w, W is [F][K]).  A W of fewer than K rows: the other columns of X are zero padding."""
     K = X.shape[1] if K is None else K
     F = (W.shape[0] if trans_w else W.shape[1]) if F is None else F
-    _check(load().hgnn_linear(X.shape[0], K, F, _ptr(X, torch.float16), _ld(X), _ptr(W, torch.float16), _ld(W),
+    n, KW = X.shape[0], K if trans_w else W.shape[0]
+    if KW < K:  # the columns of X from KW on are padding: nothing is read past the rows of W
+        _check(load().hgnn_linear_padded(n, K, KW, F, _ptr(X, torch.float16), _ld(X), _ptr(W, torch.float16), _ld(W),
+                                         _ptr(Y, torch.float16), _ld(Y), _stream(stream)))
+        return
+    _check(load().hgnn_linear(n, K, F, _ptr(X, torch.float16), _ld(X), _ptr(W, torch.float16), _ld(W),
                               1 if trans_w else 0, _ptr(Y, torch.float16), _ld(Y), _stream(stream)))
 
 

@@ -33,6 +33,7 @@ struct LinearArgs {
   int KC;     // columns of X (rows of W) held in LDS at a time; a multiple of 32, and of the 128 columns of a group when K > KC
   int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
   int wvec;   // W may be read in 16-byte pieces
+  int KW;     // rows of W that exist (trans == 0): the others count as zero
 };
 
 // The weight tile W[kc .. kc+KC)[fc0 .. fc0+FC) into LDS in the order in which the products read it: fragment
@@ -71,7 +72,7 @@ __device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __res
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         row[j] = zero;
-        if (8 * k8 < kn) {  // K is a multiple of 8: the eight rows are inside the matrix or outside together
+        if (8 * k8 < kn && kc + 8 * k8 + j < a.KW) {
           const half_t* src = a.W + int64_t(kc + 8 * k8 + j) * a.ldw + fc0 + 8 * f8;
           if (a.wvec && 8 * f8 + 8 <= fn) {
             row[j] = *reinterpret_cast<const half8_t*>(src);
@@ -486,12 +487,9 @@ constexpr int kFeatGradBlocks = 1024;
 
 using namespace hgnn;
 
-extern "C" {
-
-hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* W, int64_t ldw,
-                        int32_t trans_w, hgnn_half* Y, int64_t ldy, void* stream) {
+static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW, int32_t F, const hgnn_half* X, int64_t ldx,
+                               const hgnn_half* W, int64_t ldw, int32_t trans_w, hgnn_half* Y, int64_t ldy, void* stream) {
   clear_error();
-  const char* who = "hgnn_linear";
   HGNN_REQUIRE(n >= 0 && K > 0 && F > 0, HGNN_EINVAL, "%s: n = %lld, K = %d, F = %d", who, static_cast<long long>(n), K, F);
   HGNN_REQUIRE(ldx >= K && ldy >= F && ldw >= (trans_w ? K : F), HGNN_EINVAL, "%s: leading dimension smaller than the row", who);
   HGNN_REQUIRE(K <= 65536 && F <= 65536, HGNN_EUNSUPPORTED, "%s: K = %d / F = %d above 65536", who, K, F);
@@ -500,7 +498,7 @@ hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int
   HGNN_REQUIRE(K % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y), HGNN_EUNSUPPORTED,
                "%s: needs K %% 8 == 0, ldx %% 8 == 0, ldy %% 8 == 0 and 16-byte aligned X, Y (pad with zeros)", who);
   LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw, trans_w ? 1 : 0,
-               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0};
+               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, KW};
   a.wvec = ldw % 8 == 0 && aligned16(W) ? 1 : 0;
   const int k32 = (K + 31) / 32 * 32, f32 = (F + 31) / 32 * 32;
   // short rows: several row tiles per wave, where that still leaves four waves for every compute unit
@@ -551,6 +549,22 @@ hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int
   if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, grid, threads, lds, s);
   if (nt == 4) return launch_linear<4, 1, false>(a, grid, threads, lds, s);
   return launch_linear<8, 1, false>(a, grid, threads, lds, s);
+}
+
+extern "C" {
+
+hgnn_status hgnn_linear(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* W, int64_t ldw,
+                        int32_t trans_w, hgnn_half* Y, int64_t ldy, void* stream) {
+  return linear_impl("hgnn_linear", n, K, K, F, X, ldx, W, ldw, trans_w, Y, ldy, stream);
+}
+
+hgnn_status hgnn_linear_padded(int64_t n, int32_t K, int32_t KW, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* W,
+                               int64_t ldw, hgnn_half* Y, int64_t ldy, void* stream) {
+  if (KW < 0 || KW > K) {
+    clear_error();
+    return fail(HGNN_EINVAL, "hgnn_linear_padded: KW = %d outside [0, K = %d]", KW, K);
+  }
+  return linear_impl("hgnn_linear_padded", n, K, KW, F, X, ldx, W, ldw, 0, Y, ldy, stream);
 }
 
 size_t hgnn_linear_wgrad_workspace(int32_t K, int32_t F) {

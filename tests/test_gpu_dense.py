@@ -223,3 +223,19 @@ def test_dense_at_dense_degree_size(hgnn, dev):
     hgnn.hgnn_linear_wgrad(Xd, Gd, dW, ws)
     dref, dsabs = oracle.linear_wgrad(X, G, want_sabs=True)
     check_f32("wgrad full", down(dW), dref, dsabs)
+
+
+@pytest.mark.parametrize("K,KW,F", [(104, 100, 256), (48, 42, 128), (104, 97, 8), (640, 601, 200)])
+def test_linear_weight_of_fewer_rows(hgnn, dev, K, KW, F):
+    """X padded to K columns, W of KW rows: what lies behind W in memory is not read."""
+    n = 700
+    r = np.random.default_rng(K + F)
+    Xh = np.zeros((n, K), dtype=np.float16)
+    Xh[:, :KW] = f16(r.standard_normal((n, KW)))
+    Wh = f16(r.standard_normal((KW, F)))
+    buf = torch.full((K + 8, F), float("nan"), dtype=torch.float16, device=dev)
+    buf[:KW] = up(Wh, dev)
+    Y = torch.empty((n, F), dtype=torch.float16, device=dev)
+    hgnn.hgnn_linear(up(Xh, dev), buf[:KW], Y)
+    ref, sabs = oracle.linear(np.ascontiguousarray(Xh[:, :KW]), Wh, want_sabs=True)
+    compare("linear, W of fewer rows", down(Y), ref, sabs)
