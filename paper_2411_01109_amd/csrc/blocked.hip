@@ -67,7 +67,7 @@ __global__ void block_delta_kernel(const int* __restrict__ cut, const int* __res
 
 // every non-zero k of the graph goes to its block, keeping its place inside the row piece
 __global__ void block_fill_kernel(hgnn_csr g, const int* __restrict__ cut, const int* __restrict__ goff, int nb, int width,
-                                  int* __restrict__ bcol, int* __restrict__ beid) {
+                                  int* __restrict__ bcol, uint16_t* __restrict__ bcol16, int* __restrict__ beid) {
   const int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= g.nnz) return;
   const int r = row_of_edge(g.rowptr, g.nrows, k);
@@ -75,10 +75,11 @@ __global__ void block_fill_kernel(hgnn_csr g, const int* __restrict__ cut, const
   const int b = c / width;
   const int64_t dest = int64_t(goff[int64_t(b) * g.nrows + r]) + (k - cut[int64_t(r) * (nb + 1) + b]);
   bcol[dest] = c;
+  if (bcol16) bcol16[dest] = uint16_t(c - b * width);
   beid[dest] = g.eid ? g.eid[k] : int(k);
 }
 
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_t s) {
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, hipStream_t s) {
   const int V = g->nrows;
   const int64_t E = g->nnz;
   const int width = int(ceil_div(g->ncols, nb));
@@ -95,6 +96,7 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_
   if (e == hipSuccess) e = dev_malloc(&goff, sizeof(int) * n_flat);
   if (e == hipSuccess) e = dev_malloc(&p->brp, sizeof(int) * size_t(nb) * (size_t(V) + 1));
   if (e == hipSuccess) e = dev_malloc(&p->bcol, sizeof(int) * size_t(E));
+  if (e == hipSuccess && tasks && width <= 65536) e = dev_malloc(&p->bcol16, sizeof(uint16_t) * size_t(E));
   if (e == hipSuccess) e = dev_malloc(&p->beid, sizeof(int) * size_t(E));
   // partial rows twice over and three scalars per row and head: the fused GAT pass that saves for its backward
   // leaves two vectors and (max, sum, masked sum) per block; row sums of edge tensors use one scalar
@@ -111,7 +113,7 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_
   if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
   if (e == hipSuccess) {
     block_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(nb) * (V + 1), kBlock))), kBlock, 0, s>>>(goff, V, nb, E, p->brp);
-    block_fill_kernel<<<dim3(unsigned(ceil_div(E, kBlock))), kBlock, 0, s>>>(*g, cut, goff, nb, width, p->bcol, p->beid);
+    block_fill_kernel<<<dim3(unsigned(ceil_div(E, kBlock))), kBlock, 0, s>>>(*g, cut, goff, nb, width, p->bcol, p->bcol16, p->beid);
     block_delta_kernel<<<dim3(unsigned(ceil_div(int64_t(n_flat), kBlock))), kBlock, 0, s>>>(cut, goff, V, nb, p->bdelta);
     e = hipGetLastError();
   }

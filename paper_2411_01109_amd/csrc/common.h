@@ -318,6 +318,8 @@ struct hgnn_row_tasks {
   int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
   hgnn_task_sec* sec = nullptr;  // [nb]
   int32_t n_split = 0, n_slots = 0;
+  const uint16_t* col16 = nullptr;  // column blocks of at most 65536 columns: the column ids less the block's first (the plan's)
+  int32_t width = 0;                // columns per block
   std::vector<hgnn_task_sec> host;  // sec on the host
   hgnn_half* staging = nullptr;  // [2][n_slots][max_F] partial vectors (second set: masked vectors of the saving GAT pass)
   float* stage_mz = nullptr;     // [3][n_slots][max_H] scalars of the partial vectors of the fused GAT passes
@@ -367,6 +369,7 @@ struct hgnn_plan {
   int32_t block_width = 0;
   int32_t* brp = nullptr;           // [nb][nrows+1] offset arrays of the blocks
   int32_t* bcol = nullptr;          // [nnz] column ids, block-major
+  uint16_t* bcol16 = nullptr;       // [nnz] the same less b*block_width, where the blocks' row tasks are used and 16 bits do
   int32_t* beid = nullptr;          // [nnz] slot in the edge tensors of every blocked non-zero: the creating graph's eid, else its CSR position
   int32_t* bdelta = nullptr;        // [nb][nrows] CSR position in the whole graph of a blocked non-zero = its block position + bdelta[b][row]
   std::vector<int64_t> boff;        // [nb+1] first non-zero of every block in bcol / beid
@@ -417,7 +420,7 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
 void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub);
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, hipStream_t s);
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, hipStream_t s);  // tasks: row tasks will walk them
 constexpr int kSliceMaxCols = 16384;  // columns per slice: 8 bytes each fill 128 KB of the 160 KB of LDS a workgroup may hold
 // row tasks in two steps around a host wait: task_count launches the counting passes, task_build takes their result
 struct TaskSource {

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
-      load_run<Rd::E, false>(a.col, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
 #pragma unroll
       for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
 #pragma unroll

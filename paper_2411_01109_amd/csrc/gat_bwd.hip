@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
-      load_run<Rd::E, false>(a.col, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
       if (NEAR) {
 #pragma unroll
         for (int m = 0; m < Rd::E; m += 4)

@@ -512,6 +512,7 @@ static void destroy_plan(hgnn_plan* p) {
   destroy_tasks(p->btasks);
   dev_free(p->brp);
   dev_free(p->bcol);
+  dev_free(p->bcol16);
   dev_free(p->beid);
   dev_free(p->bdelta);
   dev_free(p->bstage);
@@ -596,7 +597,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         if (nb > 16) nb = 16;
       }
     }
-    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) st = build_col_blocks(p, g, nb, s);
+    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) st = build_col_blocks(p, g, nb, !(p->auto_blocks && g->ncols >= 2 * nb), s);
     // A call that reads edge values through the edge-id map gathers from two tables at once: the feature rows of the
     // block's columns and, for each of those columns, the 128-byte line of the edge tensor that the walk is currently
     // passing (the slots of one source row are consecutive).  Both sets grow with the block's width, so such calls get
@@ -620,7 +621,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         f->l2_bytes = p->l2_bytes;
         f->llc_bytes = p->llc_bytes;
         f->auto_blocks = true;
-        st = build_col_blocks(f, g, 2 * p->nb, s);
+        st = build_col_blocks(f, g, 2 * p->nb, true, s);
       }
     }
     if (st == HGNN_OK && p->nb > 1) st = build_block_tasks(p->fine ? p->fine : p, s);

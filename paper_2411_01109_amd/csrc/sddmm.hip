@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
-      load_run<Rd::E, false>(a.col, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
 #pragma unroll
       for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
 #pragma unroll

@@ -594,8 +594,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
       int c[E], e[E];
       hv_t wv[E];
       float cs[E];
-      if (nt) load_run<E, true>(a.col, i0, end, c);
-      else load_run<E, false>(a.col, i0, end, c);
+      load_cols<E>(v, a.col, nt, w.block, i0, end, c);
       if (MAPPED) {
         if (nt) load_run<E, true>(a.eid, i0, end, e);
         else load_run<E, false>(a.eid, i0, end, e);

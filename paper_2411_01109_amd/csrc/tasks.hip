@@ -287,7 +287,10 @@ hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s) {
   if (st != HGNN_OK) return st;
   st = task_build(q, c, p->max_F, p->max_H, &p->btasks, s);
   HGNN_HIP(hipStreamSynchronize(s));
-  return st;
+  if (st != HGNN_OK) return st;
+  p->btasks->col16 = p->bcol16;
+  p->btasks->width = p->block_width;
+  return HGNN_OK;
 }
 
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F) {
