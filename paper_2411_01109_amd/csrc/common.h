@@ -376,9 +376,8 @@ struct hgnn_plan {
   std::vector<hgnn_plan*> sub;      // [nb] segment plans of the blocks
   hgnn_seg_block* bdesc = nullptr;  // [nb] the blocks' arrays, for kernels that walk all blocks in one launch
   hgnn_row_tasks* tasks = nullptr;   // of the whole graph
-  hgnn_row_tasks* btasks = nullptr;  // of the column blocks (nb > 1; not where `fine` takes their place)
-  hgnn_plan* fine = nullptr;        // the same graph in twice the blocks (blocked arrays only), for the SpMM that gathers edge
-                                    // values through the edge-id map and for the SDDMM; only where the automatic rule
+  hgnn_row_tasks* btasks = nullptr;  // of the column blocks (nb > 1; null where every pass takes those of `fine`)
+  hgnn_plan* fine = nullptr;        // the same graph in twice the blocks (blocked arrays only); only where the automatic rule
                                     // chose the blocks
   hgnn_half* bstage = nullptr;      // [2][nb][nrows][max_F] per-block partial outputs (second set: masked GAT partials)
   float* bsum = nullptr;            // [nb][nrows][max_H][2] per-block partial row sums of edge tensors / GAT (max, sum), then [nb][nrows][max_H] masked sums
@@ -421,6 +420,8 @@ void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub);
 hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, hipStream_t s);  // tasks: row tasks will walk them
+// the cut whose blocks a pass walks; narrow: a pass that gathers from two tables at once or leaves no partial rows behind
+inline const hgnn_plan* walked_cut(const hgnn_plan* p, bool narrow) { return p->fine && (narrow || !p->btasks) ? p->fine : p; }
 constexpr int kSliceMaxCols = 16384;  // columns per slice: 8 bytes each fill 128 KB of the 160 KB of LDS a workgroup may hold
 // row tasks in two steps around a host wait: task_count launches the counting passes, task_build takes their result
 struct TaskSource {

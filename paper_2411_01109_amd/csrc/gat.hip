@@ -601,7 +601,7 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   const bool save = out_masked != nullptr;
   if (p->nb <= 1) return run_gat_tasks(p, p->tasks, a, g->ncols, s);
   // column-blocked plan: every block leaves normalised partial rows and their (m, z[, zm/z]) per row; one pass merges them
-  if (p->fine) p = p->fine;
+  p = walked_cut(p, false);
   const size_t V = size_t(p->nrows);
   const size_t flat = size_t(p->nb) * V;
   half_t* bstage = reinterpret_cast<half_t*>(p->bstage);

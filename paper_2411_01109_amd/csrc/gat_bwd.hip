@@ -434,7 +434,7 @@ static hgnn_status run_bwd_tasks(const hgnn_plan* q, const hgnn_row_tasks* t, Ga
 template <bool VEC>
 static hgnn_status run_bwd_pass(const hgnn_plan* q, const hgnn_csr* gg, GatBwdArgs a, hipStream_t s) {
   if (q->nb <= 1) return run_bwd_tasks<VEC>(q, q->tasks, a, gg->ncols, s);
-  if (q->fine) q = q->fine;
+  q = walked_cut(q, false);
   const size_t V = size_t(q->nrows);
   const int64_t ds_stride = int64_t(V) * q->max_H * 2;
   const int L = pow2_at_least(a.F / 8);

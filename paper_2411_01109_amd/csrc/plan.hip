@@ -583,6 +583,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
   st = plan_build_arrays(p, g, s, false);
   if (st == HGNN_OK) {
     int nb = col_blocks;
+    bool narrow_only = false;  // every pass over blocks takes the finer cut
     p->auto_blocks = nb == 0;
     if (nb == 0) {
       // automatic: block only when the feature table is too large for an XCD's L2 (beyond three times its size)
@@ -595,9 +596,14 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         nb = int(table / (2.0 * double(p->l2_bytes)) + 0.5);
         if (nb < 2) nb = 2;
         if (nb > 16) nb = 16;
+        // all passes walk the finer cut below where a row still has 32 non-zeros or more in each of its blocks on
+        // average: slices of 3.7 MB come from L2 at 26 TB/s, of 7.5 MB at 15 TB/s, but every piece of a row costs a
+        // partial row written and read again, as much as some ten gathers.  233 000 columns x 64, 4 -> 8 blocks: at 489
+        // non-zeros a row 1.2 times as fast, at 172 slower (attention forward 524 -> 646 us, backward 552 -> 586).
+        narrow_only = mean_deg >= 64.0 * nb && g->ncols >= 2 * nb;
       }
     }
-    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) st = build_col_blocks(p, g, nb, !(p->auto_blocks && g->ncols >= 2 * nb), s);
+    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) st = build_col_blocks(p, g, nb, !narrow_only, s);
     // A call that reads edge values through the edge-id map gathers from two tables at once: the feature rows of the
     // block's columns and, for each of those columns, the 128-byte line of the edge tensor that the walk is currently
     // passing (the slots of one source row are consecutive).  Both sets grow with the block's width, so such calls get
@@ -624,7 +630,8 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         st = build_col_blocks(f, g, 2 * p->nb, true, s);
       }
     }
-    if (st == HGNN_OK && p->nb > 1) st = build_block_tasks(p->fine ? p->fine : p, s);
+    if (st == HGNN_OK && p->nb > 1 && !narrow_only) st = build_block_tasks(p, s);
+    if (st == HGNN_OK && p->fine) st = build_block_tasks(p->fine, s);
     // column slices for the per-edge passes over per-vertex scalars: where a row's share of a slice still is a piece
     // of 16 non-zeros or more on average
     if (st == HGNN_OK && col_blocks == 0 && g->nrows > 0 && g->nnz > 0) {

@@ -614,7 +614,7 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
     // edge-id map maps its blocks to that map's slots)
     const hgnn_row_tasks* t = p->tasks;
     if (p->nb > 1 && !p->block_eid) {
-      if (p->fine) p = p->fine;
+      p = walked_cut(p, true);
       t = p->btasks;
       a.col = p->bcol;
       a.delta = p->bdelta;
