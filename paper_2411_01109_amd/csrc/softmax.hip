@@ -28,7 +28,6 @@ struct EdgeRowArgs {
   const half_t* x1;  //                      backward: dalpha
   const half_t* x2;  //                      backward: e (LeakyReLU mask) or nullptr
   half_t* out;       // forward: alpha.      backward: de.      rowsum: [nrows][H]
-  float* out_f32;    // rowsum only: when set, the sums are written here in fp32 instead of out
   int64_t total;     // nnz * H
   int nrows, H;
   int team_max;      // rows longer than this are left by the sub-wave teams to a wave each
@@ -264,10 +263,7 @@ __device__ __forceinline__ void rowsum_row(const EdgeRowArgs& a, const Team& tea
   team.template reduce<H, false>(s);
   if (team.rank == 0) {
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-      if (a.out_f32) a.out_f32[int64_t(row) * H + h] = s[h];
-      else a.out[int64_t(row) * H + h] = half_t(s[h]);
-    }
+    for (int h = 0; h < H; ++h) a.out[int64_t(row) * H + h] = half_t(s[h]);
   }
 }
 
@@ -482,9 +478,7 @@ __global__ __launch_bounds__(kBlock) void edge_hub_rowsum_kernel(EdgeRowArgs a, 
   const int first = big_first[r], cnt = c.count[first];
   float s = 0.f;
   for (int k = 0; k < cnt; ++k) s += c.part[(int64_t(first + k) * a.H + h) * 2];
-  const int64_t o = int64_t(a.big_row[r]) * a.H + h;
-  if (a.out_f32) a.out_f32[o] = s;
-  else a.out[o] = half_t(s);
+  a.out[int64_t(a.big_row[r]) * a.H + h] = half_t(s);
 }
 
 // Scalar path for head counts that do not divide 8: one thread per (row, head).
@@ -497,8 +491,7 @@ __global__ __launch_bounds__(kBlock) void edge_row_scalar_kernel(EdgeRowArgs a) 
   if (OP == kSum) {
     float s = 0.f;
     for (int k = beg; k < end; ++k) s += float(a.x0[(a.eid ? int64_t(a.eid[k]) : int64_t(k)) * a.H + h]);
-    if (a.out_f32) a.out_f32[idx] = s;
-    else a.out[idx] = half_t(s);
+    a.out[idx] = half_t(s);
     return;
   }
   if (beg == end) return;
@@ -605,6 +598,103 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
   return HGNN_OK;
 }
 
+// ---- row sums through an edge-id map, over row tasks ---------------------------------------------------------------------
+// Every value is a gather of its own, so the L2s' requests bound the pass; pieces of at most S non-zeros keep the waves
+// level whatever the row lengths are, and a lane holds four gathers and the next four slots in flight.  Over column blocks the
+// gathered lines are those of one block's columns.
+struct RowsumArgs {
+  const int* eid;  // slots, in the order of the tasks' column array
+  const half_t* t;
+  half_t* out;     // [nrows][H], or
+  float* part;     // [nb][nrows][H] when the tasks are those of column blocks
+  float* stage;    // [slots][H] sums of the pieces of rows that have several
+  int64_t nrows;
+  template <int H>
+  __device__ __forceinline__ void store(int block, int row, const float (&s)[H]) const {
+    if (part) {
+      float* const p = part + (int64_t(block) * nrows + row) * H;
+#pragma unroll
+      for (int h = 0; h < H; ++h) p[h] = s[h];
+    } else {
+#pragma unroll
+      for (int h = 0; h < H; ++h) out[int64_t(row) * H + h] = half_t(s[h]);
+    }
+  }
+};
+constexpr int kRowsumL = 8;  // lanes per group
+
+template <int H>
+__global__ __launch_bounds__(kWave) void rowsum_task_kernel(RowsumArgs a, TaskView v) {
+  typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
+  constexpr int E = Round<kRowsumL>::E;
+  const int lane = threadIdx.x, l = lane % kRowsumL;
+  const TaskWave w = task_enter<kRowsumL>(v, blockIdx.x, lane / kRowsumL);
+  float s[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) s[h] = 0.f;
+  if (w.z1 > w.z0) {
+    for (int i = w.z0 + lane; i < w.z1; i += kWave) a.template store<H>(w.block, v.zrow[i], s);
+    return;
+  }
+  int k = w.beg + l * E;
+  int end = w.beg + w.span < w.end ? w.beg + w.span : w.end;
+  int id[E];
+  load_run<E, true>(a.eid, k, end, id);  // positions past the end hold slot 0: read, not added
+  for (int base = w.beg; base < w.end; base += w.step) {
+    hv_t x[E];
+#pragma unroll
+    for (int m = 0; m < E; ++m) x[m] = *reinterpret_cast<const hv_t*>(a.t + int64_t(id[m]) * H);
+    const int kn = k + w.step, past = base + w.step + w.span;
+    const int endn = past < w.end ? past : w.end;
+    load_run<E, true>(a.eid, kn, endn, id);
+#pragma unroll
+    for (int m = 0; m < E; ++m)
+#pragma unroll
+      for (int h = 0; h < H; ++h) s[h] += k + m < end ? float(x[m][h]) : 0.f;
+    k = kn;
+    end = endn;
+  }
+  if (w.whole) team_reduce<kWave, H, false>(s);
+  else team_reduce<kRowsumL, H, false>(s);
+  if (w.row < 0 || (w.whole ? lane : l) != 0) return;
+  if (w.slot < 0) {
+    a.template store<H>(w.block, w.row, s);
+  } else {
+#pragma unroll
+    for (int h = 0; h < H; ++h) a.stage[int64_t(w.slot) * H + h] = s[h];
+  }
+}
+
+// a wave per row of several pieces
+template <int H>
+__global__ __launch_bounds__(kBlock) void rowsum_task_finish_kernel(RowsumArgs a, const int4_t* __restrict__ split, int n_split) {
+  const int i = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  if (i >= n_split) return;
+  const int4_t q = split[i];  // row, first slot, pieces, block
+  float s[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) s[h] = 0.f;
+  for (int k = lane; k < q[2]; k += kWave)
+#pragma unroll
+    for (int h = 0; h < H; ++h) s[h] += a.stage[int64_t(q[1] + k) * H + h];
+  team_reduce<kWave, H, false>(s);
+  if (lane == 0) a.template store<H>(q[3], q[0], s);
+}
+
+template <int H>
+static hgnn_status launch_rowsum_tasks(const hgnn_row_tasks* t, const RowsumArgs& a, hipStream_t s) {
+  const TaskView v = task_view(t, kWave / kRowsumL);
+  if (v.first_wave[t->nb] > 0) {
+    rowsum_task_kernel<H><<<dim3(unsigned(v.first_wave[t->nb])), kWave, 0, s>>>(a, v);
+    HGNN_LAUNCH_CHECK("rowsum_task_kernel");
+  }
+  if (v.n_split > 0) {
+    rowsum_task_finish_kernel<H><<<dim3(unsigned(ceil_div(v.n_split, kWavesPerBlock))), kBlock, 0, s>>>(a, v.split, v.n_split);
+    HGNN_LAUNCH_CHECK("rowsum_task_finish_kernel");
+  }
+  return HGNN_OK;
+}
+
 // column-blocked row sums: out[i] = sum over the blocks of their fp32 partial sums
 __global__ __launch_bounds__(kBlock) void rowsum_block_sum_kernel(const float* __restrict__ part, int nb, int64_t n,
                                                                    half_t* __restrict__ out) {
@@ -686,22 +776,20 @@ hgnn_status hgnn_edge_rowsum(const hgnn_csr* g, const hgnn_plan* p, int32_t H, c
   a.nrows = g->nrows;
   a.H = H;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (!(p && p->nb > 1 && g->eid && p->block_eid && H <= p->max_H && g->nnz > 0)) return launch_edge_rows<kSum>(g, p, a, s);
-  // column-blocked plan of a graph with an edge-id map (the transposed view): the slots a block reads
-  // lie in one contiguous part of the edge tensor, so block after block the random reads stay cache
-  // resident; fp32 partial sums per block, then one pass adds them
-  const int64_t nout = int64_t(g->nrows) * H;
-  for (int b = 0; b < p->nb; ++b) {
-    hgnn_csr view{g->nrows, g->ncols, p->boff[size_t(b) + 1] - p->boff[size_t(b)],
-                  p->brp + size_t(b) * (size_t(g->nrows) + 1), p->bcol + p->boff[size_t(b)], nullptr,
-                  p->beid + p->boff[size_t(b)]};
-    EdgeRowArgs ab = a;
-    ab.rowptr = view.rowptr;
-    ab.eid = view.eid;
-    ab.out_f32 = p->bsum + size_t(b) * size_t(nout);
-    st = launch_edge_rows<kSum>(&view, nullptr, ab, s);
-    if (st != HGNN_OK) return st;
+  if (!(p && g->eid && H <= p->max_H && g->nnz > 0 && (H == 1 || H == 2 || H == 4 || H == 8) && aligned16(t)))
+    return launch_edge_rows<kSum>(g, p, a, s);
+  const bool blocked = p->nb > 1 && p->block_eid;
+  if (blocked) p = walked_cut(p, true);
+  const hgnn_row_tasks* const tasks = blocked ? p->btasks : p->tasks;
+  const RowsumArgs r{blocked ? p->beid : g->eid, a.x0, a.out, blocked ? p->bsum : nullptr, tasks->stage_mz, g->nrows};
+  switch (H) {
+    case 1: st = launch_rowsum_tasks<1>(tasks, r, s); break;
+    case 2: st = launch_rowsum_tasks<2>(tasks, r, s); break;
+    case 4: st = launch_rowsum_tasks<4>(tasks, r, s); break;
+    default: st = launch_rowsum_tasks<8>(tasks, r, s); break;
   }
+  if (st != HGNN_OK || !blocked) return st;
+  const int64_t nout = int64_t(g->nrows) * H;
   rowsum_block_sum_kernel<<<dim3(unsigned(ceil_div(nout, kBlock))), kBlock, 0, s>>>(p->bsum, p->nb, nout, a.out);
   HGNN_LAUNCH_CHECK("rowsum_block_sum_kernel");
   return HGNN_OK;

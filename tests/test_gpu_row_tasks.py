@@ -70,3 +70,20 @@ def test_table_beyond_4_gib(hgnn, dev, H):
         ref, sabs = oracle.spmm(rowptr, col, Xh, w=wn, H=h, want_sabs=True)
         compare("far table", down(Y), ref, sabs)
     hgnn.hgnn_plan_destroy(p)
+
+
+@pytest.mark.parametrize("H,S,nb", [(1, 256, 1), (2, 64, 3), (4, 256, 2), (8, 256, 1), (8, 1, 3), (4, 2048, 1)])
+def test_row_sums_through_the_map(hgnn, dev, H, S, nb):
+    print(f"row sums H={H} S={S} nb={nb}", flush=True)
+    V = 2300
+    rowptr, col = border_graph(V, V, H + S)
+    t = f16(np.random.default_rng(H).standard_normal((col.size, H)))
+    gt = hgnn.hgnn_transpose(hgnn.Csr(up(rowptr, dev), up(col, dev)))
+    g = hgnn.hgnn_transpose(hgnn.Csr(gt.rowptr, gt.col, ncols=V))  # the border rows again, now with a map
+    rp, slots = down(g.rowptr), down(g.eid)
+    p = hgnn.hgnn_plan_create(g, S, 8, H, col_blocks=nb)
+    out = torch.full((V, H), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_edge_rowsum(g, p, H, up(t, dev), out)
+    t64 = t.astype(np.float64)[slots]
+    compare("row sums", down(out), oracle.edge_rowsum(rp, t64), oracle.edge_rowsum(rp, np.abs(t64)))
+    hgnn.hgnn_plan_destroy(p)
