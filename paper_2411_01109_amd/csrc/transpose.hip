@@ -161,6 +161,25 @@ __global__ void edge_gather_kernel(const int* __restrict__ eid, int64_t total, i
   out[j] = in[int64_t(eid[k]) * H + (j - k * H)];
 }
 
+// Sort of 64-bit words by the bits [first, last), workgroups of 1024 lanes with eight words each.  A pass moves every word
+// once however many bits it takes (43 us for 5.5 M words), so digits of nine bits where they save a pass over digits of
+// eight: 36 bits in four passes instead of five, 18 in two instead of three (5.5 M edges: list to CSR 330 -> 280 us,
+// transpose 235 -> 183).
+// Below 200 000 words a sort by merging is faster (list to CSR, 0.13 M: 93 us against 125 with digits; 0.4 M: 163 against 133).
+static hipError_t sort_words(void* tmp, size_t& tmp_bytes, rocprim::double_buffer<uint64_t>& keys, unsigned n, unsigned first,
+                             unsigned last, hipStream_t s) {
+  using rocprim::default_config;
+  using rocprim::kernel_config;
+  constexpr auto rank = rocprim::block_radix_rank_algorithm::match;
+  using Eight = rocprim::radix_sort_onesweep_config<kernel_config<512, 12>, kernel_config<1024, 8>, 8, rank>;
+  using Nine = rocprim::radix_sort_onesweep_config<kernel_config<512, 12>, kernel_config<1024, 8>, 9, rank>;
+  constexpr size_t merge_below = 200000;
+  const unsigned bits = last - first;
+  if ((bits + 8) / 9 < (bits + 7) / 8)
+    return rocprim::radix_sort_keys<rocprim::radix_sort_config<default_config, default_config, Nine, merge_below>>(tmp, tmp_bytes, keys, n, first, last, s);
+  return rocprim::radix_sort_keys<rocprim::radix_sort_config<default_config, default_config, Eight, merge_below>>(tmp, tmp_bytes, keys, n, first, last, s);
+}
+
 }  // namespace hgnn
 
 using namespace hgnn;
@@ -191,11 +210,11 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
     for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(8 * size_t(E));
     rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
     const unsigned first = unsigned(row_bits + pos_bits), last = first + unsigned(col_bits);
-    if (e == hipSuccess) e = rocprim::radix_sort_keys(nullptr, tmp_bytes, keys, unsigned(E), first, last, s);
+    if (e == hipSuccess) e = sort_words(nullptr, tmp_bytes, keys, unsigned(E), first, last, s);
     if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
     if (e == hipSuccess) {
       transpose_keys_kernel<<<per_tile, kBlock, 0, s>>>(g->rowptr, g->col, g->nrows, E, row_bits, pos_bits, keys.current());
-      e = rocprim::radix_sort_keys(tmp.p, tmp_bytes, keys, unsigned(E), first, last, s);
+      e = sort_words(tmp.p, tmp_bytes, keys, unsigned(E), first, last, s);
     }
     if (e == hipSuccess) {
       transpose_split_kernel<<<per_edge, kBlock, 0, s>>>(keys.current(), E, row_bits, pos_bits, col_T, eid_T);
@@ -259,7 +278,7 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
   rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
   rocprim::double_buffer<int> order(ids[0].as<int>(), ids[1].as<int>());
   auto sort = [&](void* t) {
-    return packed ? rocprim::radix_sort_keys(t, tmp_bytes, keys, unsigned(E), first, last, s)
+    return packed ? sort_words(t, tmp_bytes, keys, unsigned(E), first, last, s)
                   : rocprim::radix_sort_pairs(t, tmp_bytes, keys, order, unsigned(E), first, last, s);
   };
   if (e == hipSuccess) e = sort(nullptr);
