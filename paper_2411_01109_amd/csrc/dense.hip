@@ -352,6 +352,56 @@ __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
       }
 }
 
+// The same for few rows in one launch: a workgroup owns 16 x 16 values of dW and all rows, its 16 waves take 32 rows in turn
+// and are added in LDS in wave order.  Bound by latency: 64 x 64 over 1000 rows 7.6 -> 4.7 us (two launches before).  Every
+// workgroup reads its 32-byte columns of all rows, so the time grows with the rows, but no partial results are left.
+constexpr int kSmallWaves = 16;
+
+__global__ __launch_bounds__(kWave * kSmallWaves) void wgrad_small_kernel(WgradArgs a, float* __restrict__ dW, int64_t lddw) {
+  constexpr int P = 24;         // pitch: the four rows of a transposing read on different banks, 16-byte aligned
+  constexpr int U = 4;          // steps whose loads are in flight together
+  constexpr int TILE = kWgradRows * P;
+  __shared__ __align__(16) half_t lds[kSmallWaves * 2 * TILE];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int kc0 = blockIdx.x * 16, fc0 = blockIdx.y * 16;
+  half_t* const xs = lds + wave * 2 * TILE;
+  half_t* const ys = xs + TILE;
+  const int row = lane >> 1, c = 8 * (lane & 1);
+  const bool kin = kc0 + c < a.K, fin = fc0 + c < a.F;  // K and F are multiples of 8
+  float4_t acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int64_t STEP = int64_t(kSmallWaves) * kWgradRows;
+  for (int64_t r0 = int64_t(wave) * kWgradRows; r0 < a.n; r0 += U * STEP) {
+    half8_t vx[U], vy[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = r0 + u * STEP + row;
+      vx[u] = vy[u] = half8_t(0);
+      if (r < a.n && kin) vx[u] = *reinterpret_cast<const half8_t*>(a.X + r * a.ldx + kc0 + c);
+      if (r < a.n && fin) vy[u] = *reinterpret_cast<const half8_t*>(a.dY + r * a.ldy + fc0 + c);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r0 + u * STEP >= a.n) break;
+      wave_sync();  // the previous step's column reads are done
+      *reinterpret_cast<half8_t*>(xs + row * P + c) = vx[u];
+      *reinterpret_cast<half8_t*>(ys + row * P + c) = vy[u];
+      wave_sync();
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wgrad_column(xs, P, 0, lane), wgrad_column(ys, P, 0, lane), acc, 0, 0, 0);
+    }
+  }
+  float* const sum = reinterpret_cast<float*>(lds);
+  __syncthreads();
+  *reinterpret_cast<float4_t*>(sum + (wave * kWave + lane) * 4) = acc;
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e >= 256) return;
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSmallWaves; ++w) s += sum[w * 256 + e];
+  const int k = kc0 + 4 * (e >> 6) + (e & 3), f = fc0 + ((e >> 2) & 15);
+  if (k < a.K && f < a.F) dW[int64_t(k) * lddw + f] = s;
+}
+
 // out[k*out_ld + f] = sum over the partials j (part_stride apart) of in[j][e], e = k*F + f < elems; from element `split` on the
 // result goes to out2[e - split].  A workgroup takes 64 elements; its kSumSlices slices add a strided share of the partials
 // each and the slice sums are added in slice order: a fixed order whatever the launch, in one launch (two rounds of
@@ -599,6 +649,16 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   parts = std::min<int64_t>(parts, wgrad_parts(K, F));
   parts = std::max<int64_t>(1, std::min<int64_t>(parts, ceil_div(n, int64_t(kWgradRows) * WR)));
   WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
+  // few rows: one launch without partial results, up to the rows at which fetching them in 32-byte pieces costs what the
+  // second launch does.  Behind the kernel that wrote dY: 64 x 64 at 1000, 2000, 4096 rows 4.7, 6.7, 11.8 us against 7.6,
+  // 7.6, 8.1; 256 x 256 at 2000 7.9 against 20.5.  Beyond one workgroup per compute unit they queue: 608 x 128 (304)
+  // at 2000, 3000 rows 8.4, 22.7 against 20.6, 20.0
+  const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16);
+  if (n <= 2048 && n * sb * sf <= 2560 * int64_t(kCus)) {
+    wgrad_small_kernel<<<dim3(unsigned(sb), unsigned(sf)), kWave * kSmallWaves, 0, s>>>(a, dW, lddw);
+    HGNN_LAUNCH_CHECK("wgrad_small_kernel");
+    return HGNN_OK;
+  }
   const dim3 grid{unsigned(parts), unsigned(kb), unsigned(fb)};
   if (WA == 1 && WB == 1) wgrad_kernel<1, 1><<<grid, kBlock, 0, s>>>(a);
   else if (WA == 2 && WB == 1) wgrad_kernel<2, 1><<<grid, kBlock, 0, s>>>(a);

@@ -110,6 +110,13 @@ def test_linear_wgrad_dispatch_edges(hgnn, dev, n, K, F):
     test_linear_wgrad_shapes(hgnn, dev, n, K, F)
 
 
+# the one-launch form for few rows: its last row and the next, steps of 32 rows missing for some waves, partial 16-blocks
+@pytest.mark.parametrize("n,K,F", [(1, 8, 8), (32, 40, 24), (511, 64, 64), (513, 56, 48), (1999, 104, 72), (2048, 128, 64),
+                                   (2049, 64, 64), (2048, 640, 128), (2048, 640, 136)])
+def test_linear_wgrad_few_rows(hgnn, dev, n, K, F):
+    test_linear_wgrad_shapes(hgnn, dev, n, K, F)
+
+
 def test_linear_wgrad_errors(hgnn, dev):
     X = torch.zeros((64, 64), dtype=torch.float16, device=dev)
     dW = torch.zeros((64, 64), dtype=torch.float32, device=dev)
