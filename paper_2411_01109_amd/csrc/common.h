@@ -71,6 +71,7 @@ hgnn_status check_csr_args(const hgnn_csr* g, const char* who);
 // A block may be freed only when no work that uses it is in flight.
 hipError_t dev_malloc_bytes(void** out, size_t bytes);
 void dev_free(const void* p);
+bool device_idle(int dev);  // waits for everything on that device, whatever device is current; false: it could not
 template <class T>
 inline hipError_t dev_malloc(T** out, size_t bytes) {
   void* p = nullptr;
@@ -329,6 +330,7 @@ struct hgnn_row_tasks {
 constexpr int kHubEdges = 2048;  // non-zeros per chunk of a long row in the edge-row kernels
 
 struct hgnn_plan {
+  int device = 0;       // the device that was current when the plan was made: its arrays are there
   int32_t nrows = 0, ncols = 0;
   int64_t nnz = 0;
   int32_t S = 0;        // edges per segment

@@ -6,7 +6,7 @@
 //  - at most kKeepBytes per device, blocks of up to half of that; what no set-up call has asked for during the last
 //    kKeepCalls allocations is freed, everything when an allocation fails or on hgnn_release_cached_memory();
 //  - callers free a block only when no work that uses it is in flight on any stream (set-up calls synchronize their
-//    stream first, hgnn_plan_destroy the device), so a kept block may be handed to any stream or thread at once;
+//    stream first, hgnn_plan_destroy the plan's device), so a kept block may be handed to any stream or thread at once;
 //  - one mutex; blocks belong to the device that was current when they were allocated.
 #include <mutex>
 #include <unordered_map>
@@ -106,6 +106,14 @@ void dev_free(const void* cp) {
   while (!v.empty() && P.kept_bytes[dev] + bytes > kKeepBytes) release_older_than(P, dev, v.front().freed_at + 1);
   v.push_back({p, bytes, P.calls});
   P.kept_bytes[dev] += bytes;
+}
+
+bool device_idle(int dev) {
+  int cur = 0;
+  if (hipGetDevice(&cur) != hipSuccess || (cur != dev && hipSetDevice(dev) != hipSuccess)) return false;
+  const hipError_t e = hipDeviceSynchronize();
+  if (cur != dev) (void)hipSetDevice(cur);
+  return e == hipSuccess;
 }
 
 HostMail::HostMail() {

@@ -549,7 +549,7 @@ extern "C" {
 
 void hgnn_plan_destroy(hgnn_plan* p) {
   if (!p) return;
-  (void)hipDeviceSynchronize();  // calls that use the plan may be in flight, and its memory is handed to the next plan
+  (void)device_idle(p->device);  // calls that use the plan may be in flight, and its memory is handed to the next plan
   destroy_plan(p);
 }
 
@@ -569,6 +569,10 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
                col_blocks);
   hgnn_plan* p = new (std::nothrow) hgnn_plan();
   HGNN_REQUIRE(p != nullptr, HGNN_ENOMEM, "hgnn_plan_create: host allocation failed");
+  if (hipGetDevice(&p->device) != hipSuccess) {
+    delete p;
+    return fail(HGNN_EHIP, "hgnn_plan_create: no current device");
+  }
   p->nrows = g->nrows;
   p->ncols = g->ncols;
   p->nnz = g->nnz;

@@ -1,0 +1,91 @@
+"""Device memory that set-up calls hand from one to another, on the host: libhgnn.so runs on a runtime that executes nothing but
+knows which streams have work in flight (fake_hip.cpp).  A block may go back only when nothing in flight uses it."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2411_01109_amd", "libhgnn.so")
+OK, ENOMEM, EHIP = 0, 3, 4
+vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+V, E, F = 1000, 20000, 64
+
+
+class Csr(ctypes.Structure):
+    _fields_ = [("nrows", i32), ("ncols", i32), ("nnz", i64), ("rowptr", vp), ("col", vp), ("row", vp), ("eid", vp)]
+
+
+class Host:
+    """The library on the fake runtime."""
+
+    def __init__(self, fake, lib):
+        self.fake = ctypes.CDLL(fake, mode=ctypes.RTLD_GLOBAL)
+        self.lib = ctypes.CDLL(lib)
+        self.path = lib.encode()
+        self.keep = [(ctypes.c_int32 * (E + V + 2))() for _ in range(4)]
+        self.data = ctypes.addressof((ctypes.c_char * (E * F * 4)).from_buffer(bytearray(E * F * 4)))
+        self.data = (self.data + 255) // 256 * 256
+        a = [ctypes.addressof(k) for k in self.keep]
+        self.g = Csr(V, V, E, a[0], a[1], None, None)
+        self.out = a[2], a[3]
+        self.lib.hgnn_plan_destroy.argtypes = [vp]
+        self.lib.hgnn_plan_destroy.restype = None
+        self.fake.fake_launched.restype = ctypes.c_char_p
+        self.reset()
+
+    def reset(self):
+        self.lib.hgnn_release_cached_memory()
+        self.fake.fake_reset(self.path)
+
+    def plan(self, stream, col_blocks=1):
+        p = vp()
+        st = self.lib.hgnn_plan_create(ctypes.byref(self.g), 256, F, 1, col_blocks, ctypes.byref(p), vp(stream))
+        return st, p
+
+    def compute(self, p, stream):
+        """An asynchronous call that uses the plan."""
+        x = vp(self.data)
+        return self.lib.hgnn_edge_softmax(ctypes.byref(self.g), p, 1, x, x, vp(stream))
+
+
+A, B = 0x1001, 0x1002  # streams of device 0
+C = 0x2001             # of device 1
+
+
+def destroy_on_another_device(h):
+    """The plan's device is waited for, whatever device is current when it is destroyed."""
+    h.fake.hipSetDevice(1)
+    st, p = h.plan(C)
+    assert st == OK and h.compute(p, C) == OK and h.fake.fake_busy(1) == 1
+    h.fake.hipSetDevice(0)
+    h.lib.hgnn_plan_destroy(p)
+    assert h.fake.fake_freed_busy() == 0
+    d = ctypes.c_int()
+    h.fake.hipGetDevice(ctypes.byref(d))
+    assert d.value == 0
+
+
+SCENARIOS = [destroy_on_another_device]
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", so, "-ldl"])
+    return so
+
+
+@pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
+def test_blocks_in_flight(hgnn, fake, name):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, LIB, name], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    host = Host(sys.argv[1], sys.argv[2])
+    {s.__name__: s for s in SCENARIOS}[sys.argv[3]](host)
+    print("ok")
