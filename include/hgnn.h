@@ -183,7 +183,7 @@ hgnn_status hgnn_plan_block_export(const hgnn_plan* p, int32_t b, int64_t* nnz_b
 hgnn_status hgnn_plan_export(const hgnn_plan* p, int32_t* seg_row_lo, int32_t* seg_row_hi, int32_t* split_row,
                              int32_t* split_seg_lo, int32_t* split_seg_hi);
 /* Waits for the device that was current when the plan was made (any device may be current now): calls that use the plan may
- * still be in flight. */
+ * still be in flight.  May be called while a stream is being captured. */
 void hgnn_plan_destroy(hgnn_plan* p);
 /* The set-up calls keep the device memory that they and destroyed plans free for the next set-up call, at most 512 MiB per
  * device; this gives it back to the runtime at once.  May be called at any time. */

@@ -71,6 +71,8 @@ hgnn_status check_csr_args(const hgnn_csr* g, const char* who);
 // A block may be freed only when no work that uses it is in flight.
 hipError_t dev_malloc_bytes(void** out, size_t bytes);
 void dev_free(const void* p);
+void dev_release(const void* p);  // where that could not be made sure: back to the runtime, never to another call
+inline void dev_put(const void* p, bool idle) { idle ? dev_free(p) : dev_release(p); }
 bool device_idle(int dev);  // waits for everything on that device, whatever device is current; false: it could not
 template <class T>
 inline hipError_t dev_malloc(T** out, size_t bytes) {
@@ -461,7 +463,7 @@ struct TaskCounts {
 hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s);
 hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, hipStream_t s);
 hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s);
-void destroy_tasks(hgnn_row_tasks* t);
+void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s);
 hgnn_status slice_edge_score(const hgnn_plan* p, const hgnn_csr* g, const float* el, const float* er, const float* lse,
                              float slope, hgnn_half* out, hipStream_t s);

@@ -504,44 +504,45 @@ void hgnn_plan_cache_bytes(const hgnn_plan* p, int64_t* l2_bytes, int64_t* llc_b
 
 }  // extern "C"
 
-static void destroy_plan(hgnn_plan* p) {
+// idle: nothing that uses the plan is in flight
+static void destroy_plan(hgnn_plan* p, bool idle) {
   if (!p) return;
-  for (hgnn_plan* q : p->sub) destroy_plan(q);
-  destroy_plan(p->fine);
-  destroy_tasks(p->tasks);
-  destroy_tasks(p->btasks);
-  dev_free(p->brp);
-  dev_free(p->bcol);
-  dev_free(p->bcol16);
-  dev_free(p->beid);
-  dev_free(p->bdelta);
-  dev_free(p->bstage);
-  dev_free(p->bsum);
-  dev_free(p->bdesc);
-  dev_free(p->seg_row_lo);
-  dev_free(p->seg_row_hi);
-  dev_free(p->split_row);
-  dev_free(p->split_seg_lo);
-  dev_free(p->split_seg_hi);
-  dev_free(p->big_row);
-  dev_free(p->hub_chunk_row);
-  dev_free(p->hub_chunk_first);
-  dev_free(p->hub_chunk_count);
-  dev_free(p->big_first);
-  dev_free(p->hub_part);
-  dev_free(p->mid_row);
-  dev_free(p->staging);
-  dev_free(p->stage_mz);
-  dev_free(p->vscratch);
-  dev_free(p->vtab);
-  dev_free(p->goff);
-  dev_free(p->moff);
-  dev_free(p->grp_row);
-  dev_free(p->gstage);
-  dev_free(p->scut);
-  dev_free(p->chunk_row);
-  dev_free(p->col_part);
-  dev_free(p->col_poison);
+  for (hgnn_plan* q : p->sub) destroy_plan(q, idle);
+  destroy_plan(p->fine, idle);
+  destroy_tasks(p->tasks, idle);
+  destroy_tasks(p->btasks, idle);
+  dev_put(p->brp, idle);
+  dev_put(p->bcol, idle);
+  dev_put(p->bcol16, idle);
+  dev_put(p->beid, idle);
+  dev_put(p->bdelta, idle);
+  dev_put(p->bstage, idle);
+  dev_put(p->bsum, idle);
+  dev_put(p->bdesc, idle);
+  dev_put(p->seg_row_lo, idle);
+  dev_put(p->seg_row_hi, idle);
+  dev_put(p->split_row, idle);
+  dev_put(p->split_seg_lo, idle);
+  dev_put(p->split_seg_hi, idle);
+  dev_put(p->big_row, idle);
+  dev_put(p->hub_chunk_row, idle);
+  dev_put(p->hub_chunk_first, idle);
+  dev_put(p->hub_chunk_count, idle);
+  dev_put(p->big_first, idle);
+  dev_put(p->hub_part, idle);
+  dev_put(p->mid_row, idle);
+  dev_put(p->staging, idle);
+  dev_put(p->stage_mz, idle);
+  dev_put(p->vscratch, idle);
+  dev_put(p->vtab, idle);
+  dev_put(p->goff, idle);
+  dev_put(p->moff, idle);
+  dev_put(p->grp_row, idle);
+  dev_put(p->gstage, idle);
+  dev_put(p->scut, idle);
+  dev_put(p->chunk_row, idle);
+  dev_put(p->col_part, idle);
+  dev_put(p->col_poison, idle);
   delete p;
 }
 
@@ -549,8 +550,7 @@ extern "C" {
 
 void hgnn_plan_destroy(hgnn_plan* p) {
   if (!p) return;
-  (void)device_idle(p->device);  // calls that use the plan may be in flight, and its memory is handed to the next plan
-  destroy_plan(p);
+  destroy_plan(p, device_idle(p->device));  // calls that use the plan may be in flight, and its memory is handed to the next plan
 }
 
 hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F, int32_t max_H, int32_t col_blocks,

@@ -325,14 +325,14 @@ hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t
   return HGNN_OK;
 }
 
-void destroy_tasks(hgnn_row_tasks* t) {
+void destroy_tasks(hgnn_row_tasks* t, bool idle) {
   if (!t) return;
-  dev_free(t->task);
-  dev_free(t->zrow);
-  dev_free(t->split);
-  dev_free(t->sec);
-  dev_free(t->staging);
-  dev_free(t->stage_mz);
+  dev_put(t->task, idle);
+  dev_put(t->zrow, idle);
+  dev_put(t->split, idle);
+  dev_put(t->sec, idle);
+  dev_put(t->staging, idle);
+  dev_put(t->stage_mz, idle);
   delete t;
 }
 

@@ -35,9 +35,9 @@ int device_of(hipStream_t s) {
   return v == 0 ? cur : int(v / 0x1000) - 1;
 }
 void work(hipStream_t s) { busy[device_of(s)].insert(s); }
-// a call that a capture in progress does not allow (the thread that captures, in the global mode)
-bool refused() {
-  if (!capturing || mode == hipStreamCaptureModeRelaxed) return false;
+// a call that a capture in progress does not allow, in the relaxed mode or at all
+bool refused(bool always = false) {
+  if (!capturing || (mode == hipStreamCaptureModeRelaxed && !always)) return false;
   spoiled = true;
   return true;
 }
@@ -83,7 +83,7 @@ hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
-  if (refused()) return hipErrorStreamCaptureUnsupported;
+  if (refused(true)) return hipErrorStreamCaptureUnsupported;
   if (fail_waits) return hipErrorUnknown;
   busy[cur].clear();
   return hipSuccess;
@@ -107,7 +107,8 @@ hipError_t hipFree(void* p) {
   ++frees;
   const auto it = live.find(p);
   if (it == live.end()) return hipErrorInvalidValue;
-  if (!fail_waits) busy[it->second].clear();
+  if (fail_waits) return hipErrorUnknown;
+  busy[it->second].clear();
   live.erase(it);
   free(p);
   return hipSuccess;

@@ -253,3 +253,29 @@ def test_long_row_forms_under_graph_replay(hgnn, dev):
             assert np.all(np.isfinite(got[k])) and np.abs(got[k].astype(np.float32)).max() > 0
     hgnn.hgnn_plan_destroy(p)
     hgnn.hgnn_plan_destroy(pt)
+
+
+def test_a_plan_destroyed_while_another_stream_is_captured(hgnn, dev):
+    """A garbage collector may destroy a plan in the middle of a capture: the capture goes on, and the graph replays."""
+    V, F = 2000, 64
+    rowptr, col = rand_graph(V, V, 9, 4, hubs=((3, 900),))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    X = up(f16(np.random.default_rng(2).standard_normal((V, F))), dev)
+    Y, want = torch.empty_like(X), torch.empty_like(X)
+    p, old = (hgnn.hgnn_plan_create(g, 256, F, 1) for _ in range(2))
+    hgnn.hgnn_spmm_discretized(p, g, None, 1, X, want)
+    hgnn.hgnn_spmm_discretized(old, g, None, 1, X, Y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+        hgnn.hgnn_plan_destroy(old)
+        hgnn.hgnn_release_cached_memory()
+        Y.add_(1)
+    for rep in range(3):
+        Y.zero_()
+        graph.replay()
+        assert np.array_equal(down(Y), (down(want) + np.float16(1)).astype(np.float16)), rep
+        again = hgnn.hgnn_plan_create(g, 256, F, 1)  # eager set-up and destruction between the replays
+        hgnn.hgnn_plan_destroy(again)
+    hgnn.hgnn_plan_destroy(p)

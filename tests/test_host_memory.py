@@ -68,7 +68,35 @@ def destroy_on_another_device(h):
     assert d.value == 0
 
 
-SCENARIOS = [destroy_on_another_device]
+def failed_wait(h):
+    """A plan whose wait failed may still be in use: its blocks go back to the runtime, not to the next plan."""
+    st, p = h.plan(A)
+    assert st == OK
+    before = h.fake.fake_mallocs()
+    st, q = h.plan(A)
+    blocks = h.fake.fake_mallocs() - before  # of one plan: the temporaries were there
+    assert st == OK and h.compute(q, A) == OK
+    h.fake.fake_fail_waits(1)
+    h.lib.hgnn_plan_destroy(q)
+    h.fake.fake_fail_waits(0)
+    before = h.fake.fake_mallocs()
+    st, q = h.plan(B)
+    assert st == OK and blocks > 0 and h.fake.fake_mallocs() - before == blocks
+    h.lib.hgnn_plan_destroy(q)
+    h.lib.hgnn_plan_destroy(p)
+
+
+def destroyed_during_a_capture(h):
+    """Neither the capture nor the blocks are spoiled when a plan is destroyed by the thread that captures."""
+    st, p = h.plan(A)
+    assert st == OK and h.compute(p, A) == OK
+    h.fake.fake_capture(1)
+    h.lib.hgnn_plan_destroy(p)
+    assert h.fake.fake_spoiled() == 0 and h.fake.fake_freed_busy() == 0
+    h.fake.fake_capture(0)
+
+
+SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture]
 
 
 @pytest.fixture(scope="module")
