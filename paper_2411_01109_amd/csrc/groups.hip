@@ -46,11 +46,13 @@ __global__ void group_first_kernel(const int* __restrict__ rowptr, const int* __
   first[j] = rowptr[r] + int(j - goff[r]) * ng;
 }
 
+// groups of an earlier call may still be in use by calls on the plan, on whatever stream
 static void free_groups(hgnn_plan* p) {
-  dev_free(p->goff);
-  dev_free(p->moff);
-  dev_free(p->grp_row);
-  dev_free(p->gstage);
+  const bool idle = p->goff == nullptr || device_idle(p->device);
+  dev_put(p->goff, idle);
+  dev_put(p->moff, idle);
+  dev_put(p->grp_row, idle);
+  dev_put(p->gstage, idle);
   p->goff = p->moff = p->grp_row = nullptr;
   p->gstage = nullptr;
   p->ng = 0;

@@ -6,7 +6,7 @@
 //  - at most kKeepBytes per device, blocks of up to half of that; what no set-up call has asked for during the last
 //    kKeepCalls allocations is freed, everything when an allocation fails or on hgnn_release_cached_memory();
 //  - callers free a block only when no work that uses it is in flight on any stream (set-up calls synchronize their
-//    stream first, hgnn_plan_destroy the plan's device), so a kept block may be handed to any stream or thread at once; a block
+//    stream first; hgnn_plan_destroy, and calls that replace arrays of a plan, wait for the plan's device), so a kept block may be handed to any stream or thread at once; a block
 //    for which the wait failed goes back to the runtime instead;
 //  - one mutex; blocks belong to the device that was current when they were allocated.
 #include <mutex>

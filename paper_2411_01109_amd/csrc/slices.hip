@@ -259,10 +259,12 @@ __global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int
 }
 
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s) {
-  dev_free(p->scut);
-  dev_free(p->chunk_row);
-  dev_free(p->col_part);
-  dev_free(p->col_poison);
+  // slices of an earlier call may still be in use by calls on the plan, on whatever stream
+  const bool idle = p->scut == nullptr || device_idle(p->device);
+  dev_put(p->scut, idle);
+  dev_put(p->chunk_row, idle);
+  dev_put(p->col_part, idle);
+  dev_put(p->col_poison, idle);
   p->scut = p->chunk_row = nullptr;
   p->col_part = nullptr;
   p->col_poison = nullptr;

@@ -96,7 +96,24 @@ def destroyed_during_a_capture(h):
     h.fake.fake_capture(0)
 
 
-SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture]
+def replaced_groups(h):
+    """Groups that a call on the plan still uses are not given to another set-up call."""
+    st, p = h.plan(A)
+    add = lambda: h.lib.hgnn_plan_add_groups(p, ctypes.byref(h.g), 32, vp(B))
+    assert st == OK and add() == OK and h.compute(p, A) == OK and h.fake.fake_busy(0) == 1
+    assert add() == OK and h.fake.fake_freed_busy() == 0
+    h.lib.hgnn_plan_destroy(p)
+
+
+def replaced_slices(h):
+    st, p = h.plan(A)
+    add = lambda: h.lib.hgnn_plan_add_slices(p, ctypes.byref(h.g), 0, vp(B))
+    assert st == OK and add() == OK and h.compute(p, A) == OK and h.fake.fake_busy(0) == 1
+    assert add() == OK and h.fake.fake_freed_busy() == 0
+    h.lib.hgnn_plan_destroy(p)
+
+
+SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture, replaced_groups, replaced_slices]
 
 
 @pytest.fixture(scope="module")
