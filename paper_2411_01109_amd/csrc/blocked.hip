@@ -79,21 +79,21 @@ __global__ void block_fill_kernel(hgnn_csr g, const int* __restrict__ cut, const
   beid[dest] = g.eid ? g.eid[k] : int(k);
 }
 
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, hipStream_t s) {
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, SetupStream& s) {
   const int V = g->nrows;
   const int64_t E = g->nnz;
   const int width = int(ceil_div(g->ncols, nb));
   p->nb = nb;
   p->block_width = width;
   p->block_eid = g->eid != nullptr;
-  int *cut = nullptr, *cnt = nullptr, *goff = nullptr;
-  char* tmp = nullptr;
+  DevTemp cut_buf(s), cnt_buf(s), goff_buf(s), tmp(s);
   size_t tmp_bytes = 0;
   const size_t n_flat = size_t(nb) * size_t(V);
   hgnn_status rc = HGNN_OK;
-  hipError_t e = dev_malloc(&cut, sizeof(int) * size_t(V) * size_t(nb + 1));
-  if (e == hipSuccess) e = dev_malloc(&cnt, sizeof(int) * n_flat);
-  if (e == hipSuccess) e = dev_malloc(&goff, sizeof(int) * n_flat);
+  hipError_t e = cut_buf.alloc(sizeof(int) * size_t(V) * size_t(nb + 1));
+  if (e == hipSuccess) e = cnt_buf.alloc(sizeof(int) * n_flat);
+  if (e == hipSuccess) e = goff_buf.alloc(sizeof(int) * n_flat);
+  int *const cut = cut_buf.as<int>(), *const cnt = cnt_buf.as<int>(), *const goff = goff_buf.as<int>();
   if (e == hipSuccess) e = dev_malloc(&p->brp, sizeof(int) * size_t(nb) * (size_t(V) + 1));
   if (e == hipSuccess) e = dev_malloc(&p->bcol, sizeof(int) * size_t(E));
   if (e == hipSuccess && tasks && width <= 65536) e = dev_malloc(&p->bcol16, sizeof(uint16_t) * size_t(E));
@@ -109,8 +109,8 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks
     block_counts_kernel<<<dim3(unsigned(ceil_div(int64_t(n_flat), kBlock))), kBlock, 0, s>>>(cut, V, nb, cnt);
     e = rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
   }
-  if (e == hipSuccess) e = dev_malloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
-  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
+  if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp.p, tmp_bytes, cnt, goff, 0, n_flat, rocprim::plus<int>(), s);
   if (e == hipSuccess) {
     block_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(nb) * (V + 1), kBlock))), kBlock, 0, s>>>(goff, V, nb, E, p->brp);
     block_fill_kernel<<<dim3(unsigned(ceil_div(E, kBlock))), kBlock, 0, s>>>(*g, cut, goff, nb, width, p->bcol, p->bcol16, p->beid);
@@ -121,17 +121,13 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks
   for (int b = 0; b < nb && e == hipSuccess; ++b) {
     int v = 0;
     e = hipMemcpyAsync(&v, goff + size_t(b) * V, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = s.wait();
     p->boff[size_t(b)] = v;
   }
   p->boff[size_t(nb)] = E;
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess)
     rc = fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "build_col_blocks: %s", hipGetErrorString(e));
-  dev_free(cut);
-  dev_free(cnt);
-  dev_free(goff);
-  dev_free(tmp);
   if (rc != HGNN_OK) return rc;
   // a segment plan per block, over the block's own CSR
   for (int b = 0; b < nb; ++b) {
@@ -174,7 +170,7 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks
   }
   HGNN_HIP(dev_malloc(&p->bdesc, sizeof(hgnn_seg_block) * size_t(nb)));
   HGNN_HIP(hipMemcpyAsync(p->bdesc, desc.data(), sizeof(hgnn_seg_block) * size_t(nb), hipMemcpyHostToDevice, s));
-  HGNN_HIP(hipStreamSynchronize(s));
+  HGNN_HIP(s.wait());
   return HGNN_OK;
 }
 

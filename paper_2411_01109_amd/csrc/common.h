@@ -82,13 +82,39 @@ inline hipError_t dev_malloc(T** out, size_t bytes) {
   return e;
 }
 
-// a device block that is freed when it goes out of scope
+// The stream of a set-up call.  Whatever is launched or copied goes through the conversion, so it knows whether anything may
+// be in flight; DevTemp and HostMail wait for that before they give their memory back, on every way out of the call.
+class SetupStream {
+ public:
+  explicit SetupStream(void* stream) : s(static_cast<hipStream_t>(stream)) {}
+  SetupStream(const SetupStream&) = delete;
+  SetupStream& operator=(const SetupStream&) = delete;
+  operator hipStream_t() {
+    idle = false;
+    return s;
+  }
+  hipError_t wait() {
+    const hipError_t e = hipStreamSynchronize(s);
+    idle = e == hipSuccess;
+    return e;
+  }
+  bool settle() { return idle || wait() == hipSuccess; }  // true: nothing of this call is in flight
+
+ private:
+  hipStream_t s;
+  bool idle = true;
+};
+
+// a device block of a set-up call that is freed when it goes out of scope
 struct DevTemp {
+  SetupStream& s;
   void* p = nullptr;
-  DevTemp() = default;
+  explicit DevTemp(SetupStream& stream) : s(stream) {}
   DevTemp(const DevTemp&) = delete;
   DevTemp& operator=(const DevTemp&) = delete;
-  ~DevTemp() { dev_free(p); }
+  ~DevTemp() {
+    if (p) dev_put(p, s.settle());
+  }
   hipError_t alloc(size_t bytes) { return dev_malloc_bytes(&p, bytes); }
   template <class T>
   T* as() const { return static_cast<T*>(p); }
@@ -98,9 +124,10 @@ struct DevTemp {
 // pageable memory costs a staging round of its own); data == nullptr when there is none left
 constexpr size_t kMailBytes = 256;
 struct HostMail {
+  SetupStream& s;
   char* data = nullptr;
   int slot = -1;
-  HostMail();
+  explicit HostMail(SetupStream& stream);
   ~HostMail();
   HostMail(const HostMail&) = delete;
   HostMail& operator=(const HostMail&) = delete;
@@ -422,8 +449,8 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
                       void* scratch, size_t scratch_bytes, bool one_sweep, hipStream_t s);
 void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub);
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, hipStream_t s);  // tasks: row tasks will walk them
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, bool sub);
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, SetupStream& s);  // tasks: row tasks will walk them
 // the cut whose blocks a pass walks; narrow: a pass that gathers from two tables at once or leaves no partial rows behind
 inline const hgnn_plan* walked_cut(const hgnn_plan* p, bool narrow) { return p->fine && (narrow || !p->btasks) ? p->fine : p; }
 constexpr int kSliceMaxCols = 16384;  // columns per slice: 8 bytes each fill 128 KB of the 160 KB of LDS a workgroup may hold
@@ -456,15 +483,16 @@ struct TaskScratch {
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
 struct TaskCounts {
+  explicit TaskCounts(SetupStream& s) : counts(s), sec(s), mail(s) {}
   DevTemp counts, sec;
   HostMail mail;
   TaskTotals* totals = nullptr;  // valid after the stream has been waited for (host memory, or a device copy)
 };
-hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s);
-hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, hipStream_t s);
-hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s);
+hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s);
+hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, SetupStream& s);
+hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s);
 void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
-hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s);
+hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s);
 hgnn_status slice_edge_score(const hgnn_plan* p, const hgnn_csr* g, const float* el, const float* er, const float* lse,
                              float slope, hgnn_half* out, hipStream_t s);
 }  // namespace hgnn

@@ -75,28 +75,28 @@ hgnn_status hgnn_plan_add_groups(hgnn_plan* p, const hgnn_csr* g, int32_t group_
                "%s: the plan was built for another graph", who);
   HGNN_REQUIRE(group_edges >= 1 && group_edges <= 1024, HGNN_EINVAL, "%s: group_edges = %d outside [1, 1024]", who,
                group_edges);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  SetupStream s(stream);
   free_groups(p);
   const int V = g->nrows;
-  int *cnt = nullptr, *mcnt = nullptr;
-  char* tmp = nullptr;
+  DevTemp cnt_buf(s), mcnt_buf(s), tmp(s);
   size_t tmp_bytes = 0;
   const size_t n1 = size_t(V) + 1;
-  hipError_t e = dev_malloc(&cnt, sizeof(int) * n1);
-  if (e == hipSuccess) e = dev_malloc(&mcnt, sizeof(int) * n1);
+  hipError_t e = cnt_buf.alloc(sizeof(int) * n1);
+  if (e == hipSuccess) e = mcnt_buf.alloc(sizeof(int) * n1);
+  int *const cnt = cnt_buf.as<int>(), *const mcnt = mcnt_buf.as<int>();
   if (e == hipSuccess) e = dev_malloc(&p->goff, sizeof(int) * n1);
   if (e == hipSuccess) e = dev_malloc(&p->moff, sizeof(int) * n1);
   if (e == hipSuccess) {
     group_counts_kernel<<<dim3(unsigned(ceil_div(int64_t(n1), kBlock))), kBlock, 0, s>>>(g->rowptr, V, group_edges, cnt, mcnt);
     e = rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, p->goff, 0, n1, rocprim::plus<int>(), s);
   }
-  if (e == hipSuccess) e = dev_malloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 16);
-  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, cnt, p->goff, 0, n1, rocprim::plus<int>(), s);
-  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp, tmp_bytes, mcnt, p->moff, 0, n1, rocprim::plus<int>(), s);
+  if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp.p, tmp_bytes, cnt, p->goff, 0, n1, rocprim::plus<int>(), s);
+  if (e == hipSuccess) e = rocprim::exclusive_scan(tmp.p, tmp_bytes, mcnt, p->moff, 0, n1, rocprim::plus<int>(), s);
   int totals[2] = {0, 0};
   if (e == hipSuccess) e = hipMemcpyAsync(&totals[0], p->goff + V, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&totals[1], p->moff + V, sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = s.wait();
   if (e == hipSuccess && totals[0] > 0) e = dev_malloc(&p->grp_row, sizeof(int) * size_t(totals[0]));
   if (e == hipSuccess && totals[1] > 0)
     e = dev_malloc(&p->gstage, sizeof(hgnn_half) * size_t(totals[1]) * size_t(p->max_F));
@@ -104,11 +104,8 @@ hgnn_status hgnn_plan_add_groups(hgnn_plan* p, const hgnn_csr* g, int32_t group_
     group_rows_kernel<<<dim3(unsigned(ceil_div(int64_t(totals[0]), kBlock))), kBlock, 0, s>>>(p->goff, V, totals[0],
                                                                                               p->grp_row);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = s.wait();
   }
-  dev_free(cnt);
-  dev_free(mcnt);
-  dev_free(tmp);
   if (e != hipSuccess) {
     free_groups(p);
     return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
@@ -131,14 +128,15 @@ hgnn_status hgnn_plan_groups_export(const hgnn_plan* p, const hgnn_csr* g, int32
   HGNN_REQUIRE(p->nrows == g->nrows && p->nnz == g->nnz, HGNN_EINVAL, "%s: the plan was built for another graph", who);
   if (p->n_groups == 0) return HGNN_OK;
   HGNN_REQUIRE(group_row && group_first, HGNN_EINVAL, "%s: output array is NULL", who);
-  int* first = nullptr;
-  HGNN_HIP(dev_malloc(&first, sizeof(int) * size_t(p->n_groups)));
-  group_first_kernel<<<dim3(unsigned(ceil_div(p->n_groups, kBlock))), kBlock, 0, nullptr>>>(g->rowptr, p->goff, p->grp_row,
-                                                                                            p->n_groups, p->ng, first);
+  SetupStream s(nullptr);
+  DevTemp first_buf(s);
+  HGNN_HIP(first_buf.alloc(sizeof(int) * size_t(p->n_groups)));
+  int* const first = first_buf.as<int>();
+  group_first_kernel<<<dim3(unsigned(ceil_div(p->n_groups, kBlock))), kBlock, 0, s>>>(g->rowptr, p->goff, p->grp_row,
+                                                                                     p->n_groups, p->ng, first);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpy(group_first, first, sizeof(int) * size_t(p->n_groups), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemcpy(group_row, p->grp_row, sizeof(int) * size_t(p->n_groups), hipMemcpyDeviceToHost);
-  dev_free(first);
   if (e != hipSuccess) return fail(HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
   return HGNN_OK;
 }

@@ -147,7 +147,7 @@ bool device_idle(int dev) {
   return e == hipSuccess;
 }
 
-HostMail::HostMail() {
+HostMail::HostMail(SetupStream& stream) : s(stream) {
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
   if (P.mail == nullptr) {
@@ -165,7 +165,7 @@ HostMail::HostMail() {
 }
 
 HostMail::~HostMail() {
-  if (slot < 0) return;
+  if (slot < 0 || !s.settle()) return;  // a kernel may still write to it: never used again
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
   P.mail_used &= ~(uint64_t(1) << slot);

@@ -355,11 +355,11 @@ __global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int
 // Builds the segment arrays, row lists and staging buffer of p for the graph g (p->S, p->nseg, p->max_F set by the
 // caller).  sub = true: p is the sub-plan of one column block; otherwise the graph is validated as well.  The host waits
 // twice: for the totals of the lists (which size the allocations) and for the arrays.
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bool sub) {
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, bool sub) {
   const int64_t E = g->nnz;
   const int nblk = int(ceil_div(g->nrows, kRowsPerBlock));
-  DevTemp facts_buf, counts_buf;
-  HostMail mail;
+  DevTemp facts_buf(s), counts_buf(s);
+  HostMail mail(s);
   HGNN_HIP(facts_buf.alloc(2 * sizeof(GraphFacts)));
   HGNN_HIP(counts_buf.alloc(sizeof(int) * kLists * (size_t(nblk) + 1)));
   GraphFacts* facts = facts_buf.as<GraphFacts>();
@@ -372,22 +372,15 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bo
   row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
   HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
   const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz)};
-  TaskCounts tc;
+  TaskCounts tc(s);
   if (!sub) {
     const hgnn_status ts = task_count(tq, tc, s);
-    if (ts != HGNN_OK) {
-      (void)hipStreamSynchronize(s);  // the blocks above go back when this returns
-      return ts;
-    }
+    if (ts != HGNN_OK) return ts;
   }
   GraphFacts f;
-  if (mail.data) {
-    HGNN_HIP(hipStreamSynchronize(s));
-    f = *totals;
-  } else {
-    HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
-    HGNN_HIP(hipStreamSynchronize(s));
-  }
+  if (!mail.data) HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
+  HGNN_HIP(s.wait());
+  if (mail.data) f = *totals;
   hgnn_status st = check_facts(f);
   if (st != HGNN_OK) return st;
   p->n_split = f.n_split;
@@ -431,17 +424,14 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, hipStream_t s, bo
   }
   if (!sub) {
     st = task_build(tq, tc, p->max_F, p->max_H, &p->tasks, s);
-    if (st != HGNN_OK) {
-      (void)hipStreamSynchronize(s);
-      return st;
-    }
+    if (st != HGNN_OK) return st;
   }
   if (!sub) {  // a column block's sub-plan only serves the SpMM kernels
     const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
     if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));
     if (g->nrows > 0) HGNN_HIP(dev_malloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));
   }
-  HGNN_HIP(hipStreamSynchronize(s));
+  HGNN_HIP(s.wait());
   return HGNN_OK;
 }
 
@@ -479,13 +469,13 @@ hgnn_status hgnn_csr_validate(const hgnn_csr* g, void* stream) {
   clear_error();
   hgnn_status st = check_csr_args(g, "hgnn_csr_validate");
   if (st != HGNN_OK) return st;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  DevTemp facts;
+  SetupStream s(stream);
+  DevTemp facts(s);
   GraphFacts f;
   HGNN_HIP(facts.alloc(sizeof(GraphFacts)));
   hipError_t e = launch_validate(g, facts.as<GraphFacts>(), s);
   if (e == hipSuccess) e = hipMemcpyAsync(&f, facts.p, sizeof(f), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess) return fail(HGNN_EHIP, "hgnn_csr_validate: %s", hipGetErrorString(e));
   return check_facts(f);
 }
@@ -583,7 +573,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
   p->big_deg = 2048;
   p->mid_deg = 32;
   device_cache_bytes(&p->l2_bytes, &p->llc_bytes);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  SetupStream s(stream);
   st = plan_build_arrays(p, g, s, false);
   if (st == HGNN_OK) {
     int nb = col_blocks;

@@ -258,7 +258,7 @@ __global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int
   chunk_row[c] = lo;
 }
 
-hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t s) {
+hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s) {
   // slices of an earlier call may still be in use by calls on the plan, on whatever stream
   const bool idle = p->scut == nullptr || device_idle(p->device);
   dev_put(p->scut, idle);
@@ -290,7 +290,7 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, hipStream_t
                                                                                                     ns, W, p->scut);
   chunk_rows_kernel<<<dim3(unsigned(ceil_div(nch + 1, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, g->nnz, nch, p->chunk_row);
   HGNN_LAUNCH_CHECK("slice_cuts_kernel / chunk_rows_kernel");
-  HGNN_HIP(hipStreamSynchronize(s));
+  HGNN_HIP(s.wait());
   p->ns = ns;
   p->slice_w = W;
   p->nch = nch;
@@ -356,7 +356,8 @@ hgnn_status hgnn_plan_add_slices(hgnn_plan* p, const hgnn_csr* g, int32_t slice_
                "%s: the plan was built for another graph", who);
   HGNN_REQUIRE(slice_cols == 0 || (slice_cols >= 64 && slice_cols <= kSliceMaxCols), HGNN_EINVAL,
                "%s: slice_cols = %d outside [64, %d] (0 = default)", who, slice_cols, kSliceMaxCols);
-  return build_col_slices(p, g, slice_cols == 0 ? kSliceMaxCols : slice_cols, static_cast<hipStream_t>(stream));
+  SetupStream s(stream);
+  return build_col_slices(p, g, slice_cols == 0 ? kSliceMaxCols : slice_cols, s);
 }
 
 int32_t hgnn_plan_num_slices(const hgnn_plan* p) { return p ? p->ns : 0; }

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
   }
 }
 
-hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s) {
+hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
   HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskCounters) * size_t(q.nb) * (size_t(nwin) + 1)));
   HGNN_HIP(c.sec.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals)));
@@ -241,7 +241,7 @@ hgnn_status task_count(const TaskSource& q, TaskCounts& c, hipStream_t s) {
 }
 
 // After a wait for the stream of task_count.  The arrays are written when the stream has been waited for again.
-hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, hipStream_t s) {
+hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, SetupStream& s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
   int* counts = c.counts.as<int>();
   int* sums = counts + size_t(kTaskCounters) * size_t(q.nb) * size_t(nwin);
@@ -274,20 +274,20 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
 }
 
 // the tasks of plan p's column blocks
-hgnn_status build_block_tasks(hgnn_plan* p, hipStream_t s) {
-  DevTemp first;
+hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
+  DevTemp first(s);
   std::vector<int32_t> host(size_t(p->nb));
   for (int b = 0; b < p->nb; ++b) host[size_t(b)] = int32_t(p->boff[size_t(b)]);
   HGNN_HIP(first.alloc(sizeof(int32_t) * size_t(p->nb)));
   HGNN_HIP(hipMemcpyAsync(first.p, host.data(), sizeof(int32_t) * size_t(p->nb), hipMemcpyHostToDevice, s));
   const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks};
-  TaskCounts c;
+  TaskCounts c(s);
   hgnn_status st = task_count(q, c, s);
-  HGNN_HIP(hipStreamSynchronize(s));
   if (st != HGNN_OK) return st;
+  HGNN_HIP(s.wait());
   st = task_build(q, c, p->max_F, p->max_H, &p->btasks, s);
-  HGNN_HIP(hipStreamSynchronize(s));
   if (st != HGNN_OK) return st;
+  HGNN_HIP(s.wait());
   p->btasks->col16 = p->bcol16;
   p->btasks->width = p->block_width;
   return HGNN_OK;

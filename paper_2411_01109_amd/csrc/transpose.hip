@@ -192,17 +192,17 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
   HGNN_REQUIRE(g->eid == nullptr, HGNN_EINVAL, "hgnn_transpose: the input graph must not carry an edge-id map");
   HGNN_REQUIRE(rowptr_T != nullptr, HGNN_EINVAL, "hgnn_transpose: rowptr_T is NULL");
   HGNN_REQUIRE(g->nnz == 0 || (col_T && eid_T), HGNN_EINVAL, "hgnn_transpose: col_T or eid_T is NULL");
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  SetupStream s(stream);
   const int64_t E = g->nnz;
   if (E == 0) {
     HGNN_HIP(hipMemsetAsync(rowptr_T, 0, sizeof(int) * (size_t(g->ncols) + 1), s));
-    HGNN_HIP(hipStreamSynchronize(s));
+    HGNN_HIP(s.wait());
     return HGNN_OK;
   }
   const int col_bits = bits_for(g->ncols), row_bits = bits_for(g->nrows), pos_bits = bits_for(E);
   const dim3 per_edge(unsigned(ceil_div(E, kBlock))), per_tile(unsigned(ceil_div(E, kExpand)));
   const dim3 per_col(unsigned(ceil_div(int64_t(g->ncols) + 1, kBlock)));
-  DevTemp buf[2], ids[2], rows, tmp;
+  DevTemp buf[2] = {DevTemp(s), DevTemp(s)}, ids[2] = {DevTemp(s), DevTemp(s)}, rows(s), tmp(s);
   size_t tmp_bytes = 0;
   hipError_t e = hipSuccess;
   if (col_bits + row_bits + pos_bits <= 64) {
@@ -239,8 +239,7 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
       e = hipGetLastError();
     }
   }
-  const hipError_t e2 = hipStreamSynchronize(s);  // also after a failure: the buffers go back
-  if (e == hipSuccess) e = e2;
+  if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "hgnn_transpose: %s", hipGetErrorString(e));
   return HGNN_OK;
@@ -255,17 +254,17 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
   HGNN_REQUIRE(rowptr != nullptr, HGNN_EINVAL, "%s: rowptr is NULL", who);
   HGNN_REQUIRE(nnz == 0 || (row && col && col_out), HGNN_EINVAL, "%s: row, col or col_out is NULL", who);
   HGNN_REQUIRE(nnz == 0 || (nrows > 0 && ncols > 0), HGNN_EINVAL, "%s: edges in a graph without rows or columns", who);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  SetupStream s(stream);
   if (nnz == 0) {
     HGNN_HIP(hipMemsetAsync(rowptr, 0, sizeof(int) * (size_t(nrows) + 1), s));
-    HGNN_HIP(hipStreamSynchronize(s));
+    HGNN_HIP(s.wait());
     return HGNN_OK;
   }
   const int row_bits = bits_for(nrows), col_bits = bits_for(ncols), pos_bits = bits_for(nnz);
   const dim3 per_edge(unsigned(ceil_div(nnz, kBlock))), per_row(unsigned(ceil_div(int64_t(nrows) + 1, kBlock)));
   const size_t E = size_t(nnz);
-  DevTemp buf[2], ids[2], bad, tmp;
-  HostMail mail;
+  DevTemp buf[2] = {DevTemp(s), DevTemp(s)}, ids[2] = {DevTemp(s), DevTemp(s)}, bad(s), tmp(s);
+  HostMail mail(s);
   size_t tmp_bytes = 0;
   int hbad = 0;
   // the list position rides in the key where it fits (or is not asked for), else beside it
@@ -296,8 +295,7 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
   }
   if (e == hipSuccess && !packed) e = hipMemcpyAsync(eid, order.current(), 4 * E, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(mail.data ? static_cast<void*>(mail.data) : &hbad, bad.p, 4, hipMemcpyDeviceToHost, s);
-  const hipError_t e2 = hipStreamSynchronize(s);  // also after a failure: the buffers go back
-  if (e == hipSuccess) e = e2;
+  if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
   if (mail.data) hbad = *reinterpret_cast<const int*>(mail.data);
   if (hbad) return fail(HGNN_EINVAL, "%s: a row id outside [0, nrows) or a column id outside [0, ncols)", who);

@@ -113,7 +113,36 @@ def replaced_slices(h):
     h.lib.hgnn_plan_destroy(p)
 
 
-SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture, replaced_groups, replaced_slices]
+def failed_calls(h):
+    """Set-up calls that fail half-way leave nothing in flight that uses the blocks they give back: every allocation fails
+    in turn, and every wait."""
+    st, p = h.plan(A)
+    assert st == OK
+    g = ctypes.byref(h.g)
+    r, c = vp(h.out[0]), vp(h.out[1])
+    calls = [lambda: h.lib.hgnn_csr_validate(g, vp(A)), lambda: h.lib.hgnn_plan_add_groups(p, g, 32, vp(A)),
+             lambda: h.lib.hgnn_plan_add_slices(p, g, 0, vp(A)), lambda: h.plan(A)[0], lambda: h.plan(A, 3)[0],
+             lambda: h.lib.hgnn_transpose(g, r, c, c, vp(A)),
+             lambda: h.lib.hgnn_coo_to_csr(V, V, i64(E), vp(h.g.rowptr), vp(h.g.col), r, c, c, vp(A))]
+    for k, call in enumerate(calls):
+        for n in range(60):
+            h.lib.hgnn_release_cached_memory()
+            h.fake.fake_fail_malloc(n)
+            st = call()
+            h.fake.fake_fail_malloc(-1)
+            assert h.fake.fake_freed_busy() == 0 and h.fake.fake_busy(0) == 0, (k, n)
+            if st == OK:
+                break
+        assert st == OK and n > 0, (k, n)
+        h.fake.fake_fail_waits(1)
+        assert call() == EHIP, k
+        assert h.fake.fake_freed_busy() == 0, k
+        h.fake.fake_fail_waits(0)
+        h.fake.hipDeviceSynchronize()
+    h.lib.hgnn_plan_destroy(p)
+
+
+SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture, replaced_groups, replaced_slices, failed_calls]
 
 
 @pytest.fixture(scope="module")
