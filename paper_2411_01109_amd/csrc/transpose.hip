@@ -50,7 +50,8 @@ __global__ void coo_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz,
 
 // The row of every non-zero, handed to put(k, row): a workgroup takes kExpand consecutive positions, its rows mark the slot
 // of their first non-zero in LDS and a running maximum spreads the ids (a search of the offset array per non-zero took
-// 196 us at 5.5 M non-zeros).
+// 196 us at 5.5 M non-zeros).  A graph may come here before anything has looked at its offset array: whatever that holds, reads
+// stay inside its nrows + 1 entries and marks inside the tile (the rows are then wrong, as the array is).
 constexpr int kExpandPerThread = 8;
 constexpr int kExpand = kBlock * kExpandPerThread;
 
@@ -63,10 +64,11 @@ __device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int 
   if (threadIdx.x < 2) s_lim[threadIdx.x] = row_of_edge(rowptr, nrows, threadIdx.x == 0 ? e0 : e0 + n - 1);
   for (int i = threadIdx.x; i < kExpand; i += kBlock) s_row[i] = -1;
   __syncthreads();
-  const int lo = s_lim[0], hi = s_lim[1];
+  const int lo = max(s_lim[0], 0), hi = min(s_lim[1], nrows - 1);
   for (int r = lo + 1 + int(threadIdx.x); r <= hi; r += kBlock) {
     const int p = rowptr[r];
-    if (rowptr[r + 1] > p) s_row[p - int(e0)] = r;
+    const int64_t at = int64_t(p) - e0;
+    if (rowptr[r + 1] > p && at >= 0 && at < n) s_row[at] = r;
   }
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;

@@ -132,3 +132,41 @@ def test_kept_memory(hgnn, dev):
     hgnn.hgnn_release_cached_memory()
     work(0)
     assert not wrong
+
+
+@pytest.mark.parametrize("wide", [False, True])  # one sort key of all fields, or two arrays
+@pytest.mark.parametrize("what", ["ends early", "ends late", "begins late", "falls", "negative", "all past the end"])
+def test_transpose_of_a_malformed_offset_array(hgnn, dev, what, wide):
+    """Transposition may come before validation: it stays inside its arrays whatever the offsets are.  The order of the columns
+    does not depend on them."""
+    print(f"transpose {what} wide={wide}", flush=True)
+    V, E = ((1 << 24) + 1, (1 << 15) + 1) if wide else (700, 5000)
+    r = np.random.default_rng(E)
+    rowptr = np.sort(r.integers(0, E + 1, V + 1)).astype(np.int32)
+    rowptr[0], rowptr[-1] = 0, E
+    col = r.integers(0, V, E).astype(np.int32)
+    if what == "ends early":
+        rowptr = np.minimum(rowptr, E - 4500)
+    elif what == "ends late":
+        rowptr[-1] = E + 100000
+    elif what == "begins late":
+        rowptr = np.maximum(rowptr, 3000)
+    elif what == "falls":
+        rowptr[V // 3], rowptr[V // 2] = E, 0
+    elif what == "negative":
+        rowptr[V // 4:V // 2] = -(1 << 31)
+    elif what == "all past the end":
+        rowptr[:] = (1 << 31) - 1
+    pad = 64
+    out = [torch.full((n + 2 * pad,), -7, dtype=torch.int32, device=dev) for n in (V + 1, E, E)]
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    from paper_2411_01109_amd import binding
+    st = hgnn.load().hgnn_transpose(g.ref, *(o[pad:].data_ptr() for o in out), binding._stream(None))
+    assert st == hgnn.HGNN_OK
+    for o in out:
+        assert (o[:pad] == -7).all() and (o[-pad:] == -7).all()
+    t = np.argsort(col, kind="stable")
+    assert np.array_equal(down(out[2][pad:-pad]), t)
+    assert np.array_equal(down(out[0][pad:-pad]), np.searchsorted(col[t], np.arange(V + 1)))
+    with pytest.raises(hgnn.HgnnError):
+        hgnn.hgnn_csr_validate(g)
