@@ -27,7 +27,7 @@ __global__ void block_cuts_kernel(const int* __restrict__ rowptr, const int* __r
   if (b < nb) {
     const int64_t key = int64_t(b) * width;
     while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
+      const int mid = lo + ((hi - lo) >> 1);
       if (col[mid] < key) lo = mid + 1;
       else hi = mid;
     }

@@ -136,14 +136,19 @@ struct HostMail {
 // row that holds CSR position k: the last r with rowptr[r] <= k (an upper bound minus one, so
 // empty rows are skipped)
 __host__ __device__ inline int row_of_edge(const int* rowptr, int nrows, int64_t k) {
-  int lo = 0, hi = nrows + 1;
+  uint32_t lo = 0, hi = uint32_t(nrows) + 1u;
   while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
+    const uint32_t mid = (lo + hi) >> 1;
     if (int64_t(rowptr[mid]) <= k) lo = mid + 1;
     else hi = mid;
   }
-  return lo - 1;
+  return int(lo) - 1;
 }
+
+// Positions of non-zeros and numbers of pieces go up to 2^31 - 1.  A walk forms sums up to a step (at most a few thousand)
+// beyond its end before it compares them, so it counts in pos_t: 32 bits hold them without a sign.
+typedef uint32_t pos_t;
+__host__ __device__ inline int pieces_of(int len, int per) { return int((pos_t(len) + pos_t(per) - 1u) / pos_t(per)); }
 
 // Orders the LDS accesses of one wave: what its lanes wrote before is visible to all its lanes after.
 // The kernels that stage a segment give every wave a private LDS region, so nothing wider than the
@@ -338,7 +343,8 @@ struct hgnn_seg_block {
 struct hgnn_task_sec {  // the pieces of one column block (or of the whole graph)
   int32_t w_off, nw;  // task[w_off ..): whole-wave pieces
   int32_t g_off, ng;  // task[g_off ..): lane-group pieces
-  int32_t z_off, nz;  // zrow[z_off ..): empty rows
+  int64_t z_off;      // zrow[z_off ..): empty rows (of all blocks: up to blocks * rows)
+  int32_t nz;
   int32_t first;      // the block's first non-zero in the task's column array
 };
 struct hgnn_row_tasks {
@@ -466,7 +472,8 @@ struct TaskSource {
 constexpr int kGroupMaxBlocks = 256;
 inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 : 128; }
 struct TaskTotals {
-  int32_t n_task, n_whole, n_zero, n_split, n_slots;
+  int64_t n_zero;
+  int32_t n_task, n_whole, n_split, n_slots;
 };
 // The same without a plan, in memory of the caller and without a host wait: the launch shape is then not known on the host, so
 // the kernels read it from `sec` and `totals` and walk the tasks with a grid stride.

@@ -216,8 +216,8 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   a.enter_block(w.block);
   if (w.z1 > w.z0) {
     const Soft<SAVE> none;
-    for (int i = w.z0 + g; i < w.z1; i += G)
-      if (active) row_store<SAVE>(a, v.zrow[i], f0, head, leader, none);
+    for (pos_t i = w.z0 + g; i < w.z1; i += G)
+      if (active) row_store<SAVE>(a, w.zrow[i], f0, head, leader, none);
     return;
   }
   int* const s_hnd = s_handles + g * Rd::PITCH;
@@ -242,8 +242,8 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   const int own = (lane & (Rd::LC - 1)) * Rd::E;
   const int edge = Ht::own_edge(l);
   Soft<SAVE> t;  // z and zm: this lane's edges only, until the end
-  for (int k = w.beg; k < w.end; k += w.step) {
-    const int end = k + w.span < w.end ? k + w.span : w.end;
+  for (pos_t k = w.beg; k < w.end; k += w.step) {
+    const pos_t end = k + w.span < w.end ? k + w.span : w.end;
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
@@ -365,13 +365,13 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (i0 + g < n_split) q = split[i0 + g];
   // merges the pieces first, first + stride, ... < end, four of them in flight at a time
-  auto take = [&](Soft<SAVE>& t, int first, int end, int stride) {
-    for (int k0 = first; k0 < end; k0 += 4 * stride) {
+  auto take = [&](Soft<SAVE>& t, pos_t first, pos_t end, pos_t stride) {
+    for (pos_t k0 = first; k0 < end; k0 += 4 * stride) {
       half8_t o[4], om[4];
       float m[4], z[4], cp[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int k = k0 + u * stride;
+        const pos_t k = k0 + u * stride;
         const int64_t slot = k < end ? k : k0;
         o[u] = *reinterpret_cast<const half8_t*>(a.staging + slot * a.stage_ld + f0c);
         om[u] = SAVE ? *reinterpret_cast<const half8_t*>(a.staging_m + slot * a.stage_ld + f0c) : o[u];

@@ -101,8 +101,8 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   a.enter_block(w.block);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum alpha * x          (VEC)
   if (w.z1 > w.z0) {
-    for (int i = w.z0 + g; i < w.z1; i += G)
-      if (active) bwd_row_store<VEC>(a, v.zrow[i], f0, head, leader, acc, 0.f);
+    for (pos_t i = w.z0 + g; i < w.z1; i += G)
+      if (active) bwd_row_store<VEC>(a, w.zrow[i], f0, head, leader, acc, 0.f);
     return;
   }
   float wacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // sum alpha * m * x
@@ -118,8 +118,8 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   else v_row = a.vtab[int64_t(row) * a.H + head];
   const int own = (lane & (Rd::LC - 1)) * Rd::E;
   const int edge = Ht::own_edge(l);
-  for (int k = w.beg; k < w.end; k += w.step) {
-    const int end = k + w.span < w.end ? k + w.span : w.end;
+  for (pos_t k = w.beg; k < w.end; k += w.step) {
+    const pos_t end = k + w.span < w.end ? k + w.span : w.end;
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
@@ -222,13 +222,13 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (i0 + g < n_split) q = split[i0 + g];
   // adds the pieces first, first + stride, ... < end, four of them in flight at a time
-  auto take = [&](float (&acc)[8], float& ds, int first, int end, int stride) {
-    for (int k0 = first; k0 < end; k0 += 4 * stride) {
+  auto take = [&](float (&acc)[8], float& ds, pos_t first, pos_t end, pos_t stride) {
+    for (pos_t k0 = first; k0 < end; k0 += 4 * stride) {
       half8_t o[4];
       float d[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int k = k0 + u * stride;
+        const pos_t k = k0 + u * stride;
         o[u] = half8_t(0);
         d[u] = 0.f;
         if (k < end) {

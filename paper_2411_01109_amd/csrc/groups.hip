@@ -20,7 +20,7 @@ __global__ void group_counts_kernel(const int* __restrict__ rowptr, int nrows, i
   const int64_t r = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (r > nrows) return;
   int c = 0;
-  if (r < nrows) c = (rowptr[r + 1] - rowptr[r] + ng - 1) / ng;
+  if (r < nrows) c = pieces_of(rowptr[r + 1] - rowptr[r], ng);
   cnt[r] = c;
   mcnt[r] = c > 1 ? c : 0;
 }
@@ -31,7 +31,7 @@ __global__ void group_rows_kernel(const int* __restrict__ goff, int nrows, int64
   if (j >= n_groups) return;
   int lo = 0, hi = nrows;  // first index in [0, nrows] whose offset exceeds j
   while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
+    const int mid = lo + ((hi - lo) >> 1);
     if (goff[mid] <= j) lo = mid + 1;
     else hi = mid;
   }

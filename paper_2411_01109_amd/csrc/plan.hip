@@ -243,7 +243,7 @@ __device__ __forceinline__ void row_memberships(const RowLists& q, int r, int (&
   m[kSplitList] = e > b && (b / q.S) != ((e - 1) / q.S);
   m[kBigList] = q.big_deg >= 0 && len > q.big_deg;
   m[kMidList] = q.big_deg >= 0 && len > q.mid_deg && len <= q.big_deg;
-  m[kChunkList] = m[kBigList] ? (len + kHubEdges - 1) / kHubEdges : 0;
+  m[kChunkList] = m[kBigList] ? pieces_of(len, kHubEdges) : 0;
 }
 
 // exclusive scan of one value per thread over the workgroup (blockDim.x == kBlock)

@@ -195,8 +195,8 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
   const int64_t shift = a.delta ? int64_t(a.delta[int64_t(w.block) * a.nrows + row]) - w.first : 0;
   const int own = (lane & (Rd::LC - 1)) * Rd::E;
   const int edge = Ht::own_edge(l);
-  for (int k = w.beg; k < w.end; k += w.step) {
-    const int end = k + w.span < w.end ? k + w.span : w.end;
+  for (pos_t k = w.beg; k < w.end; k += w.step) {
+    const pos_t end = k + w.span < w.end ? k + w.span : w.end;
     wave_sync();  // the previous round has been read
     {
       int c[Rd::E];
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
       }
     }
     wave_sync();
-    const int n = (end - k) * a.H;
+    const int n = int(end - k) * a.H;
     half_t* dst = a.out + (int64_t(k) + shift) * a.H;
     for (int j = 4 * l; j < n; j += 4 * L) {
       if (j + 4 <= n) {

@@ -94,11 +94,11 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   // Slots beyond the batch's total repeat its last slot (a valid position): for the score that stores the same value
   // twice, for the sums the repeated value is replaced by zero.  The row of a slot comes from a branch-free binary
   // search over the 65 prefix values, six LDS reads per slot; the eight searches of a round are independent chains.
-  auto plan_round = [&](int q0, int total, int (&kk)[kSliceUnroll], int (&jj)[kSliceUnroll]) {
+  auto plan_round = [&](pos_t q0, pos_t total, int (&kk)[kSliceUnroll], int (&jj)[kSliceUnroll]) {
     int q[kSliceUnroll];
 #pragma unroll
     for (int u = 0; u < kSliceUnroll; ++u) {
-      q[u] = q0 + u * kWave < total ? q0 + u * kWave : total - 1;
+      q[u] = int(q0 + u * kWave < total ? q0 + u * kWave : total - 1);
       jj[u] = 0;
     }
 #pragma unroll
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
       if (COLSUM) tt[u] = tbits[kk[u]];
     }
   };
-  auto work = [&](int q0, int total, const int (&kk)[kSliceUnroll], const int (&jj)[kSliceUnroll], const int (&cc)[kSliceUnroll],
+  auto work = [&](pos_t q0, pos_t total, const int (&kk)[kSliceUnroll], const int (&jj)[kSliceUnroll], const int (&cc)[kSliceUnroll],
                   const unsigned (&tt)[kSliceUnroll]) {
 #pragma unroll
     for (int u = 0; u < kSliceUnroll; ++u) {
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
       const int t = __shfl_up(inc, d);
       if (lane >= d) inc += t;
     }
-    const int total = __shfl(inc, kWave - 1);
+    const pos_t total = pos_t(__shfl(inc, kWave - 1));
     if (lane == 0) s_p[0] = 0;
     s_p[lane + 1] = inc;
     s_d[lane] = b - (inc - (e - b));  // first position minus first slot
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
       plan_round(lane, total, kA, jA);
       issue(kA, cA, tA);
     }
-    for (int qb = 0; qb < total; qb += kWave * kSliceUnroll) {
+    for (pos_t qb = 0; qb < total; qb += kWave * kSliceUnroll) {
       const bool more = qb + kWave * kSliceUnroll < total;
       if (more) {
         plan_round(lane + qb + kWave * kSliceUnroll, total, kB, jB);
@@ -230,7 +230,7 @@ __global__ void slice_cuts_kernel(const int* __restrict__ rowptr, const int* __r
   if (s < ns) {
     const int64_t key = int64_t(s) * W;
     while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
+      const int mid = lo + ((hi - lo) >> 1);
       if (col[mid] < key) lo = mid + 1;
       else hi = mid;
     }
@@ -251,7 +251,7 @@ __global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int
   const int64_t target = nnz * c / nch;
   int lo = 0, hi = nrows;
   while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
+    const int mid = lo + ((hi - lo) >> 1);
     if (int64_t(rowptr[mid]) < target) lo = mid + 1;
     else hi = mid;
   }

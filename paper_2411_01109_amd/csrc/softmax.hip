@@ -238,7 +238,7 @@ __device__ __forceinline__ void rowsum_row(const EdgeRowArgs& a, const Team& tea
   for (int h = 0; h < H; ++h) s[h] = 0.f;
   if (a.eid) {  // transposed view: one lane per non-zero, its H values are contiguous at slot eid[k]
     typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
-    for (int k = beg + team.rank; k < end; k += Team::size) {
+    for (pos_t k = pos_t(beg) + team.rank; k < pos_t(end); k += Team::size) {
       const int64_t slot = a.eid[k];
       if (H == 1) {
         s[0] += float(a.x0[slot]);
@@ -318,7 +318,7 @@ __device__ __forceinline__ void hub_chunk_range(const EdgeRowArgs& a, const HubC
   const int row = c.row[slot];
   beg = a.rowptr[row] + (slot - c.first[slot]) * kHubEdges;
   const int row_end = a.rowptr[row + 1];
-  end = beg + kHubEdges < row_end ? beg + kHubEdges : row_end;
+  end = row_end - beg > kHubEdges ? beg + kHubEdges : row_end;
 }
 
 template <int OP, int H>
@@ -337,7 +337,7 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
   }
   if (OP == kSum && a.eid) {
     typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
-    for (int k = beg + int(threadIdx.x); k < end; k += kHubThreads) {
+    for (pos_t k = pos_t(beg) + threadIdx.x; k < pos_t(end); k += kHubThreads) {
       const int64_t s = a.eid[k];
       if (H == 1) {
         r0[0] += float(a.x0[s]);
@@ -633,19 +633,19 @@ __global__ __launch_bounds__(kWave) void rowsum_task_kernel(RowsumArgs a, TaskVi
 #pragma unroll
   for (int h = 0; h < H; ++h) s[h] = 0.f;
   if (w.z1 > w.z0) {
-    for (int i = w.z0 + lane; i < w.z1; i += kWave) a.template store<H>(w.block, v.zrow[i], s);
+    for (pos_t i = w.z0 + lane; i < w.z1; i += kWave) a.template store<H>(w.block, w.zrow[i], s);
     return;
   }
-  int k = w.beg + l * E;
-  int end = w.beg + w.span < w.end ? w.beg + w.span : w.end;
+  pos_t k = w.beg + l * E;
+  pos_t end = w.beg + w.span < w.end ? w.beg + w.span : w.end;
   int id[E];
   load_run<E, true>(a.eid, k, end, id);  // positions past the end hold slot 0: read, not added
-  for (int base = w.beg; base < w.end; base += w.step) {
+  for (pos_t base = w.beg; base < w.end; base += w.step) {
     hv_t x[E];
 #pragma unroll
     for (int m = 0; m < E; ++m) x[m] = *reinterpret_cast<const hv_t*>(a.t + int64_t(id[m]) * H);
-    const int kn = k + w.step, past = base + w.step + w.span;
-    const int endn = past < w.end ? past : w.end;
+    const pos_t kn = k + w.step, past = base + w.step + w.span;
+    const pos_t endn = past < w.end ? past : w.end;
     load_run<E, true>(a.eid, kn, endn, id);
 #pragma unroll
     for (int m = 0; m < E; ++m)

@@ -118,23 +118,23 @@ constexpr int kLongRowMin = 256, kLongRowMax = 1024;  // the hub threshold is 8 
 // U of them in flight at a time; the column ids of the next U are fetched while the rows of
 // the current U are on their way, so one trip through the loop costs one memory latency, not two
 template <int STRIDE, bool HAS_W, int U>
-__device__ __forceinline__ void edges_accumulate(const SpmmArgs& a, int first, int end, int f0c, int head,
+__device__ __forceinline__ void edges_accumulate(const SpmmArgs& a, pos_t first, pos_t end, int f0c, int head,
                                                  float (&acc)[8]) {
   int c[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) c[u] = first + u * STRIDE < end ? a.col[first + u * STRIDE] : 0;
-  for (int k = first; k < end; k += STRIDE * U) {
+  for (pos_t k = first; k < end; k += STRIDE * U) {
     half8_t x[U];
     float wv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int kk = k + u * STRIDE;
+      const pos_t kk = k + u * STRIDE;
       x[u] = half8_t(0);
       wv[u] = 0.f;
       if (kk < end) {
         x[u] = *reinterpret_cast<const half8_t*>(a.X + int64_t(c[u]) * a.ldx + f0c);
         if (HAS_W) {
-          const int64_t slot = a.eid ? a.eid[kk] : kk;
+          const int64_t slot = a.eid ? int64_t(a.eid[kk]) : int64_t(kk);
           wv[u] = float(a.w[slot * a.H + head]);
         } else {
           wv[u] = a.one;
@@ -143,7 +143,7 @@ __device__ __forceinline__ void edges_accumulate(const SpmmArgs& a, int first, i
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int kn = k + (U + u) * STRIDE;
+      const pos_t kn = k + (U + u) * STRIDE;
       c[u] = kn < end ? a.col[kn] : 0;
     }
 #pragma unroll
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kBlock) void hub_scan_kernel(SpmmArgs a, HubLists h
     if (r >= a.nrows) break;
     const int deg = a.rowptr[r + 1] - a.rowptr[r];
     if (deg > a.long_row) {
-      my_chunks += (deg + kHubChunk - 1) / kHubChunk;
+      my_chunks += pieces_of(deg, kHubChunk);
       ++my_hubs;
     }
   }
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void hub_scan_kernel(SpmmArgs a, HubLists h
     if (r >= a.nrows) break;
     const int deg = a.rowptr[r + 1] - a.rowptr[r];
     if (deg <= a.long_row) continue;
-    const int nch = (deg + kHubChunk - 1) / kHubChunk;
+    const int nch = pieces_of(deg, kHubChunk);
     if (base + nch <= h.max_chunks && i < h.max_hubs) {  // always true for a valid rowptr
       h.hub_row[i] = int(r);
       h.hub_base[i] = base;
@@ -301,7 +301,7 @@ __device__ __forceinline__ void spmm_hub_body(const SpmmArgs& a, const HubLists&
     const int row = h.chunk_row[c];
     const int row_end = a.rowptr[row + 1];
     const int b = a.rowptr[row] + h.chunk_no[c] * kHubChunk;
-    const int e = b + kHubChunk < row_end ? b + kHubChunk : row_end;
+    const int e = row_end - b > kHubChunk ? b + kHubChunk : row_end;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     edges_accumulate<G, HAS_W, 4>(a, b + g, e, f0c, f0c / a.D, acc);
     groups_reduce<L>(acc);
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kBlock) void spmm_hub_sum_kernel(SpmmArgs a, HubLis
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
   const int row = h.hub_row[i];
-  const int nch = (a.rowptr[row + 1] - a.rowptr[row] + kHubChunk - 1) / kHubChunk;
+  const int nch = pieces_of(a.rowptr[row + 1] - a.rowptr[row], kHubChunk);
   const int pitch = (a.F + 7) & ~7;
   const float* part = h.part + int64_t(h.hub_base[i]) * pitch + f0c;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -384,7 +384,7 @@ __device__ __forceinline__ int wave_lower_bound(const int* __restrict__ col, int
     lo = nlo;
     hi = nhi;
   }
-  const int v = lo + lane < hi ? col[lo + lane] : INT_MAX;
+  const int v = lane < hi - lo ? col[lo + lane] : INT_MAX;
   return lo + __popcll(__ballot(int64_t(v) < key));
 }
 
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kBlock) void row_cuts_kernel(const int* __restrict_
       if (w > end - kWave) w = end - kWave;
       if (w < beg) w = beg;
       wlo[b] = w;
-      if (w + lane < end) v[b] = col[w + lane];
+      if (lane < end - w) v[b] = col[w + lane];
     }
   }
   int cut = lane == 0 ? beg : end;
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kBlock) void row_cuts_kernel(const int* __restrict_
   for (int b = 1; b < kMaxPasses; ++b) {
     if (b < npass) {
       const int64_t key = int64_t(b) * width;
-      const int whi = wlo[b] + kWave < end ? wlo[b] + kWave : end;
+      const int whi = end - wlo[b] > kWave ? wlo[b] + kWave : end;
       const int cnt = __popcll(__ballot(int64_t(v[b]) < key));
       int c;
       if (cnt > 0 && cnt < whi - wlo[b]) c = wlo[b] + cnt;                          // inside the window
@@ -570,8 +570,8 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   a.Y += int64_t(w.block) * a.block_y_stride;
   if (w.z1 > w.z0) {
     const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int i = w.z0 + g; i < w.z1; i += G)
-      if (active) store_row(a, v.zrow[i], f0, zero, 0.f);
+    for (pos_t i = w.z0 + g; i < w.z1; i += G)
+      if (active) store_row(a, w.zrow[i], f0, zero, 0.f);
     return;
   }
   const int H = HV > 0 ? HV : a.H;
@@ -586,9 +586,9 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   const int own = (lane & (Rd::LC - 1)) * E;
   const bool nt = MAPPED && stream_nontemporal(a.nnz);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int k = w.beg; k < w.end; k += w.step) {
-    const int end = k + w.span < w.end ? k + w.span : w.end;
-    const int i0 = k + own;
+  for (pos_t k = w.beg; k < w.end; k += w.step) {
+    const pos_t end = k + w.span < w.end ? k + w.span : w.end;
+    const pos_t i0 = k + own;
     wave_sync();  // the previous round has been read
     {
       int c[E], e[E];
@@ -607,7 +607,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
           for (int m = 0; m < E; ++m) {
             wv[m] = hv_t(half_t(0));
             if (i0 + m < end) {
-              if (WM == 1 || a.w) wv[m] = *reinterpret_cast<const hv_t*>(a.w + int64_t(MAPPED ? e[m] : i0 + m + shift) * NV);
+              if (WM == 1 || a.w) wv[m] = *reinterpret_cast<const hv_t*>(a.w + int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * NV);
               else wv[m] = hv_t(half_t(1));
             }
           }
@@ -629,7 +629,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
           for (int h = 0; h < H; ++h) {
             float x = 0.f;
             if (HV > 0) x = float(wv[m][h < NV ? h : 0]) * (WM == 2 ? cs[m] : 1.f);
-            else if (i0 + m < end) x = (a.w ? float(a.w[int64_t(MAPPED ? e[m] : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
+            else if (i0 + m < end) x = (a.w ? float(a.w[int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
             s_val[(own + m) * H + h] = factor_t(x);
           }
       }

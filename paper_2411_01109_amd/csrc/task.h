@@ -65,7 +65,7 @@ struct Round {
 
 // v[m] = p[i0 + m] for the entries below end; the others are 0
 template <int E, bool NT>
-__device__ __forceinline__ void load_run(const int* __restrict__ p, int i0, int end, int (&v)[E]) {
+__device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, pos_t end, int (&v)[E]) {
   const int* q = p + i0;
   if (i0 + E <= end) {
 #pragma unroll
@@ -102,16 +102,17 @@ template <int G>
 __device__ __forceinline__ int task_waves(const TaskView& v) {
   if (!v.totals) return v.first_wave[v.nb];
   const hgnn_task_sec s = v.sec[0];
-  return ((s.nw + 7) & ~7) + ((((s.ng + G - 1) / G) + 7) & ~7) + (s.nz + G * kZeroTurns - 1) / (G * kZeroTurns);
+  return int(((pos_t(s.nw) + 7) & ~7u) + (((pos_t(s.ng) + G - 1) / G + 7) & ~7u) + (pos_t(s.nz) + G * kZeroTurns - 1) / (G * kZeroTurns));
 }
 
 // what one wave does
 struct TaskWave {
   int block, first; // column block and its first non-zero
   bool whole;       // all lane groups share one piece
-  int z0, z1;       // z1 > z0: entries [z0, z1) of zrow, nothing else
-  int beg, end;     // this lane group's first non-zero and the end of the piece
-  int span, step;   // non-zeros per round of this group (a multiple of 8, at most Round<L>::R), and from one round to the next
+  const int* zrow;  // the block's empty rows
+  pos_t z0, z1;     // z1 > z0: entries [z0, z1) of them, nothing else
+  pos_t beg, end;   // this lane group's first non-zero and the end of the piece
+  pos_t span, step; // non-zeros per round of this group (a multiple of 8, at most Round<L>::R), and from one round to the next
   int row, slot;    // row -1: no piece for this lane group
 };
 
@@ -127,13 +128,14 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   w.block = b;
   w.first = s.first;
   w.whole = i < s.nw;
+  w.zrow = v.zrow + s.z_off;
   w.z0 = w.z1 = 0;
   int4_t t = {0, 0, -1, -1};
   if (w.whole) {
     t = v.task[s.w_off + i];
   } else {
     i -= (s.nw + 7) & ~7;  // sections begin at multiples of eight: i & 7 is the XCD
-    const int gw = (((s.ng + G - 1) / G) + 7) & ~7;
+    const int gw = int(((pos_t(s.ng) + G - 1) / G + 7) & ~7u);
     if (i < 0) {  // between two sections: nothing
     } else if (i < gw) {
       const int panel = 8 * v.chunk, full = gw / panel * panel;
@@ -141,13 +143,11 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
         const int p = i / panel * panel, j = i - p;
         i = p + (j & 7) * v.chunk + (j >> 3);
       }
-      const int k = i * G + g;
-      if (k < s.ng) t = v.task[s.g_off + k];
+      const pos_t k = pos_t(i) * G + g;
+      if (k < pos_t(s.ng)) t = v.task[pos_t(s.g_off) + k];
     } else {
-      w.z0 = (i - gw) * (G * kZeroTurns);
-      w.z1 = w.z0 + G * kZeroTurns < s.nz ? w.z0 + G * kZeroTurns : s.nz;
-      w.z0 += s.z_off;
-      w.z1 += s.z_off;
+      w.z0 = pos_t(i - gw) * (G * kZeroTurns);
+      w.z1 = w.z0 + G * kZeroTurns < pos_t(s.nz) ? w.z0 + G * kZeroTurns : pos_t(s.nz);
     }
   }
   w.beg = t[0];
@@ -156,7 +156,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   w.slot = t[3];
   w.span = w.step = Round<L>::R;
   if (w.whole) {  // the lane groups share the piece in equal runs
-    const int each = (((t[1] & 0xffff) + G - 1) / G + 7) & ~7;
+    const pos_t each = (((t[1] & 0xffff) + G - 1) / G + 7) & ~7;
     if (each < w.span) w.span = each;
     w.beg += w.span * g;
     w.step = w.span * G;
@@ -167,7 +167,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these
 // passes draw from HBM, and a gather waits behind it (114 M non-zeros x 64 in eight blocks: 0.81 -> 0.76 ms).
 template <int E>
-__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, int i0, int end, int (&c)[E]) {
+__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, pos_t end, int (&c)[E]) {
   if (v.col16) {
     const uint16_t* q = v.col16 + i0;
     const int first = block * v.width;

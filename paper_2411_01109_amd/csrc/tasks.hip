@@ -30,9 +30,8 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
   c.part = c.len;
   c.m = c.len > 0 ? 1 : 0;
   if (c.len > q.S) {
-    const int m = (c.len + q.S - 1) / q.S;
-    c.part = (c.len + m - 1) / m;
-    c.m = (c.len + c.part - 1) / c.part;
+    c.part = pieces_of(c.len, pieces_of(c.len, q.S));
+    c.m = pieces_of(c.len, c.part);
   }
   return c;
 }
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, i
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    TaskTotals t{0, 0, 0, 0, 0};
+    TaskTotals t{};
     for (int b = 0; b < nb; ++b) {
       hgnn_task_sec s;
       s.nw = sums[kTaskW * nb + b];
@@ -153,7 +152,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
     s = hgnn_task_sec{0, all[kTaskW], all[kTaskW], all[kTaskG], 0, all[kTaskZ], 0};
     if (w == 0 && threadIdx.x == 0) {
       *sec = s;
-      *totals = TaskTotals{all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskZ], all[kTaskSplit], all[kTaskSlots]};
+      *totals = TaskTotals{all[kTaskZ], all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskSplit], all[kTaskSlots]};
     }
   } else {
     s = sec[b];
@@ -161,7 +160,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
   for (int i = threadIdx.x; i <= kMaxGroupLen; i += kTaskThreads) at[i] = 0;
   if (threadIdx.x < kTaskCounters) {
     const int i = threadIdx.x;
-    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? s.z_off : (SELF ? 0 : sums[i * q.nb + b]);
+    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? 0 : (SELF ? 0 : sums[i * q.nb + b]);
     next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
   }
   __syncthreads();
@@ -197,7 +196,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
     const RowCut c = cut[u];
     const int r = w * kTaskWindow + u * kTaskThreads + int(threadIdx.x);
     int slot = -1, pos = 0, k0 = 0;
-    if (c.m == 0) zrow[atomicAdd(&next[kTaskZ], 1)] = r;
+    if (c.m == 0) zrow[s.z_off + atomicAdd(&next[kTaskZ], 1)] = r;
     if (c.m > 1) {
       slot = atomicAdd(&next[kTaskSlots], c.m);
       split[atomicAdd(&next[kTaskSplit], 1)] = make_int4(r, slot, c.m, b);
@@ -264,7 +263,7 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
     HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(tot.n_slots) * size_t(max_F)));
     HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(tot.n_slots) * size_t(max_H)));
   }
-  if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, tot.n_zero, 0};
+  if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, int32_t(tot.n_zero), 0};
   else HGNN_HIP(hipMemcpyAsync(t->host.data(), t->sec, sizeof(hgnn_task_sec) * size_t(q.nb), hipMemcpyDeviceToHost, s));
   if (nwin > 0)
     task_write_kernel<false><<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts, sums, t->sec, nullptr,

@@ -87,3 +87,77 @@ def test_row_sums_through_the_map(hgnn, dev, H, S, nb):
     t64 = t.astype(np.float64)[slots]
     compare("row sums", down(out), oracle.edge_rowsum(rp, t64), oracle.edge_rowsum(rp, np.abs(t64)))
     hgnn.hgnn_plan_destroy(p)
+
+
+def test_positions_up_to_the_last_one(hgnn, dev):
+    """2^31 - 1 non-zeros: the walks over the last pieces form sums beyond 2^31.  Every column is 0, so the results are known."""
+    if torch.cuda.get_device_properties(dev).total_memory < 100 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    E, tail = (1 << 31) - 1, [1, 7, 0, 9, 33, 255, 300, 2000]
+    rest = E - sum(tail)
+    n = -(-rest // 2000)
+    deg = torch.full((n + len(tail),), rest // n, dtype=torch.int64, device=dev)
+    deg[:rest % n] += 1
+    deg[n:] = torch.tensor(tail, device=dev)
+    V, D = deg.numel(), 8
+    rowptr = torch.zeros(V + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(deg, 0, out=rowptr[1:])
+    assert int(rowptr[-1]) == E
+    col = torch.zeros(E, dtype=torch.int32, device=dev)
+    g = hgnn.Csr(rowptr.int(), col, ncols=8)
+    x0 = torch.tensor([1, 0.5, 1, 0.5, 1, 1, 0.5, 1], dtype=torch.float16, device=dev)
+    X = torch.zeros((8, D), dtype=torch.float16, device=dev)
+    X[0] = x0
+    want = deg[:, None].float() * x0.float()  # at most 2000, halves: exact in fp16, partial sums too
+    Y = torch.empty((V, D), dtype=torch.float16, device=dev)
+
+    def check(what):
+        torch.cuda.synchronize()
+        print(what, flush=True)
+        assert torch.equal(Y.float(), want), what
+
+    p = hgnn.hgnn_plan_create(g, 256, D, 1)
+    hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+    check("discretized")
+    w = torch.ones((E, 1), dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm_discretized(p, g, w, 1, X, Y)
+    check("edge values")
+    ws = torch.empty(hgnn.hgnn_spmm_workspace(V, 8, E, D), dtype=torch.uint8, device=dev)
+    hgnn.hgnn_spmm(g, w, 1, X, Y, workspace=ws)
+    check("without a plan")
+    hgnn.hgnn_spmm(g, w, 1, X, Y)
+    check("without a workspace")
+    gm = hgnn.Csr(g.rowptr, col, ncols=8, eid=torch.arange(E, dtype=torch.int32, device=dev))
+    hgnn.hgnn_spmm_discretized(p, gm, w, 1, X, Y)
+    check("through the map")
+    sums = torch.empty((V, 1), dtype=torch.float16, device=dev)
+    for q in (p, None):
+        hgnn.hgnn_edge_rowsum(gm, q, 1, w, sums)
+        assert torch.equal(sums[:, 0].float(), deg.float()), q
+    del gm, ws
+    print("row sums", flush=True)
+    U = x0.repeat(V, 1)
+    hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, 1, D, U, X, w)
+    assert bool((w == float((x0.float() ** 2).sum())).all())
+    print("sddmm", flush=True)
+    zero = torch.zeros(D, dtype=torch.float16, device=dev)
+    lse = torch.empty((V, 1), dtype=torch.float32, device=dev)
+    hgnn.hgnn_gat_forward_fused(g, p, 1, D, U, X, zero, zero, Y, lse)
+    full = (deg > 0)[:, None]
+    assert ((Y.float() - x0.float() * full).abs() <= 1e-3).all()
+    assert ((lse[:, 0] - deg.clamp(min=1).float().log()).abs() <= 1e-4).all()
+    print("gat forward", flush=True)
+    del w
+    col_t = torch.repeat_interleave(torch.arange(V, dtype=torch.int32, device=dev), deg, output_size=E)
+    rp_t = torch.full((9,), E, dtype=torch.int32, device=dev)
+    rp_t[0] = 0
+    gt = hgnn.Csr(rp_t, col_t, ncols=V)
+    pt = hgnn.hgnn_plan_create(gt, 256, D, 1)
+    dO = torch.full((V, D), 2.0 ** -6, dtype=torch.float16, device=dev)
+    dV, d_el, d_er = torch.empty_like(X), torch.empty((V, 1), dtype=torch.float16, device=dev), torch.empty((8, 1), dtype=torch.float16, device=dev)
+    hgnn.hgnn_gat_backward_fused(g, p, gt, pt, 1, D, U, X, zero, zero, Y, lse, dO, dV, d_el, d_er)
+    total = float(full.sum()) * 2.0 ** -6  # each row's weights add up to one; 8.4 M pieces, rounded to fp16 once each
+    assert ((dV[0].float() - total).abs() <= 2e-3 * total).all() and (dV[1:] == 0).all()
+    assert (d_el.abs() <= 1e-3).all()
+    hgnn.hgnn_plan_destroy(p)
+    hgnn.hgnn_plan_destroy(pt)
