@@ -244,18 +244,20 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   Soft<SAVE> t;  // z and zm: this lane's edges only, until the end
   for (pos_t k = w.beg; k < w.end; k += w.step) {
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
+    const int n = int(end - k);
     wave_sync();  // the previous round has been read
     {
+      const int left = n - own;  // entries of this lane's run
       int c[Rd::E];
-      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, left, c);
 #pragma unroll
-      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], m < left);
 #pragma unroll
       for (int m = 0; m < Rd::E; m += 4)
         *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
     }
     wave_sync();
-    for (int q = 0; k + q < end; q += 8) {
+    for (int q = 0; q < n; q += 8) {
       int h8[8];
       const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
 #pragma unroll
       for (int j = 0; j < Ht::NS; ++j) {
         const float e = s[j] + el;
-        s[j] = k + q + j * RS + edge < end ? e : -INFINITY;
+        s[j] = q + j * RS + edge < n ? e : -INFINITY;
         const float lk = s[j] > 0.f ? s[j] : a.slope * s[j];
         above |= lk > t.m + kSlack;
       }

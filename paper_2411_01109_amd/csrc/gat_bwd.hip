@@ -120,29 +120,31 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   const int edge = Ht::own_edge(l);
   for (pos_t k = w.beg; k < w.end; k += w.step) {
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
+    const int n = int(end - k);
     wave_sync();  // the previous round has been read
     {
+      const int left = n - own;  // entries of this lane's run
       int c[Rd::E];
-      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, left, c);
       if (NEAR) {
 #pragma unroll
         for (int m = 0; m < Rd::E; m += 4)
           *reinterpret_cast<int4_t*>(s_col + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
       }
 #pragma unroll
-      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], m < left);
 #pragma unroll
       for (int m = 0; m < Rd::E; m += 4)
         *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
     }
     wave_sync();
-    for (int q = 0; k + q < end; q += 8) {
+    for (int q = 0; q < n; q += 8) {
       float4 dv[Ht::NS];
       float es[Ht::NS];
       bool in[Ht::NS];
 #pragma unroll
       for (int j = 0; j < Ht::NS; ++j) {
-        in[j] = k + q + j * RS + edge < end;
+        in[j] = q + j * RS + edge < n;
         const int c = in[j] ? s_col[q + j * RS + edge] : 0;
         if (VEC) dv[j] = a.vtab[int64_t(c) * a.H + head];
         else es[j] = a.er[int64_t(c) * a.H + head];

@@ -197,18 +197,20 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
   const int edge = Ht::own_edge(l);
   for (pos_t k = w.beg; k < w.end; k += w.step) {
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
+    const int n = int(end - k);
     wave_sync();  // the previous round has been read
     {
+      const int left = n - own;  // entries of this lane's run
       int c[Rd::E];
-      load_cols<Rd::E>(v, a.col, false, w.block, k + own, end, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k + own, left, c);
 #pragma unroll
-      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], k + own + m < end);
+      for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], m < left);
 #pragma unroll
       for (int m = 0; m < Rd::E; m += 4)
         *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
     }
     wave_sync();
-    for (int q = 0; k + q < end; q += 8) {
+    for (int q = 0; q < n; q += 8) {
       int h8[8];
       const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll
@@ -238,13 +240,13 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
       }
     }
     wave_sync();
-    const int n = int(end - k) * a.H;
+    const int nout = n * a.H;
     half_t* dst = a.out + (int64_t(k) + shift) * a.H;
-    for (int j = 4 * l; j < n; j += 4 * L) {
-      if (j + 4 <= n) {
+    for (int j = 4 * l; j < nout; j += 4 * L) {
+      if (j + 4 <= nout) {
         __builtin_memcpy(dst + j, __builtin_assume_aligned(s_out + j, 8), 8);
       } else {
-        for (int i = j; i < n; ++i) dst[i] = s_out[i];
+        for (int i = j; i < nout; ++i) dst[i] = s_out[i];
       }
     }
   }

@@ -588,25 +588,27 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (pos_t k = w.beg; k < w.end; k += w.step) {
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
+    const int n = int(end - k);
     const pos_t i0 = k + own;
+    const int left = n - own;  // entries of this lane's run
     wave_sync();  // the previous round has been read
     {
       int c[E], e[E];
       hv_t wv[E];
       float cs[E];
-      load_cols<E>(v, a.col, nt, w.block, i0, end, c);
+      load_cols<E>(v, a.col, nt, w.block, i0, left, c);
       if (MAPPED) {
-        if (nt) load_run<E, true>(a.eid, i0, end, e);
-        else load_run<E, false>(a.eid, i0, end, e);
+        if (nt) load_run<E, true>(a.eid, i0, left, e);
+        else load_run<E, false>(a.eid, i0, left, e);
       }
       if (WM != 0 && HV > 0) {
-        if (!MAPPED && (WM == 1 || a.w) && i0 + E <= end) {
+        if (!MAPPED && (WM == 1 || a.w) && left >= E) {
           __builtin_memcpy(wv, a.w + int64_t(i0 + shift) * NV, sizeof(wv));
         } else {
 #pragma unroll
           for (int m = 0; m < E; ++m) {
             wv[m] = hv_t(half_t(0));
-            if (i0 + m < end) {
+            if (m < left) {
               if (WM == 1 || a.w) wv[m] = *reinterpret_cast<const hv_t*>(a.w + int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * NV);
               else wv[m] = hv_t(half_t(1));
             }
@@ -616,10 +618,10 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         cs[m] = 0.f;
-        if (WM == 2 && i0 + m < end) cs[m] = a.col_scale[c[m]];
+        if (WM == 2 && m < left) cs[m] = a.col_scale[c[m]];
       }
 #pragma unroll
-      for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], i0 + m < end);
+      for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], m < left);
 #pragma unroll
       for (int m = 0; m < E; m += 4) *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
       if (WM == 1 && HV > 0) {
@@ -629,13 +631,13 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
           for (int h = 0; h < H; ++h) {
             float x = 0.f;
             if (HV > 0) x = float(wv[m][h < NV ? h : 0]) * (WM == 2 ? cs[m] : 1.f);
-            else if (i0 + m < end) x = (a.w ? float(a.w[int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
+            else if (m < left) x = (a.w ? float(a.w[int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
             s_val[(own + m) * H + h] = factor_t(x);
           }
       }
     }
     wave_sync();
-    for (int q = 0; k + q < end; q += 8) {
+    for (int q = 0; q < n; q += 8) {
       int h8[8];
       const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll

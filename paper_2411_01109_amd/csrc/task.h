@@ -63,18 +63,18 @@ struct Round {
   static constexpr int PITCH = R + 4;               // ints per group in the handle table
 };
 
-// v[m] = p[i0 + m] for the entries below end; the others are 0
+// v[m] = p[i0 + m] for the first `left` entries (left may be negative); the others are 0
 template <int E, bool NT>
-__device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, pos_t end, int (&v)[E]) {
+__device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, int left, int (&v)[E]) {
   const int* q = p + i0;
-  if (i0 + E <= end) {
+  if (left >= E) {
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = NT ? __builtin_nontemporal_load(q + m) : q[m];
   } else {
 #pragma unroll
     for (int m = 0; m < E; ++m) {
       v[m] = 0;
-      if (i0 + m < end) v[m] = q[m];
+      if (m < left) v[m] = q[m];
     }
   }
 }
@@ -167,11 +167,11 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these
 // passes draw from HBM, and a gather waits behind it (114 M non-zeros x 64 in eight blocks: 0.81 -> 0.76 ms).
 template <int E>
-__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, pos_t end, int (&c)[E]) {
+__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, int left, int (&c)[E]) {
   if (v.col16) {
     const uint16_t* q = v.col16 + i0;
     const int first = block * v.width;
-    if (i0 + E <= end) {
+    if (left >= E) {
       uint16_t t[E];
       __builtin_memcpy(t, q, sizeof(t));
 #pragma unroll
@@ -180,13 +180,13 @@ __device__ __forceinline__ void load_cols(const TaskView& v, const int* __restri
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         c[m] = first;
-        if (i0 + m < end) c[m] += int(q[m]);
+        if (m < left) c[m] += int(q[m]);
       }
     }
     return;
   }
-  if (nt) load_run<E, true>(col, i0, end, c);
-  else load_run<E, false>(col, i0, end, c);
+  if (nt) load_run<E, true>(col, i0, left, c);
+  else load_run<E, false>(col, i0, left, c);
 }
 
 // A table of rows of ld halves.  NEAR: its bytes stay below 2^32 - 8192, rows are read through a buffer descriptor whose
