@@ -386,18 +386,19 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
   }
 }
 
-// Every row of the graph in one launch: first the chunks of the long rows (n_chunks workgroups), then the wave-per-row tier
-// (wave_wgs workgroups), then the sub-wave teams.  The three used to be launches of their own, each with a tail in which
-// the chip drained: 5.5 M non-zeros x 4 heads, forward 75 -> 63 us with the follow-up, backward 74 -> 56, sums through a map 87 -> 80 + 5.
+// Every row of the graph in one launch: the wave-per-row tier (wave_wgs workgroups), the sub-wave teams, then the chunks of the
+// long rows (n_chunks workgroups).  As launches of their own each has a tail in which the chip drains: 5.5 M non-zeros x 4
+// heads, forward with its follow-up 70 -> 57 us, backward 61 -> 45, sums 32 -> 23.  The chunks come last because the follow-up
+// reads them again while the caches still hold them (114 M non-zeros, one head: forward 189 us with the chunks first, 184
+// last, 179 in launches of their own; backward 210, 201, 207).
 template <int OP, int LR, int H>
 __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, HubChunks c, int n_chunks, int wave_wgs) {
   constexpr int W = kHubThreads / kWave;
-  int wg = int(blockIdx.x);
-  if (wg < n_chunks) {
-    edge_hub_partial<OP, H>(a, c, wg);
+  const int wg = int(blockIdx.x), row_wgs = int(gridDim.x) - n_chunks;
+  if (wg >= row_wgs) {
+    edge_hub_partial<OP, H>(a, c, wg - row_wgs);
     return;
   }
-  wg -= n_chunks;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (wg < wave_wgs) {
     int64_t row = int64_t(wg) * W + wave;
