@@ -349,6 +349,7 @@ struct hgnn_task_sec {  // the pieces of one column block (or of the whole graph
 };
 struct hgnn_row_tasks {
   int32_t nb = 0;
+  int64_t nnz = 0;
   int4* task = nullptr;
   int32_t* zrow = nullptr;
   int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
@@ -465,6 +466,7 @@ struct TaskSource {
   const int32_t* rowptr;  // [nb][nrows+1], every block's offsets from 0
   const int32_t* first;   // device, [nb] first non-zero of every block, or nullptr (one block)
   int32_t nrows, nb, S, group_max;
+  int64_t nnz;
 };
 // Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
 // reductions across lane groups (2.1 M non-zeros x 128: 32 is 3 % better than 64; 62 M x 128: 128 is 1 % better); the pieces of

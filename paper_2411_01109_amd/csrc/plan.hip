@@ -371,7 +371,7 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, b
   if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
   row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
   HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
-  const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz)};
+  const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz), g->nnz};
   TaskCounts tc(s);
   if (!sub) {
     const hgnn_status ts = task_count(tq, tc, s);

@@ -621,7 +621,7 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
       a.col = p->bcol;
       a.delta = p->bdelta;
     }
-    const TaskView v = task_view(t, kWave / L, 128, false);
+    const TaskView v = task_view(t, kWave / L, false);
     const int waves = v.first_wave[t->nb];
     if (waves > 0) {
       if (near_table(g->ncols, ldv)) launch_dot_tasks<true>(L, LH, masked, unsigned(waves), s, a, v);

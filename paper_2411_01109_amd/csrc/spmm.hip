@@ -1367,10 +1367,8 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
   const int L = pow2_at_least((a.F + 7) / 8), G = kWave / L;
   a.staging = reinterpret_cast<half_t*>(t->staging);
   a.stage_ld = p->max_F;
-  // edge values behind a map: the slots of a column's non-zeros are consecutive over the rows, so the waves of an XCD
-  // stay on one range of rows for longer
   const bool mapped = wm != 0 && a.w && a.eid;
-  const TaskView v = task_view(t, G, mapped ? 512 : 128);
+  const TaskView v = task_view(t, G);
   const int waves = v.first_wave[t->nb];
   if (a.atomic_y && v.n_split > 0) {
     launch_zero_split(L, s, a, v);
@@ -1426,13 +1424,13 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
 // row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.79 -> 1.25 ms together.
 static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, hipStream_t s) {
   const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
-  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz)};
+  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz};
   const hgnn_status st = task_build_in(q, t, s);
   if (st != HGNN_OK) return st;
   const int L = pow2_at_least((a.F + 7) / 8);
   const bool mapped = a.w && a.eid;
   int64_t grid = 0;
-  const TaskView v = task_view(t, q, g->nnz, kWave / L, mapped ? 512 : 128, &grid);
+  const TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
   a.staging = reinterpret_cast<half_t*>(t.staging);
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;

@@ -10,6 +10,10 @@ namespace hgnn {
 
 constexpr int kMaxTaskBlocks = 64;
 constexpr int kZeroTurns = 8;  // turns of G empty rows that a wave stores
+constexpr int64_t kMixNnz = int64_t(4) << 20;  // see TaskView::mix
+// Waves in a row on one XCD.  31 M non-zeros, one head of 64, 16 / 128 / 512 / 2048 waves: weighted SpMM 383, 369, 362, 363 us, SDDMM
+// 367, 353, 349, 350, row sums through the map 334, 320, 320, 334; 114 M, SpMM through the map 2149, 1790, 1789, 1790.
+constexpr int kTaskChunk = 512;
 
 struct TaskView {
   const int4_t* task;
@@ -22,13 +26,20 @@ struct TaskView {
   int n_split, nb;
   // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
   // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
-  // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms).
+  // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms with chunks of 128).
   int chunk;
   int first_wave[kMaxTaskBlocks + 1];  // for the lane groups of this launch: waves before each block, then all of them
+  // Whole-wave pieces and waves of lane-group pieces go through the rows side by side: of the groups of eight waves (one per
+  // XCD) of a block every 2^32 / mix-th takes the former.  One kind after the other (mix = 0), the second sweeps the edge
+  // tensors and the popular rows of the table again when the caches have lost them (31 M non-zeros: row sums through the map 340
+  // -> 320 us, weighted SpMM 406 -> 396, SDDMM 415 -> 393, attention forward 403 -> 377; 62 M x 128, SpMM through the map 2.81 ->
+  // 2.76 ms).  Small graphs stay in the caches and end on long pieces that way (2.1 M, SDDMM 41.7 -> 45.1 us), plan-free calls, whose
+  // numbers are on the device, gain nothing.
+  uint32_t mix[kMaxTaskBlocks];
 };
 
 // host: the launch shape of tasks t for G lane groups per wave; zeros = false leaves the empty rows out
-inline TaskView task_view(const hgnn_row_tasks* t, int G, int chunk = 128, bool zeros = true) {
+inline TaskView task_view(const hgnn_row_tasks* t, int G, bool zeros = true) {
   TaskView v{};
   v.task = reinterpret_cast<const int4_t*>(t->task);
   v.zrow = t->zrow;
@@ -43,10 +54,12 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, int chunk = 128, bool 
     const hgnn_task_sec& s = t->host[size_t(b)];
     n = (n + 7) & ~int64_t(7);
     v.first_wave[b] = int(n);
+    const int64_t w8 = ceil_div(s.nw, 8), g8 = ceil_div(ceil_div(s.ng, G), 8);
+    v.mix[b] = t->nnz > kMixNnz && w8 > 0 && g8 > 0 ? uint32_t(((w8 << 32) + w8 + g8 - 1) / (w8 + g8)) : 0;
     n += ((s.nw + 7) & ~7) + ((ceil_div(s.ng, G) + 7) & ~int64_t(7)) + (zeros ? ceil_div(s.nz, int64_t(G) * kZeroTurns) : 0);
   }
   v.first_wave[t->nb] = int(n);
-  v.chunk = chunk;
+  v.chunk = kTaskChunk;
   while (v.chunk > 1 && int64_t(v.chunk) * 64 * t->nb > n) v.chunk >>= 1;  // eight chunks per XCD and block at least
   return v;
 }
@@ -80,7 +93,7 @@ __device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, in
 }
 
 // the same for tasks whose numbers are on the device; *grid = workgroups to launch
-inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz, int G, int chunk, int64_t* grid) {
+inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz, int G, int64_t* grid) {
   TaskView v{};
   v.task = reinterpret_cast<const int4_t*>(t.task);
   v.zrow = t.zrow;
@@ -90,7 +103,7 @@ inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz
   v.n_split = int(nnz / q.S + 1);
   v.nb = 1;
   const int64_t n = nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
-  v.chunk = chunk;
+  v.chunk = kTaskChunk;
   while (v.chunk > 1 && int64_t(v.chunk) * 64 > n) v.chunk >>= 1;
   constexpr int64_t kMostWaves = 65536;  // beyond this the waves take several tasks each
   *grid = n < kMostWaves ? (n + 7) / 8 * 8 : kMostWaves;
@@ -116,7 +129,8 @@ struct TaskWave {
   int row, slot;    // row -1: no piece for this lane group
 };
 
-// wid is the same on all lanes of the wave; g = lane / L
+// wid is the same on all lanes of the wave; g = lane / L.  Everything up to the task is scalar; a choice between two addresses to
+// load from would turn all of it into vector code (5.5 M non-zeros, SDDMM 58 -> 62 us, attention forward 82 -> 87).
 template <int L>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
   constexpr int G = kWave / L;
@@ -127,17 +141,27 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   int i = wid - v.first_wave[b];
   w.block = b;
   w.first = s.first;
-  w.whole = i < s.nw;
+  w.whole = false;
   w.zrow = v.zrow + s.z_off;
   w.z0 = w.z1 = 0;
   int4_t t = {0, 0, -1, -1};
-  if (w.whole) {
-    t = v.task[s.w_off + i];
+  // sections begin at multiples of eight: i & 7 is the XCD
+  const int nw = (s.nw + 7) & ~7, gw = int(((pos_t(s.ng) + G - 1) / G + 7) & ~7u);
+  const uint32_t mix = v.mix[b];
+  bool wh = i < nw;                        // a whole-wave piece
+  pos_t before = pos_t(wh ? i : nw) >> 3;  // groups of eight waves before this one that take those
+  if (mix && i < nw + gw) {
+    const pos_t u = pos_t(i) >> 3;
+    before = pos_t((uint64_t(u) * mix) >> 32);
+    wh = pos_t((uint64_t(u + 1) * mix) >> 32) > before;
+  }
+  if (wh) {
+    const int k = int(before * 8) + (i & 7);
+    w.whole = k < s.nw;
+    if (w.whole) t = v.task[s.w_off + k];
   } else {
-    i -= (s.nw + 7) & ~7;  // sections begin at multiples of eight: i & 7 is the XCD
-    const int gw = int(((pos_t(s.ng) + G - 1) / G + 7) & ~7u);
-    if (i < 0) {  // between two sections: nothing
-    } else if (i < gw) {
+    i -= int(before * 8);
+    if (i < gw) {
       const int panel = 8 * v.chunk, full = gw / panel * panel;
       if (i < full) {
         const int p = i / panel * panel, j = i - p;

@@ -251,6 +251,7 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
   if (c.mail.data) tot = *c.totals;
   else HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
   t->nb = q.nb;
+  t->nnz = q.nnz;
   t->n_split = tot.n_split;
   t->n_slots = tot.n_slots;
   t->host.resize(size_t(q.nb));
@@ -279,7 +280,7 @@ hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
   for (int b = 0; b < p->nb; ++b) host[size_t(b)] = int32_t(p->boff[size_t(b)]);
   HGNN_HIP(first.alloc(sizeof(int32_t) * size_t(p->nb)));
   HGNN_HIP(hipMemcpyAsync(first.p, host.data(), sizeof(int32_t) * size_t(p->nb), hipMemcpyHostToDevice, s));
-  const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks};
+  const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks, p->nnz};
   TaskCounts c(s);
   hgnn_status st = task_count(q, c, s);
   if (st != HGNN_OK) return st;

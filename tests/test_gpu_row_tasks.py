@@ -161,3 +161,29 @@ def test_positions_up_to_the_last_one(hgnn, dev):
     assert (d_el.abs() <= 1e-3).all()
     hgnn.hgnn_plan_destroy(p)
     hgnn.hgnn_plan_destroy(pt)
+
+
+def test_both_kinds_of_pieces_side_by_side(hgnn, dev):
+    """A graph beyond the size from which whole-wave and lane-group pieces alternate: every piece is taken once, for every number
+    of lane groups per wave, with one kind rare."""
+    V = 30000
+    r = np.random.default_rng(4)
+    for long_rows in (5, 9000):
+        deg = r.integers(0, 300, size=V)  # pieces up to 256, lane groups up to 32
+        deg[deg > 32] //= 9
+        deg[r.permutation(V)[:long_rows]] = 4_300_000 // long_rows if long_rows > 100 else 880_000
+        rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+        assert rowptr[-1] > 4 << 20
+        g = hgnn.Csr(up(rowptr, dev), torch.zeros(int(rowptr[-1]), dtype=torch.int32, device=dev), ncols=8)
+        w = torch.full((g.nnz, 1), 2.0 ** -10, dtype=torch.float16, device=dev)
+        for F in (8, 32, 64, 128, 512):
+            X = torch.zeros((8, F), dtype=torch.float16, device=dev)
+            X[0] = 1
+            p = hgnn.hgnn_plan_create(g, 256, F, 1)
+            Y = torch.full((V, F), 3.0, dtype=torch.float16, device=dev)
+            hgnn.hgnn_spmm_discretized(p, g, w, 1, X, Y)
+            got = down(Y).astype(np.float64)
+            want = deg * 2.0 ** -10
+            assert np.abs(got - want[:, None]).max() <= 2.0 ** -11 * want.max(), (long_rows, F)  # pieces are exact, one rounding
+            assert np.array_equal(got[want <= 2], np.broadcast_to(want[:, None], got.shape)[want <= 2]), (long_rows, F)
+            hgnn.hgnn_plan_destroy(p)
