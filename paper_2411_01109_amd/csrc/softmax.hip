@@ -386,19 +386,21 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
   }
 }
 
-// Every row of the graph in one launch: the wave-per-row tier (wave_wgs workgroups), the sub-wave teams, then the chunks of the
-// long rows (n_chunks workgroups).  As launches of their own each has a tail in which the chip drains: 5.5 M non-zeros x 4
-// heads, forward with its follow-up 70 -> 57 us, backward 61 -> 45, sums 32 -> 23.  The chunks come last because the follow-up
-// reads them again while the caches still hold them (114 M non-zeros, one head: forward 189 us with the chunks first, 184
-// last, 179 in launches of their own; backward 210, 201, 207).
+// Every row of the graph in one launch: the wave-per-row tier (wave_wgs workgroups), then the sub-wave teams, and the chunks of
+// the long rows (n_chunks workgroups) after or before them.  As launches of their own each has a tail in which the chip drains: 5.5 M non-zeros x 4
+// heads, forward with its follow-up 70 -> 57 us, backward 61 -> 45, sums 32 -> 22.5.  The softmax takes the chunks last because
+// its follow-up reads them again while the caches still hold them (114 M non-zeros, one head: forward 189 us with the chunks
+// first, 184 last, 179 in launches of their own; backward 210, 201, 207); the sums take them first (23.3 us last).
 template <int OP, int LR, int H>
 __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, HubChunks c, int n_chunks, int wave_wgs) {
   constexpr int W = kHubThreads / kWave;
-  const int wg = int(blockIdx.x), row_wgs = int(gridDim.x) - n_chunks;
-  if (wg >= row_wgs) {
-    edge_hub_partial<OP, H>(a, c, wg - row_wgs);
+  int wg = int(blockIdx.x);
+  const int first_chunk = OP == kSum ? 0 : int(gridDim.x) - n_chunks;
+  if (wg >= first_chunk && wg < first_chunk + n_chunks) {
+    edge_hub_partial<OP, H>(a, c, wg - first_chunk);
     return;
   }
+  if (OP == kSum) wg -= n_chunks;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (wg < wave_wgs) {
     int64_t row = int64_t(wg) * W + wave;
