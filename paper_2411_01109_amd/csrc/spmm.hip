@@ -1252,12 +1252,12 @@ static hgnn_status run_vgroups(const hgnn_plan* p, SpmmArgs a, int ncols, bool a
 
 // the vector forms of several heads only where they are used in earnest: edge values alone, a table below 4 GB
 template <int L, bool NEAR>
-static void launch_tasks_l(int wm, bool mapped, unsigned waves, hipStream_t s, const SpmmArgs& a, const TaskView& v,
-                           int ncols) {
+static void launch_tasks_l(int wm, bool mapped, unsigned waves, size_t least_lds, hipStream_t s, const SpmmArgs& a,
+                           const TaskView& v, int ncols) {
   const dim3 grid(waves);
 #define HGNN_TASKS(WM, MAPPED, HV)                                                                                          \
   do {                                                                                                                      \
-    const size_t lds = TaskLds<L, WM, HV>::bytes(a.H);                                                                      \
+    const size_t lds = std::max(TaskLds<L, WM, HV>::bytes(a.H), least_lds);                                                                 \
     if constexpr (WM < 2) {                                                                                                 \
       if (v.totals) {                                                                                                       \
         spmm_task_kernel<L, WM, NEAR, MAPPED, HV, true><<<grid, kWave, lds, s>>>(a, v, ncols);                              \
@@ -1315,17 +1315,39 @@ static void launch_tasks_l(int wm, bool mapped, unsigned waves, hipStream_t s, c
 }
 
 template <bool NEAR>
-static void launch_tasks(int L, int wm, bool mapped, unsigned waves, hipStream_t s, const SpmmArgs& a, const TaskView& v,
-                         int ncols) {
+static void launch_tasks(int L, int wm, bool mapped, unsigned waves, size_t least_lds, hipStream_t s, const SpmmArgs& a,
+                         const TaskView& v, int ncols) {
   switch (L) {
-    case 1: launch_tasks_l<1, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    case 2: launch_tasks_l<2, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    case 4: launch_tasks_l<4, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    case 8: launch_tasks_l<8, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    case 16: launch_tasks_l<16, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    case 32: launch_tasks_l<32, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
-    default: launch_tasks_l<64, NEAR>(wm, mapped, waves, s, a, v, ncols); break;
+    case 1: launch_tasks_l<1, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    case 2: launch_tasks_l<2, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    case 4: launch_tasks_l<4, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    case 8: launch_tasks_l<8, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    case 16: launch_tasks_l<16, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    case 32: launch_tasks_l<32, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
+    default: launch_tasks_l<64, NEAR>(wm, mapped, waves, least_lds, s, a, v, ncols); break;
   }
+}
+
+// Every wave has eight gathers a lane group in flight.  Where the gathered lines miss the L2s, 28 to 32 waves per compute unit ask
+// for more than an L2 holds (32 compute units x 32 waves x 32 rows of 256 bytes: 8.4 MB), and popular rows and shared lines of the
+// edge values are gone before the next wave wants them.  LDS that nobody uses then keeps waves out.  us, by waves per compute unit:
+//   edge values behind a map: non-zeros x heads          28     20     16     14     12
+//     2.1 M x 1 (4 MB, as an L2), 128 features           62.4   62.5   64.3   74.5   78.5
+//     5.5 M x 1 (11 MB), 64 features                      104    102    102    107    111
+//     5.5 M x 4 (44 MB)                                   130    123    122    127    132
+//     31 M x 1 (62 MB)                                    816    796    791    773    765
+//     31 M x 4 (248 MB)                                   911    885    878    848    841
+//     114 M x 1 in blocks (228 MB)                       1793   1709   1688      -   1676
+//   unmapped: table beside a last-level cache of 256 MB
+//     77 MB, 31 M non-zeros, no edge values (154 MB)      371    377    388    445    469
+//     307 MB, 62 M, by degrees                            901    871    852      -    967
+//     614 MB, 62 M, by degrees                           1849   1835   1823      -   1880
+//     614 MB, 62 M, edge values                          1800   1788   1777      -   1730
+// (tables that fit that cache gain or lose either way, so they are left alone).
+static size_t least_task_lds(bool mapped, int64_t edge_bytes, int64_t table_bytes, int64_t l2, int64_t llc) {
+  constexpr size_t kLds = 160 * 1024;  // of a compute unit
+  if (mapped && edge_bytes > l2) return edge_bytes > 12 * l2 ? kLds / 14 / 16 * 16 : kLds / 16;
+  return !mapped && table_bytes > llc ? kLds / 16 : 0;
 }
 
 static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
@@ -1375,8 +1397,9 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
     HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
   if (waves > 0) {
-    if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), s, a, v, ncols);
-    else launch_tasks<false>(L, wm, mapped, unsigned(waves), s, a, v, ncols);
+    const size_t least = least_task_lds(mapped, a.nnz * a.H * 2, int64_t(ncols) * a.ldx * 2, p->l2_bytes, p->llc_bytes);
+    if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
+    else launch_tasks<false>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     HGNN_LAUNCH_CHECK("spmm_task_kernel");
   }
   if (v.n_split > 0 && !a.atomic_y) {
@@ -1435,8 +1458,11 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;
   const int wm = a.w ? 1 : 0;
-  if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), s, a, v, g->ncols);
-  else launch_tasks<false>(L, wm, mapped, unsigned(grid), s, a, v, g->ncols);
+  int64_t l2 = 0, llc = 0;
+  device_cache_bytes(&l2, &llc);
+  const size_t least = least_task_lds(mapped, a.nnz * a.H * 2, int64_t(g->ncols) * a.ldx * 2, l2, llc);
+  if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
+  else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");
   launch_task_finish(L, s, a, v);
   HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
