@@ -222,7 +222,6 @@ struct WgradArgs {
 };
 
 constexpr int kWgradRows = 32;  // rows of X and dY per step
-constexpr int kWgradTile = 64;  // a wave owns a 64 x 64 block of dW
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4_t lds_short4_t;
@@ -529,9 +528,8 @@ static int wgrad_parts(int K, int F) {
   return q;
 }
 
-constexpr int kSumGroup = 32;  // the workspace bounds hold parts + parts / kSumGroup results
 constexpr int kCus = 256;       // compute units of an MI355X
-constexpr int kFeatGradBlocks = 1024;
+constexpr int kFeatGradBlocks = 512;  // most workgroups of the attention gradients, a partial result each
 
 }  // namespace hgnn
 
@@ -619,8 +617,7 @@ hgnn_status hgnn_linear_padded(int64_t n, int32_t K, int32_t KW, int32_t F, cons
 
 size_t hgnn_linear_wgrad_workspace(int32_t K, int32_t F) {
   if (K <= 0 || F <= 0) return 0;
-  const int parts = wgrad_parts(K, F);
-  return size_t(parts + parts / kSumGroup) * size_t(K) * size_t(F) * sizeof(float);
+  return size_t(wgrad_parts(K, F)) * size_t(K) * size_t(F) * sizeof(float);
 }
 
 hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* X, int64_t ldx, const hgnn_half* dY,
@@ -674,7 +671,7 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
 
 size_t hgnn_gat_feature_grad_workspace(int32_t H, int32_t D) {
   if (H <= 0 || D <= 0) return 0;
-  return size_t(kFeatGradBlocks + kFeatGradBlocks / kSumGroup) * 2 * size_t(H) * size_t(D) * sizeof(float);
+  return size_t(kFeatGradBlocks) * 2 * size_t(H) * size_t(D) * sizeof(float);
 }
 
 hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_half* dV, int64_t lddv, const hgnn_half* d_el,
@@ -702,7 +699,7 @@ hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_ha
                  reinterpret_cast<const half_t*>(hfeat), ldh, reinterpret_cast<half_t*>(dh), lddh, part};
   const int LP = pow2_at_least(F / 8);
   // enough workgroups for the chip, no more than a pass of rows each: every one leaves a partial result
-  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kFeatGradBlocks / 2, ceil_div(n, kBlock / LP)));
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kFeatGradBlocks, ceil_div(n, kBlock / LP)));
   dim3 grid{unsigned(blocks)};
   switch (LP) {
     case 1: gat_feature_grad_kernel<1><<<grid, kBlock, 0, s>>>(a); break;
