@@ -6,10 +6,12 @@
 // as a CSR of its own, the non-zeros whose column lies in [b*width, (b+1)*width).  Because columns
 // ascend inside a row, a block's share of a row is a contiguous piece of that row.  The SpMM then
 // runs block after block -- all compute units gather from the same slice of the table at the same
-// time, which the L2s can hold -- each block reducing its pieces with the usual segment kernels
-// into a per-block partial output, and one pass adds the nb partials of every row (no atomics).
+// time, which the L2s can hold -- over the row tasks of every block into a per-block partial output,
+// and one pass adds the nb partials of every row (no atomics).
 // One-off set-up code; rocPRIM's device scan is the library step.
 #include <string.h>
+
+#include <algorithm>
 
 #include <rocprim/device/device_scan.hpp>
 
@@ -74,12 +76,12 @@ __global__ void block_fill_kernel(hgnn_csr g, const int* __restrict__ cut, const
   const int c = g.col[k];
   const int b = c / width;
   const int64_t dest = int64_t(goff[int64_t(b) * g.nrows + r]) + (k - cut[int64_t(r) * (nb + 1) + b]);
-  bcol[dest] = c;
   if (bcol16) bcol16[dest] = uint16_t(c - b * width);
-  beid[dest] = g.eid ? g.eid[k] : int(k);
+  else bcol[dest] = c;
+  if (beid) beid[dest] = g.eid[k];
 }
 
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, SetupStream& s) {
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, SetupStream& s) {
   const int V = g->nrows;
   const int64_t E = g->nnz;
   const int width = int(ceil_div(g->ncols, nb));
@@ -89,15 +91,13 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks
   DevTemp cut_buf(s), cnt_buf(s), goff_buf(s), tmp(s);
   size_t tmp_bytes = 0;
   const size_t n_flat = size_t(nb) * size_t(V);
-  hgnn_status rc = HGNN_OK;
   hipError_t e = cut_buf.alloc(sizeof(int) * size_t(V) * size_t(nb + 1));
   if (e == hipSuccess) e = cnt_buf.alloc(sizeof(int) * n_flat);
   if (e == hipSuccess) e = goff_buf.alloc(sizeof(int) * n_flat);
   int *const cut = cut_buf.as<int>(), *const cnt = cnt_buf.as<int>(), *const goff = goff_buf.as<int>();
   if (e == hipSuccess) e = dev_malloc(&p->brp, sizeof(int) * size_t(nb) * (size_t(V) + 1));
-  if (e == hipSuccess) e = dev_malloc(&p->bcol, sizeof(int) * size_t(E));
-  if (e == hipSuccess && tasks && width <= 65536) e = dev_malloc(&p->bcol16, sizeof(uint16_t) * size_t(E));
-  if (e == hipSuccess) e = dev_malloc(&p->beid, sizeof(int) * size_t(E));
+  if (e == hipSuccess) e = width <= 65536 ? dev_malloc(&p->bcol16, sizeof(uint16_t) * size_t(E)) : dev_malloc(&p->bcol, sizeof(int) * size_t(E));
+  if (e == hipSuccess && g->eid) e = dev_malloc(&p->beid, sizeof(int) * size_t(E));
   // partial rows twice over and three scalars per row and head: the fused GAT pass that saves for its backward
   // leaves two vectors and (max, sum, masked sum) per block; row sums of edge tensors use one scalar
   if (e == hipSuccess) e = dev_malloc(&p->bstage, sizeof(hgnn_half) * 2 * n_flat * size_t(p->max_F));
@@ -127,51 +127,80 @@ hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks
   p->boff[size_t(nb)] = E;
   if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess)
-    rc = fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "build_col_blocks: %s", hipGetErrorString(e));
-  if (rc != HGNN_OK) return rc;
-  // a segment plan per block, over the block's own CSR
-  for (int b = 0; b < nb; ++b) {
-    hgnn_plan* q = new (std::nothrow) hgnn_plan();
-    if (!q) return fail(HGNN_ENOMEM, "build_col_blocks: host allocation failed");
-    p->sub.push_back(q);
-    q->nrows = V;
-    q->ncols = g->ncols;
-    q->nnz = p->boff[size_t(b) + 1] - p->boff[size_t(b)];
-    q->S = p->S;
-    q->nseg = ceil_div(q->nnz, q->S);
-    q->max_F = p->max_F;
-    q->max_H = p->max_H;
-    hgnn_csr view{V, g->ncols, q->nnz, p->brp + size_t(b) * (size_t(V) + 1), p->bcol + p->boff[size_t(b)], nullptr,
-                  p->beid + p->boff[size_t(b)]};
-    rc = plan_build_arrays(q, &view, s, true);
-    if (rc != HGNN_OK) return rc;
-  }
-  // the blocks' arrays in one device table
-  std::vector<hgnn_seg_block> desc{};
-  desc.resize(size_t(nb));
-  for (int b = 0; b < nb; ++b) {
-    const hgnn_plan* q = p->sub[size_t(b)];
-    hgnn_seg_block& d = desc[size_t(b)];
-    d.rowptr = p->brp + size_t(b) * (size_t(V) + 1);
-    d.col = p->bcol + p->boff[size_t(b)];
-    d.eid = p->beid + p->boff[size_t(b)];
-    d.delta = p->bdelta + size_t(b) * size_t(V);
-    d.seg_lo = q->seg_row_lo;
-    d.seg_hi = q->seg_row_hi;
-    d.staging = q->staging;
-    d.split_row = q->split_row;
-    d.split_lo = q->split_seg_lo;
-    d.split_hi = q->split_seg_hi;
-    d.nnz = q->nnz;
-    d.nseg = q->nseg;
-    d.n_split = q->n_split;
-    d.pad = 0;
-    d.stage_mz = q->stage_mz;
-  }
-  HGNN_HIP(dev_malloc(&p->bdesc, sizeof(hgnn_seg_block) * size_t(nb)));
-  HGNN_HIP(hipMemcpyAsync(p->bdesc, desc.data(), sizeof(hgnn_seg_block) * size_t(nb), hipMemcpyHostToDevice, s));
-  HGNN_HIP(s.wait());
+    return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "build_col_blocks: %s", hipGetErrorString(e));
   return HGNN_OK;
 }
 
+namespace {
+
+// the cut of a plan whose arrays are there, on the host, block by block
+struct HostBlock {
+  std::vector<int32_t> rowptr, col, slot;
+};
+
+hipError_t fetch_block(const hgnn_plan* c, int b, HostBlock& h) {
+  const int64_t off = c->boff[size_t(b)];
+  const size_t n = size_t(c->boff[size_t(b) + 1] - off), V = size_t(c->nrows);
+  std::vector<int32_t> delta(V);
+  std::vector<uint16_t> narrow;
+  h.rowptr.resize(V + 1);
+  h.col.resize(n);
+  h.slot.resize(n);
+  auto get = [](void* dst, const void* src, size_t bytes) { return bytes ? hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) : hipSuccess; };
+  hipError_t e = get(h.rowptr.data(), c->brp + size_t(b) * (V + 1), 4 * (V + 1));
+  if (c->bcol16) narrow.resize(n);
+  if (e == hipSuccess) e = c->bcol16 ? get(narrow.data(), c->bcol16 + off, 2 * n) : get(h.col.data(), c->bcol + off, 4 * n);
+  if (e == hipSuccess) e = c->beid ? get(h.slot.data(), c->beid + off, 4 * n) : get(delta.data(), c->bdelta + size_t(b) * V, 4 * V);
+  if (e != hipSuccess) return e;
+  for (size_t k = 0; k < narrow.size(); ++k) h.col[k] = b * c->block_width + int32_t(narrow[k]);
+  if (!c->beid)
+    for (size_t r = 0; r < V; ++r)
+      for (int32_t k = h.rowptr[r]; k < h.rowptr[r + 1]; ++k) h.slot[size_t(k)] = k + delta[r];
+  return hipSuccess;
+}
+
+}  // namespace
+
 }  // namespace hgnn
+
+using namespace hgnn;
+
+// A row's piece of block b is put together from the blocks of the cut that the plan holds: its own, or the finer one, whose
+// blocks need not end where this one does.
+extern "C" hgnn_status hgnn_plan_block_export(const hgnn_plan* p, int32_t b, int64_t* nnz_b, int32_t* rowptr_b, int32_t* col_b,
+                                              int32_t* eid_b, int32_t* seg_row_lo, int32_t* seg_row_hi) {
+  clear_error();
+  const char* who = "hgnn_plan_block_export";
+  HGNN_REQUIRE(p != nullptr, HGNN_EINVAL, "%s: plan is NULL", who);
+  HGNN_REQUIRE(p->nb > 1 && b >= 0 && b < p->nb, HGNN_EINVAL, "%s: block %d of %d", who, b, p->nb);
+  HGNN_HIP(hipDeviceSynchronize());
+  const hgnn_plan* c = p->brp ? p : p->fine;
+  const int64_t lo = int64_t(b) * p->block_width, hi = std::min<int64_t>(lo + p->block_width, p->ncols);
+  const size_t V = size_t(p->nrows);
+  std::vector<HostBlock> parts;
+  for (int f = int(lo / c->block_width); f < c->nb && int64_t(f) * c->block_width < hi; ++f) {
+    parts.emplace_back();
+    HGNN_HIP(fetch_block(c, f, parts.back()));
+  }
+  HostBlock out;
+  out.rowptr.assign(V + 1, 0);
+  for (size_t r = 0; r < V; ++r) {
+    for (const HostBlock& h : parts)
+      for (int32_t k = h.rowptr[r]; k < h.rowptr[r + 1]; ++k)
+        if (h.col[size_t(k)] >= lo && h.col[size_t(k)] < hi) {
+          out.col.push_back(h.col[size_t(k)]);
+          out.slot.push_back(h.slot[size_t(k)]);
+        }
+    out.rowptr[r + 1] = int32_t(out.col.size());
+  }
+  const int64_t n = int64_t(out.col.size());
+  if (nnz_b) *nnz_b = n;
+  if (rowptr_b) std::copy(out.rowptr.begin(), out.rowptr.end(), rowptr_b);
+  if (col_b) std::copy(out.col.begin(), out.col.end(), col_b);
+  if (eid_b) std::copy(out.slot.begin(), out.slot.end(), eid_b);
+  for (int64_t k = 0; k * p->S < n; ++k) {
+    if (seg_row_lo) seg_row_lo[k] = row_of_edge(out.rowptr.data(), p->nrows, k * p->S);
+    if (seg_row_hi) seg_row_hi[k] = row_of_edge(out.rowptr.data(), p->nrows, std::min<int64_t>((k + 1) * p->S, n) - 1);
+  }
+  return HGNN_OK;
+}

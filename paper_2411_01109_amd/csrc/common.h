@@ -182,30 +182,6 @@ __device__ __forceinline__ float head_sum1(float v, int LH) {
   return v;
 }
 
-// the same for four independent values at once (four chains in flight)
-__device__ __forceinline__ void head_sum4(float (&v)[4], int LH) {
-  if (LH >= 2) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = dpp_add<0xB1>(v[u]);
-  }
-  if (LH >= 4) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = dpp_add<0x4E>(v[u]);
-  }
-  if (LH >= 8) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = dpp_add<0x141>(v[u]);
-  }
-  if (LH >= 16) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = dpp_add<0x140>(v[u]);
-  }
-  for (int off = 16; off < LH; off <<= 1) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] += __shfl_xor(v[u], off);
-  }
-}
-
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 
@@ -263,25 +239,11 @@ __device__ __forceinline__ void seg_stage_cols(const int* __restrict__ col, int6
 
 template <bool BLOCK_SYNC = false>
 __device__ __forceinline__ void seg_stage_rows(int* s_row, int* s_blk, int lane, int per, int n, int row_lo, int row_hi,
-                                               const int* __restrict__ rowptr, int64_t e0, bool* open = nullptr) {
-  const int r0 = row_lo + 1 + lane;
-  int p0 = 0, q0 = 0, b_lo = 0, b_hi = 0;
-  if (open && n > 0) {  // a segment of the plan: row_lo <= row_hi are rows of the graph
-    const int rc = r0 <= row_hi ? r0 : row_lo;
-    p0 = rowptr[rc];
-    q0 = rowptr[rc + 1];
-    b_lo = rowptr[row_lo];
-    b_hi = rowptr[row_hi + 1];
-  }
+                                               const int* __restrict__ rowptr, int64_t e0) {
   for (int i = lane; i < kWave * per; i += kWave) s_row[i] = i == 0 ? row_lo : -1;
   if (BLOCK_SYNC) __syncthreads();
   else wave_sync();
-  if (open) {
-    if (r0 <= row_hi && q0 > p0) s_row[p0 - int(e0)] = r0;
-    open[0] = n > 0 && int64_t(b_lo) < e0;
-    open[1] = n > 0 && int64_t(b_hi) > e0 + n;
-  }
-  for (int r = open ? r0 + kWave : r0; r <= row_hi; r += kWave) {
+  for (int r = row_lo + 1 + lane; r <= row_hi; r += kWave) {
     const int p = rowptr[r], q = rowptr[r + 1];
     if (q > p) s_row[p - int(e0)] = r;
   }
@@ -316,23 +278,6 @@ __device__ __forceinline__ void seg_stage_rows(int* s_row, int* s_blk, int lane,
 }
 
 }  // namespace hgnn
-
-// One column block of a blocked plan as the kernels see it when all blocks run in one launch (device array in the plan).
-struct hgnn_seg_block {
-  const int32_t* rowptr;   // the block's own offset array [nrows+1]
-  const int32_t* col;
-  const int32_t* eid;      // slots of the creating graph's edge-id map (or CSR positions), block order
-  const int32_t* delta;    // [nrows] CSR position in the whole graph = block position + delta[row]
-  const int32_t* seg_lo;
-  const int32_t* seg_hi;
-  hgnn_half* staging;
-  const int32_t* split_row;
-  const int32_t* split_lo;
-  const int32_t* split_hi;
-  int64_t nnz, nseg;
-  int32_t n_split, pad;
-  float* stage_mz;         // scalars of the staged pieces of the fused GAT passes
-};
 
 // ---- row tasks of a plan (tasks.hip): the rows of a graph, or of its column blocks, as pieces of work for a wave ----
 // A piece of a row is at most S consecutive non-zeros (S = the plan's segment size); a row within S is one piece.  Pieces
@@ -381,7 +326,7 @@ struct hgnn_plan {
   int64_t l2_bytes = 0, llc_bytes = 0;  // cache sizes of the device the plan was built on (an XCD's L2, the cache behind the L2s)
   int32_t vec_halves = 8;  // halves a lane moves per feature load in the kernels that exist in several widths (8, 4 or 2)
   bool auto_blocks = false;  // the blocks were chosen by the automatic rule (col_blocks = 0): a call whose own table is small runs unblocked
-  bool block_eid = false;  // column blocks: built from a graph that carried an edge-id map (beid holds that map's slots)
+  bool block_eid = false;  // column blocks: built from a graph that carried an edge-id map (which beid then holds)
   int32_t* seg_row_lo = nullptr;    // [nseg]
   int32_t* seg_row_hi = nullptr;    // [nseg]
   int32_t* split_row = nullptr;     // [n_split]
@@ -397,22 +342,19 @@ struct hgnn_plan {
   int32_t* hub_chunk_count = nullptr;  // [n_hub_chunks] chunks of that row
   int32_t* big_first = nullptr;        // [n_big] slot of the first chunk of big_row[i]
   float* hub_part = nullptr;           // [n_hub_chunks][max_H][2] partial results
-  hgnn_half* staging = nullptr;     // [2][2*nseg][max_F] (second set: masked vectors of the saving GAT pass)
-  float* stage_mz = nullptr;        // [2*nseg][max_H][2] softmax (max, sum) of the staged pieces of the fused GAT pass, then [2*nseg][max_H] masked sums
   float* vscratch = nullptr;        // [(nrows + ncols) * max_H] fp32
   float* vtab = nullptr;            // [nrows][max_H][4] fp32 per-vertex (el, lse, t, -) of the fused GAT backward
   // column blocking of the SpMM (nb > 1): block b holds the non-zeros whose column lies in
-  // [b*block_width, (b+1)*block_width), stored block after block as a CSR of their own
+  // [b*block_width, (b+1)*block_width), stored block after block as a CSR of their own.  Where every pass takes the blocks of
+  // `fine`, this plan holds none of the arrays.
   int32_t nb = 1;
   int32_t block_width = 0;
   int32_t* brp = nullptr;           // [nb][nrows+1] offset arrays of the blocks
-  int32_t* bcol = nullptr;          // [nnz] column ids, block-major
-  uint16_t* bcol16 = nullptr;       // [nnz] the same less b*block_width, where the blocks' row tasks are used and 16 bits do
-  int32_t* beid = nullptr;          // [nnz] slot in the edge tensors of every blocked non-zero: the creating graph's eid, else its CSR position
-  int32_t* bdelta = nullptr;        // [nb][nrows] CSR position in the whole graph of a blocked non-zero = its block position + bdelta[b][row]
+  int32_t* bcol = nullptr;          // [nnz] column ids, block-major; or, where 16 bits do,
+  uint16_t* bcol16 = nullptr;       // [nnz] the same less b*block_width
+  int32_t* beid = nullptr;          // [nnz] the creating graph's edge-id map, block-major (block_eid)
+  int32_t* bdelta = nullptr;        // [nb][nrows] CSR position in the whole graph of a blocked non-zero = its position in the block + bdelta[b][row]
   std::vector<int64_t> boff;        // [nb+1] first non-zero of every block in bcol / beid
-  std::vector<hgnn_plan*> sub;      // [nb] segment plans of the blocks
-  hgnn_seg_block* bdesc = nullptr;  // [nb] the blocks' arrays, for kernels that walk all blocks in one launch
   hgnn_row_tasks* tasks = nullptr;   // of the whole graph
   hgnn_row_tasks* btasks = nullptr;  // of the column blocks (nb > 1; null where every pass takes those of `fine`)
   hgnn_plan* fine = nullptr;        // the same graph in twice the blocks (blocked arrays only); only where the automatic rule
@@ -456,8 +398,8 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
                       void* scratch, size_t scratch_bytes, bool one_sweep, hipStream_t s);
 void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, bool sub);
-hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, bool tasks, SetupStream& s);  // tasks: row tasks will walk them
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s);
+hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, SetupStream& s);  // p->nb > 1 from here
 // the cut whose blocks a pass walks; narrow: a pass that gathers from two tables at once or leaves no partial rows behind
 inline const hgnn_plan* walked_cut(const hgnn_plan* p, bool narrow) { return p->fine && (narrow || !p->btasks) ? p->fine : p; }
 constexpr int kSliceMaxCols = 16384;  // columns per slice: 8 bytes each fill 128 KB of the 160 KB of LDS a workgroup may hold

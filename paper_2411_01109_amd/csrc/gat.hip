@@ -28,11 +28,10 @@
 namespace hgnn {
 
 struct GatArgs {
-  const int* rowptr;
   const int* col;
   const half_t* X;  // column-side features [ncols][ldx]
   half_t* Y;        // [nrows][ldy]: the result, or (part_mz set) this block's normalised partial rows
-  int64_t ldx, ldy, nnz;
+  int64_t ldx, ldy;
   int nrows, F, H, D;
   float slope;
   const float* el;  // [nrows][H], or nullptr: formed per piece from the row's own features
@@ -579,13 +578,11 @@ static hgnn_status gat_forward_impl(const char* who, const hgnn_csr* g, const hg
   else st = gat_check(p, H, D, U, ldu, nullptr, ldv, a_l, a_r, who);
   if (st != HGNN_OK) return st;
   GatArgs a{};
-  a.rowptr = g->rowptr;
   a.col = g->col;
   a.X = reinterpret_cast<const half_t*>(Vt);
   a.Y = reinterpret_cast<half_t*>(out);
   a.ldx = ldv;
   a.ldy = ldo;
-  a.nnz = g->nnz;
   a.nrows = g->nrows;
   a.F = F;
   a.H = H;

@@ -18,12 +18,11 @@
 namespace hgnn {
 
 struct GatBwdArgs {
-  const int* rowptr;
   const int* col;
   const half_t* X;     // gathered, column-side vectors [ncols of this graph][ldx]
   const half_t* R;     // row-side vectors [nrows of this graph][ldr]
   half_t* Y;           // VEC kernels: [nrows][ldy] = sum over the row of alpha * X[col]
-  int64_t ldx, ldr, ldy, nnz;
+  int64_t ldx, ldr, ldy;
   int nrows, F, H, D;
   float slope;
   const float4* vtab;  // [destination vertex][H]: (el, lse, t, unused)
@@ -528,9 +527,7 @@ static hgnn_status gat_backward_impl(const char* who, const hgnn_csr* g, const h
   // transposed pass: rows j (sources), gathers dOut_i; dV_j and d_er_j
   if (gt->nrows > 0) {
     GatBwdArgs t = a;
-    t.rowptr = gt->rowptr;
     t.col = gt->col;
-    t.nnz = gt->nnz;
     t.nrows = gt->nrows;
     t.X = reinterpret_cast<const half_t*>(dOut);
     t.ldx = lddo;
@@ -545,9 +542,7 @@ static hgnn_status gat_backward_impl(const char* who, const hgnn_csr* g, const h
   // forward pass: rows i (destinations), gathers h_j; d_el_i only (already written above from the saved tensors)
   if (g->nrows > 0 && !saved) {
     GatBwdArgs f = a;
-    f.rowptr = g->rowptr;
     f.col = g->col;
-    f.nnz = g->nnz;
     f.nrows = g->nrows;
     f.X = reinterpret_cast<const half_t*>(Vt);
     f.ldx = ldv;

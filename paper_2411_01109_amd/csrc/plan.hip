@@ -227,7 +227,7 @@ __global__ void seg_rows_kernel(const int* __restrict__ rowptr, int nrows, int64
 // split: first and last edge of the row fall in different segments; big: longer than big_deg; mid: longer than mid_deg and
 // not big.  One pass counts the members of all three per workgroup (and the chunks of the long rows and the non-zeros of
 // the two length lists), one workgroup turns the counts into offsets and hands the totals to the host, one pass writes
-// the lists in row order.  A column block's sub-plan only needs the split rows (big_deg < 0).
+// the lists in row order.
 struct RowLists {
   const int* rowptr;
   int nrows, S, big_deg, mid_deg;
@@ -241,8 +241,8 @@ __device__ __forceinline__ void row_memberships(const RowLists& q, int r, int (&
   const int b = q.rowptr[r], e = q.rowptr[r + 1];
   len = e - b;
   m[kSplitList] = e > b && (b / q.S) != ((e - 1) / q.S);
-  m[kBigList] = q.big_deg >= 0 && len > q.big_deg;
-  m[kMidList] = q.big_deg >= 0 && len > q.mid_deg && len <= q.big_deg;
+  m[kBigList] = len > q.big_deg;
+  m[kMidList] = len > q.mid_deg && len <= q.big_deg;
   m[kChunkList] = m[kBigList] ? pieces_of(len, kHubEdges) : 0;
 }
 
@@ -352,10 +352,9 @@ __global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int
   }
 }
 
-// Builds the segment arrays, row lists and staging buffer of p for the graph g (p->S, p->nseg, p->max_F set by the
-// caller).  sub = true: p is the sub-plan of one column block; otherwise the graph is validated as well.  The host waits
-// twice: for the totals of the lists (which size the allocations) and for the arrays.
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, bool sub) {
+// Validates the graph g and builds the segment arrays, row lists and row tasks of p for it (p->S, p->nseg, p->max_F set by the
+// caller).  The host waits twice: for the totals of the lists (which size the allocations) and for the arrays.
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s) {
   const int64_t E = g->nnz;
   const int nblk = int(ceil_div(g->nrows, kRowsPerBlock));
   DevTemp facts_buf(s), counts_buf(s);
@@ -365,23 +364,20 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, b
   GraphFacts* facts = facts_buf.as<GraphFacts>();
   GraphFacts* totals = mail.data ? reinterpret_cast<GraphFacts*>(mail.data) : facts + 1;
   int* counts = counts_buf.as<int>();
-  if (sub) HGNN_HIP(hipMemsetAsync(facts, 0, sizeof(GraphFacts), s));
-  else HGNN_HIP(launch_validate(g, facts, s));
-  const RowLists q{g->rowptr, g->nrows, p->S, sub ? -1 : p->big_deg, p->mid_deg};
+  HGNN_HIP(launch_validate(g, facts, s));
+  const RowLists q{g->rowptr, g->nrows, p->S, p->big_deg, p->mid_deg};
   if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
   row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
   HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
   const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz), g->nnz};
   TaskCounts tc(s);
-  if (!sub) {
-    const hgnn_status ts = task_count(tq, tc, s);
-    if (ts != HGNN_OK) return ts;
-  }
+  hgnn_status st = task_count(tq, tc, s);
+  if (st != HGNN_OK) return st;
   GraphFacts f;
   if (!mail.data) HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
   HGNN_HIP(s.wait());
   if (mail.data) f = *totals;
-  hgnn_status st = check_facts(f);
+  st = check_facts(f);
   if (st != HGNN_OK) return st;
   p->n_split = f.n_split;
   p->n_big = f.n_big;
@@ -394,11 +390,6 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, b
     seg_rows_kernel<<<dim3(unsigned(ceil_div(p->nseg, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, E, p->S, p->nseg,
                                                                                   p->seg_row_lo, p->seg_row_hi);
     HGNN_LAUNCH_CHECK("seg_rows_kernel");
-    // staging: two partial vectors (entering piece / leaving piece) per segment
-    // (twice over, and three scalars per piece and head: the fused GAT pass that saves for its backward stages two
-    // vectors and (max, sum, masked sum) per piece); every slot that is read has been written by the same call
-    HGNN_HIP(dev_malloc(&p->staging, sizeof(hgnn_half) * size_t(4) * size_t(p->nseg) * size_t(p->max_F)));
-    HGNN_HIP(dev_malloc(&p->stage_mz, sizeof(float) * size_t(6) * size_t(p->nseg) * size_t(p->max_H)));
   }
   if (p->n_split > 0) {
     HGNN_HIP(dev_malloc(&p->split_row, sizeof(int) * size_t(p->n_split)));
@@ -422,15 +413,11 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s, b
                                                                  p->hub_chunk_count});
     HGNN_LAUNCH_CHECK("row_lists_write_kernel");
   }
-  if (!sub) {
-    st = task_build(tq, tc, p->max_F, p->max_H, &p->tasks, s);
-    if (st != HGNN_OK) return st;
-  }
-  if (!sub) {  // a column block's sub-plan only serves the SpMM kernels
-    const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
-    if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));
-    if (g->nrows > 0) HGNN_HIP(dev_malloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));
-  }
+  st = task_build(tq, tc, p->max_F, p->max_H, &p->tasks, s);
+  if (st != HGNN_OK) return st;
+  const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
+  if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));
+  if (g->nrows > 0) HGNN_HIP(dev_malloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));
   HGNN_HIP(s.wait());
   return HGNN_OK;
 }
@@ -497,7 +484,6 @@ void hgnn_plan_cache_bytes(const hgnn_plan* p, int64_t* l2_bytes, int64_t* llc_b
 // idle: nothing that uses the plan is in flight
 static void destroy_plan(hgnn_plan* p, bool idle) {
   if (!p) return;
-  for (hgnn_plan* q : p->sub) destroy_plan(q, idle);
   destroy_plan(p->fine, idle);
   destroy_tasks(p->tasks, idle);
   destroy_tasks(p->btasks, idle);
@@ -508,7 +494,6 @@ static void destroy_plan(hgnn_plan* p, bool idle) {
   dev_put(p->bdelta, idle);
   dev_put(p->bstage, idle);
   dev_put(p->bsum, idle);
-  dev_put(p->bdesc, idle);
   dev_put(p->seg_row_lo, idle);
   dev_put(p->seg_row_hi, idle);
   dev_put(p->split_row, idle);
@@ -521,8 +506,6 @@ static void destroy_plan(hgnn_plan* p, bool idle) {
   dev_put(p->big_first, idle);
   dev_put(p->hub_part, idle);
   dev_put(p->mid_row, idle);
-  dev_put(p->staging, idle);
-  dev_put(p->stage_mz, idle);
   dev_put(p->vscratch, idle);
   dev_put(p->vtab, idle);
   dev_put(p->goff, idle);
@@ -574,7 +557,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
   p->mid_deg = 32;
   device_cache_bytes(&p->l2_bytes, &p->llc_bytes);
   SetupStream s(stream);
-  st = plan_build_arrays(p, g, s, false);
+  st = plan_build_arrays(p, g, s);
   if (st == HGNN_OK) {
     int nb = col_blocks;
     bool narrow_only = false;  // every pass over blocks takes the finer cut
@@ -597,7 +580,12 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         narrow_only = mean_deg >= 64.0 * nb && g->ncols >= 2 * nb;
       }
     }
-    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) st = build_col_blocks(p, g, nb, !narrow_only, s);
+    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) {
+      p->nb = nb;
+      p->block_width = int(ceil_div(g->ncols, nb));
+      p->block_eid = g->eid != nullptr;
+      if (!narrow_only) st = build_col_blocks(p, g, nb, s);
+    }
     // A call that reads edge values through the edge-id map gathers from two tables at once: the feature rows of the
     // block's columns and, for each of those columns, the 128-byte line of the edge tensor that the walk is currently
     // passing (the slots of one source row are consecutive).  Both sets grow with the block's width, so such calls get
@@ -621,7 +609,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
         f->l2_bytes = p->l2_bytes;
         f->llc_bytes = p->llc_bytes;
         f->auto_blocks = true;
-        st = build_col_blocks(f, g, 2 * p->nb, true, s);
+        st = build_col_blocks(f, g, 2 * p->nb, s);
       }
     }
     if (st == HGNN_OK && p->nb > 1 && !narrow_only) st = build_block_tasks(p, s);
@@ -638,27 +626,6 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
     return st;
   }
   *out = p;
-  return HGNN_OK;
-}
-
-hgnn_status hgnn_plan_block_export(const hgnn_plan* p, int32_t b, int64_t* nnz_b, int32_t* rowptr_b, int32_t* col_b,
-                                   int32_t* eid_b, int32_t* seg_row_lo, int32_t* seg_row_hi) {
-  clear_error();
-  HGNN_REQUIRE(p != nullptr, HGNN_EINVAL, "hgnn_plan_block_export: plan is NULL");
-  HGNN_REQUIRE(p->nb > 1 && b >= 0 && b < p->nb, HGNN_EINVAL, "hgnn_plan_block_export: block %d of %d", b, p->nb);
-  HGNN_HIP(hipDeviceSynchronize());
-  const int64_t off = p->boff[size_t(b)], n = p->boff[size_t(b) + 1] - off;
-  if (nnz_b) *nnz_b = n;
-  if (rowptr_b)
-    HGNN_HIP(hipMemcpy(rowptr_b, p->brp + size_t(b) * (size_t(p->nrows) + 1), sizeof(int) * (size_t(p->nrows) + 1),
-                       hipMemcpyDeviceToHost));
-  if (n > 0) {
-    if (col_b) HGNN_HIP(hipMemcpy(col_b, p->bcol + off, sizeof(int) * size_t(n), hipMemcpyDeviceToHost));
-    if (eid_b) HGNN_HIP(hipMemcpy(eid_b, p->beid + off, sizeof(int) * size_t(n), hipMemcpyDeviceToHost));
-    const hgnn_plan* q = p->sub[size_t(b)];
-    if (seg_row_lo) HGNN_HIP(hipMemcpy(seg_row_lo, q->seg_row_lo, sizeof(int) * size_t(q->nseg), hipMemcpyDeviceToHost));
-    if (seg_row_hi) HGNN_HIP(hipMemcpy(seg_row_hi, q->seg_row_hi, sizeof(int) * size_t(q->nseg), hipMemcpyDeviceToHost));
-  }
   return HGNN_OK;
 }
 

@@ -22,6 +22,8 @@ std::map<void*, int> live;             // allocation -> device
 std::set<hipStream_t> busy[kDevices];  // streams with work in flight
 std::vector<std::string> launched;
 std::string launched_text;
+size_t live_bytes = 0;
+std::map<void*, size_t> sizes;
 int mallocs = 0, frees = 0, freed_busy = 0, fail_at = -1, fail_waits = 0;
 bool capturing = false, spoiled = false;
 std::string library;
@@ -59,6 +61,7 @@ int fake_mallocs() { return mallocs; }
 int fake_frees() { return frees; }
 int fake_freed_busy() { return freed_busy; }
 int fake_live() { return int(live.size()); }
+size_t fake_live_bytes() { return live_bytes; }
 int fake_spoiled() { return spoiled; }
 void fake_capture(int on) { capturing = on != 0; }
 void fake_fail_malloc(int n) { fail_at = n < 0 ? -1 : mallocs + n; }
@@ -98,7 +101,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (refused()) return hipErrorStreamCaptureUnsupported;
   if (mallocs++ == fail_at) return hipErrorInvalidValue;
   *p = calloc(n, 1);
-  if (*p) live[*p] = cur;
+  if (*p) live[*p] = cur, sizes[*p] = n, live_bytes += n;
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void* p) {
@@ -110,6 +113,7 @@ hipError_t hipFree(void* p) {
   if (fail_waits) return hipErrorUnknown;
   busy[it->second].clear();
   live.erase(it);
+  live_bytes -= sizes[p];
   free(p);
   return hipSuccess;
 }

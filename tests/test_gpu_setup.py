@@ -170,3 +170,34 @@ def test_transpose_of_a_malformed_offset_array(hgnn, dev, what, wide):
     assert np.array_equal(down(out[0][pad:-pad]), np.searchsorted(col[t], np.arange(V + 1)))
     with pytest.raises(hgnn.HgnnError):
         hgnn.hgnn_csr_validate(g)
+
+
+@pytest.mark.parametrize("ncols,mapped", [(100003, False), (100003, True), (233001, True)])
+def test_export_of_automatic_blocks(hgnn, dev, ncols, mapped):
+    """The plan keeps the finer cut alone where every pass walks it; the exported blocks are those of the coarse cut, whose borders
+    the finer one need not have."""
+    V, S = 5000, 256
+    r = np.random.default_rng(ncols)
+    rowptr = np.concatenate([[0], np.cumsum(r.integers(200, 900, V))]).astype(np.int32)
+    E = int(rowptr[-1])
+    row = np.repeat(np.arange(V), np.diff(rowptr))
+    col = r.integers(0, ncols, E)
+    col = col[np.lexsort((col, row))].astype(np.int32)
+    eid = r.permutation(E).astype(np.int32) if mapped else None
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=None if eid is None else up(eid, dev))
+    p = hgnn.hgnn_plan_create(g, S, 64, 1, col_blocks=0)
+    nb = hgnn.hgnn_plan_col_blocks(p)
+    assert nb >= 2 and hgnn.hgnn_plan_col_blocks_fine(p) == 2 * nb
+    width = -(-ncols // nb)
+    for b in range(nb):
+        x = hgnn.hgnn_plan_block_export(p, b)
+        at = np.flatnonzero((col >= b * width) & (col < (b + 1) * width))
+        assert np.array_equal(x["col"], col[at]) and np.array_equal(x["eid"], eid[at] if mapped else at)
+        rp = np.concatenate([[0], np.cumsum(np.bincount(row[at], minlength=V))])
+        assert np.array_equal(x["rowptr"], rp)
+        first = np.arange(0, at.size, S)
+        assert np.array_equal(x["seg_row_lo"], row[at][first])
+        assert np.array_equal(x["seg_row_hi"], row[at][np.minimum(first + S, at.size) - 1])
+    with pytest.raises(hgnn.HgnnError):
+        hgnn.hgnn_plan_block_export(p, nb)
+    hgnn.hgnn_plan_destroy(p)

@@ -142,7 +142,24 @@ def failed_calls(h):
     h.lib.hgnn_plan_destroy(p)
 
 
-SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture, replaced_groups, replaced_slices, failed_calls]
+def bytes_per_non_zero(h):
+    """What a plan holds for every non-zero of a graph that the automatic rule cuts into column blocks: a 16-bit column id, its slot
+    where the graph has a map, and two row ids per segment (lists of pieces aside, which depend on the rows)."""
+    h.fake.fake_live_bytes.restype = ctypes.c_size_t
+    for eid, most in ((None, 2.2), (h.g.rowptr, 6.2)):
+        total = []
+        for nnz in (1 << 24, 1 << 25):
+            h.reset()
+            h.g = Csr(20000, 120000, nnz, h.g.rowptr, h.g.col, None, eid)  # a table of 15 MB, rows of 800 and more
+            st, p = h.plan(A, 0)
+            assert st == OK and h.lib.hgnn_plan_col_blocks(p) == 2 and h.lib.hgnn_plan_col_blocks_fine(p) == 4
+            h.lib.hgnn_release_cached_memory()
+            total.append(h.fake.fake_live_bytes())
+            h.lib.hgnn_plan_destroy(p)
+        assert total[1] - total[0] <= most * (1 << 24), (eid, total)
+
+
+SCENARIOS = [destroy_on_another_device, failed_wait, destroyed_during_a_capture, replaced_groups, replaced_slices, failed_calls, bytes_per_non_zero]
 
 
 @pytest.fixture(scope="module")
