@@ -209,34 +209,6 @@ __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
   return p;
 }
 
-// four consecutive rounds of a lane's reads from an index array, in flight together: v[q] = p[i0 + q * kWave], or 0
-// from position n on.  NT is a template parameter because a run-time choice between two loads of one address is
-// folded into a single ordinary load by the compiler.
-template <bool NT>
-__device__ __forceinline__ void stream_load4(const int* __restrict__ p, int i0, int n, int (&v)[4]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + q * kWave;
-    v[q] = 0;
-    if (i < n) v[q] = NT ? __builtin_nontemporal_load(p + i) : p[i];
-  }
-}
-
-// Reads the n column ids of a segment (0 beyond n) and hands them to put(i, c) for i in [0, spad); spad is a
-// multiple of 4 * kWave (see seg_slots_per_lane).  A lane has its four loads of a round in flight together: a loop
-// of one load and one LDS store per turn waits for every load in turn, four memory latencies per 256 edges.
-template <class Put>
-__device__ __forceinline__ void seg_stage_cols(const int* __restrict__ col, int64_t e0, int lane, int spad, int n, bool nt,
-                                               Put&& put) {
-  for (int i0 = lane; i0 < spad; i0 += 4 * kWave) {
-    int c[4];
-    if (nt) stream_load4<true>(col + e0, i0, n, c);
-    else stream_load4<false>(col + e0, i0, n, c);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) put(i0 + q * kWave, c[q]);
-  }
-}
-
 template <bool BLOCK_SYNC = false>
 __device__ __forceinline__ void seg_stage_rows(int* s_row, int* s_blk, int lane, int per, int n, int row_lo, int row_hi,
                                                const int* __restrict__ rowptr, int64_t e0) {

@@ -4,7 +4,7 @@
 // Over a plan's row tasks a lane group stays inside one row: that row's vector is in registers, every lane loads 16 bytes (8
 // halves) of the column vertices' rows -- the wide per-lane load of section 5.1.3 -- eight non-zeros at a time, and the
 // eight partial dot products are summed by halves across the lanes of a head.  Results are collected in LDS and written
-// back coalesced.  The narrower loads of the vector-width study run over the plan's segments of consecutive non-zeros.
+// back coalesced.  The vector-width study of section 6.3.1 runs the same kernel with 4 or 2 halves per lane and load.
 #include "task.h"
 
 namespace hgnn {
@@ -32,166 +32,49 @@ struct SddmmArgs {
 
 constexpr int kTile = 256;  // non-zeros per wave in the kernels that run without a plan
 
-struct SddmmLds {
-  int per, spad, col_off, row_off, blk_off, out_off, total;
-};
-__host__ __device__ inline SddmmLds sddmm_lds_layout(int S, int H) {
-  SddmmLds o;
-  o.per = 4 * ((S + 255) / 256);
-  o.spad = kWave * o.per;
-  o.col_off = 0;
-  o.row_off = o.spad * 4;
-  o.blk_off = o.row_off + o.spad * 4;
-  o.out_off = o.blk_off + ((o.spad + 15) & ~15);
-  o.total = o.out_off + ((o.spad * H * 2 + 15) & ~15);
-  return o;
-}
-
-// DOT over one plan segment per wave:  out[k,h] = <U[row k, h], Vt[col k, h]>
-// VW = halves per lane and load: 4 or 2, for the vector-width study of section 6.3.1 (a head spans D/VW lanes).
-template <int L, int VW>
-__global__ __launch_bounds__(kBlock, 8) void sddmm_seg_kernel(SddmmArgs a) {
-  constexpr int G = kWave / L;
-  typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int g = lane / L, l = lane % L;
-  const int f0 = VW * l;
-  const bool active = f0 < a.F;
-  const int f0c = active ? f0 : 0;
-  const int LH = a.D / VW;  // lanes per head (power of two)
-  const int head = f0c / a.D;
-  auto load8 = [&](const half_t* p) -> hv_t { return *reinterpret_cast<const hv_t*>(p); };
-  auto dot = [&](const hv_t& x, const hv_t& y) -> float {
-    float p = 0.f;
-#pragma unroll
-    for (int i = 0; i < VW; ++i) p = fmaf(float(x[i]), float(y[i]), p);
-    return p;
-  };
-  const int lh = l % LH;
-  const int S = a.S;
-  const SddmmLds lay = sddmm_lds_layout(S, a.H);
-  unsigned char* base = smem + size_t(wave) * lay.total;
-  int* s_col = reinterpret_cast<int*>(base + lay.col_off);
-  int* s_row = reinterpret_cast<int*>(base + lay.row_off);
-  int* s_blk = reinterpret_cast<int*>(base + lay.blk_off);
-  half_t* s_out = reinterpret_cast<half_t*>(base + lay.out_off);
-
-  const int wpb = int(blockDim.x) / kWave;
-  int64_t wg = blockIdx.x;
-  const int64_t seg = wg * wpb + wave;
-  const bool valid = seg < a.nseg;
-  const int64_t e0 = seg * S;
-  const int n = valid ? int(a.nnz - e0 < S ? a.nnz - e0 : S) : 0;
-  const int row_lo = valid ? a.seg_lo[seg] : 0, row_hi = valid ? a.seg_hi[seg] : -1;
-  seg_stage_cols(a.col, e0, lane, lay.spad, n, stream_nontemporal(a.nnz), [&](int i, int c) { s_col[i] = c; });
-  seg_stage_rows(s_row, s_blk, lane, lay.per, n, row_lo, row_hi, a.rowptr, e0);
-
-  const int C = 4 * ((S + 4 * G - 1) / (4 * G));
-  const int c0 = g * C < n ? g * C : n;
-  const int c1 = c0 + C < n ? c0 + C : n;
-  int cur = -1;
-  hv_t u = hv_t(0);
-  if (c0 < c1) {
-    cur = s_row[c0];
-    u = load8(a.U + int64_t(cur) * a.ldu + f0c);
-  }
-  for (int i = c0; i < c1; i += 4) {
-    const int4_t cols = *reinterpret_cast<const int4_t*>(s_col + i);
-    const int blk = s_blk[i >> 2];
-    hv_t v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = load8(a.Vt + int64_t(cols[q]) * a.ldv + f0c);
-    float p[4];
-    if (blk == cur) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) p[q] = dot(u, v[q]);
-    } else {
-      const int4_t rows = *reinterpret_cast<const int4_t*>(s_row + i);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        p[q] = 0.f;
-        if (i + q < c1) {
-          if (rows[q] != cur) {
-            cur = rows[q];
-            u = load8(a.U + int64_t(cur) * a.ldu + f0c);
-          }
-          p[q] = dot(u, v[q]);
-        }
-      }
-    }
-    // transposing butterfly over the LH lanes of a head: 4 values -> 2 -> 1, then plain exchanges
-    if (LH >= 2) {
-      const bool b0 = lh & 1;
-      const float r0 = __shfl_xor(b0 ? p[0] : p[2], 1);
-      const float r1 = __shfl_xor(b0 ? p[1] : p[3], 1);
-      p[0] = (b0 ? p[2] : p[0]) + r0;  // edges {0,1} on even lanes, {2,3} on odd lanes
-      p[1] = (b0 ? p[3] : p[1]) + r1;
-      if (LH >= 4) {
-        const bool b1 = (lh >> 1) & 1;
-        const float r = __shfl_xor(b1 ? p[0] : p[1], 2);
-        p[0] = (b1 ? p[1] : p[0]) + r;  // edge 2*b0 + b1
-        for (int off = 4; off < LH; off <<= 1) p[0] += __shfl_xor(p[0], off);
-        const int e = i + 2 * int(b0) + int(b1);
-        if (active && lh < 4 && e < c1) s_out[e * a.H + head] = half_t(p[0]);
-      } else {
-        const int e = i + 2 * int(b0);
-        if (active && e < c1) s_out[e * a.H + head] = half_t(p[0]);
-        if (active && e + 1 < c1) s_out[(e + 1) * a.H + head] = half_t(p[1]);
-      }
-    } else if (active) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (i + q < c1) s_out[(i + q) * a.H + head] = half_t(p[q]);
-    }
-  }
-  wave_sync();
-  // coalesced write-back, 16 bytes per lane where the destination allows it
-  const int tot = n * a.H;
-  half_t* dst = a.out + e0 * a.H;
-  if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
-    const int nv = tot / 8;
-    for (int j = lane; j < nv; j += kWave)
-      reinterpret_cast<half8_t*>(dst)[j] = reinterpret_cast<const half8_t*>(s_out)[j];
-    for (int j = nv * 8 + lane; j < tot; j += kWave) dst[j] = s_out[j];
-  } else {
-    for (int j = lane; j < tot; j += kWave) dst[j] = s_out[j];
-  }
-}
-
 // DOT over row tasks: out[k,h] = <U[row, h], Vt[col k, h]>.  MASK: one head whose length is not a multiple of 8 -- the group's
 // lanes cover the padded row pitch and the elements past D are forced to zero on both operands (whatever the padding
-// columns hold).  RS = min(lanes per head, 8).  Bound: the gathers (a row of 128 bytes is one request to the L2s).  Against
+// columns hold).  VW = halves per lane and load: 8, or 4 / 2 for the vector-width study (a row then takes more lanes, a wave holds
+// fewer rows).  RS = min(lanes per head, 8).  Bound: the gathers (a row of 128 bytes is one request to the L2s).  Against
 // the walk over equal runs of non-zeros, whose row changes took most of its steps through a slow path: 114 M non-zeros, one
-// head of 64: 1.07 -> 0.98 ms; 5.5 M, four heads of 16: the same (62, 66 us).
-template <int L, bool NEAR, bool MASK, int RS>
+// head of 64 in blocks: 1.06 -> 0.92 ms; 5.5 M, four heads of 16: the same (58 us); on power-law graphs of 20 to 31 M, where the
+// gathers miss the L2s and the results of a row no longer fill lines with their neighbours', 1 to 6 % slower (31 M: one head of
+// 64 338 -> 350 us, four of 16 391 -> 393).
+template <int L, bool NEAR, bool MASK, int RS, int VW>
 __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(SddmmArgs a, TaskView v) {
   constexpr int G = kWave / L;
+  typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
   typedef Round<L> Rd;
   typedef HeadTile<RS> Ht;
   __shared__ __align__(16) int s_handles[G * Rd::PITCH];
   __shared__ __align__(16) half_t s_results[kWave * Rd::R];  // [G][R * H]: H is at most L
   const int lane = threadIdx.x;
   const int g = lane / L, l = lane % L;
-  const int f0 = 8 * l;
+  const int f0 = VW * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
   const int head = MASK ? 0 : f0c / a.D;
-  const int LH = MASK ? L : a.D / 8;        // lanes per head (power of two)
+  const int LH = MASK ? L : a.D / VW;       // lanes per head (power of two)
   const int nvalid = active ? a.F - f0 : 0; // MASK: elements of this lane's vector that exist
-  auto masked = [&](half8_t x) -> half8_t {
+  auto masked = [&](hv_t x) -> hv_t {
     if (MASK) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = i < nvalid ? x[i] : half_t(0);
+      for (int i = 0; i < VW; ++i) x[i] = i < nvalid ? x[i] : half_t(0);
     }
     return x;
+  };
+  auto dot_of = [](const hv_t& p, const hv_t& q) -> float {
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < VW; ++i) d = fmaf(float(p[i]), float(q[i]), d);
+    return d;
   };
   const TaskWave w = task_enter<L>(v, blockIdx.x, g);
   int* const s_hnd = s_handles + g * Rd::PITCH;
   half_t* const s_out = s_results + g * (Rd::R * L);
   const RowTable<NEAR> table(a.Vt, a.ncols, a.ldv, f0c);
   const int row = w.row >= 0 ? w.row : 0;
-  const half8_t ur = masked(*reinterpret_cast<const half8_t*>(a.U + int64_t(row) * a.ldu + f0c));
+  const hv_t ur = masked(*reinterpret_cast<const hv_t*>(a.U + int64_t(row) * a.ldu + f0c));
   const int64_t shift = a.delta ? int64_t(a.delta[int64_t(w.block) * a.nrows + row]) - w.first : 0;
   const int own = (lane & (Rd::LC - 1)) * Rd::E;
   const int edge = Ht::own_edge(l);
@@ -218,12 +101,12 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
         h8[u] = ha[u];
         h8[4 + u] = hb[u];
       }
-      half8_t x[8];
+      hv_t x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = table.row(h8[u]);
+      for (int u = 0; u < 8; ++u) x[u] = table.template row<VW>(h8[u]);
       float d[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) d[u] = dot8(ur, masked(x[u]));
+      for (int u = 0; u < 8; ++u) d[u] = dot_of(ur, masked(x[u]));
       if (RS == 8 && LH > 8) {  // heads of more than eight lanes: the eights are added first
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -430,39 +313,40 @@ static void launch_edge(int L, dim3 grid, size_t lds, hipStream_t s, const Sddmm
   }
 }
 
-template <int VW>
-static void launch_seg_vw(int L, dim3 grid, int threads, size_t lds, hipStream_t s, const SddmmArgs& a) {
-  switch (L) {
-    case 1: sddmm_seg_kernel<1, VW><<<grid, threads, lds, s>>>(a); break;
-    case 2: sddmm_seg_kernel<2, VW><<<grid, threads, lds, s>>>(a); break;
-    case 4: sddmm_seg_kernel<4, VW><<<grid, threads, lds, s>>>(a); break;
-    case 8: sddmm_seg_kernel<8, VW><<<grid, threads, lds, s>>>(a); break;
-    case 16: sddmm_seg_kernel<16, VW><<<grid, threads, lds, s>>>(a); break;
-    case 32: sddmm_seg_kernel<32, VW><<<grid, threads, lds, s>>>(a); break;
-    default: sddmm_seg_kernel<64, VW><<<grid, threads, lds, s>>>(a); break;
-  }
-}
-
-template <int L, bool NEAR>
+template <int L, bool NEAR, int VW>
 static void launch_dot_tasks_l(int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
-  if (mask) sddmm_task_kernel<L, NEAR, true, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v);
-  else if (lh == 1) sddmm_task_kernel<L, NEAR, false, 1><<<waves, kWave, 0, s>>>(a, v);
-  else if (lh == 2) sddmm_task_kernel<L, NEAR, false, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v);
-  else if (lh == 4) sddmm_task_kernel<L, NEAR, false, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v);
-  else sddmm_task_kernel<L, NEAR, false, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v);
+  if constexpr (VW == 8) {
+    if (mask) {
+      sddmm_task_kernel<L, NEAR, true, L < 8 ? L : 8, VW><<<waves, kWave, 0, s>>>(a, v);
+      return;
+    }
+    if (lh == 1) {
+      sddmm_task_kernel<L, NEAR, false, 1, VW><<<waves, kWave, 0, s>>>(a, v);
+      return;
+    }
+  }
+  if (lh == 2) sddmm_task_kernel<L, NEAR, false, L < 2 ? L : 2, VW><<<waves, kWave, 0, s>>>(a, v);
+  else if (lh == 4) sddmm_task_kernel<L, NEAR, false, L < 4 ? L : 4, VW><<<waves, kWave, 0, s>>>(a, v);
+  else sddmm_task_kernel<L, NEAR, false, L < 8 ? L : 8, VW><<<waves, kWave, 0, s>>>(a, v);
 }
 
-template <bool NEAR>
+template <bool NEAR, int VW>
 static void launch_dot_tasks(int L, int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
   switch (L) {
-    case 1: launch_dot_tasks_l<1, NEAR>(lh, mask, waves, s, a, v); break;
-    case 2: launch_dot_tasks_l<2, NEAR>(lh, mask, waves, s, a, v); break;
-    case 4: launch_dot_tasks_l<4, NEAR>(lh, mask, waves, s, a, v); break;
-    case 8: launch_dot_tasks_l<8, NEAR>(lh, mask, waves, s, a, v); break;
-    case 16: launch_dot_tasks_l<16, NEAR>(lh, mask, waves, s, a, v); break;
-    case 32: launch_dot_tasks_l<32, NEAR>(lh, mask, waves, s, a, v); break;
-    default: launch_dot_tasks_l<64, NEAR>(lh, mask, waves, s, a, v); break;
+    case 1: launch_dot_tasks_l<1, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    case 2: launch_dot_tasks_l<2, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    case 4: launch_dot_tasks_l<4, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    case 8: launch_dot_tasks_l<8, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    case 16: launch_dot_tasks_l<16, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    case 32: launch_dot_tasks_l<32, NEAR, VW>(lh, mask, waves, s, a, v); break;
+    default: launch_dot_tasks_l<64, NEAR, VW>(lh, mask, waves, s, a, v); break;
   }
+}
+
+template <int VW>
+static void launch_dot(bool near, int L, int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
+  if (near) launch_dot_tasks<true, VW>(L, lh, mask, waves, s, a, v);
+  else launch_dot_tasks<false, VW>(L, lh, mask, waves, s, a, v);
 }
 
 static void launch_proj(int L, dim3 grid, hipStream_t s, const half_t* feat, int64_t ld, int nv, const half_t* avec, int F,
@@ -596,22 +480,10 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
   }
   if ((vec || masked) && !score && p) {
     // halves per lane: the plan's setting, when the shape allows a narrower load than 16 bytes
-    const int vw = p->vec_halves;
-    if (vw != 8) {
-      const int lh = D / vw;
+    const int vw = p->vec_halves, lh = D / vw;
+    if (vw != 8)
       HGNN_REQUIRE(vec && F <= kWave * vw && D % vw == 0 && (lh & (lh - 1)) == 0, HGNN_EUNSUPPORTED,
                    "hgnn_sddmm: %d halves per lane needs F <= %d and D / %d a power of two", vw, kWave * vw, vw);
-      const size_t seg_per_wave = size_t(sddmm_lds_layout(a.S, H).total);
-      const int wpb = waves_per_block_for_lds(seg_per_wave, true);
-      const size_t lds = seg_per_wave * wpb;
-      if (lds <= 65536) {
-        const dim3 grid(unsigned(ceil_div(p->nseg, wpb)));
-        if (vw == 4) launch_seg_vw<4>(pow2_at_least(F / vw), grid, wpb * kWave, lds, s, a);
-        else launch_seg_vw<2>(pow2_at_least(F / vw), grid, wpb * kWave, lds, s, a);
-        HGNN_LAUNCH_CHECK("sddmm_seg_kernel");
-        return HGNN_OK;
-      }
-    }
     // column-blocked plan: block after block, so that the gathered slice of Vt stays cache resident (a plan built over an
     // edge-id map maps its blocks to that map's slots)
     const hgnn_row_tasks* t = p->tasks;
@@ -621,11 +493,14 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
       a.col = p->bcol;
       a.delta = p->bdelta;
     }
-    const TaskView v = task_view(t, kWave / L, false);
+    const int lanes = pow2_at_least((F + vw - 1) / vw);
+    const TaskView v = task_view(t, kWave / lanes, false);
     const int waves = v.first_wave[t->nb];
     if (waves > 0) {
-      if (near_table(g->ncols, ldv)) launch_dot_tasks<true>(L, LH, masked, unsigned(waves), s, a, v);
-      else launch_dot_tasks<false>(L, LH, masked, unsigned(waves), s, a, v);
+      const bool near = near_table(g->ncols, ldv);
+      if (vw == 8) launch_dot<8>(near, lanes, lh, masked, unsigned(waves), s, a, v);
+      else if (vw == 4) launch_dot<4>(near, lanes, lh, false, unsigned(waves), s, a, v);
+      else launch_dot<2>(near, lanes, lh, false, unsigned(waves), s, a, v);
       HGNN_LAUNCH_CHECK("sddmm_task_kernel");
     }
     return HGNN_OK;

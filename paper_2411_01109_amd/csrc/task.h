@@ -238,14 +238,19 @@ struct RowTable {
     if (NEAR) return valid ? int(uint32_t(c) * pitch) : int(kNoRow);
     return valid ? c : -1;
   }
-  __device__ __forceinline__ half8_t row(int h) const {
+  template <int VW = 8>  // halves per lane
+  __device__ __forceinline__ auto row(int h) const {
+    typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
     if (NEAR) {
+      typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
       typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
-      const uint4_t r = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(uint32_t(h) + lane_bytes), 0, 0);
-      return __builtin_bit_cast(half8_t, r);
+      const int at = int(uint32_t(h) + lane_bytes);
+      if constexpr (VW == 8) return __builtin_bit_cast(hv_t, uint4_t(__builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0)));
+      else if constexpr (VW == 4) return __builtin_bit_cast(hv_t, uint2_t(__builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0)));
+      else return __builtin_bit_cast(hv_t, unsigned(__builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0)));
     }
-    half8_t r = half8_t(0);
-    if (h >= 0) r = *reinterpret_cast<const half8_t*>(base + int64_t(h) * ld);
+    hv_t r = hv_t(0);
+    if (h >= 0) r = *reinterpret_cast<const hv_t*>(base + int64_t(h) * ld);
     return r;
   }
 };

@@ -187,3 +187,51 @@ def test_both_kinds_of_pieces_side_by_side(hgnn, dev):
             assert np.abs(got - want[:, None]).max() <= 2.0 ** -11 * want.max(), (long_rows, F)  # pieces are exact, one rounding
             assert np.array_equal(got[want <= 2], np.broadcast_to(want[:, None], got.shape)[want <= 2]), (long_rows, F)
             hgnn.hgnn_plan_destroy(p)
+
+
+# (H, D, S, col_blocks): every number of lanes per row and per head, pieces of one non-zero, of a round, of the largest segment
+SHAPES = [(1, 8, 1, 1), (1, 8, 256, 3), (2, 8, 32, 1), (1, 16, 64, 2), (4, 8, 256, 1), (2, 16, 33, 3), (1, 32, 2048, 1), (8, 8, 256, 1),
+          (4, 16, 256, 2), (2, 32, 100, 1), (1, 64, 256, 3), (4, 32, 256, 1), (1, 128, 1, 3), (8, 32, 256, 1), (1, 256, 64, 2), (8, 64, 256, 1)]
+
+
+@pytest.mark.parametrize("H,D,S,nb", SHAPES)
+def test_sddmm_piece_borders(hgnn, dev, H, D, S, nb):
+    """The dot products at the borders of pieces, over blocks too, at every width of the vector-width study."""
+    print(f"sddmm borders H={H} D={D} S={S} nb={nb}", flush=True)
+    V, F = 2300, H * D
+    rowptr, col = border_graph(V, V, F + S)
+    r = np.random.default_rng(F)
+    U, X = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    p = hgnn.hgnn_plan_create(g, S, F, H, col_blocks=nb)
+    ref = oracle.sddmm_dot(rowptr, col, U, X, H=H)
+    row = np.repeat(np.arange(V), np.diff(rowptr))
+    mag = (np.abs(U[row].astype(np.float64)) * np.abs(X[col].astype(np.float64))).reshape(-1, H, D).sum(-1)
+    Ud, Xd = up(U, dev), up(X, dev)
+    for vw in (8, 4, 2):
+        if F > 64 * vw:
+            continue
+        hgnn.hgnn_plan_set_vector_halves(p, vw)
+        e = torch.full((col.size, H), 7.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, H, D, Ud, Xd, e)
+        compare(f"sddmm borders, {vw} halves per lane", down(e), ref, mag)
+    hgnn.hgnn_plan_destroy(p)
+
+
+@pytest.mark.parametrize("D,S,nb", [(2, 256, 1), (6, 64, 3), (42, 256, 2), (100, 1, 1), (250, 2048, 3)])
+def test_sddmm_masked_piece_borders(hgnn, dev, D, S, nb):
+    """One head whose length is no multiple of 8; the padding columns hold what must not count."""
+    V, ld = 2300, (D + 7) // 8 * 8
+    rowptr, col = border_graph(V, V, D + S)
+    r = np.random.default_rng(D)
+    U, X = np.full((V, ld), np.nan, np.float16), np.full((V, ld), np.inf, np.float16)
+    U[:, :D], X[:, :D] = f16(r.standard_normal((V, D))), f16(r.standard_normal((V, D)))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    p = hgnn.hgnn_plan_create(g, S, ld, 1, col_blocks=nb)
+    e = torch.full((col.size, 1), 7.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, 1, D, up(U, dev), up(X, dev), e)
+    u, x = np.ascontiguousarray(U[:, :D]), np.ascontiguousarray(X[:, :D])
+    row = np.repeat(np.arange(V), np.diff(rowptr))
+    mag = (np.abs(u[row].astype(np.float64)) * np.abs(x[col].astype(np.float64))).sum(-1, keepdims=True)
+    compare("masked sddmm borders", down(e), oracle.sddmm_dot(rowptr, col, u, x), mag)
+    hgnn.hgnn_plan_destroy(p)
