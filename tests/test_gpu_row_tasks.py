@@ -235,3 +235,47 @@ def test_sddmm_masked_piece_borders(hgnn, dev, D, S, nb):
     mag = (np.abs(u[row].astype(np.float64)) * np.abs(x[col].astype(np.float64))).sum(-1, keepdims=True)
     compare("masked sddmm borders", down(e), oracle.sddmm_dot(rowptr, col, u, x), mag)
     hgnn.hgnn_plan_destroy(p)
+
+
+@pytest.mark.parametrize("flip", [False, True])  # border rows in the pass over the graph, or in the one over its transpose
+@pytest.mark.parametrize("H,D,S,nb", SHAPES)
+def test_gat_piece_borders(hgnn, dev, H, D, S, nb, flip):
+    print(f"gat borders H={H} D={D} S={S} nb={nb} flip={flip}", flush=True)
+    from test_gpu_gat_fused import bwd_reference, check_lse
+    V, F = 2300, H * D
+    rowptr, col = border_graph(V, V, F + S + 1)
+    if flip:
+        rowptr, col = oracle.transpose(rowptr, col, V)[:2]
+    r = np.random.default_rng(F + 1)
+    X, dOut = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
+    a_l, a_r = f16(0.3 * r.standard_normal(F)), f16(0.3 * r.standard_normal(F))
+    oref, lref, oabs, mref, cref = oracle.gat_forward(rowptr, col, X, X, a_l, a_r, H, want_saved=True)
+    (dV, dV_abs), (d_el, el_abs), (d_er, er_abs) = bwd_reference(rowptr, col, V, X, X, a_l, a_r, dOut, H)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    gt = hgnn.hgnn_transpose(g)
+    p, pt = (hgnn.hgnn_plan_create(x, S, F, H, col_blocks=nb) for x in (g, gt))
+    Xd, dOd, ald, ard = (up(t, dev) for t in (X, dOut, a_l, a_r))
+    half = lambda *s: torch.full(s, 7.0, dtype=torch.float16, device=dev)  # noqa: E731
+    f32 = lambda *s: torch.full(s, 7.0, dtype=torch.float32, device=dev)  # noqa: E731
+    out, outm, lse, csum, out0 = half(V, F), half(V, F), f32(V, H), f32(V, H), half(V, F)
+    hgnn.hgnn_gat_forward_fused_save(g, p, H, D, Xd, Xd, ald, ard, out, lse, outm, csum)
+    hgnn.hgnn_gat_forward_fused(g, p, H, D, Xd, Xd, ald, ard, out0)
+    compare("out", down(out), oref, oabs)
+    assert np.array_equal(down(out0).view(np.uint16), down(out).view(np.uint16))
+    check_lse("borders", down(lse), lref, np.diff(rowptr))
+    compare("out_masked", down(outm), mref, oabs)
+    assert np.abs(down(csum).astype(np.float64) - cref).max() <= 2e-3
+    # dV of a column is staged in fp16 pieces and block partials: values below 2^-14 lose up to 2^-25 with each of them (compare
+    # allows 2^-11 of the magnitude it is given)
+    dV_abs = dV_abs + 2.0 ** 11 * 2.0 ** -25 * (np.bincount(col, minlength=V)[:, None] / S + nb + 1)
+    for saved in (False, True):
+        gV, gl, gr = half(V, F), half(V, H), half(V, H)
+        if saved:
+            hgnn.hgnn_gat_backward_fused_saved(g, p, gt, pt, H, D, Xd, Xd, ald, ard, out, lse, outm, csum, dOd, gV, gl, gr)
+        else:
+            hgnn.hgnn_gat_backward_fused(g, p, gt, pt, H, D, Xd, Xd, ald, ard, out, lse, dOd, gV, gl, gr)
+        compare("dV", down(gV), dV, dV_abs)
+        compare("d_el", down(gl), d_el, el_abs, rel_l2=2e-2)  # cancelling sums, as in the tests of the shapes
+        compare("d_er", down(gr), d_er, er_abs, rel_l2=2e-2)
+    hgnn.hgnn_plan_destroy(p)
+    hgnn.hgnn_plan_destroy(pt)
