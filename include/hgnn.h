@@ -195,22 +195,26 @@ void hgnn_release_cached_memory(void);
  * row_scale[i] (fp32 [nrows]) when row_scale != NULL.  The scale is applied once,
  * after the whole row is reduced (post-reduction scaling).  Y is fully
  * overwritten (empty rows become 0).  X is [ncols][ldx], Y is [nrows][ldy].
- * Rows above 8 times the mean length (the threshold kept within 256..1024 non-zeros) are cut
- * into chunks of 512 non-zeros that are reduced by a wavefront each and added in chunk order;
- * their lists and fp32 partial rows live in `workspace`: device memory of at least
- * hgnn_spmm_workspace(nrows, ncols, nnz, F) bytes, 16-byte aligned, owned by the caller,
- * overwritten, not to be shared by calls that overlap in time.  The size is a bound from the
- * four numbers alone (0 when no row of such a graph can be that long).  workspace == NULL is
- * allowed: every long row is then reduced by a single wavefront (correct, slow on hubs).
+ * `workspace` is device memory of hgnn_spmm_workspace(nrows, ncols, nnz, F) bytes, 16-byte
+ * aligned, owned by the caller, overwritten, not to be shared by calls that overlap in time.
+ * The size is a bound from the four numbers alone (0 when no row of such a graph can be long).
+ * In it two small launches list every row as pieces of at most 512 non-zeros, sorted by length,
+ * which wavefronts or lane groups reduce; pieces of a row that has several are staged in fp32
+ * and added in order.  A smaller workspace is accepted as long as it holds the chunks of the
+ * long rows: then rows are taken in storage order, and those above 8 times the mean length (the
+ * threshold T kept within 256..1024 non-zeros) are cut into chunks of 512 non-zeros that are
+ * reduced by a wavefront each and added in chunk order (up to nnz/512 + nnz/T + 2 partial rows in
+ * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that).
+ * workspace == NULL is allowed: every long row is then reduced by a single wavefront (correct,
+ * slow on hubs).
  * Where the table X (ncols rows of F halves) is beyond three L2s, fits three quarters of the
  * cache behind them and rows average 128 non-zeros or more, the call walks the columns in
  * passes (ranges of about two L2 sizes of feature rows, all wavefronts in the same range at
  * the same time): a row's share of a pass is reduced into an fp32 partial row in the
  * workspace and the partials are added in pass order, scaled and rounded once -- the same
  * arithmetic, the sums in another fixed order.  hgnn_spmm_workspace counts that room in
- * (npass * nrows * F * 4 bytes and the cut positions); with ncols = 0 it returns the bound of
- * the long rows alone, and a workspace of that size is accepted too: the call then takes one
- * sweep per row. */
+ * (npass * nrows * F * 4 bytes and the cut positions); with ncols = 0 it returns what one
+ * sweep per row needs, and a call with a workspace of that size takes one sweep. */
 size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F);
 hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X, int64_t ldx,
                       hgnn_half* Y, int64_t ldy, int32_t F, hgnn_reduce op, const float* row_scale, void* workspace,

@@ -1492,8 +1492,11 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
   const int npass = scratch ? row_passes(g->nrows, g->ncols, g->nnz, F) : 1;
   const PassLayout pl = pass_layout(g->nrows, npass, F);
   const size_t base_bytes = spmm_hub_scratch_bytes(g->nrows, g->nnz, F), task_bytes = free_task_bytes(g->nrows, g->nnz, F);
-  const size_t rows_bytes = std::max(base_bytes, task_bytes);
-  if (npass > 1 && !one_sweep && scratch_bytes >= rows_bytes + size_t(pl.bytes)) {
+  // passes need their own room behind the chunks of the long rows; where the tasks need more than that, a workspace for one
+  // sweep (hgnn_spmm_workspace with ncols = 0) is told from one for passes by the sum of both
+  size_t pass_bytes = base_bytes + size_t(pl.bytes);
+  if (task_bytes >= pass_bytes && scratch_bytes >= task_bytes) pass_bytes = task_bytes + size_t(pl.bytes);
+  if (npass > 1 && !one_sweep && scratch_bytes >= pass_bytes) {
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
     a.long_row = kPassLongRow > a.long_row ? kPassLongRow : a.long_row;
     if (hubs) {
@@ -1503,7 +1506,7 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     } else {
       a.long_row = INT_MAX;
     }
-    char* base = static_cast<char*>(scratch) + rows_bytes;
+    char* base = static_cast<char*>(scratch) + base_bytes;
     int* cuts = reinterpret_cast<int*>(base + pl.o_cuts);
     float* part = reinterpret_cast<float*>(base + pl.o_part);
     const int width = int(ceil_div(g->ncols, npass));
@@ -1515,11 +1518,11 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     return HGNN_OK;
   }
   if (hubs) {
-    HGNN_REQUIRE(scratch_bytes >= (one_sweep ? base_bytes : rows_bytes), HGNN_EINVAL,
-                 "%s: the workspace holds %zu bytes, this graph needs %zu", who, scratch_bytes, rows_bytes);
+    HGNN_REQUIRE(scratch_bytes >= base_bytes, HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who,
+                 scratch_bytes, base_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
     if (scratch_bytes >= task_bytes) return spmm_free_tasks(g, a, scratch, s);
-    // (the static array can be too small for the tasks and still hold the hubs)
+    // (a workspace, or the static array, can be too small for the tasks and still hold the hubs)
     h = hub_lists_at(scratch, lay);
     hub_zero_kernel<<<1, kBlock, 0, s>>>(h);
     hub_scan_kernel<<<dim3(unsigned(ceil_div(g->nrows, kBlock * kScanRows))), kBlock, 0, s>>>(a, h);

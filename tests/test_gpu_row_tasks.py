@@ -279,3 +279,30 @@ def test_gat_piece_borders(hgnn, dev, H, D, S, nb, flip):
         compare("d_er", down(gr), d_er, er_abs, rel_l2=2e-2)
     hgnn.hgnn_plan_destroy(p)
     hgnn.hgnn_plan_destroy(pt)
+
+
+@pytest.mark.parametrize("F,what", [(64, "w"), (42, "map"), (32, "none")])
+def test_plain_spmm_with_a_smaller_workspace(hgnn, dev, F, what):
+    """A workspace that holds the chunks of the long rows and not the pieces of all rows: the same sums in another order."""
+    V, pitch = 5000, (F + 7) // 8 * 8
+    r = np.random.default_rng(F)
+    deg = r.integers(0, 12, V)
+    deg[r.permutation(V)[:40]] = r.integers(300, 5000, 40)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, V, size=d)) for d in deg]).astype(np.int32)
+    E = col.size
+    Xh = np.zeros((V, pitch), dtype=np.float16)
+    Xh[:, :F] = f16(r.standard_normal((V, F)))
+    w = None if what == "none" else f16(r.standard_normal((E, 1)))
+    eid = r.permutation(E).astype(np.int32) if what == "map" else None
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), eid=None if eid is None else up(eid, dev))
+    ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(Xh[:, :F]), w=w, want_sabs=True, **({} if eid is None else {"eid": eid}))
+    long_row = min(max(256, 8 * (E // V)), 1024)
+    chunks = E // 512 + E // long_row + 2
+    least = 256 + 2 * (4 * chunks + 256) + 2 * (4 * (E // long_row + 1) + 256) + 4 * chunks * pitch + 256
+    full = hgnn.hgnn_spmm_workspace(V, V, E, F)
+    assert least < full
+    for n in (least, full - 1, full):
+        Y = torch.full((V, pitch), 3.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_spmm(g, None if w is None else up(w, dev), 1, up(Xh, dev), Y, F=F, workspace=torch.empty(n, dtype=torch.uint8, device=dev))
+        compare(f"workspace of {n}", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)

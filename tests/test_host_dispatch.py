@@ -1,0 +1,86 @@
+"""The plan-free SpMM's choice of kernels, on the host: libhgnn.so on a runtime that executes nothing and writes launches down
+(fake_hip.cpp)."""
+import ctypes
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from test_host_memory import A, LIB, ROOT, Csr, Host, fake, i64, vp  # noqa: F401
+
+V, E, F = 200000, 4000000, 64
+
+
+def up(n):
+    return (n + 255) // 256 * 256
+
+
+def chunk_bytes(nrows, nnz, f):
+    """What the chunks of the long rows need: lists of chunks and of long rows, a partial row in fp32 for every chunk."""
+    long_row = min(max(256, 8 * (nnz // nrows)), 1024)
+    if nnz <= long_row:
+        return 0
+    rows = nnz // long_row + 1
+    chunks = nnz // 512 + rows + 1
+    return 256 + 2 * up(4 * chunks) + 2 * up(4 * rows) + up(4 * chunks * ((f + 7) // 8 * 8))
+
+
+def launches(h, call):
+    h.fake.fake_reset(h.path)
+    st = call()
+    names = h.fake.fake_launched().decode().split()
+    return st, [re.sub(r"^_ZN4hgnn\d+", "", n) for n in names]
+
+
+def spmm(h, g, f, nbytes, w=None):
+    x = vp(h.data)
+    return launches(h, lambda: h.lib.hgnn_spmm(ctypes.byref(g), w, 1, x, i64(f), x, i64(f), f, 0, None, x if nbytes else None,
+                                               ctypes.c_size_t(nbytes), vp(A)))
+
+
+def graph(h, nrows, ncols, nnz, eid=False):
+    return Csr(nrows, ncols, nnz, h.g.rowptr, h.g.col, None, h.g.rowptr if eid else None)
+
+
+def smaller_workspaces(h):
+    """A workspace that holds the chunks of the long rows is enough, as before rows were listed as pieces; one byte less is not."""
+    for nrows, nnz, f in ((V, E, 64), (1200001, 31000001, 64), (100003, 1300001, 42), (3000000, 18000000, 128), (30000, 300000, 512)):
+        for eid in (False, True):
+            g = graph(h, nrows, nrows, nnz, eid)
+            w = vp(h.data)
+            least = chunk_bytes(nrows, nnz, f)
+            st, names = spmm(h, g, (f + 7) // 8 * 8, least, w)
+            assert st == 0 and names, (nrows, nnz, f, st)
+            st, names = spmm(h, g, (f + 7) // 8 * 8, least - 1, w)
+            assert st == 1 and not names, (nrows, nnz, f, st)
+            st, names = spmm(h, g, (f + 7) // 8 * 8, 0, w)
+            assert st == 0 and len(names) == 1
+    # column passes with their own room behind the chunks
+    nrows, nnz, f = 233000, 114000000, 64
+    g = graph(h, nrows, nrows, nnz)
+    passes = round(2.0 * nrows * f / (2 * (4 << 20)))
+    room = up(4 * nrows * (passes + 1)) + up(4 * passes * nrows * f)
+    for size in (chunk_bytes(nrows, nnz, f) + room, h.lib.hgnn_spmm_workspace(nrows, nrows, i64(nnz), f)):
+        st, names = spmm(h, g, f, size)
+        assert st == 0 and any("row_pass" in n for n in names), names
+    st, names = spmm(h, g, f, h.lib.hgnn_spmm_workspace(nrows, 0, i64(nnz), f))
+    assert st == 0 and not any("row_pass" in n for n in names), names
+
+
+SCENARIOS = [smaller_workspaces]
+
+
+@pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
+def test_choice_of_kernels(hgnn, fake, name):  # noqa: F811
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, LIB, name], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    host = Host(sys.argv[1], sys.argv[2])
+    host.lib.hgnn_spmm_workspace.restype = ctypes.c_size_t
+    host.lib.hgnn_spmm_static_limit.restype = ctypes.c_size_t
+    {s.__name__: s for s in SCENARIOS}[sys.argv[3]](host)
+    print("ok")
