@@ -214,7 +214,8 @@ void hgnn_release_cached_memory(void);
  * workspace and the partials are added in pass order, scaled and rounded once -- the same
  * arithmetic, the sums in another fixed order.  hgnn_spmm_workspace counts that room in
  * (npass * nrows * F * 4 bytes and the cut positions); with ncols = 0 it returns what one
- * sweep per row needs, and a call with a workspace of that size takes one sweep. */
+ * sweep per row needs in the form that hgnn_spmm_static takes (the chunks where the pieces do not
+ * fit its array and the chunks do), and a call with a workspace of that size takes that. */
 size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F);
 hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X, int64_t ldx,
                       hgnn_half* Y, int64_t ldy, int32_t F, hgnn_reduce op, const float* row_scale, void* workspace,
@@ -222,9 +223,9 @@ hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, c
 
 /* hgnn_spmm for callers that cannot allocate and own no workspace: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as hgnn_spmm with a
- * workspace of hgnn_spmm_workspace(nrows, 0, nnz, F) bytes (one sweep per row, no column passes); the scratch of the long rows is a static device array of hgnn_spmm_static_limit() bytes
+ * workspace of hgnn_spmm_workspace(nrows, 0, nnz, F) bytes (one sweep per row, no column passes); the scratch is a static device array of hgnn_spmm_static_limit() bytes
  * (32 MiB) inside the library, held by every device the library runs on until the process ends.  A graph
- * whose bound for the long rows, hgnn_spmm_workspace(nrows, 0, nnz, F), exceeds that limit is refused with HGNN_EUNSUPPORTED
+ * for which hgnn_spmm_workspace(nrows, 0, nnz, F) exceeds that limit is refused with HGNN_EUNSUPPORTED
  * before anything is launched (use hgnn_spmm with a workspace).  Allocates nothing, asynchronous on
  * `stream`.  All calls on one device share the array: calls that overlap in time on one device (two
  * streams, two threads) race; order them on one stream. */

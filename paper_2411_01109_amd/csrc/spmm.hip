@@ -1548,7 +1548,10 @@ extern "C" {
 
 size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F) {
   if (nrows <= 0 || nnz <= 0 || F <= 0) return 0;
-  size_t need = std::max(spmm_hub_scratch_bytes(nrows, nnz, F), free_task_bytes(nrows, nnz, F));
+  const size_t base = spmm_hub_scratch_bytes(nrows, nnz, F), task = free_task_bytes(nrows, nnz, F), held = hgnn_spmm_static_limit();
+  // ncols = 0: what gives the results of hgnn_spmm_static, which takes the tasks only where its array holds them
+  if (ncols <= 0 && base <= held && task > held) return base;
+  size_t need = std::max(base, task);
   const int npass = ncols > 0 ? row_passes(nrows, ncols, nnz, F) : 1;
   if (npass > 1) need += size_t(pass_layout(nrows, npass, F).bytes);
   return need;

@@ -1,7 +1,7 @@
 // hgnn_spmm_static: the plan-free SpMM for callers that cannot allocate and have no workspace to hand over (code under
-// HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same kernels as hgnn_spmm; the scratch of
-// the hub kernels (chunk and hub lists, one fp32 partial row per 512-edge chunk of a long row) is a static device array
-// of kStaticScratchBytes instead of a caller's workspace.  Every device the library runs on holds its own copy of
+// HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same kernels as hgnn_spmm; the scratch (lists of
+// row tasks and their staged pieces, or of the hub kernels and their partial rows) is a static device array of
+// kStaticScratchBytes instead of a caller's workspace.  Every device the library runs on holds its own copy of
 // the array until the process ends.  All calls on one device share it: it keeps the previous call's contents (the
 // kernels reset the two counters they start from and overwrite what they read), and calls that overlap in time on one
 // device race.

@@ -69,7 +69,36 @@ def smaller_workspaces(h):
     assert st == 0 and not any("row_pass" in n for n in names), names
 
 
-SCENARIOS = [smaller_workspaces]
+def static_form(h):
+    """hgnn_spmm_static launches what hgnn_spmm does with hgnn_spmm_workspace(nrows, 0, nnz, F) bytes, and refuses what needs more
+    than its array: also where the pieces of all rows do not fit it and the chunks of the long rows do, and where passes would."""
+    limit = h.lib.hgnn_spmm_static_limit()
+    seen = set()
+    for nrows in (30, 1000, 30000, 300000, 1700000, 3000000):
+        for nnz in (200, 2000, 100000, 1500000, 8000000, 30000000, 90000000):
+            for f in (8, 40, 64, 128, 512):
+                for weighted, eid in ((False, False), (True, False), (True, True)):
+                    if f == 512 and (nrows > 100000 or nnz > 30000000):
+                        continue
+                    ld = (f + 7) // 8 * 8
+                    g = graph(h, nrows, 200000, nnz, eid)
+                    w, x = (vp(h.data) if weighted else None), vp(h.data)
+                    need = h.lib.hgnn_spmm_workspace(nrows, 0, i64(nnz), f)
+                    st, names = launches(h, lambda: h.lib.hgnn_spmm_static(ctypes.byref(g), w, 1, x, i64(ld), x, i64(ld), f, 0, None, vp(A)))
+                    assert (st == 0) == (need <= limit), (nrows, nnz, f, st, need)
+                    if st:
+                        assert st == 2 and not names
+                        seen.add("refused")
+                        continue
+                    st, same = spmm(h, g, ld, need, w)
+                    assert st == 0 and same == names, (nrows, nnz, f, weighted, eid, names, same)
+                    seen.add(names[0][:8])
+                    if need < h.lib.hgnn_spmm_workspace(nrows, 200000, i64(nnz), f):
+                        seen.add("smaller")
+    assert {"refused", "smaller", "task_cou", "hub_zero", "spmm_row"} <= seen, seen
+
+
+SCENARIOS = [smaller_workspaces, static_form]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])

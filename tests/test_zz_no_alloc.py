@@ -62,3 +62,33 @@ def test_static_scratch_rejects_what_does_not_fit(hgnn, dev):
     Y = torch.empty((50, 16), dtype=torch.float16, device=dev)
     hgnn.hgnn_spmm_static(g2, None, 1, up(Xh, dev), Y)
     compare("static, tiny graph", down(Y), *oracle.spmm(rowptr2, col2, Xh, want_sabs=True))
+
+
+@pytest.mark.parametrize("has_w,F", [(True, 64), (False, 64), (True, 8)])
+def test_static_scratch_too_small_for_the_pieces_of_all_rows(hgnn, dev, has_w, F):
+    """Many short rows: the lists of their pieces exceed the array, the chunks of the long rows do not.  The same bits as hgnn_spmm with
+    hgnn_spmm_workspace(nrows, 0, nnz, F) bytes, and the sums of the call with the full workspace."""
+    V, E = 2_000_003, 6_000_000
+    gen = torch.Generator(device=dev).manual_seed(F)
+    row = torch.randint(0, V, (E,), generator=gen, device=dev, dtype=torch.int32)
+    row[:5000] = 77
+    row[5000:5700] = V - 1
+    col = torch.randint(0, 3000, (E,), generator=gen, device=dev, dtype=torch.int32)
+    g = hgnn.hgnn_coo_to_csr(row, col, V, 3000, want_eid=False)[0]
+    X = torch.randn((3000, F), generator=gen, device=dev).half()
+    w = torch.randn((E, 1), generator=gen, device=dev).half() if has_w else None
+    need, full = hgnn.hgnn_spmm_workspace(V, 0, E, F), hgnn.hgnn_spmm_workspace(V, 3000, E, F)
+    assert need <= hgnn.hgnn_spmm_static_limit() < full
+    out = []
+    for n in (None, need, full):
+        Y = torch.full((V, F), 5.0, dtype=torch.float16, device=dev)
+        if n is None:
+            hgnn.hgnn_spmm_static(g, w, 1, X, Y)
+        else:
+            hgnn.hgnn_spmm(g, w, 1, X, Y, workspace=torch.empty(n, dtype=torch.uint8, device=dev))
+        out.append(Y)
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    # the same fp32 sums in another order: 2^-11 for each rounding, 2^-24 times the number of terms of the magnitude summed
+    mag = torch.empty_like(out[0])
+    hgnn.hgnn_spmm_static(g, None if w is None else w.abs(), 1, X.abs(), mag)
+    assert ((out[0].float() - out[2].float()).abs() <= 2.0 ** -10 * out[0].float().abs() + 2.0 ** -11 * mag.float() + 2.0 ** -24).all()
