@@ -201,7 +201,8 @@ void hgnn_release_cached_memory(void);
  * In it two small launches list every row as pieces of at most 512 non-zeros, sorted by length,
  * which wavefronts or lane groups reduce; pieces of a row that has several are staged in fp32
  * and added in order.  A smaller workspace is accepted as long as it holds the chunks of the
- * long rows: then rows are taken in storage order, and those above 8 times the mean length (the
+ * long rows: then, and for features narrower than 64 (32 with edge values) unless edge values are
+ * behind an edge-id map, rows are taken in storage order, and those above 8 times the mean length (the
  * threshold T kept within 256..1024 non-zeros) are cut into chunks of 512 non-zeros that are
  * reduced by a wavefront each and added in chunk order (up to nnz/512 + nnz/T + 2 partial rows in
  * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that).

@@ -1150,8 +1150,26 @@ static PassLayout pass_layout(int64_t nrows, int npass, int F) {
   return o;
 }
 
-// The plan-free SpMM over row tasks: what it needs of the scratch, 0 where no row can be long (then one wave per row does)
+// The plan-free SpMM over row tasks.  Against the kernels that take rows in storage order and hubs in chunks, tasks have lists to
+// write, and a wave reads its numbers from memory; they win where rows differ in length and a non-zero costs more than its
+// gather.  Behind a map tasks lose up to 27 % on uniform rows and win up to 1.9 times on skewed ones, at any width.  us, rows / tasks:
+//   non-zeros, rows         F   no edge values   edge values   behind a map
+//   1.3 M power law         8       41 / 38        47 / 41        70 / 52
+//                          64       44 / 38        61 / 39        83 / 45
+//   2 M uniform, 10 a row   8       30 / 39        33 / 46        56 / 71
+//                          32       42 / 44        47 / 47        71 / 66
+//                          64       51 / 55        59 / 56        82 / 72
+//   6 M, 200 a row         16       51 / 64        58 / 69        77 / 89
+//                          32       55 / 63        69 / 68        83 / 94
+//                          64       69 / 71       105 / 74       103 / 109
+//   18 M power law         16      263 / 295      301 / 301      598 / 603
+//                          64      372 / 349      509 / 373      825 / 669
+//   31 M power law         32      331 / 325      389 / 340      934 / 822
+//                          64      383 / 358      517 / 373     1023 / 855
+static bool free_tasks_pay(int F, bool edge_values, bool mapped) { return mapped || F >= (edge_values ? 32 : 64); }
+
 constexpr int kFreePiece = 512;  // non-zeros per piece
+// scratch of the tasks, 0 where no row can be long (then one wave per row does)
 static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
   if (hub_layout(nnz, hub_threshold(nrows, nnz), F).bytes == 0) return 0;
   return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F).bytes;
@@ -1444,7 +1462,7 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
 // The plan-free SpMM over row tasks that are listed in the scratch by two small launches: rows sorted by length and cut into
 // pieces, so that lane groups end together and a hub keeps many compute units busy, as with a plan.  Pieces are staged in
 // fp32, a row is rounded once.  A wave per G rows in storage order, hubs in chunks of their own, took as long as its longest
-// row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.79 -> 1.25 ms together.
+// row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.54 -> 1.23 ms together.
 static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, hipStream_t s) {
   const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
   const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz};
@@ -1521,7 +1539,8 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     HGNN_REQUIRE(scratch_bytes >= base_bytes, HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who,
                  scratch_bytes, base_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
-    if (scratch_bytes >= task_bytes) return spmm_free_tasks(g, a, scratch, s);
+    if (scratch_bytes >= task_bytes && free_tasks_pay(F, edge_val != nullptr, edge_val && g->eid))
+      return spmm_free_tasks(g, a, scratch, s);
     // (a workspace, or the static array, can be too small for the tasks and still hold the hubs)
     h = hub_lists_at(scratch, lay);
     hub_zero_kernel<<<1, kBlock, 0, s>>>(h);

@@ -98,7 +98,19 @@ def static_form(h):
     assert {"refused", "smaller", "task_cou", "hub_zero", "spmm_row"} <= seen, seen
 
 
-SCENARIOS = [smaller_workspaces, static_form]
+def narrow_features(h):
+    """Whatever the workspace, narrow features keep the kernels that take rows in storage order, unless values are behind a map."""
+    for nrows, nnz in ((100000, 1300000), (1200001, 31000001)):
+        for eid in (False, True):
+            g = graph(h, nrows, nrows, nnz, eid)
+            for f in (8, 24, 32, 56, 64, 128):
+                n = h.lib.hgnn_spmm_workspace(nrows, nrows, i64(nnz), f)
+                for w, least in ((None, 64), (vp(h.data), 8 if eid else 32)):
+                    st, names = spmm(h, g, f, n, w)
+                    assert st == 0 and any("task" in x for x in names) == (f >= least), (f, eid, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
