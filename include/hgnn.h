@@ -30,9 +30,14 @@
  *  - A plan owns scratch that the calls using it write (staging rows, per-vertex
  *    tables, per-block partial outputs): calls that use the same plan must be ordered
  *    on one stream, or otherwise not overlap in time; different plans are independent.
- *    The same holds for a workspace.  Host-side, the library keeps no mutable state
- *    except the thread-local error string and two per-device facts that are looked up once
- *    (the cache sizes, the address of the static scratch array of hgnn_spmm_static).
+ *    The same holds for a workspace.
+ *  - State that outlives a call, beside the plans: the thread-local error string; facts looked up
+ *    once per device (the cache sizes, the address of the static scratch array of hgnn_spmm_static,
+ *    which kernels may use more than 64 KB of LDS); and the device memory that set-up calls and
+ *    destroyed plans have freed, kept for the next set-up call (at most 512 MiB per device, blocks
+ *    of up to 256 MiB, with 64 small slots of pinned host memory).  Other allocators in the process
+ *    cannot claim that memory on their own out-of-memory path: hgnn_release_cached_memory() gives
+ *    it back, and so does the library when an allocation of its own fails.
  *  - Arithmetic: fp16 in memory, fp32 in registers, one round-to-nearest-even
  *    conversion when a value is stored.
  *  - Errors: every call returns an hgnn_status; argument errors are detected on
@@ -126,23 +131,28 @@ hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz, const int
  * gathering two bytes per non-zero.  Asynchronous on `stream`. */
 hgnn_status hgnn_edge_to_transposed(const hgnn_csr* gt, int32_t H, const hgnn_half* t, hgnn_half* t_T, void* stream);
 
-/* Segment plan for the discretized SpMM (section 5.2.1, observation rules 1-3):
- * the non-zeros are dealt out in storage order in segments of seg_edges edges,
- * segment k = [k*S, min(nnz,(k+1)*S)).  The plan holds, on the device: the row
- * of the first and last edge of every segment, the ascending list of "split"
- * rows (first and last edge in different segments) with the segments they
- * span, the list of rows longer than 2048 edges, the staging buffer for
- * conflicting partial sums (2 vectors of max_F halves per segment; the paper's
- * buffer is one vector per CTA, section 5.2.3) and per-vertex fp32 scratch of
- * 2*max_H floats per row/column for the factorised GAT score.
+/* Plan for the discretized SpMM and the edge kernels (section 5.2.1, observation rules 1-3).
+ * It holds, on the device:
+ *  - the row tasks: every row cut into pieces of at most seg_edges non-zeros; pieces of some length
+ *    take a wavefront each, shorter ones a lane group, sorted by length within windows of rows;
+ *    rows without non-zeros are listed on their own; a row of several pieces has a staging slot per
+ *    piece (twice max_F halves and 3 * max_H floats each; the paper's staging buffer is one vector
+ *    per CTA, section 5.2.3);
+ *  - the segments of seg_edges edges in storage order, segment k = [k*S, min(nnz,(k+1)*S)): the row
+ *    of the first and last edge of every segment, which the edge score walks, and the ascending
+ *    list of "split" rows (first and last edge in different segments) with the segments they span,
+ *    for hgnn_plan_export;
+ *  - the lists of rows longer than 32 and than 2048 edges, the latter in chunks, for the row-wise
+ *    edge kernels;
+ *  - per-vertex fp32 scratch of 2*max_H floats per row/column for the factorised GAT score.
  * The graph is validated first.  A plan may be used by one stream at a time.
  * seg_edges in [1, 2048]; max_F >= 8 multiple of 8; max_H >= 1.
  *
  * col_blocks: column blocking of hgnn_spmm_discretized.  1 = none.  n in [2, 64]:
- * the columns are cut into n equal ranges, the non-zeros of every range are
- * copied into a CSR of their own (a row's share of a range is a contiguous piece
- * of the row because columns ascend inside a row) with a segment plan each; the
- * SpMM then runs range after range, so that all compute units gather from one
+ * the columns are cut into n equal ranges, and a row's share of a range (a contiguous piece of the
+ * row because columns ascend inside a row) is a row of a block, with row tasks of its own; the
+ * column ids are kept block after block, in 16 bits where a range has at most 65536 columns.  The
+ * SpMM runs range after range, so that all compute units gather from one
  * slice of X at a time, into n partial outputs [n][nrows][max_F] fp16 that one
  * more pass adds per row.  Every partial still covers at most seg_edges edges and
  * is scaled before it is rounded (section 5.2.2).  0 = automatic: blocking is
@@ -150,11 +160,13 @@ hgnn_status hgnn_edge_to_transposed(const hgnn_csr* gt, int32_t H, const hgnn_ha
  * fits three quarters of the cache behind them (sizes read from the device) and rows
  * average 128 non-zeros or more; with blocks chosen this way a call whose own table
  * (ncols * ldx halves) is below that size runs unblocked (blocks asked for by number are
- * always used).  Costs nnz * 8 bytes plus the partial outputs.  A graph that is blocked by
- * the automatic rule is also kept in twice as many blocks: hgnn_spmm_discretized takes those
- * when it has edge values to read through an edge-id map (the scattered reads of the edge
- * tensor are a second table to keep in the L2s), hgnn_sddmm (dot) always (it leaves no
- * partial rows behind); the same cost once more.
+ * always used).  A graph that is blocked by the automatic rule is cut a second time, into twice
+ * as many blocks (hgnn_plan_col_blocks_fine): hgnn_spmm_discretized takes those when it has edge
+ * values to read through an edge-id map (the scattered reads of the edge tensor are a second table
+ * to keep in the L2s), hgnn_sddmm (dot) always (it leaves no partial rows behind), and where rows
+ * are long enough every call does: then only the finer cut is stored.
+ * Memory: a cut takes 2 or 4 bytes per non-zero (4 more behind an edge-id map), 8 per row and
+ * block, the tasks, and the partial outputs.
  * Edge tensors with a blocked plan: a call whose graph has no edge-id map reads them at the
  * graph's own CSR positions, whatever graph the plan was built from; a call whose graph has
  * an edge-id map reads them through the plan's blocked copy of the map, so the plan must
@@ -235,12 +247,11 @@ hgnn_status hgnn_spmm_static(const hgnn_csr* g, const hgnn_half* edge_val, int32
                              hgnn_half* Y, int64_t ldy, int32_t F, hgnn_reduce op, const float* row_scale, void* stream);
 
 /* Discretized-reduction SpMM, edge-parallel, no atomic writes (section 5.2):
- * same result as hgnn_spmm, but every wavefront reduces one segment of the plan,
- * each partial sum covers at most seg_edges edges and is scaled by s_i before it
- * is rounded to fp16 (discretized reduction scaling, section 5.2.2), rows inside
- * one segment are stored directly, partials of rows that cross a segment boundary
- * go to the plan's staging buffer and a follow-up kernel adds them in ascending
- * segment order and stores the row once (section 5.2.3).  Deterministic.
+ * same result as hgnn_spmm, but over the row tasks of the plan: a wavefront or a lane group
+ * reduces one piece of a row, each partial sum covers at most seg_edges edges and is scaled by
+ * s_i before it is rounded to fp16 (discretized reduction scaling, section 5.2.2), rows of one
+ * piece are stored directly, the pieces of longer rows go to the plan's staging buffer and a
+ * follow-up kernel adds them in order and stores the row once (section 5.2.3).  Deterministic.
  * Needs F <= 512, ld % 8 == 0, 16-byte aligned X and Y, D % 8 == 0 when edge values have
  * several heads, F <= plan max_F, and the plan of this graph. */
 hgnn_status hgnn_spmm_discretized(const hgnn_plan* p, const hgnn_csr* g, const hgnn_half* edge_val, int32_t H,
@@ -282,8 +293,8 @@ hgnn_status hgnn_spmm_discretized_fused(const hgnn_plan* p, const hgnn_csr* g, c
  * arguments, same result up to fp16 rounding order, always on the whole graph (a plan's
  * column blocks are not used).
  *  HGNN_EDGE_SEGMENTS          the library's own design, identical to hgnn_spmm_discretized.
- *  HGNN_EDGE_SEGMENTS_ATOMIC   same segment kernel, but the partials of a row that crosses a
- *      segment boundary are added to Y with packed fp16 atomic adds (rows concerned are zeroed
+ *  HGNN_EDGE_SEGMENTS_ATOMIC   same kernel, but the partials of a row of several pieces
+ *      are added to Y with packed fp16 atomic adds (rows concerned are zeroed
  *      first) instead of going through the staging buffer and the follow-up kernel; the order
  *      of those additions, hence the last bits of such rows, varies from run to run.
  *  HGNN_VERTEX_GROUPS          vertex-parallel: every row is cut into neighbour groups of at
@@ -400,9 +411,9 @@ hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_ha
  *   DOT:        sum_{d<D} U[i, h*D+d] * Vt[col[k], h*D+d],  i = row of k
  *   GAT_SCORE:  s = a_l[h].U[i,h,:] + a_r[h].Vt[col[k],h,:];  s > 0 ? s : neg_slope*s
  * U is [nrows][ldu], Vt is [ncols][ldv], a_l / a_r are [H*D] (GAT_SCORE only).
- * With a plan (p != NULL, the fast path) the kernels walk the plan's segments and
- * take row ids from rowptr; GAT_SCORE then projects every vertex once (fp32
- * scratch in the plan) and adds per edge.  Without a plan the row of a non-zero
+ * With a plan (p != NULL, the fast path) DOT walks the plan's row tasks (and column blocks);
+ * GAT_SCORE projects every vertex once (fp32 scratch in the plan) and adds per edge, over the
+ * plan's column slices or segments.  Without a plan the row of a non-zero
  * comes from g->row when given, else from a binary search in rowptr (slow).
  * g->eid must be NULL. */
 hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sddmm_op op, int32_t H, int32_t D,
@@ -415,9 +426,9 @@ hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sddmm_op op, 
  *   out[i, h*D+d] = sum_k alpha_k * Vt[col k, h*D+d],      lse[i,h] = log sum_k exp(e_k).
  * U [nrows][ldu] is the row side, Vt [ncols][ldv] the column side (the same table for a GAT
  * layer), a_l / a_r are [H*D], out is [nrows][ldo], lse is fp32 [nrows][H] or NULL.  Empty
- * rows give out = 0, lse = 0.  Walks the plan's segments (and column blocks); partial
- * results of a row are merged by rescaling to the larger maximum, pieces that cross a segment
- * border are staged as normalised fp16 vectors plus fp32 (max, sum) and merged by a follow-up
+ * rows give out = 0, lse = 0.  Walks the plan's row tasks (and column blocks); partial
+ * results of a row are merged by rescaling to the larger maximum, the pieces of a row that has
+ * several are staged as normalised fp16 vectors plus fp32 (max, sum) and merged by a follow-up
  * kernel: no atomics, deterministic.  Needs a plan with max_H >= H and max_F >= H*D,
  * D = 8 * 2^k, H*D <= 512, ld % 8 == 0 and 16-byte aligned tensors; g without edge-id map.
  * Overwrites the plan's per-vertex scratch (as hgnn_sddmm GAT_SCORE does). */

@@ -42,13 +42,11 @@ void clear_error();
       return ::hgnn::fail(HGNN_EHIP, "launch of %s: %s", name, hipGetErrorString(err__)); \
   } while (0)
 
-// Waves per workgroup for a kernel whose waves work independently on private LDS regions of per_wave bytes
-// (no workgroup barrier anywhere, so the choice is free).  Measured on MI355X: kernels that stage per-edge
-// values or scores before their main loop (a dependent chain of global loads whose length varies from wave to
-// wave) run 5-15 % faster as single-wave workgroups -- a workgroup's LDS and wave slots are only released
-// when its last wave ends, and small allocations pack the 160 KB of LDS better -- while the plain
-// unweighted segment kernel runs 4 % faster in workgroups of four (fewer dispatches, waves of consecutive
-// segments start together).  independent_waves selects the former; either way the workgroup must fit 64 KB.
+// Waves per workgroup for the kernel over neighbour groups, whose waves work independently on private LDS regions of per_wave
+// bytes (no workgroup barrier anywhere, so the choice is free).  Where waves stage edge values before their main loop (a
+// dependent chain of global loads whose length varies from wave to wave) single-wave workgroups are 5-15 % faster: a
+// workgroup's LDS and wave slots are only released when its last wave ends.  Without edge values workgroups of four were 4 %
+// faster (fewer dispatches, waves of consecutive groups start together).  Either way the workgroup must fit 64 KB.
 inline int waves_per_block_for_lds(size_t per_wave, bool independent_waves) {
   int w = independent_waves ? 1 : 4;
   while (w > 1 && per_wave * size_t(w) > 65536) w >>= 1;
@@ -151,9 +149,8 @@ typedef uint32_t pos_t;
 __host__ __device__ inline int pieces_of(int len, int per) { return int((pos_t(len) + pos_t(per) - 1u) / pos_t(per)); }
 
 // Orders the LDS accesses of one wave: what its lanes wrote before is visible to all its lanes after.
-// The kernels that stage a segment give every wave a private LDS region, so nothing wider than the
-// wave has to meet; a workgroup barrier there would only put the four waves in lock step and stall
-// three of them whenever one waits for memory.
+// Waves that have an LDS region of their own meet nobody else; a workgroup barrier there would only put the waves of a workgroup
+// in lock step and stall the others whenever one waits for memory.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -185,15 +182,15 @@ __device__ __forceinline__ float head_sum1(float v, int LH) {
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 
-// ---- per-edge row ids of one plan segment, staged in LDS by one wave ---------------------------------
+// ---- per-edge row ids of one plan segment, staged in LDS by one wave (edge_score_seg_kernel) ----------
 // A segment of n <= S consecutive edges starting at e0 touches the rows row_lo..row_hi (plan arrays).
 // Every non-empty row after row_lo marks the slot of its first edge, then a wave-wide running
 // maximum spreads the ids: s_row[i] = row of edge e0+i for i < n, -2 for the padding up to
 // 64*per slots; s_blk[i/4] = common row id of the aligned group of four edges, or -1 when they
 // differ or touch the padding.  Lane t owns the slots [t*per, (t+1)*per); per is a multiple of 4.
-// s_row / s_blk are private to the calling wave, so wave-level ordering is enough; BLOCK_SYNC = true uses
-// workgroup barriers instead (every wave of the workgroup must then call it, n = 0 without a segment),
-// which keeps the four waves of a streaming kernel in step on consecutive segments.
+// s_row / s_blk are private to the calling wave; BLOCK_SYNC = true uses workgroup barriers all the same (every wave of the
+// workgroup must then call it, n = 0 without a segment), which keeps the four waves of a streaming kernel in step on consecutive
+// segments.
 __device__ __forceinline__ int seg_slots_per_lane(int S) { return 4 * ((S + 255) / 256); }
 
 // The index arrays (column ids, edge ids) are read once per pass.  On graphs whose arrays are far larger than the

@@ -1,7 +1,7 @@
 // Single-pass GAT aggregation for gfx950: score, edge softmax and weighted sum of the neighbours'
 // features in one read of the graph, with no per-edge tensor written (the paper, sections 3.1.2 and
 // 5.2, keeps them as three kernels with an |E| x H score tensor and an |E| x H alpha tensor between
-// them; this fuses them on top of the same discretized, atomic-free segment design).
+// them; this fuses them on top of the same discretized, atomic-free design).
 //
 //   s_k = el[i,h] + er[col k,h],  e_k = LeakyReLU(s_k),  alpha_k = softmax over row i (Eq. 1),
 //   out[i, h*D+d] = sum_k alpha_k * X[col k, h*D+d],    lse[i,h] = log sum_k exp(e_k)
@@ -11,8 +11,8 @@
 // A partial result over any subset of a row's edges is kept as a triple (m, z, acc): m = largest
 // score met, z = sum exp(e - m), acc = sum exp(e - m) * x.  Two triples of the same row merge by
 // rescaling both to the larger m (the online form of Eq. 1's shift by the row maximum), so the
-// segment kernel can cut rows anywhere: lane groups carry a running triple along their chunk,
-// pieces that touch a chunk border meet in LDS, pieces that cross a segment border are staged as
+// row tasks can cut rows anywhere: a lane group carries a running triple along its piece, the groups
+// of a wave that share a long piece merge theirs across lanes, and the pieces of a row that has several are staged as
 // (m, z) in fp32 plus the normalised vector acc/z in fp16 -- a convex combination of feature rows,
 // hence never larger than the features themselves (the discretized-scaling idea of section 5.2.2
 // applied to the softmax weights) -- and a follow-up kernel merges them.  No atomics, one writer per
@@ -188,14 +188,15 @@ __device__ __forceinline__ void soft_add(Soft<SAVE>& t, const float (&p)[8 / RS]
   }
 }
 
-// Segment pass over row tasks (see spmm_task_kernel for how a wave is laid out).  The row-side term el[row] is constant in a
+// Pass over row tasks (see spmm_task_kernel for how a wave is laid out).  The row-side term el[row] is constant in a
 // lane group; the column-side term a_r.X[col] is formed from the gathered row itself (four two-way dot products per lane).
 // RS = min(lanes per head, 8).
 //
-// Bound: vector instructions, then the gathers.  The walk over equal runs of edges spent about 45 instructions per edge and
-// lane (every lane of a head repeated maximum, exponential and masks, two sums were rescaled every four edges, and most
-// steps had a row change in some lane group); this one about 27 with SAVE, 19 without.  5.5 M edges, 4 heads of 16,
-// SAVE: 169 -> 109 us; 114 M edges, one head of 64: 2.12 -> 1.06 ms; 108 k edges, eight heads of 8: 26 -> 7.5 us.
+// Bound: vector instructions (they are busy 93 % of the cycles with SAVE, 79-84 % without), then the gathers.  The walk over equal
+// runs of edges repeated maximum, exponential and masks on every lane of a head, rescaled two sums every four edges, and most steps had
+// a row change in some lane group; here a wave spends 10 vector instructions per edge with SAVE, 7 without (5.5 M edges, 4 heads of
+// 16).  A call against that walk: 5.5 M edges, 4 heads of 16, SAVE 181 -> 106 us, without 125 -> 83; 114 M edges, one head of
+// 64 in eight blocks 2.16 -> 1.08 ms, 1.48 -> 0.88 ms.
 template <int L, bool NEAR, bool SAVE, int RS>
 __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(GatArgs a, TaskView v, int ncols) {
 #pragma clang fp contract(off)

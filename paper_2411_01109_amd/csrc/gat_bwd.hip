@@ -79,8 +79,9 @@ __device__ __forceinline__ void bwd_stage_store(const GatBwdArgs& a, int64_t slo
 // (r = the row-side vector, m = the LeakyReLU slope of the edge), so the loop only accumulates the mask-weighted vector
 // wacc beside acc and one scalar; the dot product with r happens once per piece.
 //
-// Bound: the L2s' requests (two per non-zero: the vector, the packed scalars) and the products.  5.5 M non-zeros, 4 heads of
-// 16: 131 -> 107 us against the walk over equal runs; 114 M, one head of 64: 1.65 -> 1.29 ms.
+// Bound: the L2s' requests (two per non-zero: the vector, the packed scalars; 56 % of them hit at 5.5 M non-zeros, 92 % at 114 M in
+// blocks) and the vector instructions (busy 69 % and 52 % of the cycles).  The saved backward call against the walk over equal
+// runs: 5.5 M non-zeros, 4 heads of 16 166 -> 131 us; 114 M, one head of 64 1.70 -> 1.26 ms.
 template <int L, bool NEAR, bool VEC, int RS>
 __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task_kernel(GatBwdArgs a, TaskView v, int ncols) {
   constexpr int G = kWave / L;

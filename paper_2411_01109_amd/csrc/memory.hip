@@ -3,11 +3,12 @@
 // hipMalloc and hipFree cost tens to hundreds of microseconds each (a free waits for the device and unmaps), and setting a
 // graph up takes some forty of each: 4.5 of the 6.1 ms that a 5.5 M-edge list took to become a graph, its transpose and
 // two plans.  Freed blocks are therefore kept for the next set-up call:
-//  - at most kKeepBytes per device, blocks of up to half of that; what no set-up call has asked for during the last
+//  - at most kKeepBytes per device, blocks of up to half of that (so the sort buffers of graphs beyond some 33 M edges, 8 bytes an
+//    edge, are allocated and freed on every call); what no set-up call has asked for during the last
 //    kKeepCalls allocations is freed, everything when an allocation fails or on hgnn_release_cached_memory();
 //  - callers free a block only when no work that uses it is in flight on any stream (set-up calls synchronize their
-//    stream first; hgnn_plan_destroy, and calls that replace arrays of a plan, wait for the plan's device), so a kept block may be handed to any stream or thread at once; a block
-//    for which the wait failed goes back to the runtime instead;
+//    stream first; hgnn_plan_destroy, and calls that replace arrays of a plan, wait for the plan's device), so a kept block may
+//    be handed to any stream or thread at once; a block for which the wait failed goes back to the runtime instead;
 //  - one mutex; blocks belong to the device that was current when they were allocated.
 #include <mutex>
 #include <unordered_map>

@@ -1,4 +1,4 @@
-// Status strings, graph validation and the segment plan of the discretized SpMM
+// Status strings, graph validation and the plan of the discretized SpMM
 // (paper section 5.2.1: edges are dealt out in storage order in fixed-size batches,
 // observation rules 1-3).  Integer work only; everything here is one-off set-up.
 #include <stdarg.h>

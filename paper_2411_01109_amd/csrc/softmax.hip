@@ -387,8 +387,8 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
 }
 
 // Every row of the graph in one launch: the wave-per-row tier (wave_wgs workgroups), then the sub-wave teams, and the chunks of
-// the long rows (n_chunks workgroups) after or before them.  As launches of their own each has a tail in which the chip drains: 5.5 M non-zeros x 4
-// heads, forward with its follow-up 70 -> 57 us, backward 61 -> 45, sums 32 -> 22.5.  The softmax takes the chunks last because
+// the long rows (n_chunks workgroups) after or before them.  As launches of their own each has a tail in which the chip drains:
+// 5.5 M non-zeros x 4 heads, forward with its follow-up 71 -> 57 us, backward 61 -> 45, sums 32 -> 22.  The softmax takes the chunks last because
 // its follow-up reads them again while the caches still hold them (114 M non-zeros, one head: forward 189 us with the chunks
 // first, 184 last, 179 in launches of their own; backward 210, 201, 207); the sums take them first (23.3 us last).
 template <int OP, int LR, int H>

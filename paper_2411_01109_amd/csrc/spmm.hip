@@ -533,9 +533,10 @@ __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t fir
 // exactly one writer.
 //
 // Bound: the gathers, 64 bytes per clock and compute unit while the table sits in the L2s, the traffic behind the L2s
-// beyond that.  Against the walk over equal runs of non-zeros with row ids in LDS (which held 7 waves per SIMD and spent 2-3
-// times the vector instructions): R-MAT 5.5 M non-zeros x 64, weighted 88 -> 50 us; 2.1 M x 128 58 -> 42 us; a 36 k graph 17.8 ->
-// 8 us; 114 M non-zeros x 64 in blocks of 3.7 MB 1.05 -> 0.80 ms (18 TB/s of rows).
+// beyond that (62 M non-zeros x 128: 12 GB of L2 misses per call at 7.3 TB/s, vector instructions busy 27 % of the cycles).  A call
+// against the walk over equal runs of non-zeros with row ids in LDS: R-MAT 5.5 M non-zeros x 64, four heads of edge values 88 -> 59
+// us, behind a map 131 -> 123; 2.1 M x 128 with the GIN terms 62 -> 43 us; 37 k x 64 19 -> 6 us; 114 M non-zeros x 64 in blocks of
+// 3.7 MB 1.09 -> 0.83 ms (18 TB/s of rows); 62 M x 128 the same (by degrees 1.87 ms, edge values 1.73), through a map 2 % slower.
 // WM: 0 = no factor per non-zero, 1 = edge values, 2 = edge values (if any) times a column scale.  MAPPED: edge values
 // behind an edge-id map.
 // ---------------------------------------------------------------------------------------------------
@@ -1152,7 +1153,7 @@ static PassLayout pass_layout(int64_t nrows, int npass, int F) {
 
 // The plan-free SpMM over row tasks.  Against the kernels that take rows in storage order and hubs in chunks, tasks have lists to
 // write, and a wave reads its numbers from memory; they win where rows differ in length and a non-zero costs more than its
-// gather.  Behind a map tasks lose up to 27 % on uniform rows and win up to 1.9 times on skewed ones, at any width.  us, rows / tasks:
+// gather.  Behind a map they cost up to 27 % more on uniform rows and 46 % less on skewed ones.  us, rows / tasks:
 //   non-zeros, rows         F   no edge values   edge values   behind a map
 //   1.3 M power law         8       41 / 38        47 / 41        70 / 52
 //                          64       44 / 38        61 / 39        83 / 45

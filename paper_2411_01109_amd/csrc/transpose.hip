@@ -167,7 +167,8 @@ __global__ void edge_gather_kernel(const int* __restrict__ eid, int64_t total, i
 // once however many bits it takes (43 us for 5.5 M words), so digits of nine bits where they save a pass over digits of
 // eight: 36 bits in four passes instead of five, 18 in two instead of three (5.5 M edges: list to CSR 330 -> 280 us,
 // transpose 235 -> 183).
-// Below 200 000 words a sort by merging is faster (list to CSR, 0.13 M: 93 us against 125 with digits; 0.4 M: 163 against 133).
+// Below 200 000 words a sort by merging is faster where a list takes four passes (us, merging / digits: list to CSR 0.05 M 88 / 121,
+// 0.13 M 102 / 125, 0.2 M 114 / 129, 0.4 M 167 / 136; transpose, two passes, 82 / 92, 101 / 90, 109 / 89, 165 / 95).
 static hipError_t sort_words(void* tmp, size_t& tmp_bytes, rocprim::double_buffer<uint64_t>& keys, unsigned n, unsigned first,
                              unsigned last, hipStream_t s) {
   using rocprim::default_config;
