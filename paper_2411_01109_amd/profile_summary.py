@@ -7,10 +7,11 @@ rocprofv3 run of `python3 bench.py --workload W --steps N --warmup 1 --no-cpu-ba
   D/prof_W_trace/W_kernel_stats.csv          --kernel-trace --stats
   D/prof_W_fetch/W_counter_collection.csv    --pmc FETCH_SIZE
   D/prof_W_write/W_counter_collection.csv    --pmc WRITE_SIZE
-  D/prof_W_cache/W_counter_collection.csv    --pmc TCC_HIT_sum TCC_MISS_sum TCC_REQ_sum TCC_EA0_RDREQ_DRAM_sum SQ_WAVES
-                                                   SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT
-                                                   SQ_ACTIVE_INST_LDS SQ_BUSY_CYCLES SQ_WAVE_CYCLES TCP_TCC_READ_REQ_sum
-                                                   TCP_TOTAL_CACHE_ACCESSES_sum TCP_TCC_WRITE_REQ_sum GRBM_GUI_ACTIVE   (optional)
+  D/prof_W_cache/W_counter_collection.csv    --pmc TCC_HIT_sum TCC_MISS_sum TCC_REQ_sum SQ_WAVES SQ_INSTS_VMEM_RD
+                                                   SQ_INSTS_VMEM_WR SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS
+                                                   TCP_TCC_READ_REQ_sum TCP_TOTAL_CACHE_ACCESSES_sum                    (optional)
+  D/prof_W_issue/W_counter_collection.csv    --pmc SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_VMEM SQ_INSTS_VALU
+                                                   SQ_WAVE_CYCLES SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE                      (optional)
   D/prof_W_ea/W_counter_collection.csv       --pmc TCC_EA0_RDREQ_sum TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_DRAM_32B_sum
                                                    TCC_EA0_WRREQ_WRITE_DRAM_32B_sum                                      (optional)
 
@@ -26,9 +27,8 @@ import os
 import re
 import sys
 
-SETUP_KERNELS = ("validate", "expand", "iota", "source_rows", "offsets", "seg_rows", "compact", "scan_counts", "split_segs",
-                 "block_fill", "block_cuts", "block_delta", "block_counts", "block_rowptr", "hub_zero", "group_", "coo_",
-                 "list_length")
+SETUP_KERNELS = ("validate", "source_rows", "offsets", "seg_rows", "row_lists", "block_fill", "block_cuts", "block_delta",
+                 "block_counts", "block_rowptr", "hub_zero", "group_", "coo_", "transpose_", "slice_cuts", "chunk_rows")
 COPY = "__amd_rocclr_copyBuffer"
 GIB_KIB = 1048576.0
 
@@ -80,6 +80,7 @@ def main(argv):
     fetch = read_counters(os.path.join(base("fetch"), f"{W}_counter_collection.csv"))
     write = read_counters(os.path.join(base("write"), f"{W}_counter_collection.csv"))
     cache = read_counters(os.path.join(base("cache"), f"{W}_counter_collection.csv"))
+    issue = read_counters(os.path.join(base("issue"), f"{W}_counter_collection.csv"))
     ea = read_counters(os.path.join(base("ea"), f"{W}_counter_collection.csv"))
     fetch = fetch["FETCH_SIZE"] if fetch and "FETCH_SIZE" in fetch else next(iter(fetch.values()))
     write = write["WRITE_SIZE"] if write and "WRITE_SIZE" in write else next(iter(write.values()))
@@ -94,6 +95,8 @@ def main(argv):
          f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d $R/gpurun_out/prof_{W}_write -o {W} -- " + bench_cmd.format(n=2)]
     if cache:
         L.append(f"rocprofv3 --pmc {' '.join(sorted(cache))} --output-format csv -d $R/gpurun_out/prof_{W}_cache -o {W} -- " + bench_cmd.format(n=2))
+    if issue:
+        L.append(f"rocprofv3 --pmc {' '.join(sorted(issue))} --output-format csv -d $R/gpurun_out/prof_{W}_issue -o {W} -- " + bench_cmd.format(n=2))
     if ea:
         L.append(f"rocprofv3 --pmc {' '.join(sorted(ea))} --output-format csv -d $R/gpurun_out/prof_{W}_ea -o {W} -- " + bench_cmd.format(n=2))
     L.append("```\n")
@@ -164,7 +167,7 @@ def main(argv):
         L.append("\n## Cache and wave counters per launch\n")
         L.append("L2 hit rate = TCC_HIT / (TCC_HIT + TCC_MISS); L1->L2 read requests = TCP_TCC_READ_REQ (per non-zero where the kernel "
                  "walks the graph's E edges once, E taken from the workload); L1 hit rate = 1 - TCP_TCC_READ_REQ / "
-                 "TCP_TOTAL_CACHE_ACCESSES; LDS conflict share = SQ_LDS_BANK_CONFLICT / SQ_ACTIVE_INST_LDS (cycles).\n")
+                 "TCP_TOTAL_CACHE_ACCESSES; LDS conflict share = SQ_LDS_BANK_CONFLICT / (4 x SQ_ACTIVE_INST_LDS), the latter in units of 4 cycles.\n")
         L.append("| kernel | launches | L2 requests (M) | L2 hit rate | L1->L2 read req (M) | per non-zero | L1 accesses (M) | waves | "
                  "VMEM rd / wr instr (M) | LDS instr (M) | LDS conflict share |")
         L.append("|---|---:|---:|---:|---:|---:|---:|---:|---:|---:|---:|")
@@ -178,9 +181,27 @@ def main(argv):
             la, lc = mean(lact.get(k, [0.0])), mean(conf.get(k, [0.0]))
             L.append(f"| `{k}` | {len(v)} | {mean(v) / 1e6:.1f} | {hr:.3f} | {rd / 1e6:.1f} | {per_e} | {mean(t_acc.get(k, [0.0])) / 1e6:.1f} | "
                      f"{mean(waves.get(k, [0.0])):.0f} | {mean(vrd.get(k, [0.0])) / 1e6:.2f} / {mean(vwr.get(k, [0.0])) / 1e6:.2f} | "
-                     f"{mean(lds.get(k, [0.0])) / 1e6:.2f} | {lc / la if la > 0 else 0.0:.3f} |")
+                     f"{mean(lds.get(k, [0.0])) / 1e6:.2f} | {lc / (4 * la) if la > 0 else 0.0:.3f} |")
             if k in db:
                 db[k].update({"l2_hit_rate": round(hr, 4), "l1_to_l2_read_requests": round(rd), "waves": round(mean(waves.get(k, [0.0])))})
+    if issue:
+        gui, wc = issue.get("GRBM_GUI_ACTIVE", {}), issue.get("SQ_WAVE_CYCLES", {})
+        valu, vmem = issue.get("SQ_ACTIVE_INST_VALU", {}), issue.get("SQ_ACTIVE_INST_VMEM", {})
+        nvalu, wait = issue.get("SQ_INSTS_VALU", {}), issue.get("SQ_WAIT_INST_ANY", {})
+        L.append("\n## Issue and occupancy per launch\n")
+        L.append("Cycles = GRBM_GUI_ACTIVE / 8 (the counter adds the 8 XCDs); the SQ counters count in units of 4 cycles: VALU busy = "
+                 "SQ_ACTIVE_INST_VALU / (256 compute units x cycles), vector-memory issue the same with SQ_ACTIVE_INST_VMEM, waves "
+                 "per compute unit = 4 x SQ_WAVE_CYCLES / (256 x cycles), waiting to issue = SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES.\n")
+        L.append("| kernel | launches | cycles (k) | VALU busy | vector-memory issue | VALU instr (M) | waves per CU | waiting to issue |")
+        L.append("|---|---:|---:|---:|---:|---:|---:|---:|")
+        for k, v in sorted(gui.items(), key=lambda kv: -mean(kv[1])):
+            cyc = mean(v) / 8.0
+            if not is_compute(k) or not cyc:
+                continue
+            w = mean(wc.get(k, [0.0]))
+            L.append(f"| `{k}` | {len(v)} | {cyc / 1e3:.1f} | {mean(valu.get(k, [0.0])) / (256 * cyc):.3f} | "
+                     f"{mean(vmem.get(k, [0.0])) / (256 * cyc):.3f} | {mean(nvalu.get(k, [0.0])) / 1e6:.2f} | {4 * w / (256 * cyc):.1f} | "
+                     f"{mean(wait.get(k, [0.0])) / w if w else 0.0:.3f} |")
     with open(out, "w") as fh:
         fh.write("\n".join(L) + "\n")
     try:
