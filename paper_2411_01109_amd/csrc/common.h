@@ -193,10 +193,12 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 // segments.
 __device__ __forceinline__ int seg_slots_per_lane(int S) { return 4 * ((S + 255) / 256); }
 
-// The index arrays (column ids, edge ids) are read once per pass.  On graphs whose arrays are far larger than the
-// caches a non-temporal load keeps them from displacing the feature rows that the gathers reuse (config 5: 1-2 %
-// on every segment kernel, config 4 up to 3 %); on graphs that fit the Infinity Cache it would push the arrays out
-// between kernels (config 3: the next kernel's reads of the column ids 15 % slower), hence the size rule.
+// The index arrays (column ids, edge ids) are read once per pass.  Where they are far larger than the caches, passes through an
+// edge-id map, which gather from two tables, read them with non-temporal loads so that they displace fewer of the lines that
+// the gathers want again.  SpMM through the map, without / with the hint: 31 M non-zeros x 1 head 821 / 808 us, x 4 heads 857 /
+// 847, 60 M x 16 features 1681 / 1667, 62 M x 128 2681 / 2655; over column blocks, where a wave returns to the lines of the map that
+// its neighbours have read, it costs: 114 M 1620 / 1668.  Passes without a map gain nothing (SpMM 0 to 0.9 %, SDDMM 0, attention
+// forward 1 to 2.6 % slower), and where the arrays fit the last-level cache the hint would push them out between kernels.
 __host__ __device__ inline bool stream_nontemporal(int64_t nnz) { return nnz * 4 > (int64_t(64) << 20); }
 
 __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {

@@ -585,7 +585,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   int shift = 0;  // slot in the edge tensors = position + shift
   if (WM != 0 && !MAPPED && a.delta) shift = a.delta[int64_t(w.block) * a.nrows + row] - w.first;
   const int own = (lane & (Rd::LC - 1)) * E;
-  const bool nt = MAPPED && stream_nontemporal(a.nnz);
+  const bool nt = MAPPED && v.nb == 1 && stream_nontemporal(a.nnz);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (pos_t k = w.beg; k < w.end; k += w.step) {
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
