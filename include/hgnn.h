@@ -217,7 +217,8 @@ void hgnn_release_cached_memory(void);
  * behind an edge-id map, rows are taken in storage order, and those above 8 times the mean length (the
  * threshold T kept within 256..1024 non-zeros) are cut into chunks of 512 non-zeros that are
  * reduced by a wavefront each and added in chunk order (up to nnz/512 + nnz/T + 2 partial rows in
- * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that).
+ * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that, and for sizes
+ * that miss the query's answer by 512 bytes or less).
  * workspace == NULL is allowed: every long row is then reduced by a single wavefront (correct,
  * slow on hubs).
  * Where the table X (ncols rows of F halves) is beyond three L2s, fits three quarters of the

@@ -1170,6 +1170,7 @@ static PassLayout pass_layout(int64_t nrows, int npass, int F) {
 static bool free_tasks_pay(int F, bool edge_values, bool mapped) { return mapped || F >= (edge_values ? 32 : 64); }
 
 constexpr int kFreePiece = 512;  // non-zeros per piece
+constexpr size_t kNearMiss = 512;
 // scratch of the tasks, 0 where no row can be long (then one wave per row does)
 static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
   if (hub_layout(nnz, hub_threshold(nrows, nnz), F).bytes == 0) return 0;
@@ -1539,6 +1540,9 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
   if (hubs) {
     HGNN_REQUIRE(scratch_bytes >= base_bytes, HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who,
                  scratch_bytes, base_bytes);
+    // (a size that misses the query's answer by a few bytes is a mistake, not a workspace for the chunks alone)
+    HGNN_REQUIRE(one_sweep || scratch_bytes >= task_bytes || scratch_bytes == base_bytes || task_bytes - scratch_bytes > kNearMiss,
+                 HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who, scratch_bytes, task_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
     if (scratch_bytes >= task_bytes && free_tasks_pay(F, edge_val != nullptr, edge_val && g->eid))
       return spmm_free_tasks(g, a, scratch, s);

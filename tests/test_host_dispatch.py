@@ -57,6 +57,10 @@ def smaller_workspaces(h):
             assert st == 1 and not names, (nrows, nnz, f, st)
             st, names = spmm(h, g, (f + 7) // 8 * 8, 0, w)
             assert st == 0 and len(names) == 1
+            full = h.lib.hgnn_spmm_workspace(nrows, 0, i64(nnz), f)  # a few bytes less than named: refused, unless those are the chunks'
+            for short in (1, 256, 512):
+                st, names = spmm(h, g, (f + 7) // 8 * 8, full - short, w)
+                assert st == (0 if full - short == least else 1), (nrows, nnz, f, short)
     # column passes with their own room behind the chunks
     nrows, nnz, f = 233000, 114000000, 64
     g = graph(h, nrows, nrows, nnz)
