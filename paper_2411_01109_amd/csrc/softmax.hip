@@ -642,14 +642,14 @@ __global__ __launch_bounds__(kWave) void rowsum_task_kernel(RowsumArgs a, TaskVi
   pos_t k = w.beg + l * E;
   pos_t end = w.beg + w.span < w.end ? w.beg + w.span : w.end;
   int id[E];
-  load_run<E, true>(a.eid, k, int(end - k), id);  // positions past the end hold slot 0: read, not added
+  load_run<E, true>(a.eid, k, RunLeft{int(end - k)}, id);  // positions past the end hold slot 0: read, not added
   for (pos_t base = w.beg; base < w.end; base += w.step) {
     hv_t x[E];
 #pragma unroll
     for (int m = 0; m < E; ++m) x[m] = *reinterpret_cast<const hv_t*>(a.t + int64_t(id[m]) * H);
     const pos_t kn = k + w.step, past = base + w.step + w.span;
     const pos_t endn = past < w.end ? past : w.end;
-    load_run<E, true>(a.eid, kn, int(endn - kn), id);
+    load_run<E, true>(a.eid, kn, RunLeft{int(endn - kn)}, id);
     const int left = int(end - k);
 #pragma unroll
     for (int m = 0; m < E; ++m)

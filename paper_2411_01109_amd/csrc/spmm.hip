@@ -552,6 +552,15 @@ struct TaskLds {
   static size_t bytes(int H) { return size_t(kHandles) + (WM == 0 ? 0 : size_t(G) * size_t(pitch(H)) * sizeof(factor_t)); }
 };
 
+// Which form the walk takes: what is left is cheaper where a run is asked of several arrays, positions where it is the ids alone (by
+// position / by what is left, us: 5.5 M non-zeros x 4 heads of edge values 60.9 / 59.0; a GIN layer without edge values, 42 M x 16
+// features, whose ids come from HBM, 463 / 480).
+template <bool BY_POSITION>
+__device__ __forceinline__ auto run_of(pos_t i0, pos_t end, int left) {
+  if constexpr (BY_POSITION) return RunEnd{i0, end};
+  else return RunLeft{left};
+}
+
 template <int L, int WM, bool NEAR, bool MAPPED, int HV>
 __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, int wid) {
   constexpr int G = kWave / L;
@@ -591,25 +600,25 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
     const pos_t end = k + w.span < w.end ? k + w.span : w.end;
     const int n = int(end - k);
     const pos_t i0 = k + own;
-    const int left = n - own;  // entries of this lane's run
+    const auto run = run_of<WM == 0>(i0, end, n - own);  // this lane's run
     wave_sync();  // the previous round has been read
     {
       int c[E], e[E];
       hv_t wv[E];
       float cs[E];
-      load_cols<E>(v, a.col, nt, w.block, i0, left, c);
+      load_cols<E>(v, a.col, nt, w.block, i0, run, c);
       if (MAPPED) {
-        if (nt) load_run<E, true>(a.eid, i0, left, e);
-        else load_run<E, false>(a.eid, i0, left, e);
+        if (nt) load_run<E, true>(a.eid, i0, run, e);
+        else load_run<E, false>(a.eid, i0, run, e);
       }
       if (WM != 0 && HV > 0) {
-        if (!MAPPED && (WM == 1 || a.w) && left >= E) {
+        if (!MAPPED && (WM == 1 || a.w) && run.template all<E>()) {
           __builtin_memcpy(wv, a.w + int64_t(i0 + shift) * NV, sizeof(wv));
         } else {
 #pragma unroll
           for (int m = 0; m < E; ++m) {
             wv[m] = hv_t(half_t(0));
-            if (m < left) {
+            if (run.has(m)) {
               if (WM == 1 || a.w) wv[m] = *reinterpret_cast<const hv_t*>(a.w + int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * NV);
               else wv[m] = hv_t(half_t(1));
             }
@@ -619,10 +628,10 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         cs[m] = 0.f;
-        if (WM == 2 && m < left) cs[m] = a.col_scale[c[m]];
+        if (WM == 2 && run.has(m)) cs[m] = a.col_scale[c[m]];
       }
 #pragma unroll
-      for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], m < left);
+      for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], run.has(m));
 #pragma unroll
       for (int m = 0; m < E; m += 4) *reinterpret_cast<int4_t*>(s_hnd + own + m) = int4_t{c[m], c[m + 1], c[m + 2], c[m + 3]};
       if (WM == 1 && HV > 0) {
@@ -632,13 +641,13 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
           for (int h = 0; h < H; ++h) {
             float x = 0.f;
             if (HV > 0) x = float(wv[m][h < NV ? h : 0]) * (WM == 2 ? cs[m] : 1.f);
-            else if (m < left) x = (a.w ? float(a.w[int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
+            else if (run.has(m)) x = (a.w ? float(a.w[int64_t(MAPPED ? pos_t(e[m]) : i0 + m + shift) * H + h]) : 1.f) * (WM == 2 ? cs[m] : 1.f);
             s_val[(own + m) * H + h] = factor_t(x);
           }
       }
     }
     wave_sync();
-    for (int q = 0; q < n; q += 8) {
+    for (int q = 0; WM == 0 ? k + pos_t(q) < end : q < n; q += 8) {
       int h8[8];
       const int4_t ha = *reinterpret_cast<const int4_t*>(s_hnd + q), hb = *reinterpret_cast<const int4_t*>(s_hnd + q + 4);
 #pragma unroll

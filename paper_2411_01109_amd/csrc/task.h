@@ -76,18 +76,32 @@ struct Round {
   static constexpr int PITCH = R + 4;               // ints per group in the handle table
 };
 
-// v[m] = p[i0 + m] for the first `left` entries (left may be negative); the others are 0
-template <int E, bool NT>
-__device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, int left, int (&v)[E]) {
+// The entries of a run that exist, m = 0, 1, ...: by what is left (which may be negative), or by position.
+struct RunLeft {
+  int left;
+  __device__ __forceinline__ bool has(int m) const { return m < left; }
+  template <int E>
+  __device__ __forceinline__ bool all() const { return left >= E; }
+};
+struct RunEnd {
+  pos_t i0, end;
+  __device__ __forceinline__ bool has(int m) const { return i0 + pos_t(m) < end; }
+  template <int E>
+  __device__ __forceinline__ bool all() const { return i0 + pos_t(E) <= end; }
+};
+
+// v[m] = p[i0 + m] for the entries that exist; the others are 0
+template <int E, bool NT, class Run>
+__device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, Run run, int (&v)[E]) {
   const int* q = p + i0;
-  if (left >= E) {
+  if (run.template all<E>()) {
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = NT ? __builtin_nontemporal_load(q + m) : q[m];
   } else {
 #pragma unroll
     for (int m = 0; m < E; ++m) {
       v[m] = 0;
-      if (m < left) v[m] = q[m];
+      if (run.has(m)) v[m] = q[m];
     }
   }
 }
@@ -190,12 +204,12 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
 
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these
 // passes draw from HBM, and a gather waits behind it (114 M non-zeros x 64 in eight blocks: 0.81 -> 0.76 ms).
-template <int E>
-__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, int left, int (&c)[E]) {
+template <int E, class Run>
+__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, Run run, int (&c)[E]) {
   if (v.col16) {
     const uint16_t* q = v.col16 + i0;
     const int first = block * v.width;
-    if (left >= E) {
+    if (run.template all<E>()) {
       uint16_t t[E];
       __builtin_memcpy(t, q, sizeof(t));
 #pragma unroll
@@ -204,13 +218,13 @@ __device__ __forceinline__ void load_cols(const TaskView& v, const int* __restri
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         c[m] = first;
-        if (m < left) c[m] += int(q[m]);
+        if (run.has(m)) c[m] += int(q[m]);
       }
     }
     return;
   }
-  if (nt) load_run<E, true>(col, i0, left, c);
-  else load_run<E, false>(col, i0, left, c);
+  if (nt) load_run<E, true>(col, i0, run, c);
+  else load_run<E, false>(col, i0, run, c);
 }
 
 // A table of rows of ld halves.  NEAR: its bytes stay below 2^32 - 8192, rows are read through a buffer descriptor whose

@@ -88,17 +88,17 @@ def main(argv):
     kf, kw = GIB_KIB / cal_f, GIB_KIB / cal_w  # true KiB per counted KiB
     bench_cmd = f"python3 $R/bench.py --workload {W} --steps {{n}} --warmup 1 --no-cpu-baseline --no-hbm-busy --calib-copy"
     L = [f"# rocprofv3 summary: hgnn kernels on {title} (one MI355X, bench.py step)\n",
-         "Commands (run from /tmp with TMPDIR=/tmp, R = repository root; the tables are made from their CSV output by "
+         "Commands (run from /tmp with TMPDIR=/tmp, R = repository root, D = a directory of your choice; the tables are made from their CSV output by "
          "`python -m paper_2411_01109_amd.profile_summary`):\n", "```",
-         f"rocprofv3 --kernel-trace --stats --output-format csv -d $R/gpurun_out/prof_{W}_trace -o {W} -- " + bench_cmd.format(n=5),
-         f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d $R/gpurun_out/prof_{W}_fetch -o {W} -- " + bench_cmd.format(n=2),
-         f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d $R/gpurun_out/prof_{W}_write -o {W} -- " + bench_cmd.format(n=2)]
+         f"rocprofv3 --kernel-trace --stats --output-format csv -d $D/prof_{W}_trace -o {W} -- " + bench_cmd.format(n=5),
+         f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d $D/prof_{W}_fetch -o {W} -- " + bench_cmd.format(n=2),
+         f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d $D/prof_{W}_write -o {W} -- " + bench_cmd.format(n=2)]
     if cache:
-        L.append(f"rocprofv3 --pmc {' '.join(sorted(cache))} --output-format csv -d $R/gpurun_out/prof_{W}_cache -o {W} -- " + bench_cmd.format(n=2))
+        L.append(f"rocprofv3 --pmc {' '.join(sorted(cache))} --output-format csv -d $D/prof_{W}_cache -o {W} -- " + bench_cmd.format(n=2))
     if issue:
-        L.append(f"rocprofv3 --pmc {' '.join(sorted(issue))} --output-format csv -d $R/gpurun_out/prof_{W}_issue -o {W} -- " + bench_cmd.format(n=2))
+        L.append(f"rocprofv3 --pmc {' '.join(sorted(issue))} --output-format csv -d $D/prof_{W}_issue -o {W} -- " + bench_cmd.format(n=2))
     if ea:
-        L.append(f"rocprofv3 --pmc {' '.join(sorted(ea))} --output-format csv -d $R/gpurun_out/prof_{W}_ea -o {W} -- " + bench_cmd.format(n=2))
+        L.append(f"rocprofv3 --pmc {' '.join(sorted(ea))} --output-format csv -d $D/prof_{W}_ea -o {W} -- " + bench_cmd.format(n=2))
     L.append("```\n")
     L.append(f"Counter calibration: the 1 GiB device-to-device copy of `--calib-copy` (`{COPY}`) reads FETCH_SIZE = {cal_f:.1f} KiB "
              f"and WRITE_SIZE = {cal_w:.1f} KiB for 1048576 KiB moved each way, so fetch bytes = FETCH_SIZE x {kf:.3f} KiB and write "
