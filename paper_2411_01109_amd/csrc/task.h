@@ -33,8 +33,9 @@ struct TaskView {
   // XCD) of a block every 2^32 / mix-th takes the former.  One kind after the other (mix = 0), the second sweeps the edge
   // tensors and the popular rows of the table again when the caches have lost them (31 M non-zeros: row sums through the map 340
   // -> 320 us, weighted SpMM 406 -> 396, SDDMM 415 -> 393, attention forward 403 -> 377; 62 M x 128, SpMM through the map 2.81 ->
-  // 2.76 ms).  Small graphs stay in the caches and end on long pieces that way (2.1 M, SDDMM 41.7 -> 45.1 us), plan-free calls, whose
-  // numbers are on the device, gain nothing.
+  // 2.76 ms; 20 M x 8 heads of 8, through the map 632 -> 566).  Small graphs stay in the caches and end on long pieces that way (2.1 M,
+  // SDDMM 41.7 -> 45.1 us); where nearly all pieces are long there is nothing to come back to (6 M, 35 a row, no edge values 124.7 ->
+  // 127.5); plan-free calls, whose numbers are on the device, gain nothing.
   uint32_t mix[kMaxTaskBlocks];
 };
 
@@ -55,7 +56,7 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool zeros = true) {
     n = (n + 7) & ~int64_t(7);
     v.first_wave[b] = int(n);
     const int64_t w8 = ceil_div(s.nw, 8), g8 = ceil_div(ceil_div(s.ng, G), 8);
-    v.mix[b] = t->nnz > kMixNnz && w8 > 0 && g8 > 0 ? uint32_t(((w8 << 32) + w8 + g8 - 1) / (w8 + g8)) : 0;
+    v.mix[b] = t->nnz > kMixNnz && w8 > 0 && w8 <= 4 * g8 ? uint32_t(((w8 << 32) + w8 + g8 - 1) / (w8 + g8)) : 0;
     n += ((s.nw + 7) & ~7) + ((ceil_div(s.ng, G) + 7) & ~int64_t(7)) + (zeros ? ceil_div(s.nz, int64_t(G) * kZeroTurns) : 0);
   }
   v.first_wave[t->nb] = int(n);
