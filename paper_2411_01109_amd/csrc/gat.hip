@@ -523,7 +523,7 @@ static hgnn_status run_gat_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, Ga
   a.staging_m = a.staging + size_t(t->n_slots) * size_t(p->max_F);
   a.stage_c = t->stage_mz + size_t(2) * size_t(t->n_slots) * size_t(p->max_H);
   const int L = pow2_at_least(a.F / 8), G = kWave / L, lh = a.D / 8;
-  const TaskView v = task_view(t, G);
+  const TaskView v = task_view(t, G, comes_back(false, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     const bool near = near_table(ncols, a.ldx);

@@ -1419,7 +1419,7 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
   a.staging = reinterpret_cast<half_t*>(t->staging);
   a.stage_ld = p->max_F;
   const bool mapped = wm != 0 && a.w && a.eid;
-  const TaskView v = task_view(t, G);
+  const TaskView v = task_view(t, G, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
   const int waves = v.first_wave[t->nb];
   if (a.atomic_y && v.n_split > 0) {
     launch_zero_split(L, s, a, v);

@@ -10,7 +10,7 @@ namespace hgnn {
 
 constexpr int kMaxTaskBlocks = 64;
 constexpr int kZeroTurns = 8;  // turns of G empty rows that a wave stores
-constexpr int64_t kMixNnz = int64_t(4) << 20;  // see TaskView::mix
+constexpr int64_t kMixNnz = int64_t(4) << 20;  // see comes_back()
 // Waves in a row on one XCD.  31 M non-zeros, one head of 64, 16 / 128 / 512 / 2048 waves: weighted SpMM 383, 369, 362, 363 us, SDDMM
 // 367, 353, 349, 350, row sums through the map 334, 320, 320, 334; 114 M, SpMM through the map 2149, 1790, 1789, 1790.
 constexpr int kTaskChunk = 512;
@@ -29,18 +29,25 @@ struct TaskView {
   // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms with chunks of 128).
   int chunk;
   int first_wave[kMaxTaskBlocks + 1];  // for the lane groups of this launch: waves before each block, then all of them
-  // Whole-wave pieces and waves of lane-group pieces go through the rows side by side: of the groups of eight waves (one per
-  // XCD) of a block every 2^32 / mix-th takes the former.  One kind after the other (mix = 0), the second sweeps the edge
-  // tensors and the popular rows of the table again when the caches have lost them (31 M non-zeros: row sums through the map 340
-  // -> 320 us, weighted SpMM 406 -> 396, SDDMM 415 -> 393, attention forward 403 -> 377; 62 M x 128, SpMM through the map 2.81 ->
-  // 2.76 ms; 20 M x 8 heads of 8, through the map 632 -> 566).  Small graphs stay in the caches and end on long pieces that way (2.1 M,
-  // SDDMM 41.7 -> 45.1 us); where nearly all pieces are long there is nothing to come back to (6 M, 35 a row, no edge values 124.7 ->
-  // 127.5); plan-free calls, whose numbers are on the device, gain nothing.
+  // Whole-wave pieces and waves of lane-group pieces go through the rows side by side (comes_back() below): of the groups of eight
+  // waves (one per XCD) of a block every 2^32 / mix-th takes the former.  mix = 0: one kind after the other.
   uint32_t mix[kMaxTaskBlocks];
 };
 
+// Whether the second of two kinds of pieces, one after the other, would sweep lines again that the caches have lost: those of edge
+// tensors behind a map, or of the popular rows of a table that a last-level cache of 256 MB no longer holds beside the streams.  us, one
+// after the other / side by side:
+//   through the map: 5.5 M non-zeros x 1 SpMM 106.5 / 102.5, x 4 128.6 / 123.1, row sums 67.6 / 64.8; 20 M x 8 SpMM 632 / 566
+//   512 MB, 13 M: SpMM 738 / 692; 154 MB, 31 M: weighted SpMM 406 / 396, SDDMM 415 / 393, attention forward 403 / 377; 128 MB, 20 M x 8:
+//     weighted SpMM 294 / 281
+//   77 MB, 12 M: weighted SpMM 127 / 130, SDDMM 125 / 125; 33 MB, 5.5 M x 4: SpMM 59.3 / 59.0, SDDMM 58.8 / 58.2; 15 MB, 7.3 M x 128: attention
+//     forward 128 / 131.5, backward 140 / 143
+// Small graphs stay in the caches and end on long pieces that way (2.1 M, SDDMM 41.7 / 45.1), where nearly all pieces are long there is
+// nothing to come back to (6 M, 35 a row: SpMM 124.7 / 127.5); plan-free calls, whose numbers are on the device, gain nothing.
+inline bool comes_back(bool mapped, int64_t table_bytes, int64_t llc) { return mapped || table_bytes > llc / 8 * 3; }
+
 // host: the launch shape of tasks t for G lane groups per wave; zeros = false leaves the empty rows out
-inline TaskView task_view(const hgnn_row_tasks* t, int G, bool zeros = true) {
+inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool zeros = true) {
   TaskView v{};
   v.task = reinterpret_cast<const int4_t*>(t->task);
   v.zrow = t->zrow;
@@ -56,7 +63,7 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool zeros = true) {
     n = (n + 7) & ~int64_t(7);
     v.first_wave[b] = int(n);
     const int64_t w8 = ceil_div(s.nw, 8), g8 = ceil_div(ceil_div(s.ng, G), 8);
-    v.mix[b] = t->nnz > kMixNnz && w8 > 0 && w8 <= 4 * g8 ? uint32_t(((w8 << 32) + w8 + g8 - 1) / (w8 + g8)) : 0;
+    v.mix[b] = comes_back && t->nnz > kMixNnz && w8 > 0 && w8 <= 4 * g8 ? uint32_t(((w8 << 32) + w8 + g8 - 1) / (w8 + g8)) : 0;
     n += ((s.nw + 7) & ~7) + ((ceil_div(s.ng, G) + 7) & ~int64_t(7)) + (zeros ? ceil_div(s.nz, int64_t(G) * kZeroTurns) : 0);
   }
   v.first_wave[t->nb] = int(n);
