@@ -1372,9 +1372,13 @@ static void launch_tasks(int L, int wm, bool mapped, unsigned waves, size_t leas
 //     307 MB, 62 M, by degrees                            901    871    852      -    967
 //     614 MB, 62 M, by degrees                           1849   1835   1823      -   1880
 //     614 MB, 62 M, edge values                          1800   1788   1777      -   1730
-// (tables that fit that cache gain or lose either way, so they are left alone).
-static size_t least_task_lds(bool mapped, int64_t edge_bytes, int64_t table_bytes, int64_t l2, int64_t llc) {
+// (tables that fit that cache gain or lose either way, so they are left alone).  A wave of short rows is mostly its own start and
+// end, which other waves must cover (28 / 16 waves: 7 non-zeros a row over 1.06 GB 960 / 1004 us, through the map 1186 / 1229; 13 a
+// row over 614 MB, no edge values, 866 / 907).
+static size_t least_task_lds(bool mapped, const SpmmArgs& a, int64_t ncols, int64_t l2, int64_t llc) {
   constexpr size_t kLds = 160 * 1024;  // of a compute unit
+  const int64_t edge_bytes = a.nnz * a.H * 2, table_bytes = ncols * a.ldx * 2;
+  if (a.nnz < int64_t(16) * a.nrows) return 0;
   if (mapped && edge_bytes > l2) return edge_bytes > 12 * l2 ? kLds / 14 / 16 * 16 : kLds / 16;
   return !mapped && table_bytes > llc ? kLds / 16 : 0;
 }
@@ -1426,7 +1430,7 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
     HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
   if (waves > 0) {
-    const size_t least = least_task_lds(mapped, a.nnz * a.H * 2, int64_t(ncols) * a.ldx * 2, p->l2_bytes, p->llc_bytes);
+    const size_t least = least_task_lds(mapped, a, ncols, p->l2_bytes, p->llc_bytes);
     if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     else launch_tasks<false>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     HGNN_LAUNCH_CHECK("spmm_task_kernel");
@@ -1489,7 +1493,7 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   const int wm = a.w ? 1 : 0;
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  const size_t least = least_task_lds(mapped, a.nnz * a.H * 2, int64_t(g->ncols) * a.ldx * 2, l2, llc);
+  const size_t least = least_task_lds(mapped, a, g->ncols, l2, llc);
   if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");
