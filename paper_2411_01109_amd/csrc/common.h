@@ -267,6 +267,8 @@ struct hgnn_row_tasks {
   int32_t nb = 0;
   int64_t nnz = 0;
   int4* task = nullptr;
+  int4* rtask = nullptr;         // pieces of the rows that are cut at column ranges, range after range (ranges.hip); all staged
+  int32_t n_rtask = 0;
   int32_t* zrow = nullptr;
   int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
   hgnn_task_sec* sec = nullptr;  // [nb]
@@ -369,7 +371,7 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
                       void* scratch, size_t scratch_bytes, bool one_sweep, hipStream_t s);
 void device_cache_bytes(int64_t* l2, int64_t* llc);  // of the current device
 size_t spmm_hub_scratch_bytes(int32_t nrows, int64_t nnz, int32_t F);  // scratch of the plan-free SpMM's hub kernels alone
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s);
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, SetupStream& s);  // blocks: build_col_blocks follows
 hgnn_status build_col_blocks(hgnn_plan* p, const hgnn_csr* g, int nb, SetupStream& s);  // p->nb > 1 from here
 // the cut whose blocks a pass walks; narrow: a pass that gathers from two tables at once or leaves no partial rows behind
 inline const hgnn_plan* walked_cut(const hgnn_plan* p, bool narrow) { return p->fine && (narrow || !p->btasks) ? p->fine : p; }
@@ -380,7 +382,9 @@ struct TaskSource {
   const int32_t* first;   // device, [nb] first non-zero of every block, or nullptr (one block)
   int32_t nrows, nb, S, group_max;
   int64_t nnz;
+  int32_t range_min;      // rows of at least so many non-zeros are left to ranges.hip (one block), or kNoRanges
 };
+constexpr int kNoRanges = 0x7fffffff;
 // Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
 // reductions across lane groups (2.1 M non-zeros x 128: 32 is 3 % better than 64; 62 M x 128: 128 is 1 % better); the pieces of
 // column blocks come in numbers and are bound by the L2s (114 M non-zeros: 256 is 3 % better than 128).
@@ -388,8 +392,10 @@ constexpr int kGroupMaxBlocks = 256;
 inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 : 128; }
 struct TaskTotals {
   int64_t n_zero;
-  int32_t n_task, n_whole, n_split, n_slots;
+  int32_t n_task, n_whole, n_split, n_slots, n_long, n_range;  // n_long rows in n_range pieces by ranges.hip
 };
+constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for equal neighbours; few, because the short rows of a
+                                   // window share cache lines of the column array and of edge tensors (see TaskView::chunk)
 // The same without a plan, in memory of the caller and without a host wait: the launch shape is then not known on the host, so
 // the kernels read it from `sec` and `totals` and walk the tasks with a grid stride.
 struct TaskScratch {
@@ -405,13 +411,20 @@ struct TaskScratch {
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
 struct TaskCounts {
-  explicit TaskCounts(SetupStream& s) : counts(s), sec(s), mail(s) {}
-  DevTemp counts, sec;
+  explicit TaskCounts(SetupStream& s) : counts(s), sec(s), ranges(s), mail(s) {}
+  DevTemp counts, sec, ranges;
   HostMail mail;
   TaskTotals* totals = nullptr;  // valid after the stream has been waited for (host memory, or a device copy)
+  const int* long_at = nullptr;  // device, [windows] long rows before each window of kTaskWindow rows, and
+  const int* n_long = nullptr;   // how many there are
 };
 hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s);
 hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, SetupStream& s);
+// ranges.hip: long rows cut at the borders of column ranges
+constexpr int kRanges = 8;  // as many as there are XCDs
+int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2);
+hgnn_status range_count(const TaskSource& q, const int32_t* col, int ncols, TaskCounts& c, SetupStream& s);
+hgnn_status range_write(const TaskSource& q, const TaskCounts& c, const TaskTotals& t, int4* task, int4* split, SetupStream& s);
 hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s);
 void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s);

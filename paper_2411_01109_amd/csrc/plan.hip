@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int
 
 // Validates the graph g and builds the segment arrays, row lists and row tasks of p for it (p->S, p->nseg, p->max_F set by the
 // caller).  The host waits twice: for the totals of the lists (which size the allocations) and for the arrays.
-hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s) {
+hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, SetupStream& s) {
   const int64_t E = g->nnz;
   const int nblk = int(ceil_div(g->nrows, kRowsPerBlock));
   DevTemp facts_buf(s), counts_buf(s);
@@ -369,9 +369,11 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, SetupStream& s) {
   if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
   row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
   HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
-  const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz), g->nnz};
+  const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz), g->nnz,
+                      blocks ? kNoRanges : range_min_row(E, g->ncols, p->max_F, p->S, p->l2_bytes)};
   TaskCounts tc(s);
   hgnn_status st = task_count(tq, tc, s);
+  if (st == HGNN_OK && tq.range_min != kNoRanges) st = range_count(tq, g->col, g->ncols, tc, s);
   if (st != HGNN_OK) return st;
   GraphFacts f;
   if (!mail.data) HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
@@ -557,30 +559,31 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
   p->mid_deg = 32;
   device_cache_bytes(&p->l2_bytes, &p->llc_bytes);
   SetupStream s(stream);
-  st = plan_build_arrays(p, g, s);
-  if (st == HGNN_OK) {
-    int nb = col_blocks;
-    bool narrow_only = false;  // every pass over blocks takes the finer cut
-    p->auto_blocks = nb == 0;
-    if (nb == 0) {
-      // automatic: block only when the feature table is too large for an XCD's L2 (beyond three times its size)
-      // but fits the last-level cache with room for the streams (three quarters of it), and rows are long enough
-      // that a row piece per block still amortises its partial vector; about two L2 sizes of feature rows per block
-      const double table = double(g->ncols) * max_F * 2.0;
-      const double mean_deg = g->nrows > 0 ? double(g->nnz) / g->nrows : 0.0;
-      nb = 1;
-      if (table > 3.0 * double(p->l2_bytes) && table < 0.75 * double(p->llc_bytes) && mean_deg >= 128.0) {
-        nb = int(table / (2.0 * double(p->l2_bytes)) + 0.5);
-        if (nb < 2) nb = 2;
-        if (nb > 16) nb = 16;
-        // all passes walk the finer cut below where a row still has 32 non-zeros or more in each of its blocks on
-        // average: slices of 3.7 MB come from L2 at 26 TB/s, of 7.5 MB at 15 TB/s, but every piece of a row costs a
-        // partial row written and read again, as much as some ten gathers.  233 000 columns x 64, 4 -> 8 blocks: at 489
-        // non-zeros a row 1.2 times as fast, at 172 slower (attention forward 524 -> 646 us, backward 552 -> 586).
-        narrow_only = mean_deg >= 64.0 * nb && g->ncols >= 2 * nb;
-      }
+  int nb = col_blocks;
+  bool narrow_only = false;  // every pass over blocks takes the finer cut
+  p->auto_blocks = nb == 0;
+  if (nb == 0) {
+    // automatic: block only when the feature table is too large for an XCD's L2 (beyond three times its size)
+    // but fits the last-level cache with room for the streams (three quarters of it), and rows are long enough
+    // that a row piece per block still amortises its partial vector; about two L2 sizes of feature rows per block
+    const double table = double(g->ncols) * max_F * 2.0;
+    const double mean_deg = g->nrows > 0 ? double(g->nnz) / g->nrows : 0.0;
+    nb = 1;
+    if (table > 3.0 * double(p->l2_bytes) && table < 0.75 * double(p->llc_bytes) && mean_deg >= 128.0) {
+      nb = int(table / (2.0 * double(p->l2_bytes)) + 0.5);
+      if (nb < 2) nb = 2;
+      if (nb > 16) nb = 16;
+      // all passes walk the finer cut below where a row still has 32 non-zeros or more in each of its blocks on
+      // average: slices of 3.7 MB come from L2 at 26 TB/s, of 7.5 MB at 15 TB/s, but every piece of a row costs a
+      // partial row written and read again, as much as some ten gathers.  233 000 columns x 64, 4 -> 8 blocks: at 489
+      // non-zeros a row 1.2 times as fast, at 172 slower (attention forward 524 -> 646 us, backward 552 -> 586).
+      narrow_only = mean_deg >= 64.0 * nb && g->ncols >= 2 * nb;
     }
-    if (nb > 1 && g->nnz > 0 && g->ncols >= nb) {
+  }
+  const bool blocks = nb > 1 && g->nnz > 0 && g->ncols >= nb;
+  st = plan_build_arrays(p, g, blocks, s);
+  if (st == HGNN_OK) {
+    if (blocks) {
       p->nb = nb;
       p->block_width = int(ceil_div(g->ncols, nb));
       p->block_eid = g->eid != nullptr;

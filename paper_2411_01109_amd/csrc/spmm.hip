@@ -533,10 +533,11 @@ __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t fir
 // exactly one writer.
 //
 // Bound: the gathers, 64 bytes per clock and compute unit while the table sits in the L2s, the traffic behind the L2s
-// beyond that (62 M non-zeros x 128: 12 GB of L2 misses per call at 7.3 TB/s, vector instructions busy 27 % of the cycles).  A call
+// beyond that (62 M non-zeros x 128: 8.9 GB of L2 misses per call at 7.0 TB/s, 11.9 at 7.4 where no row is cut at column ranges).  A call
 // against the walk over equal runs of non-zeros with row ids in LDS: R-MAT 5.5 M non-zeros x 64, four heads of edge values 88 -> 59
 // us, behind a map 131 -> 123; 2.1 M x 128 with the GIN terms 62 -> 43 us; 37 k x 64 19 -> 6 us; 114 M non-zeros x 64 in blocks of
-// 3.7 MB 1.09 -> 0.83 ms (18 TB/s of rows); 62 M x 128 the same (by degrees 1.87 ms, edge values 1.73), through a map 2 % slower.
+// 3.7 MB 1.09 -> 0.83 ms (18 TB/s of rows); 62 M x 128 with edge values 1.73 -> 1.29,
+// through a map 2.76 -> 2.04.
 // WM: 0 = no factor per non-zero, 1 = edge values, 2 = edge values (if any) times a column scale.  MAPPED: edge values
 // behind an edge-id map.
 // ---------------------------------------------------------------------------------------------------
@@ -1357,30 +1358,37 @@ static void launch_tasks(int L, int wm, bool mapped, unsigned waves, size_t leas
   }
 }
 
-// Every wave has eight gathers a lane group in flight.  Where the gathered lines miss the L2s, 28 to 32 waves per compute unit ask
-// for more than an L2 holds (32 compute units x 32 waves x 32 rows of 256 bytes: 8.4 MB), and popular rows and shared lines of the
+// Every wave has eight gathers a lane group in flight.  Where the gathered lines miss the L2s, 28 to 32 waves per compute unit ask for
+// more than an L2 holds (32 compute units x 32 waves x 32 rows of 256 bytes: 8.4 MB), and popular rows and shared lines of the
 // edge values are gone before the next wave wants them.  LDS that nobody uses then keeps waves out.  us, by waves per compute unit:
 //   edge values behind a map: non-zeros x heads          28     20     16     14     12
 //     2.1 M x 1 (4 MB, as an L2), 128 features           62.4   62.5   64.3   74.5   78.5
 //     5.5 M x 1 (11 MB), 64 features                      104    102    102    107    111
 //     5.5 M x 4 (44 MB)                                   130    123    122    127    132
-//     31 M x 1 (62 MB)                                    816    796    791    773    765
-//     31 M x 4 (248 MB)                                   911    885    878    848    841
 //     114 M x 1 in blocks (228 MB)                       1793   1709   1688      -   1676
+//    long rows cut at column ranges:
+//     12 M x 1 (24 MB)                                    232    225    222    222
+//     31 M x 4 (248 MB)                                   746    708    707    740
+//     62 M x 1 (124 MB), 128 features                    2075   2048   2043   2042
+//     log-normal rows, 26 M x 4 (204 MB), 128 features   1284   1230   1169   1189
+//     60 M x 1 (120 MB), 16 features                     1479   1438   1422   1374
 //   unmapped: table beside a last-level cache of 256 MB
 //     77 MB, 31 M non-zeros, no edge values (154 MB)      371    377    388    445    469
+//    no row cut at column ranges:
 //     307 MB, 62 M, by degrees                            901    871    852      -    967
 //     614 MB, 62 M, by degrees                           1849   1835   1823      -   1880
-//     614 MB, 62 M, edge values                          1800   1788   1777      -   1730
-// (tables that fit that cache gain or lose either way, so they are left alone).  A wave of short rows is mostly its own start and
-// end, which other waves must cover (28 / 16 waves: 7 non-zeros a row over 1.06 GB 960 / 1004 us, through the map 1186 / 1229; 13 a
-// row over 614 MB, no edge values, 866 / 907).
-static size_t least_task_lds(bool mapped, const SpmmArgs& a, int64_t ncols, int64_t l2, int64_t llc) {
+//    long rows cut at column ranges:
+//     307 MB, 62 M, by degrees                            740    763    783    876
+//     614 MB, 62 M, edge values                          1327   1328   1329   1357
+// (tables that fit that cache, and the rows of one range in an L2, gain or lose either way, so they are left alone).  A wave of short
+// rows is mostly its own start and end, which other waves must cover (28 / 16 waves: 7 non-zeros a row over 1.06 GB 960 / 1004 us, through
+// the map 1186 / 1229; 13 a row over 614 MB, no edge values, 866 / 907).
+static size_t least_task_lds(bool mapped, bool ranges, const SpmmArgs& a, int64_t ncols, int64_t l2, int64_t llc) {
   constexpr size_t kLds = 160 * 1024;  // of a compute unit
   const int64_t edge_bytes = a.nnz * a.H * 2, table_bytes = ncols * a.ldx * 2;
   if (a.nnz < int64_t(16) * a.nrows) return 0;
-  if (mapped && edge_bytes > l2) return edge_bytes > 12 * l2 ? kLds / 14 / 16 * 16 : kLds / 16;
-  return !mapped && table_bytes > llc ? kLds / 16 : 0;
+  if (mapped && edge_bytes > l2) return edge_bytes > 12 * l2 && !ranges ? kLds / 14 / 16 * 16 : kLds / 16;
+  return !mapped && !ranges && table_bytes > llc ? kLds / 16 : 0;
 }
 
 static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
@@ -1430,7 +1438,7 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
     HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
   if (waves > 0) {
-    const size_t least = least_task_lds(mapped, a, ncols, p->l2_bytes, p->llc_bytes);
+    const size_t least = least_task_lds(mapped, t->n_rtask > 0, a, ncols, p->l2_bytes, p->llc_bytes);
     if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     else launch_tasks<false>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     HGNN_LAUNCH_CHECK("spmm_task_kernel");
@@ -1480,7 +1488,7 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
 // row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.54 -> 1.23 ms together.
 static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, hipStream_t s) {
   const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
-  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz};
+  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz, kNoRanges};
   const hgnn_status st = task_build_in(q, t, s);
   if (st != HGNN_OK) return st;
   const int L = pow2_at_least((a.F + 7) / 8);
@@ -1493,7 +1501,7 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   const int wm = a.w ? 1 : 0;
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  const size_t least = least_task_lds(mapped, a, g->ncols, l2, llc);
+  const size_t least = least_task_lds(mapped, false, a, g->ncols, l2, llc);
   if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");

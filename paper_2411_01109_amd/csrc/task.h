@@ -17,6 +17,8 @@ constexpr int kTaskChunk = 512;
 
 struct TaskView {
   const int4_t* task;
+  const int4_t* rtask;       // pieces of rows cut at column ranges: an eighth per XCD, so that its L2 keeps to one range of the table
+  int n_rtask, rshare;       // how many; per XCD (a multiple of the lane groups of a wave)
   const int* zrow;
   const hgnn_task_sec* sec;
   const int4_t* split;
@@ -57,7 +59,10 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool 
   v.width = t->width;
   v.n_split = t->n_split;
   v.nb = t->nb;
-  int64_t n = 0;
+  v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
+  v.n_rtask = t->n_rtask;
+  v.rshare = int(ceil_div(ceil_div(t->n_rtask, kRanges), G) * G);
+  int64_t n = int64_t(kRanges) * v.rshare / G;
   for (int b = 0; b < t->nb; ++b) {
     const hgnn_task_sec& s = t->host[size_t(b)];
     n = (n + 7) & ~int64_t(7);
@@ -157,6 +162,21 @@ template <int L>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
   constexpr int G = kWave / L;
   TaskWave w;
+  if (wid < v.first_wave[0]) {  // never where the numbers are on the device
+    const int i = (wid >> 3) * G + g, k = (wid & 7) * v.rshare + i;
+    int4_t t = {0, 0, -1, -1};
+    if (k < v.n_rtask) t = v.rtask[k];
+    w.block = w.first = 0;
+    w.whole = false;
+    w.zrow = v.zrow;
+    w.z0 = w.z1 = 0;
+    w.beg = t[0];
+    w.end = t[0] + t[1];
+    w.row = t[2];
+    w.slot = t[3];
+    w.span = w.step = Round<L>::R;
+    return w;
+  }
   int b = 0;
   while (b + 1 < v.nb && wid >= v.first_wave[b + 1]) ++b;
   const hgnn_task_sec s = v.sec[b];

@@ -11,13 +11,13 @@
 
 namespace hgnn {
 
-constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for equal neighbours; few, because the short rows of a
-                                   // window share cache lines of the column array and of edge tensors (see TaskView::chunk)
 constexpr int kTaskThreads = 256;
 constexpr int kTaskRowsPerThread = kTaskWindow / kTaskThreads;
 constexpr int kMaxGroupLen = 256;
 static_assert(kGroupMaxBlocks <= kMaxGroupLen, "table of lengths");
-enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters };
+enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters, kTaskLong = kTaskCounters, kTaskAll };  // kTaskLong: with a plan
+
+constexpr int kLongRow = -1, kNone = -2;  // RowCut::m of a row for ranges.hip, and of no row
 
 struct RowCut {
   int len, part, m;  // non-zeros, non-zeros per piece, pieces
@@ -29,7 +29,9 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
   if (c.len < 0) c.len = 0;  // an offset array that validation will reject
   c.part = c.len;
   c.m = c.len > 0 ? 1 : 0;
-  if (c.len > q.S) {
+  if (c.len >= q.range_min) {
+    c.m = kLongRow;
+  } else if (c.len > q.S) {
     c.part = pieces_of(c.len, pieces_of(c.len, q.S));
     c.m = pieces_of(c.len, c.part);
   }
@@ -38,30 +40,32 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
 
 // counts[q][b][window]
 __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, int nwin, int* __restrict__ counts) {
-  __shared__ int total[kTaskCounters];
+  __shared__ int total[kTaskAll];
   const int b = blockIdx.y;
+  const int counters = q.range_min == kNoRanges ? kTaskCounters : kTaskAll;
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
-  if (threadIdx.x < kTaskCounters) total[threadIdx.x] = 0;
+  if (threadIdx.x < kTaskAll) total[threadIdx.x] = 0;
   __syncthreads();
-  int n[kTaskCounters] = {0, 0, 0, 0, 0};
+  int n[kTaskAll] = {0, 0, 0, 0, 0, 0};
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(blockIdx.x) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     if (r >= q.nrows) break;
     const RowCut c = cut_row(q, rp, int(r));
-    if (c.m == 0) ++n[kTaskZ];
+    if (c.m == kLongRow) ++n[kTaskLong];
+    else if (c.m == 0) ++n[kTaskZ];
     else n[c.part > q.group_max ? kTaskW : kTaskG] += c.m;
     if (c.m > 1) {
       ++n[kTaskSplit];
       n[kTaskSlots] += c.m;
     }
   }
-  for (int i = 0; i < kTaskCounters; ++i) {
+  for (int i = 0; i < kTaskAll; ++i) {
     int v = n[i];
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = total[threadIdx.x];
+  if (int(threadIdx.x) < counters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = total[threadIdx.x];
 }
 
 // One workgroup: exclusive scans over the windows of every (counter, block), then the sections of the blocks.  A wave per
@@ -70,7 +74,8 @@ __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, i
                                                                   hgnn_task_sec* __restrict__ sec, TaskTotals* out) {
   const int nb = q.nb;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  for (int i = wave; i < kTaskCounters * nb; i += kTaskThreads / kWave) {
+  const int counters = q.range_min == kNoRanges ? kTaskCounters : kTaskAll;
+  for (int i = wave; i < counters * nb; i += kTaskThreads / kWave) {
     int* c = counts + int64_t(i) * nwin;
     int carry = 0;
     for (int w0 = 0; w0 < nwin; w0 += kWave) {
@@ -107,6 +112,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, i
       t.n_slots += slots;
       sec[b] = s;
     }
+    if (counters == kTaskAll) t.n_long = sums[kTaskLong * nb];
     *out = t;
   }
 }
@@ -152,7 +158,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
     s = hgnn_task_sec{0, all[kTaskW], all[kTaskW], all[kTaskG], 0, all[kTaskZ], 0};
     if (w == 0 && threadIdx.x == 0) {
       *sec = s;
-      *totals = TaskTotals{all[kTaskZ], all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskSplit], all[kTaskSlots]};
+      *totals = TaskTotals{all[kTaskZ], all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskSplit], all[kTaskSlots], 0, 0};
     }
   } else {
     s = sec[b];
@@ -167,7 +173,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
   RowCut cut[kTaskRowsPerThread];
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
-    cut[u] = RowCut{0, 0, -1};  // no row
+    cut[u] = RowCut{0, 0, kNone};
     if (r < q.nrows) cut[u] = cut_row(q, rp, int(r));
     if (cut[u].m > 0 && cut[u].part <= q.group_max) {
       const int last = cut[u].len - (cut[u].m - 1) * cut[u].part;
@@ -227,11 +233,13 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
 
 hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
-  HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskCounters) * size_t(q.nb) * (size_t(nwin) + 1)));
+  HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskAll) * size_t(q.nb) * (size_t(nwin) + 1)));
   HGNN_HIP(c.sec.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals)));
   int* counts = c.counts.as<int>();
-  int* sums = counts + size_t(kTaskCounters) * size_t(q.nb) * size_t(nwin);
+  int* sums = counts + size_t(kTaskAll) * size_t(q.nb) * size_t(nwin);
   hgnn_task_sec* sec = c.sec.as<hgnn_task_sec>();
+  c.long_at = counts + size_t(kTaskLong) * size_t(q.nb) * size_t(nwin);
+  c.n_long = sums + size_t(kTaskLong) * size_t(q.nb);
   c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(sec + q.nb);
   if (nwin > 0) task_count_kernel<<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts);
   task_scan_kernel<<<1, kTaskThreads, 0, s>>>(q, nwin, counts, sums, sec, c.totals);
@@ -243,7 +251,7 @@ hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s) {
 hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, SetupStream& s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
   int* counts = c.counts.as<int>();
-  int* sums = counts + size_t(kTaskCounters) * size_t(q.nb) * size_t(nwin);
+  int* sums = counts + size_t(kTaskAll) * size_t(q.nb) * size_t(nwin);
   hgnn_row_tasks* t = new (std::nothrow) hgnn_row_tasks();
   if (!t) return fail(HGNN_ENOMEM, "task_build: host allocation failed");
   *out = t;  // the plan owns it from here
@@ -252,17 +260,18 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
   else HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
   t->nb = q.nb;
   t->nnz = q.nnz;
-  t->n_split = tot.n_split;
-  t->n_slots = tot.n_slots;
+  t->n_split = tot.n_split + tot.n_long;
+  t->n_slots = tot.n_slots + tot.n_range;
+  t->n_rtask = tot.n_range;
   t->host.resize(size_t(q.nb));
   t->sec = c.sec.as<hgnn_task_sec>();
   c.sec.p = nullptr;
   HGNN_HIP(dev_malloc(&t->task, sizeof(int4) * size_t(tot.n_task > 0 ? tot.n_task : 1)));
   HGNN_HIP(dev_malloc(&t->zrow, sizeof(int) * size_t(tot.n_zero > 0 ? tot.n_zero : 1)));
-  if (tot.n_split > 0) {
-    HGNN_HIP(dev_malloc(&t->split, sizeof(int4) * size_t(tot.n_split)));
-    HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(tot.n_slots) * size_t(max_F)));
-    HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(tot.n_slots) * size_t(max_H)));
+  if (t->n_split > 0) {
+    HGNN_HIP(dev_malloc(&t->split, sizeof(int4) * size_t(t->n_split)));
+    HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(t->n_slots) * size_t(max_F)));
+    HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(t->n_slots) * size_t(max_H)));
   }
   if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, int32_t(tot.n_zero), 0};
   else HGNN_HIP(hipMemcpyAsync(t->host.data(), t->sec, sizeof(hgnn_task_sec) * size_t(q.nb), hipMemcpyDeviceToHost, s));
@@ -270,6 +279,10 @@ hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H,
     task_write_kernel<false><<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts, sums, t->sec, nullptr,
                                                                                           t->task, t->zrow, t->split);
   HGNN_LAUNCH_CHECK("task_write_kernel");
+  if (tot.n_range > 0) {
+    HGNN_HIP(dev_malloc(&t->rtask, sizeof(int4) * size_t(tot.n_range)));
+    return range_write(q, c, tot, t->rtask, t->split + tot.n_split, s);
+  }
   return HGNN_OK;
 }
 
@@ -280,7 +293,7 @@ hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
   for (int b = 0; b < p->nb; ++b) host[size_t(b)] = int32_t(p->boff[size_t(b)]);
   HGNN_HIP(first.alloc(sizeof(int32_t) * size_t(p->nb)));
   HGNN_HIP(hipMemcpyAsync(first.p, host.data(), sizeof(int32_t) * size_t(p->nb), hipMemcpyHostToDevice, s));
-  const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks, p->nnz};
+  const TaskSource q{p->brp, first.as<int32_t>(), p->nrows, p->nb, p->S, kGroupMaxBlocks, p->nnz, kNoRanges};
   TaskCounts c(s);
   hgnn_status st = task_count(q, c, s);
   if (st != HGNN_OK) return st;
@@ -329,6 +342,7 @@ void destroy_tasks(hgnn_row_tasks* t, bool idle) {
   if (!t) return;
   dev_put(t->task, idle);
   dev_put(t->zrow, idle);
+  dev_put(t->rtask, idle);
   dev_put(t->split, idle);
   dev_put(t->sec, idle);
   dev_put(t->staging, idle);

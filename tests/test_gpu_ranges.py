@@ -1,0 +1,121 @@
+"""Long rows cut at the borders of column ranges (plans of more than 4 Mi non-zeros over a table beyond the eight L2s): row lengths around
+the segment size, rows inside one range, rows that touch only the columns at the borders, empty ranges, every walk that takes them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity import compare, down, f16, up
+
+pytestmark = pytest.mark.gpu
+
+V, NCOLS, S, MAX_F = 30000, 30011, 64, 576  # the plan's table is 34.6 MB
+
+
+@pytest.fixture(scope="module")
+def graph():
+    r = np.random.default_rng(7)
+    width = -(-NCOLS // 8)
+    deg = r.integers(110, 200, size=V)
+    deg[r.permutation(V)[:3000]] = r.integers(0, 70, size=3000)
+    lens = (0, 1, S - 1, S, S + 1, S + 2, 2 * S, 8 * S - 1, 8 * S, 8 * S + 1, 2047, 4097, 9000)
+    deg[:len(lens)] = lens
+    deg[-len(lens):] = lens
+    col = [np.sort(r.integers(0, NCOLS, size=d)) for d in deg]
+    borders = np.array([b for x in range(1, 8) for b in (x * width - 1, x * width)])
+    special = [np.zeros(300), np.full(300, NCOLS - 1), r.integers(0, width, size=700), r.integers(3 * width, 4 * width, size=1000),
+               np.tile(borders, 20), np.concatenate([np.zeros(100), np.full(1, NCOLS - 1)]), np.full(2 * S + 1, width)]
+    for i, c in enumerate(special):
+        deg[50 + i] = c.size
+        col[50 + i] = np.sort(c)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate(col).astype(np.int32)
+    assert col.size > 4 << 20
+    return rowptr, col
+
+
+@pytest.mark.parametrize("F,H", [(8, 1), (42, 1), (32, 4), (24, 3)])
+@pytest.mark.parametrize("what", ["plain", "w", "map", "scaled"])
+def test_spmm(hgnn, dev, graph, F, H, what):
+    print(f"ranges F={F} H={H} {what}", flush=True)
+    r = np.random.default_rng(F + H)
+    rowptr, col = graph
+    pitch = (F + 7) // 8 * 8
+    w = None if what == "plain" else f16(r.standard_normal((col.size, H)))
+    H = 1 if w is None else H
+    g, ncols, eid = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=NCOLS), NCOLS, None
+    if what == "map":  # the long rows again, now with a map
+        t = hgnn.hgnn_transpose(g)
+        g = hgnn.hgnn_transpose(hgnn.Csr(t.rowptr, t.col, ncols=V))
+        eid = down(g.eid)
+    Xh = np.zeros((ncols, pitch), dtype=np.float16)
+    Xh[:, :F] = f16(r.standard_normal((ncols, F)))
+    p = hgnn.hgnn_plan_create(g, S, MAX_F, H, col_blocks=1)
+    Y = torch.full((V, pitch), 3.0, dtype=torch.float16, device=dev)
+    wd = None if w is None else up(w, dev)
+    if what == "scaled":
+        cs = r.uniform(0.5, 2.0, size=ncols).astype(np.float32)
+        hgnn.hgnn_spmm_discretized_fused(p, g, wd, H, up(Xh, dev), Y, op=hgnn.HGNN_MEAN, col_scale=up(cs, dev), F=F)
+        ref, sabs = scaled(rowptr, col, Xh[:, :F], w, cs, H)
+    else:
+        hgnn.hgnn_spmm_discretized(p, g, wd, H, up(Xh, dev), Y, F=F)
+        ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(Xh[:, :F]), w=w, H=H, want_sabs=True, **({} if eid is None else {"eid": eid}))
+    compare("ranges", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+
+
+def scaled(rowptr, col, X, w, cs, H):
+    """Mean of w * cs[col] * X[col], and the same over magnitudes, in float64."""
+    F = X.shape[1]
+    out = []
+    for f in (lambda a: a, np.abs):
+        t = f(w.astype(np.float64)).repeat(F // H, axis=1) * (f(X.astype(np.float64)) * cs[:, None].astype(np.float64))[col]
+        y = np.add.reduceat(np.concatenate([t, np.zeros((1, F))]), rowptr[:-1], axis=0)
+        deg = np.diff(rowptr)
+        y[deg == 0] = 0
+        out.append(y / np.maximum(deg, 1)[:, None])
+    return out
+
+
+@pytest.mark.parametrize("H,D", [(1, 64), (4, 16), (8, 8)])
+def test_attention(hgnn, dev, graph, H, D):
+    """Saving forward and its backward against the oracle (forward) and the walk over rows in one range (backward)."""
+    print(f"ranges attention H={H} D={D}", flush=True)
+    rowptr, col = graph
+    F = H * D
+    r = np.random.default_rng(H)
+    U, X, dO = (f16(r.standard_normal((n, F))) for n in (V, NCOLS, V))
+    a_l, a_r = f16(0.2 * r.standard_normal(F)), f16(0.2 * r.standard_normal(F))
+    ref, ref_lse, sabs = oracle.gat_forward(rowptr, col, U, X, a_l, a_r, H, slope=0.2)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=NCOLS)
+    gt = hgnn.hgnn_transpose(g)
+    Ud, Xd, dOd, al, ar = up(U, dev), up(X, dev), up(dO, dev), up(a_l, dev), up(a_r, dev)
+    got = []
+    for max_f in (F, MAX_F):
+        p, pt = (hgnn.hgnn_plan_create(x, S, max_f, H, col_blocks=1) for x in (g, gt))
+        half = lambda *n: torch.full(n, 7.0, dtype=torch.float16, device=dev)
+        f32 = lambda *n: torch.full(n, 7.0, dtype=torch.float32, device=dev)
+        out, outm, lse, csum = half(V, F), half(V, F), f32(V, H), f32(V, H)
+        hgnn.hgnn_gat_forward_fused_save(g, p, H, D, Ud, Xd, al, ar, out, lse, outm, csum)
+        out0, lse0 = half(V, F), f32(V, H)
+        hgnn.hgnn_gat_forward_fused(g, p, H, D, Ud, Xd, al, ar, out0, lse0)
+        assert torch.equal(out, out0) and torch.equal(lse, lse0)
+        dV, d_el, d_er = half(NCOLS, F), half(V, H), half(NCOLS, H)
+        hgnn.hgnn_gat_backward_fused_saved(g, p, gt, pt, H, D, Ud, Xd, al, ar, out, lse, outm, csum, dOd, dV, d_el, d_er)
+        dot = torch.full((col.size, H), 7.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, H, D, dOd, Xd, dot)
+        sums = half(NCOLS, H)
+        hgnn.hgnn_edge_rowsum(gt, pt, H, dot, sums)
+        got.append([down(t) for t in (out, outm, lse, csum, dV, d_el, d_er, dot, sums)])
+        hgnn.hgnn_plan_destroy(p)
+        hgnn.hgnn_plan_destroy(pt)
+    compare("out", got[1][0], ref, sabs)
+    deg = np.diff(rowptr)
+    assert np.abs(got[1][2][deg > 0] - ref_lse[deg > 0]).max() <= 2e-3 + 1e-3 * np.abs(ref_lse).max()
+    for name, a, b in zip(("out", "outm", "lse", "csum", "dV", "d_el", "d_er", "dot", "sums"), got[0], got[1]):
+        if name == "dot":  # the same products in the same order
+            assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
+            continue
+        a, b = a.astype(np.float64), b.astype(np.float64)
+        # two results of sums that are rounded to fp16 up to three times each; 2^-11 relative to the terms of a cancelling sum
+        assert np.linalg.norm(a - b) <= 4e-3 * np.linalg.norm(a), (name, np.linalg.norm(a - b) / np.linalg.norm(a))
