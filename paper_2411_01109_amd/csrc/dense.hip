@@ -96,6 +96,24 @@ __device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __res
   }
 }
 
+// eight consecutive features of a row of Y from the two result tiles that hold them
+__device__ __forceinline__ void linear_store(const LinearArgs& a, int64_t row, int f, const float4_t& lo, const float4_t& hi) {
+  half8_t h;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    h[j] = half_t(lo[j]);
+    h[4 + j] = half_t(hi[j]);
+  }
+  half_t* dst = a.Y + row * a.ldy + f;
+  if (f + 8 <= a.F) {
+    *reinterpret_cast<half8_t*>(dst) = h;
+  } else if (f < a.F) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < a.F - f) dst[j] = h[j];
+  }
+}
+
 // Y[16*RT rows per wave and step] = X . W on the matrix cores, formed transposed (features x rows): a lane holds values of
 // ONE row of Y, and with the feature order of linear_load_w they are whole 16-byte pieces, four lanes to 64 consecutive
 // bytes of a row; a load of X is likewise 64 consecutive bytes of 16 rows.  NT tiles of 16 features per pass over the
@@ -189,25 +207,64 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
         if (row >= a.n) continue;
 #pragma unroll
         for (int b = 0; b < NT / 2; ++b) {
-          const int f = fc0 + 16 * NT * pass + 32 * b + 8 * q;
-          half8_t h;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            h[j] = half_t(acc[r][2 * b][j]);
-            h[4 + j] = half_t(acc[r][2 * b + 1][j]);
-          }
-          half_t* dst = a.Y + row * a.ldy + f;
-          if (f + 8 <= a.F) {
-            *reinterpret_cast<half8_t*>(dst) = h;
-          } else if (f < a.F) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-              if (j < a.F - f) dst[j] = h[j];
-          }
+          linear_store(a, row, fc0 + 16 * NT * pass + 32 * b + 8 * q, acc[r][2 * b], acc[r][2 * b + 1]);
         }
       }
     }
   }
+}
+
+// The same for few rows with many columns, where a wave of linear_kernel is one chain of loads: here KP waves share a tile of 16 rows,
+// each takes at most kSplitSteps steps of 32 columns, whose loads all go out before the weight is brought in, and the partial
+// results are added through LDS in the order of the parts.  One row block per workgroup.  Bound by the latencies of a launch, of the
+// rows and of the weight, which more lanes bring in: 19 717 x 504 -> 64 12.9 -> 10.0 us (its bytes take 4.6), 4096 x 504 -> 64 9.0 -> 6.0.
+constexpr int kSplitSteps = 10;
+
+template <int NT, int KP>
+__global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  half_t* Wf = reinterpret_cast<half_t*>(lds_raw);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, tiles = blockDim.x / (kWave * KP);
+  const int tile = wave / KP, part = wave % KP;
+  const int i = lane & 15, q = lane >> 4;
+  const int KS = a.KC / 32, per = (KS + KP - 1) / KP, s0 = part * per, sn = min(per, KS - s0);  // sn may be negative
+  const int64_t row = (int64_t(blockIdx.x) * tiles + tile) * 16 + i;
+  const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  half8_t x[kSplitSteps];
+#pragma unroll
+  for (int u = 0; u < kSplitSteps; ++u) {
+    x[u] = zero;
+    const int k = 32 * (s0 + u) + 8 * q;
+    if (u < sn && row < a.n && k < a.K) x[u] = *reinterpret_cast<const half8_t*>(a.X + row * a.ldx + k);
+  }
+  linear_load_w(a, Wf, 0, 0);
+  __syncthreads();
+  float4_t acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < kSplitSteps; ++u) {
+    if (u < sn) {  // uniform over the wave
+      const half_t* w = Wf + (int64_t(s0 + u) * kWave + lane) * 8;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8_t*>(w + int64_t(t) * KS * (kWave * 8)), x[u], acc[t], 0, 0, 0);
+    }
+  }
+  __syncthreads();  // the weight has been read: its place holds the partial results
+  float4_t* const sum = reinterpret_cast<float4_t*>(lds_raw) + lane;
+  if (part > 0) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) sum[(((part - 1) * tiles + tile) * NT + t) * kWave] = acc[t];
+  }
+  __syncthreads();
+  if (part > 0 || row >= a.n) return;
+#pragma unroll
+  for (int p = 1; p < KP; ++p)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] += sum[(((p - 1) * tiles + tile) * NT + t) * kWave];
+#pragma unroll
+  for (int b = 0; b < NT / 2; ++b) linear_store(a, row, 32 * b + 8 * q, acc[2 * b], acc[2 * b + 1]);
 }
 
 // ---- weight gradient ---------------------------------------------------------------------------------
@@ -501,22 +558,33 @@ __global__ __launch_bounds__(kBlock) void gat_feature_grad_kernel(FeatGradArgs a
 
 constexpr int kLinearLds = 152 * 1024;  // most bytes of W a workgroup keeps (of the 160 KB of a compute unit)
 
-template <int NT, int RT, bool CHUNKED>
-static hgnn_status launch_linear(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+template <void (*KERNEL)(LinearArgs)>
+static hgnn_status launch_linear_kernel(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
   // beyond 64 KB of dynamic LDS the runtime wants to be told, once per kernel and device
   static bool told[64] = {};
   if (lds > 65536) {
     int dev = 0;
     HGNN_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64 || !told[dev]) {
-      HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_kernel<NT, RT, CHUNKED>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   kLinearLds));
+      HGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, kLinearLds));
       if (dev >= 0 && dev < 64) told[dev] = true;
     }
   }
-  linear_kernel<NT, RT, CHUNKED><<<grid, threads, lds, s>>>(a);
+  KERNEL<<<grid, threads, lds, s>>>(a);
   HGNN_LAUNCH_CHECK("linear_kernel");
   return HGNN_OK;
+}
+
+template <int NT, int RT, bool CHUNKED>
+static hgnn_status launch_linear(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED>>(a, grid, threads, lds, s);
+}
+
+template <int KP>
+static hgnn_status launch_linear_split(int nt, const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (nt == 2) return launch_linear_kernel<linear_split_kernel<2, KP>>(a, grid, threads, lds, s);
+  if (nt == 4) return launch_linear_kernel<linear_split_kernel<4, KP>>(a, grid, threads, lds, s);
+  return launch_linear_kernel<linear_split_kernel<8, KP>>(a, grid, threads, lds, s);
 }
 
 static int wgrad_parts(int K, int F) {
@@ -575,6 +643,25 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   const int least = lds <= 16 * 1024 ? 1 : (lds <= 32 * 1024 ? 2 : 4);
   const int64_t tiles = ceil_div(n, int64_t(16) * RT);
   while (wpw > least && ceil_div(tiles, wpw) < kCus) wpw /= 2;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  // Few rows with many columns: as many row tiles per workgroup as give every compute unit one, and waves beside them up to 16 that
+  // share a tile's columns.  us, a chain of loads per wave / shared (inputs out of the caches):
+  //   K, F               1000        4096        8192       12000       19717       25000       32768 rows
+  //   128, 64          5.9 / 5.0   5.6 / 4.7   4.8 / 4.8   5.2 / 5.0   6.1 / 5.7   6.5 / 6.4   7.2 / 7.1
+  //   128, 128, W^T    7.2 / 5.0   7.1 / 4.7   7.5 / 5.0   8.2 / 5.4   7.4 / 6.5   8.2 / 7.9   9.1 / 8.8
+  //   256, 64          6.4 / 5.0   6.7 / 5.4   6.9 / 5.7   7.8 / 6.1   8.0 / 7.0   8.5 / 8.1   9.0 / 9.1
+  //   504, 64          8.6 / 5.5   9.0 / 6.0   9.2 / 6.6  10.9 / 8.1  12.9 / 10.0 14.0 / 12.1 13.5 / 13.3
+  //   504, 128, W^T   13.2 / 8.1  13.3 / 8.8  13.6 / 9.4  16.1 / 10.5 24.3 / 13.6 24.4 / 16.5 17.8 / 17.8
+  //   1024, 64        16.3 / 8.6  16.4 / 9.0  21.7 / 11.7 22.1 / 12.2
+  // at 40 000 rows (two rounds of workgroups) 10 to 40 % slower.
+  const int T = int(std::max<int64_t>(2, ceil_div(tiles, kCus))), KP = T <= 4 ? 4 : (T == 5 ? 3 : 2);
+  if (RT == 1 && T <= 8 && K >= 128 && k32 <= KP * kSplitSteps * 32 && F <= 128 && a.KC == k32 && a.FC == 16 * nt) {
+    const size_t need = std::max(lds, size_t(KP - 1) * size_t(T) * size_t(nt) * kWave * sizeof(float4_t));
+    const dim3 grid{unsigned(ceil_div(tiles, T)), 1u, 1u};
+    const int threads = T * KP * kWave;
+    return KP == 4 ? launch_linear_split<4>(nt, a, grid, threads, need, s)
+                   : (KP == 3 ? launch_linear_split<3>(nt, a, grid, threads, need, s) : launch_linear_split<2>(nt, a, grid, threads, need, s));
+  }
   const int fy = int(ceil_div(F, a.FC));
   const int64_t nrb = ceil_div(tiles, wpw);
   // persistent workgroups, as many as fit the chip at once, each with the same number of row blocks (to one)
@@ -583,7 +670,6 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   const int64_t want = ceil_div(nrb, per);
   HGNN_REQUIRE(want <= 0x7fffffff && fy <= 65535, HGNN_EUNSUPPORTED, "%s: grid too large", who);
   const dim3 grid{unsigned(want), unsigned(fy), 1u};
-  hipStream_t s = static_cast<hipStream_t>(stream);
   const int threads = wpw * kWave;
   if (a.KC < K) {
     if (nt == 2) return launch_linear<2, 1, true>(a, grid, threads, lds, s);

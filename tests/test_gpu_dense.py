@@ -62,6 +62,15 @@ def test_linear_dispatch_edges(hgnn, dev, n, K, F, trans):
     test_linear_shapes(hgnn, dev, n, K, F, trans, 0, 0)
 
 
+# few rows with many columns: tiles of 16 rows per workgroup and waves that share a tile's columns change with the rows
+@pytest.mark.parametrize("n,K,F,trans", [(1, 128, 2, False), (15, 136, 16, True), (17, 1280, 64, False), (31, 1288, 64, False),
+                                         (8191, 608, 42, False), (8193, 504, 64, True), (12289, 256, 128, False), (16400, 504, 32, False),
+                                         (20480, 960, 8, True), (20481, 640, 40, False), (32767, 136, 128, True), (32768, 648, 24, False),
+                                         (32769, 128, 64, False)])
+def test_linear_shared_columns(hgnn, dev, n, K, F, trans):
+    test_linear_shapes(hgnn, dev, n, K, F, trans, 0, 0)
+
+
 def test_linear_identity_and_zero_rows(hgnn, dev):
     n, K = 777, 96
     r = np.random.default_rng(5)
