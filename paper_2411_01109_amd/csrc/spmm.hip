@@ -562,7 +562,7 @@ __device__ __forceinline__ auto run_of(pos_t i0, pos_t end, int left) {
   else return RunLeft{left};
 }
 
-template <int L, int WM, bool NEAR, bool MAPPED, int HV>
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, bool RANGES>
 __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, int wid) {
   constexpr int G = kWave / L;
   typedef Round<L> Rd;
@@ -577,7 +577,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;  // idle lanes of a group load a valid address and drop the result
-  const TaskWave w = task_enter<L>(v, wid, g);
+  const TaskWave w = task_enter<L, RANGES>(v, wid, g);
   a.Y += int64_t(w.block) * a.block_y_stride;
   if (w.z1 > w.z0) {
     const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -701,9 +701,9 @@ template <int L, int WM, bool NEAR, bool MAPPED, int HV, bool LOOP>
 __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
   if (LOOP) {
     const int n = task_waves<kWave / L>(v);
-    for (int wid = blockIdx.x; wid < n; wid += gridDim.x) spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, wid);
+    for (int wid = blockIdx.x; wid < n; wid += gridDim.x) spmm_task<L, WM, NEAR, MAPPED, HV, false>(a, v, ncols, wid);
   } else {
-    spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, blockIdx.x);
+    spmm_task<L, WM, NEAR, MAPPED, HV, true>(a, v, ncols, blockIdx.x);
   }
 }
 

@@ -158,11 +158,12 @@ struct TaskWave {
 
 // wid is the same on all lanes of the wave; g = lane / L.  Everything up to the task is scalar; a choice between two addresses to
 // load from would turn all of it into vector code (5.5 M non-zeros, SDDMM 58 -> 62 us, attention forward 82 -> 87).
-template <int L>
+// RANGES: there may be pieces of rows cut at column ranges (never where the numbers are on the device).
+template <int L, bool RANGES = true>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
   constexpr int G = kWave / L;
   TaskWave w;
-  if (wid < v.first_wave[0]) {  // never where the numbers are on the device
+  if (RANGES && wid < v.first_wave[0]) {
     const int i = (wid >> 3) * G + g, k = (wid & 7) * v.rshare + i;
     int4_t t = {0, 0, -1, -1};
     if (k < v.n_rtask) t = v.rtask[k];

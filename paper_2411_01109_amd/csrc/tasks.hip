@@ -38,11 +38,13 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
   return c;
 }
 
-// counts[q][b][window]
+// counts[q][b][window]; RANGES: long rows are counted, too, and left out of the others
+template <bool RANGES>
 __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, int nwin, int* __restrict__ counts) {
+  constexpr int counters = RANGES ? kTaskAll : kTaskCounters;
   __shared__ int total[kTaskAll];
   const int b = blockIdx.y;
-  const int counters = q.range_min == kNoRanges ? kTaskCounters : kTaskAll;
+  if (!RANGES) q.range_min = kNoRanges;
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
   if (threadIdx.x < kTaskAll) total[threadIdx.x] = 0;
   __syncthreads();
@@ -59,7 +61,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, 
       n[kTaskSlots] += c.m;
     }
   }
-  for (int i = 0; i < kTaskAll; ++i) {
+  for (int i = 0; i < counters; ++i) {
     int v = n[i];
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
@@ -132,6 +134,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
   __shared__ int before[kTaskCounters], all[kTaskCounters];
   hgnn_task_sec s;
   if (SELF) {
+    q.range_min = kNoRanges;
     if (threadIdx.x < kTaskCounters) before[threadIdx.x] = all[threadIdx.x] = 0;
     __syncthreads();
     int b4[kTaskCounters] = {0, 0, 0, 0, 0}, sum[kTaskCounters] = {0, 0, 0, 0, 0};
@@ -241,7 +244,9 @@ hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s) {
   c.long_at = counts + size_t(kTaskLong) * size_t(q.nb) * size_t(nwin);
   c.n_long = sums + size_t(kTaskLong) * size_t(q.nb);
   c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(sec + q.nb);
-  if (nwin > 0) task_count_kernel<<<dim3(unsigned(nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, nwin, counts);
+  const dim3 grid(unsigned(nwin), unsigned(q.nb));
+  if (nwin > 0 && q.range_min == kNoRanges) task_count_kernel<false><<<grid, kTaskThreads, 0, s>>>(q, nwin, counts);
+  else if (nwin > 0) task_count_kernel<true><<<grid, kTaskThreads, 0, s>>>(q, nwin, counts);
   task_scan_kernel<<<1, kTaskThreads, 0, s>>>(q, nwin, counts, sums, sec, c.totals);
   HGNN_LAUNCH_CHECK("task_count_kernel / task_scan_kernel");
   return HGNN_OK;
@@ -331,7 +336,7 @@ TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F
 
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
-  task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
+  task_count_kernel<false><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
   task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow,
                                                                             t.split);
   HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
