@@ -1,0 +1,230 @@
+// Stable radix sort of 64-bit words for the set-up calls: digits of up to nine bits, two or three launches a pass (digits of every tile
+// counted, counts scanned over the tiles where there are many, tiles sorted in LDS and written in runs).  The first pass forms its words from whatever the
+// caller has, so no array of keys is written and read beforehand.  No workgroup waits for another one.
+#pragma once
+
+#include "common.h"
+
+namespace hgnn {
+
+constexpr int kSortThreads = 1024, kSortPer = 8, kSortTile = kSortThreads * kSortPer;
+constexpr int kSortBits = 9, kSortBins = 1 << kSortBits;
+constexpr int kSortWaves = kSortThreads / kWave;
+constexpr int kFewTiles = 64;  // up to so many, every tile adds up the counts itself: a launch less a pass, 4 to 5 us
+
+struct SortPass {
+  int64_t n;
+  int shift, bits;
+  int ntiles;
+  uint32_t* counts;  // [ntiles][kSortBins] items of a tile in every bin, then items of the earlier tiles there
+  uint32_t* totals;  // [kSortBins]
+  __device__ __forceinline__ int digit(uint64_t w) const { return int(uint32_t(w >> shift) & ((1u << bits) - 1u)); }
+};
+
+// Sources of words: load(k, scratch) after prepare(first, n, scratch) by the whole workgroup, whose tile begins at item `first`;
+// scratch is kSortTile ints of LDS.  count(k) is a word with the same digit.
+struct SortWords {
+  const uint64_t* words;
+  __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
+  __device__ __forceinline__ uint64_t load(int64_t k, int, const int*) const { return words[k]; }
+  __device__ __forceinline__ uint64_t count(int64_t k) const { return words[k]; }
+};
+
+// Bound by the read of the items.  Lanes of a wave often meet in one bin (behind a pass over the low bits of a column, the entries of a
+// popular column): eight copies of the counts, 17 -> 10.5 us for 5.5 M words of a power-law graph.
+constexpr int kSortCopies = 8, kSortPitch = kSortBins + 1;
+
+template <class Source>
+__global__ __launch_bounds__(kSortThreads) void sort_count_kernel(SortPass p, Source src) {
+  __shared__ uint32_t hist[kSortCopies * kSortPitch];
+  for (int i = threadIdx.x; i < kSortCopies * kSortPitch; i += kSortThreads) hist[i] = 0;
+  __syncthreads();
+  const int64_t first = int64_t(blockIdx.x) * kSortTile + threadIdx.x;
+  int d[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int64_t k = first + j * kSortThreads;
+    d[j] = -1;
+    if (k < p.n) d[j] = p.digit(src.count(k));
+  }
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j)
+    if (d[j] >= 0) atomicAdd(&hist[(threadIdx.x % kSortCopies) * kSortPitch + d[j]], 1u);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSortBins; i += kSortThreads) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int c = 0; c < kSortCopies; ++c) v += hist[c * kSortPitch + i];
+    p.counts[int64_t(blockIdx.x) * kSortBins + i] = v;
+  }
+}
+
+// exclusive scan of the counts of every bin over the tiles, in place: a workgroup takes 16 bins, its 64 slices a share of the tiles each
+constexpr int kScanBins = 16, kScanSlices = kSortThreads / kScanBins;
+
+__global__ __launch_bounds__(kSortThreads) static void sort_scan_kernel(SortPass p) {
+  __shared__ uint32_t sums[kScanSlices][kScanBins];
+  const int x = threadIdx.x % kScanBins, y = threadIdx.x / kScanBins;
+  const int per = (p.ntiles + kScanSlices - 1) / kScanSlices, t0 = y * per, t1 = min(t0 + per, p.ntiles);
+  uint32_t* const c = p.counts + blockIdx.x * kScanBins + x;
+  uint32_t s = 0;
+#pragma unroll 8
+  for (int t = t0; t < t1; ++t) s += c[int64_t(t) * kSortBins];
+  sums[y][x] = s;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int i = 0; i < y; ++i) before += sums[i][x];
+  if (y == kScanSlices - 1) p.totals[blockIdx.x * kScanBins + x] = before + s;
+#pragma unroll 8
+  for (int t = t0; t < t1; ++t) {
+    const uint32_t v = c[int64_t(t) * kSortBins];
+    c[int64_t(t) * kSortBins] = before;
+    before += v;
+  }
+}
+
+// exclusive scan over the first kSortBins threads of the workgroup; every thread calls it
+__device__ __forceinline__ uint32_t sort_bin_scan(uint32_t v, uint32_t* s_wave) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t incl = v;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const uint32_t t = __shfl_up(incl, d);
+    if (lane >= d) incl += t;
+  }
+  __syncthreads();  // what a previous scan left has been read
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave && w < kSortBins / kWave; ++w) before += s_wave[w];
+  return before + incl - v;
+}
+
+// A tile: every wave ranks its 512 consecutive items by digit (lanes of equal digit find each other by ballots, so the order of equal
+// digits is kept), the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
+// items of the tile are a run of 16 on average.  5.5 M words: 27.5 us (3.2 TB/s of reads and writes; half of it vector instructions of
+// the ranks), a pass 44 with its count and scan, where a library pass with look-back and its two fills took 52; the words that the first
+// pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 221 us, transpose 180 -> 127; 50 000 words,
+// which a library merge sort was faster for, 77 -> 70 and 70 -> 52.
+template <class Source>
+__global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass p, Source src, uint64_t* __restrict__ out) {
+  __shared__ __align__(16) unsigned char lds[kSortTile * sizeof(uint64_t)];
+  __shared__ uint32_t s_to[kSortBins];  // where the first item of a bin goes, less its place in the tile
+  __shared__ uint32_t s_at[kSortBins];  // place of a bin's first item in the tile
+  __shared__ uint32_t s_wave[kSortWaves];
+  int* const scratch = reinterpret_cast<int*>(lds);
+  uint16_t (*const hist)[kSortBins] = reinterpret_cast<uint16_t (*)[kSortBins]>(lds);
+  uint64_t* const item = reinterpret_cast<uint64_t*>(lds);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t first = int64_t(blockIdx.x) * kSortTile;
+  const int n = int(p.n - first < kSortTile ? p.n - first : kSortTile);
+  const int bin = threadIdx.x;
+  uint32_t total = 0, earlier = 0;
+  if (bin < kSortBins) {
+    if (p.ntiles <= kFewTiles) {
+#pragma unroll 8
+      for (int t = 0; t < p.ntiles; ++t) {
+        const uint32_t c = p.counts[t * kSortBins + bin];
+        total += c;
+        earlier += t < int(blockIdx.x) ? c : 0;
+      }
+    } else {
+      total = p.totals[bin];
+      earlier = p.counts[int64_t(blockIdx.x) * kSortBins + bin];
+    }
+  }
+  src.prepare(first, n, scratch);
+  uint64_t w[kSortPer];
+  const int mine = wave * (kWave * kSortPer) + lane;
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = mine + j * kWave;
+    w[j] = ~uint64_t(0);  // behind all items of the last bin
+    if (i < n) w[j] = src.load(first + i, i, scratch);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSortWaves * kSortBins / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(lds)[i] = 0;
+  __syncthreads();
+  uint32_t rank[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int d = p.digit(w[j]);
+    uint32_t lo = ~0u, hi = ~0u;  // lanes whose digit agrees so far
+#pragma unroll
+    for (int b = 0; b < kSortBits; ++b) {
+      const uint32_t bit = uint32_t(__builtin_amdgcn_sbfe(d, b, 1));  // 0 or all ones
+      const uint64_t ones = __ballot(bit != 0);
+      lo &= ~(uint32_t(ones) ^ bit);
+      hi &= ~(uint32_t(ones >> 32) ^ bit);
+    }
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    const uint32_t before = hist[wave][d];
+    rank[j] = before + below;
+    wave_sync();
+    if (below == 0) hist[wave][d] = uint16_t(before + __popc(lo) + __popc(hi));
+    wave_sync();
+  }
+  __syncthreads();
+  uint32_t here = 0;
+  if (bin < kSortBins) {
+#pragma unroll
+    for (int v = 0; v < kSortWaves; ++v) {
+      const uint32_t c = hist[v][bin];
+      hist[v][bin] = uint16_t(here);
+      here += c;
+    }
+  }
+  const uint32_t at = sort_bin_scan(here, s_wave);
+  const uint32_t base = sort_bin_scan(total, s_wave);
+  if (bin < kSortBins) {
+    s_at[bin] = at;
+    s_to[bin] = base + earlier - at;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int d = p.digit(w[j]);
+    rank[j] += s_at[d] + hist[wave][d];
+  }
+  __syncthreads();  // the items take the place of the counts
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) item[rank[j]] = w[j];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = j * kSortThreads + threadIdx.x;
+    if (i >= n) break;
+    const uint64_t v = item[i];
+    out[s_to[p.digit(v)] + uint32_t(i)] = v;
+  }
+}
+
+inline size_t sort_scratch_bytes(int64_t n) { return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortTile)) + 1); }
+
+// Sorts n >= 1 words by their bits [first, last).  The words come from src; the sorted ones are in the returned one of the two buffers.
+template <class Source>
+static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, uint64_t* buf0, uint64_t* buf1, void* scratch, hipStream_t s) {
+  SortPass p{};
+  p.n = n;
+  p.ntiles = int(ceil_div(n, kSortTile));
+  p.totals = static_cast<uint32_t*>(scratch);
+  p.counts = p.totals + kSortBins;
+  const int bits = last - first, npass = (bits + kSortBits - 1) / kSortBits;
+  const dim3 grid{unsigned(p.ntiles)};
+  uint64_t *in = buf1, *out = buf0;
+  p.shift = first;
+  for (int i = 0; i < npass; ++i) {
+    p.bits = (last - p.shift + npass - i - 1) / (npass - i);
+    if (i == 0) sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, src);
+    else sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in});
+    if (p.ntiles > kFewTiles) sort_scan_kernel<<<kSortBins / kScanBins, kSortThreads, 0, s>>>(p);
+    if (i == 0) sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, src, out);
+    else sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in}, out);
+    p.shift += p.bits;
+    in = out;
+    out = in == buf0 ? buf1 : buf0;
+  }
+  return in;
+}
+
+}  // namespace hgnn

@@ -1,12 +1,13 @@
 // CSR of the transposed graph plus the edge-id map, for the backward SpMM dX <- A_w^T dY
 // (paper section 2.1.2), and CSR from a COO edge list (section 2.1.1).  One-off set-up: a stable radix sort of
-// the non-zeros by column id, or by (row id, column id) (rocPRIM's device radix sort is the library step), then
-// offsets by binary search.
+// the non-zeros by column id, or by (row id, column id), as words that carry everything (sort.h); where the fields do not fit 64 bits,
+// keys and positions go through rocPRIM's device radix sort.
 #include <string.h>
 
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "common.h"
+#include "sort.h"
 
 namespace hgnn {
 
@@ -24,28 +25,73 @@ __global__ void offsets_kernel(const Key* __restrict__ sorted, int shift, int64_
   rowptr_T[j] = int(lo);
 }
 
-// COO -> CSR: key = (row, col, list position) packed into one 64-bit word (position_bits = 0: without it), so that one
-// stable sort of the leading fields orders the edges by row, then column, then position in the list; bad receives 1 when
-// an id is out of range (such an edge gets row and column 0)
-__global__ void coo_keys_kernel(const int* __restrict__ row, const int* __restrict__ col, int64_t nnz, int nrows, int ncols, int col_bits,
-                                int position_bits, uint64_t* __restrict__ keys, int* __restrict__ ids, int* __restrict__ bad) {
+// COO -> CSR: a word is (row, col, list position) (position_bits = 0: without it), so that one stable sort of the leading fields
+// orders the edges by row, then column, then position in the list; bad receives 1 when an id is out of range (such an edge gets row and
+// column 0)
+struct CooWords {
+  const int *row, *col;
+  int nrows, ncols, col_bits, position_bits;
+  int* bad;
+  __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
+  __device__ __forceinline__ uint64_t word(int64_t k, bool& ok) const {
+    const int r = row[k], c = col[k];
+    ok = r >= 0 && r < nrows && c >= 0 && c < ncols;
+    const uint64_t rc = ok ? (uint64_t(uint32_t(r)) << col_bits) | uint64_t(uint32_t(c)) : 0;
+    return position_bits ? (rc << position_bits) | uint64_t(k) : rc;
+  }
+  __device__ __forceinline__ uint64_t load(int64_t k, int, const int*) const {
+    bool ok;
+    const uint64_t w = word(k, ok);
+    if (!ok) *bad = 1;
+    return w;
+  }
+  __device__ __forceinline__ uint64_t count(int64_t k) const {
+    bool ok;
+    return word(k, ok);
+  }
+};
+
+// the same in two arrays where the three fields do not fit 64 bits
+__global__ void coo_keys_kernel(CooWords w, int64_t nnz, uint64_t* __restrict__ keys, int* __restrict__ ids) {
   int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= nnz) return;
-  const int r = row[k], c = col[k];
-  const bool ok = r >= 0 && r < nrows && c >= 0 && c < ncols;
-  if (!ok) atomicOr(bad, 1);
-  const uint64_t rc = ok ? (uint64_t(uint32_t(r)) << col_bits) | uint64_t(uint32_t(c)) : 0;
-  keys[k] = position_bits ? (rc << position_bits) | uint64_t(k) : rc;
-  if (ids) ids[k] = int(k);
+  keys[k] = w.load(k, 0, nullptr);
+  ids[k] = int(k);
 }
 
-__global__ void coo_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int col_bits, int position_bits,
-                                 int* __restrict__ col_out, int* __restrict__ eid) {
-  int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (k >= nnz) return;
-  const uint64_t key = keys[k];
-  col_out[k] = int(uint32_t(key >> position_bits) & ((uint32_t(1) << col_bits) - 1u));
-  if (eid) eid[k] = int(uint32_t(key) & ((uint32_t(1) << position_bits) - 1u));
+// Sorted words taken apart: the low `position_bits` to pos (may be null), the next `id_bits` to id, and offset[r] = number of words
+// whose leading `lead_bits` are < r, for r = 0 .. nlead.  The workgroup that holds the first word of a row writes that row's offset and
+// those of the empty rows before it, long stretches of them with all its threads.  Bound by memory: 17.2 us for 5.5 M words (5.1 TB/s).
+__global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __restrict__ words, int64_t nnz, int position_bits, int id_bits,
+                                                            int lead_bits, int nlead, int* __restrict__ id, int* __restrict__ pos,
+                                                            int* __restrict__ offset) {
+  constexpr int kAlone = 16;
+  __shared__ int s_n, s_gap[kBlock + 1][3];
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  const int64_t k = blockIdx.x * int64_t(kBlock) + threadIdx.x;
+  auto lead_of = [&](uint64_t w) { return int(min(uint64_t(nlead), (w >> (position_bits + id_bits)) & ((uint64_t(1) << lead_bits) - 1))); };
+  auto fill = [&](int from, int to, int64_t v) {  // offset[from .. to] = v
+    if (to - from < kAlone) {
+      for (int r = from; r <= to; ++r) offset[r] = int(v);
+    } else {
+      const int i = atomicAdd(&s_n, 1);
+      s_gap[i][0] = from;
+      s_gap[i][1] = to;
+      s_gap[i][2] = int(v);
+    }
+  };
+  if (k < nnz) {
+    const uint64_t w = words[k];
+    id[k] = int(uint32_t(w >> position_bits) & ((uint32_t(1) << id_bits) - 1u));
+    if (pos) pos[k] = int(uint32_t(w) & ((uint32_t(1) << position_bits) - 1u));
+    const int r = lead_of(w), q = k > 0 ? lead_of(words[k - 1]) : -1;
+    if (r > q) fill(q + 1, r, k);
+    if (k == nnz - 1 && r < nlead) fill(r + 1, nlead, nnz);
+  }
+  __syncthreads();
+  for (int i = 0; i < s_n; ++i)
+    for (int r = s_gap[i][0] + int(threadIdx.x); r <= s_gap[i][1]; r += kBlock) offset[r] = s_gap[i][2];
 }
 
 // The row of every non-zero, handed to put(k, row): a workgroup takes kExpand consecutive positions, its rows mark the slot
@@ -55,17 +101,37 @@ __global__ void coo_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz,
 constexpr int kExpandPerThread = 8;
 constexpr int kExpand = kBlock * kExpandPerThread;
 
-template <class Put>
-__device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int nrows, int64_t nnz, Put&& put) {
-  __shared__ int s_row[kExpand];
-  __shared__ int s_max[kBlock / kWave], s_lim[2];
-  const int64_t e0 = int64_t(blockIdx.x) * kExpand;
-  const int n = int(nnz - e0 < kExpand ? nnz - e0 : kExpand);
-  if (threadIdx.x < 2) s_lim[threadIdx.x] = row_of_edge(rowptr, nrows, threadIdx.x == 0 ? e0 : e0 + n - 1);
-  for (int i = threadIdx.x; i < kExpand; i += kBlock) s_row[i] = -1;
+// row_of_edge by a whole wave, 64 places looked at in each step; every entry is read inside the array whatever it holds
+__device__ __forceinline__ int wave_row_of_edge(const int* __restrict__ rowptr, int nrows, int64_t k) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int64_t lo = 0, hi = int64_t(nrows) + 1;  // the first entry above k is in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave, at = lo + lane * step;
+    const int not_above = __popcll(__ballot(at < hi && int64_t(rowptr[at]) <= k));
+    // in an ascending array those lanes are the first ones
+    if (not_above == 0) {
+      hi = lo;
+    } else {
+      const int64_t last = lo + (not_above - 1) * step;  // not above
+      hi = last + step < hi ? last + step : hi;
+      lo = last + 1;
+    }
+  }
+  return int(lo) - 1;
+}
+
+// s_row[i] = row of position e0 + i, i < n <= 8 THREADS; the workgroup has been waited for at the end
+template <int THREADS>
+__device__ __forceinline__ void expand_tile(const int* __restrict__ rowptr, int nrows, int64_t e0, int n, int* s_row) {
+  __shared__ int s_max[THREADS / kWave], s_lim[2];
+  if (threadIdx.x < 2 * kWave) {
+    const int w = threadIdx.x / kWave, r = wave_row_of_edge(rowptr, nrows, w == 0 ? e0 : e0 + n - 1);
+    if ((threadIdx.x & (kWave - 1)) == 0) s_lim[w] = r;
+  }
+  for (int i = threadIdx.x; i < THREADS * kExpandPerThread; i += THREADS) s_row[i] = -1;
   __syncthreads();
   const int lo = max(s_lim[0], 0), hi = min(s_lim[1], nrows - 1);
-  for (int r = lo + 1 + int(threadIdx.x); r <= hi; r += kBlock) {
+  for (int r = lo + 1 + int(threadIdx.x); r <= hi; r += THREADS) {
     const int p = rowptr[r];
     const int64_t at = int64_t(p) - e0;
     if (rowptr[r + 1] > p && at >= 0 && at < n) s_row[at] = r;
@@ -92,26 +158,28 @@ __device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int 
 #pragma unroll
   for (int j = 0; j < kExpandPerThread; ++j) s_row[threadIdx.x * kExpandPerThread + j] = max(v[j], excl);
   __syncthreads();
+}
+
+template <class Put>
+__device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int nrows, int64_t nnz, Put&& put) {
+  __shared__ int s_row[kExpand];
+  const int64_t e0 = int64_t(blockIdx.x) * kExpand;
+  const int n = int(nnz - e0 < kExpand ? nnz - e0 : kExpand);
+  expand_tile<kBlock>(rowptr, nrows, e0, n, s_row);
   for (int i = threadIdx.x; i < n; i += kBlock) put(e0 + i, s_row[i]);
 }
 
-// transposition keys: (column, row, position) packed into one word; sorting the columns' bits brings everything along
-__global__ __launch_bounds__(kBlock) void transpose_keys_kernel(const int* __restrict__ rowptr, const int* __restrict__ col, int nrows,
-                                                                int64_t nnz, int row_bits, int position_bits,
-                                                                uint64_t* __restrict__ keys) {
-  expand_rows(rowptr, nrows, nnz, [&](int64_t k, int r) {
-    keys[k] = (((uint64_t(uint32_t(col[k])) << row_bits) | uint64_t(uint32_t(r))) << position_bits) | uint64_t(k);
-  });
-}
-
-__global__ void transpose_split_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int row_bits, int position_bits,
-                                       int* __restrict__ col_T, int* __restrict__ eid_T) {
-  int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (k >= nnz) return;
-  const uint64_t key = keys[k];
-  eid_T[k] = int(uint32_t(key) & ((uint32_t(1) << position_bits) - 1u));
-  col_T[k] = int(uint32_t(key >> position_bits) & ((uint32_t(1) << row_bits) - 1u));
-}
+// transposition: a word is (column, row, position); sorting the columns' bits brings everything along
+struct TransposeWords {
+  const int *rowptr, *col;
+  int nrows, row_bits, position_bits;
+  static_assert(kSortPer == kExpandPerThread, "a tile is expanded by its workgroup");
+  __device__ __forceinline__ void prepare(int64_t first, int n, int* s_row) const { expand_tile<kSortThreads>(rowptr, nrows, first, n, s_row); }
+  __device__ __forceinline__ uint64_t load(int64_t k, int i, const int* s_row) const {
+    return (((uint64_t(uint32_t(col[k])) << row_bits) | uint64_t(uint32_t(s_row[i]))) << position_bits) | uint64_t(k);
+  }
+  __device__ __forceinline__ uint64_t count(int64_t k) const { return uint64_t(uint32_t(col[k])) << (row_bits + position_bits); }
+};
 
 // the same in two arrays where the three fields do not fit 64 bits: column keys with positions; rows of all positions
 __global__ __launch_bounds__(kBlock) void transpose_rows_kernel(const int* __restrict__ rowptr, const int* __restrict__ col, int nrows,
@@ -163,26 +231,6 @@ __global__ void edge_gather_kernel(const int* __restrict__ eid, int64_t total, i
   out[j] = in[int64_t(eid[k]) * H + (j - k * H)];
 }
 
-// Sort of 64-bit words by the bits [first, last), workgroups of 1024 lanes with eight words each.  A pass moves every word
-// once however many bits it takes (43 us for 5.5 M words), so digits of nine bits where they save a pass over digits of
-// eight: 36 bits in four passes instead of five, 18 in two instead of three (5.5 M edges: list to CSR 330 -> 280 us,
-// transpose 235 -> 183).
-// Below 200 000 words a sort by merging is faster where a list takes four passes (us, merging / digits: list to CSR 0.05 M 88 / 121,
-// 0.13 M 102 / 125, 0.2 M 114 / 129, 0.4 M 167 / 136; transpose, two passes, 82 / 92, 101 / 90, 109 / 89, 165 / 95).
-static hipError_t sort_words(void* tmp, size_t& tmp_bytes, rocprim::double_buffer<uint64_t>& keys, unsigned n, unsigned first,
-                             unsigned last, hipStream_t s) {
-  using rocprim::default_config;
-  using rocprim::kernel_config;
-  constexpr auto rank = rocprim::block_radix_rank_algorithm::match;
-  using Eight = rocprim::radix_sort_onesweep_config<kernel_config<512, 12>, kernel_config<1024, 8>, 8, rank>;
-  using Nine = rocprim::radix_sort_onesweep_config<kernel_config<512, 12>, kernel_config<1024, 8>, 9, rank>;
-  constexpr size_t merge_below = 200000;
-  const unsigned bits = last - first;
-  if ((bits + 8) / 9 < (bits + 7) / 8)
-    return rocprim::radix_sort_keys<rocprim::radix_sort_config<default_config, default_config, Nine, merge_below>>(tmp, tmp_bytes, keys, n, first, last, s);
-  return rocprim::radix_sort_keys<rocprim::radix_sort_config<default_config, default_config, Eight, merge_below>>(tmp, tmp_bytes, keys, n, first, last, s);
-}
-
 }  // namespace hgnn
 
 using namespace hgnn;
@@ -211,17 +259,12 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
   if (col_bits + row_bits + pos_bits <= 64) {
     // one word per non-zero carries its row and position through a sort of the columns alone: no gather afterwards
     for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(8 * size_t(E));
-    rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
-    const unsigned first = unsigned(row_bits + pos_bits), last = first + unsigned(col_bits);
-    if (e == hipSuccess) e = sort_words(nullptr, tmp_bytes, keys, unsigned(E), first, last, s);
-    if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
+    if (e == hipSuccess) e = tmp.alloc(sort_scratch_bytes(E));
     if (e == hipSuccess) {
-      transpose_keys_kernel<<<per_tile, kBlock, 0, s>>>(g->rowptr, g->col, g->nrows, E, row_bits, pos_bits, keys.current());
-      e = sort_words(tmp.p, tmp_bytes, keys, unsigned(E), first, last, s);
-    }
-    if (e == hipSuccess) {
-      transpose_split_kernel<<<per_edge, kBlock, 0, s>>>(keys.current(), E, row_bits, pos_bits, col_T, eid_T);
-      offsets_kernel<uint64_t><<<per_col, kBlock, 0, s>>>(keys.current(), int(first), E, g->ncols, rowptr_T);
+      const int first = row_bits + pos_bits;
+      const uint64_t* words = sort_words(TransposeWords{g->rowptr, g->col, g->nrows, row_bits, pos_bits}, E, first, first + col_bits,
+                                         buf[0].as<uint64_t>(), buf[1].as<uint64_t>(), tmp.p, s);
+      split_words_kernel<<<per_edge, kBlock, 0, s>>>(words, E, pos_bits, row_bits, col_bits, g->ncols, col_T, eid_T, rowptr_T);
       e = hipGetLastError();
     }
   } else {
@@ -264,7 +307,7 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
     return HGNN_OK;
   }
   const int row_bits = bits_for(nrows), col_bits = bits_for(ncols), pos_bits = bits_for(nnz);
-  const dim3 per_edge(unsigned(ceil_div(nnz, kBlock))), per_row(unsigned(ceil_div(int64_t(nrows) + 1, kBlock)));
+  const dim3 per_edge(unsigned(ceil_div(nnz, kBlock)));
   const size_t E = size_t(nnz);
   DevTemp buf[2] = {DevTemp(s), DevTemp(s)}, ids[2] = {DevTemp(s), DevTemp(s)}, bad(s), tmp(s);
   HostMail mail(s);
@@ -274,33 +317,40 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
   const bool packed = !eid || row_bits + col_bits + pos_bits <= 64;
   const int in_key = packed && eid ? pos_bits : 0;
   const unsigned first = unsigned(in_key), last = first + unsigned(row_bits + col_bits);
-  hipError_t e = bad.alloc(4);
+  // the flag is host memory where there is a slot: one copy and one fill less
+  int* flag = reinterpret_cast<int*>(mail.data);
+  hipError_t e = hipSuccess;
+  if (flag) *flag = 0;
+  else e = bad.alloc(4);
   for (int i = 0; i < 2 && e == hipSuccess; ++i) e = buf[i].alloc(8 * E);
   for (int i = 0; i < 2 && e == hipSuccess && !packed; ++i) e = ids[i].alloc(4 * E);
   rocprim::double_buffer<uint64_t> keys(buf[0].as<uint64_t>(), buf[1].as<uint64_t>());
   rocprim::double_buffer<int> order(ids[0].as<int>(), ids[1].as<int>());
-  auto sort = [&](void* t) {
-    return packed ? sort_words(t, tmp_bytes, keys, unsigned(E), first, last, s)
-                  : rocprim::radix_sort_pairs(t, tmp_bytes, keys, order, unsigned(E), first, last, s);
-  };
-  if (e == hipSuccess) e = sort(nullptr);
+  auto sort_pairs = [&](void* t) { return rocprim::radix_sort_pairs(t, tmp_bytes, keys, order, unsigned(E), first, last, s); };
+  if (packed) tmp_bytes = sort_scratch_bytes(nnz);
+  else if (e == hipSuccess) e = sort_pairs(nullptr);
   if (e == hipSuccess) e = tmp.alloc(tmp_bytes);
-  if (e == hipSuccess) e = hipMemsetAsync(bad.p, 0, 4, s);
+  if (e == hipSuccess && !flag) e = hipMemsetAsync(bad.p, 0, 4, s);
   if (e == hipSuccess) {
-    coo_keys_kernel<<<per_edge, kBlock, 0, s>>>(row, col, nnz, nrows, ncols, col_bits, in_key, keys.current(),
-                                                packed ? nullptr : order.current(), bad.as<int>());
-    e = sort(tmp.p);
-  }
-  if (e == hipSuccess) {
-    coo_split_kernel<<<per_edge, kBlock, 0, s>>>(keys.current(), nnz, col_bits, in_key, col_out, packed ? eid : nullptr);
-    offsets_kernel<uint64_t><<<per_row, kBlock, 0, s>>>(keys.current(), in_key + col_bits, nnz, nrows, rowptr);
-    e = hipGetLastError();
+    const CooWords src{row, col, nrows, ncols, col_bits, in_key, flag ? flag : bad.as<int>()};
+    const uint64_t* words = nullptr;
+    if (packed) {
+      words = sort_words(src, nnz, int(first), int(last), buf[0].as<uint64_t>(), buf[1].as<uint64_t>(), tmp.p, s);
+    } else {
+      coo_keys_kernel<<<per_edge, kBlock, 0, s>>>(src, nnz, keys.current(), order.current());
+      e = sort_pairs(tmp.p);
+      words = keys.current();
+    }
+    if (e == hipSuccess) {
+      split_words_kernel<<<per_edge, kBlock, 0, s>>>(words, nnz, in_key, col_bits, row_bits, nrows, col_out, packed ? eid : nullptr, rowptr);
+      e = hipGetLastError();
+    }
   }
   if (e == hipSuccess && !packed) e = hipMemcpyAsync(eid, order.current(), 4 * E, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(mail.data ? static_cast<void*>(mail.data) : &hbad, bad.p, 4, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && !flag) e = hipMemcpyAsync(&hbad, bad.p, 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = s.wait();
   if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? HGNN_ENOMEM : HGNN_EHIP, "%s: %s", who, hipGetErrorString(e));
-  if (mail.data) hbad = *reinterpret_cast<const int*>(mail.data);
+  if (flag) hbad = *static_cast<volatile const int*>(flag);
   if (hbad) return fail(HGNN_EINVAL, "%s: a row id outside [0, nrows) or a column id outside [0, ncols)", who);
   return HGNN_OK;
 }

@@ -42,6 +42,33 @@ def test_sort_keys(hgnn, dev, V, E):
     check_lists(hgnn, dev, V, row, col)
 
 
+# a tile of the sort is 8192 words, up to 64 tiles add up their counts themselves; digits of 1 to 9 bits
+@pytest.mark.parametrize("V,E", [(2, 8191), (512, 8192), (513, 8193), (1 << 18, 64 * 8192), ((1 << 18) + 1, 64 * 8192 + 1), (37, 600000),
+                                 (1 << 20, 1200000)])
+def test_sort_tiles(hgnn, dev, V, E):
+    print(f"setup tiles V={V} E={E}", flush=True)
+    r = np.random.default_rng(V + E)
+    row, col = (r.integers(0, V, E).astype(np.int32) for _ in range(2))
+    row[E // 2:E // 2 + E // 5] = V - 1  # a hub in the last row, long stretches of empty rows beside it
+    row[row > V * 3 // 4] = V - 1
+    col[: E // 8] = col[0]
+    check_lists(hgnn, dev, V, row, col)
+
+
+@pytest.mark.parametrize("E", [1, 8193, 700000])
+def test_ids_out_of_range(hgnn, dev, E):
+    V = 1000
+    r = np.random.default_rng(E)
+    for which, bad in ((0, -1), (0, V), (1, -5), (1, 1 << 30)):
+        ids = [r.integers(0, V, E).astype(np.int32) for _ in range(2)]
+        ids[which][E - 1] = bad
+        with pytest.raises(hgnn.HgnnError) as e:
+            hgnn.hgnn_coo_to_csr(up(ids[0], dev), up(ids[1], dev), V, V)
+        assert "outside" in str(e.value)
+        ids[which][E - 1] = 0
+        check_lists(hgnn, dev, V, ids[0], ids[1])
+
+
 def test_plan_lists(hgnn, dev):
     """Rows shorter and longer than every threshold of a plan, empty rows between them."""
     r = np.random.default_rng(3)
