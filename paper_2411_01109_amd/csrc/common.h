@@ -167,6 +167,19 @@ __device__ __forceinline__ float dpp_add(float v) {
   return v + __int_as_float(t);
 }
 
+// sum over the wave on all lanes, vector instructions only
+__device__ __forceinline__ int wave_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);
+  typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+  uint2_t r = __builtin_amdgcn_permlane16_swap(unsigned(v), unsigned(v), false, false);
+  v = int(r[0] + r[1]);
+  r = __builtin_amdgcn_permlane32_swap(unsigned(v), unsigned(v), false, false);
+  return int(r[0] + r[1]);
+}
+
 // All-reduce (sum) over the LH consecutive, LH-aligned lanes of a head; LH is a power of two.  After the
 // quads are summed, a mirror inside 8 (16) lanes pairs every lane with one of the other quad (half), whose
 // partial sum is the same on all its lanes; beyond a row of 16 lanes the exchange goes through ds_bpermute.
@@ -411,20 +424,25 @@ struct TaskScratch {
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
 struct TaskCounts {
-  explicit TaskCounts(SetupStream& s) : counts(s), sec(s), ranges(s), mail(s) {}
-  DevTemp counts, sec, ranges;
+  explicit TaskCounts(SetupStream& s) : counts(s), secs(s), ranges(s), mail(s) {}
+  DevTemp counts, secs, ranges;
   HostMail mail;
+  int nwin = 0;
+  int* count = nullptr;          // device, [kTaskAll][nb][nwin]
+  int* sums = nullptr;           // device, [kTaskAll][nb]
+  hgnn_task_sec* sec = nullptr;  // device, [nb]
   TaskTotals* totals = nullptr;  // valid after the stream has been waited for (host memory, or a device copy)
-  const int* long_at = nullptr;  // device, [windows] long rows before each window of kTaskWindow rows, and
+  TaskTotals got{};              // the same on the host, from task_allocate on
+  const int* long_at = nullptr;  // device, [nwin] long rows before each window of kTaskWindow rows, and
   const int* n_long = nullptr;   // how many there are
 };
-hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s);
-hgnn_status task_build(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out, SetupStream& s);
+hgnn_status task_prepare(const TaskSource& q, TaskCounts& c);
+hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out);
 // ranges.hip: long rows cut at the borders of column ranges
 constexpr int kRanges = 8;  // as many as there are XCDs
 int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2);
 hgnn_status range_count(const TaskSource& q, const int32_t* col, int ncols, TaskCounts& c, SetupStream& s);
-hgnn_status range_write(const TaskSource& q, const TaskCounts& c, const TaskTotals& t, int4* task, int4* split, SetupStream& s);
+hgnn_status range_write(const TaskSource& q, const TaskCounts& c, hgnn_row_tasks* t, SetupStream& s);
 hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s);
 void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s);

@@ -9,7 +9,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "common.h"
+#include "task_build.h"
 
 namespace hgnn {
 
@@ -123,14 +123,15 @@ __global__ void validate_rowptr_kernel(hgnn_csr g, GraphFacts* f) {
   if (bad) atomicMax(&f->bad, 8 - bad);
 }
 
-__device__ __forceinline__ void add_block_total(int v, unsigned long long* total) {  // blockDim.x == kBlock
-  __shared__ int part[kBlock / kWave];
+template <int THREADS>
+__device__ __forceinline__ void add_block_total(int v, unsigned long long* total) {  // blockDim.x == THREADS
+  __shared__ int part[THREADS / kWave];
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
   if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     int t = 0;
-    for (int w = 0; w < kBlock / kWave; ++w) t += part[w];
+    for (int w = 0; w < THREADS / kWave; ++w) t += part[w];
     if (t) atomicAdd(total, (unsigned long long)t);
   }
 }
@@ -140,39 +141,39 @@ __device__ __forceinline__ void add_block_total(int v, unsigned long long* total
 // inside a row (43 us with a search of the row of every drop at 5.5 M non-zeros).  Few workgroups, each adding its total
 // once: thousands of additions to one address took longer than the pass (51 us).
 constexpr int kEdgesPerThread = 8;
-constexpr int kFactBlocks = 512;  // most workgroups that add to a fact
-__global__ __launch_bounds__(kBlock) void validate_edges_kernel(hgnn_csr g, GraphFacts* f, int64_t edge_blocks) {
+constexpr int kFactBlocks = 512;  // most workgroups that add to a fact: of 1024 lanes, all that the chip holds (with 256 lanes
+                                  // 16 us at 5.5 M non-zeros, 29 with an edge-id map; 14 and 16)
+constexpr int kFactThreads = 1024;
+__global__ __launch_bounds__(kFactThreads) void validate_edges_kernel(hgnn_csr g, GraphFacts* f, int64_t edge_blocks) {
   if (f->bad) return;  // written by the launch before
   if (int64_t(blockIdx.x) >= edge_blocks) {
     int ok = 0;
-    for (int64_t r = (int64_t(blockIdx.x) - edge_blocks) * kBlock + threadIdx.x; r < g.nrows;
-         r += (int64_t(gridDim.x) - edge_blocks) * kBlock) {
+    for (int64_t r = (int64_t(blockIdx.x) - edge_blocks) * kFactThreads + threadIdx.x; r < g.nrows;
+         r += (int64_t(gridDim.x) - edge_blocks) * kFactThreads) {
       const int b = g.rowptr[r], e = g.rowptr[r + 1];
       if (b < e && b > 0) ok += g.col[b - 1] > g.col[b];
     }
-    add_block_total(ok, &f->drops_ok);
+    add_block_total<kFactThreads>(ok, &f->drops_ok);
     return;
   }
   int bad = 0, drops = 0;
-  for (int64_t i0 = int64_t(blockIdx.x) * (kBlock * kEdgesPerThread) + threadIdx.x; i0 < g.nnz;
-       i0 += edge_blocks * (kBlock * kEdgesPerThread)) {
-    int c[kEdgesPerThread], before[kEdgesPerThread];
+  for (int64_t i0 = int64_t(blockIdx.x) * (kFactThreads * kEdgesPerThread) + threadIdx.x; i0 < g.nnz;
+       i0 += edge_blocks * (kFactThreads * kEdgesPerThread)) {
+    int c[kEdgesPerThread], before[kEdgesPerThread], e[kEdgesPerThread];
 #pragma unroll
     for (int u = 0; u < kEdgesPerThread; ++u) {
-      const int64_t i = i0 + u * kBlock;
+      const int64_t i = i0 + u * kFactThreads;
       c[u] = i < g.nnz ? g.col[i] : 0;
       before[u] = i < g.nnz && i > 0 ? g.col[i - 1] : -1;
+      e[u] = g.eid && i < g.nnz ? g.eid[i] : 0;
     }
 #pragma unroll
     for (int u = 0; u < kEdgesPerThread; ++u) {
-      const int64_t i = i0 + u * kBlock;
+      const int64_t i = i0 + u * kFactThreads;
       if (i >= g.nnz) break;
       int b = 0;
       if (c[u] < 0 || c[u] >= g.ncols) b = 4;
-      if (!b && g.eid) {
-        const int e = g.eid[i];
-        if (e < 0 || int64_t(e) >= g.nnz) b = 5;
-      }
+      if (!b && (e[u] < 0 || int64_t(e[u]) >= g.nnz)) b = 5;
       if (!b && g.row) {
         const int r = g.row[i];
         if (r < 0 || r >= g.nrows) b = 6;
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kBlock) void validate_edges_kernel(hgnn_csr g, Grap
     }
   }
   if (bad) atomicMax(&f->bad_edge, 8 - bad);
-  add_block_total(drops, &f->drops);
+  add_block_total<kFactThreads>(drops, &f->drops);
 }
 
 static const char* const kRule[] = {"ok",
@@ -195,16 +196,20 @@ static const char* const kRule[] = {"ok",
                                     "a COO row id disagrees with rowptr",
                                     "column ids are not ascending inside a row"};
 
+static hipError_t launch_validate_edges(const hgnn_csr* g, GraphFacts* facts, hipStream_t s) {
+  if (g->nnz > 0) {
+    const int64_t eb = std::min<int64_t>(kFactBlocks, ceil_div(g->nnz, int64_t(kFactThreads) * kEdgesPerThread));
+    const int64_t rb = std::min<int64_t>(kFactBlocks / 2, ceil_div(g->nrows, kFactThreads));
+    validate_edges_kernel<<<dim3(unsigned(eb + rb)), kFactThreads, 0, s>>>(*g, facts, eb);
+  }
+  return hipGetLastError();
+}
+
 static hipError_t launch_validate(const hgnn_csr* g, GraphFacts* facts, hipStream_t s) {
   hipError_t e = hipMemsetAsync(facts, 0, sizeof(GraphFacts), s);
   if (e != hipSuccess) return e;
   validate_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) + 1, kBlock))), kBlock, 0, s>>>(*g, facts);
-  if (g->nnz > 0) {
-    const int64_t eb = std::min<int64_t>(kFactBlocks, ceil_div(g->nnz, int64_t(kBlock) * kEdgesPerThread));
-    const int64_t rb = std::min<int64_t>(kFactBlocks / 2, ceil_div(g->nrows, kBlock));
-    validate_edges_kernel<<<dim3(unsigned(eb + rb)), kBlock, 0, s>>>(*g, facts, eb);
-  }
-  return hipGetLastError();
+  return launch_validate_edges(g, facts, s);
 }
 
 static hgnn_status check_facts(const GraphFacts& f) {
@@ -214,9 +219,8 @@ static hgnn_status check_facts(const GraphFacts& f) {
 }
 
 // ---- first and last row of every segment: binary searches in the offset array ------------------------
-__global__ void seg_rows_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int S, int64_t nseg,
-                                int* __restrict__ lo, int* __restrict__ hi) {
-  int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+__device__ __forceinline__ void seg_rows(const int* __restrict__ rowptr, int nrows, int64_t nnz, int S, int64_t nseg, int64_t k,
+                                         int* __restrict__ lo, int* __restrict__ hi) {
   if (k >= nseg) return;
   int64_t e0 = k * S, e1 = e0 + S < nnz ? e0 + S : nnz;
   lo[k] = row_of_edge(rowptr, nrows, e0);
@@ -269,28 +273,50 @@ __device__ inline int block_exclusive_scan(int v, int* total) {
   return before + incl - v;
 }
 
-__global__ __launch_bounds__(kBlock) void row_lists_count_kernel(RowLists q, int nblk, int* __restrict__ counts, GraphFacts* f) {
-  const int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
-  int c[kLists] = {0, 0, 0, 0}, listed = 0;
+// A workgroup per window of rows (kRowsPerBlock = kTaskWindow): the rules of the offset array, the members of the row lists and the
+// pieces of the row tasks.  The three as launches of their own took 14 us at 262 144 rows, this one 9.
+static_assert(kRowsPerBlock == kTaskWindow && kBlock == kTaskThreads, "row lists and row tasks share their windows");
+__global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists q, TaskSource tq, int nblk, int* __restrict__ counts,
+                                                            int* __restrict__ task_counts, GraphFacts* f) {
+  constexpr int kListed = kLists + kTaskAll, kSums = kListed + 1;
+  __shared__ int s_total[kSums];
+  if (threadIdx.x < kSums) s_total[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t base = int64_t(blockIdx.x) * kRowsPerBlock + threadIdx.x * kRowsPerThread;
+  int bad = 0;
+  if (base == 0) {
+    if (g.rowptr[0] != 0) bad = 1;
+    else if (int64_t(g.rowptr[g.nrows]) != g.nnz) bad = 2;
+  }
+  int c[kLists] = {0, 0, 0, 0}, n[kTaskAll] = {0, 0, 0, 0, 0, 0}, listed = 0;
   for (int u = 0; u < kRowsPerThread; ++u) {
     if (base + u >= q.nrows) break;
+    const int r = int(base) + u;
     int m[kLists], len;
-    row_memberships(q, base + u, m, len);
+    row_memberships(q, r, m, len);
+    if (!bad && len < 0) bad = 3;
     for (int i = 0; i < kLists; ++i) c[i] += m[i];
     if (m[kBigList] || m[kMidList]) listed += len;
+    task_count_row(tq, g.rowptr, r, n);
   }
-  for (int i = 0; i < kLists; ++i) {
-    int total;
-    (void)block_exclusive_scan(c[i], &total);
-    if (threadIdx.x == 0) counts[i * nblk + blockIdx.x] = total;
+  if (bad) atomicMax(&f->bad, 8 - bad);
+#pragma unroll
+  for (int i = 0; i < kSums; ++i) {
+    const int v = wave_sum(i < kLists ? c[i < kLists ? i : 0] : (i < kListed ? n[i < kListed && i >= kLists ? i - kLists : 0] : listed));
+    if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&s_total[i], v);
   }
-  add_block_total(listed, &f->listed);
+  __syncthreads();
+  if (nblk == 0) return;  // no rows
+  const int i = threadIdx.x;
+  const int counters = tq.range_min == kNoRanges ? kTaskCounters : kTaskAll;
+  if (i < kLists) counts[i * nblk + blockIdx.x] = s_total[i];
+  else if (i < kLists + counters) task_counts[int64_t(i - kLists) * nblk + blockIdx.x] = s_total[i];
+  else if (i == kListed && s_total[i]) atomicAdd(&f->listed, (unsigned long long)s_total[i]);
 }
 
 // one workgroup: exclusive scans of the n block counts of every list in place; the totals and what earlier passes left in
 // `facts` go to `out` (host memory)
-__global__ __launch_bounds__(kBlock) void row_lists_scan_kernel(int* __restrict__ counts, int n, const GraphFacts* __restrict__ facts,
-                                                                GraphFacts* out) {
+__device__ __forceinline__ void row_lists_scan(int* __restrict__ counts, int n, const GraphFacts* __restrict__ facts, GraphFacts* out) {
   int carry[kLists] = {0, 0, 0, 0};
   for (int base = 0; base < n; base += kBlock) {
     const int i = base + threadIdx.x;
@@ -312,12 +338,20 @@ __global__ __launch_bounds__(kBlock) void row_lists_scan_kernel(int* __restrict_
   }
 }
 
+// two workgroups: the row lists and the row tasks
+__global__ __launch_bounds__(kBlock) void plan_scan_kernel(TaskSource tq, int n, int* __restrict__ counts, const GraphFacts* __restrict__ facts,
+                                                          GraphFacts* out, int* __restrict__ task_counts, int* __restrict__ sums,
+                                                          hgnn_task_sec* __restrict__ sec, TaskTotals* totals) {
+  if (blockIdx.x == 0) row_lists_scan(counts, n, facts, out);
+  else task_scan(tq, n, task_counts, sums, sec, totals);
+}
+
 struct RowListArrays {
   int *split_row, *split_lo, *split_hi, *big_row, *big_first, *mid_row, *chunk_row, *chunk_first, *chunk_count;
 };
 
-__global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int nblk, const int* __restrict__ offsets, RowListArrays o) {
-  const int base = blockIdx.x * kRowsPerBlock + threadIdx.x * kRowsPerThread;
+__device__ __forceinline__ void row_lists_write(const RowLists& q, int b, int nblk, const int* __restrict__ offsets, const RowListArrays& o) {
+  const int base = b * kRowsPerBlock + threadIdx.x * kRowsPerThread;
   int m[kRowsPerThread][kLists], c[kLists] = {0, 0, 0, 0}, pos[kLists];
   for (int u = 0; u < kRowsPerThread; ++u) {
     for (int i = 0; i < kLists; ++i) m[u][i] = 0;
@@ -327,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int
   }
   for (int i = 0; i < kLists; ++i) {
     int total;
-    pos[i] = offsets[i * nblk + blockIdx.x] + block_exclusive_scan(c[i], &total);
+    pos[i] = offsets[i * nblk + b] + block_exclusive_scan(c[i], &total);
   }
   for (int u = 0; u < kRowsPerThread; ++u) {
     const int r = base + u;
@@ -352,6 +386,19 @@ __global__ __launch_bounds__(kBlock) void row_lists_write_kernel(RowLists q, int
   }
 }
 
+// Workgroups for the windows of the row tasks, then (with members) for those of the row lists, then for the segments: none needs
+// what another one writes, and as launches of their own they took 25 us at 5.5 M non-zeros, mostly latency, in one 11.
+__global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n, const int* __restrict__ task_counts, const int* __restrict__ sums,
+                                                           hgnn_task_sec* __restrict__ sec, int4* __restrict__ task, int* __restrict__ zrow,
+                                                           int4* __restrict__ split, RowLists q, int list_blocks,
+                                                           const int* __restrict__ offsets, RowListArrays o, int64_t nseg,
+                                                           int* __restrict__ seg_lo, int* __restrict__ seg_hi) {
+  const int b = int(blockIdx.x);
+  if (b < n) task_write<false>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split);
+  else if (b < n + list_blocks) row_lists_write(q, b - n, n, offsets, o);
+  else seg_rows(q.rowptr, q.nrows, tq.nnz, q.S, nseg, (int64_t(b) - n - list_blocks) * kBlock + threadIdx.x, seg_lo, seg_hi);
+}
+
 // Validates the graph g and builds the segment arrays, row lists and row tasks of p for it (p->S, p->nseg, p->max_F set by the
 // caller).  The host waits twice: for the totals of the lists (which size the allocations) and for the arrays.
 hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, SetupStream& s) {
@@ -364,16 +411,18 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   GraphFacts* facts = facts_buf.as<GraphFacts>();
   GraphFacts* totals = mail.data ? reinterpret_cast<GraphFacts*>(mail.data) : facts + 1;
   int* counts = counts_buf.as<int>();
-  HGNN_HIP(launch_validate(g, facts, s));
   const RowLists q{g->rowptr, g->nrows, p->S, p->big_deg, p->mid_deg};
-  if (nblk > 0) row_lists_count_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts, facts);
-  row_lists_scan_kernel<<<1, kBlock, 0, s>>>(counts, nblk, facts, totals);
-  HGNN_LAUNCH_CHECK("row_lists_count_kernel / row_lists_scan_kernel");
   const TaskSource tq{g->rowptr, nullptr, g->nrows, 1, p->S, task_group_max(g->nnz), g->nnz,
                       blocks ? kNoRanges : range_min_row(E, g->ncols, p->max_F, p->S, p->l2_bytes)};
   TaskCounts tc(s);
-  hgnn_status st = task_count(tq, tc, s);
-  if (st == HGNN_OK && tq.range_min != kNoRanges) st = range_count(tq, g->col, g->ncols, tc, s);
+  hgnn_status st = task_prepare(tq, tc);
+  if (st != HGNN_OK) return st;
+  HGNN_HIP(hipMemsetAsync(facts, 0, sizeof(GraphFacts), s));
+  plan_count_kernel<<<dim3(unsigned(nblk > 0 ? nblk : 1)), kBlock, 0, s>>>(*g, q, tq, nblk, counts, tc.count, facts);
+  HGNN_HIP(launch_validate_edges(g, facts, s));
+  plan_scan_kernel<<<2, kBlock, 0, s>>>(tq, nblk, counts, facts, totals, tc.count, tc.sums, tc.sec, tc.totals);
+  HGNN_LAUNCH_CHECK("plan_count_kernel / plan_scan_kernel");
+  if (tq.range_min != kNoRanges) st = range_count(tq, g->col, g->ncols, tc, s);
   if (st != HGNN_OK) return st;
   GraphFacts f;
   if (!mail.data) HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
@@ -389,9 +438,6 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   if (E > 0) {
     HGNN_HIP(dev_malloc(&p->seg_row_lo, sizeof(int) * size_t(p->nseg)));
     HGNN_HIP(dev_malloc(&p->seg_row_hi, sizeof(int) * size_t(p->nseg)));
-    seg_rows_kernel<<<dim3(unsigned(ceil_div(p->nseg, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, E, p->S, p->nseg,
-                                                                                  p->seg_row_lo, p->seg_row_hi);
-    HGNN_LAUNCH_CHECK("seg_rows_kernel");
   }
   if (p->n_split > 0) {
     HGNN_HIP(dev_malloc(&p->split_row, sizeof(int) * size_t(p->n_split)));
@@ -408,15 +454,22 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
     HGNN_HIP(dev_malloc(&p->hub_chunk_count, sizeof(int) * nc));
     HGNN_HIP(dev_malloc(&p->hub_part, sizeof(float) * 2 * nc * size_t(p->max_H)));
   }
-  if (p->n_split + p->n_mid + p->n_big > 0) {
-    row_lists_write_kernel<<<nblk, kBlock, 0, s>>>(q, nblk, counts,
-                                                   RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row,
-                                                                 p->big_first, p->mid_row, p->hub_chunk_row, p->hub_chunk_first,
-                                                                 p->hub_chunk_count});
-    HGNN_LAUNCH_CHECK("row_lists_write_kernel");
-  }
-  st = task_build(tq, tc, p->max_F, p->max_H, &p->tasks, s);
+  st = task_allocate(tq, tc, p->max_F, p->max_H, &p->tasks);
   if (st != HGNN_OK) return st;
+  const int list_blocks = p->n_split + p->n_mid + p->n_big > 0 ? nblk : 0;
+  const int64_t grid = int64_t(nblk) + list_blocks + ceil_div(p->nseg, kBlock);
+  if (grid > 0) {
+    plan_write_kernel<<<dim3(unsigned(grid)), kBlock, 0, s>>>(
+        tq, nblk, tc.count, tc.sums, p->tasks->sec, p->tasks->task, p->tasks->zrow, p->tasks->split, q, list_blocks, counts,
+        RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row, p->big_first, p->mid_row, p->hub_chunk_row,
+                      p->hub_chunk_first, p->hub_chunk_count},
+        p->nseg, p->seg_row_lo, p->seg_row_hi);
+    HGNN_LAUNCH_CHECK("plan_write_kernel");
+  }
+  if (tc.got.n_range > 0) {
+    st = range_write(tq, tc, p->tasks, s);
+    if (st != HGNN_OK) return st;
+  }
   const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
   if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));
   if (g->nrows > 0) HGNN_HIP(dev_malloc(&p->vtab, sizeof(float) * 4 * size_t(g->nrows) * size_t(p->max_H)));

@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kRangeThreads) void range_write_kernel(RangeLists a
   }
 }
 
-// after task_count: the long rows and their pieces, counted; the number of pieces is in c.totals with the others
+// after the counts of the row tasks: the long rows and their pieces, counted; the number of pieces is in c.totals with the others
 hgnn_status range_count(const TaskSource& q, const int32_t* col, int ncols, TaskCounts& c, SetupStream& s) {
   size_t bytes = 0;
   (void)range_lists(q, c, &bytes);
@@ -236,10 +236,10 @@ hgnn_status range_count(const TaskSource& q, const int32_t* col, int ncols, Task
   return HGNN_OK;
 }
 
-// t.n_range pieces into task, t.n_long rows into split
-hgnn_status range_write(const TaskSource& q, const TaskCounts& c, const TaskTotals& t, int4* task, int4* split, SetupStream& s) {
+// the c.got.n_range pieces and, behind the other rows of several pieces, the c.got.n_long rows they belong to
+hgnn_status range_write(const TaskSource& q, const TaskCounts& c, hgnn_row_tasks* t, SetupStream& s) {
   const RangeLists a = range_lists(q, c, nullptr);
-  range_write_kernel<<<dim3(unsigned(ceil_div(t.n_long, kRangeWindow))), kRangeThreads, 0, s>>>(a, t.n_slots, task, split);
+  range_write_kernel<<<dim3(unsigned(ceil_div(c.got.n_long, kRangeWindow))), kRangeThreads, 0, s>>>(a, c.got.n_slots, t->rtask, t->split + c.got.n_split);
   HGNN_LAUNCH_CHECK("range_write_kernel");
   return HGNN_OK;
 }
