@@ -280,7 +280,7 @@ struct hgnn_row_tasks {
   int32_t nb = 0;
   int64_t nnz = 0;
   int4* task = nullptr;
-  int4* rtask = nullptr;         // pieces of the rows that are cut at column ranges, range after range (ranges.hip); all staged
+  int4* rtask = nullptr;         // pieces of the rows that are cut at column ranges, range after range (ranges.h); all staged
   int32_t n_rtask = 0;
   int32_t* zrow = nullptr;
   int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
@@ -395,7 +395,7 @@ struct TaskSource {
   const int32_t* first;   // device, [nb] first non-zero of every block, or nullptr (one block)
   int32_t nrows, nb, S, group_max;
   int64_t nnz;
-  int32_t range_min;      // rows of at least so many non-zeros are left to ranges.hip (one block), or kNoRanges
+  int32_t range_min;      // rows of at least so many non-zeros are left to ranges.h (one block), or kNoRanges
 };
 constexpr int kNoRanges = 0x7fffffff;
 // Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
@@ -405,7 +405,7 @@ constexpr int kGroupMaxBlocks = 256;
 inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 : 128; }
 struct TaskTotals {
   int64_t n_zero;
-  int32_t n_task, n_whole, n_split, n_slots, n_long, n_range;  // n_long rows in n_range pieces by ranges.hip
+  int32_t n_task, n_whole, n_split, n_slots, n_long, n_range;  // n_long rows in n_range pieces by ranges.h
 };
 constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for equal neighbours; few, because the short rows of a
                                    // window share cache lines of the column array and of edge tensors (see TaskView::chunk)
@@ -424,25 +424,21 @@ struct TaskScratch {
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
 struct TaskCounts {
-  explicit TaskCounts(SetupStream& s) : counts(s), secs(s), ranges(s), mail(s) {}
-  DevTemp counts, secs, ranges;
+  explicit TaskCounts(SetupStream& s) : counts(s), secs(s), mail(s) {}
+  DevTemp counts, secs;
   HostMail mail;
   int nwin = 0;
   int* count = nullptr;          // device, [kTaskAll][nb][nwin]
   int* sums = nullptr;           // device, [kTaskAll][nb]
   hgnn_task_sec* sec = nullptr;  // device, [nb]
   TaskTotals* totals = nullptr;  // valid after the stream has been waited for (host memory, or a device copy)
+  int* n_range = nullptr;        // beside it, where rows are cut at column ranges (ranges = true): what becomes got.n_range
+  bool ranges = false;
   TaskTotals got{};              // the same on the host, from task_allocate on
-  const int* long_at = nullptr;  // device, [nwin] long rows before each window of kTaskWindow rows, and
-  const int* n_long = nullptr;   // how many there are
+  const int* long_at = nullptr;  // device, [nwin] long rows before each window of kTaskWindow rows
 };
 hgnn_status task_prepare(const TaskSource& q, TaskCounts& c);
 hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out);
-// ranges.hip: long rows cut at the borders of column ranges
-constexpr int kRanges = 8;  // as many as there are XCDs
-int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2);
-hgnn_status range_count(const TaskSource& q, const int32_t* col, int ncols, TaskCounts& c, SetupStream& s);
-hgnn_status range_write(const TaskSource& q, const TaskCounts& c, hgnn_row_tasks* t, SetupStream& s);
 hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s);
 void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s);

@@ -9,7 +9,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "task_build.h"
+#include "ranges.h"
 
 namespace hgnn {
 
@@ -144,20 +144,26 @@ constexpr int kEdgesPerThread = 8;
 constexpr int kFactBlocks = 512;  // most workgroups that add to a fact: of 1024 lanes, all that the chip holds (with 256 lanes
                                   // 16 us at 5.5 M non-zeros, 29 with an edge-id map; 14 and 16)
 constexpr int kFactThreads = 1024;
-__global__ __launch_bounds__(kFactThreads) void validate_edges_kernel(hgnn_csr g, GraphFacts* f, int64_t edge_blocks) {
+__global__ __launch_bounds__(kFactThreads) void validate_edges_kernel(hgnn_csr g, GraphFacts* f, int64_t edge_blocks, int64_t row_blocks,
+                                                                    RangeLists ranges) {
   if (f->bad) return;  // written by the launch before
-  if (int64_t(blockIdx.x) >= edge_blocks) {
+  // windows whose long rows are cut beside the checks come first: theirs are the longest chains
+  const int64_t b = int64_t(blockIdx.x) - ranges.nwin;
+  if (b < 0) {
+    range_cut<kFactThreads>(ranges, int(blockIdx.x));
+    return;
+  }
+  if (b >= edge_blocks) {
     int ok = 0;
-    for (int64_t r = (int64_t(blockIdx.x) - edge_blocks) * kFactThreads + threadIdx.x; r < g.nrows;
-         r += (int64_t(gridDim.x) - edge_blocks) * kFactThreads) {
-      const int b = g.rowptr[r], e = g.rowptr[r + 1];
-      if (b < e && b > 0) ok += g.col[b - 1] > g.col[b];
+    for (int64_t r = (b - edge_blocks) * kFactThreads + threadIdx.x; r < g.nrows; r += row_blocks * kFactThreads) {
+      const int p = g.rowptr[r], e = g.rowptr[r + 1];
+      if (p < e && p > 0) ok += g.col[p - 1] > g.col[p];
     }
     add_block_total<kFactThreads>(ok, &f->drops_ok);
     return;
   }
   int bad = 0, drops = 0;
-  for (int64_t i0 = int64_t(blockIdx.x) * (kFactThreads * kEdgesPerThread) + threadIdx.x; i0 < g.nnz;
+  for (int64_t i0 = b * (kFactThreads * kEdgesPerThread) + threadIdx.x; i0 < g.nnz;
        i0 += edge_blocks * (kFactThreads * kEdgesPerThread)) {
     int c[kEdgesPerThread], before[kEdgesPerThread], e[kEdgesPerThread];
 #pragma unroll
@@ -196,11 +202,12 @@ static const char* const kRule[] = {"ok",
                                     "a COO row id disagrees with rowptr",
                                     "column ids are not ascending inside a row"};
 
-static hipError_t launch_validate_edges(const hgnn_csr* g, GraphFacts* facts, hipStream_t s) {
+// ranges.nwin windows beside the checks (0: none)
+static hipError_t launch_validate_edges(const hgnn_csr* g, GraphFacts* facts, const RangeLists& ranges, hipStream_t s) {
   if (g->nnz > 0) {
     const int64_t eb = std::min<int64_t>(kFactBlocks, ceil_div(g->nnz, int64_t(kFactThreads) * kEdgesPerThread));
     const int64_t rb = std::min<int64_t>(kFactBlocks / 2, ceil_div(g->nrows, kFactThreads));
-    validate_edges_kernel<<<dim3(unsigned(eb + rb)), kFactThreads, 0, s>>>(*g, facts, eb);
+    validate_edges_kernel<<<dim3(unsigned(eb + rb + ranges.nwin)), kFactThreads, 0, s>>>(*g, facts, eb, rb, ranges);
   }
   return hipGetLastError();
 }
@@ -209,7 +216,7 @@ static hipError_t launch_validate(const hgnn_csr* g, GraphFacts* facts, hipStrea
   hipError_t e = hipMemsetAsync(facts, 0, sizeof(GraphFacts), s);
   if (e != hipSuccess) return e;
   validate_rowptr_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) + 1, kBlock))), kBlock, 0, s>>>(*g, facts);
-  return launch_validate_edges(g, facts, s);
+  return launch_validate_edges(g, facts, RangeLists{}, s);
 }
 
 static hgnn_status check_facts(const GraphFacts& f) {
@@ -338,12 +345,19 @@ __device__ __forceinline__ void row_lists_scan(int* __restrict__ counts, int n, 
   }
 }
 
-// two workgroups: the row lists and the row tasks
+// two workgroups: the row lists and the row tasks; a third: the pieces at column ranges
 __global__ __launch_bounds__(kBlock) void plan_scan_kernel(TaskSource tq, int n, int* __restrict__ counts, const GraphFacts* __restrict__ facts,
                                                           GraphFacts* out, int* __restrict__ task_counts, int* __restrict__ sums,
-                                                          hgnn_task_sec* __restrict__ sec, TaskTotals* totals) {
-  if (blockIdx.x == 0) row_lists_scan(counts, n, facts, out);
-  else task_scan(tq, n, task_counts, sums, sec, totals);
+                                                          hgnn_task_sec* __restrict__ sec, TaskTotals* totals, RangeLists ranges,
+                                                          int* n_range) {
+  if (blockIdx.x == 0) {
+    row_lists_scan(counts, n, facts, out);
+  } else if (blockIdx.x == 1) {
+    task_scan(tq, n, task_counts, sums, sec, totals);
+  } else {
+    const int all = range_scan_all(ranges);
+    if (threadIdx.x == 0) *n_range = all;
+  }
 }
 
 struct RowListArrays {
@@ -386,17 +400,28 @@ __device__ __forceinline__ void row_lists_write(const RowLists& q, int b, int nb
   }
 }
 
-// Workgroups for the windows of the row tasks, then (with members) for those of the row lists, then for the segments: none needs
+// Workgroups for the windows of the row tasks, then (with members) for those of the row lists and of the rows cut at column ranges, then
+// for the segments: none needs
 // what another one writes, and as launches of their own they took 25 us at 5.5 M non-zeros, mostly latency, in one 11.
 __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n, const int* __restrict__ task_counts, const int* __restrict__ sums,
                                                            hgnn_task_sec* __restrict__ sec, int4* __restrict__ task, int* __restrict__ zrow,
                                                            int4* __restrict__ split, RowLists q, int list_blocks,
                                                            const int* __restrict__ offsets, RowListArrays o, int64_t nseg,
-                                                           int* __restrict__ seg_lo, int* __restrict__ seg_hi) {
-  const int b = int(blockIdx.x);
-  if (b < n) task_write<false>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split);
-  else if (b < n + list_blocks) row_lists_write(q, b - n, n, offsets, o);
-  else seg_rows(q.rowptr, q.nrows, tq.nnz, q.S, nseg, (int64_t(b) - n - list_blocks) * kBlock + threadIdx.x, seg_lo, seg_hi);
+                                                           int* __restrict__ seg_lo, int* __restrict__ seg_hi, RangeLists ranges,
+                                                           int range_blocks, const int* __restrict__ long_at, int first_slot,
+                                                           int4* __restrict__ rtask, int4* __restrict__ rsplit) {
+  // (those of the column ranges, the longest chains, come first)
+  const int b = int(blockIdx.x) - range_blocks;
+  if (b < 0) {
+    const int w = int(blockIdx.x) * kRangeGroup;
+    range_write(ranges, w, long_at[w], first_slot, rtask, rsplit);
+  } else if (b < n) {
+    task_write<false>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split);
+  } else if (b < n + list_blocks) {
+    row_lists_write(q, b - n, n, offsets, o);
+  } else {
+    seg_rows(q.rowptr, q.nrows, tq.nnz, q.S, nseg, (int64_t(b) - n - list_blocks) * kBlock + threadIdx.x, seg_lo, seg_hi);
+  }
 }
 
 // Validates the graph g and builds the segment arrays, row lists and row tasks of p for it (p->S, p->nseg, p->max_F set by the
@@ -419,11 +444,16 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   if (st != HGNN_OK) return st;
   HGNN_HIP(hipMemsetAsync(facts, 0, sizeof(GraphFacts), s));
   plan_count_kernel<<<dim3(unsigned(nblk > 0 ? nblk : 1)), kBlock, 0, s>>>(*g, q, tq, nblk, counts, tc.count, facts);
-  HGNN_HIP(launch_validate_edges(g, facts, s));
-  plan_scan_kernel<<<2, kBlock, 0, s>>>(tq, nblk, counts, facts, totals, tc.count, tc.sums, tc.sec, tc.totals);
+  RangeLists ranges{};
+  DevTemp range_mem(s);
+  tc.ranges = tq.range_min != kNoRanges && nblk > 0;
+  if (tc.ranges) {
+    HGNN_HIP(range_mem.alloc(range_bytes(g->nrows, nblk)));
+    ranges = range_lists(tq, g->col, g->ncols, nblk, range_mem.p);
+  }
+  HGNN_HIP(launch_validate_edges(g, facts, ranges, s));
+  plan_scan_kernel<<<tc.ranges ? 3 : 2, kBlock, 0, s>>>(tq, nblk, counts, facts, totals, tc.count, tc.sums, tc.sec, tc.totals, ranges, tc.n_range);
   HGNN_LAUNCH_CHECK("plan_count_kernel / plan_scan_kernel");
-  if (tq.range_min != kNoRanges) st = range_count(tq, g->col, g->ncols, tc, s);
-  if (st != HGNN_OK) return st;
   GraphFacts f;
   if (!mail.data) HGNN_HIP(hipMemcpyAsync(&f, totals, sizeof(f), hipMemcpyDeviceToHost, s));
   HGNN_HIP(s.wait());
@@ -457,18 +487,16 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   st = task_allocate(tq, tc, p->max_F, p->max_H, &p->tasks);
   if (st != HGNN_OK) return st;
   const int list_blocks = p->n_split + p->n_mid + p->n_big > 0 ? nblk : 0;
-  const int64_t grid = int64_t(nblk) + list_blocks + ceil_div(p->nseg, kBlock);
+  const int range_blocks = tc.got.n_range > 0 ? int(ceil_div(nblk, kRangeGroup)) : 0;
+  const int64_t grid = int64_t(nblk) + list_blocks + range_blocks + ceil_div(p->nseg, kBlock);
+  hgnn_row_tasks* const t = p->tasks;
   if (grid > 0) {
     plan_write_kernel<<<dim3(unsigned(grid)), kBlock, 0, s>>>(
-        tq, nblk, tc.count, tc.sums, p->tasks->sec, p->tasks->task, p->tasks->zrow, p->tasks->split, q, list_blocks, counts,
+        tq, nblk, tc.count, tc.sums, t->sec, t->task, t->zrow, t->split, q, list_blocks, counts,
         RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row, p->big_first, p->mid_row, p->hub_chunk_row,
                       p->hub_chunk_first, p->hub_chunk_count},
-        p->nseg, p->seg_row_lo, p->seg_row_hi);
+        p->nseg, p->seg_row_lo, p->seg_row_hi, ranges, range_blocks, tc.long_at, tc.got.n_slots, t->rtask, t->split + tc.got.n_split);
     HGNN_LAUNCH_CHECK("plan_write_kernel");
-  }
-  if (tc.got.n_range > 0) {
-    st = range_write(tq, tc, p->tasks, s);
-    if (st != HGNN_OK) return st;
   }
   const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);
   if (nv > 0) HGNN_HIP(dev_malloc(&p->vscratch, sizeof(float) * nv));

@@ -1,0 +1,235 @@
+// Long rows of a graph whose feature table misses the L2s, cut at the borders of column ranges.  Integer work only; set-up.
+//
+// Eight L2s of 4 MB keep the popular rows of a large table eight times over when every XCD gathers from all of it.  Columns ascend
+// inside a row, so a row's share of a column range is a run of its non-zeros, and a run is a piece of the row like any other (task.h):
+// nothing is copied or re-ordered.  The pieces are listed range after range and an eighth of the list goes to each XCD, whose L2 then
+// sees an eighth of the columns.  What it costs is a staged partial row per (row, range), so only rows that have several pieces anyway
+// are cut; on a power law they hold most of the non-zeros (62 M x 128: L2 hits 31 -> 49 %, misses 11.9 -> 8.9 GB a call).
+#pragma once
+
+#include "task_build.h"
+
+namespace hgnn {
+
+constexpr int kRanges = 8;        // as many as there are XCDs
+constexpr int kRangeGroup = 4;    // windows of kTaskWindow rows whose pieces are sorted by length together (1, 2, 4: 5.5 M non-zeros x 4
+                                  // heads, attention forward 110, 103, 102 us, SDDMM 62.5, 59.8, 58.6; a plan 76, 79, 82)
+constexpr int kRangePiece = 256;  // most non-zeros of a piece (also at most S)
+
+// Where rows are cut.  A segment size is the least length because such rows leave staged partial rows (fp16, as ever) in any case.
+// us a call, rows in pieces of S / at column ranges (F = 64 and one head if not said; power law unless log-normal):
+//   table, non-zeros                  SpMM, edge values   behind a map   SDDMM       attention fwd (saving), bwd
+//   614 MB, 62 M, F = 128               1711 / 1285        2683 / 2043
+//   307 MB, 62 M, F = 64 by degrees      870 / 740
+//   154 MB, 31 M                         359 / 328          772 / 624    350 / 332
+//   256 MB, 13 M, F = 256                747 / 618         1012 / 783
+//   77 MB, 60 M, F = 16                  738 / 611         1640 / 1422
+//   77 MB, 12 M                          129 / 118          280 / 222    125 / 115
+//   134 MB, 26 M log-normal, 4 heads     930 / 819         1183 / 1169   937 / 802
+//   67 MB, 5.5 M, F = 128                                                            179 / 166, 213 / 195
+//   34 MB, 21 M                          142 / 135          352 / 312    136 / 128
+//   34 MB, 5.5 M, 4 heads                 59 / 59           123 / 114     59 / 59    105 / 102, 132 / 124
+//   13 MB, 8 M                            58 / 61           106 / 101     52 / 52
+//   8 MB, 8 M                             56 / 64            96 / 94      50 / 53
+//   34 MB, 2.1 M, F = 128: GIN layer forward 44 / 46; 10 MB, 1.3 M: by degrees 30 / 48
+// The cuts ride beside the checks of the columns and the lists beside the others (a plan of 5.5 M non-zeros 72 -> 82 us), so the line lies
+// where the calls begin to gain: at four L2s.
+static int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2) {
+  constexpr int64_t kLeastNnz = int64_t(4) << 20;
+  return nnz > kLeastNnz && ncols * max_F * 2 > 4 * l2 ? S + 1 : kNoRanges;
+}
+
+// Every window of kTaskWindow rows cuts its own long rows; the pieces of a window and range are sorted by length together.
+struct RangeLists {
+  const int* rowptr;
+  const int* col;
+  int* cuts;   // [nrows][kRanges - 1] where a long row's share of the ranges from the second on begins
+  int* count;  // [kRanges][nwin] pieces, then where they go
+  int* slots;  // [nwin] pieces of a window's rows, then the first of them
+  int nrows, nwin, piece, min_row, width;
+};
+
+static size_t range_bytes(int nrows, int nwin) { return sizeof(int) * ((kRanges - 1) * size_t(nrows) + (kRanges + 1) * size_t(nwin)); }
+
+static RangeLists range_lists(const TaskSource& q, const int* col, int ncols, int nwin, void* mem) {
+  RangeLists a{};
+  a.rowptr = q.rowptr;
+  a.col = col;
+  a.nrows = q.nrows;
+  a.nwin = nwin;
+  a.piece = q.S < kRangePiece ? q.S : kRangePiece;
+  a.min_row = q.range_min;
+  a.width = int(ceil_div(ncols, kRanges));
+  a.cuts = static_cast<int*>(mem);
+  a.count = a.cuts + (kRanges - 1) * size_t(q.nrows);
+  a.slots = a.count + kRanges * size_t(nwin);
+  return a;
+}
+
+struct RangeShare {
+  int beg, len, part, m;  // first non-zero, non-zeros, non-zeros per piece, pieces
+};
+__device__ __forceinline__ RangeShare range_share(int piece, int beg, int end) {
+  RangeShare s{beg, end - beg, 0, 0};
+  if (s.len > piece) {  // few: three divisions for everyone were 40 us of a plan of 5.5 M non-zeros
+    s.part = pieces_of(s.len, pieces_of(s.len, piece));
+    s.m = pieces_of(s.len, s.part);
+  } else if (s.len > 0) {  // (columns that validation will reject can lead to less)
+    s.part = s.len;
+    s.m = 1;
+  }
+  return s;
+}
+// the share of range x of long row r, whose cuts are there
+__device__ __forceinline__ RangeShare range_share_of(const RangeLists& a, int r, int x) {
+  const int* c = a.cuts + int64_t(r) * (kRanges - 1);
+  return range_share(a.piece, x == 0 ? a.rowptr[r] : c[x - 1], x == kRanges - 1 ? a.rowptr[r + 1] : c[x]);
+}
+
+// Window w by a workgroup of THREADS: a lane per (long row, range), the first non-zero of the range by binary search; its end is where
+// the next lane's begins.  Offsets have been checked, columns have not.
+template <int THREADS>
+__device__ __forceinline__ void range_cut(const RangeLists& a, int w) {
+  __shared__ int s_row[kTaskWindow], s_n, s_count[kRanges];
+  if (threadIdx.x == 0) s_n = 0;
+  if (threadIdx.x < kRanges) s_count[threadIdx.x] = 0;
+  __syncthreads();
+  for (int u = 0; u < kTaskWindow; u += THREADS) {
+    const int64_t r = int64_t(w) * kTaskWindow + u + threadIdx.x;
+    if (r < a.nrows && a.rowptr[r + 1] - a.rowptr[r] >= a.min_row) s_row[atomicAdd(&s_n, 1)] = int(r);
+  }
+  __syncthreads();
+  const int n = s_n, x = threadIdx.x % kRanges;
+  for (int i0 = 0; i0 < n; i0 += THREADS / kRanges) {  // uniform: lanes exchange
+    const int i = i0 + int(threadIdx.x) / kRanges;
+    const bool ok = i < n;
+    const int row = ok ? s_row[i] : 0;
+    const int end = ok ? a.rowptr[row + 1] : 0;
+    pos_t lo = ok ? pos_t(a.rowptr[row]) : 0, hi = pos_t(end);
+    if (x > 0) {
+      const int64_t first = int64_t(x) * a.width;
+      while (lo < hi) {
+        const pos_t mid = (lo + hi) / 2;
+        if (a.col[mid] < first) lo = mid + 1;
+        else hi = mid;
+      }
+      if (ok) a.cuts[int64_t(row) * (kRanges - 1) + x - 1] = int(lo);
+    }
+    const int next = __shfl_down(int(lo), 1, kRanges);
+    const int m = range_share(a.piece, int(lo), x == kRanges - 1 ? end : next).m;
+    if (ok && m) atomicAdd(&s_count[x], m);
+  }
+  __syncthreads();
+  if (threadIdx.x < kRanges) a.count[int(threadIdx.x) * a.nwin + w] = s_count[threadIdx.x];
+  if (threadIdx.x == 0) {
+    int all = 0;
+    for (int j = 0; j < kRanges; ++j) all += s_count[j];
+    a.slots[w] = all;
+  }
+}
+
+// inclusive scan over the workgroup of kTaskThreads of one value per thread; *total on all threads
+__device__ __forceinline__ int range_scan(int v, int* s_wave, int* total) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int incl = v;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if (lane >= d) incl += t;
+  }
+  __syncthreads();  // what a previous scan left has been read
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int w = 0; w < kTaskThreads / kWave; ++w) {
+    if (w < wave) before += s_wave[w];
+    all += s_wave[w];
+  }
+  *total = all;
+  return before + incl;
+}
+
+// one workgroup of kTaskThreads: exclusive scans in place; all pieces
+__device__ __forceinline__ int range_scan_all(const RangeLists& a) {
+  __shared__ int s_wave[kTaskThreads / kWave];
+  auto scan = [&](int* v, int n) {
+    int carry = 0;
+    for (int i0 = 0; i0 < n; i0 += kTaskThreads) {
+      const int i = i0 + int(threadIdx.x), x = i < n ? v[i] : 0;
+      int total;
+      const int incl = range_scan(x, s_wave, &total);
+      if (i < n) v[i] = carry + incl - x;
+      carry += total;
+    }
+    return carry;
+  };
+  (void)scan(a.slots, a.nwin);
+  return scan(a.count, kRanges * a.nwin);
+}
+
+// kRangeGroup windows from window w on by a workgroup of kTaskThreads, a lane per (long row, range) as in range_cut: the pieces of a range by length, so that
+// the lane groups of a wave end together; the slots of a row's pieces follow each other through the ranges.  long_before: long rows of
+// the windows before this one.
+__device__ __forceinline__ void range_write(const RangeLists& a, int w, int long_before, int first_slot, int4* __restrict__ task,
+                                            int4* __restrict__ split) {
+  __shared__ int s_row[kRangeGroup * kTaskWindow], s_n, at[kRanges][kRangePiece + 1];
+  __shared__ int s_wave[kTaskThreads / kWave];
+  const int t = threadIdx.x, x = t % kRanges;
+  if (t == 0) s_n = 0;
+  for (int k = t; k < kRanges * (kRangePiece + 1); k += kTaskThreads) at[0][k] = 0;
+  __syncthreads();
+  {
+    constexpr int kRowsEach = kRangeGroup * kTaskRowsPerThread;
+    int len[kRowsEach];
+#pragma unroll
+    for (int u = 0; u < kRowsEach; ++u) {
+      const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + t;
+      len[u] = r < a.nrows ? a.rowptr[r + 1] - a.rowptr[r] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsEach; ++u)
+      if (len[u] >= a.min_row) s_row[atomicAdd(&s_n, 1)] = w * kTaskWindow + u * kTaskThreads + t;
+  }
+  __syncthreads();
+  const int n = s_n;
+  constexpr int kRows = kTaskThreads / kRanges;
+  for (int i = t / kRanges; i < n; i += kRows) {
+    const RangeShare s = range_share_of(a, s_row[i], x);
+    if (s.m > 1) atomicAdd(&at[x][s.part], s.m - 1);
+    if (s.m > 0) atomicAdd(&at[x][s.len - (s.m - 1) * s.part], 1);
+  }
+  __syncthreads();
+  const int lane = t & (kWave - 1);
+  const bool rising = w / kRangeGroup % 2 != 0;  // in turn, so that a wave across two groups of windows takes equal lengths, too
+  for (int y = t / kWave; y < kRanges; y += kTaskThreads / kWave) {
+    int carry = a.count[y * a.nwin + w];
+    for (int k0 = 0; k0 <= kRangePiece; k0 += kWave) {
+      const int k = rising ? k0 + lane : kRangePiece - k0 - lane;
+      const bool in = k >= 0 && k <= kRangePiece;
+      const int c = in ? at[y][k] : 0;
+      int incl = c;
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int v = __shfl_up(incl, d);
+        if (lane >= d) incl += v;
+      }
+      if (in) at[y][k] = carry + incl - c;
+      carry += __shfl(incl, kWave - 1);
+    }
+  }
+  int next = first_slot + a.slots[w];
+  for (int i0 = 0; i0 < n; i0 += kRows) {  // uniform: the workgroup scans
+    const int i = i0 + t / kRanges;
+    RangeShare s{0, 0, 0, 0};
+    if (i < n) s = range_share_of(a, s_row[i], x);
+    int total;
+    const int incl = range_scan(s.m, s_wave, &total);  // (its barriers are behind the offsets in `at`)
+    const int slot = next + incl - s.m, end = __shfl(next + incl, kRanges - 1, kRanges);
+    if (i < n && x == 0) split[long_before + i] = make_int4(s_row[i], slot, end - slot, 0);
+    for (int j = 0; j < s.m; ++j) {
+      const int len = j + 1 < s.m ? s.part : s.len - j * s.part;
+      task[atomicAdd(&at[x][len], 1)] = make_int4(s.beg + j * s.part, len, s_row[i], slot + j);
+    }
+    next += total;
+  }
+}
+
+}  // namespace hgnn

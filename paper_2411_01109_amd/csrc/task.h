@@ -9,6 +9,7 @@
 namespace hgnn {
 
 constexpr int kMaxTaskBlocks = 64;
+constexpr int kXcds = 8;
 constexpr int kZeroTurns = 8;  // turns of G empty rows that a wave stores
 constexpr int64_t kMixNnz = int64_t(4) << 20;  // see comes_back()
 // Waves in a row on one XCD.  31 M non-zeros, one head of 64, 16 / 128 / 512 / 2048 waves: weighted SpMM 383, 369, 362, 363 us, SDDMM
@@ -61,8 +62,8 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool 
   v.nb = t->nb;
   v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
   v.n_rtask = t->n_rtask;
-  v.rshare = int(ceil_div(ceil_div(t->n_rtask, kRanges), G) * G);
-  int64_t n = int64_t(kRanges) * v.rshare / G;
+  v.rshare = int(ceil_div(ceil_div(t->n_rtask, kXcds), G) * G);
+  int64_t n = int64_t(kXcds) * v.rshare / G;
   for (int b = 0; b < t->nb; ++b) {
     const hgnn_task_sec& s = t->host[size_t(b)];
     n = (n + 7) & ~int64_t(7);

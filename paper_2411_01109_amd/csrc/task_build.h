@@ -11,7 +11,7 @@ constexpr int kMaxGroupLen = 256;
 static_assert(kGroupMaxBlocks <= kMaxGroupLen, "table of lengths");
 enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters, kTaskLong = kTaskCounters, kTaskAll };  // kTaskLong: with a plan
 
-constexpr int kLongRow = -1, kNone = -2;  // RowCut::m of a row for ranges.hip, and of no row
+constexpr int kLongRow = -1, kNone = -2;  // RowCut::m of a row for ranges.h, and of no row
 
 struct RowCut {
   int len, part, m;  // non-zeros, non-zeros per piece, pieces

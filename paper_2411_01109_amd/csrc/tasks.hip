@@ -51,13 +51,13 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
 hgnn_status task_prepare(const TaskSource& q, TaskCounts& c) {
   c.nwin = int(ceil_div(q.nrows, kTaskWindow));
   HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskAll) * size_t(q.nb) * (size_t(c.nwin) + 1)));
-  HGNN_HIP(c.secs.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals)));
+  HGNN_HIP(c.secs.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals) + sizeof(int)));
   c.count = c.counts.as<int>();
   c.sums = c.count + size_t(kTaskAll) * size_t(q.nb) * size_t(c.nwin);
   c.sec = c.secs.as<hgnn_task_sec>();
   c.long_at = c.count + size_t(kTaskLong) * size_t(q.nb) * size_t(c.nwin);
-  c.n_long = c.sums + size_t(kTaskLong) * size_t(q.nb);
   c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(c.sec + q.nb);
+  c.n_range = reinterpret_cast<int*>(c.totals + 1);
   return HGNN_OK;
 }
 
@@ -76,8 +76,13 @@ hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max
   if (!t) return fail(HGNN_ENOMEM, "hgnn_plan_create: host allocation failed");
   *out = t;  // the plan owns it from here
   TaskTotals& tot = c.got;
-  if (c.mail.data) tot = *c.totals;
-  else HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
+  if (c.mail.data) {
+    tot = *c.totals;
+    if (c.ranges) tot.n_range = *c.n_range;
+  } else {
+    HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
+    if (c.ranges) HGNN_HIP(hipMemcpy(&tot.n_range, c.n_range, sizeof(int), hipMemcpyDeviceToHost));
+  }
   t->nb = q.nb;
   t->nnz = q.nnz;
   t->n_split = tot.n_split + tot.n_long;

@@ -1,4 +1,4 @@
-"""Long rows cut at the borders of column ranges (plans of more than 4 Mi non-zeros over a table beyond the eight L2s): row lengths around
+"""Long rows cut at the borders of column ranges (plans of more than 4 Mi non-zeros over a table beyond four L2s): row lengths around
 the segment size, rows inside one range, rows that touch only the columns at the borders, empty ranges, every walk that takes them."""
 import numpy as np
 import pytest
@@ -9,7 +9,7 @@ from parity import compare, down, f16, up
 
 pytestmark = pytest.mark.gpu
 
-V, NCOLS, S, MAX_F = 30000, 30011, 64, 576  # the plan's table is 34.6 MB
+V, NCOLS, S, MAX_F = 30000, 30011, 64, 288  # the plan's table is 17.3 MB
 
 
 @pytest.fixture(scope="module")
