@@ -353,7 +353,8 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
 constexpr int kShortPieces = 8;
 
 template <int L, bool SAVE>
-__global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int4_t* __restrict__ split, int n_split) {
+__global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
+#pragma clang fp contract(off)
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -362,10 +363,11 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   const int f0c = active ? f0 : 0;
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
-  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
   if (i0 >= n_split) return;
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
-  if (i0 + g < n_split) q = split[i0 + g];
+  if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
+  const int alone = per_wave > 1 ? kShortPieces : 0;
   // merges the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](Soft<SAVE>& t, pos_t first, pos_t end, pos_t stride) {
     for (pos_t k0 = first; k0 < end; k0 += 4 * stride) {
@@ -386,32 +388,29 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
         if (k0 + u * stride < end) soft_merge_normalised<SAVE>(t, m[u], z[u], cp[u], o[u], om[u]);
     }
   };
-  if (q[2] > 0 && q[2] <= kShortPieces) {
+  if (q[2] > 0 && q[2] <= alone) {
     Soft<SAVE> t;
     take(t, q[1], q[1] + q[2], 1);
     GatArgs b = a;
     b.enter_block(q[3]);
     if (active) row_store<SAVE>(b, q[0], f0, head, leader, t);
   }
-  for (int j = 0; j < G; ++j) {
+  for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= kShortPieces) continue;
+    if (n <= alone) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     Soft<SAVE> t;
     take(t, first + g, first + n, G);
+    const float M = across_groups_max<L>(t.m);
+    t.scale(M == -INFINITY ? 1.f : __expf(t.m - M));  // exp(-inf) = 0 drops a lane group without a piece
+    t.m = M;
+    t.z = across_groups_sum<L>(t.z);
 #pragma unroll
-    for (int off = L; off < kWave; off <<= 1) {
-      Soft<SAVE> o;
-      o.m = __shfl_xor(t.m, off);
-      o.z = __shfl_xor(t.z, off);
+    for (int i = 0; i < 8; ++i) t.acc[i] = across_groups_sum<L>(t.acc[i]);
+    if (SAVE) {
+      t.zm = across_groups_sum<L>(t.zm);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o.acc[i] = __shfl_xor(t.acc[i], off);
-      if (SAVE) {
-        o.zm = __shfl_xor(t.zm, off);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o.accm[i] = __shfl_xor(t.accm[i], off);
-      }
-      soft_merge<SAVE>(t, o);
+      for (int i = 0; i < 8; ++i) t.accm[i] = across_groups_sum<L>(t.accm[i]);
     }
     GatArgs b = a;
     b.enter_block(bj);
@@ -478,20 +477,22 @@ static void launch_gat_tasks(int L, int lh, unsigned waves, hipStream_t s, const
 }
 
 template <int L>
-static void launch_gat_finish_l(bool save, dim3 grid, hipStream_t s, const GatArgs& a, const TaskView& v) {
-  if (save) gat_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split);
-  else gat_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split);
+static void launch_gat_finish_l(bool save, dim3 grid, int per_wave, hipStream_t s, const GatArgs& a, const TaskView& v) {
+  if (save) gat_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+  else gat_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
 }
 
-static void launch_gat_finish(int L, bool save, dim3 grid, hipStream_t s, const GatArgs& a, const TaskView& v) {
+static void launch_gat_finish(int L, bool save, hipStream_t s, const GatArgs& a, const TaskView& v) {
+  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
-    case 1: launch_gat_finish_l<1>(save, grid, s, a, v); break;
-    case 2: launch_gat_finish_l<2>(save, grid, s, a, v); break;
-    case 4: launch_gat_finish_l<4>(save, grid, s, a, v); break;
-    case 8: launch_gat_finish_l<8>(save, grid, s, a, v); break;
-    case 16: launch_gat_finish_l<16>(save, grid, s, a, v); break;
-    case 32: launch_gat_finish_l<32>(save, grid, s, a, v); break;
-    default: launch_gat_finish_l<64>(save, grid, s, a, v); break;
+    case 1: launch_gat_finish_l<1>(save, grid, per_wave, s, a, v); break;
+    case 2: launch_gat_finish_l<2>(save, grid, per_wave, s, a, v); break;
+    case 4: launch_gat_finish_l<4>(save, grid, per_wave, s, a, v); break;
+    case 8: launch_gat_finish_l<8>(save, grid, per_wave, s, a, v); break;
+    case 16: launch_gat_finish_l<16>(save, grid, per_wave, s, a, v); break;
+    case 32: launch_gat_finish_l<32>(save, grid, per_wave, s, a, v); break;
+    default: launch_gat_finish_l<64>(save, grid, per_wave, s, a, v); break;
   }
 }
 
@@ -534,7 +535,7 @@ static hgnn_status run_gat_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, Ga
     HGNN_LAUNCH_CHECK("gat_task_kernel");
   }
   if (v.n_split > 0) {
-    launch_gat_finish(L, save, dim3(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * G))), s, a, v);
+    launch_gat_finish(L, save, s, a, v);
     HGNN_LAUNCH_CHECK("gat_finish_kernel");
   }
   return HGNN_OK;

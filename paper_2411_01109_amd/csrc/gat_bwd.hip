@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
 
 // Follow-up kernel: sums the staged pieces of every row that has several, in order.
 template <int L, bool VEC>
-__global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, const int4_t* __restrict__ split, int n_split) {
+__global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -219,10 +219,11 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   const int f0c = active ? f0 : 0;
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
-  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
   if (i0 >= n_split) return;
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
-  if (i0 + g < n_split) q = split[i0 + g];
+  if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
+  const int alone = per_wave > 1 ? 8 : 0;  // pieces that a lane group adds by itself
   // adds the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](float (&acc)[8], float& ds, pos_t first, pos_t end, pos_t stride) {
     for (pos_t k0 = first; k0 < end; k0 += 4 * stride) {
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
       }
     }
   };
-  if (q[2] > 0 && q[2] <= 8) {
+  if (q[2] > 0 && q[2] <= alone) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
     take(acc, ds, q[1], q[1] + q[2], 1);
@@ -256,21 +257,18 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
     b.enter_block(q[3]);
     if (active) bwd_row_store<VEC>(b, q[0], f0, head, leader, acc, ds);
   }
-  for (int j = 0; j < G; ++j) {
+  for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= 8) continue;
+    if (n <= alone) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
     take(acc, ds, first + g, first + n, G);
+    if (VEC) {
 #pragma unroll
-    for (int off = L; off < kWave; off <<= 1) {
-      if (VEC) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], off);
-      }
-      ds += __shfl_xor(ds, off);
+      for (int i = 0; i < 8; ++i) acc[i] = across_groups_sum<L>(acc[i]);
     }
+    ds = across_groups_sum<L>(ds);
     GatBwdArgs b = a;
     b.enter_block(bj);
     if (g == 0 && active) bwd_row_store<VEC>(b, rj, f0, head, leader, acc, ds);
@@ -373,15 +371,16 @@ static void launch_bwd_tasks(int L, int lh, unsigned waves, hipStream_t s, const
 
 template <bool VEC>
 static void launch_bwd_finish(int L, hipStream_t s, const GatBwdArgs& a, const TaskView& v) {
-  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
+  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
-    case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 2: gat_bwd_finish_kernel<2, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 4: gat_bwd_finish_kernel<4, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 8: gat_bwd_finish_kernel<8, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 16: gat_bwd_finish_kernel<16, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    case 32: gat_bwd_finish_kernel<32, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
-    default: gat_bwd_finish_kernel<64, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split); break;
+    case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 2: gat_bwd_finish_kernel<2, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 4: gat_bwd_finish_kernel<4, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 8: gat_bwd_finish_kernel<8, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 16: gat_bwd_finish_kernel<16, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 32: gat_bwd_finish_kernel<32, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    default: gat_bwd_finish_kernel<64, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
   }
 }
 

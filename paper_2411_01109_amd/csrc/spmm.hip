@@ -735,7 +735,7 @@ __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t f
 
 // F32: pieces staged in fp32, n_split is a bound and the number is in *totals
 template <int L, bool F32>
-__global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split,
+__global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split, int per_wave,
                                                                   const TaskTotals* __restrict__ totals) {
   if (F32) n_split = totals->n_split;
   constexpr int G = kWave / L;
@@ -744,26 +744,28 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G;
+  const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
   if (i0 >= n_split) return;
   int4_t q = {0, 0, 0, 0};
-  if (i0 + g < n_split) q = split[i0 + g];
+  if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
+  const int alone = per_wave > 1 ? kFinishShort : 0;
   half_t* const Y = a.Y;
-  if (q[2] > 0 && q[2] <= kFinishShort) {
+  if (q[2] > 0 && q[2] <= alone) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
     else pieces_accumulate<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
     a.Y = Y + int64_t(q[3]) * a.block_y_stride;
     if (active) store_row(a, q[0], f0, acc, 1.f);
   }
-  for (int j = 0; j < G; ++j) {
+  for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= kFinishShort) continue;
+    if (n <= alone) continue;
     const int r = __shfl(q[0], j * L), first = __shfl(q[1], j * L), b = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
     else pieces_accumulate<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
-    groups_reduce<L>(acc);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = across_groups_sum<L>(acc[i]);
     a.Y = Y + int64_t(b) * a.block_y_stride;
     if (g == 0 && active) store_row(a, r, f0, acc, 1.f);
   }
@@ -1405,21 +1407,22 @@ static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const Tas
 }
 
 template <int L>
-static void launch_task_finish_l(dim3 grid, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
-  if (a.stage32) spmm_task_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, v.totals);
-  else spmm_task_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, nullptr);
+static void launch_task_finish_l(dim3 grid, int per_wave, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
+  if (a.stage32) spmm_task_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, v.totals);
+  else spmm_task_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, nullptr);
 }
 
 static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
-  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * (kWave / L))));
+  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
-    case 1: launch_task_finish_l<1>(grid, s, a, v); break;
-    case 2: launch_task_finish_l<2>(grid, s, a, v); break;
-    case 4: launch_task_finish_l<4>(grid, s, a, v); break;
-    case 8: launch_task_finish_l<8>(grid, s, a, v); break;
-    case 16: launch_task_finish_l<16>(grid, s, a, v); break;
-    case 32: launch_task_finish_l<32>(grid, s, a, v); break;
-    default: launch_task_finish_l<64>(grid, s, a, v); break;
+    case 1: launch_task_finish_l<1>(grid, per_wave, s, a, v); break;
+    case 2: launch_task_finish_l<2>(grid, per_wave, s, a, v); break;
+    case 4: launch_task_finish_l<4>(grid, per_wave, s, a, v); break;
+    case 8: launch_task_finish_l<8>(grid, per_wave, s, a, v); break;
+    case 16: launch_task_finish_l<16>(grid, per_wave, s, a, v); break;
+    case 32: launch_task_finish_l<32>(grid, per_wave, s, a, v); break;
+    default: launch_task_finish_l<64>(grid, per_wave, s, a, v); break;
   }
 }
 

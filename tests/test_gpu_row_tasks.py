@@ -306,3 +306,42 @@ def test_plain_spmm_with_a_smaller_workspace(hgnn, dev, F, what):
         Y = torch.full((V, pitch), 3.0, dtype=torch.float16, device=dev)
         hgnn.hgnn_spmm(g, None if w is None else up(w, dev), 1, up(Xh, dev), Y, F=F, workspace=torch.empty(n, dtype=torch.uint8, device=dev))
         compare(f"workspace of {n}", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)
+
+
+@pytest.mark.parametrize("V", [65536, 65537])
+def test_many_rows_of_several_pieces(hgnn, dev, V):
+    """Up to 65536 rows of several pieces take a wave each in the follow-up kernels, more of them a lane group; pieces of one non-zero."""
+    print(f"follow-up rows V={V}", flush=True)
+    r = np.random.default_rng(V)
+    deg = r.integers(2, 6, size=V)
+    deg[:12] = (8, 9, 10, 16, 17, 31, 33, 40, 64, 65, 66, 300)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, V, size=d)) for d in deg]).astype(np.int32)
+    H, D = 2, 8
+    F = H * D
+    X, dO = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
+    w = f16(r.standard_normal((col.size, H)))
+    a_l, a_r = f16(0.3 * r.standard_normal(F)), f16(0.3 * r.standard_normal(F))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    gt = hgnn.hgnn_transpose(g)
+    p, pt, pt1 = (hgnn.hgnn_plan_create(x, s, F, H, col_blocks=1) for x, s in ((g, 1), (gt, 256), (gt, 1)))
+    half = lambda *s: torch.full(s, 7.0, dtype=torch.float16, device=dev)
+    f32 = lambda *s: torch.full(s, 7.0, dtype=torch.float32, device=dev)
+    Y = half(V, F)
+    hgnn.hgnn_spmm_discretized(p, g, up(w, dev), H, up(X, dev), Y)
+    ref, sabs = oracle.spmm(rowptr, col, X, w=w, H=H, want_sabs=True)
+    compare("follow-up", down(Y), ref, sabs)
+    Xd, ald, ard, dOd = up(X, dev), up(a_l, dev), up(a_r, dev), up(dO, dev)
+    out, outm, lse, csum = half(V, F), half(V, F), f32(V, H), f32(V, H)
+    hgnn.hgnn_gat_forward_fused_save(g, p, H, D, Xd, Xd, ald, ard, out, lse, outm, csum)
+    oref, lref, oabs, mref, cref = oracle.gat_forward(rowptr, col, X, X, a_l, a_r, H, slope=0.2, want_saved=True)
+    compare("out", down(out), oref, oabs)
+    compare("out_masked", down(outm), mref, oabs)
+    assert np.abs(down(csum) - cref).max() <= 2e-3 and np.abs(down(lse) - lref).max() <= 2e-3 + 1e-3 * np.abs(lref).max()
+    got = []
+    for q in (pt, pt1):
+        dV, d_el, d_er = half(V, F), half(V, H), half(V, H)
+        hgnn.hgnn_gat_backward_fused_saved(g, p, gt, q, H, D, Xd, Xd, ald, ard, out, lse, outm, csum, dOd, dV, d_el, d_er)
+        got.append([down(t).astype(np.float64) for t in (dV, d_el, d_er)])
+    for a, b in zip(*got):  # one rounding of a row against one of each of its pieces beside it
+        assert np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(a)
