@@ -194,19 +194,22 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
     cbool = lambda v: "true" if v else "false"
     near = cbool(V * X.stride(0) * 2 < (1 << 32) - 8192)  # the table is addressed in 32 bits
 
-    def task_name(hw, mapped=True, per_edge=False, free=False):
+    def task_name(hw, mapped=True, per_edge=False, free=0):
         """The SpMM over row tasks: lanes per row, 0 = no edge value / 1 = edge values / 2 = a factor per column, table within
-        32 bits, values behind the edge-id map, heads of an edge's values read at once, tasks counted on the device."""
+        32 bits, values behind the edge-id map, heads of an edge's values read at once, tasks counted on the device (1) and long
+        rows cut at column ranges there (2)."""
         return (f"hgnn::spmm_task_kernel<{Lg}, {2 if per_edge else (1 if hw else 0)}, {near}, {cbool(hw and mapped)}, {max(hw, 1)}, "
-                f"{cbool(free)}>")
+                f"{free}>")
 
     # the plan-free SpMM walks the columns in passes where its workspace has room for the partial rows (with one column there
     # are none); otherwise row tasks, for narrow features rows and the chunks of long rows in one launch
-    passes = ws_bytes > hgnn.hgnn_spmm_workspace(V, 1, E, F)
+    more = ws_bytes > hgnn.hgnn_spmm_workspace(V, 1, E, F)
+    passes = more and E >= 128 * V  # else the room is for long rows cut at column ranges
+    wide = V * F * 2 >= ((128 << 20) if F >= 128 else (256 << 20))
 
     def row_name(hw, mapped):
         if not passes and ws_bytes and (F >= (32 if hw else 64) or (hw and mapped)):
-            return task_name(hw, mapped, free=True)
+            return task_name(hw, mapped, free=2 if more and ((hw and mapped) or wide) else 1)
         return f"hgnn::spmm_{'row_pass' if passes else ('row_hub' if ws_bytes else 'row')}_kernel<{Lg}, {cbool(hw)}>"
 
     ops = []  # (name, kernel or a pattern of its name, min bytes, fn, requested bytes)

@@ -218,7 +218,10 @@ void hgnn_release_cached_memory(void);
  * threshold T kept within 256..1024 non-zeros) are cut into chunks of 512 non-zeros that are
  * reduced by a wavefront each and added in chunk order (up to nnz/512 + nnz/T + 2 partial rows in
  * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that, and for sizes
- * that miss the query's answer by 512 bytes or less).
+ * that miss the room of the pieces by 512 bytes or less).
+ * Beyond 4 Mi non-zeros, where the table X is larger than the L2s together, the query's answer also has
+ * room for rows of more than 256 non-zeros in pieces that end where column ranges do; where that pays
+ * (edge values behind a map; wide or large tables) the call takes it.  With a smaller workspace it does not.
  * workspace == NULL is allowed: every long row is then reduced by a single wavefront (correct,
  * slow on hubs).
  * Where the table X (ncols rows of F halves) is beyond three L2s, fits three quarters of the

@@ -422,7 +422,19 @@ struct TaskScratch {
   size_t bytes;
 };
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
+// What it takes beside that to cut the long rows at column ranges (they are then all of the rows that have several pieces).
+struct RangeScratch {
+  int32_t* lists;      // ranges.h
+  int32_t* long_rows;  // [windows]
+  TaskTotals* totals;  // n_split: the long rows, n_range: their pieces
+  int4* task;
+  float* staging;
+  int64_t cap;         // most pieces
+  size_t bytes;
+};
+RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const RangeScratch& r, const int32_t* col, int ncols, hipStream_t s);
 struct TaskCounts {
   explicit TaskCounts(SetupStream& s) : counts(s), secs(s), mail(s) {}
   DevTemp counts, secs;

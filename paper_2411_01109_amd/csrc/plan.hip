@@ -414,7 +414,12 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
   const int b = int(blockIdx.x) - range_blocks;
   if (b < 0) {
     const int w = int(blockIdx.x) * kRangeGroup;
-    range_write(ranges, w, long_at[w], first_slot, rtask, rsplit);
+    RangePlace at;
+#pragma unroll
+    for (int x = 0; x < kRanges; ++x) at.task[x] = ranges.count[x * ranges.nwin + w];
+    at.slot = first_slot + ranges.slots[w];
+    at.split = long_at[w];
+    range_write(ranges, w, at, rtask, rsplit);
   } else if (b < n) {
     task_write<false>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split);
   } else if (b < n + list_blocks) {
@@ -422,6 +427,29 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
   } else {
     seg_rows(q.rowptr, q.nrows, tq.nnz, q.S, nseg, (int64_t(b) - n - list_blocks) * kBlock + threadIdx.x, seg_lo, seg_hi);
   }
+}
+
+// Where rows are cut.  A segment size is the least length because such rows leave staged partial rows (fp16, as ever) in any case.
+// us a call, rows in pieces of S / at column ranges (F = 64 and one head if not said; power law unless log-normal):
+//   table, non-zeros                  SpMM, edge values   behind a map   SDDMM       attention fwd (saving), bwd
+//   614 MB, 62 M, F = 128               1711 / 1285        2683 / 2043
+//   307 MB, 62 M, F = 64 by degrees      870 / 740
+//   154 MB, 31 M                         359 / 328          772 / 624    350 / 332
+//   256 MB, 13 M, F = 256                747 / 618         1012 / 783
+//   77 MB, 60 M, F = 16                  738 / 611         1640 / 1422
+//   77 MB, 12 M                          129 / 118          280 / 222    125 / 115
+//   134 MB, 26 M log-normal, 4 heads     930 / 819         1183 / 1169   937 / 802
+//   67 MB, 5.5 M, F = 128                                                            179 / 166, 213 / 195
+//   34 MB, 21 M                          142 / 135          352 / 312    136 / 128
+//   34 MB, 5.5 M, 4 heads                 59 / 59           123 / 114     59 / 59    105 / 102, 132 / 124
+//   13 MB, 8 M                            58 / 61           106 / 101     52 / 52
+//   8 MB, 8 M                             56 / 64            96 / 94      50 / 53
+//   34 MB, 2.1 M, F = 128: GIN layer forward 44 / 46; 10 MB, 1.3 M: by degrees 30 / 48
+// The cuts ride beside the checks of the columns and the lists beside the others (a plan of 5.5 M non-zeros 72 -> 82 us), so the line lies
+// where the calls begin to gain: at four L2s.
+static int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2) {
+  constexpr int64_t kLeastNnz = int64_t(4) << 20;
+  return nnz > kLeastNnz && ncols * max_F * 2 > 4 * l2 ? S + 1 : kNoRanges;
 }
 
 // Validates the graph g and builds the segment arrays, row lists and row tasks of p for it (p->S, p->nseg, p->max_F set by the

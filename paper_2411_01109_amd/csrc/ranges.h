@@ -16,29 +16,6 @@ constexpr int kRangeGroup = 4;    // windows of kTaskWindow rows whose pieces ar
                                   // heads, attention forward 110, 103, 102 us, SDDMM 62.5, 59.8, 58.6; a plan 76, 79, 82)
 constexpr int kRangePiece = 256;  // most non-zeros of a piece (also at most S)
 
-// Where rows are cut.  A segment size is the least length because such rows leave staged partial rows (fp16, as ever) in any case.
-// us a call, rows in pieces of S / at column ranges (F = 64 and one head if not said; power law unless log-normal):
-//   table, non-zeros                  SpMM, edge values   behind a map   SDDMM       attention fwd (saving), bwd
-//   614 MB, 62 M, F = 128               1711 / 1285        2683 / 2043
-//   307 MB, 62 M, F = 64 by degrees      870 / 740
-//   154 MB, 31 M                         359 / 328          772 / 624    350 / 332
-//   256 MB, 13 M, F = 256                747 / 618         1012 / 783
-//   77 MB, 60 M, F = 16                  738 / 611         1640 / 1422
-//   77 MB, 12 M                          129 / 118          280 / 222    125 / 115
-//   134 MB, 26 M log-normal, 4 heads     930 / 819         1183 / 1169   937 / 802
-//   67 MB, 5.5 M, F = 128                                                            179 / 166, 213 / 195
-//   34 MB, 21 M                          142 / 135          352 / 312    136 / 128
-//   34 MB, 5.5 M, 4 heads                 59 / 59           123 / 114     59 / 59    105 / 102, 132 / 124
-//   13 MB, 8 M                            58 / 61           106 / 101     52 / 52
-//   8 MB, 8 M                             56 / 64            96 / 94      50 / 53
-//   34 MB, 2.1 M, F = 128: GIN layer forward 44 / 46; 10 MB, 1.3 M: by degrees 30 / 48
-// The cuts ride beside the checks of the columns and the lists beside the others (a plan of 5.5 M non-zeros 72 -> 82 us), so the line lies
-// where the calls begin to gain: at four L2s.
-static int range_min_row(int64_t nnz, int64_t ncols, int max_F, int S, int64_t l2) {
-  constexpr int64_t kLeastNnz = int64_t(4) << 20;
-  return nnz > kLeastNnz && ncols * max_F * 2 > 4 * l2 ? S + 1 : kNoRanges;
-}
-
 // Every window of kTaskWindow rows cuts its own long rows; the pieces of a window and range are sorted by length together.
 struct RangeLists {
   const int* rowptr;
@@ -46,6 +23,7 @@ struct RangeLists {
   int* cuts;   // [nrows][kRanges - 1] where a long row's share of the ranges from the second on begins
   int* count;  // [kRanges][nwin] pieces, then where they go
   int* slots;  // [nwin] pieces of a window's rows, then the first of them
+  int* long_rows;  // [nwin] long rows of a window, or nullptr (a plan has their number from its other counts)
   int nrows, nwin, piece, min_row, width;
 };
 
@@ -125,6 +103,7 @@ __device__ __forceinline__ void range_cut(const RangeLists& a, int w) {
     int all = 0;
     for (int j = 0; j < kRanges; ++j) all += s_count[j];
     a.slots[w] = all;
+    if (a.long_rows) a.long_rows[w] = n;
   }
 }
 
@@ -166,15 +145,63 @@ __device__ __forceinline__ int range_scan_all(const RangeLists& a) {
   return scan(a.count, kRanges * a.nwin);
 }
 
+// Where a group of windows puts its pieces and rows.
+struct RangePlace {
+  int task[kRanges];  // the first piece of every range
+  int slot, split;    // the first staging slot and the first entry of the rows of several pieces
+};
+
+// the same where nothing has scanned the counts: what the windows before w hold, and in *all (pieces, long rows) what all of them do
+__device__ __forceinline__ RangePlace range_place(const RangeLists& a, int w, int* all) {
+  constexpr int kSums = kRanges + 2;  // pieces of every range, pieces, long rows
+  __shared__ int s_before[kSums], s_all[kSums];
+  if (threadIdx.x < kSums) s_before[threadIdx.x] = s_all[threadIdx.x] = 0;
+  __syncthreads();
+  for (int i = kSums - 1; i >= 0; --i) {
+    const int* v = i < kRanges ? a.count + i * a.nwin : (i == kRanges ? a.slots : a.long_rows);
+    int before = 0, sum = 0;
+#pragma unroll 4
+    for (int j = threadIdx.x; j < a.nwin; j += kTaskThreads) {
+      const int n = v[j];
+      sum += n;
+      before += j < w ? n : 0;
+    }
+    before = wave_sum(before);
+    sum = wave_sum(sum);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+      atomicAdd(&s_before[i], before);
+      atomicAdd(&s_all[i], sum);
+    }
+    if (i == kSums - 1) {
+      __syncthreads();
+      if (s_all[i] == 0) break;  // no long rows
+    }
+  }
+  __syncthreads();
+  RangePlace p;
+  int first = 0;
+#pragma unroll
+  for (int x = 0; x < kRanges; ++x) {
+    p.task[x] = first + s_before[x];
+    first += s_all[x];
+  }
+  p.slot = s_before[kRanges];
+  p.split = s_before[kRanges + 1];
+  all[0] = s_all[kRanges];
+  all[1] = s_all[kRanges + 1];
+  return p;
+}
+
 // kRangeGroup windows from window w on by a workgroup of kTaskThreads, a lane per (long row, range) as in range_cut: the pieces of a range by length, so that
-// the lane groups of a wave end together; the slots of a row's pieces follow each other through the ranges.  long_before: long rows of
-// the windows before this one.
-__device__ __forceinline__ void range_write(const RangeLists& a, int w, int long_before, int first_slot, int4* __restrict__ task,
-                                            int4* __restrict__ split) {
+// the lane groups of a wave end together; the slots of a row's pieces follow each other through the ranges.
+__device__ __forceinline__ void range_write(const RangeLists& a, int w, const RangePlace& place, int4* __restrict__ task, int4* __restrict__ split) {
   __shared__ int s_row[kRangeGroup * kTaskWindow], s_n, at[kRanges][kRangePiece + 1];
-  __shared__ int s_wave[kTaskThreads / kWave];
+  __shared__ int s_wave[kTaskThreads / kWave], s_first[kRanges];
   const int t = threadIdx.x, x = t % kRanges;
   if (t == 0) s_n = 0;
+#pragma unroll
+  for (int y = 0; y < kRanges; ++y)
+    if (t == y) s_first[y] = place.task[y];
   for (int k = t; k < kRanges * (kRangePiece + 1); k += kTaskThreads) at[0][k] = 0;
   __syncthreads();
   {
@@ -201,7 +228,7 @@ __device__ __forceinline__ void range_write(const RangeLists& a, int w, int long
   const int lane = t & (kWave - 1);
   const bool rising = w / kRangeGroup % 2 != 0;  // in turn, so that a wave across two groups of windows takes equal lengths, too
   for (int y = t / kWave; y < kRanges; y += kTaskThreads / kWave) {
-    int carry = a.count[y * a.nwin + w];
+    int carry = s_first[y];
     for (int k0 = 0; k0 <= kRangePiece; k0 += kWave) {
       const int k = rising ? k0 + lane : kRangePiece - k0 - lane;
       const bool in = k >= 0 && k <= kRangePiece;
@@ -215,7 +242,7 @@ __device__ __forceinline__ void range_write(const RangeLists& a, int w, int long
       carry += __shfl(incl, kWave - 1);
     }
   }
-  int next = first_slot + a.slots[w];
+  int next = place.slot;
   for (int i0 = 0; i0 < n; i0 += kRows) {  // uniform: the workgroup scans
     const int i = i0 + t / kRanges;
     RangeShare s{0, 0, 0, 0};
@@ -223,7 +250,7 @@ __device__ __forceinline__ void range_write(const RangeLists& a, int w, int long
     int total;
     const int incl = range_scan(s.m, s_wave, &total);  // (its barriers are behind the offsets in `at`)
     const int slot = next + incl - s.m, end = __shfl(next + incl, kRanges - 1, kRanges);
-    if (i < n && x == 0) split[long_before + i] = make_int4(s_row[i], slot, end - slot, 0);
+    if (i < n && x == 0) split[place.split + i] = make_int4(s_row[i], slot, end - slot, 0);
     for (int j = 0; j < s.m; ++j) {
       const int len = j + 1 < s.m ? s.part : s.len - j * s.part;
       task[atomicAdd(&at[x][len], 1)] = make_int4(s.beg + j * s.part, len, s_row[i], slot + j);

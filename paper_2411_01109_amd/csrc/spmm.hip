@@ -562,8 +562,8 @@ __device__ __forceinline__ auto run_of(pos_t i0, pos_t end, int left) {
   else return RunLeft{left};
 }
 
-template <int L, int WM, bool NEAR, bool MAPPED, int HV, bool RANGES>
-__device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, int wid) {
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, class Enter>
+__device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, Enter&& enter) {
   constexpr int G = kWave / L;
   typedef Round<L> Rd;
   typedef TaskLds<L, WM, HV> Lds;
@@ -577,7 +577,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;  // idle lanes of a group load a valid address and drop the result
-  const TaskWave w = task_enter<L, RANGES>(v, wid, g);
+  const TaskWave w = enter(g);
   a.Y += int64_t(w.block) * a.block_y_stride;
   if (w.z1 > w.z0) {
     const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -696,14 +696,17 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
   }
 }
 
-// LOOP: the number of tasks is only known on the device, a wave takes several (the loop costs registers: not with a plan)
-template <int L, int WM, bool NEAR, bool MAPPED, int HV, bool LOOP>
+// LOOP: 1 = the number of tasks is only known on the device, a wave takes several (the loop costs registers: not with a plan); 2 = also
+// pieces at column ranges (their branch costs the others 1 to 2 %)
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, int LOOP>
 __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
   if (LOOP) {
-    const int n = task_waves<kWave / L>(v);
-    for (int wid = blockIdx.x; wid < n; wid += gridDim.x) spmm_task<L, WM, NEAR, MAPPED, HV, false>(a, v, ncols, wid);
+    const RangeWaves ranges = LOOP == 2 ? range_waves<kWave / L>(v) : RangeWaves{0, 0, 0};
+    const int n = ranges.waves + task_waves<kWave / L>(v);
+    for (int wid = blockIdx.x; wid < n; wid += gridDim.x)
+      spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L>(v, wid, g, ranges); });
   } else {
-    spmm_task<L, WM, NEAR, MAPPED, HV, true>(a, v, ncols, blockIdx.x);
+    spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L>(v, blockIdx.x, g); });
   }
 }
 
@@ -1182,11 +1185,42 @@ static PassLayout pass_layout(int64_t nrows, int npass, int F) {
 static bool free_tasks_pay(int F, bool edge_values, bool mapped) { return mapped || F >= (edge_values ? 32 : 64); }
 
 constexpr int kFreePiece = 512;  // non-zeros per piece
+constexpr int kRangeRow = 256;   // longer rows are cut at column ranges where that pays
 constexpr size_t kNearMiss = 512;
 // scratch of the tasks, 0 where no row can be long (then one wave per row does)
 static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
   if (hub_layout(nnz, hub_threshold(nrows, nnz), F).bytes == 0) return 0;
   return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F).bytes;
+}
+
+// Where long rows of the plan-free SpMM are cut at column ranges, as with a plan: room for it where the table is beyond what the L2s hold
+// together, and done where it pays.  The pieces are staged in fp32, so rows of 257 non-zeros are long enough.  us, rows in pieces /
+// at column ranges, listing included (some 12 us of it):
+//                                       edge values    behind a map
+//   31 M power law, 154 MB, F = 64         366 / 380       853 / 683
+//   54 M, 307 MB, F = 64                   755 / 698      1740 / 1398
+//   12 M, 77 MB, F = 64                    138 / 145       292 / 253
+//   12 M, 154 MB, F = 128                  281 / 255       479 / 395
+//   5.5 M, 67 MB, F = 128                  119 / 126       192 / 176
+//   5.5 M, 134 MB, F = 256                 255 / 220       342 / 283
+//   14 M, 512 MB, F = 256                  766 / 684       995 / 874
+//   60 M, 77 MB, F = 16                    742 / 741      1840 / 1545
+//   20 M log-normal, 51 MB, F = 64         400 / 398       725 / 728
+//   20 M uniform (no long row), 128 MB     420 / 420       777 / 777
+//   5.5 M, 34 MB, F = 64                    71 / 80        121 / 122
+static bool free_ranges_fit(int64_t ncols, int64_t nnz, int F, int64_t l2) { return nnz > (int64_t(4) << 20) && ncols * F * 2 > 8 * l2; }
+static bool free_ranges_pay(bool mapped, int64_t ncols, int F) {
+  int64_t l2 = 0, llc = 0;
+  device_cache_bytes(&l2, &llc);
+  return mapped || ncols * F * 2 >= (F >= 128 ? llc / 2 : llc);
+}
+static size_t free_range_offset(size_t hub_bytes, size_t task_bytes) { return (std::max(hub_bytes, task_bytes) + 255) / 256 * 256; }
+// their scratch behind that of the tasks and hub chunks; 0: none
+static size_t free_range_bytes(int64_t nrows, int64_t ncols, int64_t nnz, int F) {
+  int64_t l2 = 0, llc = 0;
+  device_cache_bytes(&l2, &llc);
+  if (!free_ranges_fit(ncols, nnz, F, l2) || free_task_bytes(nrows, nnz, F) == 0) return 0;
+  return range_scratch_at(nullptr, nrows, nnz, kRangeRow, F).bytes;
 }
 
 static HubLists hub_lists_at(void* base, const HubLayout& o) {
@@ -1291,12 +1325,16 @@ static void launch_tasks_l(int wm, bool mapped, unsigned waves, size_t least_lds
   do {                                                                                                                      \
     const size_t lds = std::max(TaskLds<L, WM, HV>::bytes(a.H), least_lds);                                                                 \
     if constexpr (WM < 2) {                                                                                                 \
+      if (v.rtotals) {                                                                                                      \
+        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 2><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
+        break;                                                                                                              \
+      }                                                                                                                     \
       if (v.totals) {                                                                                                       \
-        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, true><<<grid, kWave, lds, s>>>(a, v, ncols);                              \
+        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 1><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
         break;                                                                                                              \
       }                                                                                                                     \
     }                                                                                                                       \
-    spmm_task_kernel<L, WM, NEAR, MAPPED, HV, false><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
+    spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 0><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
   } while (0)
   const int hv = (reinterpret_cast<uintptr_t>(a.w) & uintptr_t(2 * a.H - 1)) == 0 ? a.H : 0;
   if (wm == 0) {
@@ -1487,27 +1525,29 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
 
 // The plan-free SpMM over row tasks that are listed in the scratch by two small launches: rows sorted by length and cut into
 // pieces, so that lane groups end together and a hub keeps many compute units busy, as with a plan.  Pieces are staged in
-// fp32, a row is rounded once.  A wave per G rows in storage order, hubs in chunks of their own, took as long as its longest
+// fp32, a row is rounded once; long rows at column ranges where range_scratch is given.  A wave per G rows in storage order, hubs in chunks of their own, took as long as its longest
 // row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.54 -> 1.23 ms together.
-static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, hipStream_t s) {
+static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, void* range_scratch, hipStream_t s) {
   const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
-  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz, kNoRanges};
-  const hgnn_status st = task_build_in(q, t, s);
+  const RangeScratch r = range_scratch_at(range_scratch, g->nrows, g->nnz, kRangeRow, a.F);
+  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz, range_scratch ? kRangeRow + 1 : kNoRanges};
+  const hgnn_status st = range_scratch ? task_build_in(q, t, r, g->col, g->ncols, s) : task_build_in(q, t, s);
   if (st != HGNN_OK) return st;
   const int L = pow2_at_least((a.F + 7) / 8);
   const bool mapped = a.w && a.eid;
   int64_t grid = 0;
-  const TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
-  a.staging = reinterpret_cast<half_t*>(t.staging);
+  TaskView v = task_view(t, range_scratch ? &r : nullptr, q, g->nnz, kWave / L, &grid);
+  a.staging = reinterpret_cast<half_t*>(range_scratch ? r.staging : t.staging);
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;
   const int wm = a.w ? 1 : 0;
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  const size_t least = least_task_lds(mapped, false, a, g->ncols, l2, llc);
+  const size_t least = least_task_lds(mapped, range_scratch != nullptr, a, g->ncols, l2, llc);
   if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");
+  if (range_scratch) v.totals = r.totals;  // the rows of several pieces are the long ones
   launch_task_finish(L, s, a, v);
   HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
   return HGNN_OK;
@@ -1568,8 +1608,12 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
     HGNN_REQUIRE(one_sweep || scratch_bytes >= task_bytes || scratch_bytes == base_bytes || task_bytes - scratch_bytes > kNearMiss,
                  HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who, scratch_bytes, task_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
-    if (scratch_bytes >= task_bytes && free_tasks_pay(F, edge_val != nullptr, edge_val && g->eid))
-      return spmm_free_tasks(g, a, scratch, s);
+    if (scratch_bytes >= task_bytes && free_tasks_pay(F, edge_val != nullptr, edge_val && g->eid)) {
+      const size_t range_at = free_range_offset(base_bytes, task_bytes), range_bytes = free_range_bytes(g->nrows, g->ncols, g->nnz, F);
+      const bool ranges = range_bytes > 0 && npass == 1 && !one_sweep && scratch_bytes >= range_at + range_bytes &&
+                          free_ranges_pay(edge_val && g->eid, g->ncols, F);
+      return spmm_free_tasks(g, a, scratch, ranges ? static_cast<char*>(scratch) + range_at : nullptr, s);
+    }
     // (a workspace, or the static array, can be too small for the tasks and still hold the hubs)
     h = hub_lists_at(scratch, lay);
     hub_zero_kernel<<<1, kBlock, 0, s>>>(h);
@@ -1601,8 +1645,9 @@ size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F)
   if (ncols <= 0 && base <= held && task > held) return base;
   size_t need = std::max(base, task);
   const int npass = ncols > 0 ? row_passes(nrows, ncols, nnz, F) : 1;
-  if (npass > 1) need += size_t(pass_layout(nrows, npass, F).bytes);
-  return need;
+  if (npass > 1) return need + size_t(pass_layout(nrows, npass, F).bytes);
+  const size_t ranges = ncols > 0 ? free_range_bytes(nrows, ncols, nnz, F) : 0;
+  return ranges > 0 ? free_range_offset(base, task) + ranges : need;
 }
 
 hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X, int64_t ldx,

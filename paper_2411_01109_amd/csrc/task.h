@@ -20,6 +20,7 @@ struct TaskView {
   const int4_t* task;
   const int4_t* rtask;       // pieces of rows cut at column ranges: an eighth per XCD, so that its L2 keeps to one range of the table
   int n_rtask, rshare;       // how many; per XCD (a multiple of the lane groups of a wave)
+  const TaskTotals* rtotals; // device; without a plan, where rows are cut at column ranges: how many pieces there are
   const int* zrow;
   const hgnn_task_sec* sec;
   const int4_t* split;
@@ -49,6 +50,9 @@ struct TaskView {
 // nothing to come back to (6 M, 35 a row: SpMM 124.7 / 127.5); plan-free calls, whose numbers are on the device, gain nothing.
 inline bool comes_back(bool mapped, int64_t table_bytes, int64_t llc) { return mapped || table_bytes > llc / 8 * 3; }
 
+// pieces at column ranges per XCD, whole waves of G lane groups of them
+__host__ __device__ inline int range_share(int n, int G) { return int((pos_t(n) + kXcds * G - 1) / (kXcds * G)) * G; }
+
 // host: the launch shape of tasks t for G lane groups per wave; zeros = false leaves the empty rows out
 inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool zeros = true) {
   TaskView v{};
@@ -62,7 +66,7 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool 
   v.nb = t->nb;
   v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
   v.n_rtask = t->n_rtask;
-  v.rshare = int(ceil_div(ceil_div(t->n_rtask, kXcds), G) * G);
+  v.rshare = range_share(t->n_rtask, G);
   int64_t n = int64_t(kXcds) * v.rshare / G;
   for (int b = 0; b < t->nb; ++b) {
     const hgnn_task_sec& s = t->host[size_t(b)];
@@ -121,7 +125,7 @@ __device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, Ru
 }
 
 // the same for tasks whose numbers are on the device; *grid = workgroups to launch
-inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz, int G, int64_t* grid) {
+inline TaskView task_view(const TaskScratch& t, const RangeScratch* r, const TaskSource& q, int64_t nnz, int G, int64_t* grid) {
   TaskView v{};
   v.task = reinterpret_cast<const int4_t*>(t.task);
   v.zrow = t.zrow;
@@ -130,7 +134,11 @@ inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz
   v.totals = t.totals;
   v.n_split = int(nnz / q.S + 1);
   v.nb = 1;
-  const int64_t n = nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
+  if (r) {
+    v.rtask = reinterpret_cast<const int4_t*>(r->task);
+    v.rtotals = r->totals;
+  }
+  const int64_t n = (r ? int64_t(kXcds) * range_share(int(r->cap), G) / G : 0) + nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
   v.chunk = kTaskChunk;
   while (v.chunk > 1 && int64_t(v.chunk) * 64 > n) v.chunk >>= 1;
   constexpr int64_t kMostWaves = 65536;  // beyond this the waves take several tasks each
@@ -165,15 +173,23 @@ struct TaskWave {
 
 // wid is the same on all lanes of the wave; g = lane / L.  Everything up to the task is scalar; a choice between two addresses to
 // load from would turn all of it into vector code (5.5 M non-zeros, SDDMM 58 -> 62 us, attention forward 82 -> 87).
-// RANGES: there may be pieces of rows cut at column ranges (never where the numbers are on the device).
-template <int L, bool RANGES = true>
-__device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
+// ranges: the pieces of rows cut at column ranges, if any.
+struct RangeWaves {
+  int waves, share, n;  // waves that take them, pieces per XCD, pieces
+};
+template <int G>
+__device__ __forceinline__ RangeWaves range_waves(const TaskView& v) {  // without a plan
+  const int n = v.rtotals ? v.rtotals->n_range : 0, share = range_share(n, G);
+  return RangeWaves{share / G * kXcds, share, n};
+}
+template <int L>
+__device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g, const RangeWaves& ranges) {
   constexpr int G = kWave / L;
   TaskWave w;
-  if (RANGES && wid < v.first_wave[0]) {
-    const int i = (wid >> 3) * G + g, k = (wid & 7) * v.rshare + i;
+  if (wid < ranges.waves) {
+    const int i = (wid >> 3) * G + g, k = (wid & 7) * ranges.share + i;
     int4_t t = {0, 0, -1, -1};
-    if (k < v.n_rtask) t = v.rtask[k];
+    if (k < ranges.n) t = v.rtask[k];
     w.block = w.first = 0;
     w.whole = false;
     w.zrow = v.zrow;
@@ -185,6 +201,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
     w.span = w.step = Round<L>::R;
     return w;
   }
+  wid += v.first_wave[0] - ranges.waves;  // (no change with a plan)
   int b = 0;
   while (b + 1 < v.nb && wid >= v.first_wave[b + 1]) ++b;
   const hgnn_task_sec s = v.sec[b];
@@ -236,6 +253,11 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
     w.step = w.span * G;
   }
   return w;
+}
+
+template <int L>
+__device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
+  return task_enter<L>(v, wid, g, RangeWaves{v.first_wave[0], v.rshare, v.n_rtask});
 }
 
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these

@@ -106,7 +106,6 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
   __shared__ int before[kTaskCounters], all[kTaskCounters];
   hgnn_task_sec s;
   if (SELF) {
-    q.range_min = kNoRanges;
     if (threadIdx.x < kTaskCounters) before[threadIdx.x] = all[threadIdx.x] = 0;
     __syncthreads();
     int b4[kTaskCounters] = {0, 0, 0, 0, 0}, sum[kTaskCounters] = {0, 0, 0, 0, 0};

@@ -7,7 +7,9 @@
 // runs gave for free, lane groups that end together, comes from sorting the rows of a window by length.
 #include <string.h>
 
-#include "task_build.h"
+#include <algorithm>
+
+#include "ranges.h"
 
 namespace hgnn {
 
@@ -158,6 +160,83 @@ hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t
   task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow,
                                                                             t.split);
   HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
+  return HGNN_OK;
+}
+
+RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F) {
+  // a long row has more than S non-zeros and at most kRanges pieces beside one per kRangePiece non-zeros
+  const int64_t nwin = ceil_div(nrows, kTaskWindow);
+  RangeScratch r{};
+  char* const p = static_cast<char*>(base);
+  int64_t at = 0;
+  auto take = [&](int64_t bytes) {
+    char* x = p ? p + at : nullptr;
+    at += (bytes + 255) / 256 * 256;
+    return x;
+  };
+  r.cap = kRanges * (nnz / S + 1) + nnz / std::min<int64_t>(S, kRangePiece) + 1;
+  r.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
+  r.lists = reinterpret_cast<int32_t*>(take(int64_t(range_bytes(int(nrows), int(nwin)))));
+  r.long_rows = reinterpret_cast<int32_t*>(take(nwin * 4));
+  r.task = reinterpret_cast<int4*>(take(r.cap * 16));
+  r.staging = reinterpret_cast<float*>(take(r.cap * int64_t((F + 7) & ~7) * 4));
+  r.bytes = size_t(at);
+  return r;
+}
+
+// Without a plan and with column ranges: two launches, in each of which the workgroups for the long rows come first.
+__global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, int nwin, int* __restrict__ counts, RangeLists ranges) {
+  if (int(blockIdx.x) < nwin) {
+    range_cut<kTaskThreads>(ranges, int(blockIdx.x));
+    return;
+  }
+  __shared__ int total[kTaskCounters];
+  const int w = int(blockIdx.x) - nwin;
+  if (threadIdx.x < kTaskCounters) total[threadIdx.x] = 0;
+  __syncthreads();
+  int n[kTaskAll] = {0, 0, 0, 0, 0, 0};
+  for (int u = 0; u < kTaskRowsPerThread; ++u) {
+    const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
+    if (r >= q.nrows) break;
+    task_count_row(q, q.rowptr, int(r), n);
+  }
+#pragma unroll
+  for (int i = 0; i < kTaskCounters; ++i) {
+    const int v = wave_sum(n[i]);
+    if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
+  }
+  __syncthreads();
+  if (threadIdx.x < kTaskCounters) counts[int64_t(threadIdx.x) * nwin + w] = total[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts, hgnn_task_sec* __restrict__ sec,
+                                                                   TaskTotals* __restrict__ totals, int4* __restrict__ task,
+                                                                   int* __restrict__ zrow, int4* __restrict__ split, RangeLists ranges,
+                                                                   int range_blocks, TaskTotals* __restrict__ range_totals,
+                                                                   int4* __restrict__ rtask) {
+  const int b = int(blockIdx.x) - range_blocks;
+  if (b >= 0) {
+    task_write<true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split);
+    return;
+  }
+  const int w = int(blockIdx.x) * kRangeGroup;
+  int all[2];
+  const RangePlace place = range_place(ranges, w, all);
+  if (all[1] > 0) range_write(ranges, w, place, rtask, split);
+  if (w == 0 && threadIdx.x == 0) {
+    range_totals->n_range = all[0];
+    range_totals->n_split = all[1];
+  }
+}
+
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const RangeScratch& r, const int32_t* col, int ncols, hipStream_t s) {
+  const int nwin = int(ceil_div(q.nrows, kTaskWindow)), range_blocks = int(ceil_div(nwin, kRangeGroup));
+  RangeLists ranges = range_lists(q, col, ncols, nwin, r.lists);
+  ranges.long_rows = r.long_rows;
+  free_count_kernel<<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
+  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, t.sec, t.totals, t.task, t.zrow, t.split,
+                                                                               ranges, range_blocks, r.totals, r.task);
+  HGNN_LAUNCH_CHECK("free_count_kernel / free_write_kernel");
   return HGNN_OK;
 }
 

@@ -119,3 +119,44 @@ def test_attention(hgnn, dev, graph, H, D):
         a, b = a.astype(np.float64), b.astype(np.float64)
         # two results of sums that are rounded to fp16 up to three times each; 2^-11 relative to the terms of a cancelling sum
         assert np.linalg.norm(a - b) <= 4e-3 * np.linalg.norm(a), (name, np.linalg.norm(a - b) / np.linalg.norm(a))
+
+
+# without a plan: beyond 4 Mi non-zeros and 34 MB of table, rows below 128 non-zeros on average (no column passes)
+@pytest.mark.parametrize("F,H,ncols,mapped,has_w", [(32, 1, 600011, True, True), (32, 4, 600011, True, True), (42, 1, 500009, True, True),
+                                                    (128, 1, 600011, False, True), (128, 1, 600011, False, False)])
+def test_without_a_plan(hgnn, dev, F, H, ncols, mapped, has_w):
+    print(f"ranges without a plan F={F} H={H} ncols={ncols} mapped={mapped} values={has_w}", flush=True)
+    r = np.random.default_rng(F + H)
+    nrows, width = 40003, -(-ncols // 8)
+    deg = r.integers(60, 160, size=nrows)
+    lens = (0, 1, 255, 256, 257, 258, 511, 512, 513, 2047, 2048, 2049, 9000, 30000)
+    deg[:len(lens)] = lens
+    deg[-len(lens):] = lens
+    col = [np.sort(r.integers(0, ncols, size=d)) for d in deg]
+    borders = np.array([b for x in range(1, 8) for b in (x * width - 1, x * width)])
+    for i, c in enumerate((np.zeros(300), np.full(300, ncols - 1), r.integers(3 * width, 4 * width, size=1000), np.tile(borders, 20))):
+        deg[2000 * i + 1500] = c.size
+        col[2000 * i + 1500] = np.sort(c)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate(col).astype(np.int32)
+    E = col.size
+    assert 4 << 20 < E < 128 * nrows
+    pitch = (F + 7) // 8 * 8
+    X = np.zeros((ncols, pitch), dtype=np.float16)
+    X[:, :F] = f16(r.standard_normal((ncols, F)))
+    w = f16(r.standard_normal((E, H))) if has_w else None
+    eid = r.permutation(E).astype(np.int32) if mapped else None
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=None if eid is None else up(eid, dev))
+    need, less = hgnn.hgnn_spmm_workspace(nrows, ncols, E, F), hgnn.hgnn_spmm_workspace(nrows, 0, E, F)
+    assert need > less > 0
+    Xd, wd = up(X, dev), None if w is None else up(w, dev)
+    out = []
+    for n, fill in ((need, 255), (need, 0), (less, 0)):  # what the workspace holds beforehand does not matter
+        ws = torch.full((n,), fill, dtype=torch.uint8, device=dev)
+        Y = torch.full((nrows, pitch), 3.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_spmm(g, wd, H, Xd, Y, F=F, workspace=ws)
+        out.append(down(Y))
+    assert np.array_equal(out[0].view(np.uint16), out[1].view(np.uint16))
+    ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(X[:, :F]), w=w, H=H, want_sabs=True, **({} if eid is None else {"eid": eid}))
+    for y in (out[0], out[2]):
+        compare("without a plan", np.ascontiguousarray(y[:, :F]), ref, sabs)

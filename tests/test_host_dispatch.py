@@ -114,7 +114,23 @@ def narrow_features(h):
                     assert st == 0 and any("task" in x for x in names) == (f >= least), (f, eid, names)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features]
+def column_ranges(h):
+    """Long rows are cut at column ranges where the workspace is the query's for the graph's columns and that pays, never below 4 Mi
+    non-zeros or over a table that the L2s hold together, and never in the static form."""
+    for nrows, ncols, nnz, f, eid, want in ((1200001, 1200001, 31000001, 64, True, True), (1200001, 1200001, 31000001, 64, False, False),
+                                            (2400000, 2400000, 54000000, 64, False, True), (600000, 600000, 12000000, 128, False, True),
+                                            (262144, 262144, 5505024, 64, True, False), (600000, 600000, 4000000, 128, True, False)):
+        g = graph(h, nrows, ncols, nnz, eid)
+        w = vp(h.data)
+        full, less = (h.lib.hgnn_spmm_workspace(nrows, c, i64(nnz), f) for c in (ncols, 0))
+        for size, take in ((full, want), (full + 4096, want), (full - 1, False), (less, False)):
+            if size < less:  # the answer has no room for ranges, and one byte less has none for the pieces
+                continue
+            st, names = spmm(h, g, f, size, w)
+            assert st == 0 and any("free_count" in x for x in names) == take, (nrows, nnz, f, eid, size, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
