@@ -428,8 +428,9 @@ struct RangeScratch {
   int32_t* long_rows;  // [windows]
   TaskTotals* totals;  // n_split: the long rows, n_range: their pieces
   int4* task;
+  int4* split;
   float* staging;
-  int64_t cap;         // most pieces
+  int64_t cap, rows;   // most pieces, most long rows
   size_t bytes;
 };
 RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);

@@ -740,8 +740,11 @@ __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t f
 template <int L, bool F32>
 __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split, int per_wave,
                                                                   const TaskTotals* __restrict__ totals) {
-  if (F32) n_split = totals->n_split;
   constexpr int G = kWave / L;
+  if (F32) {
+    n_split = totals->n_split;
+    per_wave = finish_rows_per_wave(n_split, G);
+  }
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
@@ -1452,7 +1455,9 @@ static void launch_task_finish_l(dim3 grid, int per_wave, hipStream_t s, const S
 
 static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
   const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
-  const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
+  // a bound on the rows (fp32) may be above a line that their number is below
+  const int64_t waves = std::max<int64_t>(ceil_div(v.n_split, per_wave), a.stage32 ? std::min(v.n_split, kFinishAlone) : 0);
+  const dim3 grid(unsigned(ceil_div(waves, kWavesPerBlock)));
   switch (L) {
     case 1: launch_task_finish_l<1>(grid, per_wave, s, a, v); break;
     case 2: launch_task_finish_l<2>(grid, per_wave, s, a, v); break;
@@ -1547,7 +1552,11 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");
-  if (range_scratch) v.totals = r.totals;  // the rows of several pieces are the long ones
+  if (range_scratch) {  // the rows of several pieces are the long ones
+    v.totals = r.totals;
+    v.split = reinterpret_cast<const int4_t*>(r.split);
+    v.n_split = int(r.rows);
+  }
   launch_task_finish(L, s, a, v);
   HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
   return HGNN_OK;

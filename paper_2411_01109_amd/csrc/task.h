@@ -150,7 +150,8 @@ inline TaskView task_view(const TaskScratch& t, const RangeScratch* r, const Tas
 // wave), or one in all, whose lane groups then take a piece each and add across the wave.  The launch is a few latencies long and a wave of
 // G rows is a chain of them; us, G rows / one: 4000 rows x 64, saving attention 13.7 / 9.4, its backward 9.0 / 6.4; 800 rows x 42, SpMM
 // 5.3 / 4.7 (a GCN layer of 1.3 M non-zeros 89.3 / 84.8); 35 600 rows x 128 46 / 45.  Rows in great numbers have few pieces each.
-inline int finish_rows_per_wave(int n_split, int G) { return n_split <= 65536 ? 1 : G; }
+constexpr int kFinishAlone = 65536;
+__host__ __device__ inline int finish_rows_per_wave(int n_split, int G) { return n_split <= kFinishAlone ? 1 : G; }
 
 // waves of work behind a view (G lane groups per wave)
 template <int G>

@@ -174,11 +174,13 @@ RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int
     at += (bytes + 255) / 256 * 256;
     return x;
   };
-  r.cap = kRanges * (nnz / S + 1) + nnz / std::min<int64_t>(S, kRangePiece) + 1;
+  r.rows = nnz / (S + 1) + 1;
+  r.cap = kRanges * r.rows + nnz / std::min<int64_t>(S, kRangePiece) + 1;
   r.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
   r.lists = reinterpret_cast<int32_t*>(take(int64_t(range_bytes(int(nrows), int(nwin)))));
   r.long_rows = reinterpret_cast<int32_t*>(take(nwin * 4));
   r.task = reinterpret_cast<int4*>(take(r.cap * 16));
+  r.split = reinterpret_cast<int4*>(take(r.rows * 16));
   r.staging = reinterpret_cast<float*>(take(r.cap * int64_t((F + 7) & ~7) * 4));
   r.bytes = size_t(at);
   return r;
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
                                                                    TaskTotals* __restrict__ totals, int4* __restrict__ task,
                                                                    int* __restrict__ zrow, int4* __restrict__ split, RangeLists ranges,
                                                                    int range_blocks, TaskTotals* __restrict__ range_totals,
-                                                                   int4* __restrict__ rtask) {
+                                                                   int4* __restrict__ rtask, int4* __restrict__ rsplit) {
   const int b = int(blockIdx.x) - range_blocks;
   if (b >= 0) {
     task_write<true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split);
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
   const int w = int(blockIdx.x) * kRangeGroup;
   int all[2];
   const RangePlace place = range_place(ranges, w, all);
-  if (all[1] > 0) range_write(ranges, w, place, rtask, split);
+  if (all[1] > 0) range_write(ranges, w, place, rtask, rsplit);
   if (w == 0 && threadIdx.x == 0) {
     range_totals->n_range = all[0];
     range_totals->n_split = all[1];
@@ -235,7 +237,7 @@ hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const Range
   ranges.long_rows = r.long_rows;
   free_count_kernel<<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
   free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, t.sec, t.totals, t.task, t.zrow, t.split,
-                                                                               ranges, range_blocks, r.totals, r.task);
+                                                                               ranges, range_blocks, r.totals, r.task, r.split);
   HGNN_LAUNCH_CHECK("free_count_kernel / free_write_kernel");
   return HGNN_OK;
 }

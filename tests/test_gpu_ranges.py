@@ -160,3 +160,27 @@ def test_without_a_plan(hgnn, dev, F, H, ncols, mapped, has_w):
     ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(X[:, :F]), w=w, H=H, want_sabs=True, **({} if eid is None else {"eid": eid}))
     for y in (out[0], out[2]):
         compare("without a plan", np.ascontiguousarray(y[:, :F]), ref, sabs)
+
+
+@pytest.mark.parametrize("rows,least,most", [(18000, 257, 300), (18000, 257, 480), (70000, 257, 260)])
+def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most):
+    """Most non-zeros in rows that are barely long: more of them than there are pieces of 512, and more than take a wave each."""
+    print(f"ranges without a plan, {rows} rows of {least} to {most}", flush=True)
+    F, ncols = 8, 2200003
+    r = np.random.default_rng(rows + most)
+    deg = np.zeros(3 * rows, dtype=np.int64)
+    deg[::3] = r.integers(least, most + 1, size=rows)
+    deg[1::3] = r.integers(0, 3, size=rows)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    assert 4 << 20 < E < 128 * deg.size and rows > E // 512 + 1
+    row = np.repeat(np.arange(deg.size), deg)
+    col = (np.sort(row * ncols + r.integers(0, ncols, size=E)) - row * ncols).astype(np.int32)
+    Xh, w, eid = f16(r.standard_normal((ncols, F))), f16(r.standard_normal((E, 1))), r.permutation(E).astype(np.int32)
+    n = hgnn.hgnn_spmm_workspace(deg.size, ncols, E, F)
+    assert n > hgnn.hgnn_spmm_workspace(deg.size, 0, E, F)
+    Y = torch.full((deg.size, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm(hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=up(eid, dev)), up(w, dev), 1, up(Xh, dev), Y, F=F,
+                   workspace=torch.full((n,), 255, dtype=torch.uint8, device=dev))
+    ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
+    compare("many long rows", down(Y), ref, sabs)
