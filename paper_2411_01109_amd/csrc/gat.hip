@@ -483,7 +483,7 @@ static void launch_gat_finish_l(bool save, dim3 grid, int per_wave, hipStream_t 
 }
 
 static void launch_gat_finish(int L, bool save, hipStream_t s, const GatArgs& a, const TaskView& v) {
-  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const int per_wave = finish_rows_per_wave(v.n_split, v.n_slots, kWave / L);
   const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
     case 1: launch_gat_finish_l<1>(save, grid, per_wave, s, a, v); break;

@@ -371,7 +371,7 @@ static void launch_bwd_tasks(int L, int lh, unsigned waves, hipStream_t s, const
 
 template <bool VEC>
 static void launch_bwd_finish(int L, hipStream_t s, const GatBwdArgs& a, const TaskView& v) {
-  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const int per_wave = finish_rows_per_wave(v.n_split, v.n_slots, kWave / L);
   const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
     case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;

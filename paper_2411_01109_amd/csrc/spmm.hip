@@ -743,7 +743,7 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   constexpr int G = kWave / L;
   if (F32) {
     n_split = totals->n_split;
-    per_wave = finish_rows_per_wave(n_split, G);
+    per_wave = finish_rows_per_wave(n_split, totals->n_slots, G);
   }
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -1454,7 +1454,7 @@ static void launch_task_finish_l(dim3 grid, int per_wave, hipStream_t s, const S
 }
 
 static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
-  const int per_wave = finish_rows_per_wave(v.n_split, kWave / L);
+  const int per_wave = finish_rows_per_wave(v.n_split, v.n_slots, kWave / L);
   // a bound on the rows (fp32) may be above a line that their number is below
   const int64_t waves = std::max<int64_t>(ceil_div(v.n_split, per_wave), a.stage32 ? std::min(v.n_split, kFinishAlone) : 0);
   const dim3 grid(unsigned(ceil_div(waves, kWavesPerBlock)));

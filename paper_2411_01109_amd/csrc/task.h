@@ -24,6 +24,7 @@ struct TaskView {
   const int* zrow;
   const hgnn_task_sec* sec;
   const int4_t* split;
+  int n_slots;               // pieces of the rows in split (on the host only with a plan)
   const uint16_t* col16;     // column ids as 16-bit offsets from block * width, or nullptr: the graph's own
   int width;
   const TaskTotals* totals;  // device; set where the host does not know the numbers (then one block, n_split is a bound)
@@ -64,6 +65,7 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool 
   v.width = t->width;
   v.n_split = t->n_split;
   v.nb = t->nb;
+  v.n_slots = t->n_slots;
   v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
   v.n_rtask = t->n_rtask;
   v.rshare = range_share(t->n_rtask, G);
@@ -149,9 +151,12 @@ inline TaskView task_view(const TaskScratch& t, const RangeScratch* r, const Tas
 // Rows of several pieces per wave in the follow-up kernels: one for each of the G lane groups (longer rows one after the other by the whole
 // wave), or one in all, whose lane groups then take a piece each and add across the wave.  The launch is a few latencies long and a wave of
 // G rows is a chain of them; us, G rows / one: 4000 rows x 64, saving attention 13.7 / 9.4, its backward 9.0 / 6.4; 800 rows x 42, SpMM
-// 5.3 / 4.7 (a GCN layer of 1.3 M non-zeros 89.3 / 84.8); 35 600 rows x 128 46 / 45.  Rows in great numbers have few pieces each.
+// 5.3 / 4.7 (a GCN layer of 1.3 M non-zeros 89.3 / 84.8); 35 600 rows x 128 46 / 45.  Many rows of two or three pieces (long rows of
+// column blocks: some 50 000 of 114 M non-zeros x 64) are work for all lane groups: SpMM 7.5 / 20, saving attention 16 / 41.
 constexpr int kFinishAlone = 65536;
-__host__ __device__ inline int finish_rows_per_wave(int n_split, int G) { return n_split <= kFinishAlone ? 1 : G; }
+__host__ __device__ inline int finish_rows_per_wave(int n_split, int n_slots, int G) {
+  return n_split <= 8192 || (n_split <= kFinishAlone && n_slots / 6 >= n_split) ? 1 : G;
+}
 
 // waves of work behind a view (G lane groups per wave)
 template <int G>

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
   const RangePlace place = range_place(ranges, w, all);
   if (all[1] > 0) range_write(ranges, w, place, rtask, rsplit);
   if (w == 0 && threadIdx.x == 0) {
-    range_totals->n_range = all[0];
+    range_totals->n_range = range_totals->n_slots = all[0];
     range_totals->n_split = all[1];
   }
 }
