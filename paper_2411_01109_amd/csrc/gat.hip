@@ -347,9 +347,9 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   else stage_store<SAVE>(a, w.slot, f0, head, leader, t);
 }
 
-// Follow-up kernel: merges the staged pieces of every row that has several and stores the row.  A wave owns G such rows;
-// rows of up to kShortPieces pieces are merged by their own lane group, hubs by the whole wave with a final merge across
-// the groups.
+// Follow-up kernel: merges the staged pieces of every row that has several and stores the row.  A wave owns one such
+// row, or G (finish_rows_per_wave): then rows of up to kShortPieces pieces are merged by their own lane group, hubs by the whole
+// wave with a final merge across the groups.
 constexpr int kShortPieces = 8;
 
 template <int L, bool SAVE>

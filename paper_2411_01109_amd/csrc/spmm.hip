@@ -711,8 +711,8 @@ __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) 
 }
 
 // Pass 2 (section 5.2.3): adds the staged fp16 pieces of every row that has several (fp32, in order) and stores the row
-// once.  A wave owns G rows: rows of at most kFinishShort pieces are summed by their own lane group, longer ones by the
-// whole wave.
+// once.  A wave owns one row, or G: then rows of at most kFinishShort pieces are summed by their own lane group, longer ones
+// by the whole wave (finish_rows_per_wave).
 template <int STRIDE>
 __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t first, int64_t last, int f0, float (&acc)[8]) {
   const float* p = reinterpret_cast<const float*>(a.staging) + f0;
