@@ -251,9 +251,21 @@ __device__ __forceinline__ void range_write(const RangeLists& a, int w, const Ra
     const int incl = range_scan(s.m, s_wave, &total);  // (its barriers are behind the offsets in `at`)
     const int slot = next + incl - s.m, end = __shfl(next + incl, kRanges - 1, kRanges);
     if (i < n && x == 0) split[place.split + i] = make_int4(s_row[i], slot, end - slot, 0);
-    for (int j = 0; j < s.m; ++j) {
-      const int len = j + 1 < s.m ? s.part : s.len - j * s.part;
-      task[atomicAdd(&at[x][len], 1)] = make_int4(s.beg + j * s.part, len, s_row[i], slot + j);
+    // All pieces but the last are equally long, so they follow each other in the list.  Where there are many the whole wave writes them: a
+    // row of 3 M non-zeros was a serial loop of eight lanes, a plan with S = 256 358 us instead of 154, with S = 4 19 ms instead of 1.8.
+    int first = 0, last = 0;
+    if (s.m > 1) first = atomicAdd(&at[x][s.part], s.m - 1);
+    if (s.m > 0) last = atomicAdd(&at[x][s.len - (s.m - 1) * s.part], 1);
+    const int row = i < n ? s_row[i] : 0;
+    if (s.m > 0) task[last] = make_int4(s.beg + (s.m - 1) * s.part, s.len - (s.m - 1) * s.part, row, slot + s.m - 1);
+    constexpr int kFew = 4;
+    if (s.m <= kFew)
+      for (int j = 0; j < s.m - 1; ++j) task[first + j] = make_int4(s.beg + j * s.part, s.part, row, slot + j);
+    for (unsigned long long many = __ballot(s.m > kFew); many; many &= many - 1) {
+      const int src = __ffsll((long long)many) - 1;
+      const int m = __shfl(s.m, src), part = __shfl(s.part, src), beg = __shfl(s.beg, src), r = __shfl(row, src), sl = __shfl(slot, src);
+      const int f = __shfl(first, src);
+      for (int j = lane; j < m - 1; j += kWave) task[f + j] = make_int4(beg + j * part, part, r, sl + j);
     }
     next += total;
   }

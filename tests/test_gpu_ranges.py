@@ -1,5 +1,7 @@
 """Long rows cut at the borders of column ranges (plans of more than 4 Mi non-zeros over a table beyond four L2s): row lengths around
 the segment size, rows inside one range, rows that touch only the columns at the borders, empty ranges, every walk that takes them."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -184,3 +186,45 @@ def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most):
                    workspace=torch.full((n,), 255, dtype=torch.uint8, device=dev))
     ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
     compare("many long rows", down(Y), ref, sabs)
+
+
+@pytest.mark.parametrize("S", [4, 64, 256])
+def test_a_very_long_row(hgnn, dev, S):
+    """Half of all non-zeros in one row, most of them in one column range: its many pieces are written by a wave, so a plan with column
+    ranges takes about as long as one without (a lane alone took ten times as long at S = 4, twice at 256)."""
+    print(f"ranges, very long row S={S}", flush=True)
+    n, E, F = 200000, 6000000, 64
+    r = np.random.default_rng(S)
+    deg = np.bincount(r.integers(0, n, size=E // 2), minlength=n)
+    deg[77] += E - deg.sum()
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    row = np.repeat(np.arange(n), deg)
+    c = r.integers(0, n, size=E)
+    hub = np.arange(rowptr[77], rowptr[78])
+    c[hub[: hub.size * 3 // 4]] %= 1000
+    col = (np.sort(row * n + c) - row * n).astype(np.int32)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=n)
+
+    def plan_time(max_f):
+        best = 1e9
+        for _ in range(5):
+            t = time.perf_counter()
+            hgnn.hgnn_plan_destroy(hgnn.hgnn_plan_create(g, S, max_f, 1, col_blocks=1))
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    narrow, wide = plan_time(8), plan_time(F)
+    assert wide <= 3 * narrow + 100e-6, (narrow, wide)
+    w, Xh = f16(r.standard_normal((E, 1))), f16(r.standard_normal((n, F)))
+    ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True)
+    Y = torch.full((n, F), 3.0, dtype=torch.float16, device=dev)
+    p = hgnn.hgnn_plan_create(g, S, F, 1, col_blocks=1)
+    hgnn.hgnn_spmm_discretized(p, g, up(w, dev), 1, up(Xh, dev), Y)
+    compare("very long row", down(Y), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+    ident = hgnn.Csr(g.rowptr, g.col, ncols=n, eid=torch.arange(E, dtype=torch.int32, device=dev))
+    X2 = np.concatenate([Xh, Xh], axis=1)  # beyond eight L2s
+    Y2 = torch.full((n, 2 * F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm(ident, up(w, dev), 1, up(X2, dev), Y2,
+                   workspace=torch.full((hgnn.hgnn_spmm_workspace(n, n, E, 2 * F),), 255, dtype=torch.uint8, device=dev))
+    compare("very long row without a plan", np.ascontiguousarray(down(Y2)[:, F:]), ref, sabs)
