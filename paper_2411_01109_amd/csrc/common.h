@@ -280,17 +280,20 @@ struct hgnn_row_tasks {
   int32_t nb = 0;
   int64_t nnz = 0;
   int4* task = nullptr;
-  int4* rtask = nullptr;         // pieces of the rows that are cut at column ranges, range after range (ranges.h); all staged
+  // The rows of several pieces once more, cut at column ranges (ranges.h): pieces range after range, all staged.  A call takes them in the
+  // place of the ordinary pieces of those rows where its own table is large enough (at_ranges in task.h); n_rtask = 0: there are none.
+  int4* rtask = nullptr;
   int32_t n_rtask = 0;
   int32_t* zrow = nullptr;
-  int4* split = nullptr;         // rows with several pieces: (row, first slot, pieces, block)
-  hgnn_task_sec* sec = nullptr;  // [nb]
+  int4* split = nullptr;         // [n_split] rows with several pieces: (row, first slot, pieces, block); with column ranges as many again for those
+  hgnn_task_sec* sec = nullptr;  // [nb]; with column ranges a second one, without the rows that are cut there
   int32_t n_split = 0, n_slots = 0;
+  int32_t stage_slots = 0;       // of the staging arrays: n_slots, or n_rtask where that is more
   const uint16_t* col16 = nullptr;  // column blocks of at most 65536 columns: the column ids less the block's first (the plan's)
   int32_t width = 0;                // columns per block
   std::vector<hgnn_task_sec> host;  // sec on the host
-  hgnn_half* staging = nullptr;  // [2][n_slots][max_F] partial vectors (second set: masked vectors of the saving GAT pass)
-  float* stage_mz = nullptr;     // [3][n_slots][max_H] scalars of the partial vectors of the fused GAT passes
+  hgnn_half* staging = nullptr;  // [2][stage_slots][max_F] partial vectors (second set: masked vectors of the saving GAT pass)
+  float* stage_mz = nullptr;     // [3][stage_slots][max_H] scalars of the partial vectors of the fused GAT passes
 };
 
 // The plan object behind the opaque handle of the C ABI.
@@ -395,7 +398,7 @@ struct TaskSource {
   const int32_t* first;   // device, [nb] first non-zero of every block, or nullptr (one block)
   int32_t nrows, nb, S, group_max;
   int64_t nnz;
-  int32_t range_min;      // rows of at least so many non-zeros are left to ranges.h (one block), or kNoRanges
+  int32_t range_min;      // rows of at least so many non-zeros are cut by ranges.h, too (one block), or kNoRanges
 };
 constexpr int kNoRanges = 0x7fffffff;
 // Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
@@ -405,7 +408,8 @@ constexpr int kGroupMaxBlocks = 256;
 inline int task_group_max(int64_t nnz) { return nnz <= (int64_t(8) << 20) ? 32 : 128; }
 struct TaskTotals {
   int64_t n_zero;
-  int32_t n_task, n_whole, n_split, n_slots, n_long, n_range;  // n_long rows in n_range pieces by ranges.h
+  int32_t n_task, n_whole, n_split, n_slots;
+  int32_t n_long_whole, n_long_group, n_range;  // of n_task: pieces of the rows from range_min on; their pieces by ranges.h
 };
 constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for equal neighbours; few, because the short rows of a
                                    // window share cache lines of the column array and of edge tensors (see TaskView::chunk)
@@ -448,7 +452,7 @@ struct TaskCounts {
   int* n_range = nullptr;        // beside it, where rows are cut at column ranges (ranges = true): what becomes got.n_range
   bool ranges = false;
   TaskTotals got{};              // the same on the host, from task_allocate on
-  const int* long_at = nullptr;  // device, [nwin] long rows before each window of kTaskWindow rows
+  const int* split_at = nullptr;  // device, [nwin] rows of several pieces before each window of kTaskWindow rows
 };
 hgnn_status task_prepare(const TaskSource& q, TaskCounts& c);
 hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out);

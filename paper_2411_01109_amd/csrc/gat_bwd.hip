@@ -417,7 +417,7 @@ static hgnn_status run_bwd_tasks(const hgnn_plan* q, const hgnn_row_tasks* t, Ga
   a.stage_ds = t->stage_mz;
   a.stage_ld = q->max_F;
   const int L = pow2_at_least(a.F / 8), lh = a.D / 8;
-  const TaskView v = task_view(t, kWave / L, comes_back(false, int64_t(ncols) * a.ldx * 2, q->llc_bytes));
+  const TaskView v = task_view(t, kWave / L, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, q->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, q->llc_bytes));
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     if (near_table(ncols, a.ldx)) launch_bwd_tasks<true, VEC>(L, lh, unsigned(waves), s, a, v, ncols);

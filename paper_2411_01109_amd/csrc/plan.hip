@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
     if (g.rowptr[0] != 0) bad = 1;
     else if (int64_t(g.rowptr[g.nrows]) != g.nnz) bad = 2;
   }
-  int c[kLists] = {0, 0, 0, 0}, n[kTaskAll] = {0, 0, 0, 0, 0, 0}, listed = 0;
+  int c[kLists] = {0, 0, 0, 0}, n[kTaskAll] = {}, listed = 0;
   for (int u = 0; u < kRowsPerThread; ++u) {
     if (base + u >= q.nrows) break;
     const int r = int(base) + u;
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
     if (!bad && len < 0) bad = 3;
     for (int i = 0; i < kLists; ++i) c[i] += m[i];
     if (m[kBigList] || m[kMidList]) listed += len;
-    task_count_row(tq, g.rowptr, r, n);
+    task_count_row<true>(tq, g.rowptr, r, n);
   }
   if (bad) atomicMax(&f->bad, 8 - bad);
 #pragma unroll
@@ -408,8 +408,8 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
                                                            int4* __restrict__ split, RowLists q, int list_blocks,
                                                            const int* __restrict__ offsets, RowListArrays o, int64_t nseg,
                                                            int* __restrict__ seg_lo, int* __restrict__ seg_hi, RangeLists ranges,
-                                                           int range_blocks, const int* __restrict__ long_at, int first_slot,
-                                                           int4* __restrict__ rtask, int4* __restrict__ rsplit) {
+                                                           int range_blocks, const int* __restrict__ split_at, int4* __restrict__ rtask,
+                                                           int4* __restrict__ rsplit) {
   // (those of the column ranges, the longest chains, come first)
   const int b = int(blockIdx.x) - range_blocks;
   if (b < 0) {
@@ -417,11 +417,11 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
     RangePlace at;
 #pragma unroll
     for (int x = 0; x < kRanges; ++x) at.task[x] = ranges.count[x * ranges.nwin + w];
-    at.slot = first_slot + ranges.slots[w];
-    at.split = long_at[w];
+    at.slot = ranges.slots[w];
+    at.split = split_at[w];
     range_write(ranges, w, at, rtask, rsplit);
   } else if (b < n) {
-    task_write<false>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split);
+    task_write<false, true>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split, false);
   } else if (b < n + list_blocks) {
     row_lists_write(q, b - n, n, offsets, o);
   } else {
@@ -429,8 +429,10 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
   }
 }
 
-// Where rows are cut.  A segment size is the least length because such rows leave staged partial rows (fp16, as ever) in any case.
-// us a call, rows in pieces of S / at column ranges (F = 64 and one head if not said; power law unless log-normal):
+// Which plans have long rows cut at column ranges, beside the ordinary pieces of those rows (at_ranges in task.h says which a call takes).  A
+// segment size is the least length because such rows leave staged partial rows (fp16, as ever) in any case: as many at S, more at the
+// ranges, and the sum of their roundings no larger (rows of 257, 1000, 4000 non-zeros 2.04e-4 against 2.06e-4, 2.11 against 2.07, 2.10
+// against 2.12 relative to float64).  us a call, rows in pieces of S / at column ranges (F = 64 and one head if not said; power law unless log-normal):
 //   table, non-zeros                  SpMM, edge values   behind a map   SDDMM       attention fwd (saving), bwd
 //   614 MB, 62 M, F = 128               1711 / 1285        2683 / 2043
 //   307 MB, 62 M, F = 64 by degrees      870 / 740
@@ -523,7 +525,7 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
         tq, nblk, tc.count, tc.sums, t->sec, t->task, t->zrow, t->split, q, list_blocks, counts,
         RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row, p->big_first, p->mid_row, p->hub_chunk_row,
                       p->hub_chunk_first, p->hub_chunk_count},
-        p->nseg, p->seg_row_lo, p->seg_row_hi, ranges, range_blocks, tc.long_at, tc.got.n_slots, t->rtask, t->split + tc.got.n_split);
+        p->nseg, p->seg_row_lo, p->seg_row_hi, ranges, range_blocks, tc.split_at, t->rtask, t->split + t->n_split);
     HGNN_LAUNCH_CHECK("plan_write_kernel");
   }
   const size_t nv = (size_t(g->nrows) + size_t(g->ncols)) * size_t(p->max_H);

@@ -494,7 +494,7 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
       a.delta = p->bdelta;
     }
     const int lanes = pow2_at_least((F + vw - 1) / vw);
-    const TaskView v = task_view(t, kWave / lanes, comes_back(false, int64_t(g->ncols) * ldv * 2, p->llc_bytes), false);
+    const TaskView v = task_view(t, kWave / lanes, at_ranges(t, kRangesDot, int64_t(g->ncols) * F * 2, p->l2_bytes), comes_back(false, int64_t(g->ncols) * ldv * 2, p->llc_bytes), false);
     const int waves = v.first_wave[t->nb];
     if (waves > 0) {
       const bool near = near_table(g->ncols, ldv);

@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kBlock) void rowsum_task_finish_kernel(RowsumArgs a
 
 template <int H>
 static hgnn_status launch_rowsum_tasks(const hgnn_row_tasks* t, const RowsumArgs& a, hipStream_t s) {
-  const TaskView v = task_view(t, kWave / kRowsumL, true);
+  const TaskView v = task_view(t, kWave / kRowsumL, at_ranges(t, kRangesSums, t->nnz * H * 2, 0), true);
   if (v.first_wave[t->nb] > 0) {
     rowsum_task_kernel<H><<<dim3(unsigned(v.first_wave[t->nb])), kWave, 0, s>>>(a, v);
     HGNN_LAUNCH_CHECK("rowsum_task_kernel");

@@ -1477,14 +1477,16 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
   a.staging = reinterpret_cast<half_t*>(t->staging);
   a.stage_ld = p->max_F;
   const bool mapped = wm != 0 && a.w && a.eid;
-  const TaskView v = task_view(t, G, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
+  // (the comparison variant with atomic additions rounds each to fp16: as many as there are segments)
+  const bool ranges = !a.atomic_y && at_ranges(t, mapped ? kRangesMapped : kRangesSpmm, int64_t(ncols) * a.F * 2, p->l2_bytes);
+  const TaskView v = task_view(t, G, ranges, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
   const int waves = v.first_wave[t->nb];
   if (a.atomic_y && v.n_split > 0) {
     launch_zero_split(L, s, a, v);
     HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
   if (waves > 0) {
-    const size_t least = least_task_lds(mapped, t->n_rtask > 0, a, ncols, p->l2_bytes, p->llc_bytes);
+    const size_t least = least_task_lds(mapped, ranges, a, ncols, p->l2_bytes, p->llc_bytes);
     if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     else launch_tasks<false>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     HGNN_LAUNCH_CHECK("spmm_task_kernel");

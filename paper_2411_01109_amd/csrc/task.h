@@ -54,24 +54,45 @@ inline bool comes_back(bool mapped, int64_t table_bytes, int64_t llc) { return m
 // pieces at column ranges per XCD, whole waves of G lane groups of them
 __host__ __device__ inline int range_share(int n, int G) { return int((pos_t(n) + kXcds * G - 1) / (kXcds * G)) * G; }
 
-// host: the launch shape of tasks t for G lane groups per wave; zeros = false leaves the empty rows out
-inline TaskView task_view(const hgnn_row_tasks* t, int G, bool comes_back, bool zeros = true) {
+// Whether a call takes the pieces at column ranges that the plan has: from so many halves of an L2 on in the table it gathers from, which may
+// be narrower than what the plan was made for.  us, ordinary pieces / at column ranges, power law if not said:
+//   table, non-zeros          SpMM        edge values   behind a map   SDDMM        attention fwd   saving       bwd
+//   1 MB, 8 M                 41 / 58       45 / 73       95 / 151      43 / 77       52 / 63       68 / 70      74 / 102
+//   4.2 MB, 5.5 M             47 / 58       53 / 67      110 / 124      50 / 71       57 / 64       72 / 70      91 / 102
+//   8.4 MB, 4.5 M             36 / 41       38 / 40       71 / 61       34 / 38       48 / 45       59 / 55      67 / 66
+//   8.4 MB, 5.5 M             48 / 55       52 / 56      108 / 94       51 / 53       61 / 56       73 / 66      95 / 91
+//   9.6 MB, 12 M             102 / 105     115 / 129     290 / 285     116 / 128     112 / 110     132 / 128    240 / 210
+//   16.8 MB, 4.5 M            39 / 42       40 / 41       75 / 64       37 / 37       55 / 51       74 / 68      77 / 74
+//   16.8 MB, 5.5 M            48 / 49       51 / 48      107 / 85       48 / 45       62 / 56       77 / 70      99 / 90
+//   19 MB, 12 M              104 / 98      112 / 111     285 / 244     109 / 107     112 / 104     130 / 120    246 / 204
+//   34 MB, 8 M                61 / 58       63 / 61      150 / 116      62 / 59       84 / 77      114 / 103    135 / 122
+//   8.4 MB, 20 M log-normal  225 / 201     251 / 231     539 / 541     238 / 217     229 / 207     243 / 224    414 / 413
+// Row sums through a map, which gather edge values: 5.5 M 49 / 42, of four heads 81 / 60, 36 M 384 / 269, 20 M log-normal 286 / 286.
+enum RangesFrom { kRangesSpmm = 8, kRangesMapped = 3, kRangesDot = 6, kRangesAttention = 3, kRangesSums = 0 };
+inline bool at_ranges(const hgnn_row_tasks* t, RangesFrom from, int64_t table_bytes, int64_t l2) {
+  return t->n_rtask > 0 && 2 * table_bytes > from * l2;
+}
+
+// host: the launch shape of tasks t for G lane groups per wave, the long rows in ordinary pieces or at column ranges; zeros = false
+// leaves the empty rows out
+inline TaskView task_view(const hgnn_row_tasks* t, int G, bool ranges, bool comes_back, bool zeros = true) {
   TaskView v{};
+  const int sec = ranges ? t->nb : 0;
   v.task = reinterpret_cast<const int4_t*>(t->task);
   v.zrow = t->zrow;
-  v.sec = t->sec;
-  v.split = reinterpret_cast<const int4_t*>(t->split);
+  v.sec = t->sec + sec;
+  v.split = reinterpret_cast<const int4_t*>(t->split) + (ranges ? t->n_split : 0);
   v.col16 = t->col16;
   v.width = t->width;
   v.n_split = t->n_split;
   v.nb = t->nb;
-  v.n_slots = t->n_slots;
+  v.n_slots = ranges ? t->n_rtask : t->n_slots;
   v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
-  v.n_rtask = t->n_rtask;
-  v.rshare = range_share(t->n_rtask, G);
+  v.n_rtask = ranges ? t->n_rtask : 0;
+  v.rshare = range_share(v.n_rtask, G);
   int64_t n = int64_t(kXcds) * v.rshare / G;
   for (int b = 0; b < t->nb; ++b) {
-    const hgnn_task_sec& s = t->host[size_t(b)];
+    const hgnn_task_sec& s = t->host[size_t(sec + b)];
     n = (n + 7) & ~int64_t(7);
     v.first_wave[b] = int(n);
     const int64_t w8 = ceil_div(s.nw, 8), g8 = ceil_div(ceil_div(s.ng, G), 8);

@@ -9,23 +9,26 @@ constexpr int kTaskThreads = 256;
 constexpr int kTaskRowsPerThread = kTaskWindow / kTaskThreads;
 constexpr int kMaxGroupLen = 256;
 static_assert(kGroupMaxBlocks <= kMaxGroupLen, "table of lengths");
-enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters, kTaskLong = kTaskCounters, kTaskAll };  // kTaskLong: with a plan
+// kTaskLongW, kTaskLongG: W and G of the rows from range_min on, which have a part of the lists to themselves
+enum { kTaskW, kTaskG, kTaskZ, kTaskSplit, kTaskSlots, kTaskCounters, kTaskLongW = kTaskCounters, kTaskLongG, kTaskAll };
 
-constexpr int kLongRow = -1, kNone = -2;  // RowCut::m of a row for ranges.h, and of no row
+constexpr int kNone = -1;  // RowCut::m of no row
 
 struct RowCut {
   int len, part, m;  // non-zeros, non-zeros per piece, pieces
+  bool far;          // cut at column ranges, too
 };
 
+// RANGES: there may be rows from q.range_min on
+template <bool RANGES>
 __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, int r) {
   RowCut c;
   c.len = rp[r + 1] - rp[r];
   if (c.len < 0) c.len = 0;  // an offset array that validation will reject
   c.part = c.len;
   c.m = c.len > 0 ? 1 : 0;
-  if (c.len >= q.range_min) {
-    c.m = kLongRow;
-  } else if (c.len > q.S) {
+  c.far = RANGES && q.range_min != kNoRanges && c.len >= q.range_min;
+  if (c.len > q.S) {
     c.part = pieces_of(c.len, pieces_of(c.len, q.S));
     c.m = pieces_of(c.len, c.part);
   }
@@ -33,11 +36,18 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
 }
 
 // what row r adds to the counters
-__device__ __forceinline__ void task_count_row(const TaskSource& q, const int* rp, int r, int (&n)[kTaskAll]) {
-  const RowCut c = cut_row(q, rp, r);
-  if (c.m == kLongRow) ++n[kTaskLong];
-  else if (c.m == 0) ++n[kTaskZ];
-  else n[c.part > q.group_max ? kTaskW : kTaskG] += c.m;
+template <bool RANGES, int N>
+__device__ __forceinline__ void task_count_row(const TaskSource& q, const int* rp, int r, int (&n)[N]) {
+  static_assert(N == (RANGES ? kTaskAll : kTaskCounters), "counters");
+  const RowCut c = cut_row<RANGES>(q, rp, r);
+  const bool whole = c.part > q.group_max;
+  if (c.m == 0) {
+    ++n[kTaskZ];
+  } else if (RANGES && c.far) {
+    n[whole ? int(kTaskLongW) : int(kTaskLongG)] += c.m;
+  } else {
+    n[whole ? kTaskW : kTaskG] += c.m;
+  }
   if (c.m > 1) {
     ++n[kTaskSplit];
     n[kTaskSlots] += c.m;
@@ -73,6 +83,13 @@ __device__ __forceinline__ void task_scan(const TaskSource& q, int nwin, int* __
       hgnn_task_sec s;
       s.nw = sums[kTaskW * nb + b];
       s.ng = sums[kTaskG * nb + b];
+      if (counters == kTaskAll) {  // (one block) the short rows alone, then all
+        t.n_long_whole = sums[kTaskLongW];
+        t.n_long_group = sums[kTaskLongG];
+        sec[1] = hgnn_task_sec{0, s.nw, s.nw + t.n_long_whole, s.ng, 0, sums[kTaskZ], 0};
+        s.nw += t.n_long_whole;
+        s.ng += t.n_long_group;
+      }
       s.nz = sums[kTaskZ * nb + b];
       s.w_off = t.n_task;
       s.g_off = t.n_task + s.nw;
@@ -88,37 +105,38 @@ __device__ __forceinline__ void task_scan(const TaskSource& q, int nwin, int* __
       t.n_slots += slots;
       sec[b] = s;
     }
-    if (counters == kTaskAll) t.n_long = sums[kTaskLong * nb];
     *out = t;
   }
 }
 
 // One workgroup per window and block: counting sort of the lane-group pieces by falling length.  The order of equal
 // pieces depends on the order in which the LDS counters are reached; no result does.  SELF (one block): every workgroup adds
-// up the counts of the windows before it, instead of a launch that scans them; the first leaves section and totals.
-template <bool SELF>
+// up the counts of the windows before it, instead of a launch that scans them; the first leaves section and totals.  Pieces of rows from
+// q.range_min on follow those of the others, or are left out (drop).
+template <bool SELF, bool RANGES>
 __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin, const int* __restrict__ counts, const int* __restrict__ sums,
                                            hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals, int4* __restrict__ task,
-                                           int* __restrict__ zrow, int4* __restrict__ split) {
-  __shared__ int at[kMaxGroupLen + 1];  // pieces of each length, then where the next one goes
-  __shared__ int next[kTaskCounters];
+                                           int* __restrict__ zrow, int4* __restrict__ split, bool drop) {
+  constexpr int kLists = RANGES ? 2 : 1, kNext = RANGES ? int(kTaskAll) : int(kTaskCounters);
+  __shared__ int at[kLists][kMaxGroupLen + 1];  // pieces of each length, then where the next one goes; [1]: of rows from range_min on
+  __shared__ int next[kNext];
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
-  __shared__ int before[kTaskCounters], all[kTaskCounters];
+  __shared__ int before[kNext], all[kNext];
   hgnn_task_sec s;
   if (SELF) {
-    if (threadIdx.x < kTaskCounters) before[threadIdx.x] = all[threadIdx.x] = 0;
+    if (threadIdx.x < kNext) before[threadIdx.x] = all[threadIdx.x] = 0;
     __syncthreads();
-    int b4[kTaskCounters] = {0, 0, 0, 0, 0}, sum[kTaskCounters] = {0, 0, 0, 0, 0};
+    int b4[kNext] = {}, sum[kNext] = {};
     for (int j = threadIdx.x; j < nwin; j += kTaskThreads) {
 #pragma unroll
-      for (int i = 0; i < kTaskCounters; ++i) {
+      for (int i = 0; i < kNext; ++i) {
         const int n = counts[int64_t(i) * nwin + j];
         sum[i] += n;
         b4[i] += j < w ? n : 0;
       }
     }
 #pragma unroll
-    for (int i = 0; i < kTaskCounters; ++i) {
+    for (int i = 0; i < kNext; ++i) {
       for (int off = kWave / 2; off > 0; off >>= 1) {
         b4[i] += __shfl_down(b4[i], off);
         sum[i] += __shfl_down(sum[i], off);
@@ -129,49 +147,62 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
       }
     }
     __syncthreads();
-    s = hgnn_task_sec{0, all[kTaskW], all[kTaskW], all[kTaskG], 0, all[kTaskZ], 0};
+    int nw = all[kTaskW], ng = all[kTaskG];
+    if constexpr (RANGES) {
+      if (!drop) {
+        nw += all[kTaskLongW];
+        ng += all[kTaskLongG];
+      }
+    }
+    s = hgnn_task_sec{0, nw, nw, ng, 0, all[kTaskZ], 0};
     if (w == 0 && threadIdx.x == 0) {
       *sec = s;
-      *totals = TaskTotals{all[kTaskZ], all[kTaskW] + all[kTaskG], all[kTaskW], all[kTaskSplit], all[kTaskSlots], 0, 0};
+      const int n_split = RANGES && drop ? 0 : all[kTaskSplit], n_slots = RANGES && drop ? 0 : all[kTaskSlots];
+      *totals = TaskTotals{all[kTaskZ], nw + ng, nw, n_split, n_slots, 0, 0, 0};
     }
   } else {
     s = sec[b];
   }
-  for (int i = threadIdx.x; i <= kMaxGroupLen; i += kTaskThreads) at[i] = 0;
-  if (threadIdx.x < kTaskCounters) {
+  for (int i = threadIdx.x; i < kLists * (kMaxGroupLen + 1); i += kTaskThreads) at[0][i] = 0;
+  if (threadIdx.x < (RANGES && q.range_min != kNoRanges ? int(kTaskAll) : int(kTaskCounters))) {
     const int i = threadIdx.x;
-    const int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? 0 : (SELF ? 0 : sums[i * q.nb + b]);
+    int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? 0 : (SELF ? 0 : sums[i * q.nb + b]);
+    if (RANGES && i == kTaskLongW) base = s.w_off + (SELF ? all[kTaskW] : sums[kTaskW]);  // (one block)
+    if (RANGES && i == kTaskLongG) base = s.g_off + (SELF ? all[kTaskG] : sums[kTaskG]);
     next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
   }
   __syncthreads();
   RowCut cut[kTaskRowsPerThread];
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
-    cut[u] = RowCut{0, 0, kNone};
-    if (r < q.nrows) cut[u] = cut_row(q, rp, int(r));
+    cut[u] = RowCut{0, 0, kNone, false};
+    if (r < q.nrows) cut[u] = cut_row<RANGES>(q, rp, int(r));
+    if (RANGES && drop && cut[u].far) cut[u].m = kNone;
     if (cut[u].m > 0 && cut[u].part <= q.group_max) {
+      int* const a = at[RANGES && cut[u].far ? 1 : 0];
       const int last = cut[u].len - (cut[u].m - 1) * cut[u].part;
-      if (cut[u].m > 1) atomicAdd(&at[cut[u].part], cut[u].m - 1);
-      atomicAdd(&at[last], 1);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kWave) {  // longest first
-    int carry = next[kTaskG];
-    for (int i0 = kMaxGroupLen; i0 >= 0; i0 -= kWave) {
-      const int i = i0 - int(threadIdx.x);
-      const int n = i >= 0 ? at[i] : 0;
-      int incl = n;
-      for (int d = 1; d < kWave; d <<= 1) {
-        const int t = __shfl_up(incl, d);
-        if (int(threadIdx.x) >= d) incl += t;
-      }
-      if (i >= 0) at[i] = carry + incl - n;
-      carry += __shfl(incl, kWave - 1);
+      if (cut[u].m > 1) atomicAdd(&a[cut[u].part], cut[u].m - 1);
+      atomicAdd(&a[last], 1);
     }
   }
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1);
+  if (threadIdx.x < kLists * kWave) {  // longest first
+    const int y = threadIdx.x / kWave;
+    int carry = next[RANGES && y ? int(kTaskLongG) : int(kTaskG)];
+    for (int i0 = kMaxGroupLen; i0 >= 0; i0 -= kWave) {
+      const int i = i0 - lane;
+      const int n = i >= 0 ? at[y][i] : 0;
+      int incl = n;
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+      }
+      if (i >= 0) at[y][i] = carry + incl - n;
+      carry += __shfl(incl, kWave - 1);
+    }
+  }
+  __syncthreads();
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const RowCut c = cut[u];
     const int r = w * kTaskWindow + u * kTaskThreads + int(threadIdx.x);
@@ -183,24 +214,24 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     }
     const bool whole = c.part > q.group_max;
     if (c.m > 0) {
-      if (whole) pos = atomicAdd(&next[kTaskW], c.m);
+      if (whole) pos = atomicAdd(&next[RANGES && c.far ? int(kTaskLongW) : int(kTaskW)], c.m);
       k0 = s.first + rp[r];
     }
-    auto piece = [&](int j, int k, int part, int m, int len, bool wh, int at_w, int row, int sl) {
+    auto piece = [&](int j, int k, int part, int m, int len, bool wh, bool far, int at_w, int row, int sl) {
       const int n = j + 1 < m ? part : len - j * part;
-      const int p = wh ? at_w + j : atomicAdd(&at[n], 1);
+      const int p = wh ? at_w + j : atomicAdd(&at[RANGES && far ? 1 : 0][n], 1);
       task[p] = make_int4(k + j * part, n | (b << 16), row, sl < 0 ? -1 : sl + j);
     };
     constexpr int kFew = 4;
     if (c.m <= kFew)
-      for (int j = 0; j < c.m; ++j) piece(j, k0, c.part, c.m, c.len, whole, pos, r, slot);
+      for (int j = 0; j < c.m; ++j) piece(j, k0, c.part, c.m, c.len, whole, c.far, pos, r, slot);
     // a row of many pieces: the whole wave writes them (its own lane took 20 us for the longest row of a power-law graph)
     for (unsigned long long many = __ballot(c.m > kFew); many; many &= many - 1) {
       const int src = __ffsll((long long)many) - 1;
       const int m = __shfl(c.m, src), k = __shfl(k0, src), part = __shfl(c.part, src), len = __shfl(c.len, src);
       const int at_w = __shfl(pos, src), row = __shfl(r, src), sl = __shfl(slot, src);
-      const bool wh = part > q.group_max;
-      for (int j = lane; j < m; j += kWave) piece(j, k, part, m, len, wh, at_w, row, sl);
+      const bool wh = part > q.group_max, far = RANGES && __shfl(int(c.far), src);
+      for (int j = lane; j < m; j += kWave) piece(j, k, part, m, len, wh, far, at_w, row, sl);
     }
   }
 }

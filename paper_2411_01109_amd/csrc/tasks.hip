@@ -17,15 +17,14 @@ namespace hgnn {
 __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, int nwin, int* __restrict__ counts) {
   __shared__ int total[kTaskCounters];
   const int b = blockIdx.y;
-  q.range_min = kNoRanges;
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
   if (threadIdx.x < kTaskCounters) total[threadIdx.x] = 0;
   __syncthreads();
-  int n[kTaskAll] = {0, 0, 0, 0, 0, 0};
+  int n[kTaskCounters] = {0, 0, 0, 0, 0};
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(blockIdx.x) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     if (r >= q.nrows) break;
-    task_count_row(q, rp, int(r), n);
+    task_count_row<false>(q, rp, int(r), n);
   }
   for (int i = 0; i < kTaskCounters; ++i) {
     int v = n[i];
@@ -46,19 +45,20 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
                                                                    const int* __restrict__ sums, hgnn_task_sec* __restrict__ sec,
                                                                    TaskTotals* __restrict__ totals, int4* __restrict__ task,
                                                                    int* __restrict__ zrow, int4* __restrict__ split) {
-  task_write<SELF>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split);
+  task_write<SELF, false>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split, false);
 }
 
 // room for the counts of q, which the caller's kernels or task_count form
 hgnn_status task_prepare(const TaskSource& q, TaskCounts& c) {
   c.nwin = int(ceil_div(q.nrows, kTaskWindow));
   HGNN_HIP(c.counts.alloc(sizeof(int) * size_t(kTaskAll) * size_t(q.nb) * (size_t(c.nwin) + 1)));
-  HGNN_HIP(c.secs.alloc(sizeof(hgnn_task_sec) * size_t(q.nb) + sizeof(TaskTotals) + sizeof(int)));
+  const size_t nsec = size_t(q.nb) + (q.range_min != kNoRanges ? 1 : 0);
+  HGNN_HIP(c.secs.alloc(sizeof(hgnn_task_sec) * nsec + sizeof(TaskTotals) + sizeof(int)));
   c.count = c.counts.as<int>();
   c.sums = c.count + size_t(kTaskAll) * size_t(q.nb) * size_t(c.nwin);
   c.sec = c.secs.as<hgnn_task_sec>();
-  c.long_at = c.count + size_t(kTaskLong) * size_t(q.nb) * size_t(c.nwin);
-  c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(c.sec + q.nb);
+  c.split_at = c.count + size_t(kTaskSplit) * size_t(q.nb) * size_t(c.nwin);
+  c.totals = c.mail.data ? reinterpret_cast<TaskTotals*>(c.mail.data) : reinterpret_cast<TaskTotals*>(c.sec + nsec);
   c.n_range = reinterpret_cast<int*>(c.totals + 1);
   return HGNN_OK;
 }
@@ -87,21 +87,27 @@ hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max
   }
   t->nb = q.nb;
   t->nnz = q.nnz;
-  t->n_split = tot.n_split + tot.n_long;
-  t->n_slots = tot.n_slots + tot.n_range;
+  t->n_split = tot.n_split;
+  t->n_slots = tot.n_slots;
   t->n_rtask = tot.n_range;
-  t->host.resize(size_t(q.nb));
+  t->stage_slots = std::max(t->n_slots, t->n_rtask);
+  const int nsec = q.nb + (tot.n_range > 0 ? 1 : 0);
+  t->host.resize(size_t(nsec));
   t->sec = c.sec;
   c.secs.p = nullptr;
   HGNN_HIP(dev_malloc(&t->task, sizeof(int4) * size_t(tot.n_task > 0 ? tot.n_task : 1)));
   HGNN_HIP(dev_malloc(&t->zrow, sizeof(int) * size_t(tot.n_zero > 0 ? tot.n_zero : 1)));
   if (t->n_split > 0) {
-    HGNN_HIP(dev_malloc(&t->split, sizeof(int4) * size_t(t->n_split)));
-    HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(t->n_slots) * size_t(max_F)));
-    HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(t->n_slots) * size_t(max_H)));
+    HGNN_HIP(dev_malloc(&t->split, sizeof(int4) * size_t(t->n_split) * (tot.n_range > 0 ? 2 : 1)));
+    HGNN_HIP(dev_malloc(&t->staging, sizeof(hgnn_half) * 2 * size_t(t->stage_slots) * size_t(max_F)));
+    HGNN_HIP(dev_malloc(&t->stage_mz, sizeof(float) * 3 * size_t(t->stage_slots) * size_t(max_H)));
   }
   if (q.nb == 1) t->host[0] = hgnn_task_sec{0, tot.n_whole, tot.n_whole, tot.n_task - tot.n_whole, 0, int32_t(tot.n_zero), 0};
-  if (tot.n_range > 0) HGNN_HIP(dev_malloc(&t->rtask, sizeof(int4) * size_t(tot.n_range)));
+  if (tot.n_range > 0) {  // (one block)
+    const int whole = tot.n_whole - tot.n_long_whole, group = tot.n_task - tot.n_whole - tot.n_long_group;
+    t->host[1] = hgnn_task_sec{0, whole, tot.n_whole, group, 0, int32_t(tot.n_zero), 0};
+    HGNN_HIP(dev_malloc(&t->rtask, sizeof(int4) * size_t(tot.n_range)));
+  }
   return HGNN_OK;
 }
 
@@ -145,7 +151,7 @@ TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F
   };
   t.sec = reinterpret_cast<hgnn_task_sec*>(take(sizeof(hgnn_task_sec)));
   t.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
-  t.counts = reinterpret_cast<int32_t*>(take(nwin * kTaskCounters * 4));
+  t.counts = reinterpret_cast<int32_t*>(take(nwin * kTaskAll * 4));
   t.task = reinterpret_cast<int4*>(take((nrows + over) * 16));
   t.zrow = reinterpret_cast<int32_t*>(take(nrows * 4));
   t.split = reinterpret_cast<int4*>(take(over * 16));
@@ -192,23 +198,23 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
     range_cut<kTaskThreads>(ranges, int(blockIdx.x));
     return;
   }
-  __shared__ int total[kTaskCounters];
+  __shared__ int total[kTaskAll];
   const int w = int(blockIdx.x) - nwin;
-  if (threadIdx.x < kTaskCounters) total[threadIdx.x] = 0;
+  if (threadIdx.x < kTaskAll) total[threadIdx.x] = 0;
   __syncthreads();
-  int n[kTaskAll] = {0, 0, 0, 0, 0, 0};
+  int n[kTaskAll] = {};
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     if (r >= q.nrows) break;
-    task_count_row(q, q.rowptr, int(r), n);
+    task_count_row<true>(q, q.rowptr, int(r), n);
   }
 #pragma unroll
-  for (int i = 0; i < kTaskCounters; ++i) {
+  for (int i = 0; i < kTaskAll; ++i) {
     const int v = wave_sum(n[i]);
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskCounters) counts[int64_t(threadIdx.x) * nwin + w] = total[threadIdx.x];
+  if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = total[threadIdx.x];
 }
 
 __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts, hgnn_task_sec* __restrict__ sec,
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
                                                                    int4* __restrict__ rtask, int4* __restrict__ rsplit) {
   const int b = int(blockIdx.x) - range_blocks;
   if (b >= 0) {
-    task_write<true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split);
+    task_write<true, true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split, true);
     return;
   }
   const int w = int(blockIdx.x) * kRangeGroup;

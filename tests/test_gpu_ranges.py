@@ -11,7 +11,9 @@ from parity import compare, down, f16, up
 
 pytestmark = pytest.mark.gpu
 
-V, NCOLS, S, MAX_F = 30000, 30011, 64, 288  # the plan's table is 17.3 MB
+# Tables of the calls below: 18.7 MB and more in SpMM (four L2s are 16.8), 16.6 MB in attention and dot products and 6.4 in their backward,
+# where a plan for MAX_F has column ranges and one for F has none.
+V, NCOLS, S, MAX_F = 50021, 130003, 64, 288
 
 
 @pytest.fixture(scope="module")
@@ -36,7 +38,7 @@ def graph():
     return rowptr, col
 
 
-@pytest.mark.parametrize("F,H", [(8, 1), (42, 1), (32, 4), (24, 3)])
+@pytest.mark.parametrize("F,H", [(72, 1), (74, 1), (96, 4), (72, 3)])
 @pytest.mark.parametrize("what", ["plain", "w", "map", "scaled"])
 def test_spmm(hgnn, dev, graph, F, H, what):
     print(f"ranges F={F} H={H} {what}", flush=True)
@@ -228,3 +230,57 @@ def test_a_very_long_row(hgnn, dev, S):
     hgnn.hgnn_spmm(ident, up(w, dev), 1, up(X2, dev), Y2,
                    workspace=torch.full((hgnn.hgnn_spmm_workspace(n, n, E, 2 * F),), 255, dtype=torch.uint8, device=dev))
     compare("very long row without a plan", np.ascontiguousarray(down(Y2)[:, F:]), ref, sabs)
+
+
+def test_calls_that_keep_ordinary_pieces(hgnn, dev, graph):
+    """Calls over a narrow table walk the same pieces whatever the plan was made for; only the row sums gather from something else."""
+    print("ranges, narrow calls", flush=True)
+    rowptr, col = graph
+    F, r = 8, np.random.default_rng(1)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=NCOLS)
+    t = hgnn.hgnn_transpose(g)
+    gm = hgnn.hgnn_transpose(hgnn.Csr(t.rowptr, t.col, ncols=V))
+    X, U = up(f16(r.standard_normal((NCOLS, F))), dev), up(f16(r.standard_normal((V, F))), dev)
+    w = up(f16(r.standard_normal((col.size, 1))), dev)
+    a_l, a_r = (up(f16(r.standard_normal(F)), dev) for _ in range(2))
+    got = []
+    for max_f in (F, MAX_F):
+        p, pm = (hgnn.hgnn_plan_create(x, S, max_f, 1, col_blocks=1) for x in (g, gm))
+        half = lambda *n: torch.full(n, 3.0, dtype=torch.float16, device=dev)
+        Y, Yw, Ym, out, lse, dot = half(V, F), half(V, F), half(V, F), half(V, F), half(V, 1).float(), half(col.size, 1)
+        hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+        hgnn.hgnn_spmm_discretized(p, g, w, 1, X, Yw)
+        hgnn.hgnn_spmm_discretized(pm, gm, w, 1, X, Ym)
+        hgnn.hgnn_gat_forward_fused(g, p, 1, F, U, X, a_l, a_r, out, lse)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, 1, F, U, X, dot)
+        got.append([down(x).view(np.uint8) for x in (Y, Yw, Ym, out, lse, dot)])
+        for x in (p, pm):
+            hgnn.hgnn_plan_destroy(x)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+def test_atomic_additions(hgnn, dev, graph):
+    """The variant that adds every piece to the row in fp16 rounds as often as there are segments, whatever the plan was made for: the
+    expected square of the error is a sum over the additions, so twice the additions would show as 1.4 times the error."""
+    print("ranges, atomic additions", flush=True)
+    rowptr, col = graph
+    F, r = 72, np.random.default_rng(2)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=NCOLS)
+    Xh = f16(r.standard_normal((NCOLS, F)))
+    ref = oracle.spmm(rowptr, col, Xh)
+    deg = np.diff(rowptr)
+    rows = (deg > 2 * S) & (deg <= 3 * S)  # of three segments' pieces; with column ranges of eight
+    X, err = up(Xh, dev), {}
+    n = int(rowptr[V // 2])  # half of the graph has no column ranges
+    assert n < 4 << 20
+    for name, h in (("half", hgnn.Csr(up(rowptr[: V // 2 + 1].copy(), dev), up(col[:n].copy(), dev), ncols=NCOLS)), ("all", g)):
+        m = h.rowptr.numel() - 1
+        Y = torch.full((m, F), 3.0, dtype=torch.float16, device=dev)
+        p = hgnn.hgnn_plan_create(h, S, MAX_F, 1, col_blocks=1)
+        hgnn.hgnn_spmm_discretized_variant(p, h, None, 1, X, Y, variant=hgnn.HGNN_EDGE_SEGMENTS_ATOMIC)
+        k = rows[: V // 2]
+        d = down(Y)[: V // 2][k].astype(np.float64) - ref[: V // 2][k]
+        err[name] = np.linalg.norm(d) / np.linalg.norm(ref[: V // 2][k])
+        hgnn.hgnn_plan_destroy(p)
+    assert err["all"] <= 1.1 * err["half"], err
