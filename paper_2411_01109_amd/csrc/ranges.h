@@ -15,6 +15,9 @@ constexpr int kRanges = 8;        // as many as there are XCDs
 constexpr int kRangeGroup = 4;    // windows of kTaskWindow rows whose pieces are sorted by length together (1, 2, 4: 5.5 M non-zeros x 4
                                   // heads, attention forward 110, 103, 102 us, SDDMM 62.5, 59.8, 58.6; a plan 76, 79, 82)
 constexpr int kRangePiece = 256;  // most non-zeros of a piece (also at most S)
+// Fewest non-zeros of a piece on average, for the memory: two partial rows are staged for each in a plan.  Graphs with small S would
+// gain below it, too: 5 M non-zeros in rows of 50, F = 128, S = 32, 6 to a piece: SpMM 172 / 152 us, staging 106 / 417 MB.
+constexpr int kRangeLeastMean = 8;
 
 // Every window of kTaskWindow rows cuts its own long rows; the pieces of a window and range are sorted by length together.
 struct RangeLists {

@@ -85,6 +85,7 @@ hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max
     HGNN_HIP(hipMemcpy(&tot, c.totals, sizeof(tot), hipMemcpyDeviceToHost));
     if (c.ranges) HGNN_HIP(hipMemcpy(&tot.n_range, c.n_range, sizeof(int), hipMemcpyDeviceToHost));
   }
+  if (tot.n_range > q.nnz / kRangeLeastMean) tot.n_range = 0;
   t->nb = q.nb;
   t->nnz = q.nnz;
   t->n_split = tot.n_split;

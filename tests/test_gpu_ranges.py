@@ -232,6 +232,31 @@ def test_a_very_long_row(hgnn, dev, S):
     compare("very long row without a plan", np.ascontiguousarray(down(Y2)[:, F:]), ref, sabs)
 
 
+@pytest.mark.parametrize("S,most", [(32, 180), (64, 60)])
+def test_memory_of_short_segments(hgnn, dev, S, most):
+    """Rows of about 50 non-zeros in segments of 32 have two pieces, in eight column ranges they would have eight: 417 MB of staging."""
+    print(f"ranges, memory S={S}", flush=True)
+    n, E, F = 100000, 5000000, 128
+    r = np.random.default_rng(S)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(r.integers(0, n, size=E), minlength=n))]).astype(np.int32)
+    row = np.repeat(np.arange(n), np.diff(rowptr))
+    col = (np.sort(row * n + r.integers(0, n, size=E)) - row * n).astype(np.int32)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=n)
+    Xh = f16(r.standard_normal((n, F)))
+    X, Y = up(Xh, dev), torch.full((n, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_release_cached_memory()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    p = hgnn.hgnn_plan_create(g, S, F, 1, col_blocks=1)
+    used = free - torch.cuda.mem_get_info()[0]
+    hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+    ref, sabs = oracle.spmm(rowptr, col, Xh, want_sabs=True)
+    compare("short segments", down(Y), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+    hgnn.hgnn_release_cached_memory()
+    assert used < most << 20, used
+
+
 def test_calls_that_keep_ordinary_pieces(hgnn, dev, graph):
     """Calls over a narrow table walk the same pieces whatever the plan was made for; only the row sums gather from something else."""
     print("ranges, narrow calls", flush=True)
