@@ -219,9 +219,11 @@ void hgnn_release_cached_memory(void);
  * reduced by a wavefront each and added in chunk order (up to nnz/512 + nnz/T + 2 partial rows in
  * fp32, F rounded up to a multiple of 8, and their lists; HGNN_EINVAL below that, and for sizes
  * that miss the room of the pieces by 512 bytes or less).
- * Beyond 4 Mi non-zeros, where the table X is larger than the L2s together, the query's answer also has
- * room for rows of more than 256 non-zeros in pieces that end where column ranges do; where that pays
- * (edge values behind a map; wide or large tables) the call takes it.  With a smaller workspace it does not.
+ * Beyond 4 Mi non-zeros, where the table X is larger than the L2s together and F <= 512, the query's answer
+ * also has room for rows of more than 256 non-zeros in pieces that end where column ranges do: a staged row
+ * and 16 bytes for every 128 non-zeros in all, and 44 bytes for every 257 (31 M non-zeros x 64: 96 MB instead
+ * of 57).  Where that pays (edge values behind a map; wide or large tables) the call takes them, if the graph
+ * has no more such pieces.  With a smaller workspace, for instance the answer for ncols = 1, it does not.
  * workspace == NULL is allowed: every long row is then reduced by a single wavefront (correct,
  * slow on hubs).
  * Where the table X (ncols rows of F halves) is beyond three L2s, fits three quarters of the

@@ -423,23 +423,16 @@ struct TaskScratch {
   int32_t* zrow;
   int4* split;
   float* staging;  // [slots][F rounded up to a multiple of 8] fp32
+  int4* rtask;     // [cap] pieces of the rows from range_min on at column ranges, or nullptr; the lists that lead there behind it
+  int32_t* range_lists;
+  int32_t* cuts;
+  int64_t cap;     // most pieces at column ranges: where a graph would have more, its long rows stay in ordinary pieces
+  int64_t rows;    // most rows of several pieces
   size_t bytes;
 };
-TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);  // base may be null: sizes only
-// What it takes beside that to cut the long rows at column ranges (they are then all of the rows that have several pieces).
-struct RangeScratch {
-  int32_t* lists;      // ranges.h
-  int32_t* long_rows;  // [windows]
-  TaskTotals* totals;  // n_split: the long rows, n_range: their pieces
-  int4* task;
-  int4* split;
-  float* staging;
-  int64_t cap, rows;   // most pieces, most long rows
-  size_t bytes;
-};
-RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F);
-hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s);
-hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const RangeScratch& r, const int32_t* col, int ncols, hipStream_t s);
+// base may be null: sizes only; range_min = kNoRanges: without column ranges
+TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F, int range_min);
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const int32_t* col, int ncols, hipStream_t s);
 struct TaskCounts {
   explicit TaskCounts(SetupStream& s) : counts(s), secs(s), mail(s) {}
   DevTemp counts, secs;

@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
     at.split = split_at[w];
     range_write(ranges, w, at, rtask, rsplit);
   } else if (b < n) {
-    task_write<false, true>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split, false);
+    task_write<false, true>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split, 0);
   } else if (b < n + list_blocks) {
     row_lists_write(q, b - n, n, offsets, o);
   } else {
@@ -478,8 +478,10 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   DevTemp range_mem(s);
   tc.ranges = tq.range_min != kNoRanges && nblk > 0;
   if (tc.ranges) {
-    HGNN_HIP(range_mem.alloc(range_bytes(g->nrows, nblk)));
-    ranges = range_lists(tq, g->col, g->ncols, nblk, range_mem.p);
+    const size_t cut_bytes = range_cut_bytes(g->nrows, E, tq.range_min);
+    HGNN_HIP(range_mem.alloc(cut_bytes + sizeof(int) * (kRanges + 1) * size_t(nblk)));
+    int* const count = reinterpret_cast<int*>(static_cast<char*>(range_mem.p) + cut_bytes);
+    ranges = range_lists(tq, g->col, g->ncols, nblk, range_mem.as<int>(), count, count + kRanges * size_t(nblk), nullptr);
   }
   HGNN_HIP(launch_validate_edges(g, facts, ranges, s));
   plan_scan_kernel<<<tc.ranges ? 3 : 2, kBlock, 0, s>>>(tq, nblk, counts, facts, totals, tc.count, tc.sums, tc.sec, tc.totals, ranges, tc.n_range);

@@ -23,16 +23,21 @@ constexpr int kRangeLeastMean = 8;
 struct RangeLists {
   const int* rowptr;
   const int* col;
-  int* cuts;   // [nrows][kRanges - 1] where a long row's share of the ranges from the second on begins
+  int* cuts;   // [range_cut_rows][kRanges - 1] where a long row's share of the ranges from the second on begins
   int* count;  // [kRanges][nwin] pieces, then where they go
   int* slots;  // [nwin] pieces of a window's rows, then the first of them
   int* long_rows;  // [nwin] long rows of a window, or nullptr (a plan has their number from its other counts)
   int nrows, nwin, piece, min_row, width;
+  bool by_row;  // where a row's cuts are: a place for every row, or for every min_row non-zeros (no two long rows share one)
+  __device__ __forceinline__ int* cuts_of(int row, int beg) const { return cuts + int64_t(by_row ? row : beg / min_row) * (kRanges - 1); }
 };
 
-static size_t range_bytes(int nrows, int nwin) { return sizeof(int) * ((kRanges - 1) * size_t(nrows) + (kRanges + 1) * size_t(nwin)); }
+static int64_t range_cut_rows(int64_t nrows, int64_t nnz, int min_row) { return nrows < nnz / min_row + 1 ? nrows : nnz / min_row + 1; }
+static size_t range_cut_bytes(int64_t nrows, int64_t nnz, int min_row) {
+  return sizeof(int) * (kRanges - 1) * size_t(range_cut_rows(nrows, nnz, min_row));
+}
 
-static RangeLists range_lists(const TaskSource& q, const int* col, int ncols, int nwin, void* mem) {
+static RangeLists range_lists(const TaskSource& q, const int* col, int ncols, int nwin, int* cuts, int* count, int* slots, int* long_rows) {
   RangeLists a{};
   a.rowptr = q.rowptr;
   a.col = col;
@@ -41,9 +46,11 @@ static RangeLists range_lists(const TaskSource& q, const int* col, int ncols, in
   a.piece = q.S < kRangePiece ? q.S : kRangePiece;
   a.min_row = q.range_min;
   a.width = int(ceil_div(ncols, kRanges));
-  a.cuts = static_cast<int*>(mem);
-  a.count = a.cuts + (kRanges - 1) * size_t(q.nrows);
-  a.slots = a.count + kRanges * size_t(nwin);
+  a.by_row = range_cut_rows(q.nrows, q.nnz, q.range_min) == q.nrows;
+  a.cuts = cuts;
+  a.count = count;
+  a.slots = slots;
+  a.long_rows = long_rows;
   return a;
 }
 
@@ -63,12 +70,15 @@ __device__ __forceinline__ RangeShare range_share(int piece, int beg, int end) {
 }
 // the share of range x of long row r, whose cuts are there
 __device__ __forceinline__ RangeShare range_share_of(const RangeLists& a, int r, int x) {
-  const int* c = a.cuts + int64_t(r) * (kRanges - 1);
-  return range_share(a.piece, x == 0 ? a.rowptr[r] : c[x - 1], x == kRanges - 1 ? a.rowptr[r + 1] : c[x]);
+  const int beg = a.rowptr[r], end = a.rowptr[r + 1];
+  const int* c = a.cuts_of(r, beg);
+  return range_share(a.piece, x == 0 ? beg : c[x - 1], x == kRanges - 1 ? end : c[x]);
 }
 
 // Window w by a workgroup of THREADS: a lane per (long row, range), the first non-zero of the range by binary search; its end is where
-// the next lane's begins.  Offsets have been checked, columns have not.
+// the next lane's begins.  Columns may be in any order: searches for rising values in the same array part where a middle element is
+// below one value and not the other, the former ends behind it and the latter at or before it, so the cuts ascend and every non-zero
+// is in one piece whatever the array holds.
 template <int THREADS>
 __device__ __forceinline__ void range_cut(const RangeLists& a, int w) {
   __shared__ int s_row[kTaskWindow], s_n, s_count[kRanges];
@@ -85,8 +95,8 @@ __device__ __forceinline__ void range_cut(const RangeLists& a, int w) {
     const int i = i0 + int(threadIdx.x) / kRanges;
     const bool ok = i < n;
     const int row = ok ? s_row[i] : 0;
-    const int end = ok ? a.rowptr[row + 1] : 0;
-    pos_t lo = ok ? pos_t(a.rowptr[row]) : 0, hi = pos_t(end);
+    const int beg = ok ? a.rowptr[row] : 0, end = ok ? a.rowptr[row + 1] : 0;
+    pos_t lo = pos_t(beg), hi = pos_t(end);
     if (x > 0) {
       const int64_t first = int64_t(x) * a.width;
       while (lo < hi) {
@@ -94,7 +104,7 @@ __device__ __forceinline__ void range_cut(const RangeLists& a, int w) {
         if (a.col[mid] < first) lo = mid + 1;
         else hi = mid;
       }
-      if (ok) a.cuts[int64_t(row) * (kRanges - 1) + x - 1] = int(lo);
+      if (ok) a.cuts_of(row, beg)[x - 1] = int(lo);
     }
     const int next = __shfl_down(int(lo), 1, kRanges);
     const int m = range_share(a.piece, int(lo), x == kRanges - 1 ? end : next).m;

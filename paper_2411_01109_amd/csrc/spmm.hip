@@ -1193,7 +1193,7 @@ constexpr size_t kNearMiss = 512;
 // scratch of the tasks, 0 where no row can be long (then one wave per row does)
 static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
   if (hub_layout(nnz, hub_threshold(nrows, nnz), F).bytes == 0) return 0;
-  return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F).bytes;
+  return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F, kNoRanges).bytes;
 }
 
 // Where long rows of the plan-free SpMM are cut at column ranges, as with a plan: room for it where the table is beyond what the L2s hold
@@ -1217,13 +1217,12 @@ static bool free_ranges_pay(bool mapped, int64_t ncols, int F) {
   device_cache_bytes(&l2, &llc);
   return mapped || ncols * F * 2 >= (F >= 128 ? llc / 2 : llc);
 }
-static size_t free_range_offset(size_t hub_bytes, size_t task_bytes) { return (std::max(hub_bytes, task_bytes) + 255) / 256 * 256; }
-// their scratch behind that of the tasks and hub chunks; 0: none
+// scratch of the tasks with column ranges; 0: no call takes them
 static size_t free_range_bytes(int64_t nrows, int64_t ncols, int64_t nnz, int F) {
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  if (!free_ranges_fit(ncols, nnz, F, l2) || free_task_bytes(nrows, nnz, F) == 0) return 0;
-  return range_scratch_at(nullptr, nrows, nnz, kRangeRow, F).bytes;
+  if (F > 512 || !free_ranges_fit(ncols, nnz, F, l2) || free_task_bytes(nrows, nnz, F) == 0) return 0;
+  return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F, kRangeRow + 1).bytes;
 }
 
 static HubLists hub_lists_at(void* base, const HubLayout& o) {
@@ -1532,33 +1531,27 @@ static void launch_block_sum(int L, dim3 grid, hipStream_t s, const SpmmArgs& a,
 
 // The plan-free SpMM over row tasks that are listed in the scratch by two small launches: rows sorted by length and cut into
 // pieces, so that lane groups end together and a hub keeps many compute units busy, as with a plan.  Pieces are staged in
-// fp32, a row is rounded once; long rows at column ranges where range_scratch is given.  A wave per G rows in storage order, hubs in chunks of their own, took as long as its longest
-// row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.54 -> 1.23 ms together.
-static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, void* range_scratch, hipStream_t s) {
-  const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F);
-  const RangeScratch r = range_scratch_at(range_scratch, g->nrows, g->nnz, kRangeRow, a.F);
-  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz, range_scratch ? kRangeRow + 1 : kNoRanges};
-  const hgnn_status st = range_scratch ? task_build_in(q, t, r, g->col, g->ncols, s) : task_build_in(q, t, s);
+// fp32, a row is rounded once; long rows are cut at column ranges where asked for.  A wave per G rows in storage order, hubs in chunks of their own, took as long
+// as its longest row: 31 M non-zeros x 64 with values, graph and transpose through the map, 1.54 -> 1.23 ms together.
+static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch, bool ranges, hipStream_t s) {
+  const TaskSource q{g->rowptr, nullptr, g->nrows, 1, kFreePiece, task_group_max(g->nnz), g->nnz, ranges ? kRangeRow + 1 : kNoRanges};
+  const TaskScratch t = task_scratch_at(scratch, g->nrows, g->nnz, kFreePiece, a.F, q.range_min);
+  const hgnn_status st = task_build_in(q, t, g->col, g->ncols, s);
   if (st != HGNN_OK) return st;
   const int L = pow2_at_least((a.F + 7) / 8);
   const bool mapped = a.w && a.eid;
   int64_t grid = 0;
-  TaskView v = task_view(t, range_scratch ? &r : nullptr, q, g->nnz, kWave / L, &grid);
-  a.staging = reinterpret_cast<half_t*>(range_scratch ? r.staging : t.staging);
+  const TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
+  a.staging = reinterpret_cast<half_t*>(t.staging);
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;
   const int wm = a.w ? 1 : 0;
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  const size_t least = least_task_lds(mapped, range_scratch != nullptr, a, g->ncols, l2, llc);
+  const size_t least = least_task_lds(mapped, ranges, a, g->ncols, l2, llc);
   if (near_table(g->ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   else launch_tasks<false>(L, wm, mapped, unsigned(grid), least, s, a, v, g->ncols);
   HGNN_LAUNCH_CHECK("spmm_task_kernel");
-  if (range_scratch) {  // the rows of several pieces are the long ones
-    v.totals = r.totals;
-    v.split = reinterpret_cast<const int4_t*>(r.split);
-    v.n_split = int(r.rows);
-  }
   launch_task_finish(L, s, a, v);
   HGNN_LAUNCH_CHECK("spmm_task_finish_kernel");
   return HGNN_OK;
@@ -1620,10 +1613,10 @@ hgnn_status spmm_rows(const char* who, const hgnn_csr* g, const hgnn_half* edge_
                  HGNN_EINVAL, "%s: the workspace holds %zu bytes, this graph needs %zu", who, scratch_bytes, task_bytes);
     HGNN_REQUIRE((reinterpret_cast<uintptr_t>(scratch) & 15u) == 0, HGNN_EINVAL, "%s: the workspace must be 16-byte aligned", who);
     if (scratch_bytes >= task_bytes && free_tasks_pay(F, edge_val != nullptr, edge_val && g->eid)) {
-      const size_t range_at = free_range_offset(base_bytes, task_bytes), range_bytes = free_range_bytes(g->nrows, g->ncols, g->nnz, F);
-      const bool ranges = range_bytes > 0 && npass == 1 && !one_sweep && scratch_bytes >= range_at + range_bytes &&
+      const size_t range_bytes = free_range_bytes(g->nrows, g->ncols, g->nnz, F);
+      const bool ranges = range_bytes > 0 && npass == 1 && !one_sweep && scratch_bytes >= range_bytes &&
                           free_ranges_pay(edge_val && g->eid, g->ncols, F);
-      return spmm_free_tasks(g, a, scratch, ranges ? static_cast<char*>(scratch) + range_at : nullptr, s);
+      return spmm_free_tasks(g, a, scratch, ranges, s);
     }
     // (a workspace, or the static array, can be too small for the tasks and still hold the hubs)
     h = hub_lists_at(scratch, lay);
@@ -1657,8 +1650,7 @@ size_t hgnn_spmm_workspace(int32_t nrows, int32_t ncols, int64_t nnz, int32_t F)
   size_t need = std::max(base, task);
   const int npass = ncols > 0 ? row_passes(nrows, ncols, nnz, F) : 1;
   if (npass > 1) return need + size_t(pass_layout(nrows, npass, F).bytes);
-  const size_t ranges = ncols > 0 ? free_range_bytes(nrows, ncols, nnz, F) : 0;
-  return ranges > 0 ? free_range_offset(base, task) + ranges : need;
+  return std::max(need, ncols > 0 ? free_range_bytes(nrows, ncols, nnz, F) : 0);
 }
 
 hgnn_status hgnn_spmm(const hgnn_csr* g, const hgnn_half* edge_val, int32_t H, const hgnn_half* X, int64_t ldx,

@@ -148,20 +148,18 @@ __device__ __forceinline__ void load_run(const int* __restrict__ p, pos_t i0, Ru
 }
 
 // the same for tasks whose numbers are on the device; *grid = workgroups to launch
-inline TaskView task_view(const TaskScratch& t, const RangeScratch* r, const TaskSource& q, int64_t nnz, int G, int64_t* grid) {
+inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz, int G, int64_t* grid) {
   TaskView v{};
   v.task = reinterpret_cast<const int4_t*>(t.task);
   v.zrow = t.zrow;
   v.sec = t.sec;
   v.split = reinterpret_cast<const int4_t*>(t.split);
   v.totals = t.totals;
-  v.n_split = int(nnz / q.S + 1);
+  v.n_split = int(t.rows);
   v.nb = 1;
-  if (r) {
-    v.rtask = reinterpret_cast<const int4_t*>(r->task);
-    v.rtotals = r->totals;
-  }
-  const int64_t n = (r ? int64_t(kXcds) * range_share(int(r->cap), G) / G : 0) + nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
+  v.rtask = reinterpret_cast<const int4_t*>(t.rtask);
+  if (t.rtask) v.rtotals = t.totals;
+  const int64_t n = int64_t(kXcds) * range_share(int(t.cap), G) / G + nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
   v.chunk = kTaskChunk;
   while (v.chunk > 1 && int64_t(v.chunk) * 64 > n) v.chunk >>= 1;
   constexpr int64_t kMostWaves = 65536;  // beyond this the waves take several tasks each

@@ -112,31 +112,33 @@ __device__ __forceinline__ void task_scan(const TaskSource& q, int nwin, int* __
 // One workgroup per window and block: counting sort of the lane-group pieces by falling length.  The order of equal
 // pieces depends on the order in which the LDS counters are reached; no result does.  SELF (one block): every workgroup adds
 // up the counts of the windows before it, instead of a launch that scans them; the first leaves section and totals.  Pieces of rows from
-// q.range_min on follow those of the others, or are left out (drop).
+// q.range_min on follow those of the others.  With both they are left out if no more than range_cap pieces take their place, whose number
+// of every window follows the counters.
 template <bool SELF, bool RANGES>
 __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin, const int* __restrict__ counts, const int* __restrict__ sums,
                                            hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals, int4* __restrict__ task,
-                                           int* __restrict__ zrow, int4* __restrict__ split, bool drop) {
-  constexpr int kLists = RANGES ? 2 : 1, kNext = RANGES ? int(kTaskAll) : int(kTaskCounters);
+                                           int* __restrict__ zrow, int4* __restrict__ split, int range_cap) {
+  constexpr int kLists = RANGES ? 2 : 1, kNext = RANGES ? int(kTaskAll) : int(kTaskCounters), kAdd = kNext + (RANGES ? 1 : 0);
   __shared__ int at[kLists][kMaxGroupLen + 1];  // pieces of each length, then where the next one goes; [1]: of rows from range_min on
   __shared__ int next[kNext];
   const int* rp = q.rowptr + int64_t(b) * (int64_t(q.nrows) + 1);
-  __shared__ int before[kNext], all[kNext];
+  __shared__ int before[kAdd], all[kAdd];
   hgnn_task_sec s;
+  bool drop = false;
   if (SELF) {
-    if (threadIdx.x < kNext) before[threadIdx.x] = all[threadIdx.x] = 0;
+    if (threadIdx.x < kAdd) before[threadIdx.x] = all[threadIdx.x] = 0;
     __syncthreads();
-    int b4[kNext] = {}, sum[kNext] = {};
+    int b4[kAdd] = {}, sum[kAdd] = {};
     for (int j = threadIdx.x; j < nwin; j += kTaskThreads) {
 #pragma unroll
-      for (int i = 0; i < kNext; ++i) {
+      for (int i = 0; i < kAdd; ++i) {
         const int n = counts[int64_t(i) * nwin + j];
         sum[i] += n;
         b4[i] += j < w ? n : 0;
       }
     }
 #pragma unroll
-    for (int i = 0; i < kNext; ++i) {
+    for (int i = 0; i < kAdd; ++i) {
       for (int off = kWave / 2; off > 0; off >>= 1) {
         b4[i] += __shfl_down(b4[i], off);
         sum[i] += __shfl_down(sum[i], off);
@@ -149,6 +151,7 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     __syncthreads();
     int nw = all[kTaskW], ng = all[kTaskG];
     if constexpr (RANGES) {
+      drop = all[kTaskAll] <= range_cap;
       if (!drop) {
         nw += all[kTaskLongW];
         ng += all[kTaskLongG];
@@ -157,8 +160,14 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     s = hgnn_task_sec{0, nw, nw, ng, 0, all[kTaskZ], 0};
     if (w == 0 && threadIdx.x == 0) {
       *sec = s;
-      const int n_split = RANGES && drop ? 0 : all[kTaskSplit], n_slots = RANGES && drop ? 0 : all[kTaskSlots];
-      *totals = TaskTotals{all[kTaskZ], nw + ng, nw, n_split, n_slots, 0, 0, 0};
+      totals->n_zero = all[kTaskZ];
+      totals->n_task = nw + ng;
+      totals->n_whole = nw;
+      if (!drop) {
+        totals->n_split = all[kTaskSplit];
+        totals->n_slots = all[kTaskSlots];
+        totals->n_range = 0;
+      }
     }
   } else {
     s = sec[b];

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, 
                                                                    const int* __restrict__ sums, hgnn_task_sec* __restrict__ sec,
                                                                    TaskTotals* __restrict__ totals, int4* __restrict__ task,
                                                                    int* __restrict__ zrow, int4* __restrict__ split) {
-  task_write<SELF, false>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split, false);
+  task_write<SELF, false>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split, 0);
 }
 
 // room for the counts of q, which the caller's kernels or task_count form
@@ -138,10 +138,15 @@ hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
   return HGNN_OK;
 }
 
-TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F) {
+// A staged row for every so many non-zeros is room enough for power-law graphs (one for 150 to 200; log-normal rows of 120 on average 143).
+// What a graph could have at most, eight pieces in rows of 257, is one for 29: 31 M non-zeros x 64 388 MB of workspace instead of 96.
+constexpr int kFreeRangeMean = 128;
+
+TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F, int range_min) {
   // bounds from the sizes alone: a row of more than S non-zeros has at most len / S + 1 pieces, and there are fewer than
   // nnz / S such rows
   const int64_t nwin = ceil_div(nrows, kTaskWindow), over = nnz / S + 1;
+  const bool ranges = range_min != kNoRanges;
   TaskScratch t{};
   char* const p = static_cast<char*>(base);
   int64_t at = 0;
@@ -150,50 +155,26 @@ TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F
     at += (bytes + 255) / 256 * 256;
     return r;
   };
+  t.rows = ranges ? std::max(over, nnz / range_min + 1) : over;
+  t.cap = ranges ? nnz / kFreeRangeMean : 0;
   t.sec = reinterpret_cast<hgnn_task_sec*>(take(sizeof(hgnn_task_sec)));
   t.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
-  t.counts = reinterpret_cast<int32_t*>(take(nwin * kTaskAll * 4));
+  t.counts = reinterpret_cast<int32_t*>(take(nwin * (ranges ? int(kTaskAll) + 1 : int(kTaskCounters)) * 4));
   t.task = reinterpret_cast<int4*>(take((nrows + over) * 16));
   t.zrow = reinterpret_cast<int32_t*>(take(nrows * 4));
-  t.split = reinterpret_cast<int4*>(take(over * 16));
-  t.staging = reinterpret_cast<float*>(take(2 * over * int64_t((F + 7) & ~7) * 4));
+  t.split = reinterpret_cast<int4*>(take(t.rows * 16));
+  t.staging = reinterpret_cast<float*>(take(std::max(2 * over, t.cap) * int64_t((F + 7) & ~7) * 4));
+  if (ranges) {
+    t.rtask = reinterpret_cast<int4*>(take(t.cap * 16));
+    t.range_lists = reinterpret_cast<int32_t*>(take(nwin * (kRanges + 1) * 4));
+    t.cuts = reinterpret_cast<int32_t*>(take(int64_t(range_cut_bytes(nrows, nnz, range_min))));
+  }
   t.bytes = size_t(at);
   return t;
 }
 
-hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, hipStream_t s) {
-  const int nwin = int(ceil_div(q.nrows, kTaskWindow));
-  task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
-  task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow,
-                                                                            t.split);
-  HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
-  return HGNN_OK;
-}
-
-RangeScratch range_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F) {
-  // a long row has more than S non-zeros and at most kRanges pieces beside one per kRangePiece non-zeros
-  const int64_t nwin = ceil_div(nrows, kTaskWindow);
-  RangeScratch r{};
-  char* const p = static_cast<char*>(base);
-  int64_t at = 0;
-  auto take = [&](int64_t bytes) {
-    char* x = p ? p + at : nullptr;
-    at += (bytes + 255) / 256 * 256;
-    return x;
-  };
-  r.rows = nnz / (S + 1) + 1;
-  r.cap = kRanges * r.rows + nnz / std::min<int64_t>(S, kRangePiece) + 1;
-  r.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
-  r.lists = reinterpret_cast<int32_t*>(take(int64_t(range_bytes(int(nrows), int(nwin)))));
-  r.long_rows = reinterpret_cast<int32_t*>(take(nwin * 4));
-  r.task = reinterpret_cast<int4*>(take(r.cap * 16));
-  r.split = reinterpret_cast<int4*>(take(r.rows * 16));
-  r.staging = reinterpret_cast<float*>(take(r.cap * int64_t((F + 7) & ~7) * 4));
-  r.bytes = size_t(at);
-  return r;
-}
-
-// Without a plan and with column ranges: two launches, in each of which the workgroups for the long rows come first.
+// Without a plan and with column ranges: two launches, in each of which the workgroups for the long rows come first.  The second adds up the
+// pieces at column ranges and leaves the long rows in ordinary pieces where they are more than there is room for.
 __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, int nwin, int* __restrict__ counts, RangeLists ranges) {
   if (int(blockIdx.x) < nwin) {
     range_cut<kTaskThreads>(ranges, int(blockIdx.x));
@@ -218,33 +199,40 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
   if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = total[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts, hgnn_task_sec* __restrict__ sec,
-                                                                   TaskTotals* __restrict__ totals, int4* __restrict__ task,
-                                                                   int* __restrict__ zrow, int4* __restrict__ split, RangeLists ranges,
-                                                                   int range_blocks, TaskTotals* __restrict__ range_totals,
-                                                                   int4* __restrict__ rtask, int4* __restrict__ rsplit) {
+__global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, int range_cap, const int* __restrict__ counts,
+                                                                  hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals,
+                                                                  int4* __restrict__ task, int* __restrict__ zrow, int4* __restrict__ split,
+                                                                  RangeLists ranges, int range_blocks, int4* __restrict__ rtask) {
   const int b = int(blockIdx.x) - range_blocks;
   if (b >= 0) {
-    task_write<true, true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split, true);
+    task_write<true, true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split, range_cap);
     return;
   }
   const int w = int(blockIdx.x) * kRangeGroup;
   int all[2];
   const RangePlace place = range_place(ranges, w, all);
-  if (all[1] > 0) range_write(ranges, w, place, rtask, rsplit);
+  if (all[0] > range_cap) return;
+  if (all[1] > 0) range_write(ranges, w, place, rtask, split);
   if (w == 0 && threadIdx.x == 0) {
-    range_totals->n_range = range_totals->n_slots = all[0];
-    range_totals->n_split = all[1];
+    totals->n_range = totals->n_slots = all[0];
+    totals->n_split = all[1];
   }
 }
 
-hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const RangeScratch& r, const int32_t* col, int ncols, hipStream_t s) {
-  const int nwin = int(ceil_div(q.nrows, kTaskWindow)), range_blocks = int(ceil_div(nwin, kRangeGroup));
-  RangeLists ranges = range_lists(q, col, ncols, nwin, r.lists);
-  ranges.long_rows = r.long_rows;
+hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const int32_t* col, int ncols, hipStream_t s) {
+  const int nwin = int(ceil_div(q.nrows, kTaskWindow));
+  if (q.range_min == kNoRanges) {
+    task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
+    task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow, t.split);
+    HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
+    return HGNN_OK;
+  }
+  const int range_blocks = int(ceil_div(nwin, kRangeGroup));
+  const RangeLists ranges = range_lists(q, col, ncols, nwin, t.cuts, t.range_lists, t.counts + int(kTaskAll) * int64_t(nwin),
+                                        t.range_lists + kRanges * int64_t(nwin));
   free_count_kernel<<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
-  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, t.sec, t.totals, t.task, t.zrow, t.split,
-                                                                               ranges, range_blocks, r.totals, r.task, r.split);
+  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, int(t.cap), t.counts, t.sec, t.totals, t.task, t.zrow,
+                                                                               t.split, ranges, range_blocks, t.rtask);
   HGNN_LAUNCH_CHECK("free_count_kernel / free_write_kernel");
   return HGNN_OK;
 }

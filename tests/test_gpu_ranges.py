@@ -177,9 +177,11 @@ def test_without_a_plan(hgnn, dev, F, H, ncols, mapped, has_w):
         compare("without a plan", np.ascontiguousarray(y[:, :F]), ref, sabs)
 
 
+@pytest.mark.parametrize("spread", [True, False])
 @pytest.mark.parametrize("rows,least,most", [(18000, 257, 300), (18000, 257, 480), (70000, 257, 260)])
-def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most):
-    """Most non-zeros in rows that are barely long: more of them than there are pieces of 512, and more than take a wave each."""
+def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most, spread):
+    """Most non-zeros in rows that are barely long: more of them than there are pieces of 512, and more than take a wave each.  Over all
+    columns they have more pieces at column ranges than there is room for, inside one range two each."""
     print(f"ranges without a plan, {rows} rows of {least} to {most}", flush=True)
     F, ncols = 8, 2200003
     r = np.random.default_rng(rows + most)
@@ -190,7 +192,12 @@ def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most):
     E = int(rowptr[-1])
     assert 4 << 20 < E < 128 * deg.size and rows > E // 512 + 1
     row = np.repeat(np.arange(deg.size), deg)
-    col = (np.sort(row * ncols + r.integers(0, ncols, size=E)) - row * ncols).astype(np.int32)
+    c = r.integers(0, ncols, size=E)
+    if not spread:
+        width = -(-ncols // 8)
+        c = np.minimum(c % width + row % 8 * width, ncols - 1)
+    col = (np.sort(row * ncols + c) - row * ncols).astype(np.int32)
+    assert (8 * rows > E // 128) and (2 * rows <= E // 128)
     Xh, w, eid = f16(r.standard_normal((ncols, F))), f16(r.standard_normal((E, 1))), r.permutation(E).astype(np.int32)
     n = hgnn.hgnn_spmm_workspace(deg.size, ncols, E, F)
     assert n > hgnn.hgnn_spmm_workspace(deg.size, 0, E, F)
@@ -199,6 +206,49 @@ def test_without_a_plan_many_long_rows(hgnn, dev, rows, least, most):
                    workspace=torch.full((n,), 255, dtype=torch.uint8, device=dev))
     ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
     compare("many long rows", down(Y), ref, sabs)
+
+
+@pytest.mark.parametrize("spare", [0, -1])
+def test_without_a_plan_room(hgnn, dev, spare):
+    """Exactly as many pieces at column ranges as there is room for, and one more than that."""
+    print(f"ranges without a plan, {spare} pieces to spare", flush=True)
+    F, ncols, n = 8, 2200003, 5000
+    width = -(-ncols // 8)
+    r = np.random.default_rng(3)
+    E = 1024 * n + spare
+    deg = np.concatenate([np.full(n, 304), np.full((E - 304 * n) // 100, 100), [(E - 304 * n) % 100]])
+    deg = deg[r.permutation(deg.size)]
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    assert rowptr[-1] == E and E // 128 == 8 * n + spare and E < 128 * deg.size
+    row = np.repeat(np.arange(deg.size), deg)
+    k = np.arange(E) - rowptr[:-1].astype(np.int64)[row]
+    c = np.where(deg[row] == 304, np.minimum(k // 38 * width + r.integers(0, width, size=E), ncols - 1), r.integers(0, ncols, size=E))
+    col = (np.sort(row * ncols + c) - row * ncols).astype(np.int32)  # 38 non-zeros in every range
+    Xh, w, eid = f16(r.standard_normal((ncols, F))), f16(r.standard_normal((E, 1))), r.permutation(E).astype(np.int32)
+    Y = torch.full((deg.size, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm(hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=up(eid, dev)), up(w, dev), 1, up(Xh, dev), Y, F=F,
+                   workspace=torch.full((hgnn.hgnn_spmm_workspace(deg.size, ncols, E, F),), 255, dtype=torch.uint8, device=dev))
+    ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
+    compare("room", down(Y), ref, sabs)
+
+
+def test_without_a_plan_any_order(hgnn, dev):
+    """Rows whose columns do not ascend: still every non-zero once."""
+    print("ranges without a plan, columns in any order", flush=True)
+    F, ncols, n = 8, 2200003, 60000
+    r = np.random.default_rng(4)
+    deg = r.integers(0, 120, size=n)
+    deg[:2000] = r.integers(257, 3000, size=2000)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    assert 4 << 20 < E < 128 * n
+    col = r.integers(0, ncols, size=E).astype(np.int32)
+    Xh, w, eid = f16(r.standard_normal((ncols, F))), f16(r.standard_normal((E, 1))), r.permutation(E).astype(np.int32)
+    Y = torch.full((n, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm(hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=up(eid, dev)), up(w, dev), 1, up(Xh, dev), Y, F=F,
+                   workspace=torch.full((hgnn.hgnn_spmm_workspace(n, ncols, E, F),), 255, dtype=torch.uint8, device=dev))
+    ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
+    compare("any order", down(Y), ref, sabs)
 
 
 @pytest.mark.parametrize("S", [4, 64, 256])
