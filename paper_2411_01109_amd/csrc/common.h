@@ -417,6 +417,7 @@ constexpr int kTaskWindow = 1024;  // rows that are sorted together: enough for 
 // the kernels read it from `sec` and `totals` and walk the tasks with a grid stride.
 struct TaskScratch {
   int32_t* counts;
+  int32_t* sums;
   hgnn_task_sec* sec;
   TaskTotals* totals;
   int4* task;

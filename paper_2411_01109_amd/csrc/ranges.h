@@ -164,13 +164,20 @@ struct RangePlace {
   int slot, split;    // the first staging slot and the first entry of the rows of several pieces
 };
 
-// the same where nothing has scanned the counts: what the windows before w hold, and in *all (pieces, long rows) what all of them do
-__device__ __forceinline__ RangePlace range_place(const RangeLists& a, int w, int* all) {
+// the same without a plan: what the windows before w hold, and in *all (pieces, long rows) what all of them do.  Unless a launch has scanned
+// the counts (then sums are the totals of slots, counts and long rows), the workgroup adds them up.
+__device__ __forceinline__ RangePlace range_place(const RangeLists& a, int w, const int* __restrict__ sums, int* all) {
   constexpr int kSums = kRanges + 2;  // pieces of every range, pieces, long rows
   __shared__ int s_before[kSums], s_all[kSums];
   if (threadIdx.x < kSums) s_before[threadIdx.x] = s_all[threadIdx.x] = 0;
   __syncthreads();
-  for (int i = kSums - 1; i >= 0; --i) {
+  if (sums && threadIdx.x < kSums) {
+    const int i = threadIdx.x;
+    const int* v = i < kRanges ? a.count + i * a.nwin : (i == kRanges ? a.slots : a.long_rows);
+    s_before[i] = v[w];
+    s_all[i] = sums[i < kRanges ? i + 1 : (i == kRanges ? 0 : i)];
+  }
+  for (int i = sums ? -1 : kSums - 1; i >= 0; --i) {
     const int* v = i < kRanges ? a.count + i * a.nwin : (i == kRanges ? a.slots : a.long_rows);
     int before = 0, sum = 0;
 #pragma unroll 4

@@ -111,7 +111,7 @@ __device__ __forceinline__ void task_scan(const TaskSource& q, int nwin, int* __
 
 // One workgroup per window and block: counting sort of the lane-group pieces by falling length.  The order of equal
 // pieces depends on the order in which the LDS counters are reached; no result does.  SELF (one block): every workgroup adds
-// up the counts of the windows before it, instead of a launch that scans them; the first leaves section and totals.  Pieces of rows from
+// up the counts of the windows before it, unless a launch has scanned them (then sums are their totals); the first leaves section and totals.  Pieces of rows from
 // q.range_min on follow those of the others.  With both they are left out if no more than range_cap pieces take their place, whose number
 // of every window follows the counters.
 template <bool SELF, bool RANGES>
@@ -126,29 +126,34 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
   hgnn_task_sec s;
   bool drop = false;
   if (SELF) {
-    if (threadIdx.x < kAdd) before[threadIdx.x] = all[threadIdx.x] = 0;
+    if (threadIdx.x < kAdd) {
+      before[threadIdx.x] = sums ? counts[int64_t(threadIdx.x) * nwin + w] : 0;
+      all[threadIdx.x] = sums ? sums[threadIdx.x] : 0;
+    }
     __syncthreads();
-    int b4[kAdd] = {}, sum[kAdd] = {};
-    for (int j = threadIdx.x; j < nwin; j += kTaskThreads) {
+    if (!sums) {
+      int b4[kAdd] = {}, sum[kAdd] = {};
+      for (int j = threadIdx.x; j < nwin; j += kTaskThreads) {
+#pragma unroll
+        for (int i = 0; i < kAdd; ++i) {
+          const int n = counts[int64_t(i) * nwin + j];
+          sum[i] += n;
+          b4[i] += j < w ? n : 0;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kAdd; ++i) {
-        const int n = counts[int64_t(i) * nwin + j];
-        sum[i] += n;
-        b4[i] += j < w ? n : 0;
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+          b4[i] += __shfl_down(b4[i], off);
+          sum[i] += __shfl_down(sum[i], off);
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+          atomicAdd(&before[i], b4[i]);
+          atomicAdd(&all[i], sum[i]);
+        }
       }
+      __syncthreads();
     }
-#pragma unroll
-    for (int i = 0; i < kAdd; ++i) {
-      for (int off = kWave / 2; off > 0; off >>= 1) {
-        b4[i] += __shfl_down(b4[i], off);
-        sum[i] += __shfl_down(sum[i], off);
-      }
-      if ((threadIdx.x & (kWave - 1)) == 0) {
-        atomicAdd(&before[i], b4[i]);
-        atomicAdd(&all[i], sum[i]);
-      }
-    }
-    __syncthreads();
     int nw = all[kTaskW], ng = all[kTaskG];
     if constexpr (RANGES) {
       drop = all[kTaskAll] <= range_cap;

@@ -40,6 +40,34 @@ __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, i
   task_scan(q, nwin, counts, sums, sec, out);
 }
 
+// Without a plan: exclusive scans of the counts of the windows in place, a workgroup for every array of them (n_first of those at `first`,
+// the others at `second`), and their totals.
+constexpr int kFreeScanThreads = 1024;
+__global__ __launch_bounds__(kFreeScanThreads) void free_scan_kernel(int nwin, int* __restrict__ first, int n_first, int* __restrict__ second,
+                                                                      int* __restrict__ sums) {
+  __shared__ int s_wave[kFreeScanThreads / kWave];
+  const int i = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int* const v = i < n_first ? first + int64_t(i) * nwin : second + int64_t(i - n_first) * nwin;
+  const int per = (nwin + kFreeScanThreads - 1) / kFreeScanThreads, j0 = min(int(threadIdx.x) * per, nwin), j1 = min(j0 + per, nwin);
+  int own = 0;
+  for (int j = j0; j < j1; ++j) own += v[j];
+  int incl = own;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if (lane >= d) incl += t;
+  }
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int at = incl - own;
+  for (int w = 0; w < wave; ++w) at += s_wave[w];
+  if (threadIdx.x == kFreeScanThreads - 1) sums[i] = at + own;
+  for (int j = j0; j < j1; ++j) {
+    const int n = v[j];
+    v[j] = at;
+    at += n;
+  }
+}
+
 template <bool SELF>
 __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts,
                                                                    const int* __restrict__ sums, hgnn_task_sec* __restrict__ sec,
@@ -142,6 +170,9 @@ hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
 // What a graph could have at most, eight pieces in rows of 257, is one for 29: 31 M non-zeros x 64 388 MB of workspace instead of 96.
 constexpr int kFreeRangeMean = 128;
 
+constexpr int64_t kSumsAt = 64;  // in the 256 bytes of the totals
+static_assert(sizeof(TaskTotals) <= kSumsAt && kSumsAt + sizeof(int) * (kTaskAll + kRanges + 2) <= 256, "room");
+
 TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F, int range_min) {
   // bounds from the sizes alone: a row of more than S non-zeros has at most len / S + 1 pieces, and there are fewer than
   // nnz / S such rows
@@ -158,7 +189,8 @@ TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F
   t.rows = ranges ? std::max(over, nnz / range_min + 1) : over;
   t.cap = ranges ? nnz / kFreeRangeMean : 0;
   t.sec = reinterpret_cast<hgnn_task_sec*>(take(sizeof(hgnn_task_sec)));
-  t.totals = reinterpret_cast<TaskTotals*>(take(sizeof(TaskTotals)));
+  t.totals = reinterpret_cast<TaskTotals*>(take(kSumsAt + sizeof(int) * (kTaskAll + kRanges + 2)));
+  t.sums = t.totals ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(t.totals) + kSumsAt) : nullptr;
   t.counts = reinterpret_cast<int32_t*>(take(nwin * (ranges ? int(kTaskAll) + 1 : int(kTaskCounters)) * 4));
   t.task = reinterpret_cast<int4*>(take((nrows + over) * 16));
   t.zrow = reinterpret_cast<int32_t*>(take(nrows * 4));
@@ -200,17 +232,18 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
 }
 
 __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, int range_cap, const int* __restrict__ counts,
+                                                                  const int* __restrict__ sums,
                                                                   hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals,
                                                                   int4* __restrict__ task, int* __restrict__ zrow, int4* __restrict__ split,
                                                                   RangeLists ranges, int range_blocks, int4* __restrict__ rtask) {
   const int b = int(blockIdx.x) - range_blocks;
   if (b >= 0) {
-    task_write<true, true>(q, b, 0, nwin, counts, nullptr, sec, totals, task, zrow, split, range_cap);
+    task_write<true, true>(q, b, 0, nwin, counts, sums, sec, totals, task, zrow, split, range_cap);
     return;
   }
   const int w = int(blockIdx.x) * kRangeGroup;
   int all[2];
-  const RangePlace place = range_place(ranges, w, all);
+  const RangePlace place = range_place(ranges, w, sums ? sums + kTaskAll : nullptr, all);
   if (all[0] > range_cap) return;
   if (all[1] > 0) range_write(ranges, w, place, rtask, split);
   if (w == 0 && threadIdx.x == 0) {
@@ -219,11 +252,17 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
   }
 }
 
+// Up to so many windows every workgroup adds up the counts of all of them, beyond a launch scans them first: the additions grow with the square of
+// the rows.  us a call, added up / scanned, in pieces and at column ranges: 0.4 M rows 99.3 / 99.0, 98.5 / 98.1; 0.7 M 174 / 173, 168 / 162;
+// 1.5 M 238 / 235, 232 / 222; 2.4 M 638 / 628, 587 / 569; 10 M 1268 / 1203, 1366 / 1203; 20 M 1971 / 1736, 2365 / 1781; 0.2 M 57.7 / 58.5, 57.2 / 58.0.
+constexpr int kFreeScanWindows = 400;
 hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const int32_t* col, int ncols, hipStream_t s) {
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
+  int* const sums = nwin > kFreeScanWindows ? t.sums : nullptr;
   if (q.range_min == kNoRanges) {
     task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
-    task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, nullptr, t.sec, t.totals, t.task, t.zrow, t.split);
+    if (sums) free_scan_kernel<<<kTaskCounters, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskCounters, nullptr, sums);
+    task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, sums, t.sec, t.totals, t.task, t.zrow, t.split);
     HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
     return HGNN_OK;
   }
@@ -231,7 +270,8 @@ hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const int32
   const RangeLists ranges = range_lists(q, col, ncols, nwin, t.cuts, t.range_lists, t.counts + int(kTaskAll) * int64_t(nwin),
                                         t.range_lists + kRanges * int64_t(nwin));
   free_count_kernel<<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
-  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, int(t.cap), t.counts, t.sec, t.totals, t.task, t.zrow,
+  if (sums) free_scan_kernel<<<kTaskAll + kRanges + 2, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskAll + 1, t.range_lists, sums);
+  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, int(t.cap), t.counts, sums, t.sec, t.totals, t.task, t.zrow,
                                                                                t.split, ranges, range_blocks, t.rtask);
   HGNN_LAUNCH_CHECK("free_count_kernel / free_write_kernel");
   return HGNN_OK;

@@ -232,6 +232,30 @@ def test_without_a_plan_room(hgnn, dev, spare):
     compare("room", down(Y), ref, sabs)
 
 
+@pytest.mark.parametrize("n", [409600, 409601])
+def test_without_a_plan_many_windows(hgnn, dev, n):
+    """400 windows of rows add up their counts, more have them scanned; in pieces and with column ranges."""
+    print(f"ranges without a plan, {n} rows", flush=True)
+    F, ncols = 8, 2200003
+    r = np.random.default_rng(n)
+    deg = r.integers(0, 20, size=n)
+    deg[r.permutation(n)[:1000]] = r.integers(200, 1200, size=1000)
+    deg[-3:] = (0, 700, 2000)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    assert E > 4 << 20
+    row = np.repeat(np.arange(n), deg)
+    col = (np.sort(row * ncols + r.integers(0, ncols, size=E)) - row * ncols).astype(np.int32)
+    Xh, w, eid = f16(r.standard_normal((ncols, F))), f16(r.standard_normal((E, 1))), r.permutation(E).astype(np.int32)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols, eid=up(eid, dev))
+    ref, sabs = oracle.spmm(rowptr, col, Xh, w=w, H=1, want_sabs=True, eid=eid)
+    for cols in (1, ncols):
+        Y = torch.full((n, F), 3.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_spmm(g, up(w, dev), 1, up(Xh, dev), Y, F=F,
+                       workspace=torch.full((hgnn.hgnn_spmm_workspace(n, cols, E, F),), 255, dtype=torch.uint8, device=dev))
+        compare("many windows", down(Y), ref, sabs)
+
+
 def test_without_a_plan_any_order(hgnn, dev):
     """Rows whose columns do not ascend: still every non-zero once."""
     print("ranges without a plan, columns in any order", flush=True)

@@ -141,7 +141,17 @@ def room_for_column_ranges(h):
     assert h.lib.hgnn_spmm_workspace(1200001, 1200001, i64(31000001), 520) == h.lib.hgnn_spmm_workspace(1200001, 1, i64(31000001), 520)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges]
+def many_windows(h):
+    """Beyond 400 windows of 1024 rows a launch scans their counts, for pieces and with column ranges, instead of every workgroup."""
+    for nrows in (409600, 409601, 20000000):
+        g = graph(h, nrows, 5000000, 41000000, True)
+        for ncols, kind in ((1, "task_write"), (5000000, "free_write")):
+            st, names = spmm(h, g, 16, h.lib.hgnn_spmm_workspace(nrows, ncols, i64(41000000), 16), vp(h.data))
+            assert st == 0 and any(kind in n for n in names), names
+            assert any("free_scan" in n for n in names) == (nrows > 409600), (nrows, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
