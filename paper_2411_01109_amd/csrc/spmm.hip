@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) 
     const RangeWaves ranges = LOOP == 2 ? range_waves<kWave / L>(v) : RangeWaves{0, 0, 0};
     const int n = ranges.waves + task_waves<kWave / L>(v);
     for (int wid = blockIdx.x; wid < n; wid += gridDim.x)
-      spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L>(v, wid, g, ranges); });
+      spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L, LOOP>(v, wid, g, ranges); });
   } else {
     spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L>(v, blockIdx.x, g); });
   }
@@ -1211,7 +1211,6 @@ static size_t free_task_bytes(int64_t nrows, int64_t nnz, int F) {
 //   20 M log-normal, 51 MB, F = 64         400 / 398       725 / 728
 //   20 M uniform (no long row), 128 MB     420 / 420       777 / 777
 //   5.5 M, 34 MB, F = 64                    71 / 80        121 / 122
-static bool free_ranges_fit(int64_t ncols, int64_t nnz, int F, int64_t l2) { return nnz > (int64_t(4) << 20) && ncols * F * 2 > 8 * l2; }
 static bool free_ranges_pay(bool mapped, int64_t ncols, int F) {
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
@@ -1219,9 +1218,10 @@ static bool free_ranges_pay(bool mapped, int64_t ncols, int F) {
 }
 // scratch of the tasks with column ranges; 0: no call takes them
 static size_t free_range_bytes(int64_t nrows, int64_t ncols, int64_t nnz, int F) {
+  if (nnz <= int64_t(4) << 20 || F > 512 || free_task_bytes(nrows, nnz, F) == 0) return 0;
   int64_t l2 = 0, llc = 0;
   device_cache_bytes(&l2, &llc);
-  if (F > 512 || !free_ranges_fit(ncols, nnz, F, l2) || free_task_bytes(nrows, nnz, F) == 0) return 0;
+  if (ncols * F * 2 <= 8 * l2) return 0;
   return task_scratch_at(nullptr, nrows, nnz, kFreePiece, F, kRangeRow + 1).bytes;
 }
 

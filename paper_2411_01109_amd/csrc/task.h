@@ -198,7 +198,7 @@ struct TaskWave {
 
 // wid is the same on all lanes of the wave; g = lane / L.  Everything up to the task is scalar; a choice between two addresses to
 // load from would turn all of it into vector code (5.5 M non-zeros, SDDMM 58 -> 62 us, attention forward 82 -> 87).
-// ranges: the pieces of rows cut at column ranges, if any.
+// ranges: the pieces of rows cut at column ranges, if any.  FREE: the view is one without a plan (1: without column ranges either).
 struct RangeWaves {
   int waves, share, n;  // waves that take them, pieces per XCD, pieces
 };
@@ -207,11 +207,11 @@ __device__ __forceinline__ RangeWaves range_waves(const TaskView& v) {  // witho
   const int n = v.rtotals ? v.rtotals->n_range : 0, share = range_share(n, G);
   return RangeWaves{share / G * kXcds, share, n};
 }
-template <int L>
+template <int L, int FREE>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g, const RangeWaves& ranges) {
   constexpr int G = kWave / L;
   TaskWave w;
-  if (wid < ranges.waves) {
+  if (FREE != 1 && wid < ranges.waves) {
     const int i = (wid >> 3) * G + g, k = (wid & 7) * ranges.share + i;
     int4_t t = {0, 0, -1, -1};
     if (k < ranges.n) t = v.rtask[k];
@@ -226,11 +226,14 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
     w.span = w.step = Round<L>::R;
     return w;
   }
-  wid += v.first_wave[0] - ranges.waves;  // (no change with a plan)
-  int b = 0;
-  while (b + 1 < v.nb && wid >= v.first_wave[b + 1]) ++b;
+  int b = 0, i = wid;
+  if (FREE) {
+    if (FREE == 2) i -= ranges.waves;
+  } else {
+    while (b + 1 < v.nb && wid >= v.first_wave[b + 1]) ++b;
+    i -= v.first_wave[b];
+  }
   const hgnn_task_sec s = v.sec[b];
-  int i = wid - v.first_wave[b];
   w.block = b;
   w.first = s.first;
   w.whole = false;
@@ -239,7 +242,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   int4_t t = {0, 0, -1, -1};
   // sections begin at multiples of eight: i & 7 is the XCD
   const int nw = (s.nw + 7) & ~7, gw = int(((pos_t(s.ng) + G - 1) / G + 7) & ~7u);
-  const uint32_t mix = v.mix[b];
+  const uint32_t mix = FREE ? 0 : v.mix[b];
   bool wh = i < nw;                        // a whole-wave piece
   pos_t before = pos_t(wh ? i : nw) >> 3;  // groups of eight waves before this one that take those
   if (mix && i < nw + gw) {
@@ -282,7 +285,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
 
 template <int L>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
-  return task_enter<L>(v, wid, g, RangeWaves{v.first_wave[0], v.rshare, v.n_rtask});
+  return task_enter<L, 0>(v, wid, g, RangeWaves{v.first_wave[0], v.rshare, v.n_rtask});
 }
 
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these
