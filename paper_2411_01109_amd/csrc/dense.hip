@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
 }
 
 // The same for few rows in one launch: a workgroup owns 16 x 16 values of dW and all rows, its 16 waves take 32 rows in turn
-// and are added in LDS in wave order.  Bound by latency: 64 x 64 over 1000 rows 7.6 -> 4.7 us (two launches before).  Every
+// and are added in LDS in wave order.  Bound by latency: 64 x 64 over 1000 rows 4.3 us, in two launches 5.7.  Every
 // workgroup reads its 32-byte columns of all rows, so the time grows with the rows, but no partial results are left.
 constexpr int kSmallWaves = 16;
 
@@ -745,11 +745,21 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   parts = std::max<int64_t>(1, std::min<int64_t>(parts, ceil_div(n, int64_t(kWgradRows) * WR)));
   WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
   // few rows: one launch without partial results, up to the rows at which fetching them in 32-byte pieces costs what the
-  // second launch does.  Behind the kernel that wrote dY: 64 x 64 at 1000, 2000, 4096 rows 4.7, 6.7, 11.8 us against 7.6,
-  // 7.6, 8.1; 256 x 256 at 2000 7.9 against 20.5.  Beyond one workgroup per compute unit they queue: 608 x 128 (304)
-  // at 2000, 3000 rows 8.4, 22.7 against 20.6, 20.0
-  const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16);
-  if (n <= 2048 && n * sb * sf <= 2560 * int64_t(kCus)) {
+  // second launch and the partial results do, later the larger dW is.  us behind the kernel that wrote dY, one launch / two:
+  //   K x F         1000        1500        2000        2500        3000        4096        6000 rows
+  //   16 x 16     2.8 / 5.0   3.1 / 5.1   3.6 / 5.2   4.1 / 5.3   4.5 / 5.4   5.4 / 5.5   6.6 / 5.8
+  //   32 x 32     3.2 / 5.5   4.0 / 5.4   4.5 / 5.4   5.4 / 5.7   6.0 / 5.8   7.5 / 5.8   9.3 / 6.2
+  //   64 x 16     3.3 / 5.2   4.1 / 5.2   4.6 / 5.4   5.6 / 5.5   6.0 / 5.6   7.3 / 5.7  10.0 / 6.0
+  //   64 x 64     4.3 / 5.7   5.3 / 5.7   6.6 / 5.8   7.6 / 6.0   8.4 / 6.1  11.1 / 6.2  14.6 / 6.6
+  //   128 x 64    4.2 / 6.0   5.3 / 6.3   6.5 / 6.5   7.5 / 6.8   8.3 / 7.0  11.0 / 7.5  14.4 / 8.6
+  //   128 x 128   4.6 / 7.0   5.8 / 7.7   7.2 / 8.4   8.2 / 9.2   9.1 / 9.9  12.0 / 10.4 16.6 / 12.4
+  //   256 x 128   4.6 / 8.1   5.8 / 9.2   7.1 / 10.4  8.3 / 11.5  9.0 / 13.1 11.7 / 13.7 15.4 / 18.8
+  //   512 x 64    4.3 / 6.8   5.4 / 7.5   6.4 / 8.0   7.4 / 8.7   8.2 / 9.4  10.3 / 10.6 14.2 / 13.8
+  //   256 x 256   5.3 / 11.4  6.8 / 13.3  8.4 / 15.8  9.9 / 18.4 10.8 / 20.9 14.3 / 21.4 19.4 / 20.3
+  // Beyond one workgroup per compute unit they queue: 608 x 128 (304) at 2000, 3000, 4096 rows 9.2, 15.1, 23.4 against 18.5, 19.1, 19.3
+  const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16), size = int64_t(K) * F;
+  const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 3000 : 4096));
+  if (n <= few && n * sb * sf <= 2560 * int64_t(kCus)) {
     wgrad_small_kernel<<<dim3(unsigned(sb), unsigned(sf)), kWave * kSmallWaves, 0, s>>>(a, dW, lddw);
     HGNN_LAUNCH_CHECK("wgrad_small_kernel");
     return HGNN_OK;

@@ -151,7 +151,16 @@ def many_windows(h):
             assert any("free_scan" in n for n in names) == (nrows > 409600), (nrows, names)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows]
+def weight_gradient(h):
+    """One launch for few rows, the more the larger dW is, while its workgroups fit the chip at once; two beyond."""
+    x = vp(h.data)
+    for K, F, most in ((16, 16, 2400), (64, 16, 2400), (64, 64, 1700), (128, 64, 1700), (128, 128, 3000), (256, 128, 4096), (256, 256, 2560)):
+        for n in (1, most, most + 1):
+            st, names = launches(h, lambda: h.lib.hgnn_linear_wgrad(i64(n), K, F, x, i64(K), x, i64(F), x, i64(F), x, ctypes.c_size_t(1 << 30), vp(A)))
+            assert st == 0 and len(names) == (1 if n <= most else 2), (n, K, F, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
