@@ -170,11 +170,21 @@ inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz
 // Rows of several pieces per wave in the follow-up kernels: one for each of the G lane groups (longer rows one after the other by the whole
 // wave), or one in all, whose lane groups then take a piece each and add across the wave.  The launch is a few latencies long and a wave of
 // G rows is a chain of them; us, G rows / one: 4000 rows x 64, saving attention 13.7 / 9.4, its backward 9.0 / 6.4; 800 rows x 42, SpMM
-// 5.3 / 4.7 (a GCN layer of 1.3 M non-zeros 89.3 / 84.8); 35 600 rows x 128 46 / 45.  Many rows of two or three pieces (long rows of
-// column blocks: some 50 000 of 114 M non-zeros x 64) are work for all lane groups: SpMM 7.5 / 20, saving attention 16 / 41.
+// 5.3 / 4.7 (a GCN layer of 1.3 M non-zeros 89.3 / 84.8).  Many rows of two or three pieces (long rows of
+// column blocks: some 50 000 of 114 M non-zeros x 64) are work for all lane groups: SpMM 7.5 / 20, saving attention 16 / 41.  Between them it
+// turns on the rows of more than eight pieces, which a wave of G rows takes one after the other.  Whole calls, us, one / G rows (weighted SpMM;
+// saving attention), rows of so many pieces on average:
+//   F = 64   4175 of 2.6, log-normal   31.6 / 32.4;  59.5 / 60.7      F = 16    8881 of 6.2, power law   49.8 / 56.0;  95.6 / 105.1
+//            6221 of 2.7, log-normal   33.0 / 33.4;  63.7 / 64.4               17041 of 7.2, power law   43.4 / 47.7;  57.3 / 63.1
+//            8881 of 6.2, power law    54.6 / 55.1; 112.2 / 114.5     F = 128   8881 of 6.2, power law   81.5 / 82.3; 166.0 / 166.1
+//            9728 of 3.1, log-normal   36.4 / 36.1;  72.1 / 71.8               16143 of 4.1, log-normal  77.5 / 76.1; 130.6 / 128.0
+//           17041 of 7.2, power law    58.1 / 57.0; 101.2 / 98.8               20927 of 6.4, log-normal  80.4 / 78.9; 107.6 / 105.1
+//           22472 of 8.0, log-normal  446.1 / 442.3; 468.6 / 462.6             35608 of 9.5, power law  1312.6 / 1314.7; 1615 / 1624
+//           21061 of 10, power law    288.0 / 288.2; 380.6 / 379.4
 constexpr int kFinishAlone = 65536;
 __host__ __device__ inline int finish_rows_per_wave(int n_split, int n_slots, int G) {
-  return n_split <= 8192 || (n_split <= kFinishAlone && n_slots / 6 >= n_split) ? 1 : G;
+  const int many = G >= 32 ? 6 : 9;  // pieces a row
+  return n_split <= 8192 || (n_split <= kFinishAlone && n_slots / many >= n_split) ? 1 : G;
 }
 
 // waves of work behind a view (G lane groups per wave)

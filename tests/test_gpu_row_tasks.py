@@ -308,16 +308,21 @@ def test_plain_spmm_with_a_smaller_workspace(hgnn, dev, F, what):
         compare(f"workspace of {n}", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)
 
 
-@pytest.mark.parametrize("V", [65536, 65537])
-def test_many_rows_of_several_pieces(hgnn, dev, V):
-    """Up to 65536 rows of several pieces take a wave each in the follow-up kernels, more of them a lane group; pieces of one non-zero."""
-    print(f"follow-up rows V={V}", flush=True)
+# up to 8192 rows of several pieces, and up to 65536 of nine on average (of six where a wave holds 32 rows or more), take a wave each in the
+# follow-up kernels, others a lane group: both sides of every line, the average by one piece; a piece is one non-zero
+@pytest.mark.parametrize("V,least,most,fewer,D", [(8192, 2, 6, 0, 8), (8193, 2, 6, 0, 8), (8192, 2, 6, 0, 32), (8193, 2, 6, 0, 32),
+                                                  (65536, 6, 14, 0, 8), (65537, 6, 14, 0, 8), (65536, 9, 14, 0, 32), (65537, 9, 14, 0, 32),
+                                                  (9000, 6, 6, 0, 8), (9000, 6, 6, 1, 8), (9000, 9, 9, 0, 32), (9000, 9, 9, 1, 32)])
+def test_many_rows_of_several_pieces(hgnn, dev, V, least, most, fewer, D):
+    print(f"follow-up rows V={V} pieces {least}..{most} less {fewer} D={D}", flush=True)
     r = np.random.default_rng(V)
-    deg = r.integers(2, 6, size=V)
-    deg[:12] = (8, 9, 10, 16, 17, 31, 33, 40, 64, 65, 66, 300)
+    deg = r.integers(least, most + 1, size=V)
+    if least < most:
+        deg[:12] = (8, 9, 10, 16, 17, 31, 33, 40, 64, 65, 66, 300)
+    deg[V // 2] -= fewer
     rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
     col = np.concatenate([np.sort(r.integers(0, V, size=d)) for d in deg]).astype(np.int32)
-    H, D = 2, 8
+    H = 2
     F = H * D
     X, dO = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
     w = f16(r.standard_normal((col.size, H)))
