@@ -221,7 +221,7 @@ void hgnn_release_cached_memory(void);
  * that miss the room of the pieces by 512 bytes or less).
  * Beyond 4 Mi non-zeros, where the table X is larger than the L2s together and F <= 512, the query's answer
  * also has room for rows of more than 256 non-zeros in pieces that end where column ranges do: a staged row
- * and 16 bytes for every 128 non-zeros in all, and 44 bytes for every 257 (31 M non-zeros x 64: 96 MB instead
+ * and 16 bytes for every 128 non-zeros in all, and 44 bytes for every 256 (31 M non-zeros x 64: 96 MB instead
  * of 57).  Where that pays (edge values behind a map; wide or large tables) the call takes them, if the graph
  * has no more such pieces.  With a smaller workspace, for instance the answer for ncols = 1, it does not.
  * workspace == NULL is allowed: every long row is then reduced by a single wavefront (correct,

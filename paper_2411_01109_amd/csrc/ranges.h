@@ -28,11 +28,19 @@ struct RangeLists {
   int* slots;  // [nwin] pieces of a window's rows, then the first of them
   int* long_rows;  // [nwin] long rows of a window, or nullptr (a plan has their number from its other counts)
   int nrows, nwin, piece, min_row, width;
-  bool by_row;  // where a row's cuts are: a place for every row, or for every min_row non-zeros (no two long rows share one)
-  __device__ __forceinline__ int* cuts_of(int row, int beg) const { return cuts + int64_t(by_row ? row : beg / min_row) * (kRanges - 1); }
+  int shift;  // where a row's cuts are: a place for every row (-1), or for every 2^shift <= min_row non-zeros (no two long rows share one)
+  __device__ __forceinline__ int* cuts_of(int row, int beg) const { return cuts + int64_t(shift < 0 ? row : beg >> shift) * (kRanges - 1); }
 };
 
-static int64_t range_cut_rows(int64_t nrows, int64_t nnz, int min_row) { return nrows < nnz / min_row + 1 ? nrows : nnz / min_row + 1; }
+static int range_cut_shift(int min_row) {
+  int s = 0;
+  while (min_row >> (s + 1)) ++s;
+  return s;
+}
+static int64_t range_cut_rows(int64_t nrows, int64_t nnz, int min_row) {
+  const int64_t places = (nnz >> range_cut_shift(min_row)) + 1;
+  return nrows < places ? nrows : places;
+}
 static size_t range_cut_bytes(int64_t nrows, int64_t nnz, int min_row) {
   return sizeof(int) * (kRanges - 1) * size_t(range_cut_rows(nrows, nnz, min_row));
 }
@@ -46,7 +54,7 @@ static RangeLists range_lists(const TaskSource& q, const int* col, int ncols, in
   a.piece = q.S < kRangePiece ? q.S : kRangePiece;
   a.min_row = q.range_min;
   a.width = int(ceil_div(ncols, kRanges));
-  a.by_row = range_cut_rows(q.nrows, q.nnz, q.range_min) == q.nrows;
+  a.shift = range_cut_rows(q.nrows, q.nnz, q.range_min) == q.nrows ? -1 : range_cut_shift(q.range_min);
   a.cuts = cuts;
   a.count = count;
   a.slots = slots;

@@ -132,11 +132,11 @@ def column_ranges(h):
 
 def room_for_column_ranges(h):
     """Beside the pieces of all rows the query counts at most a staged row and a list entry per 128 non-zeros, the cuts and an entry for every
-    257, and ten counts per 1024 rows; nothing for features that no call over pieces takes."""
+    256, and ten counts per 1024 rows; nothing for features that no call over pieces takes."""
     for nrows, nnz, f in ((1200001, 31000001, 64), (2400000, 62000000, 128), (600000, 14000000, 256), (20000000, 40000000, 8), (200000, 6000000, 128)):
         ld = (f + 7) // 8 * 8
         full, less = (h.lib.hgnn_spmm_workspace(nrows, n, i64(nnz), f) for n in (nrows, 1))
-        room = nnz // 128 * (4 * ld + 16) + (nnz // 257 + 1) * (28 + 16) + (nrows // 1024 + 1) * 48 + 4096
+        room = nnz // 128 * (4 * ld + 16) + (nnz // 256 + 1) * (28 + 16) + (nrows // 1024 + 1) * 48 + 4096
         assert 0 < full - less <= room, (nrows, nnz, f, full, less, room)
     assert h.lib.hgnn_spmm_workspace(1200001, 1200001, i64(31000001), 520) == h.lib.hgnn_spmm_workspace(1200001, 1, i64(31000001), 520)
 
