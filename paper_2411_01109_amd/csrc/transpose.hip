@@ -59,19 +59,62 @@ __global__ void coo_keys_kernel(CooWords w, int64_t nnz, uint64_t* __restrict__ 
   ids[k] = int(k);
 }
 
+// by a whole wave, 64 places looked at in each step: how many of n places come before the first where before() does not hold; every place is
+// looked at inside [0, n) whatever before() says
+template <class Before>
+__device__ __forceinline__ int64_t wave_partition(int64_t n, Before&& before) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int64_t lo = 0, hi = n;  // the answer is in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave, at = lo + lane * step;
+    const int held = __popcll(__ballot(at < hi && before(at)));
+    // of a sorted array those lanes are the first ones
+    if (held == 0) {
+      hi = lo;
+    } else {
+      const int64_t last = lo + (held - 1) * step;  // holds there
+      hi = last + step < hi ? last + step : hi;
+      lo = last + 1;
+    }
+  }
+  return lo;
+}
+
+// row_of_edge by a whole wave
+__device__ __forceinline__ int wave_row_of_edge(const int* __restrict__ rowptr, int nrows, int64_t k) {
+  return int(wave_partition(int64_t(nrows) + 1, [&](int64_t r) { return int64_t(rowptr[r]) <= k; })) - 1;
+}
+
 // Sorted words taken apart: the low `position_bits` to pos (may be null), the next `id_bits` to id, and offset[r] = number of words
 // whose leading `lead_bits` are < r, for r = 0 .. nlead.  The workgroup that holds the first word of a row writes that row's offset and
 // those of the empty rows before it, long stretches of them with all its threads.  Bound by memory: 17.2 us for 5.5 M words (5.1 TB/s).
+// A workgroup takes some 75 us for a stretch of a million (33 M vertices with all edges at one: 1.2 of 1.8 ms).  GAPS: windows of offsets that
+// are equal throughout are left to workgroups of their own, the first `gap_blocks`, one for each window; 1.3 us at 5.5 M words.
+constexpr int kGapWindow = 1024;
+template <bool GAPS>
 __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __restrict__ words, int64_t nnz, int position_bits, int id_bits,
-                                                            int lead_bits, int nlead, int* __restrict__ id, int* __restrict__ pos,
-                                                            int* __restrict__ offset) {
+                                                            int lead_bits, int nlead, int gap_blocks, int* __restrict__ id,
+                                                            int* __restrict__ pos, int* __restrict__ offset) {
   constexpr int kAlone = 16;
-  __shared__ int s_n, s_gap[kBlock + 1][3];
+  __shared__ int s_n, s_gap[(GAPS ? 2 : 1) * (kBlock + 1)][3];
+  auto lead_of = [&](uint64_t w) { return int(min(uint64_t(nlead), (w >> (position_bits + id_bits)) & ((uint64_t(1) << lead_bits) - 1))); };
+  if (GAPS && int(blockIdx.x) < gap_blocks) {
+    const int64_t a = int64_t(blockIdx.x) * kGapWindow, b = a + kGapWindow - 1 < nlead ? a + kGapWindow - 1 : nlead;
+    const int w = threadIdx.x / kWave;
+    if (w < 2) {
+      const int64_t n = wave_partition(nnz, [&](int64_t i) { return lead_of(words[i]) < (w == 0 ? a : b); });
+      if ((threadIdx.x & (kWave - 1)) == 0) s_gap[0][w] = int(n);
+    }
+    __syncthreads();
+    const int v = s_gap[0][0];
+    if (v == s_gap[0][1])
+      for (int64_t r = a + threadIdx.x; r <= b; r += kBlock) offset[r] = v;
+    return;
+  }
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
-  const int64_t k = blockIdx.x * int64_t(kBlock) + threadIdx.x;
-  auto lead_of = [&](uint64_t w) { return int(min(uint64_t(nlead), (w >> (position_bits + id_bits)) & ((uint64_t(1) << lead_bits) - 1))); };
-  auto fill = [&](int from, int to, int64_t v) {  // offset[from .. to] = v
+  const int64_t k = (int64_t(blockIdx.x) - (GAPS ? gap_blocks : 0)) * kBlock + threadIdx.x;
+  auto fill_part = [&](int from, int to, int64_t v) {
     if (to - from < kAlone) {
       for (int r = from; r <= to; ++r) offset[r] = int(v);
     } else {
@@ -80,6 +123,18 @@ __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __r
       s_gap[i][1] = to;
       s_gap[i][2] = int(v);
     }
+  };
+  auto fill = [&](int from, int to, int64_t v) {  // offset[from .. to] = v
+    if (GAPS) {  // but for the windows inside: [a, b) are those (the last one may be shorter)
+      const int64_t a = (int64_t(from) + kGapWindow - 1) / kGapWindow * kGapWindow;
+      const int64_t b = to == nlead ? int64_t(nlead) + 1 : (int64_t(to) + 1) / kGapWindow * kGapWindow;
+      if (a < b) {
+        if (from < a) fill_part(from, int(a) - 1, v);
+        if (b <= to) fill_part(int(b), to, v);
+        return;
+      }
+    }
+    fill_part(from, to, v);
   };
   if (k < nnz) {
     const uint64_t w = words[k];
@@ -94,31 +149,22 @@ __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __r
     for (int r = s_gap[i][0] + int(threadIdx.x); r <= s_gap[i][1]; r += kBlock) offset[r] = s_gap[i][2];
 }
 
+constexpr int kLongGap = 65536;  // offsets
+static void launch_split_words(const uint64_t* words, int64_t nnz, int position_bits, int id_bits, int lead_bits, int nlead, int* id, int* pos,
+                               int* offset, hipStream_t s) {
+  // (sixteen words or more for every offset: the sort takes ten times as long as the longest stretch there can be)
+  const int64_t edges = ceil_div(nnz, kBlock), gaps = nlead > kLongGap && nnz < 16 * int64_t(nlead) ? ceil_div(int64_t(nlead) + 1, kGapWindow) : 0;
+  const dim3 grid(unsigned(edges + gaps));
+  if (gaps) split_words_kernel<true><<<grid, kBlock, 0, s>>>(words, nnz, position_bits, id_bits, lead_bits, nlead, int(gaps), id, pos, offset);
+  else split_words_kernel<false><<<grid, kBlock, 0, s>>>(words, nnz, position_bits, id_bits, lead_bits, nlead, 0, id, pos, offset);
+}
+
 // The row of every non-zero, handed to put(k, row): a workgroup takes kExpand consecutive positions, its rows mark the slot
 // of their first non-zero in LDS and a running maximum spreads the ids (a search of the offset array per non-zero took
 // 196 us at 5.5 M non-zeros).  A graph may come here before anything has looked at its offset array: whatever that holds, reads
 // stay inside its nrows + 1 entries and marks inside the tile (the rows are then wrong, as the array is).
 constexpr int kExpandPerThread = 8;
 constexpr int kExpand = kBlock * kExpandPerThread;
-
-// row_of_edge by a whole wave, 64 places looked at in each step; every entry is read inside the array whatever it holds
-__device__ __forceinline__ int wave_row_of_edge(const int* __restrict__ rowptr, int nrows, int64_t k) {
-  const int lane = threadIdx.x & (kWave - 1);
-  int64_t lo = 0, hi = int64_t(nrows) + 1;  // the first entry above k is in [lo, hi]
-  while (lo < hi) {
-    const int64_t step = (hi - lo + kWave - 1) / kWave, at = lo + lane * step;
-    const int not_above = __popcll(__ballot(at < hi && int64_t(rowptr[at]) <= k));
-    // in an ascending array those lanes are the first ones
-    if (not_above == 0) {
-      hi = lo;
-    } else {
-      const int64_t last = lo + (not_above - 1) * step;  // not above
-      hi = last + step < hi ? last + step : hi;
-      lo = last + 1;
-    }
-  }
-  return int(lo) - 1;
-}
 
 // s_row[i] = row of position e0 + i, i < n <= 8 THREADS; the workgroup has been waited for at the end
 template <int THREADS>
@@ -264,7 +310,7 @@ extern "C" hgnn_status hgnn_transpose(const hgnn_csr* g, int32_t* rowptr_T, int3
       const int first = row_bits + pos_bits;
       const uint64_t* words = sort_words(TransposeWords{g->rowptr, g->col, g->nrows, row_bits, pos_bits}, E, first, first + col_bits,
                                          buf[0].as<uint64_t>(), buf[1].as<uint64_t>(), tmp.p, s);
-      split_words_kernel<<<per_edge, kBlock, 0, s>>>(words, E, pos_bits, row_bits, col_bits, g->ncols, col_T, eid_T, rowptr_T);
+      launch_split_words(words, E, pos_bits, row_bits, col_bits, g->ncols, col_T, eid_T, rowptr_T, s);
       e = hipGetLastError();
     }
   } else {
@@ -342,7 +388,7 @@ extern "C" hgnn_status hgnn_coo_to_csr(int32_t nrows, int32_t ncols, int64_t nnz
       words = keys.current();
     }
     if (e == hipSuccess) {
-      split_words_kernel<<<per_edge, kBlock, 0, s>>>(words, nnz, in_key, col_bits, row_bits, nrows, col_out, packed ? eid : nullptr, rowptr);
+      launch_split_words(words, nnz, in_key, col_bits, row_bits, nrows, col_out, packed ? eid : nullptr, rowptr, s);
       e = hipGetLastError();
     }
   }

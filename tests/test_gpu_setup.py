@@ -1,6 +1,7 @@
 """Set-up calls at the edges of their dispatch: edge lists and transposes whose fields do and do not fit one 64-bit sort key,
 row lists of every kind, graphs rejected by each rule, and the memory that set-up calls keep for one another."""
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -53,6 +54,35 @@ def test_sort_tiles(hgnn, dev, V, E):
     row[row > V * 3 // 4] = V - 1
     col[: E // 8] = col[0]
     check_lists(hgnn, dev, V, row, col)
+
+
+# long stretches of empty rows and columns: by the workgroup that finds them, or beyond 65536 with few words to each in windows of 1024
+@pytest.mark.parametrize("V", [65536, 65537, 66559, 66560, 66561, 5000011])
+def test_long_gaps(hgnn, dev, V):
+    print(f"setup gaps V={V}", flush=True)
+    r = np.random.default_rng(V)
+    some = [0, 1, 1022, 1023, 1024, 1025, 2047, 2048, 3071, 5000, 40959, V - 1025, V - 1024, V - 2, V - 1]
+    for ids in ([V // 2], [0], [V - 1], [1023], [1024], some, some[1:-1]):
+        row = np.array(ids, dtype=np.int32)[r.integers(0, len(ids), 3000)]
+        check_lists(hgnn, dev, V, row, r.permutation(row))
+
+
+def test_time_of_a_long_gap(hgnn, dev):
+    """All edges at one vertex of many: the offsets of the others are written by many workgroups (one took six times as long as a uniform list)."""
+    V, E = 1 << 25, 4000000
+    best = {}
+    for what in ("uniform", "one"):
+        r = np.random.default_rng(1)
+        row, col = (up(r.integers(0, V, E).astype(np.int32), dev) for _ in range(2))
+        if what == "one":
+            row.fill_(V // 2)
+        best[what] = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            hgnn.hgnn_coo_to_csr(row, col, V, V, want_eid=False)
+            best[what] = min(best[what], time.perf_counter() - t)
+    assert best["one"] <= 3 * best["uniform"], best
 
 
 @pytest.mark.parametrize("E", [1, 8193, 700000])
