@@ -18,6 +18,7 @@ struct SortPass {
   int ntiles;
   uint32_t* counts;  // [ntiles][kSortBins] items of a tile in every bin, then items of the earlier tiles there
   uint32_t* totals;  // [kSortBins]
+  uint32_t* shares;  // [kScanShares][kSortBins] items of a share of the tiles in every bin
   __device__ __forceinline__ int digit(uint64_t w) const { return int(uint32_t(w >> shift) & ((1u << bits) - 1u)); }
 };
 
@@ -59,22 +60,41 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(SortPass p, So
   }
 }
 
-// exclusive scan of the counts of every bin over the tiles, in place: a workgroup takes 16 bins, its 64 slices a share of the tiles each
+// Exclusive scan of the counts of every bin over the tiles, in place: a workgroup takes 16 bins, its 64 slices a share of the tiles each.
+// Beyond kScanTiles tiles (25 M words) the tiles are scanned in kScanShares shares by workgroups of their own, after a launch that adds each of
+// them up.  us, in one / add + scan: 9 M words 7 / 5 + 7, 20 M 14 / 5 + 9, 114 M 108 / 12 + 27.
 constexpr int kScanBins = 16, kScanSlices = kSortThreads / kScanBins;
+constexpr int kScanTiles = 3072, kScanShares = 16;
 
+enum ScanPart { kScanAll, kScanAdd, kScanShare };  // everything, the sums of the shares, the shares behind their sums
+template <ScanPart PART>
 __global__ __launch_bounds__(kSortThreads) static void sort_scan_kernel(SortPass p) {
   __shared__ uint32_t sums[kScanSlices][kScanBins];
-  const int x = threadIdx.x % kScanBins, y = threadIdx.x / kScanBins;
-  const int per = (p.ntiles + kScanSlices - 1) / kScanSlices, t0 = y * per, t1 = min(t0 + per, p.ntiles);
-  uint32_t* const c = p.counts + blockIdx.x * kScanBins + x;
+  const int x = threadIdx.x % kScanBins, y = threadIdx.x / kScanBins, bin = blockIdx.x * kScanBins + x;
+  int first = 0, end = p.ntiles;
+  if (PART != kScanAll) {
+    const int share = (p.ntiles + kScanShares - 1) / kScanShares;
+    first = min(int(blockIdx.y) * share, p.ntiles);
+    end = min(first + share, p.ntiles);
+  }
+  const int per = (end - first + kScanSlices - 1) / kScanSlices, t0 = first + y * per, t1 = min(t0 + per, end);
+  uint32_t* const c = p.counts + bin;
   uint32_t s = 0;
 #pragma unroll 8
   for (int t = t0; t < t1; ++t) s += c[int64_t(t) * kSortBins];
   sums[y][x] = s;
   __syncthreads();
   uint32_t before = 0;
+  if (PART == kScanAdd) {
+    if (y > 0) return;
+    for (int i = 0; i < kScanSlices; ++i) before += sums[i][x];
+    p.shares[blockIdx.y * kSortBins + bin] = before;
+    return;
+  }
+  if (PART == kScanShare)
+    for (int i = 0; i < int(blockIdx.y); ++i) before += p.shares[i * kSortBins + bin];
   for (int i = 0; i < y; ++i) before += sums[i][x];
-  if (y == kScanSlices - 1) p.totals[blockIdx.x * kScanBins + x] = before + s;
+  if (y == kScanSlices - 1 && (PART == kScanAll || blockIdx.y == kScanShares - 1)) p.totals[bin] = before + s;
 #pragma unroll 8
   for (int t = t0; t < t1; ++t) {
     const uint32_t v = c[int64_t(t) * kSortBins];
@@ -199,7 +219,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   }
 }
 
-inline size_t sort_scratch_bytes(int64_t n) { return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortTile)) + 1); }
+inline size_t sort_scratch_bytes(int64_t n) { return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortTile)) + 1 + kScanShares); }
 
 // Sorts n >= 1 words by their bits [first, last).  The words come from src; the sorted ones are in the returned one of the two buffers.
 template <class Source>
@@ -208,7 +228,8 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
   p.n = n;
   p.ntiles = int(ceil_div(n, kSortTile));
   p.totals = static_cast<uint32_t*>(scratch);
-  p.counts = p.totals + kSortBins;
+  p.shares = p.totals + kSortBins;
+  p.counts = p.shares + kScanShares * kSortBins;
   const int bits = last - first, npass = (bits + kSortBits - 1) / kSortBits;
   const dim3 grid{unsigned(p.ntiles)};
   uint64_t *in = buf1, *out = buf0;
@@ -217,7 +238,15 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
     p.bits = (last - p.shift + npass - i - 1) / (npass - i);
     if (i == 0) sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, src);
     else sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in});
-    if (p.ntiles > kFewTiles) sort_scan_kernel<<<kSortBins / kScanBins, kSortThreads, 0, s>>>(p);
+    if (p.ntiles > kFewTiles) {
+      constexpr int kGroups = kSortBins / kScanBins;
+      if (p.ntiles <= kScanTiles) {
+        sort_scan_kernel<kScanAll><<<kGroups, kSortThreads, 0, s>>>(p);
+      } else {
+        sort_scan_kernel<kScanAdd><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
+        sort_scan_kernel<kScanShare><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
+      }
+    }
     if (i == 0) sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, src, out);
     else sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in}, out);
     p.shift += p.bits;

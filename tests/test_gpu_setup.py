@@ -56,6 +56,24 @@ def test_sort_tiles(hgnn, dev, V, E):
     check_lists(hgnn, dev, V, row, col)
 
 
+@pytest.mark.parametrize("E", [3072 * 8192, 3072 * 8192 + 1])
+def test_many_tiles(hgnn, dev, E):
+    """The counts of up to 3072 tiles are scanned in one, of more in shares."""
+    V = 100003
+    print(f"setup E={E}", flush=True)
+    gen = torch.Generator(device=dev).manual_seed(E)
+    row, col = (torch.randint(0, V, (E,), generator=gen, device=dev, dtype=torch.int32) for _ in range(2))
+    row[E // 2:E // 2 + E // 5] = 3
+    g, eid = hgnn.hgnn_coo_to_csr(row, col, V, V)
+    key, order = torch.sort(row.long() * V + col, stable=True)
+    assert torch.equal(eid.long(), order) and torch.equal(g.col.long(), key % V)
+    bounds = torch.arange(V + 1, device=dev)
+    assert torch.equal(g.rowptr.long(), torch.searchsorted(key // V, bounds))
+    gt = hgnn.hgnn_transpose(g)
+    c, t = torch.sort(g.col.long(), stable=True)
+    assert torch.equal(gt.eid.long(), t) and torch.equal(gt.col.long(), (key // V)[t]) and torch.equal(gt.rowptr.long(), torch.searchsorted(c, bounds))
+
+
 # long stretches of empty rows and columns: by the workgroup that finds them, or beyond 65536 with few words to each in windows of 1024
 @pytest.mark.parametrize("V", [65536, 65537, 66559, 66560, 66561, 5000011])
 def test_long_gaps(hgnn, dev, V):
