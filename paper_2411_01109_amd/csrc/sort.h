@@ -1,7 +1,9 @@
-// Stable radix sort of 64-bit words for the set-up calls: digits of up to nine bits, two or three launches a pass (digits of every tile
+// Stable sort of 64-bit words for the set-up calls: by radix, digits of up to nine bits, two or three launches a pass (digits of every tile
 // counted, counts scanned over the tiles where there are many, tiles sorted in LDS and written in runs).  The first pass forms its words from whatever the
 // caller has, so no array of keys is written and read beforehand.  No workgroup waits for another one.
 #pragma once
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -120,8 +122,31 @@ __device__ __forceinline__ uint32_t sort_bin_scan(uint32_t v, uint32_t* s_wave) 
   return before + incl - v;
 }
 
-// A tile: every wave ranks its 512 consecutive items by digit (lanes of equal digit find each other by ballots, so the order of equal
-// digits is kept), the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
+// Ranks of a wave's 64 PER consecutive items among its items of the same digit: lanes of equal digit find each other by ballots, so the order of
+// equal digits is kept.  hist: the wave's counts of the digits, zero beforehand.
+template <int PER>
+__device__ __forceinline__ void sort_wave_ranks(const SortPass& p, const uint64_t (&w)[PER], uint16_t* hist, uint32_t (&rank)[PER]) {
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int d = p.digit(w[j]);
+    uint32_t lo = ~0u, hi = ~0u;  // lanes whose digit agrees so far
+#pragma unroll
+    for (int b = 0; b < kSortBits; ++b) {
+      const uint32_t bit = uint32_t(__builtin_amdgcn_sbfe(d, b, 1));  // 0 or all ones
+      const uint64_t ones = __ballot(bit != 0);
+      lo &= ~(uint32_t(ones) ^ bit);
+      hi &= ~(uint32_t(ones >> 32) ^ bit);
+    }
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    const uint32_t before = hist[d];
+    rank[j] = before + below;
+    wave_sync();
+    if (below == 0) hist[d] = uint16_t(before + __popc(lo) + __popc(hi));
+    wave_sync();
+  }
+}
+
+// A tile: every wave ranks its 512 consecutive items by digit, the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
 // items of the tile are a run of 16 on average.  5.5 M words: 27.5 us (3.2 TB/s of reads and writes; half of it vector instructions of
 // the ranks), a pass 44 with its count and scan, where a library pass with look-back and its two fills took 52; the words that the first
 // pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 221 us, transpose 180 -> 127; 50 000 words,
@@ -166,24 +191,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   for (int i = threadIdx.x; i < kSortWaves * kSortBins / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(lds)[i] = 0;
   __syncthreads();
   uint32_t rank[kSortPer];
-#pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int d = p.digit(w[j]);
-    uint32_t lo = ~0u, hi = ~0u;  // lanes whose digit agrees so far
-#pragma unroll
-    for (int b = 0; b < kSortBits; ++b) {
-      const uint32_t bit = uint32_t(__builtin_amdgcn_sbfe(d, b, 1));  // 0 or all ones
-      const uint64_t ones = __ballot(bit != 0);
-      lo &= ~(uint32_t(ones) ^ bit);
-      hi &= ~(uint32_t(ones >> 32) ^ bit);
-    }
-    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-    const uint32_t before = hist[wave][d];
-    rank[j] = before + below;
-    wave_sync();
-    if (below == 0) hist[wave][d] = uint16_t(before + __popc(lo) + __popc(hi));
-    wave_sync();
-  }
+  sort_wave_ranks(p, w, hist[wave], rank);
   __syncthreads();
   uint32_t here = 0;
   if (bin < kSortBins) {
@@ -219,6 +227,100 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   }
 }
 
+// Up to kFewMerged tiles (one, where one pass does): every tile is sorted by all its digits in LDS, in one launch, and the words of several
+// tiles find their places by searches in the others.  A pass of two launches for every nine bits is mostly latency there.  List to CSR, us,
+// passes / this: 1000 words over 100 vertices 40 / 24, over 100 000 91 / 32; 8192 over 5000 59 / 41; 33 000 over 30 000 85 / 54; 65 536 over
+// 100 49 / 48, over 5000 65 / 55, over 100 000 85 / 61; in 16 tiles 131 072 over 100 51 / 83, over 100 000 87 / 96.  Transpose (one pass up to
+// 512 vertices): 8192 over 100 32 / 28, 16 384 33 / 35; 65 536 over 5000 50 / 48.
+constexpr int kFewMerged = 8;
+
+// PER: items of a thread; the counts, and the rows that a source expands, take 32 KB of LDS in any case
+template <class Source, int PER>
+__global__ __launch_bounds__(kSortThreads) void sort_tile_kernel(SortPass p, int last, Source src, uint64_t* __restrict__ out) {
+  __shared__ __align__(16) unsigned char lds[(PER > 4 ? PER : 4) * kSortThreads * sizeof(uint64_t)];
+  __shared__ uint32_t s_at[kSortBins], s_wave[kSortWaves];
+  uint16_t (*const hist)[kSortBins] = reinterpret_cast<uint16_t (*)[kSortBins]>(lds);
+  uint64_t* const item = reinterpret_cast<uint64_t*>(lds);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, bin = threadIdx.x;
+  const int64_t first = int64_t(blockIdx.x) * (PER * kSortThreads);
+  const int n = int(p.n - first < PER * kSortThreads ? p.n - first : PER * kSortThreads);
+  src.prepare(first, n, reinterpret_cast<int*>(lds));
+  uint64_t w[PER];
+  const int mine = wave * (kWave * PER) + lane;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int i = mine + j * kWave;
+    w[j] = ~uint64_t(0);  // behind all items in every pass
+    if (i < n) w[j] = src.load(first + i, i, reinterpret_cast<const int*>(lds));
+  }
+  for (; p.shift < last; p.shift += p.bits) {
+    p.bits = min(p.bits, last - p.shift);
+    __syncthreads();  // the words have been read
+    for (int i = threadIdx.x; i < kSortWaves * kSortBins / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(lds)[i] = 0;
+    __syncthreads();
+    uint32_t rank[PER];
+    sort_wave_ranks(p, w, hist[wave], rank);
+    __syncthreads();
+    uint32_t here = 0;
+    if (bin < kSortBins) {
+#pragma unroll
+      for (int v = 0; v < kSortWaves; ++v) {
+        const uint32_t c = hist[v][bin];
+        hist[v][bin] = uint16_t(here);
+        here += c;
+      }
+    }
+    const uint32_t at = sort_bin_scan(here, s_wave);
+    if (bin < kSortBins) s_at[bin] = at;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int d = p.digit(w[j]);
+      rank[j] += s_at[d] + hist[wave][d];
+    }
+    __syncthreads();  // the items take the place of the counts
+#pragma unroll
+    for (int j = 0; j < PER; ++j) item[rank[j]] = w[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) w[j] = item[mine + j * kWave];
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int i = mine + j * kWave;
+    if (i < n) out[first + i] = w[j];
+  }
+}
+
+// Words of sorted tiles in their places: a word's own, and how many words of each of the other tiles are before it, LANES lanes to a word.
+// Equal words of earlier tiles are before it.  Places are inside the array whatever it holds.
+template <int LANES>
+__global__ __launch_bounds__(kBlock) void sort_merge_kernel(SortPass p, int last, const uint64_t* __restrict__ in, uint64_t* __restrict__ out) {
+  const int64_t i = (blockIdx.x * int64_t(kBlock) + threadIdx.x) / LANES;
+  const int u = threadIdx.x % LANES, t = int(i / kSortTile);
+  if (i >= p.n) return;  // (all lanes of a word)
+  auto key = [&](uint64_t w) { return (w << (64 - last)) >> (64 - last + p.shift); };
+  const uint64_t w = in[i], k = key(w);
+  int place = 0;
+  if (u == t) {
+    place = int(i) - t * kSortTile;
+  } else if (u < p.ntiles) {
+    const uint64_t* const v = in + int64_t(u) * kSortTile;
+    const int n = int(p.n - int64_t(u) * kSortTile < kSortTile ? p.n - int64_t(u) * kSortTile : kSortTile);
+#pragma unroll
+    for (int step = kSortTile; step > 0; step >>= 1) {
+      const int at = place + step;
+      if (at <= n) {
+        const uint64_t o = key(v[at - 1]);
+        if (o < k || (o == k && u < t)) place = at;
+      }
+    }
+  }
+#pragma unroll
+  for (int d = 1; d < LANES; d <<= 1) place += __shfl_xor(place, d);
+  if (u == 0) out[place] = w;
+}
+
 inline size_t sort_scratch_bytes(int64_t n) { return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortTile)) + 1 + kScanShares); }
 
 // Sorts n >= 1 words by their bits [first, last).  The words come from src; the sorted ones are in the returned one of the two buffers.
@@ -234,6 +336,20 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
   const dim3 grid{unsigned(p.ntiles)};
   uint64_t *in = buf1, *out = buf0;
   p.shift = first;
+  if (p.ntiles <= (npass > 1 ? kFewMerged : 1)) {
+    p.bits = (bits + npass - 1) / npass;
+    if (n <= 2 * kSortThreads) sort_tile_kernel<Source, 2><<<grid, kSortThreads, 0, s>>>(p, last, src, buf0);
+    else sort_tile_kernel<Source, kSortPer><<<grid, kSortThreads, 0, s>>>(p, last, src, buf0);
+    if (p.ntiles == 1) return buf0;
+    auto merge = [&](auto lanes) {
+      constexpr int L = decltype(lanes)::value;
+      sort_merge_kernel<L><<<dim3(unsigned(ceil_div(n * L, kBlock))), kBlock, 0, s>>>(p, last, buf0, buf1);
+    };
+    if (p.ntiles <= 2) merge(std::integral_constant<int, 2>());
+    else if (p.ntiles <= 4) merge(std::integral_constant<int, 4>());
+    else merge(std::integral_constant<int, kFewMerged>());
+    return buf1;
+  }
   for (int i = 0; i < npass; ++i) {
     p.bits = (last - p.shift + npass - i - 1) / (npass - i);
     if (i == 0) sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, src);

@@ -74,6 +74,19 @@ def test_many_tiles(hgnn, dev, E):
     assert torch.equal(gt.eid.long(), t) and torch.equal(gt.col.long(), (key // V)[t]) and torch.equal(gt.rowptr.long(), torch.searchsorted(c, bounds))
 
 
+# up to 2048 words in one launch, up to 8192 in another form of it, up to eight tiles of those merged where a pass is not enough
+@pytest.mark.parametrize("E", [1, 63, 1025, 2047, 2048, 2049, 8191, 8193, 16384, 16385, 32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("V", [1, 300, 513, 70000, 1 << 20])
+def test_sort_few_words(hgnn, dev, V, E):
+    print(f"setup few words V={V} E={E}", flush=True)
+    r = np.random.default_rng(V + E)
+    row, col = (r.integers(0, V, E).astype(np.int32) for _ in range(2))
+    row[E // 2:E // 2 + E // 5] = V - 1
+    col[: E // 8] = col[0]
+    row[E // 3:E // 3 + 9], col[E // 3:E // 3 + 9] = V // 2, V // 3  # one edge several times
+    check_lists(hgnn, dev, V, row, col)
+
+
 # long stretches of empty rows and columns: by the workgroup that finds them, or beyond 65536 with few words to each in windows of 1024
 @pytest.mark.parametrize("V", [65536, 65537, 66559, 66560, 66561, 5000011])
 def test_long_gaps(hgnn, dev, V):
