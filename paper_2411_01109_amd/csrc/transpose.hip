@@ -88,32 +88,61 @@ __device__ __forceinline__ int wave_row_of_edge(const int* __restrict__ rowptr, 
 // Sorted words taken apart: the low `position_bits` to pos (may be null), the next `id_bits` to id, and offset[r] = number of words
 // whose leading `lead_bits` are < r, for r = 0 .. nlead.  The workgroup that holds the first word of a row writes that row's offset and
 // those of the empty rows before it, long stretches of them with all its threads.  Bound by memory: 17.2 us for 5.5 M words (5.1 TB/s).
-// A workgroup takes some 75 us for a stretch of a million (33 M vertices with all edges at one: 1.2 of 1.8 ms).  GAPS: windows of offsets that
-// are equal throughout are left to workgroups of their own, the first `gap_blocks`, one for each window; 1.3 us at 5.5 M words.
-constexpr int kGapWindow = 1024;
-template <bool GAPS>
+// FORM kSplitGaps: a workgroup takes some 75 us for a stretch of a million (33 M vertices with all edges at one: 1.2 of 1.8 ms), so windows of
+// kSplitWindow offsets that are equal throughout are left to workgroups of their own, the first `windows`; 1.3 us at 5.5 M words.
+// kSplitSearch: those workgroups write all offsets, by searches among the words of those rows.  With few words most stretches are long enough
+// to be written one after the other: 1000 words over 100 000 rows 70 / 47 us a list, 131 072 over 300 000 103 / 107.
+enum SplitForm { kSplitFill, kSplitGaps, kSplitSearch };
+constexpr int kSplitWindow = 1024, kStagedWords = 4096;
+template <SplitForm FORM>
 __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __restrict__ words, int64_t nnz, int position_bits, int id_bits,
-                                                            int lead_bits, int nlead, int gap_blocks, int* __restrict__ id,
-                                                            int* __restrict__ pos, int* __restrict__ offset) {
+                                                            int lead_bits, int nlead, int windows, int* __restrict__ id, int* __restrict__ pos,
+                                                            int* __restrict__ offset) {
   constexpr int kAlone = 16;
-  __shared__ int s_n, s_gap[(GAPS ? 2 : 1) * (kBlock + 1)][3];
+  __shared__ int s_n, s_gap[(FORM == kSplitGaps ? 2 : 1) * (kBlock + 1)][3];
   auto lead_of = [&](uint64_t w) { return int(min(uint64_t(nlead), (w >> (position_bits + id_bits)) & ((uint64_t(1) << lead_bits) - 1))); };
-  if (GAPS && int(blockIdx.x) < gap_blocks) {
-    const int64_t a = int64_t(blockIdx.x) * kGapWindow, b = a + kGapWindow - 1 < nlead ? a + kGapWindow - 1 : nlead;
+  if (FORM != kSplitFill && int(blockIdx.x) < windows) {
+    const int64_t a = int64_t(blockIdx.x) * kSplitWindow, b = a + kSplitWindow - 1 < nlead ? a + kSplitWindow - 1 : nlead;
     const int w = threadIdx.x / kWave;
     if (w < 2) {
       const int64_t n = wave_partition(nnz, [&](int64_t i) { return lead_of(words[i]) < (w == 0 ? a : b); });
       if ((threadIdx.x & (kWave - 1)) == 0) s_gap[0][w] = int(n);
     }
     __syncthreads();
-    const int v = s_gap[0][0];
-    if (v == s_gap[0][1])
-      for (int64_t r = a + threadIdx.x; r <= b; r += kBlock) offset[r] = v;
+    const int from = s_gap[0][0], n = s_gap[0][1] - from;
+    if (FORM == kSplitGaps) {
+      if (n == 0)
+        for (int64_t r = a + threadIdx.x; r <= b; r += kBlock) offset[r] = from;
+      return;
+    }
+    __shared__ int s_lead[FORM == kSplitSearch ? kStagedWords : 1];
+    if (n <= kStagedWords) {
+      for (int i = threadIdx.x; i < n; i += kBlock) s_lead[i] = lead_of(words[from + i]);
+      __syncthreads();
+    }
+    constexpr int kEach = kSplitWindow / kBlock;
+    int at[kEach] = {};  // words below, searched for side by side
+    for (int step = n > 0 ? 1 << (31 - __clz(n)) : 0; step > 0; step >>= 1)
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {
+        const int i = at[j] + step;
+        if (i <= n) {
+          const int lead = n <= kStagedWords ? s_lead[i - 1] : lead_of(words[from + i - 1]);
+          if (lead < a + j * kBlock + int(threadIdx.x)) at[j] = i;
+        }
+      }
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int64_t r = a + j * kBlock + threadIdx.x;
+      if (r <= b) offset[r] = from + at[j];
+    }
     return;
   }
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
-  const int64_t k = (int64_t(blockIdx.x) - (GAPS ? gap_blocks : 0)) * kBlock + threadIdx.x;
+  if (FORM != kSplitSearch) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+  }
+  const int64_t k = (int64_t(blockIdx.x) - (FORM != kSplitFill ? windows : 0)) * kBlock + threadIdx.x;
   auto fill_part = [&](int from, int to, int64_t v) {
     if (to - from < kAlone) {
       for (int r = from; r <= to; ++r) offset[r] = int(v);
@@ -125,9 +154,9 @@ __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __r
     }
   };
   auto fill = [&](int from, int to, int64_t v) {  // offset[from .. to] = v
-    if (GAPS) {  // but for the windows inside: [a, b) are those (the last one may be shorter)
-      const int64_t a = (int64_t(from) + kGapWindow - 1) / kGapWindow * kGapWindow;
-      const int64_t b = to == nlead ? int64_t(nlead) + 1 : (int64_t(to) + 1) / kGapWindow * kGapWindow;
+    if (FORM == kSplitGaps) {  // but for the windows inside: [a, b) are those (the last one may be shorter)
+      const int64_t a = (int64_t(from) + kSplitWindow - 1) / kSplitWindow * kSplitWindow;
+      const int64_t b = to == nlead ? int64_t(nlead) + 1 : (int64_t(to) + 1) / kSplitWindow * kSplitWindow;
       if (a < b) {
         if (from < a) fill_part(from, int(a) - 1, v);
         if (b <= to) fill_part(int(b), to, v);
@@ -140,23 +169,25 @@ __global__ __launch_bounds__(kBlock) void split_words_kernel(const uint64_t* __r
     const uint64_t w = words[k];
     id[k] = int(uint32_t(w >> position_bits) & ((uint32_t(1) << id_bits) - 1u));
     if (pos) pos[k] = int(uint32_t(w) & ((uint32_t(1) << position_bits) - 1u));
-    const int r = lead_of(w), q = k > 0 ? lead_of(words[k - 1]) : -1;
-    if (r > q) fill(q + 1, r, k);
-    if (k == nnz - 1 && r < nlead) fill(r + 1, nlead, nnz);
+    if (FORM != kSplitSearch) {
+      const int r = lead_of(w), q = k > 0 ? lead_of(words[k - 1]) : -1;
+      if (r > q) fill(q + 1, r, k);
+      if (k == nnz - 1 && r < nlead) fill(r + 1, nlead, nnz);
+    }
   }
+  if (FORM == kSplitSearch) return;
   __syncthreads();
   for (int i = 0; i < s_n; ++i)
     for (int r = s_gap[i][0] + int(threadIdx.x); r <= s_gap[i][1]; r += kBlock) offset[r] = s_gap[i][2];
 }
 
-constexpr int kLongGap = 65536;  // offsets
 static void launch_split_words(const uint64_t* words, int64_t nnz, int position_bits, int id_bits, int lead_bits, int nlead, int* id, int* pos,
                                int* offset, hipStream_t s) {
-  // (sixteen words or more for every offset: the sort takes ten times as long as the longest stretch there can be)
-  const int64_t edges = ceil_div(nnz, kBlock), gaps = nlead > kLongGap && nnz < 16 * int64_t(nlead) ? ceil_div(int64_t(nlead) + 1, kGapWindow) : 0;
-  const dim3 grid(unsigned(edges + gaps));
-  if (gaps) split_words_kernel<true><<<grid, kBlock, 0, s>>>(words, nnz, position_bits, id_bits, lead_bits, nlead, int(gaps), id, pos, offset);
-  else split_words_kernel<false><<<grid, kBlock, 0, s>>>(words, nnz, position_bits, id_bits, lead_bits, nlead, 0, id, pos, offset);
+  // (with sixteen words for every offset the sort takes ten times as long as the longest stretch that there can be)
+  const SplitForm form = nnz < nlead / 8 ? kSplitSearch : (nlead > 65536 && nnz < 16 * int64_t(nlead) ? kSplitGaps : kSplitFill);
+  const int64_t edges = ceil_div(nnz, kBlock), windows = form == kSplitFill ? 0 : ceil_div(int64_t(nlead) + 1, kSplitWindow);
+  const auto kernel = form == kSplitFill ? split_words_kernel<kSplitFill> : (form == kSplitGaps ? split_words_kernel<kSplitGaps> : split_words_kernel<kSplitSearch>);
+  kernel<<<dim3(unsigned(edges + windows)), kBlock, 0, s>>>(words, nnz, position_bits, id_bits, lead_bits, nlead, int(windows), id, pos, offset);
 }
 
 // The row of every non-zero, handed to put(k, row): a workgroup takes kExpand consecutive positions, its rows mark the slot
@@ -177,6 +208,19 @@ __device__ __forceinline__ void expand_tile(const int* __restrict__ rowptr, int 
   for (int i = threadIdx.x; i < THREADS * kExpandPerThread; i += THREADS) s_row[i] = -1;
   __syncthreads();
   const int lo = max(s_lim[0], 0), hi = min(s_lim[1], nrows - 1);
+  if (hi - lo > 16 * n) {  // few positions among many rows: the row of each by search (8192 over 1 M rows, a transpose 329 -> 86 us)
+    int r[kExpandPerThread];
+#pragma unroll
+    for (int j = 0; j < kExpandPerThread; ++j) r[j] = lo;
+    for (int step = 1 << (31 - __clz(hi - lo)); step > 0; step >>= 1)
+#pragma unroll
+      for (int j = 0; j < kExpandPerThread; ++j)
+        if (hi - r[j] >= step && int64_t(rowptr[r[j] + step]) <= e0 + j * THREADS + int(threadIdx.x)) r[j] += step;
+#pragma unroll
+    for (int j = 0; j < kExpandPerThread; ++j) s_row[j * THREADS + threadIdx.x] = r[j];
+    __syncthreads();
+    return;
+  }
   for (int r = lo + 1 + int(threadIdx.x); r <= hi; r += THREADS) {
     const int p = rowptr[r];
     const int64_t at = int64_t(p) - e0;

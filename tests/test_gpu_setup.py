@@ -87,14 +87,16 @@ def test_sort_few_words(hgnn, dev, V, E):
     check_lists(hgnn, dev, V, row, col)
 
 
-# long stretches of empty rows and columns: by the workgroup that finds them, or beyond 65536 with few words to each in windows of 1024
-@pytest.mark.parametrize("V", [65536, 65537, 66559, 66560, 66561, 5000011])
-def test_long_gaps(hgnn, dev, V):
-    print(f"setup gaps V={V}", flush=True)
+# long stretches of empty rows and columns, by the number of words to an offset: written where they are found, from 65537 offsets on but for
+# windows of 1024; with few words all offsets by search, with many words to a window too
+@pytest.mark.parametrize("V,E", [(23000, 3000), (24008, 3000), (24009, 3000), (65536, 9000), (65537, 9000), (66559, 9000), (66560, 9000), (66561, 9000),
+                                 (1 << 20, 300000), (5000011, 3000), (5000011, 625001), (5000011, 625002), (100000, 1600000), (100001, 1600000)])
+def test_long_gaps(hgnn, dev, V, E):
+    print(f"setup gaps V={V} E={E}", flush=True)
     r = np.random.default_rng(V)
-    some = [0, 1, 1022, 1023, 1024, 1025, 2047, 2048, 3071, 5000, 40959, V - 1025, V - 1024, V - 2, V - 1]
-    for ids in ([V // 2], [0], [V - 1], [1023], [1024], some, some[1:-1]):
-        row = np.array(ids, dtype=np.int32)[r.integers(0, len(ids), 3000)]
+    some = [0, 1, 1022, 1023, 1024, 1025, 2047, 2048, 3071, 5000, 20959, V - 1025, V - 1024, V - 2, V - 1]
+    for ids in ([V // 2], [0], [V - 1], [1023], [1024], some, some[1:-1])[: 7 if E < 10000 else 1 if E < 1000000 else 6]:
+        row = np.array(ids, dtype=np.int32)[r.integers(0, len(ids), E)]
         check_lists(hgnn, dev, V, row, r.permutation(row))
 
 
@@ -114,6 +116,22 @@ def test_time_of_a_long_gap(hgnn, dev):
             hgnn.hgnn_coo_to_csr(row, col, V, V, want_eid=False)
             best[what] = min(best[what], time.perf_counter() - t)
     assert best["one"] <= 3 * best["uniform"], best
+
+
+def test_time_of_few_words(hgnn, dev):
+    """Few words over many vertices: a few launches and no loop over the stretches between them (twice as long as this many)."""
+    V, E = 100000, 1000
+    r = np.random.default_rng(1)
+    row, col = (up(r.integers(0, V, E).astype(np.int32), dev) for _ in range(2))
+    best = {}
+    for v in (V, 1 << 16):
+        best[v] = 1e9
+        for _ in range(30):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            hgnn.hgnn_coo_to_csr(row % v, col % v, v, v)
+            best[v] = min(best[v], time.perf_counter() - t)
+    assert best[V] < 80e-6, best
 
 
 @pytest.mark.parametrize("E", [1, 8193, 700000])
