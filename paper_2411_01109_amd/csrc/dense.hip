@@ -207,7 +207,21 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
         if (row >= a.n) continue;
 #pragma unroll
         for (int b = 0; b < NT / 2; ++b) {
-          linear_store(a, row, fc0 + 16 * NT * pass + 32 * b + 8 * q, acc[r][2 * b], acc[r][2 * b + 1]);
+          const int f = fc0 + 16 * NT * pass + 32 * b + 8 * q;
+          half8_t h;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            h[j] = half_t(acc[r][2 * b][j]);
+            h[4 + j] = half_t(acc[r][2 * b + 1][j]);
+          }
+          half_t* dst = a.Y + row * a.ldy + f;
+          if (f + 8 <= a.F) {
+            *reinterpret_cast<half8_t*>(dst) = h;
+          } else if (f < a.F) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              if (j < a.F - f) dst[j] = h[j];
+          }
         }
       }
     }
