@@ -680,8 +680,12 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   //   504, 128, W^T   13.2 / 8.1  13.3 / 8.8  13.6 / 9.4  16.1 / 10.5 24.3 / 13.6 24.4 / 16.5 17.8 / 17.8
   //   1024, 64        16.3 / 8.6  16.4 / 9.0  21.7 / 11.7 22.1 / 12.2
   // at 40 000 rows (two rounds of workgroups) 10 to 40 % slower.
+  // Behind the kernel that wrote X, in the caches, a chain of few steps ends sooner: 256, 64 at 32 768 rows 7.9 / 8.6, 256, 128 10.5 / 11.3; 128, 64
+  // at 8192 5.2 / 5.5, at 5000 6.6 / 5.4, W^T 5.6 / 4.6 and 7.1 / 4.5; 128, 128 at 8192, 20 000, 27 000 7.2 / 6.5, 7.5 / 7.3, 7.8 / 8.1; 128, 32 at 2000
+  // 4.5 / 4.6.
   const int T = int(std::max<int64_t>(2, ceil_div(tiles, kCus))), KP = T <= 4 ? 4 : (T == 5 ? 3 : 2);
-  if (RT == 1 && T <= 8 && K >= 128 && k32 <= KP * kSplitSteps * 32 && F <= 128 && a.KC == k32 && a.FC == 16 * nt) {
+  const bool shared = K > 256 ? T <= 8 : (K > 128 ? T <= 7 : K == 128 && T <= 5 && (trans_w || F > 64 || (F > 32 && n < 8192)));
+  if (RT == 1 && shared && k32 <= KP * kSplitSteps * 32 && F <= 128 && a.KC == k32 && a.FC == 16 * nt) {
     const size_t need = std::max(lds, size_t(KP - 1) * size_t(T) * size_t(nt) * kWave * sizeof(float4_t));
     const dim3 grid{unsigned(ceil_div(tiles, T)), 1u, 1u};
     const int threads = T * KP * kWave;

@@ -160,7 +160,19 @@ def weight_gradient(h):
             assert st == 0 and len(names) == (1 if n <= most else 2), (n, K, F, names)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient]
+def shared_columns(h):
+    """Waves share a tile's columns up to as many rows as that pays for, by the columns; for 128 of them by the weight, too."""
+    x = vp(h.data)
+    for K, F, trans, most in ((608, 64, 0, 32768), (264, 128, 1, 32768), (256, 128, 0, 28672), (136, 8, 0, 28672), (128, 128, 0, 20480), (128, 64, 1, 20480),
+                              (128, 64, 0, 8191), (128, 40, 0, 8191), (128, 32, 0, 0), (120, 64, 1, 0)):
+        for n in (1, most, most + 1):
+            st, names = launches(h, lambda: h.lib.hgnn_linear(i64(n), K, F, x, i64(K), x, i64(K if trans else F), trans, x, i64(F), vp(A)))
+            assert st == 0 and len(names) == (n > 0), (n, K, F, names)
+            if n:
+                assert ("linear_split" in names[0]) == (n <= most), (n, K, F, trans, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
