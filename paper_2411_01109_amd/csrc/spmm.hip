@@ -1425,6 +1425,10 @@ static void launch_tasks(int L, int wm, bool mapped, unsigned waves, size_t leas
 // (tables that fit that cache, and the rows of one range in an L2, gain or lose either way, so they are left alone).  A wave of short
 // rows is mostly its own start and end, which other waves must cover (28 / 16 waves: 7 non-zeros a row over 1.06 GB 960 / 1004 us, through
 // the map 1186 / 1229; 13 a row over 614 MB, no edge values, 866 / 907).
+// Unmapped and with a plan, which knows how many pieces at column ranges there are, those decide from one for every 320 non-zeros on; fewer leave
+// most rows as they are.  28 / 16 waves: power law, 62 M x 64 by degrees (one for 229) 617 / 642; log-normal, 55 M x 128 (one for 380)
+// 1924 / 1903, 14 M x 256 (one for 1300) 954 / 938, 27 M x 128 (one for 1500) 1093 / 1055.  Without a plan the host does not know: 27 M x 128
+// with edge values, no long row 1058 / 1034, power law 638 / 650, 62 M x 64 770 / 781.
 static size_t least_task_lds(bool mapped, bool ranges, const SpmmArgs& a, int64_t ncols, int64_t l2, int64_t llc) {
   constexpr size_t kLds = 160 * 1024;  // of a compute unit
   const int64_t edge_bytes = a.nnz * a.H * 2, table_bytes = ncols * a.ldx * 2;
@@ -1468,6 +1472,8 @@ static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const Ta
   }
 }
 
+static bool mostly_ranges(const hgnn_row_tasks* t) { return int64_t(t->n_rtask) * 320 >= t->nnz; }
+
 // Pass 1 and pass 2 of the discretized SpMM over the row tasks t of plan p, whose column array `a.col` indexes (with a.eid,
 // a.delta beside it); a.Y / a.ldy / a.block_y_stride describe the result, or the column blocks' partial results.
 static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmArgs a, int ncols, hipStream_t s) {
@@ -1485,7 +1491,7 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
     HGNN_LAUNCH_CHECK("zero_split_rows_kernel");
   }
   if (waves > 0) {
-    const size_t least = least_task_lds(mapped, ranges, a, ncols, p->l2_bytes, p->llc_bytes);
+    const size_t least = least_task_lds(mapped, ranges && (mapped || mostly_ranges(t)), a, ncols, p->l2_bytes, p->llc_bytes);
     if (near_table(ncols, a.ldx)) launch_tasks<true>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     else launch_tasks<false>(L, wm, mapped, unsigned(waves), least, s, a, v, ncols);
     HGNN_LAUNCH_CHECK("spmm_task_kernel");
