@@ -78,6 +78,23 @@ def test_spmm(hgnn, dev, graph, F, H, what):
     hgnn.hgnn_plan_destroy(p)
 
 
+@pytest.mark.parametrize("S", [64, 1000])
+def test_table_beyond_the_last_level_cache(hgnn, dev, graph, S):
+    """Most rows, or a few, have pieces at column ranges: more waves in flight, or fewer."""
+    print(f"ranges, 282 MB table, S={S}", flush=True)
+    rowptr, col = graph
+    F = 128
+    X = torch.randn((NCOLS, F), generator=torch.Generator(device=dev).manual_seed(S), device=dev).half()
+    w = f16(np.random.default_rng(S).standard_normal((col.size, 1)))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=NCOLS)
+    p = hgnn.hgnn_plan_create(g, S, F, 1, col_blocks=1)
+    Y = torch.full((V, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm_discretized(p, g, up(w, dev), 1, X, Y)
+    ref, sabs = oracle.spmm(rowptr, col, down(X), w=w, H=1, want_sabs=True)
+    compare("large table", down(Y), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+
+
 def scaled(rowptr, col, X, w, cs, H):
     """Mean of w * cs[col] * X[col], and the same over magnitudes, in float64."""
     F = X.shape[1]
