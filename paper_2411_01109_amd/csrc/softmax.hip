@@ -5,8 +5,8 @@
 // sub-wave group of LR lanes (LR chosen from the mean row length, so short rows do not idle a
 // whole wave) or a whole wave; rows longer than the plan's threshold are cut into chunks, a
 // workgroup each, whose partial results a second launch combines.
-// Every lane moves 16 bytes (8 halves) per access: the slice is walked in 8-element vectors
-// aligned to the tensor's base, the ragged first and last vector are masked, and because H
+// Every lane moves 16 bytes (8 halves) per access: the slice is walked in the 8-element vectors,
+// aligned to the tensor's base, that lie in it whole, and the few non-zeros at its two ends by themselves; because H
 // divides 8 the head of each of a lane's 8 elements is fixed.  A row that fits the lanes'
 // registers is read once.  exp, sums and the division stay in fp32; the exponent is <= 0, so
 // the numerator is in (0,1] (section 3.1.2) and alpha is rounded once.
@@ -21,16 +21,16 @@ constexpr int kKeepVec = 2;     // 8-element vectors per lane held in registers
 struct EdgeRowArgs {
   const int* rowptr;
   const int* big_row;
-  const int* row_list;  // when set, the wave-per-row tier takes its rows from this list of n_list rows
+  const int* row_list;  // the tier of longer rows goes through this list, or through all rows
   int n_list;
   const int* eid;
   const half_t* x0;  // forward: e.          backward: alpha.   rowsum: t
   const half_t* x1;  //                      backward: dalpha
   const half_t* x2;  //                      backward: e (LeakyReLU mask) or nullptr
   half_t* out;       // forward: alpha.      backward: de.      rowsum: [nrows][H]
-  int64_t total;     // nnz * H
   int nrows, H;
   int team_max;      // rows longer than this are left by the sub-wave teams to a wave each
+  int list_max;      // of the longer rows those above this take a wave each, the others a team of 16 lanes (0: all a wave each)
   int wave_max;      // rows longer than this go to the chunked kernels (INT_MAX: there are none)
   float slope;
 };
@@ -75,191 +75,242 @@ struct SubWaveTeam {  // LR consecutive lanes of a wave
   }
 };
 
-// 8 elements starting at the 8-aligned index b; a vector that would cross the end of the tensor is read by element
-__device__ __forceinline__ half8_t load_vec(const half_t* p, int64_t b, int64_t total) {
-  if (b + 8 <= total) return *reinterpret_cast<const half8_t*>(p + b);
-  half8_t v = half8_t(0);
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    if (b + q < total) v[q] = p[b + q];
-  return v;
-}
-// load_vec with the elements outside [j0, j1) replaced by `fill` (the neutral value of what the caller does with
-// them), so that the passes over the vector need no bounds checks of their own: two 32-bit compares and a select
-// per element, once, instead of two 64-bit compares per element and pass
-__device__ __forceinline__ half8_t load_vec_in(const half_t* p, int64_t b, int64_t total, int64_t j0, int64_t j1, half_t fill) {
-  half8_t v = load_vec(p, b, total);
-  const int lo = j0 > b ? int(j0 - b) : 0;          // first valid element
-  const int hi = j1 - b < 8 ? int(j1 - b) : 8;      // one past the last valid element
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    if (q < lo || q >= hi) v[q] = fill;
-  return v;
-}
-__device__ __forceinline__ void store_vec(half_t* p, int64_t b, const half8_t& v, int64_t j0, int64_t j1) {
-  if (b >= j0 && b + 8 <= j1) {
-    *reinterpret_cast<half8_t*>(p + b) = v;
-  } else {
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      if (b + q >= j0 && b + q < j1) p[b + q] = v[q];
+// The non-zeros [beg, end) of a row (or of a chunk of one) as the vectors of 8 elements that lie in it whole, and what is left at its two
+// ends, fewer non-zeros than a vector holds on either side.  Whole vectors need no masks; the ends are dealt out to the lanes, H elements of a
+// non-zero each.  With masks on every vector and the vectors at the ends stored by element a wave with a row of 100 non-zeros x 4 heads spent
+// 530 vector instructions, and these bound the pass; with the ends apart and such rows sharing waves, us, forward; backward; row sums: 5.5 M
+// power law x 4 heads 58 -> 40; 45 -> 44; 23 -> 19, one head 25 -> 17; 24 -> 20; 12.6 -> 9.5; 20 M x 4 196 -> 135; 194 -> 193; 66 -> 49; 40 M
+// log-normal, one head 87 -> 53; 113 -> 91; 56 -> 36; 3 M uniform, one head 8.3 -> 6.5; 8.5 -> 8.0; 3.8 -> 3.8; without a plan 18.7 -> 10.1;
+// 20.6 -> 12.0.
+template <int H>
+struct Span {
+  static constexpr int kPer = 8 / H;           // non-zeros in a vector
+  static constexpr int kEnds = 2 * (kPer - 1);  // at most so many non-zeros outside whole vectors
+  pos_t beg, body, tail;   // non-zeros: the first, the first of the whole vectors, the first behind them
+  int n_head, n_body, n_tail;  // n_body counts vectors
+  __device__ __forceinline__ Span(int first, int last) {
+    const pos_t b = pos_t(first), e = pos_t(last), up = (b + kPer - 1) & ~pos_t(kPer - 1), down = e & ~pos_t(kPer - 1);
+    beg = b;
+    body = up < e ? up : e;
+    n_head = int(body - b);
+    n_body = down > up ? int((down - up) / kPer) : 0;
+    tail = down >= up ? down : e;
+    n_tail = int(e - tail);
   }
-}
+  __device__ __forceinline__ bool has(int i) const { return i < kPer - 1 ? i < n_head : i - (kPer - 1) < n_tail; }
+  __device__ __forceinline__ pos_t end_at(int i) const { return i < kPer - 1 ? beg + pos_t(i) : tail + pos_t(i - (kPer - 1)); }
+};
+
+// The part of a span that a lane of a team of SIZE holds: KEEP vectors in registers (lane `rank` has every SIZE-th one), and its share
+// of the ends.
+template <int H, int SIZE, int KEEP>
+struct Held {
+  typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
+  static constexpr int NE = (Span<H>::kEnds + SIZE - 1) / SIZE;
+  half8_t v[KEEP];
+  hv_t e[NE > 0 ? NE : 1];
+  __device__ __forceinline__ void load(const half_t* p, const Span<H>& s, int rank, half_t fill) {
+    const half8_t* const q = reinterpret_cast<const half8_t*>(p + int64_t(s.body) * H);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+      v[i] = half8_t(fill);
+      const int t = rank + SIZE * i;
+      if (t < s.n_body) v[i] = q[t];
+    }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+      e[i] = hv_t(fill);
+      const int t = rank + SIZE * i;
+      if (t < Span<H>::kEnds && s.has(t)) e[i] = *reinterpret_cast<const hv_t*>(p + int64_t(s.end_at(t)) * H);
+    }
+  }
+};
 
 // ---- forward: one row by one team ----------------------------------------------------------------------
-template <int H, class Team>
-__device__ __forceinline__ void softmax_fwd_row(const EdgeRowArgs& a, const Team& team, int64_t j0, int64_t j1) {
-  const int64_t a0 = j0 & ~int64_t(7);
-  const int64_t nvec = (j1 - a0 + 7) >> 3;
-  half8_t keep[kKeepVec];
+template <int H, int KEEP, class Team>
+__device__ __forceinline__ void softmax_fwd_row(const EdgeRowArgs& a, const Team& team, int beg, int end) {
+  constexpr int SIZE = Team::size;
+  typedef Held<H, SIZE, KEEP> Hold;
+  typedef typename Hold::hv_t hv_t;
+  const Span<H> s(beg, end);
+  // what a lane does not have is -inf: it loses every maximum and adds exp(-inf) = 0
+  Hold x;
+  x.load(a.x0, s, team.rank, half_t(-INFINITY));
+  const half8_t* const src = reinterpret_cast<const half8_t*>(a.x0 + int64_t(s.body) * H);
+  half8_t* const dst = reinterpret_cast<half8_t*>(a.out + int64_t(s.body) * H);
   float m[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) m[h] = -INFINITY;
-  // elements of a vector that lie outside the row are read as -inf: they lose every maximum and add exp(-inf) = 0
-  const half_t ninf = half_t(-INFINITY);
   auto visit_max = [&](const half8_t& v) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) m[q % H] = fmaxf(m[q % H], float(v[q]));
   };
 #pragma unroll
-  for (int i = 0; i < kKeepVec; ++i) {
-    const int64_t t = team.rank + int64_t(Team::size) * i;
-    keep[i] = half8_t(ninf);
-    if (t < nvec) {
-      keep[i] = load_vec_in(a.x0, a0 + 8 * t, a.total, j0, j1, ninf);
-      visit_max(keep[i]);
-    }
-  }
-  for (int64_t t = team.rank + int64_t(Team::size) * kKeepVec; t < nvec; t += Team::size)
-    visit_max(load_vec_in(a.x0, a0 + 8 * t, a.total, j0, j1, ninf));
+  for (int i = 0; i < KEEP; ++i)
+    if (i == 0 || SIZE * i < s.n_body) visit_max(x.v[i]);
+#pragma unroll
+  for (int i = 0; i < Hold::NE; ++i)
+#pragma unroll
+    for (int h = 0; h < H; ++h) m[h] = fmaxf(m[h], float(x.e[i][h]));
+  for (int t = team.rank + SIZE * KEEP; t < s.n_body; t += SIZE) visit_max(src[t]);
   team.template reduce<H, true>(m);
-  float z[H];
+  float z[H], ex[KEEP][8], ee[Hold::NE > 0 ? Hold::NE : 1][H];  // the exponentials of what is held, formed once
 #pragma unroll
   for (int h = 0; h < H; ++h) z[h] = 0.f;
-  auto visit_sum = [&](const half8_t& v) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) z[q % H] += __expf(float(v[q]) - m[q % H]);
-  };
-  float ex[kKeepVec][8];  // the exponentials of the vectors held in registers, formed once
-#pragma unroll
-  for (int i = 0; i < kKeepVec; ++i) {
-    const int64_t t = team.rank + int64_t(Team::size) * i;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) ex[i][q] = 0.f;
-    if (t < nvec) {
+  for (int i = 0; i < KEEP; ++i) {
+    if (i == 0 || SIZE * i < s.n_body) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        ex[i][q] = __expf(float(keep[i][q]) - m[q % H]);
+        ex[i][q] = __expf(float(x.v[i][q]) - m[q % H]);
         z[q % H] += ex[i][q];
       }
     }
   }
-  for (int64_t t = team.rank + int64_t(Team::size) * kKeepVec; t < nvec; t += Team::size)
-    visit_sum(load_vec_in(a.x0, a0 + 8 * t, a.total, j0, j1, ninf));
+#pragma unroll
+  for (int i = 0; i < Hold::NE; ++i)
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      ee[i][h] = __expf(float(x.e[i][h]) - m[h]);
+      z[h] += ee[i][h];
+    }
+  for (int t = team.rank + SIZE * KEEP; t < s.n_body; t += SIZE) {
+    const half8_t v = src[t];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) z[q % H] += __expf(float(v[q]) - m[q % H]);
+  }
   team.template reduce<H, false>(z);
   float inv[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) inv[h] = 1.f / z[h];
-  auto emit = [&](const half8_t& v, int64_t b) {
-    half8_t o;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = half_t(__expf(float(v[q]) - m[q % H]) * inv[q % H]);
-    store_vec(a.out, b, o, j0, j1);
-  };
-#pragma unroll
-  for (int i = 0; i < kKeepVec; ++i) {
-    const int64_t t = team.rank + int64_t(Team::size) * i;
-    if (t < nvec) {
+  for (int i = 0; i < KEEP; ++i) {
+    const int t = team.rank + SIZE * i;
+    if (t < s.n_body) {
       half8_t o;
 #pragma unroll
       for (int q = 0; q < 8; ++q) o[q] = half_t(ex[i][q] * inv[q % H]);
-      store_vec(a.out, a0 + 8 * t, o, j0, j1);
+      dst[t] = o;
     }
   }
-  for (int64_t t = team.rank + int64_t(Team::size) * kKeepVec; t < nvec; t += Team::size)
-    emit(load_vec(a.x0, a0 + 8 * t, a.total), a0 + 8 * t);
+#pragma unroll
+  for (int i = 0; i < Hold::NE; ++i) {
+    const int t = team.rank + SIZE * i;
+    if (t < Span<H>::kEnds && s.has(t)) {
+      hv_t o;
+#pragma unroll
+      for (int h = 0; h < H; ++h) o[h] = half_t(ee[i][h] * inv[h]);
+      *reinterpret_cast<hv_t*>(a.out + int64_t(s.end_at(t)) * H) = o;
+    }
+  }
+  for (int t = team.rank + SIZE * KEEP; t < s.n_body; t += SIZE) {
+    const half8_t v = src[t];
+    half8_t o;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) o[q] = half_t(__expf(float(v[q]) - m[q % H]) * inv[q % H]);
+    dst[t] = o;
+  }
 }
 
 // ---- backward: t = sum alpha*dalpha (per head); de = alpha*(dalpha - t) [* LeakyReLU'(e)] --------------
-template <int H, class Team>
-__device__ __forceinline__ void softmax_bwd_row(const EdgeRowArgs& a, const Team& team, int64_t j0, int64_t j1) {
-  const int64_t a0 = j0 & ~int64_t(7);
-  const int64_t nvec = (j1 - a0 + 7) >> 3;
-  half8_t ka[kKeepVec], kd[kKeepVec];
+__device__ __forceinline__ half_t softmax_bwd_value(const EdgeRowArgs& a, half_t alpha, half_t dalpha, half_t e, float t) {
+  float d = float(alpha) * (float(dalpha) - t);
+  if (!(float(e) > 0.f)) d *= a.slope;
+  return half_t(d);
+}
+
+template <int H, int KEEP, class Team>
+__device__ __forceinline__ void softmax_bwd_row(const EdgeRowArgs& a, const Team& team, int beg, int end) {
+  constexpr int SIZE = Team::size;
+  typedef Held<H, SIZE, KEEP> Hold;
+  typedef typename Hold::hv_t hv_t;
+  const Span<H> s(beg, end);
+  // what a lane does not have is zero on both sides, so its products vanish (a neighbouring row's infinity times zero would not)
+  Hold al, da;
+  al.load(a.x0, s, team.rank, half_t(0));
+  da.load(a.x1, s, team.rank, half_t(0));
+  const int64_t first = int64_t(s.body) * H;
+  auto vec = [&](const half_t* p, int t) { return reinterpret_cast<const half8_t*>(p + first)[t]; };
+  half8_t* const dst = reinterpret_cast<half8_t*>(a.out + first);
   float t[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) t[h] = 0.f;
-  // elements outside the row are read as zero on both sides, so their products vanish (a neighbouring row's
-  // infinity times zero would not)
   auto visit = [&](const half8_t& va, const half8_t& vd) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) t[q % H] = fmaf(float(va[q]), float(vd[q]), t[q % H]);
   };
 #pragma unroll
-  for (int i = 0; i < kKeepVec; ++i) {
-    const int64_t v = team.rank + int64_t(Team::size) * i;
-    ka[i] = half8_t(0);
-    kd[i] = half8_t(0);
-    if (v < nvec) {
-      ka[i] = load_vec_in(a.x0, a0 + 8 * v, a.total, j0, j1, half_t(0));
-      kd[i] = load_vec_in(a.x1, a0 + 8 * v, a.total, j0, j1, half_t(0));
-      visit(ka[i], kd[i]);
-    }
-  }
-  for (int64_t v = team.rank + int64_t(Team::size) * kKeepVec; v < nvec; v += Team::size)
-    visit(load_vec_in(a.x0, a0 + 8 * v, a.total, j0, j1, half_t(0)), load_vec_in(a.x1, a0 + 8 * v, a.total, j0, j1, half_t(0)));
-  team.template reduce<H, false>(t);
-  auto emit = [&](const half8_t& va, const half8_t& vd, int64_t b) {
-    half8_t o;
-    half8_t ve = half8_t(1);
-    if (a.x2) ve = load_vec(a.x2, b, a.total);
+  for (int i = 0; i < KEEP; ++i)
+    if (i == 0 || SIZE * i < s.n_body) visit(al.v[i], da.v[i]);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      float d = float(va[q]) * (float(vd[q]) - t[q % H]);
-      if (!(float(ve[q]) > 0.f)) d *= a.slope;
-      o[q] = half_t(d);
-    }
-    store_vec(a.out, b, o, j0, j1);
+  for (int i = 0; i < Hold::NE; ++i)
+#pragma unroll
+    for (int h = 0; h < H; ++h) t[h] = fmaf(float(al.e[i][h]), float(da.e[i][h]), t[h]);
+  for (int v = team.rank + SIZE * KEEP; v < s.n_body; v += SIZE) visit(vec(a.x0, v), vec(a.x1, v));
+  team.template reduce<H, false>(t);
+  auto emit = [&](const half8_t& va, const half8_t& vd, int v) {
+    const half8_t ve = a.x2 ? vec(a.x2, v) : half8_t(1);
+    half8_t o;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) o[q] = softmax_bwd_value(a, va[q], vd[q], ve[q], t[q % H]);
+    dst[v] = o;
   };
 #pragma unroll
-  for (int i = 0; i < kKeepVec; ++i) {
-    const int64_t v = team.rank + int64_t(Team::size) * i;
-    if (v < nvec) emit(ka[i], kd[i], a0 + 8 * v);
+  for (int i = 0; i < KEEP; ++i) {
+    const int v = team.rank + SIZE * i;
+    if (v < s.n_body) emit(al.v[i], da.v[i], v);
   }
-  for (int64_t v = team.rank + int64_t(Team::size) * kKeepVec; v < nvec; v += Team::size)
-    emit(load_vec(a.x0, a0 + 8 * v, a.total), load_vec(a.x1, a0 + 8 * v, a.total), a0 + 8 * v);
+#pragma unroll
+  for (int i = 0; i < Hold::NE; ++i) {
+    const int v = team.rank + SIZE * i;
+    if (v < Span<H>::kEnds && s.has(v)) {
+      const int64_t at = int64_t(s.end_at(v)) * H;
+      const hv_t ve = a.x2 ? *reinterpret_cast<const hv_t*>(a.x2 + at) : hv_t(half_t(1));
+      hv_t o;
+#pragma unroll
+      for (int h = 0; h < H; ++h) o[h] = softmax_bwd_value(a, al.e[i][h], da.e[i][h], ve[h], t[h]);
+      *reinterpret_cast<hv_t*>(a.out + at) = o;
+    }
+  }
+  for (int v = team.rank + SIZE * KEEP; v < s.n_body; v += SIZE)
+    emit(vec(a.x0, v), vec(a.x1, v), v);
 }
 
 // ---- row sums: out[row,h] = sum over the row of t[slot(k), h] -------------------------------------------
+// s += what the lane `rank` of `size` holds of the non-zeros [beg, end)
+template <int H, int SIZE>
+__device__ __forceinline__ void rowsum_share(const EdgeRowArgs& a, int rank, int beg, int end, float (&s)[H]) {
+  typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
+  if (a.eid) {  // transposed view: one lane per non-zero, its H values are contiguous at slot eid[k]
+    for (pos_t k = pos_t(beg) + rank; k < pos_t(end); k += SIZE) {
+      const hv_t v = *reinterpret_cast<const hv_t*>(a.x0 + int64_t(a.eid[k]) * H);
+#pragma unroll
+      for (int h = 0; h < H; ++h) s[h] += float(v[h]);
+    }
+    return;
+  }
+  const Span<H> sp(beg, end);
+  Held<H, SIZE, 1> x;
+  x.load(a.x0, sp, rank, half_t(0));
+  const half8_t* const src = reinterpret_cast<const half8_t*>(a.x0 + int64_t(sp.body) * H);
+  auto add = [&](const half8_t& v) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q % H] += float(v[q]);
+  };
+  add(x.v[0]);
+#pragma unroll
+  for (int i = 0; i < x.NE; ++i)
+#pragma unroll
+    for (int h = 0; h < H; ++h) s[h] += float(x.e[i][h]);
+  for (int t = rank + SIZE; t < sp.n_body; t += SIZE) add(src[t]);
+}
+
 template <int H, class Team>
 __device__ __forceinline__ void rowsum_row(const EdgeRowArgs& a, const Team& team, int row, int beg, int end) {
   float s[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) s[h] = 0.f;
-  if (a.eid) {  // transposed view: one lane per non-zero, its H values are contiguous at slot eid[k]
-    typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
-    for (pos_t k = pos_t(beg) + team.rank; k < pos_t(end); k += Team::size) {
-      const int64_t slot = a.eid[k];
-      if (H == 1) {
-        s[0] += float(a.x0[slot]);
-      } else {
-        const hv_t v = *reinterpret_cast<const hv_t*>(a.x0 + slot * H);
-#pragma unroll
-        for (int h = 0; h < H; ++h) s[h] += float(v[h]);
-      }
-    }
-  } else {
-    const int64_t j0 = int64_t(beg) * H, j1 = int64_t(end) * H;
-    const int64_t a0 = j0 & ~int64_t(7);
-    const int64_t nvec = (j1 - a0 + 7) >> 3;
-    for (int64_t t = team.rank; t < nvec; t += Team::size) {
-      const int64_t b = a0 + 8 * t;
-      const half8_t v = load_vec(a.x0, b, a.total);
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (b + q >= j0 && b + q < j1) s[q % H] += float(v[q]);
-    }
-  }
+  rowsum_share<H, Team::size>(a, team.rank, beg, end, s);
   team.template reduce<H, false>(s);
   if (team.rank == 0) {
 #pragma unroll
@@ -268,16 +319,18 @@ __device__ __forceinline__ void rowsum_row(const EdgeRowArgs& a, const Team& tea
 }
 
 enum { kFwd = 0, kBwd = 1, kSum = 2 };
+// vectors a lane holds of a listed row or of a chunk: registers for eight waves a SIMD (seven with four heads), four with eight heads
+__host__ __device__ constexpr int edge_keep(int op, int H) { return op == kFwd && H < 8 ? 4 : 2; }
 
-// one row by the team of LR lanes that the calling lane belongs to
-template <int OP, int LR, int H>
+// one row by the team of LR lanes that the calling lane belongs to, KEEP vectors a lane in registers
+template <int OP, int LR, int H, int KEEP = kKeepVec>
 __device__ __forceinline__ void edge_row(const EdgeRowArgs& a, int row, int beg, int end) {
   const SubWaveTeam<LR> team;
   if (OP == kSum) {
     rowsum_row<H>(a, team, row, beg, end);
   } else if (end > beg) {
-    if (OP == kFwd) softmax_fwd_row<H>(a, team, int64_t(beg) * H, int64_t(end) * H);
-    else softmax_bwd_row<H>(a, team, int64_t(beg) * H, int64_t(end) * H);
+    if (OP == kFwd) softmax_fwd_row<H, KEEP>(a, team, beg, end);
+    else softmax_bwd_row<H, KEEP>(a, team, beg, end);
   }
 }
 
@@ -326,52 +379,76 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
   __shared__ float sm[(kHubThreads / kWave) * 8];
   int beg, end;
   hub_chunk_range(a, c, slot, beg, end);
-  const int64_t j0 = int64_t(beg) * H, j1 = int64_t(end) * H;
-  const int64_t a0 = j0 & ~int64_t(7);
-  const int64_t nvec = (j1 - a0 + 7) >> 3;
   float r0[H], r1[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) {
     r0[h] = OP == kFwd ? -INFINITY : 0.f;
     r1[h] = 0.f;
   }
-  if (OP == kSum && a.eid) {
-    typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
-    for (pos_t k = pos_t(beg) + threadIdx.x; k < pos_t(end); k += kHubThreads) {
-      const int64_t s = a.eid[k];
-      if (H == 1) {
-        r0[0] += float(a.x0[s]);
-      } else {
-        const hv_t v = *reinterpret_cast<const hv_t*>(a.x0 + s * H);
-#pragma unroll
-        for (int h = 0; h < H; ++h) r0[h] += float(v[h]);
-      }
-    }
+  const int rank = threadIdx.x;
+  if (OP == kSum) {
+    rowsum_share<H, kHubThreads>(a, rank, beg, end, r0);
+    hub_block_reduce<H, false>(r0, sm);
   } else {
-    for (int64_t t = threadIdx.x; t < nvec; t += kHubThreads) {
-      const int64_t b = a0 + 8 * t;
-      const half8_t v = load_vec(a.x0, b, a.total);
-      half8_t d = half8_t(0);
-      if (OP == kBwd) d = load_vec(a.x1, b, a.total);
+    // a chunk is kHubEdges * H / 8 vectors and its ends at most
+    constexpr int ALL = kHubEdges * H / 8 / kHubThreads, KEEP = ALL < edge_keep(OP, H) ? ALL : edge_keep(OP, H);
+    typedef Held<H, kHubThreads, KEEP> Hold;
+    const Span<H> s(beg, end);
+    const int64_t first = int64_t(s.body) * H;
+    auto vec = [&](const half_t* p, int t) { return reinterpret_cast<const half8_t*>(p + first)[t]; };
+    Hold x;
+    x.load(a.x0, s, rank, half_t(OP == kFwd ? -INFINITY : 0.f));
+    if (OP == kFwd) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (b + q < j0 || b + q >= j1) continue;
-        if (OP == kFwd) r0[q % H] = fmaxf(r0[q % H], float(v[q]));
-        else if (OP == kBwd) r0[q % H] = fmaf(float(v[q]), float(d[q]), r0[q % H]);
-        else r0[q % H] += float(v[q]);
+      for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r0[q % H] = fmaxf(r0[q % H], float(x.v[i][q]));
+#pragma unroll
+      for (int i = 0; i < Hold::NE; ++i)
+#pragma unroll
+        for (int h = 0; h < H; ++h) r0[h] = fmaxf(r0[h], float(x.e[i][h]));
+      for (int t = rank + kHubThreads * KEEP; KEEP < ALL && t < s.n_body; t += kHubThreads) {
+        const half8_t v = vec(a.x0, t);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r0[q % H] = fmaxf(r0[q % H], float(v[q]));
       }
-    }
-  }
-  hub_block_reduce<H, OP == kFwd>(r0, sm);
-  if (OP == kFwd) {  // second walk (cache resident): the sum of exp relative to the chunk's maximum
-    for (int64_t t = threadIdx.x; t < nvec; t += kHubThreads) {
-      const int64_t b = a0 + 8 * t;
-      const half8_t v = load_vec(a.x0, b, a.total);
+      hub_block_reduce<H, true>(r0, sm);  // then the sum of exp relative to the chunk's maximum
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (b + q >= j0 && b + q < j1) r1[q % H] += __expf(float(v[q]) - r0[q % H]);
+      for (int i = 0; i < KEEP; ++i)
+        if (rank + kHubThreads * i < s.n_body) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) r1[q % H] += __expf(float(x.v[i][q]) - r0[q % H]);
+        }
+#pragma unroll
+      for (int i = 0; i < Hold::NE; ++i)
+        if (rank + kHubThreads * i < Span<H>::kEnds && s.has(rank + kHubThreads * i)) {
+#pragma unroll
+          for (int h = 0; h < H; ++h) r1[h] += __expf(float(x.e[i][h]) - r0[h]);
+        }
+      for (int t = rank + kHubThreads * KEEP; KEEP < ALL && t < s.n_body; t += kHubThreads) {
+        const half8_t v = vec(a.x0, t);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r1[q % H] += __expf(float(v[q]) - r0[q % H]);
+      }
+      hub_block_reduce<H, false>(r1, sm);
+    } else {
+      Hold d;
+      d.load(a.x1, s, rank, half_t(0));
+#pragma unroll
+      for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r0[q % H] = fmaf(float(x.v[i][q]), float(d.v[i][q]), r0[q % H]);
+#pragma unroll
+      for (int i = 0; i < Hold::NE; ++i)
+#pragma unroll
+        for (int h = 0; h < H; ++h) r0[h] = fmaf(float(x.e[i][h]), float(d.e[i][h]), r0[h]);
+      for (int t = rank + kHubThreads * KEEP; KEEP < ALL && t < s.n_body; t += kHubThreads) {
+        const half8_t v = vec(a.x0, t), w = vec(a.x1, t);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r0[q % H] = fmaf(float(v[q]), float(w[q]), r0[q % H]);
+      }
+      hub_block_reduce<H, false>(r0, sm);
     }
-    hub_block_reduce<H, false>(r1, sm);
   }
   if (threadIdx.x < H) {
     float v0 = 0.f, v1 = 0.f;
@@ -388,9 +465,12 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
 
 // Every row of the graph in one launch: the wave-per-row tier (wave_wgs workgroups), then the sub-wave teams, and the chunks of
 // the long rows (n_chunks workgroups) after or before them.  As launches of their own each has a tail in which the chip drains:
-// 5.5 M non-zeros x 4 heads, forward with its follow-up 71 -> 57 us, backward 61 -> 45, sums 32 -> 22.  The softmax takes the chunks last because
-// its follow-up reads them again while the caches still hold them (114 M non-zeros, one head: forward 189 us with the chunks
-// first, 184 last, 179 in launches of their own; backward 210, 201, 207); the sums take them first (23.3 us last).
+// 5.5 M non-zeros x 4 heads, forward with its follow-up 71 -> 57 us, backward 61 -> 45, sums 32 -> 22, when a wave took each of the longer rows.
+// The softmax takes the chunks last because its follow-up reads them again while the caches still hold them (then, 114 M non-zeros, one head:
+// forward 189 us with the chunks first, 184 last, 179 in launches of their own; backward 210, 201, 207); the sums take them first (23.3 us last).
+// Longer rows: a workgroup takes 16 rows, listed or not, a team of 16 lanes each where that is four vectors a lane at most; the longer ones
+// among them are dealt out to its waves.
+constexpr int kListTeam = 16, kListRows = kHubThreads / kListTeam;
 template <int OP, int LR, int H>
 __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, HubChunks c, int n_chunks, int wave_wgs) {
   constexpr int W = kHubThreads / kWave;
@@ -402,15 +482,34 @@ __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, H
   }
   if (OP == kSum) wg -= n_chunks;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (wg < wave_wgs) {
-    int64_t row = int64_t(wg) * W + wave;
-    if (a.row_list) {
-      if (row >= a.n_list) return;
-      row = a.row_list[row];
+  if (wg < wave_wgs && a.list_max > 0) {
+    const int64_t i = (int64_t(wg) * W + wave) * (kWave / kListTeam) + lane / kListTeam;
+    int row = 0, beg = 0, end = 0;
+    if (i < a.n_list) {
+      row = a.row_list ? a.row_list[i] : int(i);
+      beg = a.rowptr[row];
+      end = a.rowptr[row + 1];
     }
-    if (row >= a.nrows) return;
+    const int len = end - beg;
+    const bool ok = len > a.team_max && len <= a.wave_max, whole = len > a.list_max;
+    __shared__ int s_whole[kListRows], s_n;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    if (ok && whole && lane % kListTeam == 0) s_whole[atomicAdd(&s_n, 1)] = row;
+    if (ok && !whole) edge_row<OP, kListTeam, H, edge_keep(OP, H)>(a, row, beg, end);
+    __syncthreads();
+    for (int k = wave; k < s_n; k += W) {
+      const int r = __builtin_amdgcn_readfirstlane(s_whole[k]);
+      edge_row<OP, kWave, H>(a, r, a.rowptr[r], a.rowptr[r + 1]);
+    }
+    return;
+  }
+  if (wg < wave_wgs) {
+    const int64_t i = int64_t(wg) * W + wave;
+    if (i >= a.n_list) return;
+    const int row = a.row_list[i];
     const int beg = a.rowptr[row], end = a.rowptr[row + 1];
-    if (end - beg > a.team_max && end - beg <= a.wave_max) edge_row<OP, kWave, H>(a, int(row), beg, end);
+    if (end - beg > a.team_max && end - beg <= a.wave_max) edge_row<OP, kWave, H>(a, row, beg, end);
     return;
   }
   const int64_t row = (int64_t(wg - wave_wgs) * W + wave) * (kWave / LR) + lane / LR;
@@ -447,28 +546,34 @@ __global__ __launch_bounds__(kHubThreads) void edge_hub_emit_kernel(EdgeRowArgs 
 #pragma unroll
     for (int h = 0; h < H; ++h) S[h] = 1.f / S[h];
   }
-  const int64_t j0 = int64_t(beg) * H, j1 = int64_t(end) * H;
-  const int64_t a0 = j0 & ~int64_t(7);
-  const int64_t nvec = (j1 - a0 + 7) >> 3;
-  for (int64_t t = threadIdx.x; t < nvec; t += kHubThreads) {
-    const int64_t b = a0 + 8 * t;
-    const half8_t v = load_vec(a.x0, b, a.total);
-    half8_t o;
-    if (OP == kFwd) {
+  typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
+  const Span<H> s(beg, end);
+  const int64_t body = int64_t(s.body) * H;
+  auto value = [&](half_t x, half_t d, half_t e, int h) {
+    if (OP == kFwd) return half_t(__expf(float(x) - M[h]) * S[h]);
+    return softmax_bwd_value(a, x, d, e, S[h]);
+  };
+  for (int t = threadIdx.x; t < s.n_body; t += kHubThreads) {
+    auto vec = [&](const half_t* p) { return reinterpret_cast<const half8_t*>(p + body)[t]; };
+    const half8_t x = vec(a.x0);
+    half8_t d = half8_t(0), e = half8_t(1), o;
+    if (OP == kBwd) d = vec(a.x1);
+    if (OP == kBwd && a.x2) e = vec(a.x2);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) o[q] = half_t(__expf(float(v[q]) - M[q % H]) * S[q % H]);
-    } else {
-      const half8_t d = load_vec(a.x1, b, a.total);
-      half8_t e = half8_t(1);
-      if (a.x2) e = load_vec(a.x2, b, a.total);
+    for (int q = 0; q < 8; ++q) o[q] = value(x[q], d[q], e[q], q % H);
+    reinterpret_cast<half8_t*>(a.out + body)[t] = o;
+  }
+  const int i = threadIdx.x;
+  if (i < Span<H>::kEnds && s.has(i)) {
+    const int64_t at = int64_t(s.end_at(i)) * H;
+    auto unit = [&](const half_t* p) { return *reinterpret_cast<const hv_t*>(p + at); };
+    const hv_t x = unit(a.x0);
+    hv_t d = hv_t(half_t(0)), e = hv_t(half_t(1)), o;
+    if (OP == kBwd) d = unit(a.x1);
+    if (OP == kBwd && a.x2) e = unit(a.x2);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        float g = float(v[q]) * (float(d[q]) - S[q % H]);
-        if (!(float(e[q]) > 0.f)) g *= a.slope;
-        o[q] = half_t(g);
-      }
-    }
-    store_vec(a.out, b, o, j0, j1);
+    for (int h = 0; h < H; ++h) o[h] = value(x[h], d[h], e[h], h);
+    *reinterpret_cast<hv_t*>(a.out + at) = o;
   }
 }
 
@@ -528,6 +633,12 @@ static void launch_rows_h(int LR, dim3 grid, hipStream_t s, const EdgeRowArgs& a
   }
 }
 
+// Whether the listed rows share workgroups (kListTeam), or take a wave each: with four heads a row of 100 non-zeros fills most of a wave, and few
+// rows are then better spread.  us, a wave each / shared, forward; backward: 5.5 M non-zeros, 28 000 listed rows, H = 1 22 / 16.7; 22 / 19.5,
+// H = 4 52 / 40; 47 / 44, H = 8 86 / 77; 94 / 103; 1.5 M, 9000 listed rows, H = 1 11 / 9.5; 10.5 / 9.9, H = 2 15 / 13; 17 / 16, H = 4 28 / 28;
+// 28 / 33, H = 8 52 / 57; 48 / 58.
+static bool list_teams_pay(int H, int n_list) { return H <= 2 || (H == 4 && n_list >= 16384); }
+
 // Launches the row kernel (and the follow-up of the chunks when a plan lists long rows) for H in {1,2,4,8}.
 template <int OP>
 static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeRowArgs a, hipStream_t s) {
@@ -563,14 +674,13 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
   if (LR == kWave) t1 = INT_MAX;  // every row has a wave anyway
   a.team_max = t1;
   a.wave_max = big > 0 ? big : INT_MAX;
-  const int64_t rows_per_wg = kHubThreads / kWave;
+  constexpr int64_t rows_per_wg = kHubThreads / kWave;
   int64_t wave_wgs = 0;
   if (LR < kWave && !(big > 0 && t1 >= big)) {
-    if (mid_list) {
-      a.row_list = p->mid_row;
-      a.n_list = p->n_mid;
-    }
-    wave_wgs = ceil_div(mid_list ? int64_t(p->n_mid) : int64_t(g->nrows), rows_per_wg);
+    a.row_list = mid_list ? p->mid_row : nullptr;
+    a.n_list = mid_list ? p->n_mid : g->nrows;
+    if (!mid_list || list_teams_pay(H, p->n_mid)) a.list_max = OP == kSum && a.eid ? 4 * kListTeam : 4 * 8 * kListTeam / H;
+    wave_wgs = ceil_div(a.n_list, a.list_max > 0 ? kListRows : rows_per_wg);
   }
   const int n_chunks = big > 0 ? p->n_hub_chunks : 0;
   const HubChunks c = big > 0 ? HubChunks{p->hub_chunk_row, p->hub_chunk_first, p->hub_chunk_count, p->hub_part} : HubChunks{};
@@ -737,7 +847,6 @@ hgnn_status hgnn_edge_softmax(const hgnn_csr* g, const hgnn_plan* p, int32_t H, 
   a.rowptr = g->rowptr;
   a.x0 = reinterpret_cast<const half_t*>(e);
   a.out = reinterpret_cast<half_t*>(alpha);
-  a.total = g->nnz * H;
   a.nrows = g->nrows;
   a.H = H;
   return launch_edge_rows<kFwd>(g, p, a, static_cast<hipStream_t>(stream));
@@ -757,7 +866,6 @@ hgnn_status hgnn_edge_softmax_bwd(const hgnn_csr* g, const hgnn_plan* p, int32_t
   a.x1 = reinterpret_cast<const half_t*>(dalpha);
   a.x2 = reinterpret_cast<const half_t*>(e);
   a.out = reinterpret_cast<half_t*>(de);
-  a.total = g->nnz * H;
   a.nrows = g->nrows;
   a.H = H;
   a.slope = neg_slope;
@@ -776,7 +884,6 @@ hgnn_status hgnn_edge_rowsum(const hgnn_csr* g, const hgnn_plan* p, int32_t H, c
   a.eid = g->eid;
   a.x0 = reinterpret_cast<const half_t*>(t);
   a.out = reinterpret_cast<half_t*>(out);
-  a.total = g->nnz * H;
   a.nrows = g->nrows;
   a.H = H;
   hipStream_t s = static_cast<hipStream_t>(stream);

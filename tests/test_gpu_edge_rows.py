@@ -1,0 +1,67 @@
+"""The row passes over edge tensors at the borders of their vectors, teams and chunks: rows of every length around them, beginning at every
+offset inside a vector, with neighbours whose values must not leak."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity import compare, down, f16, up
+
+pytestmark = pytest.mark.gpu
+
+# around a vector of 8 elements, a team's and a wave's registers, the listed rows (32), the chunks (2048)
+EDGES = (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1025, 2047, 2048, 2049, 2056,
+         4096, 4097)
+
+
+def lengths(short_rows, seed):
+    r = np.random.default_rng(seed)
+    some = np.concatenate([np.array([n, k], np.int64) for k in range(8) for n in EDGES])  # each from eight offsets on
+    return np.concatenate([some, r.integers(0, 6, short_rows)])
+
+
+@pytest.mark.parametrize("H", [1, 2, 4, 8])
+@pytest.mark.parametrize("short_rows", [0, 1500, 60000])
+def test_row_passes_at_borders(hgnn, dev, H, short_rows):
+    print(f"edge rows H={H} short={short_rows}", flush=True)
+    deg = lengths(short_rows, H)
+    V = deg.size
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    r = np.random.default_rng(H)
+    col = np.zeros(E, np.int32)  # (one column: the passes only read the offsets)
+    rows = np.repeat(np.arange(V), deg)
+    e16, da16, t16 = f16(3 * r.standard_normal((E, H))), f16(r.standard_normal((E, H))), f16(r.standard_normal((E, H)))
+    lone = np.flatnonzero(deg == 1)[::3]  # rows of one non-zero between others: infinite there, and nowhere else
+    at = rowptr[lone]
+    t16[at] = np.float16(np.inf)
+    da_inf = da16.copy()
+    da_inf[at] = np.float16(np.inf)
+    e16[rowptr[np.flatnonzero(deg > 4)], 0] = np.float16(-np.inf)  # weight zero
+    others = np.ones(V, bool)
+    others[lone] = False
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=1)
+    p = hgnn.hgnn_plan_create(g, 256, 64, 8)
+    ref = oracle.edge_softmax(rowptr, e16.astype(np.float64))
+    t64 = np.where(np.isfinite(t16), t16, 0).astype(np.float64)
+    for plan in (p, None):
+        alpha = torch.full((E, H), -1.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_edge_softmax(g, plan, H, up(e16, dev), alpha)
+        a16 = down(alpha).copy()
+        # exp and the division in fp32, one rounding to fp16: half an ulp, and 2^-20 for what precedes it
+        assert np.all(np.abs(a16.astype(np.float64) - ref) <= ref * (2.0 ** -11 + 2.0 ** -18) + 2.0 ** -24)
+        de = torch.full((E, H), 9.0, dtype=torch.float16, device=dev)
+        for e in (None, e16):
+            hgnn.hgnn_edge_softmax_bwd(g, plan, H, alpha, up(da_inf, dev), de, e=None if e is None else up(e, dev), neg_slope=0.2)
+            a64, d64 = a16.astype(np.float64), da16.astype(np.float64)
+            want = oracle.edge_softmax_bwd(rowptr, a64, d64, e=None if e is None else e.astype(np.float64))
+            mag = np.zeros((V, H))
+            np.add.at(mag, rows, np.abs(a64 * d64))
+            keep = others[rows]
+            compare("de", down(de)[keep], want[keep], (a64 * (np.abs(d64) + mag[rows]) + 2.0 ** -14)[keep])
+        out = torch.full((V, H), 9.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_edge_rowsum(g, plan, H, up(t16, dev), out)
+        got = down(out)
+        assert np.all(np.isinf(got[lone]))
+        compare("row sums", got[others], oracle.edge_rowsum(rowptr, t64)[others], oracle.edge_rowsum(rowptr, np.abs(t64))[others])
+    hgnn.hgnn_plan_destroy(p)
