@@ -24,17 +24,23 @@ struct SortPass {
   __device__ __forceinline__ int digit(uint64_t w) const { return int(uint32_t(w >> shift) & ((1u << bits) - 1u)); }
 };
 
-// Sources of words: load(k, scratch) after prepare(first, n, scratch) by the whole workgroup, whose tile begins at item `first`;
-// scratch is kSortTile ints of LDS.  count(k) is a word with the same digit.
+// Sources of words: load(first, n, mine, scratch, w) gives a lane the items mine, mine + 64, ... of the n of the tile that begins at item `first`
+// (those past the end are the last one again: no load is behind a branch), after prepare(first, n, scratch) by the whole workgroup; scratch is
+// kSortTile ints of LDS.  count(p, k) is a word with the digit of pass p.
 struct SortWords {
   const uint64_t* words;
   __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
-  __device__ __forceinline__ uint64_t load(int64_t k, int, const int*) const { return words[k]; }
-  __device__ __forceinline__ uint64_t count(int64_t k) const { return words[k]; }
+  template <int PER>
+  __device__ __forceinline__ void load(int64_t first, int n, int mine, const int*, uint64_t (&w)[PER]) const {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) w[j] = words[first + min(mine + j * kWave, n - 1)];
+  }
+  __device__ __forceinline__ uint64_t count(const SortPass&, int64_t k) const { return words[k]; }
 };
 
 // Bound by the read of the items.  Lanes of a wave often meet in one bin (behind a pass over the low bits of a column, the entries of a
-// popular column): eight copies of the counts, 17 -> 10.5 us for 5.5 M words of a power-law graph.
+// popular column): eight copies of the counts, 17 -> 10.5 us for 5.5 M words of a power-law graph; with no load behind a branch 7.9 (from a
+// list of edges, rows read only where the digit reaches into them, 16.5 -> 7.1).
 constexpr int kSortCopies = 8, kSortPitch = kSortBins + 1;
 
 template <class Source>
@@ -47,8 +53,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(SortPass p, So
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j) {
     const int64_t k = first + j * kSortThreads;
-    d[j] = -1;
-    if (k < p.n) d[j] = p.digit(src.count(k));
+    d[j] = p.digit(src.count(p, k < p.n ? k : p.n - 1));
+    if (k >= p.n) d[j] = -1;
   }
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j)
@@ -123,33 +129,54 @@ __device__ __forceinline__ uint32_t sort_bin_scan(uint32_t v, uint32_t* s_wave) 
 }
 
 // Ranks of a wave's 64 PER consecutive items among its items of the same digit: lanes of equal digit find each other by ballots, so the order of
-// equal digits is kept.  hist: the wave's counts of the digits, zero beforehand.
+// equal digits is kept.  hist: the wave's counts of the digits, zero beforehand.  Four instructions a bit and item (60 -> 41 an item, the
+// scatter of 5.5 M words 27.4 -> 25.4 us).
+constexpr uint32_t kOrXor = 0xF6;  // a | (b ^ c)
 template <int PER>
 __device__ __forceinline__ void sort_wave_ranks(const SortPass& p, const uint64_t (&w)[PER], uint16_t* hist, uint32_t (&rank)[PER]) {
+  constexpr int N = 2;  // items side by side: a ballot is not read by the instruction behind it
+  static_assert(PER % N == 0, "items in pairs");
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int d = p.digit(w[j]);
-    uint32_t lo = ~0u, hi = ~0u;  // lanes whose digit agrees so far
+  for (int j0 = 0; j0 < PER; j0 += N) {
+    int d[N];
+    uint32_t lo[N], hi[N];  // lanes whose digit differs
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      d[u] = p.digit(w[j0 + u]);
+      lo[u] = hi[u] = 0;
+    }
 #pragma unroll
     for (int b = 0; b < kSortBits; ++b) {
-      const uint32_t bit = uint32_t(__builtin_amdgcn_sbfe(d, b, 1));  // 0 or all ones
-      const uint64_t ones = __ballot(bit != 0);
-      lo &= ~(uint32_t(ones) ^ bit);
-      hi &= ~(uint32_t(ones >> 32) ^ bit);
+      uint32_t bit[N];  // 0 or all ones
+      uint64_t ones[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        bit[u] = uint32_t(__builtin_amdgcn_sbfe(d[u], b, 1));
+        asm("" : "+v"(bit[u]));  // (one instruction for both uses)
+        ones[u] = __ballot(bit[u] != 0);
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        lo[u] = __builtin_amdgcn_bitop3_b32(lo[u], uint32_t(ones[u]), bit[u], kOrXor);
+        hi[u] = __builtin_amdgcn_bitop3_b32(hi[u], uint32_t(ones[u] >> 32), bit[u], kOrXor);
+      }
     }
-    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-    const uint32_t before = hist[d];
-    rank[j] = before + below;
-    wave_sync();
-    if (below == 0) hist[d] = uint16_t(before + __popc(lo) + __popc(hi));
-    wave_sync();
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(~hi[u], __builtin_amdgcn_mbcnt_lo(~lo[u], 0));
+      const uint32_t before = hist[d[u]];
+      rank[j0 + u] = before + below;
+      wave_sync();
+      if (below == 0) hist[d[u]] = uint16_t(before + __popc(~lo[u]) + __popc(~hi[u]));
+      wave_sync();
+    }
   }
 }
 
 // A tile: every wave ranks its 512 consecutive items by digit, the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
-// items of the tile are a run of 16 on average.  5.5 M words: 27.5 us (3.2 TB/s of reads and writes; half of it vector instructions of
-// the ranks), a pass 44 with its count and scan, where a library pass with look-back and its two fills took 52; the words that the first
-// pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 221 us, transpose 180 -> 127; 50 000 words,
+// items of the tile are a run of 16 on average.  5.5 M words: 25.4 us (3.5 TB/s of reads and writes; a third of it vector instructions of
+// the ranks), a pass 39 with its count and scan, where a library pass with look-back and its two fills took 52; the words that the first
+// pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 191 us, transpose 180 -> 114; 50 000 words,
 // which a library merge sort was faster for, 77 -> 70 and 70 -> 52.
 template <class Source>
 __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass p, Source src, uint64_t* __restrict__ out) {
@@ -181,12 +208,10 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   src.prepare(first, n, scratch);
   uint64_t w[kSortPer];
   const int mine = wave * (kWave * kSortPer) + lane;
+  src.load(first, n, mine, scratch, w);
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int i = mine + j * kWave;
-    w[j] = ~uint64_t(0);  // behind all items of the last bin
-    if (i < n) w[j] = src.load(first + i, i, scratch);
-  }
+  for (int j = 0; j < kSortPer; ++j)
+    if (mine + j * kWave >= n) w[j] = ~uint64_t(0);  // behind all items of the last bin
   __syncthreads();
   for (int i = threadIdx.x; i < kSortWaves * kSortBins / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(lds)[i] = 0;
   __syncthreads();
@@ -247,12 +272,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_tile_kernel(SortPass p, int
   src.prepare(first, n, reinterpret_cast<int*>(lds));
   uint64_t w[PER];
   const int mine = wave * (kWave * PER) + lane;
+  src.load(first, n, mine, reinterpret_cast<const int*>(lds), w);
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int i = mine + j * kWave;
-    w[j] = ~uint64_t(0);  // behind all items in every pass
-    if (i < n) w[j] = src.load(first + i, i, reinterpret_cast<const int*>(lds));
-  }
+  for (int j = 0; j < PER; ++j)
+    if (mine + j * kWave >= n) w[j] = ~uint64_t(0);  // behind all items in every pass
   for (; p.shift < last; p.shift += p.bits) {
     p.bits = min(p.bits, last - p.shift);
     __syncthreads();  // the words have been read

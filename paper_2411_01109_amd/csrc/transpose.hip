@@ -26,28 +26,35 @@ __global__ void offsets_kernel(const Key* __restrict__ sorted, int shift, int64_
 }
 
 // COO -> CSR: a word is (row, col, list position) (position_bits = 0: without it), so that one stable sort of the leading fields
-// orders the edges by row, then column, then position in the list; bad receives 1 when an id is out of range (such an edge gets row and
-// column 0)
+// orders the edges by row, then column, then position in the list; bad receives 1 when an id is out of range (which then counts as 0)
 struct CooWords {
   const int *row, *col;
   int nrows, ncols, col_bits, position_bits;
   int* bad;
   __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
-  __device__ __forceinline__ uint64_t word(int64_t k, bool& ok) const {
-    const int r = row[k], c = col[k];
-    ok = r >= 0 && r < nrows && c >= 0 && c < ncols;
-    const uint64_t rc = ok ? (uint64_t(uint32_t(r)) << col_bits) | uint64_t(uint32_t(c)) : 0;
+  __device__ __forceinline__ uint64_t word(int r, int c, int64_t k, bool& ok) const {
+    const bool rok = uint32_t(r) < uint32_t(nrows), cok = uint32_t(c) < uint32_t(ncols);
+    ok = ok && rok && cok;
+    const uint64_t rc = (uint64_t(uint32_t(rok ? r : 0)) << col_bits) | uint64_t(uint32_t(cok ? c : 0));
     return position_bits ? (rc << position_bits) | uint64_t(k) : rc;
   }
-  __device__ __forceinline__ uint64_t load(int64_t k, int, const int*) const {
-    bool ok;
-    const uint64_t w = word(k, ok);
+  template <int PER>
+  __device__ __forceinline__ void load(int64_t first, int n, int mine, const int*, uint64_t (&w)[PER]) const {
+    int r[PER], c[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int64_t k = first + min(mine + j * kWave, n - 1);
+      r[j] = row[k];
+      c[j] = col[k];
+    }
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) w[j] = word(r[j], c[j], first + min(mine + j * kWave, n - 1), ok);
     if (!ok) *bad = 1;
-    return w;
   }
-  __device__ __forceinline__ uint64_t count(int64_t k) const {
-    bool ok;
-    return word(k, ok);
+  __device__ __forceinline__ uint64_t count(const SortPass& p, int64_t k) const {  // (the rows only where the digit reaches into them)
+    bool ok = true;
+    return word(p.shift + p.bits > position_bits + col_bits ? row[k] : 0, col[k], k, ok);
   }
 };
 
@@ -55,7 +62,9 @@ struct CooWords {
 __global__ void coo_keys_kernel(CooWords w, int64_t nnz, uint64_t* __restrict__ keys, int* __restrict__ ids) {
   int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (k >= nnz) return;
-  keys[k] = w.load(k, 0, nullptr);
+  bool ok = true;
+  keys[k] = w.word(w.row[k], w.col[k], k, ok);
+  if (!ok) *w.bad = 1;
   ids[k] = int(k);
 }
 
@@ -265,10 +274,15 @@ struct TransposeWords {
   int nrows, row_bits, position_bits;
   static_assert(kSortPer == kExpandPerThread, "a tile is expanded by its workgroup");
   __device__ __forceinline__ void prepare(int64_t first, int n, int* s_row) const { expand_tile<kSortThreads>(rowptr, nrows, first, n, s_row); }
-  __device__ __forceinline__ uint64_t load(int64_t k, int i, const int* s_row) const {
-    return (((uint64_t(uint32_t(col[k])) << row_bits) | uint64_t(uint32_t(s_row[i]))) << position_bits) | uint64_t(k);
+  template <int PER>
+  __device__ __forceinline__ void load(int64_t first, int n, int mine, const int* s_row, uint64_t (&w)[PER]) const {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = min(mine + j * kWave, n - 1);
+      w[j] = (((uint64_t(uint32_t(col[first + i])) << row_bits) | uint64_t(uint32_t(s_row[i]))) << position_bits) | uint64_t(first + i);
+    }
   }
-  __device__ __forceinline__ uint64_t count(int64_t k) const { return uint64_t(uint32_t(col[k])) << (row_bits + position_bits); }
+  __device__ __forceinline__ uint64_t count(const SortPass&, int64_t k) const { return uint64_t(uint32_t(col[k])) << (row_bits + position_bits); }
 };
 
 // the same in two arrays where the three fields do not fit 64 bits: column keys with positions; rows of all positions
