@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
     {
       const int left = n - own;  // entries of this lane's run
       int c[Rd::E];
-      load_cols<Rd::E>(v, a.col, false, w.block, k + own, RunLeft{left}, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k, own, RunLeft{left}, c);
 #pragma unroll
       for (int m = 0; m < Rd::E; ++m) c[m] = table.handle(c[m], m < left);
 #pragma unroll

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
     {
       const int left = n - own;  // entries of this lane's run
       int c[Rd::E];
-      load_cols<Rd::E>(v, a.col, false, w.block, k + own, RunLeft{left}, c);
+      load_cols<Rd::E>(v, a.col, false, w.block, k, own, RunLeft{left}, c);
       if (NEAR) {
 #pragma unroll
         for (int m = 0; m < Rd::E; m += 4)

@@ -607,7 +607,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
       int c[E], e[E];
       hv_t wv[E];
       float cs[E];
-      load_cols<E>(v, a.col, nt, w.block, i0, run, c);
+      load_cols<E>(v, a.col, nt, w.block, k, own, run, c);
       if (MAPPED) {
         if (nt) load_run<E, true>(a.eid, i0, run, e);
         else load_run<E, false>(a.eid, i0, run, e);

@@ -29,6 +29,7 @@ struct TaskView {
   int width;
   const TaskTotals* totals;  // device; set where the host does not know the numbers (then one block, n_split is a bound)
   int n_split, nb;
+  pos_t nnz;                 // entries of the column array that is walked
   // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
   // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
   // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms with chunks of 128).
@@ -86,6 +87,7 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool ranges, bool come
   v.width = t->width;
   v.n_split = t->n_split;
   v.nb = t->nb;
+  v.nnz = pos_t(t->nnz);
   v.n_slots = ranges ? t->n_rtask : t->n_slots;
   v.rtask = reinterpret_cast<const int4_t*>(t->rtask);
   v.n_rtask = ranges ? t->n_rtask : 0;
@@ -157,6 +159,7 @@ inline TaskView task_view(const TaskScratch& t, const TaskSource& q, int64_t nnz
   v.totals = t.totals;
   v.n_split = int(t.rows);
   v.nb = 1;
+  v.nnz = pos_t(nnz);
   v.rtask = reinterpret_cast<const int4_t*>(t.rtask);
   if (t.rtask) v.rtotals = t.totals;
   const int64_t n = int64_t(kXcds) * range_share(int(t.cap), G) / G + nnz / (q.group_max + 1) + ceil_div(q.nrows + nnz / q.S + 1, G) + ceil_div(q.nrows, int64_t(G) * kZeroTurns) + 24;
@@ -300,27 +303,32 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
 
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these
 // passes draw from HBM, and a gather waits behind it (114 M non-zeros x 64 in eight blocks: 0.81 -> 0.76 ms).
+// A lane's run begins `own` entries behind the round of its lane group.  The ids of entries that do not exist are not defined: 16-bit ids are
+// read as a vector also where a piece ends among them (what follows belongs to other pieces), and where a lane has none at all from the
+// beginning of the round, a line that is asked for anyway.  Read by entry at the ends of pieces they were a chain of four waits, and nearly every
+// wave has a lane there (114 M x 64: SpMM 827 -> 818 us, SDDMM 914 -> 903, attention backward 1254 -> 1241).
 template <int E, class Run>
-__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t i0, Run run, int (&c)[E]) {
+__device__ __forceinline__ void load_cols(const TaskView& v, const int* __restrict__ col, bool nt, int block, pos_t round, int own, Run run, int (&c)[E]) {
   if (v.col16) {
-    const uint16_t* q = v.col16 + i0;
-    const int first = block * v.width;
-    if (run.template all<E>()) {
-      uint16_t t[E];
-      __builtin_memcpy(t, q, sizeof(t));
-#pragma unroll
-      for (int m = 0; m < E; ++m) c[m] = first + int(t[m]);
+    const pos_t at = run.has(0) ? round + pos_t(own) : round;
+    uint32_t t[E / 2];
+    if (at + pos_t(E) <= v.nnz) {
+      __builtin_memcpy(t, v.col16 + at, sizeof(t));
     } else {
+      const pos_t last = v.nnz - 1;
 #pragma unroll
-      for (int m = 0; m < E; ++m) {
-        c[m] = first;
-        if (run.has(m)) c[m] += int(q[m]);
+      for (int m = 0; m < E; m += 2) {
+        const pos_t i = at + pos_t(m);
+        t[m / 2] = uint32_t(v.col16[i < last ? i : last]) | uint32_t(v.col16[i + 1 < last ? i + 1 : last]) << 16;
       }
     }
+    const int first = block * v.width;
+#pragma unroll
+    for (int m = 0; m < E; ++m) c[m] = first + int(m & 1 ? t[m / 2] >> 16 : t[m / 2] & 0xffffu);
     return;
   }
-  if (nt) load_run<E, true>(col, i0, run, c);
-  else load_run<E, false>(col, i0, run, c);
+  if (nt) load_run<E, true>(col, round + pos_t(own), run, c);
+  else load_run<E, false>(col, round + pos_t(own), run, c);
 }
 
 // A table of rows of ld halves.  NEAR: its bytes stay below 2^32 - 8192, rows are read through a buffer descriptor whose
