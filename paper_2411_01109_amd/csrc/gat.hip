@@ -197,11 +197,11 @@ __device__ __forceinline__ void soft_add(Soft<SAVE>& t, const float (&p)[8 / RS]
 // a row change in some lane group; here a wave spends 10 vector instructions per edge with SAVE, 7 without (5.5 M edges, 4 heads of
 // 16).  A call against that walk: 5.5 M edges, 4 heads of 16, SAVE 181 -> 106 us, without 125 -> 83; 114 M edges, one head of
 // 64 in eight blocks 2.16 -> 1.08 ms, 1.48 -> 0.88 ms.
-template <int L, bool NEAR, bool SAVE, int RS>
+template <int L, bool NEAR, bool SAVE, int RS, int MOST>
 __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(GatArgs a, TaskView v, int ncols) {
 #pragma clang fp contract(off)
   constexpr int G = kWave / L;
-  typedef Round<L> Rd;
+  typedef Round<L, MOST> Rd;
   typedef HeadTile<RS> Ht;
   __shared__ __align__(16) int s_handles[G * Rd::PITCH];
   const int lane = threadIdx.x;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;  // the lane that writes its head's scalars
   const int LH = a.D / 8;                         // lanes per head, a power of two
-  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   a.enter_block(w.block);
   if (w.z1 > w.z0) {
     const Soft<SAVE> none;
@@ -457,10 +457,13 @@ __global__ __launch_bounds__(kBlock) void gat_block_merge_kernel(GatArgs a, GatB
 
 template <int L, bool NEAR, bool SAVE>
 static void launch_gat_tasks_l(int lh, unsigned waves, hipStream_t s, const GatArgs& a, const TaskView& v, int ncols) {
-  if (lh == 1) gat_task_kernel<L, NEAR, SAVE, 1><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else if (lh == 2) gat_task_kernel<L, NEAR, SAVE, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else if (lh == 4) gat_task_kernel<L, NEAR, SAVE, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else gat_task_kernel<L, NEAR, SAVE, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v, ncols);
+  with_round<L, NEAR>(v, [&](auto most) {
+    constexpr int M = decltype(most)::value;
+    if (lh == 1) gat_task_kernel<L, NEAR, SAVE, 1, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else if (lh == 2) gat_task_kernel<L, NEAR, SAVE, L < 2 ? L : 2, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else if (lh == 4) gat_task_kernel<L, NEAR, SAVE, L < 4 ? L : 4, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else gat_task_kernel<L, NEAR, SAVE, L < 8 ? L : 8, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+  });
 }
 
 template <bool NEAR, bool SAVE>
@@ -524,7 +527,8 @@ static hgnn_status run_gat_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, Ga
   a.staging_m = a.staging + size_t(t->stage_slots) * size_t(p->max_F);
   a.stage_c = t->stage_mz + size_t(2) * size_t(t->stage_slots) * size_t(p->max_H);
   const int L = pow2_at_least(a.F / 8), G = kWave / L, lh = a.D / 8;
-  const TaskView v = task_view(t, G, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, p->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
+  TaskView v = task_view(t, G, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, p->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
+  v.longer = long_rounds(t->nb, t->nnz, G, 4);
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     const bool near = near_table(ncols, a.ldx);

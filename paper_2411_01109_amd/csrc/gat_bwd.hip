@@ -82,10 +82,10 @@ __device__ __forceinline__ void bwd_stage_store(const GatBwdArgs& a, int64_t slo
 // Bound: the L2s' requests (two per non-zero: the vector, the packed scalars; 56 % of them hit at 5.5 M non-zeros, 92 % at 114 M in
 // blocks) and the vector instructions (busy 69 % and 52 % of the cycles).  The saved backward call against the walk over equal
 // runs: 5.5 M non-zeros, 4 heads of 16 166 -> 131 us; 114 M, one head of 64 1.70 -> 1.26 ms.
-template <int L, bool NEAR, bool VEC, int RS>
+template <int L, bool NEAR, bool VEC, int RS, int MOST>
 __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task_kernel(GatBwdArgs a, TaskView v, int ncols) {
   constexpr int G = kWave / L;
-  typedef Round<L> Rd;
+  typedef Round<L, MOST> Rd;
   typedef HeadTile<RS> Ht;
   __shared__ __align__(16) int s_handles[G * Rd::PITCH];
   __shared__ __align__(16) int s_raw[NEAR ? G * Rd::PITCH : 4];
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
   const int LH = a.D / 8;
-  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   a.enter_block(w.block);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum alpha * x          (VEC)
   if (w.z1 > w.z0) {
@@ -350,10 +350,13 @@ __global__ __launch_bounds__(kBlock) void gat_vtab_kernel(VertexArgs a) {
 
 template <int L, bool NEAR, bool VEC>
 static void launch_bwd_tasks_l(int lh, unsigned waves, hipStream_t s, const GatBwdArgs& a, const TaskView& v, int ncols) {
-  if (lh == 1) gat_bwd_task_kernel<L, NEAR, VEC, 1><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else if (lh == 2) gat_bwd_task_kernel<L, NEAR, VEC, L < 2 ? L : 2><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else if (lh == 4) gat_bwd_task_kernel<L, NEAR, VEC, L < 4 ? L : 4><<<waves, kWave, 0, s>>>(a, v, ncols);
-  else gat_bwd_task_kernel<L, NEAR, VEC, L < 8 ? L : 8><<<waves, kWave, 0, s>>>(a, v, ncols);
+  with_round<L, NEAR>(v, [&](auto most) {
+    constexpr int M = decltype(most)::value;
+    if (lh == 1) gat_bwd_task_kernel<L, NEAR, VEC, 1, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else if (lh == 2) gat_bwd_task_kernel<L, NEAR, VEC, L < 2 ? L : 2, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else if (lh == 4) gat_bwd_task_kernel<L, NEAR, VEC, L < 4 ? L : 4, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+    else gat_bwd_task_kernel<L, NEAR, VEC, L < 8 ? L : 8, M><<<waves, kWave, 0, s>>>(a, v, ncols);
+  });
 }
 
 template <bool NEAR, bool VEC>
@@ -417,7 +420,8 @@ static hgnn_status run_bwd_tasks(const hgnn_plan* q, const hgnn_row_tasks* t, Ga
   a.stage_ds = t->stage_mz;
   a.stage_ld = q->max_F;
   const int L = pow2_at_least(a.F / 8), lh = a.D / 8;
-  const TaskView v = task_view(t, kWave / L, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, q->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, q->llc_bytes));
+  TaskView v = task_view(t, kWave / L, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, q->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, q->llc_bytes));
+  v.longer = long_rounds(t->nb, t->nnz, kWave / L, 8);
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     if (near_table(ncols, a.ldx)) launch_bwd_tasks<true, VEC>(L, lh, unsigned(waves), s, a, v, ncols);

@@ -40,14 +40,14 @@ constexpr int kTile = 256;  // non-zeros per wave in the kernels that run withou
 // head of 64 in blocks: 1.06 -> 0.92 ms; 5.5 M, four heads of 16: the same (58 us); on power-law graphs of 20 to 31 M, where the
 // gathers miss the L2s and the results of a row no longer fill lines with their neighbours', 1 to 6 % slower (31 M: one head of
 // 64 338 -> 350 us, four of 16 391 -> 393).
-template <int L, bool NEAR, bool MASK, int RS, int VW>
+template <int L, bool NEAR, bool MASK, int RS, int VW, int MOST>
 __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(SddmmArgs a, TaskView v) {
   constexpr int G = kWave / L;
   typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
-  typedef Round<L> Rd;
+  typedef Round<L, MOST> Rd;
   typedef HeadTile<RS> Ht;
   __shared__ __align__(16) int s_handles[G * Rd::PITCH];
-  __shared__ __align__(16) half_t s_results[kWave * Rd::R];  // [G][R * H]: H is at most L
+  extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const int g = lane / L, l = lane % L;
   const int f0 = VW * l;
@@ -69,9 +69,9 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
     for (int i = 0; i < VW; ++i) d = fmaf(float(p[i]), float(q[i]), d);
     return d;
   };
-  const TaskWave w = task_enter<L>(v, blockIdx.x, g);
+  const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   int* const s_hnd = s_handles + g * Rd::PITCH;
-  half_t* const s_out = s_results + g * (Rd::R * L);
+  half_t* const s_out = reinterpret_cast<half_t*>(smem) + g * (Rd::R * a.H);  // [G][R * H]
   const RowTable<NEAR> table(a.Vt, a.ncols, a.ldv, f0c);
   const int row = w.row >= 0 ? w.row : 0;
   const hv_t ur = masked(*reinterpret_cast<const hv_t*>(a.U + int64_t(row) * a.ldu + f0c));
@@ -315,19 +315,23 @@ static void launch_edge(int L, dim3 grid, size_t lds, hipStream_t s, const Sddmm
 
 template <int L, bool NEAR, int VW>
 static void launch_dot_tasks_l(int lh, bool mask, unsigned waves, hipStream_t s, const SddmmArgs& a, const TaskView& v) {
-  if constexpr (VW == 8) {
-    if (mask) {
-      sddmm_task_kernel<L, NEAR, true, L < 8 ? L : 8, VW><<<waves, kWave, 0, s>>>(a, v);
-      return;
+  with_round<L, NEAR && VW == 8>(v, [&](auto most) {
+    constexpr int M = decltype(most)::value;
+    const size_t lds = size_t(kWave / L) * size_t(Round<L, M>::R) * size_t(a.H) * sizeof(half_t);  // results
+    if constexpr (VW == 8) {
+      if (mask) {
+        sddmm_task_kernel<L, NEAR, true, L < 8 ? L : 8, VW, M><<<waves, kWave, lds, s>>>(a, v);
+        return;
+      }
+      if (lh == 1) {
+        sddmm_task_kernel<L, NEAR, false, 1, VW, M><<<waves, kWave, lds, s>>>(a, v);
+        return;
+      }
     }
-    if (lh == 1) {
-      sddmm_task_kernel<L, NEAR, false, 1, VW><<<waves, kWave, 0, s>>>(a, v);
-      return;
-    }
-  }
-  if (lh == 2) sddmm_task_kernel<L, NEAR, false, L < 2 ? L : 2, VW><<<waves, kWave, 0, s>>>(a, v);
-  else if (lh == 4) sddmm_task_kernel<L, NEAR, false, L < 4 ? L : 4, VW><<<waves, kWave, 0, s>>>(a, v);
-  else sddmm_task_kernel<L, NEAR, false, L < 8 ? L : 8, VW><<<waves, kWave, 0, s>>>(a, v);
+    if (lh == 2) sddmm_task_kernel<L, NEAR, false, L < 2 ? L : 2, VW, M><<<waves, kWave, lds, s>>>(a, v);
+    else if (lh == 4) sddmm_task_kernel<L, NEAR, false, L < 4 ? L : 4, VW, M><<<waves, kWave, lds, s>>>(a, v);
+    else sddmm_task_kernel<L, NEAR, false, L < 8 ? L : 8, VW, M><<<waves, kWave, lds, s>>>(a, v);
+  });
 }
 
 template <bool NEAR, int VW>
@@ -494,7 +498,8 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
       a.delta = p->bdelta;
     }
     const int lanes = pow2_at_least((F + vw - 1) / vw);
-    const TaskView v = task_view(t, kWave / lanes, at_ranges(t, kRangesDot, int64_t(g->ncols) * F * 2, p->l2_bytes), comes_back(false, int64_t(g->ncols) * ldv * 2, p->llc_bytes), false);
+    TaskView v = task_view(t, kWave / lanes, at_ranges(t, kRangesDot, int64_t(g->ncols) * F * 2, p->l2_bytes), comes_back(false, int64_t(g->ncols) * ldv * 2, p->llc_bytes), false);
+    v.longer = long_rounds(t->nb, t->nnz, kWave / lanes, 4 + 2 * H);
     const int waves = v.first_wave[t->nb];
     if (waves > 0) {
       const bool near = near_table(g->ncols, ldv);

@@ -739,9 +739,10 @@ constexpr int kRowsumL = 8;  // lanes per group
 template <int H>
 __global__ __launch_bounds__(kWave) void rowsum_task_kernel(RowsumArgs a, TaskView v) {
   typedef _Float16 hv_t __attribute__((ext_vector_type(H)));
-  constexpr int E = Round<kRowsumL>::E;
+  typedef Round<kRowsumL, 32> Rd;
+  constexpr int E = Rd::E;
   const int lane = threadIdx.x, l = lane % kRowsumL;
-  const TaskWave w = task_enter<kRowsumL>(v, blockIdx.x, lane / kRowsumL);
+  const TaskWave w = task_enter<kRowsumL, Rd::R>(v, blockIdx.x, lane / kRowsumL);
   float s[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) s[h] = 0.f;

@@ -542,9 +542,9 @@ __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t fir
 // behind an edge-id map.
 // ---------------------------------------------------------------------------------------------------
 // HV: heads of the edge values where they are read as one vector (1, 2, 4 or 8; aligned to it), 0 = any number.
-template <int L, int WM, int HV>
+template <int L, int WM, int HV, int MOST>
 struct TaskLds {
-  typedef Round<L> Rd;
+  typedef Round<L, MOST> Rd;
   static constexpr int G = kWave / L;
   static constexpr int kHandles = G * Rd::PITCH * 4;
   typedef typename std::conditional<WM == 2 || HV == 0, float, half_t>::type factor_t;
@@ -562,11 +562,11 @@ __device__ __forceinline__ auto run_of(pos_t i0, pos_t end, int left) {
   else return RunLeft{left};
 }
 
-template <int L, int WM, bool NEAR, bool MAPPED, int HV, class Enter>
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, int MOST, class Enter>
 __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int ncols, Enter&& enter) {
   constexpr int G = kWave / L;
-  typedef Round<L> Rd;
-  typedef TaskLds<L, WM, HV> Lds;
+  typedef Round<L, MOST> Rd;
+  typedef TaskLds<L, WM, HV, MOST> Lds;
   typedef typename Lds::factor_t factor_t;
   constexpr int NV = HV > 0 ? HV : 1;
   constexpr int E = Rd::E;
@@ -698,15 +698,16 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
 
 // LOOP: 1 = the number of tasks is only known on the device, a wave takes several (the loop costs registers: not with a plan); 2 = also
 // pieces at column ranges (their branch costs the others 1 to 2 %)
-template <int L, int WM, bool NEAR, bool MAPPED, int HV, int LOOP>
+template <int L, int WM, bool NEAR, bool MAPPED, int HV, int LOOP, int MOST>
 __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) void spmm_task_kernel(SpmmArgs a, TaskView v, int ncols) {
+  constexpr int R = Round<L, MOST>::R;
   if (LOOP) {
     const RangeWaves ranges = LOOP == 2 ? range_waves<kWave / L>(v) : RangeWaves{0, 0, 0};
     const int n = ranges.waves + task_waves<kWave / L>(v);
     for (int wid = blockIdx.x; wid < n; wid += gridDim.x)
-      spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L, LOOP>(v, wid, g, ranges); });
+      spmm_task<L, WM, NEAR, MAPPED, HV, MOST>(a, v, ncols, [&](int g) { return task_enter<L, R, LOOP>(v, wid, g, ranges); });
   } else {
-    spmm_task<L, WM, NEAR, MAPPED, HV>(a, v, ncols, [&](int g) { return task_enter<L>(v, blockIdx.x, g); });
+    spmm_task<L, WM, NEAR, MAPPED, HV, MOST>(a, v, ncols, [&](int g) { return task_enter<L, R>(v, blockIdx.x, g); });
   }
 }
 
@@ -1325,18 +1326,21 @@ static void launch_tasks_l(int wm, bool mapped, unsigned waves, size_t least_lds
   const dim3 grid(waves);
 #define HGNN_TASKS(WM, MAPPED, HV)                                                                                          \
   do {                                                                                                                      \
-    const size_t lds = std::max(TaskLds<L, WM, HV>::bytes(a.H), least_lds);                                                                 \
-    if constexpr (WM < 2) {                                                                                                 \
-      if (v.rtotals) {                                                                                                      \
-        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 2><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
-        break;                                                                                                              \
+    with_round<L, NEAR && (WM == 0 || HV == 1 || (WM == 1 && (HV == 2 || HV == 4)))>(v, [&](auto most) {                    \
+      constexpr int M = decltype(most)::value;                                                                              \
+      const size_t lds = std::max(TaskLds<L, WM, HV, M>::bytes(a.H), least_lds);                                            \
+      if constexpr (WM < 2) {                                                                                               \
+        if (v.rtotals) {                                                                                                    \
+          spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 2, M><<<grid, kWave, lds, s>>>(a, v, ncols);                            \
+          return;                                                                                                           \
+        }                                                                                                                   \
+        if (v.totals) {                                                                                                     \
+          spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 1, M><<<grid, kWave, lds, s>>>(a, v, ncols);                            \
+          return;                                                                                                           \
+        }                                                                                                                   \
       }                                                                                                                     \
-      if (v.totals) {                                                                                                       \
-        spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 1><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
-        break;                                                                                                              \
-      }                                                                                                                     \
-    }                                                                                                                       \
-    spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 0><<<grid, kWave, lds, s>>>(a, v, ncols);                                 \
+      spmm_task_kernel<L, WM, NEAR, MAPPED, HV, 0, M><<<grid, kWave, lds, s>>>(a, v, ncols);                                \
+    });                                                                                                                     \
   } while (0)
   const int hv = (reinterpret_cast<uintptr_t>(a.w) & uintptr_t(2 * a.H - 1)) == 0 ? a.H : 0;
   if (wm == 0) {
@@ -1472,6 +1476,9 @@ static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const Ta
   }
 }
 
+// LDS for each non-zero of a round: its handle and its factors
+static int task_entry_bytes(int wm, const SpmmArgs& a) { return 4 + (wm == 0 ? 0 : a.H * (wm == 1 ? 2 : 4)); }
+
 static bool mostly_ranges(const hgnn_row_tasks* t) { return int64_t(t->n_rtask) * 320 >= t->nnz; }
 
 // Pass 1 and pass 2 of the discretized SpMM over the row tasks t of plan p, whose column array `a.col` indexes (with a.eid,
@@ -1484,7 +1491,8 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
   const bool mapped = wm != 0 && a.w && a.eid;
   // (the comparison variant with atomic additions rounds each to fp16: as many as there are segments)
   const bool ranges = !a.atomic_y && at_ranges(t, mapped ? kRangesMapped : kRangesSpmm, int64_t(ncols) * a.F * 2, p->l2_bytes);
-  const TaskView v = task_view(t, G, ranges, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
+  TaskView v = task_view(t, G, ranges, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
+  v.longer = long_rounds(t->nb, t->nnz, G, task_entry_bytes(wm, a));
   const int waves = v.first_wave[t->nb];
   if (a.atomic_y && v.n_split > 0) {
     launch_zero_split(L, s, a, v);
@@ -1547,7 +1555,8 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   const int L = pow2_at_least((a.F + 7) / 8);
   const bool mapped = a.w && a.eid;
   int64_t grid = 0;
-  const TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
+  TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
+  v.longer = long_rounds(1, g->nnz, kWave / L, task_entry_bytes(a.w ? 1 : 0, a));
   a.staging = reinterpret_cast<half_t*>(t.staging);
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;

@@ -30,6 +30,7 @@ struct TaskView {
   const TaskTotals* totals;  // device; set where the host does not know the numbers (then one block, n_split is a bound)
   int n_split, nb;
   pos_t nnz;                 // entries of the column array that is walked
+  bool longer;               // host: rounds of 64 (long_rounds)
   // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
   // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
   // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms with chunks of 128).
@@ -51,6 +52,28 @@ struct TaskView {
 // Small graphs stay in the caches and end on long pieces that way (2.1 M, SDDMM 41.7 / 45.1), where nearly all pieces are long there is
 // nothing to come back to (6 M, 35 a row: SpMM 124.7 / 127.5); plan-free calls, whose numbers are on the device, gain nothing.
 inline bool comes_back(bool mapped, int64_t table_bytes, int64_t llc) { return mapped || table_bytes > llc / 8 * 3; }
+
+// ---- rounds: up to R consecutive non-zeros of a lane group, whose table handles and factors are put in LDS together ----
+// A lane reads E consecutive column ids as vectors, so a group's round is one or two cache lines of the column array.
+// Read 32 bytes at a time, the lines were asked for four times and the gathers waited for each (114 M non-zeros: 832 ->
+// 782 us).  The rows of the LDS tables are 4 entries longer than a round: the groups then read different banks.
+// MOST: 32, or 64 where lane groups have longer pieces: a wave is without gathers while it waits for ids, half as often then.  us, rounds of
+// 32 / 64: 114 M x 64 in blocks, SpMM 818 / 789, with values 957 / 913, through the map 1601 / 1569, SDDMM 905 / 847, attention forward 1106 /
+// 1083, backward 1242 / 1211; 62 M x 128 1326 / 1307; plan-free, 31 M x 64 382 / 376, through the map 677 / 656 (rounds of 128: 782, 920, 1586,
+// 1180, 1060, 1225; 1318; 370, 674).
+template <int L, int MOST>
+struct Round {
+  static constexpr int LC = L < 8 ? L : 8;          // lanes that read ids (the others of a wider group repeat them)
+  static constexpr int R = L < 4 ? 8 * L : (L < 8 ? 32 : MOST);
+  static constexpr int E = R / LC;
+  static constexpr int PITCH = R + 4;               // ints per group in the handle table
+};
+// host: whether a call takes rounds of 64 whose non-zeros take entry_bytes of LDS each.  Not where all pieces of lane groups have 32 non-zeros at
+// most (5.5 M non-zeros x 4 heads: SpMM 57 / 62 us, SDDMM 59 / 71; 1.3 M x 42 27.1 / 27.9; pieces at column ranges, which may be longer, are too few
+// there), nor where a wave would take more than 6.5 KB, which keeps waves out.
+inline bool long_rounds(int nb, int64_t nnz, int G, int entry_bytes) {
+  return (nb > 1 || task_group_max(nnz) > 32) && G <= kWave / 8 && G * 64 * entry_bytes <= 6656;
+}
 
 // pieces at column ranges per XCD, whole waves of G lane groups of them
 __host__ __device__ inline int range_share(int n, int G) { return int((pos_t(n) + kXcds * G - 1) / (kXcds * G)) * G; }
@@ -107,17 +130,17 @@ inline TaskView task_view(const hgnn_row_tasks* t, int G, bool ranges, bool come
   return v;
 }
 
-// ---- rounds: up to R consecutive non-zeros of a lane group, whose table handles and factors are put in LDS together ----
-// A lane reads E consecutive column ids as vectors, so a group's round is one or two cache lines of the column array.
-// Read 32 bytes at a time, the lines were asked for four times and the gathers waited for each (114 M non-zeros: 832 ->
-// 782 us).  The rows of the LDS tables are 4 entries longer than a round: the groups then read different banks.
-template <int L>
-struct Round {
-  static constexpr int LC = L < 8 ? L : 8;          // lanes that read ids (the others of a wider group repeat them)
-  static constexpr int R = L < 4 ? 8 * L : 32;
-  static constexpr int E = R / LC;
-  static constexpr int PITCH = R + 4;               // ints per group in the handle table
-};
+// f(the most non-zeros of a round) for a launch; the long form exists for tables below 4 GB
+template <int L, bool NEAR, class F>
+inline void with_round(const TaskView& v, F&& f) {
+  if constexpr (L >= 8 && NEAR) {
+    if (v.longer) {
+      f(std::integral_constant<int, 64>());
+      return;
+    }
+  }
+  f(std::integral_constant<int, 32>());
+}
 
 // The entries of a run that exist, m = 0, 1, ...: by what is left (which may be negative), or by position.
 struct RunLeft {
@@ -205,7 +228,7 @@ struct TaskWave {
   const int* zrow;  // the block's empty rows
   pos_t z0, z1;     // z1 > z0: entries [z0, z1) of them, nothing else
   pos_t beg, end;   // this lane group's first non-zero and the end of the piece
-  pos_t span, step; // non-zeros per round of this group (a multiple of 8, at most Round<L>::R), and from one round to the next
+  pos_t span, step; // non-zeros per round of this group (a multiple of 8, at most its R), and from one round to the next
   int row, slot;    // row -1: no piece for this lane group
 };
 
@@ -220,7 +243,7 @@ __device__ __forceinline__ RangeWaves range_waves(const TaskView& v) {  // witho
   const int n = v.rtotals ? v.rtotals->n_range : 0, share = range_share(n, G);
   return RangeWaves{share / G * kXcds, share, n};
 }
-template <int L, int FREE>
+template <int L, int R, int FREE>  // R: of the Round
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g, const RangeWaves& ranges) {
   constexpr int G = kWave / L;
   TaskWave w;
@@ -236,7 +259,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
     w.end = t[0] + t[1];
     w.row = t[2];
     w.slot = t[3];
-    w.span = w.step = Round<L>::R;
+    w.span = w.step = R;
     return w;
   }
   int b = 0, i = wid;
@@ -286,7 +309,7 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   w.end = t[0] + (t[1] & 0xffff);
   w.row = t[2];
   w.slot = t[3];
-  w.span = w.step = Round<L>::R;
+  w.span = w.step = R;
   if (w.whole) {  // the lane groups share the piece in equal runs
     const pos_t each = (((t[1] & 0xffff) + G - 1) / G + 7) & ~7;
     if (each < w.span) w.span = each;
@@ -296,9 +319,9 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   return w;
 }
 
-template <int L>
+template <int L, int R>
 __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g) {
-  return task_enter<L, 0>(v, wid, g, RangeWaves{v.first_wave[0], v.rshare, v.n_rtask});
+  return task_enter<L, R, 0>(v, wid, g, RangeWaves{v.first_wave[0], v.rshare, v.n_rtask});
 }
 
 // The column ids of a round.  Blocks of the plan's own cut carry them in 16 bits: the ids are the one stream that these

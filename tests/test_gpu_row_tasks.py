@@ -51,6 +51,50 @@ def test_piece_borders(hgnn, dev, F, H, S, nb, what):
     hgnn.hgnn_plan_destroy(p)
 
 
+@pytest.mark.parametrize("F,H,what", [(64, 1, "plain"), (64, 1, "w"), (64, 2, "map"), (64, 4, "w"), (64, 4, "map"), (64, 8, "w"), (128, 1, "norm"), (128, 8, "w"),
+                                      (256, 4, "map"), (512, 1, "norm"), (16, 1, "w")])
+def test_rounds_of_blocks_at_borders(hgnn, dev, F, H, what):
+    """Pieces of column blocks around a batch of ids, a round of 64 and the longest lane-group piece (256), SpMM and dot products."""
+    print(f"rounds F={F} H={H} {what}", flush=True)
+    lens = (0, 1, 7, 8, 9, 31, 32, 33, 39, 40, 41, 63, 64, 65, 95, 96, 97, 127, 128, 129, 191, 193, 255, 256)
+    V, half = 64 * len(lens), 32 * len(lens)
+    r = np.random.default_rng(F + H)
+    pick = lambda n, lo: np.sort(r.choice(half, n, replace=False)) + lo  # noqa: E731
+    parts = [np.concatenate([pick(lens[i % len(lens)], 0), pick(lens[(i // len(lens) + i) % len(lens)], half)]) for i in range(V)]
+    rowptr = np.concatenate([[0], np.cumsum([q.size for q in parts])]).astype(np.int32)
+    col = np.concatenate(parts).astype(np.int32)
+    X, U = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
+    w = f16(r.standard_normal((col.size, H))) if what in ("w", "map") else None
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    eid = None
+    if what == "map":  # (a graph that carries a map need not come from hgnn_transpose)
+        eid = r.permutation(col.size).astype(np.int32)
+        g = hgnn.Csr(up(rowptr, dev), up(col, dev), eid=up(eid, dev))
+    p = hgnn.hgnn_plan_create(g, 256, F, H, col_blocks=2)
+    Y = torch.full((V, F), 3.0, dtype=torch.float16, device=dev)
+    kw = {}
+    if what == "norm":
+        cs, rs = (r.uniform(0.5, 2, V).astype(np.float32) for _ in range(2))
+        kw = {"row_scale": up(rs, dev), "col_scale": up(cs, dev)}
+    hgnn.hgnn_spmm_discretized_fused(p, g, None if w is None else up(w, dev), H, up(X, dev), Y, F=F, **kw)
+    if what == "norm":
+        dense = np.zeros((V, V))
+        np.add.at(dense, (np.repeat(np.arange(V), np.diff(rowptr)), col), 1.0)
+        ref = rs[:, None].astype(np.float64) * (dense @ (cs[:, None].astype(np.float64) * X.astype(np.float64)))
+        sabs = rs[:, None].astype(np.float64) * (dense @ (cs[:, None].astype(np.float64) * np.abs(X.astype(np.float64))))
+    else:
+        ref, sabs = oracle.spmm(rowptr, col, X, w=w, H=H if w is not None else 1, want_sabs=True, **({"eid": eid} if eid is not None else {}))
+    compare("rounds of blocks", down(Y), ref, sabs)
+    D = F // H
+    if what != "map" and D % 8 == 0:
+        e = torch.full((col.size, H), 7.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, H, D, up(U, dev), up(X, dev), e)
+        row = np.repeat(np.arange(V), np.diff(rowptr))
+        mag = (np.abs(U[row].astype(np.float64)) * np.abs(X[col].astype(np.float64))).reshape(-1, H, D).sum(-1)
+        compare("dot products of blocks", down(e), oracle.sddmm_dot(rowptr, col, U, X, H=H), mag)
+    hgnn.hgnn_plan_destroy(p)
+
+
 @pytest.mark.parametrize("H", [1, 4])
 def test_table_beyond_4_gib(hgnn, dev, H):
     """Rows 2.2 M halves apart: the table spans 4.8 GB, its rows are read by 64-bit addresses."""
