@@ -12,6 +12,7 @@
 // columns 8*(l / 16) .. +7.  Operand B is 32 x 16: lane l holds column l % 16, rows 8*(l / 16) .. +7.
 // The 16 x 16 result: lane l holds column l % 16, rows 4*(l / 16) .. +3.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 
 #include "common.h"
@@ -289,7 +290,7 @@ struct WgradArgs {
   int64_t ldx;
   const half_t* dY;
   int64_t ldy;
-  float* part;  // [gridDim.x][K][F] fp32
+  float* part;  // [gridDim.x][tiles of 16 x 16 of dW][256] fp32
 };
 
 constexpr int kWgradRows = 32;  // rows of X and dY per step
@@ -318,7 +319,8 @@ __device__ __forceinline__ half8_t wgrad_column(const half_t* tile, int pitch, i
 // atomics, the same bits on every run.  WA = WB = 2 lets X and dY of up to 128 columns be read once; the form before
 // (a 64 x 64 block per wave, columns picked by 2-byte LDS reads, a partial per wave) read both twice and was bound by
 // those reads.  The teams' blocks are added by all teams, a share of the columns each, which also write it: 4096 rows 64 x 64 6.6 -> 4.7 us
-// (one team that added the others in turn and wrote), 262 144 rows 16.9 -> 14.8.
+// (one team that added the others in turn and wrote).  They are written as the lanes hold them, tile after tile, 16 bytes
+// a lane; row by row, 4 bytes a lane in pieces of 64 bytes, 262 144 rows took 0.5 us more.
 template <int WA, int WB>
 __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
   constexpr int WT = WA * WB, WR = 4 / WT;     // waves in a team, teams
@@ -419,18 +421,18 @@ __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
       }
     }
   }
-  float* out = a.part + int64_t(blockIdx.x) * a.K * a.F;
-  const int i = lane & 15, q = lane >> 4;
+  // tile after tile of 16 x 16 as the lanes hold it, 16 bytes each
+  const int tk = (a.K + 15) / 16, tf = (a.F + 15) / 16;
+  float* const out = a.part + (int64_t(blockIdx.x) * tk * tf * kWave + lane) * 4;
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
     if (WR > 1 && x / XS != team) continue;
+    const int tx = kc0 / 16 + 4 * wa + x;
 #pragma unroll
-    for (int y = 0; y < 4; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int k = kc0 + 64 * wa + 16 * x + 4 * q + r, f = fc0 + 64 * wb + 16 * y + i;
-        if (k < a.K && f < a.F) out[int64_t(k) * a.F + f] = acc[x][y][r];
-      }
+    for (int y = 0; y < 4; ++y) {
+      const int ty = fc0 / 16 + 4 * wb + y;
+      if (tx < tk && ty < tf) __builtin_memcpy(out + (int64_t(tx) * tf + ty) * (kWave * 4), &acc[x][y], 16);  // (the workspace is 4-byte aligned)
+    }
   }
 }
 
@@ -484,12 +486,15 @@ __global__ __launch_bounds__(kWave * kSmallWaves) void wgrad_small_kernel(WgradA
   if (k < a.K && f < a.F) dW[int64_t(k) * lddw + f] = s;
 }
 
-// out[k*out_ld + f] = sum over the partials j (part_stride apart) of in[j][e], e = k*F + f < elems; from element `split` on the
-// result goes to out2[e - split].  A workgroup takes 64 elements; its kSumSlices slices add a strided share of the partials
+// TILES: out[k*out_ld + f] = sum over the partials j (part_stride apart) of in[j][e], e in the tiles of wgrad_kernel (elems = K: rows of the
+// result); else out[e], and from element `split` on out2[e - split].  A workgroup takes 64 elements; its kSumSlices slices add a strided share of the partials
 // each and the slice sums are added in slice order: a fixed order whatever the launch, in one launch (two rounds of
-// launches cost 4-5 us each on the smallest layers, more than the addition).
+// launches cost 4-5 us each on the smallest layers, more than the addition).  Bound by the latency of a slice's loads:
+// all up to 16 are in flight together, also where there are fewer (224 partials of 64 x 64, 14 a slice, 8 at a time and
+// the rest one by one: 11.4 us with the kernel before it, now 10.0).
 constexpr int kSumSlices = 16;
 
+template <bool TILES>
 __global__ __launch_bounds__(kWave * kSumSlices) void partial_sum_kernel(const float* __restrict__ in, int64_t part_stride, int nparts,
                                                                          int64_t elems, int F, float* __restrict__ out, int64_t out_ld,
                                                                          int64_t split, float* __restrict__ out2) {
@@ -497,21 +502,44 @@ __global__ __launch_bounds__(kWave * kSumSlices) void partial_sum_kernel(const f
   const int x = threadIdx.x & (kWave - 1), y = threadIdx.x / kWave;
   const int64_t e = int64_t(blockIdx.x) * kWave + x;
   float s = 0.f;
-  if (e < elems) {
-#pragma unroll 8
-    for (int j = y; j < nparts; j += kSumSlices) s += in[int64_t(j) * part_stride + e];
+  if (e < (TILES ? part_stride : elems)) {
+    constexpr int U = 16;  // loads in flight: a thread's chain of them is the time
+    int j = __builtin_amdgcn_readfirstlane(y);  // a slice is a wave
+    float v[U];
+    for (; j + (U - 1) * kSumSlices < nparts; j += U * kSumSlices) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = in[int64_t(j + u * kSumSlices) * part_stride + e];
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += v[u];
+    }
+    // the last r < U of them by the bits of r, also together
+    const int r = j < nparts ? (nparts - j + kSumSlices - 1) / kSumSlices : 0;
+#pragma unroll
+    for (int b = U / 2; b > 0; b /= 2) {
+#pragma unroll
+      for (int u = 0; u < b; ++u) v[U - 2 * b + u] = 0.f;
+      if (r & b) {
+#pragma unroll
+        for (int u = 0; u < b; ++u) v[U - 2 * b + u] = in[int64_t(j + u * kSumSlices) * part_stride + e];
+        j += b * kSumSlices;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U - 1; ++u) s += v[u];
   }
   red[y][x] = s;
   __syncthreads();
-  if (y != 0 || e >= elems) return;
+  if (y != 0) return;
   s = 0.f;
 #pragma unroll
   for (int j = 0; j < kSumSlices; ++j) s += red[j][x];
-  if (e >= split) {
-    out2[e - split] = s;
-  } else {
-    const int64_t k = e / F;
-    out[k * out_ld + (e - k * F)] = s;
+  if (TILES) {
+    const int tf = (F + 15) / 16, tile = int(e >> 8), lane = int(e >> 2) & (kWave - 1);
+    const int k = 16 * (tile / tf) + 4 * (lane >> 4) + int(e & 3), f = 16 * (tile % tf) + (lane & 15);
+    if (k < elems && f < F) out[int64_t(k) * out_ld + f] = s;
+  } else if (e < elems) {
+    if (e >= split) out2[e - split] = s;
+    else out[e] = s;
   }
 }
 
@@ -756,27 +784,38 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   // up to 64 columns on a side: one wave wide; else two, so that up to 128 columns are read once
   const int WA = K <= 64 ? 1 : 2, WB = F <= 64 ? 1 : 2;
   const int kb = int(ceil_div(K, 64 * WA)), fb = int(ceil_div(F, 64 * WB)), WR = 4 / (WA * WB);
-  // three workgroups per compute unit over all blocks of dW, but no more than there are steps of rows and no more
-  // partial results than the workspace holds
-  int64_t parts = std::max<int64_t>(1, int64_t(3) * kCus / (int64_t(kb) * fb));
-  parts = std::min<int64_t>(parts, wgrad_parts(K, F));
-  parts = std::max<int64_t>(1, std::min<int64_t>(parts, ceil_div(n, int64_t(kWgradRows) * WR)));
+  const int64_t tiles = ceil_div(K, 16) * ceil_div(F, 16), blocks = int64_t(kb) * fb, steps = ceil_div(n, int64_t(kWgradRows) * WR);
+  // Partial results: a step of a workgroup takes some 0.6 us, a partial result about 4.5 ns and 0.45 ns for each of its
+  // tiles (written and added): steps / parts * step + parts * partial is least at the root below.  us with it and with
+  // as many partials as are resident: 25 000 rows of 64 x 64 7.5 and 7.8, 100 000 10.0 and 16.1, of 128 x 128 12.5 and
+  // 19.0, 16.8 and 20.4, 50 000 of 504 x 64 17.7 and 19.8; beyond some 10^6 rows the two are the same.
+  int64_t parts = std::llround(std::sqrt(1400. * double(steps) / double(10 + tiles)));
+  // a single block: whole rounds of one workgroup per compute unit (300 000 rows of 64 x 64: 256 17.7, 288 19.4, 512 19.1)
+  if (blocks == 1 && parts > kCus && parts < 2 * kCus) parts = kCus;
+  // No more than the workspace holds (64 at least of sides of 8: a quarter of the tile) and than there are steps, three
+  // workgroups per compute unit of 128 x 128 values and two of the others (233 000 rows of 608 x 64: 480 of them 62.4,
+  // 510 74.6, 680 and more 67.4); eight XCDs take the workgroups in turn, so a multiple of eight leaves the blocks of the
+  // same rows on one L2
+  int64_t most = std::min<int64_t>((WR == 1 ? 3 : 2) * kCus / blocks, int64_t(wgrad_parts(K, F)) * K * F / (tiles * 256));
+  if (most >= 16) most = most / 8 * 8;
+  if (parts >= 16) parts = (parts + 7) / 8 * 8;
+  parts = std::max<int64_t>(1, std::min(std::min(parts, most), steps));
   WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
   // few rows: one launch without partial results, up to the rows at which fetching them in 32-byte pieces costs what the
   // second launch and the partial results do, later the larger dW is.  us behind the kernel that wrote dY, one launch / two:
   //   K x F         1000        1500        2000        2500        3000        4096        6000 rows
-  //   16 x 16     2.8 / 5.0   3.1 / 5.1   3.6 / 5.2   4.1 / 5.3   4.5 / 5.4   5.4 / 5.5   6.6 / 5.8
-  //   32 x 32     3.2 / 5.5   4.0 / 5.4   4.5 / 5.4   5.4 / 5.7   6.0 / 5.8   7.5 / 5.8   9.3 / 6.2
-  //   64 x 16     3.3 / 5.2   4.1 / 5.2   4.6 / 5.4   5.6 / 5.5   6.0 / 5.6   7.3 / 5.7  10.0 / 6.0
-  //   64 x 64     4.3 / 5.7   5.3 / 5.7   6.6 / 5.8   7.6 / 6.0   8.4 / 6.1  11.1 / 6.2  14.6 / 6.6
-  //   128 x 64    4.2 / 6.0   5.3 / 6.3   6.5 / 6.5   7.5 / 6.8   8.3 / 7.0  11.0 / 7.5  14.4 / 8.6
-  //   128 x 128   4.6 / 7.0   5.8 / 7.7   7.2 / 8.4   8.2 / 9.2   9.1 / 9.9  12.0 / 10.4 16.6 / 12.4
-  //   256 x 128   4.6 / 8.1   5.8 / 9.2   7.1 / 10.4  8.3 / 11.5  9.0 / 13.1 11.7 / 13.7 15.4 / 18.8
-  //   512 x 64    4.3 / 6.8   5.4 / 7.5   6.4 / 8.0   7.4 / 8.7   8.2 / 9.4  10.3 / 10.6 14.2 / 13.8
-  //   256 x 256   5.3 / 11.4  6.8 / 13.3  8.4 / 15.8  9.9 / 18.4 10.8 / 20.9 14.3 / 21.4 19.4 / 20.3
-  // Beyond one workgroup per compute unit they queue: 608 x 128 (304) at 2000, 3000, 4096 rows 9.2, 15.1, 23.4 against 18.5, 19.1, 19.3
+  //   16 x 16     3.4 / 5.1   3.4 / 5.2   3.8 / 5.1   4.3 / 5.1   4.8 / 5.2   5.4 / 5.2   6.9 / 5.3
+  //   32 x 32     3.2 / 5.4   4.0 / 5.2   4.4 / 5.3   5.2 / 5.4   5.8 / 5.3   7.3 / 5.3   9.0 / 5.4
+  //   64 x 16     3.3 / 5.4   4.0 / 5.3   4.6 / 5.4   5.6 / 5.5   6.0 / 5.4   7.6 / 5.5   9.9 / 5.6
+  //   64 x 64     4.4 / 5.6   5.4 / 5.6   6.6 / 5.7   7.7 / 5.8   8.3 / 5.6  11.3 / 5.8  15.6 / 5.9
+  //   128 x 64    4.3 / 5.4   5.5 / 5.6   6.4 / 5.7   7.5 / 5.8   8.2 / 6.3  11.0 / 6.5  14.8 / 6.9
+  //   128 x 128   4.5 / 5.9   5.6 / 6.3   7.0 / 6.8   8.1 / 6.4   8.9 / 7.0  11.8 / 7.7  16.5 / 8.0
+  //   256 x 128   4.3 / 7.0   5.4 / 7.0   6.9 / 7.5   8.0 / 8.0   8.9 / 8.1  11.4 / 9.0  15.1 / 9.8
+  //   512 x 64    4.2 / 7.0   5.4 / 7.0   6.4 / 7.8   7.2 / 7.7   7.9 / 7.6  10.4 / 8.2  14.1 / 9.0
+  //   256 x 256   5.1 / 9.3   6.6 / 9.5   8.3 / 10.6  9.7 / 10.9 10.8 / 11.4 14.2 / 12.8 19.4 / 13.9
+  // Beyond one workgroup per compute unit they queue: 608 x 128 (304) at 2000, 3000, 4096 rows 9.2, 15.2, 23.3 against 11.3, 12.0, 13.4
   const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16), size = int64_t(K) * F;
-  const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 3000 : 4096));
+  const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 2000 : (size < 256 * 256 ? 2500 : 3000)));
   if (n <= few && n * sb * sf <= 2560 * int64_t(kCus)) {
     wgrad_small_kernel<<<dim3(unsigned(sb), unsigned(sf)), kWave * kSmallWaves, 0, s>>>(a, dW, lddw);
     HGNN_LAUNCH_CHECK("wgrad_small_kernel");
@@ -788,9 +827,7 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   else if (WA == 1) wgrad_kernel<1, 2><<<grid, kBlock, 0, s>>>(a);
   else wgrad_kernel<2, 2><<<grid, kBlock, 0, s>>>(a);
   HGNN_LAUNCH_CHECK("wgrad_kernel");
-  const int64_t elems = int64_t(K) * F;
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(elems, kWave))), kWave * kSumSlices, 0, s>>>(part, elems, int(parts), elems, F, dW, lddw,
-                                                                                         elems, nullptr);
+  partial_sum_kernel<true><<<dim3(unsigned(tiles * 4)), kWave * kSumSlices, 0, s>>>(part, tiles * 256, int(parts), K, F, dW, lddw, 0, nullptr);
   HGNN_LAUNCH_CHECK("partial_sum_kernel");
   return HGNN_OK;
 }
@@ -838,7 +875,7 @@ hgnn_status hgnn_gat_feature_grad(int64_t n, int32_t H, int32_t D, const hgnn_ha
   }
   HGNN_LAUNCH_CHECK("gat_feature_grad_kernel");
   // the partial of workgroup b is [2][F]: one row of 2F elements, whose second half is da_r
-  partial_sum_kernel<<<dim3(unsigned(ceil_div(2 * F, kWave))), kWave * kSumSlices, 0, s>>>(part, 2 * int64_t(F), int(blocks),
+  partial_sum_kernel<false><<<dim3(unsigned(ceil_div(2 * F, kWave))), kWave * kSumSlices, 0, s>>>(part, 2 * int64_t(F), int(blocks),
                                                                                          2 * int64_t(F), F, da_l, F, F, da_r);
   HGNN_LAUNCH_CHECK("partial_sum_kernel");
   return HGNN_OK;
