@@ -198,12 +198,9 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 // ---- per-edge row ids of one plan segment, staged in LDS by one wave (edge_score_seg_kernel) ----------
 // A segment of n <= S consecutive edges starting at e0 touches the rows row_lo..row_hi (plan arrays).
 // Every non-empty row after row_lo marks the slot of its first edge, then a wave-wide running
-// maximum spreads the ids: s_row[i] = row of edge e0+i for i < n, -2 for the padding up to
-// 64*per slots; s_blk[i/4] = common row id of the aligned group of four edges, or -1 when they
-// differ or touch the padding.  Lane t owns the slots [t*per, (t+1)*per); per is a multiple of 4.
-// s_row / s_blk are private to the calling wave; BLOCK_SYNC = true uses workgroup barriers all the same (every wave of the
-// workgroup must then call it, n = 0 without a segment), which keeps the four waves of a streaming kernel in step on consecutive
-// segments.
+// maximum spreads the ids: s_row[i] = row of edge e0+i for i < n.  Lane t owns the slots [t*per, (t+1)*per); per is a
+// multiple of 4.  s_row is private to the calling wave.  `between` runs when the first offsets are on their way: loads
+// issued there are in flight while the rows are staged.
 __device__ __forceinline__ int seg_slots_per_lane(int S) { return 4 * ((S + 255) / 256); }
 
 // The index arrays (column ids, edge ids) are read once per pass.  Where they are far larger than the caches, passes through an
@@ -221,44 +218,43 @@ __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
   return p;
 }
 
-template <bool BLOCK_SYNC = false>
-__device__ __forceinline__ void seg_stage_rows(int* s_row, int* s_blk, int lane, int per, int n, int row_lo, int row_hi,
-                                               const int* __restrict__ rowptr, int64_t e0) {
-  for (int i = lane; i < kWave * per; i += kWave) s_row[i] = i == 0 ? row_lo : -1;
-  if (BLOCK_SYNC) __syncthreads();
-  else wave_sync();
-  for (int r = row_lo + 1 + lane; r <= row_hi; r += kWave) {
-    const int p = rowptr[r], q = rowptr[r + 1];
+__device__ __forceinline__ int wave_max_scan(int v) {  // inclusive
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));  // row_bcast:15, row_bcast:31
+  return max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+}
+
+template <class F>
+__device__ __forceinline__ void seg_stage_rows(int* s_row, int lane, int per, int row_lo, int row_hi, const int* __restrict__ rowptr,
+                                               int64_t e0, F&& between) {
+  int r = row_lo + 1 + lane, p = 0, q = 0;
+  if (r <= row_hi) p = rowptr[r], q = rowptr[r + 1];
+  between();
+  for (int i = 4 * lane; i < kWave * per; i += 4 * kWave) *reinterpret_cast<int4_t*>(s_row + i) = int4_t{-1, -1, -1, -1};
+  wave_sync();
+  if (q > p) s_row[p - int(e0)] = r;
+  for (r += kWave; r <= row_hi; r += kWave) {
+    p = rowptr[r], q = rowptr[r + 1];
     if (q > p) s_row[p - int(e0)] = r;
   }
-  if (BLOCK_SYNC) __syncthreads();
-  else wave_sync();
-  const int b0 = lane * per;
-  int run = -1;
-  for (int j = 0; j < per; ++j) {
-    run = max(run, s_row[b0 + j]);
-    s_row[b0 + j] = run;
+  wave_sync();
+  int4_t* const own = reinterpret_cast<int4_t*>(s_row + lane * per);
+  int run = row_lo;  // the first edges' row; ids grow
+  for (int j = 0; j < per / 4; ++j) {
+    const int4_t v = own[j];
+    run = max(max(max(run, v[0]), max(v[1], v[2])), v[3]);
   }
-  int inc = run;
+  run = __builtin_amdgcn_update_dpp(row_lo, wave_max_scan(run), 0x138, 0xf, 0xf, false);  // of the lanes before: wave_shr:1
+  for (int j = 0; j < per / 4; ++j) {
+    int4_t v = own[j];
 #pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int t = __shfl_up(inc, d);
-    if (lane >= d) inc = max(inc, t);
+    for (int i = 0; i < 4; ++i) v[i] = run = max(run, v[i]);
+    own[j] = v;
   }
-  int excl = __shfl_up(inc, 1);
-  if (lane == 0) excl = -1;
-  for (int j = 0; j < per; j += 4) {
-    int v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      v[q] = max(s_row[b0 + j + q], excl);
-      if (b0 + j + q >= n) v[q] = -2;
-      s_row[b0 + j + q] = v[q];
-    }
-    s_blk[(b0 + j) >> 2] = (v[0] == v[1] && v[1] == v[2] && v[2] == v[3]) ? v[0] : -1;
-  }
-  if (BLOCK_SYNC) __syncthreads();
-  else wave_sync();
+  wave_sync();
 }
 
 }  // namespace hgnn

@@ -205,11 +205,18 @@ __global__ __launch_bounds__(kBlock) void sddmm_scalar_kernel(SddmmArgs a) {
   a.out[idx] = half_t(p);
 }
 
-// Factorised GAT score, step 1: proj[v,h] = <avec[h], feat[v,h]> for every vertex, fp32.
+// Factorised GAT score, step 1: proj[v,h] = <avec[h], feat[v,h]> for every vertex, fp32, on both sides (one launch: where
+// they are the same features a row comes from memory once, 262 144 rows of 64 halves 8.6 + 8.6 -> 11.5 us).
+struct ProjSide {
+  const half_t* feat;
+  int64_t ld;
+  int nv;  // 0: this side is not wanted
+  const half_t* avec;
+  float* proj;
+};
+
 template <int L>
-__global__ __launch_bounds__(kBlock) void vertex_proj_kernel(const half_t* __restrict__ feat, int64_t ld, int nv,
-                                                              const half_t* __restrict__ avec, int F, int D,
-                                                              float* __restrict__ proj, int H) {
+__global__ __launch_bounds__(kBlock) void vertex_proj_kernel(ProjSide u, ProjSide w, int F, int D, int H) {
   constexpr int G = kWave / L;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
@@ -217,29 +224,38 @@ __global__ __launch_bounds__(kBlock) void vertex_proj_kernel(const half_t* __res
   const bool active = f0 < F;
   const int LH = D / 8;
   const int64_t v = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G + g;
-  float p = 0.f;
-  if (active && v < nv)
-    p = dot8(*reinterpret_cast<const half8_t*>(avec + f0), *reinterpret_cast<const half8_t*>(feat + v * ld + f0));
-  for (int off = 1; off < LH; off <<= 1) p += __shfl_xor(p, off);
-  if (active && v < nv && (l % LH) == 0) proj[v * H + l / LH] = p;
+  const bool inu = active && v < u.nv, inw = active && v < w.nv;
+  float p = 0.f, q = 0.f;
+  if (inu) p = dot8(*reinterpret_cast<const half8_t*>(u.avec + f0), *reinterpret_cast<const half8_t*>(u.feat + v * u.ld + f0));
+  if (inw) q = dot8(*reinterpret_cast<const half8_t*>(w.avec + f0), *reinterpret_cast<const half8_t*>(w.feat + v * w.ld + f0));
+  for (int off = 1; off < LH; off <<= 1) {
+    p += __shfl_xor(p, off);
+    q += __shfl_xor(q, off);
+  }
+  if (l % LH != 0) return;
+  if (inu) u.proj[v * H + l / LH] = p;
+  if (inw) w.proj[v * H + l / LH] = q;
 }
 
 // step 2, one plan segment per wave: e[k,h] = LeakyReLU(el[row k, h] + er[col k, h]); row ids
-// come from the offset array (staged in LDS), so the only per-edge stream read is the column id.
+// come from the offset array (staged in LDS), so the only per-edge stream read is the column id.  Bound by the chain ids ->
+// er and offsets -> rows -> el: the ids and er of 256 non-zeros go out before the rows are staged, el of all of them together
+// (one step of a wave after the other, behind the rows: 5.5 M non-zeros x 4 heads 43.9 us, now 41.0; the lines of er at 3.6 clocks each
+// in a compute unit are 32).
 template <int HT>
 __global__ __launch_bounds__(kBlock) void edge_score_seg_kernel(SddmmArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int S = a.S;
   const int per = seg_slots_per_lane(S), spad = kWave * per;
-  int* s_row = reinterpret_cast<int*>(smem) + size_t(wave) * (spad + spad / 4);
-  int* s_blk = s_row + spad;
+  int* s_row = reinterpret_cast<int*>(smem) + size_t(wave) * spad;
   const int64_t seg = int64_t(blockIdx.x) * kWavesPerBlock + wave;
-  const bool valid = seg < a.nseg;
+  if (seg >= a.nseg) return;
   const int64_t e0 = seg * S;
-  const int n = valid ? int(a.nnz - e0 < S ? a.nnz - e0 : S) : 0;
-  seg_stage_rows<true>(s_row, s_blk, lane, per, n, valid ? a.seg_lo[seg] : 0, valid ? a.seg_hi[seg] : -1, a.rowptr, e0);
+  const int n = int(a.nnz - e0 < S ? a.nnz - e0 : S);
+  const int row_lo = a.seg_lo[seg], row_hi = a.seg_hi[seg];
   if (HT == 0) {  // any head count: one output element per lane and step
+    seg_stage_rows(s_row, lane, per, row_lo, row_hi, a.rowptr, e0, [] {});
     const int tot = n * a.H;
     for (int j = lane; j < tot; j += kWave) {
       const int k = j / a.H, h = j - k * a.H;
@@ -250,52 +266,72 @@ __global__ __launch_bounds__(kBlock) void edge_score_seg_kernel(SddmmArgs a) {
     }
     return;
   }
-  // H in {1,2,4,8}: a lane produces 8 consecutive outputs (8/H non-zeros) and stores them as 16 bytes
+  // H in {1,2,4,8}: a lane produces 8 consecutive outputs (8/H non-zeros) and stores them as 16 bytes, IT times over
   constexpr int H = HT > 0 ? HT : 1;
-  constexpr int EPL = 8 / H;
+  constexpr int EPL = 8 / H, STEP = kWave * EPL, IT = STEP < 256 ? 256 / STEP : 1;
   typedef float fv_t __attribute__((ext_vector_type(H)));
+  typedef int iv_t __attribute__((ext_vector_type(EPL < 4 ? EPL : 4)));
+  constexpr int W = EPL < 4 ? EPL : 4;  // ids a load
+  const int* const ids = a.col + e0;
   half_t* dst = a.out + e0 * H;
-  const bool vec_ok = (reinterpret_cast<uintptr_t>(dst) & 15u) == 0;
-  for (int kb = lane * EPL; kb < n; kb += kWave * EPL) {
-    half8_t o = half8_t(0);
-    int rows[EPL], cols[EPL];
-    if (EPL >= 4 && kb + EPL <= n && (reinterpret_cast<uintptr_t>(a.col + e0 + kb) & 15u) == 0) {  // 16-byte loads of ids
+  const bool vec_ok = (reinterpret_cast<uintptr_t>(dst) & 15u) == 0, ids_ok = (reinterpret_cast<uintptr_t>(ids) & 15u) == 0;
+  for (int k0 = 0; k0 < n; k0 += IT * STEP) {
+    fv_t vr[IT * EPL];
+    auto right = [&] {
+      int cols[IT * EPL];
 #pragma unroll
-      for (int v = 0; v < EPL / 4; ++v) {
-        const int4_t c4 = *reinterpret_cast<const int4_t*>(a.col + e0 + kb + 4 * v);
-        const int4_t r4 = *reinterpret_cast<const int4_t*>(s_row + kb + 4 * v);
+      for (int i = 0; i < IT; ++i) {
+        const int kb = k0 + i * STEP + lane * EPL;
+        if (ids_ok && kb + EPL <= n) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          cols[4 * v + q] = c4[q];
-          rows[4 * v + q] = r4[q];
+          for (int v = 0; v < EPL / W; ++v) {
+            const iv_t c = *reinterpret_cast<const iv_t*>(ids + kb + W * v);
+#pragma unroll
+            for (int q = 0; q < W; ++q) cols[i * EPL + W * v + q] = c[q];
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) cols[i * EPL + e] = ids[kb + e < n ? kb + e : n - 1];
         }
       }
-    } else {
+#pragma unroll
+      for (int e = 0; e < IT * EPL; ++e) vr[e] = *reinterpret_cast<const fv_t*>(a.er + int64_t(cols[e]) * H);
+    };
+    if (k0 == 0) seg_stage_rows(s_row, lane, per, row_lo, row_hi, a.rowptr, e0, right);
+    else right();
+    int rows[IT * EPL];
+    fv_t vl[IT * EPL];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
-        const int k = kb + e < n ? kb + e : n - 1;
-        cols[e] = a.col[e0 + k];
-        rows[e] = s_row[k];
+        const int k = k0 + i * STEP + lane * EPL + e;
+        rows[i * EPL + e] = s_row[k < n ? k : n - 1];
       }
     }
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const fv_t vl = *reinterpret_cast<const fv_t*>(a.el + int64_t(rows[e]) * H);
-      const fv_t vr = *reinterpret_cast<const fv_t*>(a.er + int64_t(cols[e]) * H);
+    for (int e = 0; e < IT * EPL; ++e) vl[e] = *reinterpret_cast<const fv_t*>(a.el + int64_t(rows[e]) * H);
 #pragma unroll
-      for (int h = 0; h < H; ++h) {
-        float s = vl[h] + vr[h];
-        s = s > 0.f ? s : a.slope * s;
-        if (a.lse) s = __expf(s - a.lse[int64_t(rows[e]) * H + h]);
-        o[e * H + h] = half_t(s);
+    for (int i = 0; i < IT; ++i) {
+      const int kb = k0 + i * STEP + lane * EPL;
+      half8_t o = half8_t(0);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          float s = vl[i * EPL + e][h] + vr[i * EPL + e][h];
+          s = s > 0.f ? s : a.slope * s;
+          if (a.lse) s = __expf(s - a.lse[int64_t(rows[i * EPL + e]) * H + h]);
+          o[e * H + h] = half_t(s);
+        }
       }
-    }
-    if (vec_ok && kb + EPL <= n) {
-      *reinterpret_cast<half8_t*>(dst + kb * H) = o;
-    } else {
+      if (vec_ok && kb + EPL <= n) {
+        *reinterpret_cast<half8_t*>(dst + kb * H) = o;
+      } else {
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (kb * H + q < n * H) dst[kb * H + q] = o[q];
+        for (int q = 0; q < 8; ++q)
+          if (kb * H + q < n * H) dst[kb * H + q] = o[q];
+      }
     }
   }
 }
@@ -353,22 +389,21 @@ static void launch_dot(bool near, int L, int lh, bool mask, unsigned waves, hipS
   else launch_dot_tasks<false, VW>(L, lh, mask, waves, s, a, v);
 }
 
-static void launch_proj(int L, dim3 grid, hipStream_t s, const half_t* feat, int64_t ld, int nv, const half_t* avec, int F,
-                        int D, float* proj, int H) {
+static void launch_proj(int L, dim3 grid, hipStream_t s, const ProjSide& u, const ProjSide& w, int F, int D, int H) {
   switch (L) {
-    case 1: vertex_proj_kernel<1><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    case 2: vertex_proj_kernel<2><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    case 4: vertex_proj_kernel<4><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    case 8: vertex_proj_kernel<8><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    case 16: vertex_proj_kernel<16><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    case 32: vertex_proj_kernel<32><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
-    default: vertex_proj_kernel<64><<<grid, kBlock, 0, s>>>(feat, ld, nv, avec, F, D, proj, H); break;
+    case 1: vertex_proj_kernel<1><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    case 2: vertex_proj_kernel<2><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    case 4: vertex_proj_kernel<4><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    case 8: vertex_proj_kernel<8><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    case 16: vertex_proj_kernel<16><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    case 32: vertex_proj_kernel<32><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
+    default: vertex_proj_kernel<64><<<grid, kBlock, 0, s>>>(u, w, F, D, H); break;
   }
 }
 
 static hgnn_status launch_edge_score(const SddmmArgs& a, int64_t seg_blocks, hipStream_t s) {
   const int spad = kWave * 4 * ((a.S + 255) / 256);
-  const size_t lds = size_t(spad + spad / 4) * sizeof(int) * kWavesPerBlock;
+  const size_t lds = size_t(spad) * sizeof(int) * kWavesPerBlock;
   const dim3 gs{unsigned(seg_blocks > 0 ? seg_blocks : 1), 1u, 1u};
   switch (a.H) {
     case 1: edge_score_seg_kernel<1><<<gs, kBlock, lds, s>>>(a); break;
@@ -403,14 +438,10 @@ hgnn_status gat_project(const hgnn_plan* p, const hgnn_csr* g, int H, int D, con
   const int L = pow2_at_least(F / 8), G = kWave / L;
   float* el = p->vscratch;
   float* er = p->vscratch + size_t(g->nrows) * H;
-  launch_proj(L, dim3(unsigned(ceil_div(g->nrows, int64_t(kWavesPerBlock) * G))), s, reinterpret_cast<const half_t*>(U), ldu,
-              g->nrows, reinterpret_cast<const half_t*>(a_l), F, D, el, H);
+  const ProjSide u{reinterpret_cast<const half_t*>(U), ldu, g->nrows, reinterpret_cast<const half_t*>(a_l), el};
+  const ProjSide w{reinterpret_cast<const half_t*>(Vt), ldv, Vt ? g->ncols : 0, reinterpret_cast<const half_t*>(a_r), er};
+  launch_proj(L, dim3(unsigned(ceil_div(std::max(u.nv, w.nv), int64_t(kWavesPerBlock) * G))), s, u, w, F, D, H);
   HGNN_LAUNCH_CHECK("vertex_proj_kernel");
-  if (Vt) {
-    launch_proj(L, dim3(unsigned(ceil_div(g->ncols, int64_t(kWavesPerBlock) * G))), s, reinterpret_cast<const half_t*>(Vt),
-                ldv, g->ncols, reinterpret_cast<const half_t*>(a_r), F, D, er, H);
-    HGNN_LAUNCH_CHECK("vertex_proj_kernel");
-  }
   return HGNN_OK;
 }
 

@@ -65,3 +65,35 @@ def test_row_passes_at_borders(hgnn, dev, H, short_rows):
         assert np.all(np.isinf(got[lone]))
         compare("row sums", got[others], oracle.edge_rowsum(rowptr, t64)[others], oracle.edge_rowsum(rowptr, np.abs(t64))[others])
     hgnn.hgnn_plan_destroy(p)
+
+
+# scores by segments of the edge list: segments below, at and above the 256 non-zeros of one round, ids at every offset inside a
+# vector, rows that are empty, longer than a segment or more than a wave to a segment, sides of different tables and sizes
+@pytest.mark.parametrize("S", [64, 256, 320, 1000])
+@pytest.mark.parametrize("H", [1, 2, 3, 4, 8])
+def test_edge_scores_by_segments(hgnn, dev, H, S):
+    print(f"scores H={H} S={S}", flush=True)
+    r = np.random.default_rng(10 * S + H)
+    deg = np.concatenate([[0, 0, 1], r.integers(0, 3, 700), [0, 700, 0, 2500, 0], r.integers(0, 40, 60), [1], np.zeros(3, np.int64)])
+    V, ncols, D, E = deg.size, 333, 8, int(deg.sum())
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    row = np.repeat(np.arange(V), deg)
+    col = r.integers(0, ncols, E).astype(np.int32)
+    col = col[np.lexsort((col, row))]
+    U, Vt = f16(r.standard_normal((V, H * D))), f16(r.standard_normal((ncols, H * D)))
+    al, ar = f16(0.3 * r.standard_normal((H, D))), f16(0.3 * r.standard_normal((H, D)))
+    parts = [np.einsum("vhd,hd->vh", f(X.astype(np.float64)).reshape(-1, H, D), f(a.astype(np.float64)))[i]
+             for f in (np.asarray, np.abs) for X, a, i in ((U, al, row), (Vt, ar, col))]
+    s = parts[0] + parts[1]
+    ref, mag = np.where(s > 0, s, 0.2 * s), parts[2] + parts[3]
+    for shift in (0, 1, 2):
+        cbuf = torch.zeros(E + shift, dtype=torch.int32, device=dev)
+        cbuf[shift:] = up(col, dev)
+        g = hgnn.Csr(up(rowptr, dev), cbuf[shift:], ncols=ncols)
+        p = hgnn.hgnn_plan_create(g, S, 64, 8)
+        obuf = torch.full((E * H + 2,), 7.0, dtype=torch.float16, device=dev)
+        out = obuf[shift:shift + E * H].view(E, H)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_GAT_SCORE, H, D, up(U, dev), up(Vt, dev), out, up(al, dev), up(ar, dev), 0.2)
+        compare("score", down(out), ref, mag)
+        assert torch.all(obuf[:shift] == 7.0) and torch.all(obuf[shift + E * H:] == 7.0)
+        hgnn.hgnn_plan_destroy(p)
