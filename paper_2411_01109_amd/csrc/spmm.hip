@@ -637,7 +637,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         cs[m] = 0.f;
-        if (WM == 2 && run.has(m)) cs[m] = a.col_scale[c[m]];
+        if (WM == 2) cs[m] = a.col_scale[run.has(m) ? c[m] : 0];  // (2.1 M x 128 47.5 -> 46.4 us; without factors 37: a line more a non-zero)
       }
 #pragma unroll
       for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], run.has(m));
