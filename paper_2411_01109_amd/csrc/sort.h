@@ -12,7 +12,9 @@ namespace hgnn {
 constexpr int kSortThreads = 1024, kSortPer = 8, kSortTile = kSortThreads * kSortPer;
 constexpr int kSortBits = 9, kSortBins = 1 << kSortBits;
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kFewTiles = 64;  // up to so many, every tile adds up the counts itself: a launch less a pass, 4 to 5 us
+// Up to so many tiles, every tile adds up the counts itself, half of the tiles by each half of its workgroup: a launch less a pass, 4 to 5 us
+// (us, list to CSR in four passes, own sums up to 128 / 256 tiles: 520 000 words in 254 tiles 84 / 98, 1.8 M in 220 119 / 129).
+constexpr int kFewTiles = 128;
 
 struct SortPass {
   int64_t n;
@@ -26,9 +28,10 @@ struct SortPass {
 
 // Sources of words: load(first, n, mine, scratch, w) gives a lane the items mine, mine + 64, ... of the n of the tile that begins at item `first`
 // (those past the end are the last one again: no load is behind a branch), after prepare(first, n, scratch) by the whole workgroup; scratch is
-// kSortTile ints of LDS.  count(p, k) is a word with the digit of pass p.
+// kSortThreads * PER ints of LDS.  count(p, k) is a word with the digit of pass p.
 struct SortWords {
   const uint64_t* words;
+  template <int PER>
   __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
   template <int PER>
   __device__ __forceinline__ void load(int64_t first, int n, int mine, const int*, uint64_t (&w)[PER]) const {
@@ -43,21 +46,21 @@ struct SortWords {
 // list of edges, rows read only where the digit reaches into them, 16.5 -> 7.1).
 constexpr int kSortCopies = 8, kSortPitch = kSortBins + 1;
 
-template <class Source>
+template <class Source, int PER>
 __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(SortPass p, Source src) {
   __shared__ uint32_t hist[kSortCopies * kSortPitch];
   for (int i = threadIdx.x; i < kSortCopies * kSortPitch; i += kSortThreads) hist[i] = 0;
   __syncthreads();
-  const int64_t first = int64_t(blockIdx.x) * kSortTile + threadIdx.x;
-  int d[kSortPer];
+  const int64_t first = int64_t(blockIdx.x) * (kSortThreads * PER) + threadIdx.x;
+  int d[PER];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int64_t k = first + j * kSortThreads;
     d[j] = p.digit(src.count(p, k < p.n ? k : p.n - 1));
     if (k >= p.n) d[j] = -1;
   }
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
+  for (int j = 0; j < PER; ++j)
     if (d[j] >= 0) atomicAdd(&hist[(threadIdx.x % kSortCopies) * kSortPitch + d[j]], 1u);
   __syncthreads();
   for (int i = threadIdx.x; i < kSortBins; i += kSortThreads) {
@@ -173,14 +176,15 @@ __device__ __forceinline__ void sort_wave_ranks(const SortPass& p, const uint64_
   }
 }
 
-// A tile: every wave ranks its 512 consecutive items by digit, the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
+// A tile: every wave ranks its consecutive items (512 with eight a thread) by digit, the ranks of the waves are put after each other, the items go to LDS in that order and from there to memory: a bin's
 // items of the tile are a run of 16 on average.  5.5 M words: 25.4 us (3.5 TB/s of reads and writes; a third of it vector instructions of
 // the ranks), a pass 39 with its count and scan, where a library pass with look-back and its two fills took 52; the words that the first
-// pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 191 us, transpose 180 -> 114; 50 000 words,
-// which a library merge sort was faster for, 77 -> 70 and 70 -> 52.
-template <class Source>
+// pass forms and the split at the end save three more passes over memory.  List to CSR 271 -> 191 us, transpose 180 -> 114; 100 000
+// words (tiles of 8192 items: 88 and 53) 58 and 39.
+template <class Source, int PER>
 __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass p, Source src, uint64_t* __restrict__ out) {
-  __shared__ __align__(16) unsigned char lds[kSortTile * sizeof(uint64_t)];
+  constexpr int TILE = kSortThreads * PER;
+  __shared__ __align__(16) unsigned char lds[TILE * sizeof(uint64_t)];
   __shared__ uint32_t s_to[kSortBins];  // where the first item of a bin goes, less its place in the tile
   __shared__ uint32_t s_at[kSortBins];  // place of a bin's first item in the tile
   __shared__ uint32_t s_wave[kSortWaves];
@@ -188,38 +192,39 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   uint16_t (*const hist)[kSortBins] = reinterpret_cast<uint16_t (*)[kSortBins]>(lds);
   uint64_t* const item = reinterpret_cast<uint64_t*>(lds);
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t first = int64_t(blockIdx.x) * kSortTile;
-  const int n = int(p.n - first < kSortTile ? p.n - first : kSortTile);
+  const int64_t first = int64_t(blockIdx.x) * TILE;
+  const int n = int(p.n - first < TILE ? p.n - first : TILE);
   const int bin = threadIdx.x;
   uint32_t total = 0, earlier = 0;
-  if (bin < kSortBins) {
-    if (p.ntiles <= kFewTiles) {
+  if (p.ntiles <= kFewTiles) {  // every other tile by either half of the workgroup
+    const int half = threadIdx.x / kSortBins;
 #pragma unroll 8
-      for (int t = 0; t < p.ntiles; ++t) {
-        const uint32_t c = p.counts[t * kSortBins + bin];
-        total += c;
-        earlier += t < int(blockIdx.x) ? c : 0;
-      }
-    } else {
-      total = p.totals[bin];
-      earlier = p.counts[int64_t(blockIdx.x) * kSortBins + bin];
+    for (int t = half; t < p.ntiles; t += 2) {
+      const uint32_t c = p.counts[t * kSortBins + bin % kSortBins];
+      total += c;
+      earlier += t < int(blockIdx.x) ? c : 0;
     }
+    if (half) s_at[bin - kSortBins] = total, s_to[bin - kSortBins] = earlier;
+  } else if (bin < kSortBins) {
+    total = p.totals[bin];
+    earlier = p.counts[int64_t(blockIdx.x) * kSortBins + bin];
   }
-  src.prepare(first, n, scratch);
-  uint64_t w[kSortPer];
-  const int mine = wave * (kWave * kSortPer) + lane;
+  src.template prepare<PER>(first, n, scratch);
+  uint64_t w[PER];
+  const int mine = wave * (kWave * PER) + lane;
   src.load(first, n, mine, scratch, w);
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
+  for (int j = 0; j < PER; ++j)
     if (mine + j * kWave >= n) w[j] = ~uint64_t(0);  // behind all items of the last bin
   __syncthreads();
   for (int i = threadIdx.x; i < kSortWaves * kSortBins / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(lds)[i] = 0;
   __syncthreads();
-  uint32_t rank[kSortPer];
+  uint32_t rank[PER];
   sort_wave_ranks(p, w, hist[wave], rank);
   __syncthreads();
   uint32_t here = 0;
   if (bin < kSortBins) {
+    if (p.ntiles <= kFewTiles) total += s_at[bin], earlier += s_to[bin];
 #pragma unroll
     for (int v = 0; v < kSortWaves; ++v) {
       const uint32_t c = hist[v][bin];
@@ -235,16 +240,16 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int d = p.digit(w[j]);
     rank[j] += s_at[d] + hist[wave][d];
   }
   __syncthreads();  // the items take the place of the counts
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) item[rank[j]] = w[j];
+  for (int j = 0; j < PER; ++j) item[rank[j]] = w[j];
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int i = j * kSortThreads + threadIdx.x;
     if (i >= n) break;
     const uint64_t v = item[i];
@@ -252,24 +257,25 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_scatter_kernel(SortPass 
   }
 }
 
-// Up to kFewMerged tiles (one, where one pass does): every tile is sorted by all its digits in LDS, in one launch, and the words of several
-// tiles find their places by searches in the others.  A pass of two launches for every nine bits is mostly latency there.  List to CSR, us,
-// passes / this: 1000 words over 100 vertices 40 / 24, over 100 000 91 / 32; 8192 over 5000 59 / 41; 33 000 over 30 000 85 / 54; 65 536 over
-// 100 49 / 48, over 5000 65 / 55, over 100 000 85 / 61; in 16 tiles 131 072 over 100 51 / 83, over 100 000 87 / 96.  Transpose (one pass up to
-// 512 vertices): 8192 over 100 32 / 28, 16 384 33 / 35; 65 536 over 5000 50 / 48.
-constexpr int kFewMerged = 8;
+// Few tiles: every one is sorted by all its digits in LDS, in one launch, and the words of several
+// tiles find their places by searches in the others.  A pass of two launches for every nine bits is mostly latency there.  us, passes / this, list
+// to CSR: three passes, 9000 words 43 / 43, 15 000 45 / 42, 24 000 48 / 43, 33 000 44 / 44, 65 000 46 / 51; four, 15 000 65 / 53, 24 000
+// 67 / 51, 50 000 65 / 53, 65 000 57 / 57.  Two passes are as fast from two tiles on (transpose, 9000 words 36 / 38, 24 000 40 / 40, 65 000 38 /
+// 47).
+constexpr int kFewMerged = 8;  // most tiles that are merged
+inline int few_merged(int passes) { return passes <= 2 ? 1 : (passes == 3 ? 4 : kFewMerged); }
 
-// PER: items of a thread; the counts, and the rows that a source expands, take 32 KB of LDS in any case
+// PER: items of a thread
 template <class Source, int PER>
 __global__ __launch_bounds__(kSortThreads) void sort_tile_kernel(SortPass p, int last, Source src, uint64_t* __restrict__ out) {
-  __shared__ __align__(16) unsigned char lds[(PER > 4 ? PER : 4) * kSortThreads * sizeof(uint64_t)];
+  __shared__ __align__(16) unsigned char lds[PER * kSortThreads * sizeof(uint64_t)];
   __shared__ uint32_t s_at[kSortBins], s_wave[kSortWaves];
   uint16_t (*const hist)[kSortBins] = reinterpret_cast<uint16_t (*)[kSortBins]>(lds);
   uint64_t* const item = reinterpret_cast<uint64_t*>(lds);
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, bin = threadIdx.x;
   const int64_t first = int64_t(blockIdx.x) * (PER * kSortThreads);
   const int n = int(p.n - first < PER * kSortThreads ? p.n - first : PER * kSortThreads);
-  src.prepare(first, n, reinterpret_cast<int*>(lds));
+  src.template prepare<PER>(first, n, reinterpret_cast<int*>(lds));
   uint64_t w[PER];
   const int mine = wave * (kWave * PER) + lane;
   src.load(first, n, mine, reinterpret_cast<const int*>(lds), w);
@@ -344,7 +350,19 @@ __global__ __launch_bounds__(kBlock) void sort_merge_kernel(SortPass p, int last
   if (u == 0) out[place] = w;
 }
 
-inline size_t sort_scratch_bytes(int64_t n) { return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortTile)) + 1 + kScanShares); }
+// Items of a thread in the passes: the tiles are as large as leaves one for nearly every compute unit, up to eight items, whose
+// runs of a bin are whole lines.  us, eight / four / two items, list to CSR; transpose (two passes):
+//   100 000 words of 20 000 vertices    79 /  65 /  58;  50 / 43 / 39        700 000 of 50 000    98 /  93 /  98;  59 / 55 / 59
+//   300 000 of 30 000                   88 /  79 /  78;  53 / 49 / 48      1 040 000 of 50 000   108 /  99 / 103;  63 / 59 / 62
+//   520 000 of 50 000                   90 /  89 /  84;  54 / 53 / 51      1 200 000 of 100 000  109 / 111 / 119;  66 / 66 / 73
+inline int sort_items(int64_t n) {
+  constexpr int64_t kTiles = 256;  // compute units
+  return n <= kTiles * 2 * kSortThreads ? 2 : (n <= kTiles * 4 * kSortThreads ? 4 : kSortPer);
+}
+
+inline size_t sort_scratch_bytes(int64_t n) {
+  return sizeof(uint32_t) * kSortBins * (size_t(ceil_div(n, kSortThreads * sort_items(n))) + 1 + kScanShares);
+}
 
 // Sorts n >= 1 words by their bits [first, last).  The words come from src; the sorted ones are in the returned one of the two buffers.
 template <class Source>
@@ -359,7 +377,7 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
   const dim3 grid{unsigned(p.ntiles)};
   uint64_t *in = buf1, *out = buf0;
   p.shift = first;
-  if (p.ntiles <= (npass > 1 ? kFewMerged : 1)) {
+  if (p.ntiles <= few_merged(npass)) {
     p.bits = (bits + npass - 1) / npass;
     if (n <= 2 * kSortThreads) sort_tile_kernel<Source, 2><<<grid, kSortThreads, 0, s>>>(p, last, src, buf0);
     else sort_tile_kernel<Source, kSortPer><<<grid, kSortThreads, 0, s>>>(p, last, src, buf0);
@@ -373,25 +391,34 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
     else merge(std::integral_constant<int, kFewMerged>());
     return buf1;
   }
-  for (int i = 0; i < npass; ++i) {
-    p.bits = (last - p.shift + npass - i - 1) / (npass - i);
-    if (i == 0) sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, src);
-    else sort_count_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in});
-    if (p.ntiles > kFewTiles) {
-      constexpr int kGroups = kSortBins / kScanBins;
-      if (p.ntiles <= kScanTiles) {
-        sort_scan_kernel<kScanAll><<<kGroups, kSortThreads, 0, s>>>(p);
-      } else {
-        sort_scan_kernel<kScanAdd><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
-        sort_scan_kernel<kScanShare><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
+  auto passes = [&](auto items) {
+    constexpr int PER = decltype(items)::value;
+    p.ntiles = int(ceil_div(n, kSortThreads * PER));
+    const dim3 tiles{unsigned(p.ntiles)};
+    for (int i = 0; i < npass; ++i) {
+      p.bits = (last - p.shift + npass - i - 1) / (npass - i);
+      if (i == 0) sort_count_kernel<Source, PER><<<tiles, kSortThreads, 0, s>>>(p, src);
+      else sort_count_kernel<SortWords, PER><<<tiles, kSortThreads, 0, s>>>(p, SortWords{in});
+      if (p.ntiles > kFewTiles) {
+        constexpr int kGroups = kSortBins / kScanBins;
+        if (p.ntiles <= kScanTiles) {
+          sort_scan_kernel<kScanAll><<<kGroups, kSortThreads, 0, s>>>(p);
+        } else {
+          sort_scan_kernel<kScanAdd><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
+          sort_scan_kernel<kScanShare><<<dim3(kGroups, kScanShares), kSortThreads, 0, s>>>(p);
+        }
       }
+      if (i == 0) sort_scatter_kernel<Source, PER><<<tiles, kSortThreads, 0, s>>>(p, src, out);
+      else sort_scatter_kernel<SortWords, PER><<<tiles, kSortThreads, 0, s>>>(p, SortWords{in}, out);
+      p.shift += p.bits;
+      in = out;
+      out = in == buf0 ? buf1 : buf0;
     }
-    if (i == 0) sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, src, out);
-    else sort_scatter_kernel<<<grid, kSortThreads, 0, s>>>(p, SortWords{in}, out);
-    p.shift += p.bits;
-    in = out;
-    out = in == buf0 ? buf1 : buf0;
-  }
+  };
+  const int per = sort_items(n);
+  if (per == 2) passes(std::integral_constant<int, 2>());
+  else if (per == 4) passes(std::integral_constant<int, 4>());
+  else passes(std::integral_constant<int, kSortPer>());
   return in;
 }
 

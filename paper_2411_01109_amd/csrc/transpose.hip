@@ -31,6 +31,7 @@ struct CooWords {
   const int *row, *col;
   int nrows, ncols, col_bits, position_bits;
   int* bad;
+  template <int PER>
   __device__ __forceinline__ void prepare(int64_t, int, int*) const {}
   __device__ __forceinline__ uint64_t word(int r, int c, int64_t k, bool& ok) const {
     const bool rok = uint32_t(r) < uint32_t(nrows), cok = uint32_t(c) < uint32_t(ncols);
@@ -206,27 +207,27 @@ static void launch_split_words(const uint64_t* words, int64_t nnz, int position_
 constexpr int kExpandPerThread = 8;
 constexpr int kExpand = kBlock * kExpandPerThread;
 
-// s_row[i] = row of position e0 + i, i < n <= 8 THREADS; the workgroup has been waited for at the end
-template <int THREADS>
+// s_row[i] = row of position e0 + i, i < n <= PER THREADS; the workgroup has been waited for at the end
+template <int THREADS, int PER>
 __device__ __forceinline__ void expand_tile(const int* __restrict__ rowptr, int nrows, int64_t e0, int n, int* s_row) {
   __shared__ int s_max[THREADS / kWave], s_lim[2];
   if (threadIdx.x < 2 * kWave) {
     const int w = threadIdx.x / kWave, r = wave_row_of_edge(rowptr, nrows, w == 0 ? e0 : e0 + n - 1);
     if ((threadIdx.x & (kWave - 1)) == 0) s_lim[w] = r;
   }
-  for (int i = threadIdx.x; i < THREADS * kExpandPerThread; i += THREADS) s_row[i] = -1;
+  for (int i = threadIdx.x; i < THREADS * PER; i += THREADS) s_row[i] = -1;
   __syncthreads();
   const int lo = max(s_lim[0], 0), hi = min(s_lim[1], nrows - 1);
   if (hi - lo > 16 * n) {  // few positions among many rows: the row of each by search (8192 over 1 M rows, a transpose 329 -> 86 us)
-    int r[kExpandPerThread];
+    int r[PER];
 #pragma unroll
-    for (int j = 0; j < kExpandPerThread; ++j) r[j] = lo;
+    for (int j = 0; j < PER; ++j) r[j] = lo;
     for (int step = 1 << (31 - __clz(hi - lo)); step > 0; step >>= 1)
 #pragma unroll
-      for (int j = 0; j < kExpandPerThread; ++j)
+      for (int j = 0; j < PER; ++j)
         if (hi - r[j] >= step && int64_t(rowptr[r[j] + step]) <= e0 + j * THREADS + int(threadIdx.x)) r[j] += step;
 #pragma unroll
-    for (int j = 0; j < kExpandPerThread; ++j) s_row[j * THREADS + threadIdx.x] = r[j];
+    for (int j = 0; j < PER; ++j) s_row[j * THREADS + threadIdx.x] = r[j];
     __syncthreads();
     return;
   }
@@ -237,10 +238,10 @@ __device__ __forceinline__ void expand_tile(const int* __restrict__ rowptr, int 
   }
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  int v[kExpandPerThread], run = lo;
+  int v[PER], run = lo;
 #pragma unroll
-  for (int j = 0; j < kExpandPerThread; ++j) {
-    run = max(run, s_row[threadIdx.x * kExpandPerThread + j]);
+  for (int j = 0; j < PER; ++j) {
+    run = max(run, s_row[threadIdx.x * PER + j]);
     v[j] = run;
   }
   int incl = run;
@@ -255,7 +256,7 @@ __device__ __forceinline__ void expand_tile(const int* __restrict__ rowptr, int 
   __syncthreads();
   for (int w = 0; w < wave; ++w) excl = max(excl, s_max[w]);
 #pragma unroll
-  for (int j = 0; j < kExpandPerThread; ++j) s_row[threadIdx.x * kExpandPerThread + j] = max(v[j], excl);
+  for (int j = 0; j < PER; ++j) s_row[threadIdx.x * PER + j] = max(v[j], excl);
   __syncthreads();
 }
 
@@ -264,7 +265,7 @@ __device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int 
   __shared__ int s_row[kExpand];
   const int64_t e0 = int64_t(blockIdx.x) * kExpand;
   const int n = int(nnz - e0 < kExpand ? nnz - e0 : kExpand);
-  expand_tile<kBlock>(rowptr, nrows, e0, n, s_row);
+  expand_tile<kBlock, kExpandPerThread>(rowptr, nrows, e0, n, s_row);
   for (int i = threadIdx.x; i < n; i += kBlock) put(e0 + i, s_row[i]);
 }
 
@@ -272,8 +273,8 @@ __device__ __forceinline__ void expand_rows(const int* __restrict__ rowptr, int 
 struct TransposeWords {
   const int *rowptr, *col;
   int nrows, row_bits, position_bits;
-  static_assert(kSortPer == kExpandPerThread, "a tile is expanded by its workgroup");
-  __device__ __forceinline__ void prepare(int64_t first, int n, int* s_row) const { expand_tile<kSortThreads>(rowptr, nrows, first, n, s_row); }
+  template <int PER>
+  __device__ __forceinline__ void prepare(int64_t first, int n, int* s_row) const { expand_tile<kSortThreads, PER>(rowptr, nrows, first, n, s_row); }
   template <int PER>
   __device__ __forceinline__ void load(int64_t first, int n, int mine, const int* s_row, uint64_t (&w)[PER]) const {
 #pragma unroll

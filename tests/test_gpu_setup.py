@@ -43,7 +43,7 @@ def test_sort_keys(hgnn, dev, V, E):
     check_lists(hgnn, dev, V, row, col)
 
 
-# a tile of the sort is 8192 words, up to 64 tiles add up their counts themselves; digits of 1 to 9 bits
+# tiles of 8192 words at most, few tiles add up their counts themselves; digits of 1 to 9 bits
 @pytest.mark.parametrize("V,E", [(2, 8191), (512, 8192), (513, 8193), (1 << 18, 64 * 8192), ((1 << 18) + 1, 64 * 8192 + 1), (37, 600000),
                                  (1 << 20, 1200000)])
 def test_sort_tiles(hgnn, dev, V, E):
@@ -54,6 +54,13 @@ def test_sort_tiles(hgnn, dev, V, E):
     row[row > V * 3 // 4] = V - 1
     col[: E // 8] = col[0]
     check_lists(hgnn, dev, V, row, col)
+
+
+# two, four and eight words a thread, counts added up by the tiles or scanned, with each number of words; one, two and four passes
+@pytest.mark.parametrize("E", [128 * 2048, 128 * 2048 + 1, 256 * 2048, 256 * 2048 + 1, 256 * 4096, 256 * 4096 + 1])
+@pytest.mark.parametrize("V", [20, 511, 70000])
+def test_sort_items_of_a_thread(hgnn, dev, V, E):
+    test_sort_tiles(hgnn, dev, V, E)
 
 
 @pytest.mark.parametrize("E", [3072 * 8192, 3072 * 8192 + 1])
