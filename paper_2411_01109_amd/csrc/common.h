@@ -359,10 +359,11 @@ struct hgnn_plan {
   // column-sum kernels keep one slice's per-column scalars in LDS
   int32_t ns = 0;                   // slices; 0 = not built
   int32_t slice_w = 0;
-  int32_t nch = 0;                  // row chunks of about nnz / nch non-zeros each (a multiple of 8)
+  int32_t nch = 0;                  // chunks of nnz / nch non-zeros each (a multiple of 8)
+  bool slice_scores = false;        // scores go over the slices too (slices.hip)
   int32_t* scut = nullptr;          // [ns+1][nrows] first CSR position of row r whose column is >= s*slice_w
-  int32_t* chunk_row = nullptr;     // [nch+1]
-  unsigned long long* col_part = nullptr;  // [nch][ncols] fixed-point partial column sums of the row chunks
+  int32_t* chunk_row = nullptr;     // row where the share of a chunk that a wave takes begins
+  unsigned long long* col_part = nullptr;  // [nch][ncols] fixed-point partial column sums of the chunks
   float* col_poison = nullptr;      // [ncols] sums of non-finite inputs; zero between calls
 };
 
@@ -448,7 +449,7 @@ hgnn_status task_prepare(const TaskSource& q, TaskCounts& c);
 hgnn_status task_allocate(const TaskSource& q, TaskCounts& c, int max_F, int max_H, hgnn_row_tasks** out);
 hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s);
 void destroy_tasks(hgnn_row_tasks* t, bool idle);  // idle: nothing that uses them is in flight
-hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s);
+hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked, SetupStream& s);  // asked: by the caller, for all that they serve
 hgnn_status slice_edge_score(const hgnn_plan* p, const hgnn_csr* g, const float* el, const float* er, const float* lse,
                              float slope, hgnn_half* out, hipStream_t s);
 }  // namespace hgnn

@@ -734,7 +734,7 @@ hgnn_status hgnn_plan_create(const hgnn_csr* g, int32_t seg_edges, int32_t max_F
     // of 16 non-zeros or more on average
     if (st == HGNN_OK && col_blocks == 0 && g->nrows > 0 && g->nnz > 0) {
       const int64_t ns = ceil_div(g->ncols, kSliceMaxCols);
-      if (double(g->nnz) / g->nrows >= 16.0 * double(ns)) st = build_col_slices(p, g, kSliceMaxCols, s);
+      if (double(g->nnz) / g->nrows >= 16.0 * double(ns)) st = build_col_slices(p, g, kSliceMaxCols, false, s);
     }
   }
   if (st != HGNN_OK) {

@@ -7,15 +7,15 @@
 // per non-zero, and the request rate of the L2s then bounds the pass at a fraction of what streaming the edge
 // arrays would take.  On gfx950 a workgroup may hold 160 KB of LDS, enough for the scalars of 16 K columns, so
 // the plan can cut the columns into slices of that width: a workgroup loads (or zeroes) the table of one slice
-// in LDS and walks the pieces of the rows of one row chunk that fall into the slice -- contiguous pieces of the
-// column array, because columns ascend inside a row -- gathering from / adding into LDS.  What is left in
+// in LDS and walks the pieces of one chunk of the non-zeros that fall into the slice -- a contiguous piece of
+// every row, because columns ascend inside a row -- gathering from / adding into LDS.  What is left in
 // memory traffic is the stream of column ids and edge values.
 //
 // Column sums are accumulated as 64-bit fixed-point integers (an fp16 value is an integer multiple of 2^-24 below
 // 2^16 in magnitude, so the conversion is exact), with LDS atomic adds: integer addition is associative, so the
 // result does not depend on the order in which the waves arrive (no run-to-run variation), and it is the exact sum,
 // rounded once on output.  Every workgroup leaves its slice's partial sums in the plan; a second kernel adds the
-// row chunks' partials per column.  Non-finite inputs (never produced by the path itself) go through a separate
+// chunks' partials per column.  Non-finite inputs (never produced by the path itself) go through a separate
 // fp32 side array so that they still poison their column's sum.
 #include "common.h"
 
@@ -29,8 +29,9 @@ constexpr int kSliceUnroll = 8;  // row pieces whose loads a wave has in flight 
 
 struct SliceArgs {
   const int* scut;       // [ns+1][nrows]: first CSR position of row r whose column is >= s*W (s = ns: end of the row)
-  const int* chunk_row;  // [nch+1] row chunks holding about nnz / nch non-zeros each
+  const int* chunk_row;  // [nch * kSliceWaves + 1] row of the first non-zero of every wave's share
   const int* col;
+  int64_t nnz;
   int nrows, ncols, ns, nch, W;
   // score (and alpha from lse)
   const float* el;   // [nrows]
@@ -80,7 +81,12 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
     else s_er[i] = a.er[col0 + i];
   }
   __syncthreads();
-  const int r0 = a.chunk_row[c], r1 = a.chunk_row[c + 1];
+  // A wave's share is as many positions of the edge arrays as every other's, and may begin and end inside a row: with whole rows, a power law's
+  // longest were a wave's work for most of the time (3.5 M non-zeros of 13 292 vertices, score 287 -> 16, column sums 371 -> 28 us; 24 M of
+  // 100 000, log-normal, 61 -> 57 and 71 -> 65).
+  const int64_t shares = int64_t(a.nch) * kSliceWaves, share = int64_t(c) * kSliceWaves + wave;
+  const int p0 = int(a.nnz * share / shares), p1 = int(a.nnz * (share + 1) / shares);
+  const int r0 = a.chunk_row[share], r1 = min(a.chunk_row[share + 1] + 1, a.nrows);
   const int* __restrict__ lo = a.scut + size_t(s) * size_t(a.nrows);
   const int* __restrict__ hi = lo + a.nrows;
   const unsigned short* __restrict__ tbits = reinterpret_cast<const unsigned short*>(a.t);
@@ -140,8 +146,8 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   auto bounds = [&](int base, int& b, int& e, float& elv, float& lsev) {
     const int r = base + lane;
     const bool in = r < r1;
-    b = in ? lo[r] : 0;
-    e = in ? hi[r] : 0;
+    b = in ? max(lo[r], p0) : 0;
+    e = in ? max(min(hi[r], p1), b) : 0;
     elv = lsev = 0.f;
     if (!COLSUM && in) {
       elv = a.el[r];
@@ -150,12 +156,11 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   };
   int nb_ = 0, ne_ = 0;
   float nel = 0.f, nlse = 0.f;
-  const int first = r0 + wave * kWave;
-  if (first < r1) bounds(first, nb_, ne_, nel, nlse);
-  for (int base = first; base < r1; base += kSliceWaves * kWave) {
+  bounds(r0, nb_, ne_, nel, nlse);
+  for (int base = r0; base < r1; base += kWave) {
     const int b = nb_, e = ne_;
     const float elv = nel, lsev = nlse;
-    if (base + kSliceWaves * kWave < r1) bounds(base + kSliceWaves * kWave, nb_, ne_, nel, nlse);  // for the next batch
+    if (base + kWave < r1) bounds(base + kWave, nb_, ne_, nel, nlse);  // for the next batch
     int inc = e - b;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -203,15 +208,24 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   }
 }
 
-// out[j] = fp16(sum over the row chunks of their partial sums of column j); the side array of non-finite inputs is
-// added and cleared
-__global__ __launch_bounds__(kBlock) void colsum_reduce_kernel(const unsigned long long* __restrict__ part, int nch, int ncols,
-                                                                float* __restrict__ poison, half_t* __restrict__ out) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= ncols) return;
-  long long sum = 0;
-  for (int c = 0; c < nch; ++c) sum += (long long)part[size_t(c) * size_t(ncols) + j];
-  double v = double(sum) * (1.0 / 16777216.0);
+// out[j] = fp16(sum over the chunks of their partial sums of column j); the side array of non-finite inputs is
+// added and cleared.  64 columns a workgroup, whose waves take a share of the chunks each: bound by the latency of a wave's loads
+// (16 chunks of 233 k columns, 4 / 16 waves: 8.2 / 12.0 us).
+__global__ __launch_bounds__(kSliceThreads) void colsum_reduce_kernel(const unsigned long long* __restrict__ part, int nch, int ncols,
+                                                                      float* __restrict__ poison, half_t* __restrict__ out) {
+  __shared__ unsigned long long sums[kSliceWaves][kWave];
+  const int x = threadIdx.x & (kWave - 1), y = threadIdx.x / kWave, waves = blockDim.x / kWave, j = blockIdx.x * kWave + x;
+  unsigned long long mine = 0;
+  if (j < ncols) {
+#pragma unroll 8
+    for (int c = y; c < nch; c += waves) mine += part[size_t(c) * size_t(ncols) + j];
+  }
+  sums[y][x] = mine;
+  __syncthreads();
+  if (y > 0 || j >= ncols) return;
+  mine = 0;
+  for (int w = 0; w < waves; ++w) mine += sums[w][x];
+  double v = double((long long)mine) * (1.0 / 16777216.0);
   const float p = poison ? poison[j] : 0.f;
   if (p != 0.f) {  // also true for nan
     v += double(p);
@@ -240,25 +254,21 @@ __global__ void slice_cuts_kernel(const int* __restrict__ rowptr, const int* __r
   scut[idx] = lo;
 }
 
-// chunk_row[c] = first row whose first non-zero is at or beyond c * nnz / nch; chunk_row[nch] = nrows
-__global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int nch, int* __restrict__ chunk_row) {
+// chunk_row[c] = the row of position c * nnz / shares; chunk_row[shares] = nrows - 1
+__global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int shares, int* __restrict__ chunk_row) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c > nch) return;
-  if (c == nch) {
-    chunk_row[c] = nrows;
-    return;
-  }
-  const int64_t target = nnz * c / nch;
+  if (c > shares) return;
+  const int64_t target = nnz * c / shares;
   int lo = 0, hi = nrows;
   while (lo < hi) {
     const int mid = lo + ((hi - lo) >> 1);
-    if (int64_t(rowptr[mid]) < target) lo = mid + 1;
+    if (int64_t(rowptr[mid]) <= target) lo = mid + 1;
     else hi = mid;
   }
-  chunk_row[c] = lo;
+  chunk_row[c] = max(lo - 1, 0);
 }
 
-hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream& s) {
+hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked, SetupStream& s) {
   // slices of an earlier call may still be in use by calls on the plan, on whatever stream
   const bool idle = p->scut == nullptr || device_idle(p->device);
   dev_put(p->scut, idle);
@@ -275,22 +285,28 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, SetupStream
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) cus = 256;
   const int ns = int(ceil_div(g->ncols, W));
   W = int(ceil_div(ceil_div(g->ncols, ns), 64) * 64);  // the same number of slices, of equal width (a short last slice would idle its compute units)
-  // one workgroup per compute unit at a time (its LDS table fills most of the 160 KB): as many row chunks as give
+  // one workgroup per compute unit at a time (its LDS table fills most of the 160 KB): as many chunks as give
   // every compute unit one (slice, chunk) pair, a multiple of 8 so that a chunk's slices share an XCD, and not so
-  // many that a chunk is shorter than a few hundred rows
+  // many that a wave has less than a round of a slice's non-zeros
   int nch = 8 * std::max(1, (cus / 8) / ns);
-  const int by_rows = 8 * int(ceil_div(g->nrows, 8 * 512));
-  if (nch > by_rows) nch = by_rows;
+  const int64_t by_work = 8 * std::max<int64_t>(1, g->nnz / (int64_t(8) * kSliceThreads * kSliceUnroll * ns));
+  if (nch > by_work) nch = int(by_work);
+  const int shares = nch * kSliceWaves;
   HGNN_HIP(dev_malloc(&p->scut, sizeof(int) * size_t(ns + 1) * size_t(g->nrows)));
-  HGNN_HIP(dev_malloc(&p->chunk_row, sizeof(int) * size_t(nch + 1)));
+  HGNN_HIP(dev_malloc(&p->chunk_row, sizeof(int) * (size_t(shares) + 1)));
   HGNN_HIP(dev_malloc(&p->col_part, sizeof(unsigned long long) * size_t(nch) * size_t(g->ncols)));
   HGNN_HIP(dev_malloc(&p->col_poison, sizeof(float) * size_t(g->ncols)));
   HGNN_HIP(hipMemsetAsync(p->col_poison, 0, sizeof(float) * size_t(g->ncols), s));
   slice_cuts_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) * (ns + 1), kBlock))), kBlock, 0, s>>>(g->rowptr, g->col, g->nrows,
                                                                                                     ns, W, p->scut);
-  chunk_rows_kernel<<<dim3(unsigned(ceil_div(nch + 1, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, g->nnz, nch, p->chunk_row);
+  chunk_rows_kernel<<<dim3(unsigned(ceil_div(shares + 1, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, g->nnz, shares, p->chunk_row);
   HGNN_LAUNCH_CHECK("slice_cuts_kernel / chunk_rows_kernel");
   HGNN_HIP(s.wait());
+  // Scores gather through the caches just as well where there are few: us, segments / slices, 1 M non-zeros of 13 292 vertices 8.4 / 14.0, 1.2 M of
+  // 4000 8.3 / 11.8, 3 M of 30 000 17.4 / 16.3, 3.5 M of 13 292 14.0 / 16.0, 5.4 M of 20 000 22.0 / 22.2, 6 M of 60 000 32.6 / 23.0 (power law 26.0 / 34.3), 8 M
+  // of 30 000 33.8 / 27.9, 20 M of 16 000 53.4 / 39.7, 24 M of 100 000 103 / 57.  Column sums have no other way.
+  constexpr int64_t kScoreNnz = int64_t(4) << 20;
+  p->slice_scores = asked || g->nnz > kScoreNnz;
   p->ns = ns;
   p->slice_w = W;
   p->nch = nch;
@@ -302,6 +318,7 @@ static SliceArgs slice_args(const hgnn_plan* p, const hgnn_csr* g) {
   a.scut = p->scut;
   a.chunk_row = p->chunk_row;
   a.col = g->col;
+  a.nnz = g->nnz;
   a.nrows = g->nrows;
   a.ncols = g->ncols;
   a.ns = p->ns;
@@ -357,7 +374,7 @@ hgnn_status hgnn_plan_add_slices(hgnn_plan* p, const hgnn_csr* g, int32_t slice_
   HGNN_REQUIRE(slice_cols == 0 || (slice_cols >= 64 && slice_cols <= kSliceMaxCols), HGNN_EINVAL,
                "%s: slice_cols = %d outside [64, %d] (0 = default)", who, slice_cols, kSliceMaxCols);
   SetupStream s(stream);
-  return build_col_slices(p, g, slice_cols == 0 ? kSliceMaxCols : slice_cols, s);
+  return build_col_slices(p, g, slice_cols == 0 ? kSliceMaxCols : slice_cols, true, s);
 }
 
 int32_t hgnn_plan_num_slices(const hgnn_plan* p) { return p ? p->ns : 0; }
@@ -380,7 +397,7 @@ hgnn_status hgnn_edge_colsum(const hgnn_csr* g, const hgnn_plan* p, int32_t H, c
   HGNN_REQUIRE(out != nullptr && (g->nnz == 0 || t != nullptr), HGNN_EINVAL, "%s: t or out is NULL", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (g->nrows == 0) {  // no rows, hence no slices: every column sum is zero
-    colsum_reduce_kernel<<<dim3(unsigned(ceil_div(g->ncols, kBlock))), kBlock, 0, s>>>(nullptr, 0, g->ncols, nullptr,
+    colsum_reduce_kernel<<<dim3(unsigned(ceil_div(g->ncols, kWave))), kWave, 0, s>>>(nullptr, 0, g->ncols, nullptr,
                                                                                        reinterpret_cast<half_t*>(out));
     HGNN_LAUNCH_CHECK("colsum_reduce_kernel");
     return HGNN_OK;
@@ -391,7 +408,7 @@ hgnn_status hgnn_edge_colsum(const hgnn_csr* g, const hgnn_plan* p, int32_t H, c
   a.poison = p->col_poison;
   st = launch_slices<true>(p, a, s);
   if (st != HGNN_OK) return st;
-  colsum_reduce_kernel<<<dim3(unsigned(ceil_div(g->ncols, kBlock))), kBlock, 0, s>>>(p->col_part, p->nch, g->ncols, p->col_poison,
+  colsum_reduce_kernel<<<dim3(unsigned(ceil_div(g->ncols, kWave))), p->nch <= 64 ? kBlock : kSliceThreads, 0, s>>>(p->col_part, p->nch, g->ncols, p->col_poison,
                                                                                      reinterpret_cast<half_t*>(out));
   HGNN_LAUNCH_CHECK("colsum_reduce_kernel");
   return HGNN_OK;

@@ -168,3 +168,36 @@ def test_slices_degenerate_graphs(hgnn, dev):
                                      a_r.reshape(1, D), 1)
             compare(f"score, {name}", down(e), e_ref, np.abs(e_ref) + 0.5)
         hgnn.hgnn_plan_destroy(p)
+
+
+# shares of waves that begin and end inside rows: rows longer than many shares, stretches of empty ones, few rows, a slice or several; the
+# last one has enough non-zeros for the slices of an automatic plan to serve the scores
+@pytest.mark.parametrize("V,ncols,E,W", [(40, 300, 70000, 0), (5000, 700, 300000, 256), (3000, 20000, 900000, 0), (9000, 9000, (4 << 20) + 77, None)])
+def test_slices_of_long_rows(hgnn, dev, V, ncols, E, W):
+    print(f"slices of long rows V={V} E={E}", flush=True)
+    r = np.random.default_rng(V)
+    row = np.where(r.random(E) < 0.6, r.choice([3, 4, V // 2, V - 2], E), r.integers(0, V, E))
+    row[(row > V // 3) & (row < V // 2)] = V // 3
+    col = np.where(r.random(E) < 0.1, 7, r.integers(0, ncols, E))
+    order = np.lexsort((col, row))
+    row, col = row[order], col[order].astype(np.int32)
+    rowptr = np.searchsorted(row, np.arange(V + 1)).astype(np.int32)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols)
+    plain = hgnn.hgnn_plan_create(g, 256, 64, 1, col_blocks=1)
+    p = hgnn.hgnn_plan_create(g, 256, 64, 1, col_blocks=1 if W is not None else 0)
+    if W is not None:
+        hgnn.hgnn_plan_add_slices(p, g, W)
+    assert hgnn.hgnn_plan_num_slices(p) > 0
+    D = 8
+    U, Vt = up(f16(r.standard_normal((V, D))), dev), up(f16(r.standard_normal((ncols, D))), dev)
+    a_l, a_r = (up(f16(r.standard_normal((1, D))), dev) for _ in range(2))
+    e = [torch.full((E, 1), 9.0, dtype=torch.float16, device=dev) for _ in range(2)]
+    for q, out in zip((p, plain), e):
+        hgnn.hgnn_sddmm(g, q, hgnn.HGNN_SDDMM_GAT_SCORE, 1, D, U, Vt, out, a_l, a_r, 0.2)
+    assert torch.equal(e[0], e[1])  # the same sums of the same fp32 values
+    t = f16(r.standard_normal((E, 1)))
+    sums = torch.full((ncols, 1), 9.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_edge_colsum(g, p, 1, up(t, dev), sums)
+    ref = np.zeros(ncols)
+    np.add.at(ref, col, t[:, 0].astype(np.float64))  # exact
+    assert np.all(np.abs(down(sums)[:, 0] - ref) <= np.abs(ref) * 2.0 ** -11 * (1 + 2.0 ** -10) + 2.0 ** -25)
