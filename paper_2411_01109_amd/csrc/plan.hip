@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
   const int i = threadIdx.x;
   const int counters = tq.range_min == kNoRanges ? kTaskCounters : kTaskAll;
   if (i < kLists) counts[i * nblk + blockIdx.x] = s_total[i];
-  else if (i < kLists + counters) task_counts[int64_t(i - kLists) * nblk + blockIdx.x] = s_total[i];
+  else if (i < kLists + counters) task_counts[int64_t(i - kLists) * nblk + blockIdx.x] = task_counter<true>(s_total + kLists, i - kLists);
   else if (i == kListed && s_total[i]) atomicAdd(&f->listed, (unsigned long long)s_total[i]);
 }
 

@@ -35,6 +35,32 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
   return c;
 }
 
+// Rows of one piece just above group_max, up to kMidLen: a window (kTaskWindow rows) leaves them to lane groups, too, where that takes most of its
+// waves away.  They are counted beside its empty rows, of which there are no more than 65535.  A wave of its own is mostly overhead there, which
+// counts where there are many; else it is the shorter chain.  us, waves / lane groups: uniform, 2 M non-zeros of 42 233 rows x 64, SpMM 28.0 / 20.9, SDDMM
+// 33.0 / 24.5, attention forward 57.8 / 31.9, backward 57.7 / 46.6; 400 000 of 8000 7.3 / 6.3, 8.6 / 8.2, 14.4 / 12.2, 16.6 / 15.6; 160 000 of 4000 5.6 /
+// 5.8, 6.6 / 7.3, 10.5 / 10.7, 12.6 / 13.7.  All rows up to 64 of a power law of 1.5 M of 30 000: 17.8 / 19.4, 16.7 / 19.4, 36.0 / 39.1, 36.1 / 39.7;
+// log-normal, 1.7 M of 60 328: 27.3 / 28.6, 27.5 / 28.7, 45.2 / 41.7, 50.6 / 47.7.  What loses: row sums behind a map of the first 24.7 / 26.3, and a plan
+// of 1.5 M takes 1 us more.
+constexpr int kMidLen = 64, kMidShift = 16;
+constexpr int64_t kMidLeastNnz = int64_t(1) << 18;
+__device__ __forceinline__ bool mid_row(const TaskSource& q, const RowCut& c) {
+  return c.m == 1 && c.part > q.group_max && c.part <= kMidLen && !c.far && q.nnz >= kMidLeastNnz;
+}
+// above 0: a window of so many rows, and pieces of lane groups and of waves beside them, takes less than half the waves with the rows in lane
+// groups, eight to a wave.  A sum over rows, of fewer than 2^27 (group_max is 32 up to 8 M non-zeros only).
+__device__ __forceinline__ int mid_gain(int mid, int group, int whole) { return 6 * mid - group - 8 * whole; }
+
+// the counters of a window from what its rows have added to them (the same rows whether long ones are cut at column ranges or not)
+template <bool RANGES>
+__device__ __forceinline__ int task_counter(const int* total, int i) {
+  const int mid = total[kTaskZ] >> kMidShift;
+  if (i == kTaskZ) return total[kTaskZ] & ((1 << kMidShift) - 1);
+  if (i != kTaskW && i != kTaskG) return total[i];
+  const int group = total[kTaskG] + (RANGES ? total[kTaskLongG] : 0), whole = total[kTaskW] + (RANGES ? total[kTaskLongW] : 0);
+  return total[i] + ((mid_gain(mid, group, whole) > 0) == (i == kTaskG) ? mid : 0);
+}
+
 // what row r adds to the counters
 template <bool RANGES, int N>
 __device__ __forceinline__ void task_count_row(const TaskSource& q, const int* rp, int r, int (&n)[N]) {
@@ -43,6 +69,8 @@ __device__ __forceinline__ void task_count_row(const TaskSource& q, const int* r
   const bool whole = c.part > q.group_max;
   if (c.m == 0) {
     ++n[kTaskZ];
+  } else if (mid_row(q, c)) {
+    n[kTaskZ] += 1 << kMidShift;
   } else if (RANGES && c.far) {
     n[whole ? int(kTaskLongW) : int(kTaskLongG)] += c.m;
   } else {
@@ -177,6 +205,8 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
   } else {
     s = sec[b];
   }
+  __shared__ int s_gain;
+  if (threadIdx.x == 0) s_gain = 0;
   for (int i = threadIdx.x; i < kLists * (kMaxGroupLen + 1); i += kTaskThreads) at[0][i] = 0;
   if (threadIdx.x < (RANGES && q.range_min != kNoRanges ? int(kTaskAll) : int(kTaskCounters))) {
     const int i = threadIdx.x;
@@ -185,14 +215,25 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     if (RANGES && i == kTaskLongG) base = s.g_off + (SELF ? all[kTaskG] : sums[kTaskG]);
     next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
   }
-  __syncthreads();
   RowCut cut[kTaskRowsPerThread];
+  int gain = 0;
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     cut[u] = RowCut{0, 0, kNone, false};
     if (r < q.nrows) cut[u] = cut_row<RANGES>(q, rp, int(r));
+    if (cut[u].m > 0) gain += mid_row(q, cut[u]) ? mid_gain(1, 0, 0) : (cut[u].part <= q.group_max ? mid_gain(0, cut[u].m, 0) : mid_gain(0, 0, cut[u].m));
     if (RANGES && drop && cut[u].far) cut[u].m = kNone;
-    if (cut[u].m > 0 && cut[u].part <= q.group_max) {
+  }
+  bool grouped = false;
+  if (q.nnz >= kMidLeastNnz && q.group_max < kMidLen) {
+    gain = wave_sum(gain);
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&s_gain, gain);
+    __syncthreads();
+    grouped = s_gain > 0;
+  }
+  auto is_whole = [&](const RowCut& c) { return c.part > q.group_max && !(grouped && mid_row(q, c)); };
+  for (int u = 0; u < kTaskRowsPerThread; ++u) {
+    if (cut[u].m > 0 && !is_whole(cut[u])) {
       int* const a = at[RANGES && cut[u].far ? 1 : 0];
       const int last = cut[u].len - (cut[u].m - 1) * cut[u].part;
       if (cut[u].m > 1) atomicAdd(&a[cut[u].part], cut[u].m - 1);
@@ -226,7 +267,7 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
       slot = atomicAdd(&next[kTaskSlots], c.m);
       split[atomicAdd(&next[kTaskSplit], 1)] = make_int4(r, slot, c.m, b);
     }
-    const bool whole = c.part > q.group_max;
+    const bool whole = is_whole(c);
     if (c.m > 0) {
       if (whole) pos = atomicAdd(&next[RANGES && c.far ? int(kTaskLongW) : int(kTaskW)], c.m);
       k0 = s.first + rp[r];

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, 
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = total[threadIdx.x];
+  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = task_counter<false>(total, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, int nwin, int* __restrict__ counts, int* __restrict__ sums,
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = total[threadIdx.x];
+  if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = task_counter<true>(total, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, int range_cap, const int* __restrict__ counts,

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import oracle
-from parity import compare, down, f16, up
+from parity import compare, down, f16, spmm_plain, up
 
 pytestmark = pytest.mark.gpu
 
@@ -48,6 +48,42 @@ def test_piece_borders(hgnn, dev, F, H, S, nb, what):
     hgnn.hgnn_spmm_discretized(p, g, wd, H, up(Xh, dev), Y, F=F)
     ref, sabs = oracle.spmm(rowptr, col, np.ascontiguousarray(Xh[:, :F]), w=w, H=H, want_sabs=True, **({"eid": eid} if eid is not None else {}))
     compare("row tasks", np.ascontiguousarray(down(Y)[:, :F]), ref, sabs)
+    hgnn.hgnn_plan_destroy(p)
+
+
+@pytest.mark.parametrize("S,less", [(256, 0), (256, 1), (64, 0), (50, 0), (24, 0)])
+def test_windows_of_middle_rows(hgnn, dev, S, less):
+    """Windows of 1024 rows whose rows of 33 to 64 non-zeros are left to lane groups or take a wave each: all of them, none, at the border of the
+    rule, beside longer and empty ones, in pieces of several to a row; graphs of 2^18 non-zeros and one fewer."""
+    print(f"middle rows S={S} less={less}", flush=True)
+    r = np.random.default_rng(S)
+    window = lambda *kinds: r.permutation(np.concatenate([np.broadcast_to(v, n) for n, v in kinds]))
+    wins = [window((1024, 47)), window((1024, r.integers(33, 65, 1024))), window((500, 64), (62, 65), (12, 1), (450, 0)),
+            window((500, 33), (374, 3), (1, 300), (149, 40)), window((512, 32), (512, 64)), window((86, 50), (516, 9), (422, 0)),
+            window((86, 50), (515, 9), (423, 0)), window((350, 64), (674, 0)), window((300, 8))]
+    deg = np.concatenate(wins)
+    deg[-1] = 0
+    deg[-1] = (1 << 18) - less - deg.sum()  # one long row
+    assert 300 < deg[-1] < 60000
+    V, F = deg.size, 16
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    row = np.repeat(np.arange(V), deg)
+    col = r.integers(0, V, row.size).astype(np.int32)
+    col = col[np.lexsort((col, row))]
+    X, w = f16(r.standard_normal((V, F))), f16(r.standard_normal((row.size, 1)))
+    g, Xd, wd = hgnn.Csr(up(rowptr, dev), up(col, dev)), up(X, dev), up(w, dev)
+    p = hgnn.hgnn_plan_create(g, S, F, 1, col_blocks=1)
+    ref, sabs = oracle.spmm(rowptr, col, X, w=w, H=1, want_sabs=True)
+    Y = torch.full((V, F), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_spmm_discretized(p, g, wd, 1, Xd, Y)
+    compare("with a plan", down(Y), ref, sabs)
+    Y.fill_(3.0)
+    spmm_plain(hgnn, g, wd, 1, Xd, Y)
+    compare("without", down(Y), ref, sabs)
+    dot = torch.full((row.size, 1), 3.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, 1, F, Xd, Xd, dot)
+    mag = np.einsum("ef,ef->e", np.abs(X[row].astype(np.float64)), np.abs(X[col].astype(np.float64)))[:, None]
+    compare("dot", down(dot), oracle.sddmm_dot(rowptr, col, X, X, H=1), mag)
     hgnn.hgnn_plan_destroy(p)
 
 
