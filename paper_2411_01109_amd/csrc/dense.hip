@@ -813,9 +813,11 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   //   256 x 128   4.3 / 7.0   5.4 / 7.0   6.9 / 7.5   8.0 / 8.0   8.9 / 8.1  11.4 / 9.0  15.1 / 9.8
   //   512 x 64    4.2 / 7.0   5.4 / 7.0   6.4 / 7.8   7.2 / 7.7   7.9 / 7.6  10.4 / 8.2  14.1 / 9.0
   //   256 x 256   5.1 / 9.3   6.6 / 9.5   8.3 / 10.6  9.7 / 10.9 10.8 / 11.4 14.2 / 12.8 19.4 / 13.9
+  // (From 128 x 128 on the lines lie where the two were level with a partial result for every step, 128 x 128 at 3000 9.1 / 9.9, 256 x 256 at 4096
+  // 14.3 / 21.4; with fewer of them two launches are up to 2 us faster for the last third of the rows.)
   // Beyond one workgroup per compute unit they queue: 608 x 128 (304) at 2000, 3000, 4096 rows 9.2, 15.2, 23.3 against 11.3, 12.0, 13.4
   const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16), size = int64_t(K) * F;
-  const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 2000 : (size < 256 * 256 ? 2500 : 3000)));
+  const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 3000 : 4096));
   if (n <= few && n * sb * sf <= 2560 * int64_t(kCus)) {
     wgrad_small_kernel<<<dim3(unsigned(sb), unsigned(sf)), kWave * kSmallWaves, 0, s>>>(a, dW, lddw);
     HGNN_LAUNCH_CHECK("wgrad_small_kernel");
