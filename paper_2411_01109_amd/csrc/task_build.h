@@ -41,7 +41,7 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
 // 33.0 / 24.5, attention forward 57.8 / 31.9, backward 57.7 / 46.6; 400 000 of 8000 7.3 / 6.3, 8.6 / 8.2, 14.4 / 12.2, 16.6 / 15.6; 160 000 of 4000 5.6 /
 // 5.8, 6.6 / 7.3, 10.5 / 10.7, 12.6 / 13.7.  All rows up to 64 of a power law of 1.5 M of 30 000: 17.8 / 19.4, 16.7 / 19.4, 36.0 / 39.1, 36.1 / 39.7;
 // log-normal, 1.7 M of 60 328: 27.3 / 28.6, 27.5 / 28.7, 45.2 / 41.7, 50.6 / 47.7.  What loses: row sums behind a map of the first 24.7 / 26.3, and a plan
-// of 1.5 M takes 1 us more.
+// of 1.5 M takes 1 us more.  The rows are read and asked before the barrier that the counters want anyway.
 constexpr int kMidLen = 64, kMidShift = 16;
 constexpr int64_t kMidLeastNnz = int64_t(1) << 18;
 __device__ __forceinline__ bool mid_row(const TaskSource& q, const RowCut& c) {
@@ -205,16 +205,6 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
   } else {
     s = sec[b];
   }
-  __shared__ int s_gain;
-  if (threadIdx.x == 0) s_gain = 0;
-  for (int i = threadIdx.x; i < kLists * (kMaxGroupLen + 1); i += kTaskThreads) at[0][i] = 0;
-  if (threadIdx.x < (RANGES && q.range_min != kNoRanges ? int(kTaskAll) : int(kTaskCounters))) {
-    const int i = threadIdx.x;
-    int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? 0 : (SELF ? 0 : sums[i * q.nb + b]);
-    if (RANGES && i == kTaskLongW) base = s.w_off + (SELF ? all[kTaskW] : sums[kTaskW]);  // (one block)
-    if (RANGES && i == kTaskLongG) base = s.g_off + (SELF ? all[kTaskG] : sums[kTaskG]);
-    next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
-  }
   RowCut cut[kTaskRowsPerThread];
   int gain = 0;
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
@@ -224,12 +214,26 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     if (cut[u].m > 0) gain += mid_row(q, cut[u]) ? mid_gain(1, 0, 0) : (cut[u].part <= q.group_max ? mid_gain(0, cut[u].m, 0) : mid_gain(0, 0, cut[u].m));
     if (RANGES && drop && cut[u].far) cut[u].m = kNone;
   }
-  bool grouped = false;
-  if (q.nnz >= kMidLeastNnz && q.group_max < kMidLen) {
+  __shared__ int s_gain[kTaskThreads / kWave];
+  const bool mids = q.nnz >= kMidLeastNnz && q.group_max < kMidLen;
+  if (mids) {
     gain = wave_sum(gain);
-    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&s_gain, gain);
-    __syncthreads();
-    grouped = s_gain > 0;
+    if ((threadIdx.x & (kWave - 1)) == 0) s_gain[threadIdx.x / kWave] = gain;
+  }
+  for (int i = threadIdx.x; i < kLists * (kMaxGroupLen + 1); i += kTaskThreads) at[0][i] = 0;
+  if (threadIdx.x < (RANGES && q.range_min != kNoRanges ? int(kTaskAll) : int(kTaskCounters))) {
+    const int i = threadIdx.x;
+    int base = i == kTaskW ? s.w_off : i == kTaskG ? s.g_off : i == kTaskZ ? 0 : (SELF ? 0 : sums[i * q.nb + b]);
+    if (RANGES && i == kTaskLongW) base = s.w_off + (SELF ? all[kTaskW] : sums[kTaskW]);  // (one block)
+    if (RANGES && i == kTaskLongG) base = s.g_off + (SELF ? all[kTaskG] : sums[kTaskG]);
+    next[i] = base + (SELF ? before[i] : counts[(int64_t(i) * q.nb + b) * nwin + w]);
+  }
+  __syncthreads();
+  bool grouped = false;
+  if (mids) {
+    gain = 0;
+    for (int i = 0; i < kTaskThreads / kWave; ++i) gain += s_gain[i];
+    grouped = gain > 0;
   }
   auto is_whole = [&](const RowCut& c) { return c.part > q.group_max && !(grouped && mid_row(q, c)); };
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
