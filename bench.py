@@ -197,9 +197,9 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
     def task_name(hw, mapped=True, per_edge=False, free=0):
         """The SpMM over row tasks: lanes per row, 0 = no edge value / 1 = edge values / 2 = a factor per column, table within
         32 bits, values behind the edge-id map, heads of an edge's values read at once, tasks counted on the device (1) and long
-        rows cut at column ranges there (2)."""
+        rows cut at column ranges there (2), non-zeros of a round."""
         return (f"hgnn::spmm_task_kernel<{Lg}, {2 if per_edge else (1 if hw else 0)}, {near}, {cbool(hw and mapped)}, {max(hw, 1)}, "
-                f"{free}>")
+                f"{free}, *>")
 
     # the plan-free SpMM walks the columns in passes where its workspace has room for the partial rows (with one column there
     # are none); otherwise row tasks, for narrow features rows and the chunks of long rows in one launch
@@ -277,7 +277,7 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
         ops.append(("gat_spmm_bwd", task_name(H), spmm_min(H, True),
                     lambda: hgnn.hgnn_spmm_discretized(plan_t, gt, alpha, H, dY, dh), spmm_req(H, True)))
         b = E * 4 + 4 * (V + 1) + 2 * (2 * V * F) + 2 * EH
-        ops.append(("sddmm_dot", f"hgnn::sddmm_task_kernel<{Lg}, {near}, false, {min(D // 8, Lg, 8)}, 8>", b,
+        ops.append(("sddmm_dot", f"hgnn::sddmm_task_kernel<{Lg}, {near}, false, {min(D // 8, Lg, 8)}, 8, *>", b,
                     lambda: hgnn.hgnn_sddmm(g, plan, hgnn.HGNN_SDDMM_DOT, H, D, dY, X, dalpha), b + E * 2 * F))
         b = 8 * EH + 4 * (V + 1)
         ops.append(("edge_softmax_bwd", f"hgnn::edge_rows_kernel<1, *, {H}>", b,
@@ -378,11 +378,15 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
     # graph is half row kernel, half hub kernel: the row kernel does not dominate the step because its call is long)
     kdb = traffic_db.get(w.name, {})
 
+    def exact_name(pattern):
+        """The kernel that a pattern stands for, where the profile holds exactly one."""
+        names = fnmatch.filter(kdb, pattern)
+        return names[0] if len(names) == 1 else pattern
+
     def profiled(i):
         """The profile's record of the kernel of op i: of one kernel, and of launches that fit into the call (a profile of
         other code than the one timed here says nothing about it), else None."""
-        names = fnmatch.filter(kdb, ops[i][1])
-        rec = kdb[names[0]] if len(names) == 1 else None
+        rec = kdb.get(exact_name(ops[i][1]))
         return rec if rec and 0 < rec.get("avg_us", 0) * 1e-3 <= 1.25 * op_avg[i] else None
 
     def kernel_time(i):
@@ -403,7 +407,7 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
     # every call launches its main kernel once (a column-blocked plan walks all its blocks inside one launch); the
     # short follow-up kernels of a call ride along in the time
     per_call = 1
-    roofline = {"bound": "hbm", "kernel": dom_kernel, "calls_per_step": len(idx), "kernel_launches_per_call": per_call,
+    roofline = {"bound": "hbm", "kernel": exact_name(dom_kernel), "calls_per_step": len(idx), "kernel_launches_per_call": per_call,
                 "achieved": round(dom_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(dom_gbps / HBM_PEAK_GBPS, 4), "traffic": traffic,
                 "algorithmic_bytes": int(dom_bytes / per_call), "avg_ms": round(dom_ms / per_call, 4),
@@ -433,7 +437,7 @@ def run_workload(args, wname, torch, np, hgnn, wl, dev, traffic_db, first, busy_
         d = {"ms": round(float(t), 4), "median_ms": round(float(op_med[i]), 4), "min_ms": round(float(op_min[i]), 4),
              "cold_ms": round(float(op_cold[i]), 4), "min_GBps": round(o[2] / (t * 1e-3) / 1e9, 1),
              "frac_of_hbm_peak": round(o[2] / (t * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
-             "req_GBps": round(o[4] / (t * 1e-3) / 1e9, 1), "kernel": o[1]}
+             "req_GBps": round(o[4] / (t * 1e-3) / 1e9, 1), "kernel": exact_name(o[1])}
         if o[0] in hbm_busy and hbm_busy[o[0]] is not None:
             d["hbm_busy_percent"] = hbm_busy[o[0]]
             if busy_cal and busy_cal.get("copy_busy_percent"):
