@@ -634,10 +634,13 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
           }
         }
       }
+      // (also without branches, 2.1 M x 128 47.5 -> 46.4 us; without factors 37: a line more a non-zero.  The factor of column 0 may be infinite)
+      if (WM == 2) {
+        float t[E];
 #pragma unroll
-      for (int m = 0; m < E; ++m) {
-        cs[m] = 0.f;
-        if (WM == 2) cs[m] = a.col_scale[run.has(m) ? c[m] : 0];  // (2.1 M x 128 47.5 -> 46.4 us; without factors 37: a line more a non-zero)
+        for (int m = 0; m < E; ++m) t[m] = a.col_scale[run.has(m) ? c[m] : 0];
+#pragma unroll
+        for (int m = 0; m < E; ++m) cs[m] = run.has(m) ? t[m] : 0.f;
       }
 #pragma unroll
       for (int m = 0; m < E; ++m) c[m] = table.handle(c[m], run.has(m));

@@ -131,6 +131,54 @@ def test_rounds_of_blocks_at_borders(hgnn, dev, F, H, what):
     hgnn.hgnn_plan_destroy(p)
 
 
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("nb", [1, 2])
+@pytest.mark.parametrize("F,H,what", [(64, 1, "none"), (64, 1, "w"), (64, 1, "map"), (64, 2, "w"), (64, 2, "map"), (42, 1, "none"), (16, 1, "w"),
+                                      (256, 1, "map")])
+def test_values_that_no_non_zero_reaches(hgnn, dev, F, H, what, nb, bad):
+    """Column factors and feature rows of columns without non-zeros (the first of the graph and of a block, the last), and the edge value of
+    slot 0, which belongs to one row: none of them is in any other row, whatever the rows leave over of a batch, a round or a wave."""
+    print(f"unreached values F={F} H={H} {what} nb={nb} {bad}", flush=True)
+    lens = np.array([1, 2, 3, 4, 5, 6, 7, 8, 9, 0, 15, 17, 31, 32, 33, 40, 41, 63, 64, 65, 95, 127, 129, 191, 255, 256, 257, 300])
+    deg = np.tile(lens, 12)
+    V, D = deg.size, F // H
+    r = np.random.default_rng(F + H + nb)
+    dead = np.array([0, V // 2, V - 1])
+    alive = np.setdiff1d(np.arange(V), dead)
+    col = np.concatenate([np.sort(r.choice(alive, n)) for n in deg]).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    row, E = np.repeat(np.arange(V), deg), col.size
+    X, cs, rs = f16(r.standard_normal((V, F))), r.uniform(0.5, 2, V).astype(np.float32), r.uniform(0.5, 2, V).astype(np.float32)
+    X[dead], cs[dead] = bad, bad
+    w = eid = None
+    keep = np.ones(V, bool)
+    if what != "none":
+        w = f16(r.standard_normal((E, H)))
+    if what == "map":
+        eid = r.permutation(E).astype(np.int32)
+        w[0] = bad  # of one non-zero
+        keep[row[eid == 0]] = False
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), eid=None if eid is None else up(eid, dev))
+    p = hgnn.hgnn_plan_create(g, 256, (F + 7) // 8 * 8, H, col_blocks=nb)
+    pitch = (F + 7) // 8 * 8
+    Xp = np.zeros((V, pitch), np.float16)
+    Xp[:, :F] = X
+    f = np.ones((E, H)) if w is None else w[slice(None) if eid is None else eid].astype(np.float64)
+    f = np.repeat(f * cs[col][:, None], D, 1)
+    for scaled in (None, torch.zeros((V, pitch), dtype=torch.float16, device=dev)):
+        Y = torch.full((V, pitch), 3.0, dtype=torch.float16, device=dev)
+        hgnn.hgnn_spmm_discretized_fused(p, g, None if w is None else up(w, dev), H, up(Xp, dev), Y, F=F, row_scale=up(rs, dev), col_scale=up(cs, dev),
+                                         scaled_x=scaled)
+        got = down(Y)[:, :F]
+        terms = np.where(keep[row][:, None], f * X[col].astype(np.float64), 0.0)
+        ref, mag = np.zeros((V, F)), np.zeros((V, F))
+        np.add.at(ref, row, terms)
+        np.add.at(mag, row, np.abs(terms))
+        compare("unreached values", got[keep], (rs[:, None] * ref)[keep], (rs[:, None] * mag)[keep])
+        assert not np.isfinite(got[~keep]).any()
+    hgnn.hgnn_plan_destroy(p)
+
+
 @pytest.mark.parametrize("H", [1, 4])
 def test_table_beyond_4_gib(hgnn, dev, H):
     """Rows 2.2 M halves apart: the table spans 4.8 GB, its rows are read by 64-bit addresses."""
