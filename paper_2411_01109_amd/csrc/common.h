@@ -359,10 +359,10 @@ struct hgnn_plan {
   // column-sum kernels keep one slice's per-column scalars in LDS
   int32_t ns = 0;                   // slices; 0 = not built
   int32_t slice_w = 0;
-  int32_t nch = 0;                  // chunks of nnz / nch non-zeros each (a multiple of 8)
+  int32_t nch = 0;                  // chunks of about as many non-zeros and rows each (a multiple of 8)
   bool slice_scores = false;        // scores go over the slices too (slices.hip)
   int32_t* scut = nullptr;          // [ns+1][nrows] first CSR position of row r whose column is >= s*slice_w
-  int32_t* chunk_row = nullptr;     // row where the share of a chunk that a wave takes begins
+  int2* slice_share = nullptr;      // row and position where the share of a chunk that a wave takes begins
   unsigned long long* col_part = nullptr;  // [nch][ncols] fixed-point partial column sums of the chunks
   float* col_poison = nullptr;      // [ncols] sums of non-finite inputs; zero between calls
 };

@@ -628,7 +628,7 @@ static void destroy_plan(hgnn_plan* p, bool idle) {
   dev_put(p->grp_row, idle);
   dev_put(p->gstage, idle);
   dev_put(p->scut, idle);
-  dev_put(p->chunk_row, idle);
+  dev_put(p->slice_share, idle);
   dev_put(p->col_part, idle);
   dev_put(p->col_poison, idle);
   delete p;

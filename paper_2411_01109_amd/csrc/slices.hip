@@ -29,9 +29,8 @@ constexpr int kSliceUnroll = 8;  // row pieces whose loads a wave has in flight 
 
 struct SliceArgs {
   const int* scut;       // [ns+1][nrows]: first CSR position of row r whose column is >= s*W (s = ns: end of the row)
-  const int* chunk_row;  // [nch * kSliceWaves + 1] row of the first non-zero of every wave's share
+  const int2* share;     // [nch * kSliceWaves + 1] row and position where every wave's share begins
   const int* col;
-  int64_t nnz;
   int nrows, ncols, ns, nch, W;
   // score (and alpha from lse)
   const float* el;   // [nrows]
@@ -81,12 +80,11 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
     else s_er[i] = a.er[col0 + i];
   }
   __syncthreads();
-  // A wave's share is as many positions of the edge arrays as every other's, and may begin and end inside a row: with whole rows, a power law's
-  // longest were a wave's work for most of the time (3.5 M non-zeros of 13 292 vertices, score 287 -> 16, column sums 371 -> 28 us; 24 M of
-  // 100 000, log-normal, 61 -> 57 and 71 -> 65).
-  const int64_t shares = int64_t(a.nch) * kSliceWaves, share = int64_t(c) * kSliceWaves + wave;
-  const int p0 = int(a.nnz * share / shares), p1 = int(a.nnz * (share + 1) / shares);
-  const int r0 = a.chunk_row[share], r1 = min(a.chunk_row[share + 1] + 1, a.nrows);
+  // A wave's share may begin and end inside a row: with whole rows, a power law's longest were a wave's work for most of the time (3.5 M
+  // non-zeros of 13 292 vertices, score 287 -> 16, column sums 371 -> 28 us; 24 M of 100 000, log-normal, 61 -> 57 and 71 -> 65).  How it is
+  // measured: share_begins_kernel.
+  const int2 from = a.share[c * kSliceWaves + wave], to = a.share[c * kSliceWaves + wave + 1];
+  const int p0 = from.y, p1 = to.y, r0 = from.x, r1 = min(to.x + 1, a.nrows);
   const int* __restrict__ lo = a.scut + size_t(s) * size_t(a.nrows);
   const int* __restrict__ hi = lo + a.nrows;
   const unsigned short* __restrict__ tbits = reinterpret_cast<const unsigned short*>(a.t);
@@ -254,28 +252,35 @@ __global__ void slice_cuts_kernel(const int* __restrict__ rowptr, const int* __r
   scut[idx] = lo;
 }
 
-// chunk_row[c] = the row of position c * nnz / shares; chunk_row[shares] = nrows - 1
-__global__ void chunk_rows_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int shares, int* __restrict__ chunk_row) {
+// A share is as much as every other, a row counted as kRowCost non-zeros, which its bounds cost whether it has any or not: of non-zeros alone, a
+// wave walked a long stretch of empty rows by itself: 16 M non-zeros, half of 1 M rows empty one after the other, score 4654 -> 39, column sums 4395 ->
+// 47 us; the same without those rows 36.8 -> 33.6 and 45.2 -> 42.5, 24 M of 100 000, log-normal, 56.0 -> 54.2 and 66.6 -> 65.4.
+constexpr int64_t kRowCost = 4;
+inline __host__ __device__ int64_t slice_cost(int64_t nrows, int64_t nnz) { return nnz + kRowCost * nrows; }
+
+__global__ void share_begins_kernel(const int* __restrict__ rowptr, int nrows, int64_t nnz, int shares, int2* __restrict__ begin) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c > shares) return;
-  const int64_t target = nnz * c / shares;
-  int lo = 0, hi = nrows;
+  const int64_t target = slice_cost(nrows, nnz) * c / shares;
+  int lo = 0, hi = nrows;  // rows that begin at or before it
   while (lo < hi) {
     const int mid = lo + ((hi - lo) >> 1);
-    if (int64_t(rowptr[mid]) <= target) lo = mid + 1;
+    if (slice_cost(mid, rowptr[mid]) <= target) lo = mid + 1;
     else hi = mid;
   }
-  chunk_row[c] = max(lo - 1, 0);
+  const int r = max(lo - 1, 0);
+  begin[c] = make_int2(r, int(min(target - kRowCost * r, int64_t(rowptr[r + 1]))));
 }
 
 hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked, SetupStream& s) {
   // slices of an earlier call may still be in use by calls on the plan, on whatever stream
   const bool idle = p->scut == nullptr || device_idle(p->device);
   dev_put(p->scut, idle);
-  dev_put(p->chunk_row, idle);
+  dev_put(p->slice_share, idle);
   dev_put(p->col_part, idle);
   dev_put(p->col_poison, idle);
-  p->scut = p->chunk_row = nullptr;
+  p->scut = nullptr;
+  p->slice_share = nullptr;
   p->col_part = nullptr;
   p->col_poison = nullptr;
   p->ns = 0;
@@ -287,20 +292,20 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked,
   W = int(ceil_div(ceil_div(g->ncols, ns), 64) * 64);  // the same number of slices, of equal width (a short last slice would idle its compute units)
   // one workgroup per compute unit at a time (its LDS table fills most of the 160 KB): as many chunks as give
   // every compute unit one (slice, chunk) pair, a multiple of 8 so that a chunk's slices share an XCD, and not so
-  // many that a wave has less than a round of a slice's non-zeros
+  // many that a wave has less than a round of a slice's non-zeros or rows
   int nch = 8 * std::max(1, (cus / 8) / ns);
-  const int64_t by_work = 8 * std::max<int64_t>(1, g->nnz / (int64_t(8) * kSliceThreads * kSliceUnroll * ns));
+  const int64_t by_work = 8 * std::max<int64_t>(1, slice_cost(g->nrows, g->nnz) / (int64_t(8) * kSliceThreads * kSliceUnroll * ns));
   if (nch > by_work) nch = int(by_work);
   const int shares = nch * kSliceWaves;
   HGNN_HIP(dev_malloc(&p->scut, sizeof(int) * size_t(ns + 1) * size_t(g->nrows)));
-  HGNN_HIP(dev_malloc(&p->chunk_row, sizeof(int) * (size_t(shares) + 1)));
+  HGNN_HIP(dev_malloc(&p->slice_share, sizeof(int2) * (size_t(shares) + 1)));
   HGNN_HIP(dev_malloc(&p->col_part, sizeof(unsigned long long) * size_t(nch) * size_t(g->ncols)));
   HGNN_HIP(dev_malloc(&p->col_poison, sizeof(float) * size_t(g->ncols)));
   HGNN_HIP(hipMemsetAsync(p->col_poison, 0, sizeof(float) * size_t(g->ncols), s));
   slice_cuts_kernel<<<dim3(unsigned(ceil_div(int64_t(g->nrows) * (ns + 1), kBlock))), kBlock, 0, s>>>(g->rowptr, g->col, g->nrows,
                                                                                                     ns, W, p->scut);
-  chunk_rows_kernel<<<dim3(unsigned(ceil_div(shares + 1, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, g->nnz, shares, p->chunk_row);
-  HGNN_LAUNCH_CHECK("slice_cuts_kernel / chunk_rows_kernel");
+  share_begins_kernel<<<dim3(unsigned(ceil_div(shares + 1, kBlock))), kBlock, 0, s>>>(g->rowptr, g->nrows, g->nnz, shares, p->slice_share);
+  HGNN_LAUNCH_CHECK("slice_cuts_kernel / share_begins_kernel");
   HGNN_HIP(s.wait());
   // Scores gather through the caches just as well where there are few: us, segments / slices, 1 M non-zeros of 13 292 vertices 8.4 / 14.0, 1.2 M of
   // 4000 8.3 / 11.8, 3 M of 30 000 17.4 / 16.3, 3.5 M of 13 292 14.0 / 16.0, 5.4 M of 20 000 22.0 / 22.2, 6 M of 60 000 32.6 / 23.0 (power law 26.0 / 34.3), 8 M
@@ -316,9 +321,8 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked,
 static SliceArgs slice_args(const hgnn_plan* p, const hgnn_csr* g) {
   SliceArgs a{};
   a.scut = p->scut;
-  a.chunk_row = p->chunk_row;
+  a.share = p->slice_share;
   a.col = g->col;
-  a.nnz = g->nnz;
   a.nrows = g->nrows;
   a.ncols = g->ncols;
   a.ns = p->ns;

@@ -28,7 +28,7 @@ import re
 import sys
 
 SETUP_KERNELS = ("validate", "source_rows", "offsets", "seg_rows", "row_lists", "block_fill", "block_cuts", "block_delta",
-                 "block_counts", "block_rowptr", "hub_zero", "group_", "coo_", "transpose_", "slice_cuts", "chunk_rows", "sort_", "split_words", "plan_")
+                 "block_counts", "block_rowptr", "hub_zero", "group_", "coo_", "transpose_", "slice_cuts", "share_begins", "sort_", "split_words", "plan_")
 COPY = "__amd_rocclr_copyBuffer"
 GIB_KIB = 1048576.0
 

@@ -201,3 +201,56 @@ def test_slices_of_long_rows(hgnn, dev, V, ncols, E, W):
     ref = np.zeros(ncols)
     np.add.at(ref, col, t[:, 0].astype(np.float64))  # exact
     assert np.all(np.abs(down(sums)[:, 0] - ref) <= np.abs(ref) * 2.0 ** -11 * (1 + 2.0 ** -10) + 2.0 ** -25)
+
+
+# stretches of rows without non-zeros, longer than the rows that have any by far: in the middle, at the end, at both, one non-zero in the midst
+@pytest.mark.parametrize("where", ["middle", "end", "all around", "lone"])
+@pytest.mark.parametrize("W", [0, 1024])
+def test_slices_beside_empty_rows(hgnn, dev, where, W):
+    print(f"slices beside empty rows {where} W={W}", flush=True)
+    full, many, ncols, D = np.full(2000, 200, np.int64), np.zeros(600000, np.int64), 4000, 8
+    deg = {"middle": [full, many, full], "end": [full, full, many], "all around": [many, full, many, full, many],
+           "lone": [full, many, [1], many, full]}[where]
+    deg = np.concatenate(deg)
+    r = np.random.default_rng(W + deg.size)
+    E = int(deg.sum())
+    t = f16(r.standard_normal((E, 1)))
+    a_l, a_r = (up(f16(r.standard_normal((1, D))), dev) for _ in range(2))
+    Vt = up(f16(r.standard_normal((ncols, D))), dev)
+    key = r.integers(0, ncols, E)
+
+    def passes(deg):
+        V, row = deg.size, np.repeat(np.arange(deg.size), deg)
+        col = key[np.lexsort((key, row))].astype(np.int32)
+        g = hgnn.Csr(up(np.concatenate([[0], np.cumsum(deg)]).astype(np.int32), dev), up(col, dev), ncols=ncols)
+        U = up(f16(np.random.default_rng(1).standard_normal((V, D))), dev)
+        out = [torch.full((E, 1), 9.0, dtype=torch.float16, device=dev) for _ in range(2)]
+        p = hgnn.hgnn_plan_create(g, 256, 64, 1, col_blocks=1)
+        hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_GAT_SCORE, 1, D, U, Vt, out[0], a_l, a_r, 0.2)  # by segments
+        hgnn.hgnn_plan_add_slices(p, g, W)
+        sums, td = torch.full((ncols, 1), 9.0, dtype=torch.float16, device=dev), up(t, dev)
+
+        def both():
+            hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_GAT_SCORE, 1, D, U, Vt, out[1], a_l, a_r, 0.2)
+            hgnn.hgnn_edge_colsum(g, p, 1, td, sums)
+
+        both()
+        assert torch.equal(out[0], out[1])  # the same sums of the same fp32 values
+        ref = np.zeros(ncols)
+        np.add.at(ref, col, t[:, 0].astype(np.float64))  # exact
+        assert np.all(np.abs(down(sums)[:, 0] - ref) <= np.abs(ref) * 2.0 ** -11 * (1 + 2.0 ** -10) + 2.0 ** -25)
+        ms = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            both()
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        hgnn.hgnn_plan_destroy(p)
+        return sorted(ms)[3]
+
+    # the empty rows are shared out like the others: 600 000 of them cost some 30 us and a wave that walks them by itself takes 10 ms
+    with_empty, without = passes(deg), passes(deg[deg > 0])
+    print(f"  {1e3 * with_empty:.0f} us, without empty rows {1e3 * without:.0f} us", flush=True)
+    assert with_empty < 8 * without + 0.5
