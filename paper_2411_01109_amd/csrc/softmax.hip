@@ -469,8 +469,17 @@ __device__ __forceinline__ void edge_hub_partial(const EdgeRowArgs& a, const Hub
 // The softmax takes the chunks last because its follow-up reads them again while the caches still hold them (then, 114 M non-zeros, one head:
 // forward 189 us with the chunks first, 184 last, 179 in launches of their own; backward 210, 201, 207); the sums take them first (23.3 us last).
 // Longer rows: a workgroup takes 16 rows, listed or not, a team of 16 lanes each where that is four vectors a lane at most; the longer ones
-// among them are dealt out to its waves.
-constexpr int kListTeam = 16, kListRows = kHubThreads / kListTeam;
+// among them are dealt out to its waves.  Rows in a row often are of one length (vertices in the order of their degrees), so that a workgroup of
+// neighbours would have sixteen of the longest: it takes four in a row from each of four places of a stretch of kDealt workgroups' rows.  5.5 M
+// power law in the order of the degrees, us, forward; backward, a wave a row / sixteen neighbours / dealt out: without a plan, one head 83; 83 / 99;
+// 113 / 51; 60, eight 623; 812 / 950; 1253 / 482; 660; listed, four heads 47; 39 / 51; 56 / 34; 42.  In no order the offsets are in more lines:
+// without a plan one head 91; 85 / 53; 59 / 55; 60, listed, four 58; 46 / 42; 45 / 40; 44, and 8 M uniform without a plan 173; 175 / 79; 88 / 85; 94
+// (stretches of 16 and 64 workgroups: order of the degrees, one head 63; 71 and 55; 64).
+constexpr int kListTeam = 16, kListRows = kHubThreads / kListTeam, kDealt = 256;
+__device__ __forceinline__ int64_t dealt_row(int wg, int wave, int team) {
+  constexpr int kTeams = kWave / kListTeam;
+  return (int64_t(wg / kDealt) * (kHubThreads / kWave) + wave) * (kDealt * kTeams) + (wg % kDealt) * kTeams + team;
+}
 template <int OP, int LR, int H>
 __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, HubChunks c, int n_chunks, int wave_wgs) {
   constexpr int W = kHubThreads / kWave;
@@ -483,7 +492,7 @@ __global__ __launch_bounds__(kHubThreads) void edge_rows_kernel(EdgeRowArgs a, H
   if (OP == kSum) wg -= n_chunks;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (wg < wave_wgs && a.list_max > 0) {
-    const int64_t i = (int64_t(wg) * W + wave) * (kWave / kListTeam) + lane / kListTeam;
+    const int64_t i = dealt_row(wg, wave, lane / kListTeam);
     int row = 0, beg = 0, end = 0;
     if (i < a.n_list) {
       row = a.row_list ? a.row_list[i] : int(i);
@@ -636,7 +645,9 @@ static void launch_rows_h(int LR, dim3 grid, hipStream_t s, const EdgeRowArgs& a
 // Whether the listed rows share workgroups (kListTeam), or take a wave each: with four heads a row of 100 non-zeros fills most of a wave, and few
 // rows are then better spread.  us, a wave each / shared, forward; backward: 5.5 M non-zeros, 28 000 listed rows, H = 1 22 / 16.7; 22 / 19.5,
 // H = 4 52 / 40; 47 / 44, H = 8 86 / 77; 94 / 103; 1.5 M, 9000 listed rows, H = 1 11 / 9.5; 10.5 / 9.9, H = 2 15 / 13; 17 / 16, H = 4 28 / 28;
-// 28 / 33, H = 8 52 / 57; 48 / 58.
+// 28 / 33, H = 8 52 / 57; 48 / 58.  Without a list they share workgroups with any number of heads, or a wave would be started for every row:
+// power law of 1.5 M, H = 4 262 / 154; 249 / 165, H = 8 480 / 350; 470 / 338; log-normal, 6 M of 60 000 rows, H = 4 56 / 45; 45 / 40, H = 8 94 / 77;
+// 103 / 95; 300 000 of 1000 rows, H = 8 56 / 40; 46 / 29.
 static bool list_teams_pay(int H, int n_list) { return H <= 2 || (H == 4 && n_list >= 16384); }
 
 // Launches the row kernel (and the follow-up of the chunks when a plan lists long rows) for H in {1,2,4,8}.
@@ -644,7 +655,7 @@ template <int OP>
 static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeRowArgs a, hipStream_t s) {
   const int H = a.H;
   // the chunked long-row kernels keep partial results in the plan, sized for its max_H heads: with more heads than
-  // that the call runs as it does without a plan (a wave for every row above the sub-wave tier)
+  // that the call runs as it does without a plan
   if (p && H > p->max_H) p = nullptr;
   if (!(H == 1 || H == 2 || H == 4 || H == 8) || !aligned16(a.x0) || !aligned16(a.out) ||
       (a.x1 && !aligned16(a.x1)) || (a.x2 && !aligned16(a.x2))) {
@@ -680,7 +691,7 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
     a.row_list = mid_list ? p->mid_row : nullptr;
     a.n_list = mid_list ? p->n_mid : g->nrows;
     if (!mid_list || list_teams_pay(H, p->n_mid)) a.list_max = OP == kSum && a.eid ? 4 * kListTeam : 4 * 8 * kListTeam / H;
-    wave_wgs = ceil_div(a.n_list, a.list_max > 0 ? kListRows : rows_per_wg);
+    wave_wgs = a.list_max > 0 ? ceil_div(a.n_list, kListRows * kDealt) * kDealt : ceil_div(a.n_list, rows_per_wg);
   }
   const int n_chunks = big > 0 ? p->n_hub_chunks : 0;
   const HubChunks c = big > 0 ? HubChunks{p->hub_chunk_row, p->hub_chunk_first, p->hub_chunk_count, p->hub_part} : HubChunks{};
