@@ -124,6 +124,36 @@ struct Held {
       if (t < Span<H>::kEnds && s.has(t)) e[i] = *reinterpret_cast<const hv_t*>(p + int64_t(s.end_at(t)) * H);
     }
   }
+  // the same of the three tensors of the backward, together; e may be null (then it is 1)
+  static __device__ __forceinline__ void load_bwd(const half_t* alpha, const half_t* dalpha, const half_t* e, const Span<H>& s, int rank, Held& al,
+                                                  Held& da, Held& el) {
+    const int64_t first = int64_t(s.body) * H;
+    const half8_t *const q0 = reinterpret_cast<const half8_t*>(alpha + first), *const q1 = reinterpret_cast<const half8_t*>(dalpha + first),
+                  *const q2 = reinterpret_cast<const half8_t*>(e + first);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+      al.v[i] = da.v[i] = half8_t(0);
+      el.v[i] = half8_t(1);
+      const int t = rank + SIZE * i;
+      if (t < s.n_body) {
+        al.v[i] = q0[t];
+        da.v[i] = q1[t];
+        if (e) el.v[i] = q2[t];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+      al.e[i] = da.e[i] = hv_t(half_t(0));
+      el.e[i] = hv_t(half_t(1));
+      const int t = rank + SIZE * i;
+      if (t < Span<H>::kEnds && s.has(t)) {
+        const int64_t at = int64_t(s.end_at(t)) * H;
+        al.e[i] = *reinterpret_cast<const hv_t*>(alpha + at);
+        da.e[i] = *reinterpret_cast<const hv_t*>(dalpha + at);
+        if (e) el.e[i] = *reinterpret_cast<const hv_t*>(e + at);
+      }
+    }
+  }
 };
 
 // ---- forward: one row by one team ----------------------------------------------------------------------
@@ -226,11 +256,15 @@ __device__ __forceinline__ void softmax_bwd_row(const EdgeRowArgs& a, const Team
   typedef typename Hold::hv_t hv_t;
   const Span<H> s(beg, end);
   // what a lane does not have is zero on both sides, so its products vanish (a neighbouring row's infinity times zero would not)
-  Hold al, da;
-  al.load(a.x0, s, team.rank, half_t(0));
-  da.load(a.x1, s, team.rank, half_t(0));
+  // All that is held is asked for together, e (1 if there is none) with the others.  Behind the sums a wave waited for it twice more, the ends'
+  // behind the stores of the vectors, and three conditions on every vector and end cost as much as masks where rows are short.  us, masked
+  // vectors / ends apart, each array by itself, e behind the sums / now: 8 M uniform of 2 M rows, one head 42 / 45 / 41, two 44 / 57 / 37; 20 M of
+  // 300 000, four heads 146 / 166 / 140; of 150 000, two 73 / 74 / 61; 20 M power law, two 108 / 103 / 86.  (20 M of 150 000 to 200 000 rows, eight
+  // heads: 219 / 230 / 230.)
+  Hold al, da, el;
   const int64_t first = int64_t(s.body) * H;
   auto vec = [&](const half_t* p, int t) { return reinterpret_cast<const half8_t*>(p + first)[t]; };
+  Hold::load_bwd(a.x0, a.x1, a.x2, s, team.rank, al, da, el);
   half8_t* const dst = reinterpret_cast<half8_t*>(a.out + first);
   float t[H];
 #pragma unroll
@@ -248,8 +282,7 @@ __device__ __forceinline__ void softmax_bwd_row(const EdgeRowArgs& a, const Team
     for (int h = 0; h < H; ++h) t[h] = fmaf(float(al.e[i][h]), float(da.e[i][h]), t[h]);
   for (int v = team.rank + SIZE * KEEP; v < s.n_body; v += SIZE) visit(vec(a.x0, v), vec(a.x1, v));
   team.template reduce<H, false>(t);
-  auto emit = [&](const half8_t& va, const half8_t& vd, int v) {
-    const half8_t ve = a.x2 ? vec(a.x2, v) : half8_t(1);
+  auto emit = [&](const half8_t& va, const half8_t& vd, const half8_t& ve, int v) {
     half8_t o;
 #pragma unroll
     for (int q = 0; q < 8; ++q) o[q] = softmax_bwd_value(a, va[q], vd[q], ve[q], t[q % H]);
@@ -258,22 +291,21 @@ __device__ __forceinline__ void softmax_bwd_row(const EdgeRowArgs& a, const Team
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
     const int v = team.rank + SIZE * i;
-    if (v < s.n_body) emit(al.v[i], da.v[i], v);
+    if (v < s.n_body) emit(al.v[i], da.v[i], el.v[i], v);
   }
 #pragma unroll
   for (int i = 0; i < Hold::NE; ++i) {
     const int v = team.rank + SIZE * i;
     if (v < Span<H>::kEnds && s.has(v)) {
       const int64_t at = int64_t(s.end_at(v)) * H;
-      const hv_t ve = a.x2 ? *reinterpret_cast<const hv_t*>(a.x2 + at) : hv_t(half_t(1));
       hv_t o;
 #pragma unroll
-      for (int h = 0; h < H; ++h) o[h] = softmax_bwd_value(a, al.e[i][h], da.e[i][h], ve[h], t[h]);
+      for (int h = 0; h < H; ++h) o[h] = softmax_bwd_value(a, al.e[i][h], da.e[i][h], el.e[i][h], t[h]);
       *reinterpret_cast<hv_t*>(a.out + at) = o;
     }
   }
   for (int v = team.rank + SIZE * KEEP; v < s.n_body; v += SIZE)
-    emit(vec(a.x0, v), vec(a.x1, v), v);
+    emit(vec(a.x0, v), vec(a.x1, v), a.x2 ? vec(a.x2, v) : half8_t(1), v);
 }
 
 // ---- row sums: out[row,h] = sum over the row of t[slot(k), h] -------------------------------------------
