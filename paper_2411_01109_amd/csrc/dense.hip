@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 
 #include "common.h"
 
@@ -283,9 +284,10 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
 }
 
 // ---- weight gradient ---------------------------------------------------------------------------------
-struct WgradArgs {
+struct WgradArgs {  // (with what the launch adds, the kernel reads 64 bytes: one line)
   int64_t n;
-  int K, F;
+  uint16_t K, F;  // 4096 at most
+  int run;        // LONG: steps whose products are added up before they are added to those of earlier steps
   const half_t* X;
   int64_t ldx;
   const half_t* dY;
@@ -321,8 +323,14 @@ __device__ __forceinline__ half8_t wgrad_column(const half_t* tile, int pitch, i
 // those reads.  The teams' blocks are added by all teams, a share of the columns each, which also write it: 4096 rows 64 x 64 6.6 -> 4.7 us
 // (one team that added the others in turn and wrote).  They are written as the lanes hold them, tile after tile, 16 bytes
 // a lane; row by row, 4 bytes a lane in pieces of 64 bytes, 262 144 rows took 0.5 us more.
-template <int WA, int WB>
-__global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
+// LONG: a workgroup adds its steps up in runs, in as many registers again (two workgroups per compute unit then).  A product of 32 rows rounds some
+// four times, and a long chain of them is what the result's error comes from.  Relative error against 64 bits, 1e-7, as many partial results as are
+// resident / fewer, of longer chains / those in runs: 19 717 rows of 504 x 64 1.2 / 1.3 / 1.2, 131 072 of 128 x 128 1.7 / 1.8 / 1.55, 233 000 of 608 x 64
+// 2.2 / 2.4 / 1.5, 2.4 M of 128 x 128 4.6 / 4.6 / 2.2, 600 000 of 608 x 128 6.2 / 6.2 / 1.9; us 15.6 / 12.2 / 12.8, 22.4 / 18.9 / 19.5, 67.4 / 60.7 / 60.6,
+// 205 / 206 / 206, 264 / 262 / 264.
+constexpr int kWgradRun = 8;
+template <int WA, int WB, bool LONG>
+__global__ __launch_bounds__(kBlock, LONG ? 2 : 3) void wgrad_kernel(WgradArgs a) {
   constexpr int WT = WA * WB, WR = 4 / WT;     // waves in a team, teams
   constexpr int NBUF = WR == 1 ? 2 : 1;        // one team: two buffers, one barrier per step
   constexpr int PX = 64 * WA + 16, PY = 64 * WB + 16;
@@ -357,12 +365,15 @@ __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
     if (WT == 1) wave_sync();
     else __syncthreads();
   };
-  float4_t acc[4][4];
+  float4_t acc[4][4], before[LONG ? 4 : 1][4];  // before: earlier runs
 #pragma unroll
   for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = float4_t{0.f, 0.f, 0.f, 0.f};
-  int buf = 0;
+    for (int y = 0; y < 4; ++y) {
+      acc[x][y] = float4_t{0.f, 0.f, 0.f, 0.f};
+      if (LONG) before[x][y] = acc[x][y];
+    }
+  int buf = 0, left = a.run;
   if (int64_t(blockIdx.x) < nsteps) load(blockIdx.x);
   for (int64_t step = blockIdx.x; step < nsteps; step += gridDim.x) {  // uniform over the workgroup
     half_t* xs = tiles + buf * TILE;
@@ -391,6 +402,22 @@ __global__ __launch_bounds__(kBlock, 3) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
       for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[x], yb[y], acc[x][y], 0, 0, 0);
     if (NBUF == 2) buf ^= 1;
+    if (LONG && --left == 0) {
+      left = a.run;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          before[x][y] += acc[x][y];
+          acc[x][y] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  }
+  if (LONG) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[x][y] += before[x][y];
   }
   // every team adds and writes a share of the block: its columns x = XS team .. of X, in the order of the teams
   constexpr int XS = 4 / WR;
@@ -792,15 +819,19 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   int64_t parts = std::llround(std::sqrt(1400. * double(steps) / double(10 + tiles)));
   // a single block: whole rounds of one workgroup per compute unit (300 000 rows of 64 x 64: 256 17.7, 288 19.4, 512 19.1)
   if (blocks == 1 && parts > kCus && parts < 2 * kCus) parts = kCus;
-  // No more than the workspace holds (64 at least of sides of 8: a quarter of the tile) and than there are steps, three
-  // workgroups per compute unit of 128 x 128 values and two of the others (233 000 rows of 608 x 64: 480 of them 62.4,
-  // 510 74.6, 680 and more 67.4); eight XCDs take the workgroups in turn, so a multiple of eight leaves the blocks of the
+  // No more than the workspace holds (64 at least of sides of 8: a quarter of the tile) and than there are steps, two
+  // workgroups per compute unit (233 000 rows of 608 x 64: 480 of them 62.4, 510 74.6, 680 and more 67.4); eight XCDs take the workgroups in turn, so a multiple of eight leaves the blocks of the
   // same rows on one L2
-  int64_t most = std::min<int64_t>((WR == 1 ? 3 : 2) * kCus / blocks, int64_t(wgrad_parts(K, F)) * K * F / (tiles * 256));
+  int64_t most = std::min<int64_t>(2 * kCus / blocks, int64_t(wgrad_parts(K, F)) * K * F / (tiles * 256));
   if (most >= 16) most = most / 8 * 8;
   if (parts >= 16) parts = (parts + 7) / 8 * 8;
   parts = std::max<int64_t>(1, std::min(std::min(parts, most), steps));
-  WgradArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
+  const int64_t each = ceil_div(steps, parts);  // steps of a workgroup
+  // where the chain is longer than the partial results that are left out made it: of several blocks those were few (9000 rows of 504 x 64, a chain of
+  // four steps 1.17 for 1.11e-7; of one block with eight 262 144 of 64 x 64 1.6 for 1.8e-7)
+  const bool in_runs = each > (blocks == 1 ? kWgradRun : 2);
+  const int run = int(ceil_div(each, std::max<int64_t>(2, ceil_div(each, kWgradRun))));
+  WgradArgs a{n, uint16_t(K), uint16_t(F), run, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(dY), ldy, part};
   // few rows: one launch without partial results, up to the rows at which fetching them in 32-byte pieces costs what the
   // second launch and the partial results do, later the larger dW is.  us behind the kernel that wrote dY, one launch / two:
   //   K x F         1000        1500        2000        2500        3000        4096        6000 rows
@@ -824,10 +855,17 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
     return HGNN_OK;
   }
   const dim3 grid{unsigned(parts), unsigned(kb), unsigned(fb)};
-  if (WA == 1 && WB == 1) wgrad_kernel<1, 1><<<grid, kBlock, 0, s>>>(a);
-  else if (WA == 2 && WB == 1) wgrad_kernel<2, 1><<<grid, kBlock, 0, s>>>(a);
-  else if (WA == 1) wgrad_kernel<1, 2><<<grid, kBlock, 0, s>>>(a);
-  else wgrad_kernel<2, 2><<<grid, kBlock, 0, s>>>(a);
+  const auto launch = [&](auto wide_x, auto wide_y) {
+    constexpr int A = decltype(wide_x)::value, B = decltype(wide_y)::value;
+    if (in_runs) wgrad_kernel<A, B, true><<<grid, kBlock, 0, s>>>(a);
+    else wgrad_kernel<A, B, false><<<grid, kBlock, 0, s>>>(a);
+  };
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, 2> two;
+  if (WA == 1 && WB == 1) launch(one, one);
+  else if (WB == 1) launch(two, one);
+  else if (WA == 1) launch(one, two);
+  else launch(two, two);
   HGNN_LAUNCH_CHECK("wgrad_kernel");
   partial_sum_kernel<true><<<dim3(unsigned(tiles * 4)), kWave * kSumSlices, 0, s>>>(part, tiles * 256, int(parts), K, F, dW, lddw, 0, nullptr);
   HGNN_LAUNCH_CHECK("partial_sum_kernel");

@@ -142,6 +142,27 @@ def test_linear_wgrad_partials(hgnn, dev, n, K, F):
     test_linear_wgrad_shapes(hgnn, dev, n, K, F)
 
 
+# steps of a workgroup that are added up in runs, for one and two waves across either side: some, many, the last run shorter
+@pytest.mark.parametrize("n,K,F", [(450000, 8, 8), (300001, 40, 24), (20000, 64, 200), (5000, 504, 64), (7001, 264, 40), (3500, 256, 256), (90001, 72, 72)])
+def test_linear_wgrad_runs(hgnn, dev, n, K, F):
+    test_linear_wgrad_shapes(hgnn, dev, n, K, F)
+
+
+@pytest.mark.parametrize("n,K,F,runs,partials", [(233000, 608, 64, 5, 96), (500000, 128, 128, 4, 512), (600000, 608, 128, 25, 96)])
+def test_linear_wgrad_error_of_long_sums(hgnn, dev, n, K, F, runs, partials):
+    """The error against 64 bits over many rows.  The k-th of r equal additions rounds to 2^-24 / sqrt(3) of its sum in the mean, whose square is k / r of
+    the result's, so a chain leaves 2^-24 / sqrt(3) * sqrt(r / 2).  A product of 32 rows rounds some four times, eight of them follow each other; then
+    the runs, a sixteenth of the partial results, and 16 sums of those.  One chain over all rows of a workgroup had 2.4 to 6.2e-7."""
+    gen = torch.Generator(device=dev).manual_seed(n)
+    X, dY = (torch.randn((n, c), generator=gen, device=dev, dtype=torch.float16) for c in (K, F))
+    dW = torch.empty((K, F), dtype=torch.float32, device=dev)
+    hgnn.hgnn_linear_wgrad(X, dY, dW, torch.empty(hgnn.hgnn_linear_wgrad_workspace(K, F), dtype=torch.uint8, device=dev))
+    ref = sum(X[i:i + 50000].double().T.contiguous() @ dY[i:i + 50000].double() for i in range(0, n, 50000))
+    rel = float((dW.double() - ref).norm() / ref.norm())
+    print(f"wgrad n={n} K={K} F={F}: relative error {rel:.2e}", flush=True)
+    assert rel <= 2.0 ** -24 / 3 ** 0.5 * (4 * 8 / 2 + runs / 2 + partials / 16 / 2 + 16 / 2) ** 0.5
+
+
 def test_linear_wgrad_errors(hgnn, dev):
     X = torch.zeros((64, 64), dtype=torch.float16, device=dev)
     dW = torch.zeros((64, 64), dtype=torch.float32, device=dev)
