@@ -283,11 +283,13 @@ __device__ inline int block_exclusive_scan(int v, int* total) {
 // A workgroup per window of rows (kRowsPerBlock = kTaskWindow): the rules of the offset array, the members of the row lists and the
 // pieces of the row tasks.  The three as launches of their own took 14 us at 262 144 rows, this one 9.
 static_assert(kRowsPerBlock == kTaskWindow && kBlock == kTaskThreads, "row lists and row tasks share their windows");
+template <bool MIDS>
 __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists q, TaskSource tq, int nblk, int* __restrict__ counts,
                                                             int* __restrict__ task_counts, GraphFacts* f) {
   constexpr int kListed = kLists + kTaskAll, kSums = kListed + 1;
-  __shared__ int s_total[kSums];
+  __shared__ int s_total[kSums], s_sample;
   if (threadIdx.x < kSums) s_total[threadIdx.x] = 0;
+  if (MIDS && threadIdx.x == 0) s_sample = 0;
   __syncthreads();
   const int64_t base = int64_t(blockIdx.x) * kRowsPerBlock + threadIdx.x * kRowsPerThread;
   int bad = 0;
@@ -295,6 +297,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
     if (g.rowptr[0] != 0) bad = 1;
     else if (int64_t(g.rowptr[g.nrows]) != g.nnz) bad = 2;
   }
+  const MidSample<MIDS> sample(tq);
   int c[kLists] = {0, 0, 0, 0}, n[kTaskAll] = {}, listed = 0;
   for (int u = 0; u < kRowsPerThread; ++u) {
     if (base + u >= q.nrows) break;
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
     if (!bad && len < 0) bad = 3;
     for (int i = 0; i < kLists; ++i) c[i] += m[i];
     if (m[kBigList] || m[kMidList]) listed += len;
-    task_count_row<true>(tq, g.rowptr, r, n);
+    task_count_row<true, MIDS>(tq, g.rowptr, r, n);
   }
   if (bad) atomicMax(&f->bad, 8 - bad);
 #pragma unroll
@@ -312,12 +315,14 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(hgnn_csr g, RowLists
     const int v = wave_sum(i < kLists ? c[i < kLists ? i : 0] : (i < kListed ? n[i < kListed && i >= kLists ? i - kLists : 0] : listed));
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&s_total[i], v);
   }
+  sample.add(&s_sample);
   __syncthreads();
   if (nblk == 0) return;  // no rows
   const int i = threadIdx.x;
   const int counters = tq.range_min == kNoRanges ? kTaskCounters : kTaskAll;
   if (i < kLists) counts[i * nblk + blockIdx.x] = s_total[i];
-  else if (i < kLists + counters) task_counts[int64_t(i - kLists) * nblk + blockIdx.x] = task_counter<true>(s_total + kLists, i - kLists);
+  else if (i < kLists + counters)
+    task_counts[int64_t(i - kLists) * nblk + blockIdx.x] = task_counter<true, MIDS>(s_total + kLists, i - kLists, MIDS && MidSample<MIDS>::many(tq, s_sample));
   else if (i == kListed && s_total[i]) atomicAdd(&f->listed, (unsigned long long)s_total[i]);
 }
 
@@ -403,6 +408,7 @@ __device__ __forceinline__ void row_lists_write(const RowLists& q, int b, int nb
 // Workgroups for the windows of the row tasks, then (with members) for those of the row lists and of the rows cut at column ranges, then
 // for the segments: none needs
 // what another one writes, and as launches of their own they took 25 us at 5.5 M non-zeros, mostly latency, in one 11.
+template <bool MIDS>
 __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n, const int* __restrict__ task_counts, const int* __restrict__ sums,
                                                            hgnn_task_sec* __restrict__ sec, int4* __restrict__ task, int* __restrict__ zrow,
                                                            int4* __restrict__ split, RowLists q, int list_blocks,
@@ -421,7 +427,7 @@ __global__ __launch_bounds__(kBlock) void plan_write_kernel(TaskSource tq, int n
     at.split = split_at[w];
     range_write(ranges, w, at, rtask, rsplit);
   } else if (b < n) {
-    task_write<false, true>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split, 0);
+    task_write<false, true, MIDS>(tq, b, 0, n, task_counts, sums, sec, nullptr, task, zrow, split, 0);
   } else if (b < n + list_blocks) {
     row_lists_write(q, b - n, n, offsets, o);
   } else {
@@ -473,7 +479,9 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   hgnn_status st = task_prepare(tq, tc);
   if (st != HGNN_OK) return st;
   HGNN_HIP(hipMemsetAsync(facts, 0, sizeof(GraphFacts), s));
-  plan_count_kernel<<<dim3(unsigned(nblk > 0 ? nblk : 1)), kBlock, 0, s>>>(*g, q, tq, nblk, counts, tc.count, facts);
+  const bool mids = has_mids(tq);
+  const auto count_kernel = mids ? plan_count_kernel<true> : plan_count_kernel<false>;
+  count_kernel<<<dim3(unsigned(nblk > 0 ? nblk : 1)), kBlock, 0, s>>>(*g, q, tq, nblk, counts, tc.count, facts);
   RangeLists ranges{};
   DevTemp range_mem(s);
   tc.ranges = tq.range_min != kNoRanges && nblk > 0;
@@ -523,7 +531,8 @@ hgnn_status plan_build_arrays(hgnn_plan* p, const hgnn_csr* g, bool blocks, Setu
   const int64_t grid = int64_t(nblk) + list_blocks + range_blocks + ceil_div(p->nseg, kBlock);
   hgnn_row_tasks* const t = p->tasks;
   if (grid > 0) {
-    plan_write_kernel<<<dim3(unsigned(grid)), kBlock, 0, s>>>(
+    const auto write_kernel = mids ? plan_write_kernel<true> : plan_write_kernel<false>;
+    write_kernel<<<dim3(unsigned(grid)), kBlock, 0, s>>>(
         tq, nblk, tc.count, tc.sums, t->sec, t->task, t->zrow, t->split, q, list_blocks, counts,
         RowListArrays{p->split_row, p->split_seg_lo, p->split_seg_hi, p->big_row, p->big_first, p->mid_row, p->hub_chunk_row,
                       p->hub_chunk_first, p->hub_chunk_count},

@@ -38,38 +38,66 @@ __device__ __forceinline__ RowCut cut_row(const TaskSource& q, const int* rp, in
 // Rows of one piece just above group_max, up to kMidLen: a window (kTaskWindow rows) leaves them to lane groups, too, where that takes most of its
 // waves away.  They are counted beside its empty rows, of which there are no more than 65535.  A wave of its own is mostly overhead there, which
 // counts where there are many; else it is the shorter chain.  us, waves / lane groups: uniform, 2 M non-zeros of 42 233 rows x 64, SpMM 28.0 / 20.9, SDDMM
-// 33.0 / 24.5, attention forward 57.8 / 31.9, backward 57.7 / 46.6; 400 000 of 8000 7.3 / 6.3, 8.6 / 8.2, 14.4 / 12.2, 16.6 / 15.6; 160 000 of 4000 5.6 /
-// 5.8, 6.6 / 7.3, 10.5 / 10.7, 12.6 / 13.7.  All rows up to 64 of a power law of 1.5 M of 30 000: 17.8 / 19.4, 16.7 / 19.4, 36.0 / 39.1, 36.1 / 39.7;
-// log-normal, 1.7 M of 60 328: 27.3 / 28.6, 27.5 / 28.7, 45.2 / 41.7, 50.6 / 47.7.  What loses: row sums behind a map of the first 24.7 / 26.3, and a plan
-// of 1.5 M takes 1 us more.  The rows are read and asked before the barrier that the counters want anyway.
+// 33.0 / 24.5, attention forward 57.8 / 31.9, backward 57.7 / 46.6; of 62 500 rows (32 on average) 28.6 / 29.5, 32.1 / 31.1, 57.9 / 45.2, 61.8 / 58.0; of 33 333
+// (60) 20.6 / 18.3, 24.1 / 21.2, 40.1 / 30.5, 41.0 / 37.7; 400 000 of 8000 7.3 / 6.4, 8.2 / 7.7, 11.2 / 10.0; of 6667 6.6 / 7.2, 7.1 / 8.3, 10.6 / 11.0; 160 000 of
+// 4000 5.6 / 5.8, 6.6 / 7.3, 10.5 / 10.7, 12.6 / 13.7.  All rows up to 64 of a power law of 1.5 M of 30 000: 17.8 / 19.4, 16.7 / 19.4, 36.0 / 39.1, 36.1 / 39.7;
+// log-normal, 1.7 M of 60 328: 27.3 / 28.6, 27.5 / 28.7, 45.2 / 41.7, 50.6 / 47.7.  What loses: row sums behind a map of the first 24.7 / 26.3, with four
+// heads of the mean 60 22.4 / 29.8.
+// In the order of the degrees other graphs have such windows, too.  With a plan they keep to waves unless the graph has kMidLeastRows of the rows
+// (power law, 1.5 M of 30 000, SpMM x 16 12.6 / 14.4, SDDMM 11.1 / 13.6; log-normal, 1.7 M of 60 328, saving attention 40.2 / 33.7, SDDMM x 64 24.6 / 22.4).  Without
+// one they do not ask (uniform, 400 000 of 6667 29.0 / 24.2; of what is in the order of its degrees only 1.7 M log-normal 50.9 / 57.2 and 5.5 M power law x 16
+// through the map 130 / 152 are slower).
+// MIDS: the graph may have them (has_mids), as a template because the smallest plan-free calls are a chain of latencies (9000 non-zeros, never / asked
+// in the kernels / as a template 15.0 / 15.9 / 15.0).
 constexpr int kMidLen = 64, kMidShift = 16;
-constexpr int64_t kMidLeastNnz = int64_t(1) << 18;
+constexpr int64_t kMidLeastNnz = int64_t(1) << 18, kMidLeastRows = 7000;
+inline bool has_mids(const TaskSource& q) { return q.nnz >= kMidLeastNnz && q.group_max < kMidLen; }
+template <bool MIDS>
 __device__ __forceinline__ bool mid_row(const TaskSource& q, const RowCut& c) {
-  return c.m == 1 && c.part > q.group_max && c.part <= kMidLen && !c.far && q.nnz >= kMidLeastNnz;
+  return MIDS && c.m == 1 && c.part > q.group_max && c.part <= kMidLen && !c.far;
 }
-// above 0: a window of so many rows, and pieces of lane groups and of waves beside them, takes less than half the waves with the rows in lane
+// above 0: so many rows, and pieces of lane groups and of waves beside them, take less than half the waves with the rows in lane
 // groups, eight to a wave.  A sum over rows, of fewer than 2^27 (group_max is 32 up to 8 M non-zeros only).
 __device__ __forceinline__ int mid_gain(int mid, int group, int whole) { return 6 * mid - group - 8 * whole; }
 
-// the counters of a window from what its rows have added to them (the same rows whether long ones are cut at column ranges or not)
-template <bool RANGES>
-__device__ __forceinline__ int task_counter(const int* total, int i) {
+// About how many of a graph's rows are such: of one for every thread of the workgroup, at equal distances, in two steps (they are asked for ahead of the
+// window's own).
+template <bool MIDS>
+struct MidSample {
+  bool mid = false;
+  __device__ __forceinline__ MidSample(const TaskSource& q) {
+    const int64_t r = int64_t(q.nrows) * (2 * int(threadIdx.x) + 1) / (2 * kTaskThreads);
+    if (MIDS && r < q.nrows) mid = mid_row<MIDS>(q, cut_row<true>(q, q.rowptr, int(r)));
+  }
+  __device__ __forceinline__ void add(int* sum) const {  // to a word of LDS
+    if (!MIDS) return;
+    const int n = __popcll(__ballot(mid));
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(sum, n);
+  }
+  static __device__ __forceinline__ bool many(const TaskSource& q, int sum) { return int64_t(sum) * q.nrows >= kMidLeastRows * kTaskThreads; }
+};
+
+// the counters of a window from what its rows have added to them (the same rows whether long ones are cut at column ranges or not); may: whether its
+// middle rows may go to lane groups
+template <bool RANGES, bool MIDS>
+__device__ __forceinline__ int task_counter(const int* total, int i, bool may = true) {
+  if (!MIDS) return total[i];
   const int mid = total[kTaskZ] >> kMidShift;
   if (i == kTaskZ) return total[kTaskZ] & ((1 << kMidShift) - 1);
   if (i != kTaskW && i != kTaskG) return total[i];
   const int group = total[kTaskG] + (RANGES ? total[kTaskLongG] : 0), whole = total[kTaskW] + (RANGES ? total[kTaskLongW] : 0);
-  return total[i] + ((mid_gain(mid, group, whole) > 0) == (i == kTaskG) ? mid : 0);
+  return total[i] + ((may && mid_gain(mid, group, whole) > 0) == (i == kTaskG) ? mid : 0);
 }
 
 // what row r adds to the counters
-template <bool RANGES, int N>
+template <bool RANGES, bool MIDS, int N>
 __device__ __forceinline__ void task_count_row(const TaskSource& q, const int* rp, int r, int (&n)[N]) {
   static_assert(N == (RANGES ? kTaskAll : kTaskCounters), "counters");
   const RowCut c = cut_row<RANGES>(q, rp, r);
   const bool whole = c.part > q.group_max;
   if (c.m == 0) {
     ++n[kTaskZ];
-  } else if (mid_row(q, c)) {
+  } else if (mid_row<MIDS>(q, c)) {
     n[kTaskZ] += 1 << kMidShift;
   } else if (RANGES && c.far) {
     n[whole ? int(kTaskLongW) : int(kTaskLongG)] += c.m;
@@ -142,7 +170,7 @@ __device__ __forceinline__ void task_scan(const TaskSource& q, int nwin, int* __
 // up the counts of the windows before it, unless a launch has scanned them (then sums are their totals); the first leaves section and totals.  Pieces of rows from
 // q.range_min on follow those of the others.  With both they are left out if no more than range_cap pieces take their place, whose number
 // of every window follows the counters.
-template <bool SELF, bool RANGES>
+template <bool SELF, bool RANGES, bool MIDS>
 __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin, const int* __restrict__ counts, const int* __restrict__ sums,
                                            hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals, int4* __restrict__ task,
                                            int* __restrict__ zrow, int4* __restrict__ split, int range_cap) {
@@ -206,19 +234,30 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
     s = sec[b];
   }
   RowCut cut[kTaskRowsPerThread];
-  int gain = 0;
-  for (int u = 0; u < kTaskRowsPerThread; ++u) {
-    const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
-    cut[u] = RowCut{0, 0, kNone, false};
-    if (r < q.nrows) cut[u] = cut_row<RANGES>(q, rp, int(r));
-    if (cut[u].m > 0) gain += mid_row(q, cut[u]) ? mid_gain(1, 0, 0) : (cut[u].part <= q.group_max ? mid_gain(0, cut[u].m, 0) : mid_gain(0, 0, cut[u].m));
-    if (RANGES && drop && cut[u].far) cut[u].m = kNone;
-  }
-  __shared__ int s_gain[kTaskThreads / kWave];
-  const bool mids = q.nnz >= kMidLeastNnz && q.group_max < kMidLen;
-  if (mids) {
-    gain = wave_sum(gain);
-    if ((threadIdx.x & (kWave - 1)) == 0) s_gain[threadIdx.x / kWave] = gain;
+  auto read_rows = [&] {
+    for (int u = 0; u < kTaskRowsPerThread; ++u) {
+      const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
+      cut[u] = RowCut{0, 0, kNone, false};
+      if (r < q.nrows) cut[u] = cut_row<RANGES>(q, rp, int(r));
+    }
+  };
+  // Middle rows are in lane groups where the window's count of waves says so; the rows are then read ahead of the barrier that the counters want
+  // anyway.
+  __shared__ int s_waves[kTaskThreads / kWave], s_counted;
+  if (MIDS) {
+    read_rows();
+    int waves = 0;  // without middle rows and those from range_min on
+    for (int u = 0; u < kTaskRowsPerThread; ++u) {
+      const RowCut& c = cut[u];
+      if (c.m > 0 && c.part > q.group_max && !c.far && !mid_row<MIDS>(q, c)) waves += c.m;
+    }
+    waves = wave_sum(waves);
+    if ((threadIdx.x & (kWave - 1)) == 0) s_waves[threadIdx.x / kWave] = waves;
+    if (threadIdx.x == 0) {
+      const int* const c = counts + (int64_t(kTaskW) * q.nb + b) * nwin + w;
+      if (SELF && !sums) s_counted = *c;
+      else s_counted = (w + 1 < nwin ? c[1] : sums[kTaskW * q.nb + b]) - *c;
+    }
   }
   for (int i = threadIdx.x; i < kLists * (kMaxGroupLen + 1); i += kTaskThreads) at[0][i] = 0;
   if (threadIdx.x < (RANGES && q.range_min != kNoRanges ? int(kTaskAll) : int(kTaskCounters))) {
@@ -230,12 +269,17 @@ __device__ __forceinline__ void task_write(TaskSource q, int w, int b, int nwin,
   }
   __syncthreads();
   bool grouped = false;
-  if (mids) {
-    gain = 0;
-    for (int i = 0; i < kTaskThreads / kWave; ++i) gain += s_gain[i];
-    grouped = gain > 0;
+  if (MIDS) {
+    int waves = 0;
+    for (int i = 0; i < kTaskThreads / kWave; ++i) waves += s_waves[i];
+    grouped = s_counted == waves;
+  } else {
+    read_rows();
   }
-  auto is_whole = [&](const RowCut& c) { return c.part > q.group_max && !(grouped && mid_row(q, c)); };
+  if (RANGES && drop)
+    for (int u = 0; u < kTaskRowsPerThread; ++u)
+      if (cut[u].far) cut[u].m = kNone;
+  auto is_whole = [&](const RowCut& c) { return c.part > q.group_max && !(MIDS && grouped && mid_row<MIDS>(q, c)); };
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     if (cut[u].m > 0 && !is_whole(cut[u])) {
       int* const a = at[RANGES && cut[u].far ? 1 : 0];

@@ -8,12 +8,14 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ranges.h"
 
 namespace hgnn {
 
 // counts[q][b][window]
+template <bool MIDS>
 __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, int nwin, int* __restrict__ counts) {
   __shared__ int total[kTaskCounters];
   const int b = blockIdx.y;
@@ -24,7 +26,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, 
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(blockIdx.x) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     if (r >= q.nrows) break;
-    task_count_row<false>(q, rp, int(r), n);
+    task_count_row<false, MIDS>(q, rp, int(r), n);
   }
   for (int i = 0; i < kTaskCounters; ++i) {
     int v = n[i];
@@ -32,7 +34,7 @@ __global__ __launch_bounds__(kTaskThreads) void task_count_kernel(TaskSource q, 
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = task_counter<false>(total, threadIdx.x);
+  if (threadIdx.x < kTaskCounters) counts[(int64_t(threadIdx.x) * q.nb + b) * nwin + blockIdx.x] = task_counter<false, MIDS>(total, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kTaskThreads) void task_scan_kernel(TaskSource q, int nwin, int* __restrict__ counts, int* __restrict__ sums,
@@ -68,12 +70,19 @@ __global__ __launch_bounds__(kFreeScanThreads) void free_scan_kernel(int nwin, i
   }
 }
 
-template <bool SELF>
+template <bool SELF, bool MIDS>
 __global__ __launch_bounds__(kTaskThreads) void task_write_kernel(TaskSource q, int nwin, const int* __restrict__ counts,
                                                                    const int* __restrict__ sums, hgnn_task_sec* __restrict__ sec,
                                                                    TaskTotals* __restrict__ totals, int4* __restrict__ task,
                                                                    int* __restrict__ zrow, int4* __restrict__ split) {
-  task_write<SELF, false>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split, 0);
+  task_write<SELF, false, MIDS>(q, blockIdx.x, blockIdx.y, nwin, counts, sums, sec, totals, task, zrow, split, 0);
+}
+
+// f(MIDS) for a launch
+template <class F>
+static void with_mids(const TaskSource& q, F&& f) {
+  if (has_mids(q)) f(std::integral_constant<bool, true>());
+  else f(std::integral_constant<bool, false>());
 }
 
 // room for the counts of q, which the caller's kernels or task_count form
@@ -94,7 +103,7 @@ hgnn_status task_prepare(const TaskSource& q, TaskCounts& c) {
 static hgnn_status task_count(const TaskSource& q, TaskCounts& c, SetupStream& s) {  // without ranges
   const hgnn_status st = task_prepare(q, c);
   if (st != HGNN_OK) return st;
-  if (c.nwin > 0) task_count_kernel<<<dim3(unsigned(c.nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, c.nwin, c.count);
+  if (c.nwin > 0) task_count_kernel<false><<<dim3(unsigned(c.nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, c.nwin, c.count);  // (of blocks)
   task_scan_kernel<<<1, kTaskThreads, 0, s>>>(q, c.nwin, c.count, c.sums, c.sec, c.totals);
   HGNN_LAUNCH_CHECK("task_count_kernel / task_scan_kernel");
   return HGNN_OK;
@@ -157,7 +166,7 @@ hgnn_status build_block_tasks(hgnn_plan* p, SetupStream& s) {
   hgnn_row_tasks* t = p->btasks;
   HGNN_HIP(hipMemcpyAsync(t->host.data(), t->sec, sizeof(hgnn_task_sec) * size_t(q.nb), hipMemcpyDeviceToHost, s));
   if (c.nwin > 0)
-    task_write_kernel<false><<<dim3(unsigned(c.nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, c.nwin, c.count, c.sums, t->sec, nullptr,
+    task_write_kernel<false, false><<<dim3(unsigned(c.nwin), unsigned(q.nb)), kTaskThreads, 0, s>>>(q, c.nwin, c.count, c.sums, t->sec, nullptr,
                                                                                             t->task, t->zrow, t->split);
   HGNN_LAUNCH_CHECK("task_write_kernel");
   HGNN_HIP(s.wait());
@@ -207,6 +216,7 @@ TaskScratch task_scratch_at(void* base, int64_t nrows, int64_t nnz, int S, int F
 
 // Without a plan and with column ranges: two launches, in each of which the workgroups for the long rows come first.  The second adds up the
 // pieces at column ranges and leaves the long rows in ordinary pieces where they are more than there is room for.
+template <bool MIDS>
 __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, int nwin, int* __restrict__ counts, RangeLists ranges) {
   if (int(blockIdx.x) < nwin) {
     range_cut<kTaskThreads>(ranges, int(blockIdx.x));
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
   for (int u = 0; u < kTaskRowsPerThread; ++u) {
     const int64_t r = int64_t(w) * kTaskWindow + u * kTaskThreads + threadIdx.x;
     if (r >= q.nrows) break;
-    task_count_row<true>(q, q.rowptr, int(r), n);
+    task_count_row<true, MIDS>(q, q.rowptr, int(r), n);
   }
 #pragma unroll
   for (int i = 0; i < kTaskAll; ++i) {
@@ -228,9 +238,10 @@ __global__ __launch_bounds__(kTaskThreads) void free_count_kernel(TaskSource q, 
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&total[i], v);
   }
   __syncthreads();
-  if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = task_counter<true>(total, threadIdx.x);
+  if (threadIdx.x < kTaskAll) counts[int64_t(threadIdx.x) * nwin + w] = task_counter<true, MIDS>(total, threadIdx.x);
 }
 
+template <bool MIDS>
 __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, int nwin, int range_cap, const int* __restrict__ counts,
                                                                   const int* __restrict__ sums,
                                                                   hgnn_task_sec* __restrict__ sec, TaskTotals* __restrict__ totals,
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(kTaskThreads) void free_write_kernel(TaskSource q, 
                                                                   RangeLists ranges, int range_blocks, int4* __restrict__ rtask) {
   const int b = int(blockIdx.x) - range_blocks;
   if (b >= 0) {
-    task_write<true, true>(q, b, 0, nwin, counts, sums, sec, totals, task, zrow, split, range_cap);
+    task_write<true, true, MIDS>(q, b, 0, nwin, counts, sums, sec, totals, task, zrow, split, range_cap);
     return;
   }
   const int w = int(blockIdx.x) * kRangeGroup;
@@ -260,19 +271,25 @@ hgnn_status task_build_in(const TaskSource& q, const TaskScratch& t, const int32
   const int nwin = int(ceil_div(q.nrows, kTaskWindow));
   int* const sums = nwin > kFreeScanWindows ? t.sums : nullptr;
   if (q.range_min == kNoRanges) {
-    task_count_kernel<<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
-    if (sums) free_scan_kernel<<<kTaskCounters, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskCounters, nullptr, sums);
-    task_write_kernel<true><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, sums, t.sec, t.totals, t.task, t.zrow, t.split);
+    with_mids(q, [&](auto mids) {
+      constexpr bool M = decltype(mids)::value;
+      task_count_kernel<M><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts);
+      if (sums) free_scan_kernel<<<kTaskCounters, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskCounters, nullptr, sums);
+      task_write_kernel<true, M><<<dim3(unsigned(nwin), 1u), kTaskThreads, 0, s>>>(q, nwin, t.counts, sums, t.sec, t.totals, t.task, t.zrow, t.split);
+    });
     HGNN_LAUNCH_CHECK("task_count_kernel / task_write_kernel");
     return HGNN_OK;
   }
   const int range_blocks = int(ceil_div(nwin, kRangeGroup));
   const RangeLists ranges = range_lists(q, col, ncols, nwin, t.cuts, t.range_lists, t.counts + int(kTaskAll) * int64_t(nwin),
                                         t.range_lists + kRanges * int64_t(nwin));
-  free_count_kernel<<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
-  if (sums) free_scan_kernel<<<kTaskAll + kRanges + 2, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskAll + 1, t.range_lists, sums);
-  free_write_kernel<<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, int(t.cap), t.counts, sums, t.sec, t.totals, t.task, t.zrow,
-                                                                               t.split, ranges, range_blocks, t.rtask);
+  with_mids(q, [&](auto mids) {
+    constexpr bool M = decltype(mids)::value;
+    free_count_kernel<M><<<dim3(unsigned(2 * nwin)), kTaskThreads, 0, s>>>(q, nwin, t.counts, ranges);
+    if (sums) free_scan_kernel<<<kTaskAll + kRanges + 2, kFreeScanThreads, 0, s>>>(nwin, t.counts, kTaskAll + 1, t.range_lists, sums);
+    free_write_kernel<M><<<dim3(unsigned(range_blocks + nwin)), kTaskThreads, 0, s>>>(q, nwin, int(t.cap), t.counts, sums, t.sec, t.totals, t.task, t.zrow,
+                                                                                     t.split, ranges, range_blocks, t.rtask);
+  });
   HGNN_LAUNCH_CHECK("free_count_kernel / free_write_kernel");
   return HGNN_OK;
 }

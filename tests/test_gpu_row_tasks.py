@@ -51,19 +51,20 @@ def test_piece_borders(hgnn, dev, F, H, S, nb, what):
     hgnn.hgnn_plan_destroy(p)
 
 
-@pytest.mark.parametrize("S,less", [(256, 0), (256, 1), (64, 0), (50, 0), (24, 0)])
-def test_windows_of_middle_rows(hgnn, dev, S, less):
+@pytest.mark.parametrize("S,less,times", [(256, 0, 1), (256, 1, 1), (64, 0, 1), (50, 0, 1), (24, 0, 1), (256, 0, 2), (64, 0, 2), (50, 0, 3), (24, 0, 3)])
+def test_windows_of_middle_rows(hgnn, dev, S, less, times):
     """Windows of 1024 rows whose rows of 33 to 64 non-zeros are left to lane groups or take a wave each: all of them, none, at the border of the
-    rule, beside longer and empty ones, in pieces of several to a row; graphs of 2^18 non-zeros and one fewer."""
-    print(f"middle rows S={S} less={less}", flush=True)
+    rule, beside longer and empty ones, in pieces of several to a row; graphs of 2^18 non-zeros and one fewer; with a plan only graphs of 7000 such
+    rows or more (4200 in one set of the windows)."""
+    print(f"middle rows S={S} less={less} times={times}", flush=True)
     r = np.random.default_rng(S)
     window = lambda *kinds: r.permutation(np.concatenate([np.broadcast_to(v, n) for n, v in kinds]))
     wins = [window((1024, 47)), window((1024, r.integers(33, 65, 1024))), window((500, 64), (62, 65), (12, 1), (450, 0)),
             window((500, 33), (374, 3), (1, 300), (149, 40)), window((512, 32), (512, 64)), window((86, 50), (516, 9), (422, 0)),
             window((86, 50), (515, 9), (423, 0)), window((350, 64), (674, 0)), window((300, 8))]
-    deg = np.concatenate(wins)
+    deg = np.concatenate(wins * times)
     deg[-1] = 0
-    deg[-1] = (1 << 18) - less - deg.sum()  # one long row
+    deg[-1] = (1 << 18) - less - deg.sum() if times == 1 else 1000  # one long row
     assert 300 < deg[-1] < 60000
     V, F = deg.size, 16
     rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
@@ -85,6 +86,44 @@ def test_windows_of_middle_rows(hgnn, dev, S, less):
     mag = np.einsum("ef,ef->e", np.abs(X[row].astype(np.float64)), np.abs(X[col].astype(np.float64)))[:, None]
     compare("dot", down(dot), oracle.sddmm_dot(rowptr, col, X, X, H=1), mag)
     hgnn.hgnn_plan_destroy(p)
+
+
+def test_middle_rows_in_order_of_lengths(hgnn, dev):
+    """A power law in the order of its degrees has windows of nothing but rows of 33 to 64 non-zeros, beside many others.  They stay with the waves
+    they have when the rows are in any order (in lane groups, 1.06 times the time of any order; with waves 0.99)."""
+    r = np.random.default_rng(1)
+    deg = np.minimum(4000, 60000 * (np.arange(30000) + 20.0) ** -0.85).astype(np.int64) + 1
+    F, both = 16, []
+    for order in (deg, r.permutation(deg)):
+        V, E = order.size, int(order.sum())
+        row = torch.repeat_interleave(torch.arange(V, device=dev), up(order, dev))
+        col = torch.sort(row * V + torch.randint(0, V, (E,), device=dev))[0] % V
+        g = hgnn.Csr(up(np.concatenate([[0], np.cumsum(order)]).astype(np.int32), dev), col.int())
+        p = hgnn.hgnn_plan_create(g, 256, F, 1, col_blocks=1)
+        X = torch.randn((V, F), device=dev).half()
+        Y, e = torch.empty_like(X), torch.empty((E, 1), dtype=torch.float16, device=dev)
+
+        def call(g=g, p=p, X=X, Y=Y, e=e):
+            hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_DOT, 1, F, X, X, e)
+            hgnn.hgnn_spmm_discretized(p, g, None, 1, X, Y)
+
+        both.append(call)
+
+    def median_us(call):
+        us = []
+        for _ in range(11):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                call()
+            b.record()
+            b.synchronize()
+            us.append(100 * a.elapsed_time(b))
+        return sorted(us)[5]
+
+    tries = [median_us(both[0]) / median_us(both[1]) for _ in range(4)]
+    print("in order / in any order: " + ", ".join(f"{t:.3f}" for t in tries), flush=True)
+    assert min(tries) < 1.03
 
 
 @pytest.mark.parametrize("F,H,what", [(64, 1, "plain"), (64, 1, "w"), (64, 2, "map"), (64, 4, "w"), (64, 4, "map"), (64, 8, "w"), (128, 1, "norm"), (128, 8, "w"),
