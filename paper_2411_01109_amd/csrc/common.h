@@ -398,7 +398,7 @@ struct TaskSource {
   int32_t range_min;      // rows of at least so many non-zeros are cut by ranges.h, too (one block), or kNoRanges
 };
 constexpr int kNoRanges = 0x7fffffff;
-// Longest piece that is left to one lane group.  Small graphs have few waves and want short chains of loads, large ones few
+// Longest piece that is left to one lane group (but for the middle rows of task_build.h).  Small graphs have few waves and want short chains of loads, large ones few
 // reductions across lane groups (2.1 M non-zeros x 128: 32 is 3 % better than 64; 62 M x 128: 128 is 1 % better); the pieces of
 // column blocks come in numbers and are bound by the L2s (114 M non-zeros: 256 is 3 % better than 128).
 constexpr int kGroupMaxBlocks = 256;

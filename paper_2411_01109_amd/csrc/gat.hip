@@ -528,7 +528,7 @@ static hgnn_status run_gat_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, Ga
   a.stage_c = t->stage_mz + size_t(2) * size_t(t->stage_slots) * size_t(p->max_H);
   const int L = pow2_at_least(a.F / 8), G = kWave / L, lh = a.D / 8;
   TaskView v = task_view(t, G, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, p->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
-  v.longer = long_rounds(t->nb, t->nnz, G, 4);
+  v.longer = long_rounds(t->nb, p->nrows, t->nnz, p->S, G, 4);
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     const bool near = near_table(ncols, a.ldx);

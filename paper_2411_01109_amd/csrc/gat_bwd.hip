@@ -421,7 +421,7 @@ static hgnn_status run_bwd_tasks(const hgnn_plan* q, const hgnn_row_tasks* t, Ga
   a.stage_ld = q->max_F;
   const int L = pow2_at_least(a.F / 8), lh = a.D / 8;
   TaskView v = task_view(t, kWave / L, at_ranges(t, kRangesAttention, int64_t(ncols) * a.F * 2, q->l2_bytes), comes_back(false, int64_t(ncols) * a.ldx * 2, q->llc_bytes));
-  v.longer = long_rounds(t->nb, t->nnz, kWave / L, 8);
+  v.longer = long_rounds(t->nb, q->nrows, t->nnz, q->S, kWave / L, 8);
   const int waves = v.first_wave[t->nb];
   if (waves > 0) {
     if (near_table(ncols, a.ldx)) launch_bwd_tasks<true, VEC>(L, lh, unsigned(waves), s, a, v, ncols);

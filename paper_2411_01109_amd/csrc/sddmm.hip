@@ -530,7 +530,7 @@ extern "C" hgnn_status hgnn_sddmm(const hgnn_csr* g, const hgnn_plan* p, hgnn_sd
     }
     const int lanes = pow2_at_least((F + vw - 1) / vw);
     TaskView v = task_view(t, kWave / lanes, at_ranges(t, kRangesDot, int64_t(g->ncols) * F * 2, p->l2_bytes), comes_back(false, int64_t(g->ncols) * ldv * 2, p->llc_bytes), false);
-    v.longer = long_rounds(t->nb, t->nnz, kWave / lanes, 4 + 2 * H);
+    v.longer = long_rounds(t->nb, p->nrows, t->nnz, p->S, kWave / lanes, 4 + 2 * H);
     const int waves = v.first_wave[t->nb];
     if (waves > 0) {
       const bool near = near_table(g->ncols, ldv);

@@ -1503,7 +1503,7 @@ static hgnn_status run_tasks(const hgnn_plan* p, const hgnn_row_tasks* t, SpmmAr
   // (the comparison variant with atomic additions rounds each to fp16: as many as there are segments)
   const bool ranges = !a.atomic_y && at_ranges(t, mapped ? kRangesMapped : kRangesSpmm, int64_t(ncols) * a.F * 2, p->l2_bytes);
   TaskView v = task_view(t, G, ranges, comes_back(mapped, int64_t(ncols) * a.ldx * 2, p->llc_bytes));
-  v.longer = long_rounds(t->nb, t->nnz, G, task_entry_bytes(wm, a));
+  v.longer = long_rounds(t->nb, p->nrows, t->nnz, p->S, G, task_entry_bytes(wm, a));
   const int waves = v.first_wave[t->nb];
   if (a.atomic_y && v.n_split > 0) {
     launch_zero_split(L, s, a, v);
@@ -1567,7 +1567,7 @@ static hgnn_status spmm_free_tasks(const hgnn_csr* g, SpmmArgs a, void* scratch,
   const bool mapped = a.w && a.eid;
   int64_t grid = 0;
   TaskView v = task_view(t, q, g->nnz, kWave / L, &grid);
-  v.longer = long_rounds(1, g->nnz, kWave / L, task_entry_bytes(a.w ? 1 : 0, a));
+  v.longer = long_rounds(1, g->nrows, g->nnz, kFreePiece, kWave / L, task_entry_bytes(a.w ? 1 : 0, a));
   a.staging = reinterpret_cast<half_t*>(t.staging);
   a.stage_ld = (a.F + 7) & ~7;
   a.stage32 = 1;

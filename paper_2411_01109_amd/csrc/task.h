@@ -2,6 +2,7 @@
 // group eight at a time and gathers table rows.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -68,11 +69,17 @@ struct Round {
   static constexpr int E = R / LC;
   static constexpr int PITCH = R + 4;               // ints per group in the handle table
 };
-// host: whether a call takes rounds of 64 whose non-zeros take entry_bytes of LDS each.  Not where all pieces of lane groups have 32 non-zeros at
-// most (5.5 M non-zeros x 4 heads: SpMM 57 / 62 us, SDDMM 59 / 71; 1.3 M x 42 27.1 / 27.9; pieces at column ranges, which may be longer, are too few
-// there), nor where a wave would take more than 6.5 KB, which keeps waves out.
-inline bool long_rounds(int nb, int64_t nnz, int G, int entry_bytes) {
-  return (nb > 1 || task_group_max(nnz) > 32) && G <= kWave / 8 && G * 64 * entry_bytes <= 6656;
+// host: whether a call takes rounds of 64 whose non-zeros take entry_bytes of LDS each; S: most non-zeros of a piece.  Not where pieces of lane groups
+// have about 32 non-zeros at most (5.5 M non-zeros x 4 heads: SpMM 57 / 62 us, SDDMM 59 / 71; 1.3 M x 42 27.1 / 27.9; the middle rows of task_build.h
+// and pieces at column ranges, which may be longer, run in two rounds), nor where a wave would take more than 6.5 KB, which keeps waves out, nor where
+// most rows take whole waves, no more than a round of 32 for each lane group (uniform, 12 M x 64, rounds of 64 / 32: 300 a row, SpMM 84.9 / 81.4, four
+// heads of values 103.0 / 98.5, attention forward 125.5 / 122.9; 500 a row 67.9 / 66.7, 84.3 / 78.9, 98.4 / 96.6; without a plan, 150 a row, through the
+// map 4 % more with 64, but 300, whose pieces are longer there, 14 % less).
+inline bool long_rounds(int nb, int64_t nrows, int64_t nnz, int S, int G, int entry_bytes) {
+  if (G > kWave / 8 || G * 64 * entry_bytes > 6656) return false;
+  if (nb > 1) return true;
+  const int64_t most = task_group_max(nnz);
+  return most > 32 && (nnz <= most * nrows || std::min(nnz, S * nrows) > 32 * G * nrows);
 }
 
 // pieces at column ranges per XCD, whole waves of G lane groups of them

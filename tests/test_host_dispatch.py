@@ -172,7 +172,19 @@ def shared_columns(h):
                 assert ("linear_split" in names[0]) == (n <= most), (n, K, F, trans, names)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns]
+def rounds(h):
+    """Rounds of 64 non-zeros where lane groups have longer pieces: not in small graphs, nor where most rows are pieces of whole waves, an eighth of
+    which to a lane group is no longer than a round of 32 (of 16 lanes, a quarter)."""
+    w = vp(h.data)
+    for f, nnz, mean, most in ((64, 4000000, 20, 32), (64, 12000000, 40, 64), (64, 12000000, 128, 64), (64, 12000000, 130, 32), (64, 12000000, 200, 32),
+                               (64, 12000000, 256, 32), (64, 12000000, 258, 64), (64, 12000000, 500, 64), (128, 12000000, 200, 64)):
+        g = graph(h, nnz // mean, nnz // mean, nnz, True)
+        st, names = spmm(h, g, f, h.lib.hgnn_spmm_workspace(nnz // mean, 0, i64(nnz), f), w)
+        kernel = [n for n in names if n.startswith("spmm_task_kernel")]
+        assert st == 0 and len(kernel) == 1 and f"Li{most}EEE" in kernel[0], (f, nnz, mean, names)
+
+
+SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns, rounds]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
