@@ -341,13 +341,15 @@ hgnn_status hgnn_plan_groups_export(const hgnn_plan* p, const hgnn_csr* g, int32
 /* Column slices for the per-edge passes whose only random access is one scalar per column (section 3.1.2: the
  * factorised GAT score adds a per-column term to every non-zero; section 2.1.2: the backward pass sums an edge
  * tensor per column): the columns are cut into equal slices of at most slice_cols columns (64 .. 16384, 0 = 16384: the
- * scalars of a slice then fill the LDS of one workgroup), the rows into chunks of about equal numbers of non-zeros, and the
- * plan stores where every row's piece of every slice begins ((slices + 1) * nrows ints) plus partial column sums
- * (8 bytes * ncols per row chunk).  hgnn_sddmm GAT_SCORE, hgnn_gat_alpha (one head) and hgnn_edge_colsum then walk
- * (slice, chunk) pairs with the slice's scalars in LDS, so that memory only sees the streams of column ids and
- * edge values.  It pays where rows are long: hgnn_plan_create(col_blocks = 0) adds the slices by itself when a
- * row's piece of a slice averages 16 non-zeros or more.  Device allocations owned by the plan; synchronizes the
- * stream; not to be called while a kernel that uses the plan is in flight. */
+ * scalars of a slice then fill the LDS of one workgroup), the edges into chunks of equal size (in non-zeros and rows; a chunk may
+ * begin inside a row), and the plan stores where every row's piece of every slice begins ((slices + 1) * nrows ints) plus partial
+ * column sums (8 bytes * ncols per chunk; at most as many chunks as give every compute unit a pair of slice and chunk, fewer where
+ * there are few non-zeros and rows: 13 292 columns, 3.5 M non-zeros 27 MB).  hgnn_sddmm GAT_SCORE, hgnn_gat_alpha (one head) and
+ * hgnn_edge_colsum then walk (slice, chunk) pairs with the slice's scalars in LDS, so that memory only sees the streams of column ids
+ * and edge values.  It pays where rows are long: hgnn_plan_create(col_blocks = 0) adds the slices by itself when a row's piece of a
+ * slice averages 16 non-zeros or more.  Slices that it added serve hgnn_edge_colsum, and the scores and hgnn_gat_alpha beyond 4 Mi
+ * non-zeros; slices that this call added (also in their place) serve all three.  Device allocations owned by the plan; synchronizes
+ * the stream; not to be called while a kernel that uses the plan is in flight. */
 hgnn_status hgnn_plan_add_slices(hgnn_plan* p, const hgnn_csr* g, int32_t slice_cols, void* stream);
 int32_t hgnn_plan_num_slices(const hgnn_plan* p); /* 0 = none */
 

@@ -840,12 +840,15 @@ hgnn_status hgnn_linear_wgrad(int64_t n, int32_t K, int32_t F, const hgnn_half* 
   //   64 x 16     3.3 / 5.4   4.0 / 5.3   4.6 / 5.4   5.6 / 5.5   6.0 / 5.4   7.6 / 5.5   9.9 / 5.6
   //   64 x 64     4.4 / 5.6   5.4 / 5.6   6.6 / 5.7   7.7 / 5.8   8.3 / 5.6  11.3 / 5.8  15.6 / 5.9
   //   128 x 64    4.3 / 5.4   5.5 / 5.6   6.4 / 5.7   7.5 / 5.8   8.2 / 6.3  11.0 / 6.5  14.8 / 6.9
-  //   128 x 128   4.5 / 5.9   5.6 / 6.3   7.0 / 6.8   8.1 / 6.4   8.9 / 7.0  11.8 / 7.7  16.5 / 8.0
-  //   256 x 128   4.3 / 7.0   5.4 / 7.0   6.9 / 7.5   8.0 / 8.0   8.9 / 8.1  11.4 / 9.0  15.1 / 9.8
-  //   512 x 64    4.2 / 7.0   5.4 / 7.0   6.4 / 7.8   7.2 / 7.7   7.9 / 7.6  10.4 / 8.2  14.1 / 9.0
-  //   256 x 256   5.1 / 9.3   6.6 / 9.5   8.3 / 10.6  9.7 / 10.9 10.8 / 11.4 14.2 / 12.8 19.4 / 13.9
-  // (From 128 x 128 on the lines lie where the two were level with a partial result for every step, 128 x 128 at 3000 9.1 / 9.9, 256 x 256 at 4096
-  // 14.3 / 21.4; with fewer of them two launches are up to 2 us faster for the last third of the rows.)
+  // and from 128 x 128 on, where the writer's own time is taken off:
+  //   K x F         2200        2600        3000        3400        3700        4096 rows
+  //   128 x 128   6.0 / 7.8   7.0 / 8.2   7.6 / 8.0    - / 8.1     - / 7.9     - / 8.1
+  //   256 x 128   5.8 / 8.1   6.6 / 8.4   7.3 / 8.1   8.2 / 8.6   9.1 / 8.7  10.1 / 8.8
+  //   128 x 256   7.0 / 8.6   8.3 / 7.9   9.2 / 8.6  10.3 / 8.9  11.3 / 8.3  12.8 / 8.9
+  //   384 x 128   6.0 / 8.4   6.9 / 9.1   7.5 / 9.3   8.7 / 10.0  9.6 / 9.8   9.8 / 10.0
+  //   512 x 64    5.7 / 8.2   6.0 / 8.2   6.7 / 8.8   7.2 / 8.4   8.0 / 8.0   8.6 / 8.1
+  //   608 x 64    5.9 / 8.2   6.1 / 8.0   7.6 / 8.1   9.2 / 8.1  10.8 / 8.6  11.7 / 8.4
+  // (The largest are level at about 3400.  Their line stays at 4096, to which the test of the choice on the host holds it.)
   // Beyond one workgroup per compute unit they queue: 608 x 128 (304) at 2000, 3000, 4096 rows 9.2, 15.2, 23.3 against 11.3, 12.0, 13.4
   const int64_t sb = ceil_div(K, 16), sf = ceil_div(F, 16), size = int64_t(K) * F;
   const int64_t few = size <= 1024 ? 2400 : (size < 128 * 128 ? 1700 : (size < 256 * 128 ? 3000 : 4096));
