@@ -27,74 +27,140 @@ struct LinearArgs {
   int K, F;
   const half_t* X;
   int64_t ldx;
-  const half_t* W;
+  const half_t* W;  // [K][F], transposed (TRANS) [F][K]
   int64_t ldw;
-  int trans;  // 0: W is [K][F]; 1: W is [F][K]
   half_t* Y;
   int64_t ldy;
   int KC;     // columns of X (rows of W) held in LDS at a time; a multiple of 32, and of the 128 columns of a group when K > KC
   int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
-  int wvec;   // W may be read in 16-byte pieces
-  int KW;     // rows of W that exist (trans == 0): the others count as zero
+  int wvec;   // W may be read in 16-byte pieces, a workgroup's part at 32-bit offsets
+  int step_f, step_k;  // transposed: the waves of a workgroup / and % pieces of 64 columns
+  int KW;     // rows of W that exist (not transposed): the others count as zero
 };
 
 // The weight tile W[kc .. kc+KC)[fc0 .. fc0+FC) into LDS in the order in which the products read it: fragment
 // (tile t of 16 features, step ks of 32 columns) is 64 lanes x 16 bytes, so every read of it is one conflict-free
 // kilobyte.  The features of a pair of tiles are dealt out so that a lane's 2 x 4 result values are 8 consecutive
 // features: tile 2b+o, row i of the tile <-> feature 32b + 8(i/4) + 4o + i%4.
-// W [F][K]: a thread moves one 16-byte piece of a row.  W [K][F]: a thread reads an 8 x 8 block and writes it transposed.
-__device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __restrict__ Wf, int kc, int fc0) {
-  const int KS = a.KC / 32;
-  const int kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0);
-  const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (a.trans) {
-    const int total = (a.FC / 16) * KS * kWave;
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int lane = idx & (kWave - 1), fr = idx >> 6;
-      const int t = fr / KS, ks = fr - t * KS;
-      const int i = lane & 15, q = lane >> 4;
-      const int f = 32 * (t >> 1) + 8 * (i >> 2) + 4 * (t & 1) + (i & 3), k = 32 * ks + 8 * q;
-      half8_t v = zero;
-      if (f < fn && k < kn) {
-        const half_t* src = a.W + int64_t(fc0 + f) * a.ldw + kc + k;
-        if (a.wvec) {
-          v = *reinterpret_cast<const half8_t*>(src);
-        } else {
+// W [F][K]: an item is 64 columns of eight features, a wave's 16-byte pieces of eight lines.  W [K][F]: an item is a block of eight features of
+// eight rows, a thread's, transposed by byte permutations.  A batch of items is fetched in one go and put into LDS later, so that the rows of
+// X can be asked for in between: behind them, by loads under conditions and with bank conflicts, the weight was up to a third of a call.
+// 100 003 rows of 64 -> 48 9.7 -> 6.8 us, 131 072 of 128 -> 64 13.5 -> 10.5, 262 144 of 64 -> 64 15.4 -> 12.4, 60 000 of 608 -> 128 28 -> 22 (without
+// any weight 5.8, 10.9, 13.2, 17.5).
+struct WeightBatch {
+  uint32_t v[32];
+  int f, k8;  // of its first item
+};
+__device__ __forceinline__ int linear_waves() { return __builtin_amdgcn_readfirstlane(int(blockDim.x) / kWave); }
+template <bool TRANS>
+__device__ __forceinline__ int linear_batch() { return TRANS ? linear_waves() * 8 : int(blockDim.x); }
+template <bool TRANS>
+__device__ __forceinline__ int linear_w_items(const LinearArgs& a) { return a.FC / 8 * (TRANS ? (a.KC + 63) / 64 : a.KC / 8); }
+
+// W^T: f(u, features / 8, columns / 64), all scalar, for the u-th item of the wave in a batch
+template <class Fn>
+__device__ __forceinline__ void linear_each_item(const LinearArgs& a, int first, Fn&& f) {
+  const int across = (a.KC + 63) / 64;
+  const int item = __builtin_amdgcn_readfirstlane(first + int(threadIdx.x) / kWave);
+  int g = __builtin_amdgcn_readfirstlane(int(unsigned(item) / unsigned(across))), c = item - g * across;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = src[j];
-        }
-      }
-      *reinterpret_cast<half8_t*>(Wf + int64_t(idx) * 8) = v;
-    }
+  for (int u = 0; u < 8; ++u) {
+    if (8 * g >= a.FC) break;
+    f(u, g, c);
+    g += a.step_f, c += a.step_k;
+    const int over = c >= across;
+    g += over, c -= over ? across : 0;
+  }
+}
+
+// where lane 16q + i of a read finds its 16 bytes in the kilobyte of a fragment: such that the writes of either form, 16 lanes of four features and
+// four q at a time, go to different banks, too
+__device__ __forceinline__ int linear_slot(int i, int q) { return 16 * q + (((i + 4 * q) & 15) ^ q); }
+
+// Whether 16-byte pieces can be read at 32-bit offsets; else linear_put_w reads all of the weight element by element with the first batch.
+template <bool TRANS>
+__device__ __forceinline__ bool linear_batched(const LinearArgs& a, int kc, int fc0) {
+  return a.wvec && (TRANS || (min(a.FC, a.F - fc0) % 8 == 0 && a.KW > kc));
+}
+
+// Positions outside the weight are read inside it, without branches between the loads; linear_put_w puts zeros in their place.
+template <bool TRANS>
+__device__ __forceinline__ void linear_fetch_w(const LinearArgs& a, WeightBatch& w, int first, int kc, int fc0) {
+  const int kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0), lane = threadIdx.x & (kWave - 1);
+  const char* const W = reinterpret_cast<const char*>(a.W + fc0 * (TRANS ? a.ldw : 1) + kc * (TRANS ? 1 : a.ldw));
+  const uint32_t pitch = uint32_t(a.ldw) * 2u;
+  if (!linear_batched<TRANS>(a, kc, fc0)) return;
+  if constexpr (TRANS) {
+    linear_each_item(a, first, [&](int u, int g, int c) {
+      const uint32_t at = uint32_t(min(8 * g + (lane >> 3), fn - 1)) * pitch + uint32_t(min(64 * c + 8 * (lane & 7), kn - 8)) * 2u;
+      __builtin_memcpy(w.v + 4 * u, __builtin_assume_aligned(W + at, 16), 16);
+    });
   } else {
-    const int F8 = a.FC / 8, total = F8 * (a.KC / 8);
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int k8 = idx / F8, f8 = idx - k8 * F8;
-      half8_t row[8];
+    const int F8 = a.FC / 8, idx = first + int(threadIdx.x);
+    w.k8 = int(unsigned(idx) / unsigned(F8)), w.f = 8 * (idx - w.k8 * F8);
+    if (__builtin_amdgcn_readfirstlane(w.k8) >= a.KC / 8) return;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        row[j] = zero;
-        if (8 * k8 < kn && kc + 8 * k8 + j < a.KW) {
-          const half_t* src = a.W + int64_t(kc + 8 * k8 + j) * a.ldw + fc0 + 8 * f8;
-          if (a.wvec && 8 * f8 + 8 <= fn) {
-            row[j] = *reinterpret_cast<const half8_t*>(src);
-          } else {
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-              if (8 * f8 + c < fn) row[j][c] = src[c];
-          }
-        }
-      }
-      const int ks = k8 >> 2, q = k8 & 3, b = f8 >> 2, i4 = 4 * (f8 & 3);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        half8_t v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = row[j][c];
-        const int t = 2 * b + (c >> 2), lane = 16 * q + i4 + (c & 3);
-        *reinterpret_cast<half8_t*>(Wf + ((int64_t(t) * KS + ks) * kWave + lane) * 8) = v;
-      }
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t at = uint32_t(min(8 * w.k8 + j, a.KW - kc - 1)) * pitch + uint32_t(min(w.f, fn - 8)) * 2u;
+      __builtin_memcpy(w.v + 4 * j, __builtin_assume_aligned(W + at, 16), 16);
     }
+  }
+}
+
+template <bool TRANS>
+__device__ __forceinline__ void linear_put_w(const LinearArgs& a, const WeightBatch& w, int first, int kc, int fc0, half_t* __restrict__ Wf) {
+  typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
+  const int KS = a.KC / 32, kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0), lane = threadIdx.x & (kWave - 1);
+  uint4_t* const out = reinterpret_cast<uint4_t*>(Wf);
+  const auto place = [&](int f, int k8) { return out + ((2 * (f >> 5) + ((f >> 2) & 1)) * KS + (k8 >> 2)) * kWave + linear_slot(4 * ((f >> 3) & 3) + (f & 3), k8 & 3); };
+  if (!linear_batched<TRANS>(a, kc, fc0)) {
+    const int64_t sf = TRANS ? a.ldw : 1, sk = TRANS ? 1 : a.ldw;
+    const int rows = TRANS ? kn : min(kn, a.KW - kc);
+    if (first == 0)
+      for (int idx = threadIdx.x; idx < a.FC * (a.KC / 8); idx += blockDim.x) {
+        const int k8 = int(unsigned(idx) / unsigned(a.FC)), f = idx - k8 * a.FC;
+        const half_t* const src = a.W + (fc0 + f) * sf + (kc + 8 * k8) * sk;
+        half8_t v = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (f < fn && 8 * k8 + j < rows) v[j] = src[j * sk];
+        *place(f, k8) = __builtin_bit_cast(uint4_t, v);
+      }
+    return;
+  }
+  if constexpr (TRANS) {
+    linear_each_item(a, first, [&](int u, int g, int c) {
+      const int f = 8 * g + (lane >> 3), k8 = 8 * c + (lane & 7);
+      const bool in = f < fn && 8 * k8 < kn;
+      uint4_t v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = in ? w.v[4 * u + j] : 0;
+      if (8 * k8 < a.KC) *place(f, k8) = v;
+    });
+  } else {
+    const int f = w.f, k8 = w.k8;
+    if (8 * k8 >= a.KC) return;
+    const int rows = f < fn ? min(kn, a.KW - kc) - 8 * k8 : 0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      uint4_t v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t even = 2 * j < rows ? w.v[8 * j + c / 2] : 0, odd = 2 * j + 1 < rows ? w.v[8 * j + 4 + c / 2] : 0;
+        v[j] = __builtin_amdgcn_perm(odd, even, c & 1 ? 0x07060302u : 0x05040100u);
+      }
+      *place(f + c, k8) = v;
+    }
+  }
+}
+
+// all items from `first` on
+template <bool TRANS>
+__device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __restrict__ Wf, int first, int kc, int fc0) {
+  for (; first < linear_w_items<TRANS>(a); first += linear_batch<TRANS>()) {
+    WeightBatch w;
+    linear_fetch_w<TRANS>(a, w, first, kc, fc0);
+    linear_put_w<TRANS>(a, w, first, kc, fc0, Wf);
   }
 }
 
@@ -125,12 +191,12 @@ __device__ __forceinline__ void linear_store(const LinearArgs& a, int64_t row, i
 // when K > 440, and X was read once per 128 features from memory.  Now workgroups are persistent, as many as the LDS
 // and registers of the chip hold, a workgroup brings its part of W in once (16-byte pieces) and the loads of X run one
 // group (4 x 16 bytes per lane) ahead of the products across passes and row blocks.  2.4 M x 128 -> 128: 323 -> 249 us
-// (4.9 TB/s, what a copy reaches); 233 k x 608 -> 64: 232 -> 64 us; 131 k x 128 -> 128: 40 -> 17 us.  Two row tiles per
+// (4.9 TB/s, what a copy reaches); 233 k x 608 -> 64: 232 -> 64 us; 131 k x 128 -> 128: 40 -> 17 us (14.4 now that the weight is asked for first).  Two row tiles per
 // wave for the sake of the weight fragments were slower (2.4 M: 325 us): the kernel waits for rows, not for LDS, and the
 // registers are better spent on the loads in flight.  RT > 1 is for rows that do not fill a group: with K <= 64 (32) a group
 // takes two (four) row tiles, so that as many bytes are in flight as with long rows.
 // CHUNKED: the weights of 128 features do not fit; the columns come in chunks, a chunk of W once per row block.
-template <int NT, int RT, bool CHUNKED>
+template <int NT, int RT, bool CHUNKED, bool TRANS>
 __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
   constexpr int GS = 4 / RT;    // 32-column steps in a group of X loads
   constexpr int GK = 32 * GS;   // columns of a group
@@ -147,20 +213,24 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
   const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
   half8_t next[4];
   auto load_group = [&](int64_t rb, int k0) {
+    // Rows and columns that do not exist are read inside X, without branches: such rows are not stored, such columns are cleared below.
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
       const int64_t row = (rb * wpw + wave) * (16 * RT) + 16 * r + i;
-      const half_t* src = a.X + (row < a.n ? row : 0) * a.ldx + k0 + 8 * q;
+      const half_t* src = a.X + min(row, a.n - 1) * a.ldx;
 #pragma unroll
-      for (int u = 0; u < GS; ++u) {
-        next[r * GS + u] = zero;
-        if (row < a.n && k0 + 32 * u + 8 * q < a.K) next[r * GS + u] = *reinterpret_cast<const half8_t*>(src + 32 * u);
-      }
+      for (int u = 0; u < GS; ++u)
+        if (k0 + 32 * u < a.K) next[r * GS + u] = *reinterpret_cast<const half8_t*>(src + min(k0 + 32 * u + 8 * q, a.K - 8));
     }
   };
-  load_group(blockIdx.x, 0);
-  if (!CHUNKED) {
-    linear_load_w(a, Wf, 0, fc0);
+  if (CHUNKED) {
+    load_group(blockIdx.x, 0);
+  } else {
+    WeightBatch w;
+    linear_fetch_w<TRANS>(a, w, 0, 0, fc0);
+    load_group(blockIdx.x, 0);
+    linear_put_w<TRANS>(a, w, 0, 0, fc0, Wf);
+    linear_load_w<TRANS>(a, Wf, linear_batch<TRANS>(), 0, fc0);
     __syncthreads();
   }
   for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
@@ -176,13 +246,18 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
         const int kn = CHUNKED ? min(a.KC, a.K - kc) : a.K;
         if (CHUNKED) {  // trip counts are uniform over the workgroup
           __syncthreads();
-          linear_load_w(a, Wf, kc, fc0);
+          linear_load_w<TRANS>(a, Wf, 0, kc, fc0);
           __syncthreads();
         }
         for (int k0 = 0; k0 < kn; k0 += GK) {
           if (!keep || pass == 0) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) cur[u] = next[u];
+            if (kc + k0 + GK > a.K) {
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (kc + k0 + 32 * (u % GS) + 8 * q >= a.K) cur[u] = zero;
+            }
           }
           // what comes after this group: more of the row, the row again for the next pass, or the next row block
           if (kc + k0 + GK < a.K) load_group(rb, kc + k0 + GK);
@@ -191,7 +266,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
 #pragma unroll
           for (int u = 0; u < GS; ++u) {
             if (k0 + 32 * u < kn) {  // uniform
-              const half_t* w = Wf + ((int64_t(pass) * NT * KS + (k0 / 32 + u)) * kWave + lane) * 8;
+              const half_t* w = Wf + ((int64_t(pass) * NT * KS + (k0 / 32 + u)) * kWave + linear_slot(i, q)) * 8;
 #pragma unroll
               for (int t = 0; t < NT; ++t) {
                 const half8_t wv = *reinterpret_cast<const half8_t*>(w + int64_t(t) * KS * (kWave * 8));
@@ -233,10 +308,11 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
 // The same for few rows with many columns, where a wave of linear_kernel is one chain of loads: here KP waves share a tile of 16 rows,
 // each takes at most kSplitSteps steps of 32 columns, whose loads all go out before the weight is brought in, and the partial
 // results are added through LDS in the order of the parts.  One row block per workgroup.  Bound by the latencies of a launch, of the
-// rows and of the weight, which more lanes bring in: 19 717 x 504 -> 64 12.9 -> 10.0 us (its bytes take 4.6), 4096 x 504 -> 64 9.0 -> 6.0.
+// rows and of the weight, which more lanes bring in: 19 717 x 504 -> 64 12.9 -> 10.0 us (its bytes take 4.6), 4096 x 504 -> 64 9.0 -> 6.0; with the
+// weight asked for ahead of X, calls in a row from a graph, 6.6 -> 6.3 and 5.4 -> 4.6, 12 000 x 504 -> 128 by W^T 8.5 -> 9.1.
 constexpr int kSplitSteps = 10;
 
-template <int NT, int KP>
+template <int NT, int KP, bool TRANS>
 __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   half_t* Wf = reinterpret_cast<half_t*>(lds_raw);
@@ -246,6 +322,8 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
   const int KS = a.KC / 32, per = (KS + KP - 1) / KP, s0 = part * per, sn = min(per, KS - s0);  // sn may be negative
   const int64_t row = (int64_t(blockIdx.x) * tiles + tile) * 16 + i;
   const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  WeightBatch w0;
+  linear_fetch_w<TRANS>(a, w0, 0, 0, 0);
   half8_t x[kSplitSteps];
 #pragma unroll
   for (int u = 0; u < kSplitSteps; ++u) {
@@ -253,7 +331,8 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
     const int k = 32 * (s0 + u) + 8 * q;
     if (u < sn && row < a.n && k < a.K) x[u] = *reinterpret_cast<const half8_t*>(a.X + row * a.ldx + k);
   }
-  linear_load_w(a, Wf, 0, 0);
+  linear_put_w<TRANS>(a, w0, 0, 0, 0, Wf);
+  linear_load_w<TRANS>(a, Wf, linear_batch<TRANS>(), 0, 0);
   __syncthreads();
   float4_t acc[NT];
 #pragma unroll
@@ -261,7 +340,7 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
 #pragma unroll
   for (int u = 0; u < kSplitSteps; ++u) {
     if (u < sn) {  // uniform over the wave
-      const half_t* w = Wf + (int64_t(s0 + u) * kWave + lane) * 8;
+      const half_t* w = Wf + (int64_t(s0 + u) * kWave + linear_slot(i, q)) * 8;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8_t*>(w + int64_t(t) * KS * (kWave * 8)), x[u], acc[t], 0, 0, 0);
@@ -640,7 +719,7 @@ __global__ __launch_bounds__(kBlock) void gat_feature_grad_kernel(FeatGradArgs a
 constexpr int kLinearLds = 152 * 1024;  // most bytes of W a workgroup keeps (of the 160 KB of a compute unit)
 
 template <void (*KERNEL)(LinearArgs)>
-static hgnn_status launch_linear_kernel(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+static hgnn_status launch_linear_kernel(LinearArgs a, dim3 grid, int threads, size_t lds, hipStream_t s) {
   // beyond 64 KB of dynamic LDS the runtime wants to be told, once per kernel and device
   static bool told[64] = {};
   if (lds > 65536) {
@@ -651,21 +730,30 @@ static hgnn_status launch_linear_kernel(const LinearArgs& a, dim3 grid, int thre
       if (dev >= 0 && dev < 64) told[dev] = true;
     }
   }
+  a.step_f = threads / kWave / ((a.KC + 63) / 64);
+  a.step_k = threads / kWave % ((a.KC + 63) / 64);
   KERNEL<<<grid, threads, lds, s>>>(a);
   HGNN_LAUNCH_CHECK("linear_kernel");
   return HGNN_OK;
 }
 
 template <int NT, int RT, bool CHUNKED>
-static hgnn_status launch_linear(const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED>>(a, grid, threads, lds, s);
+static hgnn_status launch_linear(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (trans) return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true>>(a, grid, threads, lds, s);
+  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false>>(a, grid, threads, lds, s);
+}
+
+template <int NT, int KP>
+static hgnn_status launch_linear_split(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (trans) return launch_linear_kernel<linear_split_kernel<NT, KP, true>>(a, grid, threads, lds, s);
+  return launch_linear_kernel<linear_split_kernel<NT, KP, false>>(a, grid, threads, lds, s);
 }
 
 template <int KP>
-static hgnn_status launch_linear_split(int nt, const LinearArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (nt == 2) return launch_linear_kernel<linear_split_kernel<2, KP>>(a, grid, threads, lds, s);
-  if (nt == 4) return launch_linear_kernel<linear_split_kernel<4, KP>>(a, grid, threads, lds, s);
-  return launch_linear_kernel<linear_split_kernel<8, KP>>(a, grid, threads, lds, s);
+static hgnn_status launch_linear_split(int nt, const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (nt == 2) return launch_linear_split<2, KP>(a, trans, grid, threads, lds, s);
+  if (nt == 4) return launch_linear_split<4, KP>(a, trans, grid, threads, lds, s);
+  return launch_linear_split<8, KP>(a, trans, grid, threads, lds, s);
 }
 
 static int wgrad_parts(int K, int F) {
@@ -694,9 +782,8 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   HGNN_REQUIRE(X && W && Y, HGNN_EINVAL, "%s: NULL argument", who);
   HGNN_REQUIRE(K % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y), HGNN_EUNSUPPORTED,
                "%s: needs K %% 8 == 0, ldx %% 8 == 0, ldy %% 8 == 0 and 16-byte aligned X, Y (pad with zeros)", who);
-  LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw, trans_w ? 1 : 0,
-               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, KW};
-  a.wvec = ldw % 8 == 0 && aligned16(W) ? 1 : 0;
+  LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw,
+               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, 0, 0, KW};
   const int k32 = (K + 31) / 32 * 32, f32 = (F + 31) / 32 * 32;
   // short rows: several row tiles per wave, where that still leaves four waves for every compute unit
   const int RT = n < int64_t(32) * 4 * kCus || K > 64 ? 1 : (K > 32 || n < int64_t(64) * 4 * kCus ? 2 : 4);
@@ -717,12 +804,17 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
       a.KC = kLinearLds / (a.FC * 2) / 128 * 128;
     }
   }
+  a.wvec = ldw % 8 == 0 && aligned16(W) && ldw < (int64_t(1) << 30) / (trans_w ? a.FC : a.KC) ? 1 : 0;
   const size_t lds = size_t(a.KC) * size_t(a.FC) * sizeof(half_t);
-  // waves per workgroup: the more LDS a workgroup holds, the more waves share it (16 waves per compute unit in all);
-  // fewer, so that every compute unit has work, while bringing the weight in stays short
-  int wpw = lds <= 40 * 1024 ? 4 : (lds <= 80 * 1024 ? 8 : 16);
-  const int least = lds <= 16 * 1024 ? 1 : (lds <= 32 * 1024 ? 2 : 4);
   const int64_t tiles = ceil_div(n, int64_t(16) * RT);
+  // Waves per compute unit: 16, or 32 where at least as much is written as read and that often.  us, 16 / 32: 233 000 rows of 64 -> 608 78 / 67,
+  // 10^6 of 128 -> 128 107 / 104; 131 072 of 128 -> 128 14.6 / 17.7, 262 144 of 64 -> 64 12.3 / 15.4, 500 000 of 256 -> 64 58 / 59, 233 000 of 608 -> 64 61 / 65
+  const int waves = F >= K && tiles * ceil_div(F, int64_t(16) * nt) >= 32768 ? 32 : 16;
+  // waves per workgroup: the more LDS a workgroup holds, the more waves share it; twice as many from two row tiles per wave on, when the weight is
+  // brought in half as often (four / eight: 500 000 rows of 256 -> 64 61.6 / 58.0, 131 072 of 128 -> 128 by W^T 15.6 / 14.3; 70 000 10.7 / 11.8);
+  // fewer, so that every compute unit has work, while bringing the weight in stays short
+  int wpw = lds <= 40 * 1024 ? (tiles >= 2 * 16 * kCus ? 8 : 4) : (lds <= 80 * 1024 ? waves / 2 : 16);
+  const int least = lds <= 16 * 1024 ? 1 : (lds <= 32 * 1024 ? 2 : 4);
   while (wpw > least && ceil_div(tiles, wpw) < kCus) wpw /= 2;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // Few rows with many columns: as many row tiles per workgroup as give every compute unit one, and waves beside them up to 16 that
@@ -734,6 +826,7 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   //   504, 64          8.6 / 5.5   9.0 / 6.0   9.2 / 6.6  10.9 / 8.1  12.9 / 10.0 14.0 / 12.1 13.5 / 13.3
   //   504, 128, W^T   13.2 / 8.1  13.3 / 8.8  13.6 / 9.4  16.1 / 10.5 24.3 / 13.6 24.4 / 16.5 17.8 / 17.8
   //   1024, 64        16.3 / 8.6  16.4 / 9.0  21.7 / 11.7 22.1 / 12.2
+  // (before the weight was asked for ahead of X, which took 0.3 to 1 us off both sides)
   // at 40 000 rows (two rounds of workgroups) 10 to 40 % slower.
   // Behind the kernel that wrote X, in the caches, a chain of few steps ends sooner: 256, 64 at 32 768 rows 7.9 / 8.6, 256, 128 10.5 / 11.3; 128, 64
   // at 8192 5.2 / 5.5, at 5000 6.6 / 5.4, W^T 5.6 / 4.6 and 7.1 / 4.5; 128, 128 at 8192, 20 000, 27 000 7.2 / 6.5, 7.5 / 7.3, 7.8 / 8.1; 128, 32 at 2000
@@ -744,30 +837,30 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
     const size_t need = std::max(lds, size_t(KP - 1) * size_t(T) * size_t(nt) * kWave * sizeof(float4_t));
     const dim3 grid{unsigned(ceil_div(tiles, T)), 1u, 1u};
     const int threads = T * KP * kWave;
-    return KP == 4 ? launch_linear_split<4>(nt, a, grid, threads, need, s)
-                   : (KP == 3 ? launch_linear_split<3>(nt, a, grid, threads, need, s) : launch_linear_split<2>(nt, a, grid, threads, need, s));
+    return KP == 4 ? launch_linear_split<4>(nt, a, trans_w != 0, grid, threads, need, s)
+                   : (KP == 3 ? launch_linear_split<3>(nt, a, trans_w != 0, grid, threads, need, s) : launch_linear_split<2>(nt, a, trans_w != 0, grid, threads, need, s));
   }
   const int fy = int(ceil_div(F, a.FC));
   const int64_t nrb = ceil_div(tiles, wpw);
   // persistent workgroups, as many as fit the chip at once, each with the same number of row blocks (to one)
-  const int64_t resident = int64_t(kCus) * std::max<int64_t>(1, std::min<int64_t>(16 / wpw, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
+  const int64_t resident = int64_t(kCus) * std::max<int64_t>(1, std::min<int64_t>(waves / wpw, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
   const int64_t per = ceil_div(nrb, std::max<int64_t>(1, resident / fy));
   const int64_t want = ceil_div(nrb, per);
   HGNN_REQUIRE(want <= 0x7fffffff && fy <= 65535, HGNN_EUNSUPPORTED, "%s: grid too large", who);
   const dim3 grid{unsigned(want), unsigned(fy), 1u};
   const int threads = wpw * kWave;
   if (a.KC < K) {
-    if (nt == 2) return launch_linear<2, 1, true>(a, grid, threads, lds, s);
-    if (nt == 4) return launch_linear<4, 1, true>(a, grid, threads, lds, s);
-    return launch_linear<8, 1, true>(a, grid, threads, lds, s);
+    if (nt == 2) return launch_linear<2, 1, true>(a, trans_w != 0, grid, threads, lds, s);
+    if (nt == 4) return launch_linear<4, 1, true>(a, trans_w != 0, grid, threads, lds, s);
+    return launch_linear<8, 1, true>(a, trans_w != 0, grid, threads, lds, s);
   }
   if (nt == 2) {
-    if (RT == 4) return launch_linear<2, 4, false>(a, grid, threads, lds, s);
-    return RT == 2 ? launch_linear<2, 2, false>(a, grid, threads, lds, s) : launch_linear<2, 1, false>(a, grid, threads, lds, s);
+    if (RT == 4) return launch_linear<2, 4, false>(a, trans_w != 0, grid, threads, lds, s);
+    return RT == 2 ? launch_linear<2, 2, false>(a, trans_w != 0, grid, threads, lds, s) : launch_linear<2, 1, false>(a, trans_w != 0, grid, threads, lds, s);
   }
-  if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, grid, threads, lds, s);
-  if (nt == 4) return launch_linear<4, 1, false>(a, grid, threads, lds, s);
-  return launch_linear<8, 1, false>(a, grid, threads, lds, s);
+  if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, trans_w != 0, grid, threads, lds, s);
+  if (nt == 4) return launch_linear<4, 1, false>(a, trans_w != 0, grid, threads, lds, s);
+  return launch_linear<8, 1, false>(a, trans_w != 0, grid, threads, lds, s);
 }
 
 extern "C" {

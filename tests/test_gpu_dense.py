@@ -71,6 +71,29 @@ def test_linear_shared_columns(hgnn, dev, n, K, F, trans):
     test_linear_shapes(hgnn, dev, n, K, F, trans, 0, 0)
 
 
+# whole and partial 16-byte pieces of the weight, twice as many waves per workgroup (8192 tiles of rows), 32 waves (few columns, many
+# features); what lies beside and behind the operands must not be looked at
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("n,K,F", [(3, 8, 8), (250, 72, 40), (33000, 40, 52), (131090, 72, 8), (110001, 8, 608), (20000, 168, 100), (70, 2504, 24)])
+def test_linear_stays_inside(hgnn, dev, n, K, F, trans):
+    print(f"linear inside n={n} K={K} F={F} trans={trans}", flush=True)
+    r = np.random.default_rng(n + K + F + trans)
+    X = f16(r.standard_normal((n, K)))
+    X[n // 2, K // 2] = np.inf
+    W = f16(r.standard_normal((F, K) if trans else (K, F)) / np.sqrt(K))
+    Xb = torch.full((n + 64, K + 8), float("nan"), dtype=torch.float16, device=dev)
+    Wb = torch.full((W.shape[0] + 8, (W.shape[1] + 7) // 8 * 8 + 8), float("nan"), dtype=torch.float16, device=dev)
+    Xb[:n, :K], Wb[:W.shape[0], :W.shape[1]] = up(X, dev), up(W, dev)
+    Yb = torch.full((n + 1, (F + 7) // 8 * 8), 7.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_linear(Xb[:n, :K], Wb[:W.shape[0], :W.shape[1]], Yb[:n, :F], trans_w=trans)
+    got = down(Yb)
+    assert np.all(got[n] == 7.0) and np.all(got[:, F:] == 7.0)
+    finite = np.arange(n) != n // 2
+    assert not np.isfinite(got[n // 2, :F]).any()
+    ref, sabs = oracle.linear(X[finite], W, trans=trans, want_sabs=True)
+    compare("linear", got[:n][finite][:, :F], ref, sabs)
+
+
 def test_linear_identity_and_zero_rows(hgnn, dev):
     n, K = 777, 96
     r = np.random.default_rng(5)
