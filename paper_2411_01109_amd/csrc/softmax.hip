@@ -705,6 +705,12 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
   const double per_row = mean_len * ((OP == kSum && a.eid) ? 1.0 : H / 8.0);
   int LR = 4;
   while (LR < kWave && LR < per_row) LR <<= 1;
+  // Half of the lanes where two vectors on each still hold a quarter more than the mean row: what a team spends is the exchange between its lanes,
+  // twice per head forward.  us, all / half of them: forward, 3 M of 300 000 uniform rows, four heads 19.1 / 14.4, eight 43 / 28; 3.5 M of 100 000, one
+  // head 7.6 / 7.2, two 13.1 / 10.6, four 28.4 / 19.2, eight 75 / 46; 6 M of 60 000 log-normal, four 48 / 36; sums 8.8 / 6.6, 15.8 / 12.3, 5.1 / 4.8, 6.9 / 6.3,
+  // 13.1 / 9.9, 21.5 / 20.2, 20.6 / 16.8.  With less to spare rows leave for the tier of the longer ones (6 M of 100 000, one head 9.8 / 13.5, sums
+  // 6.2 / 7.6); the backward, with three tensors in registers, gains nothing (log-normal, four heads 17.6 / 19.7).
+  if (p && OP != kBwd && !(OP == kSum && a.eid) && LR > 4 && LR >= 1.25 * per_row) LR >>= 1;
   const int big = (p && p->n_big > 0) ? p->big_deg : 0;
   a.big_row = p ? p->big_row : nullptr;
   // tier 1: sub-wave teams take the rows they can hold in registers; tier 2: a whole wave per row

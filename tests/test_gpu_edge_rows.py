@@ -113,6 +113,30 @@ def test_rows_dealt_out(hgnn, dev, V, H):
         compare("row sums", down(out), oracle.edge_rowsum(rowptr.astype(np.int32), d64), oracle.edge_rowsum(rowptr.astype(np.int32), np.abs(d64)))
 
 
+# mean lengths at which half of the lanes take a row, or just not any more; rows beyond what those hold at once, from a whole wave's lanes on
+@pytest.mark.parametrize("mean,H", [(5, 8), (12, 8), (13, 8), (10, 4), (20, 2), (25, 4), (26, 4), (35, 8), (48, 1), (100, 4), (400, 1), (420, 1)])
+def test_half_of_the_lanes(hgnn, dev, mean, H):
+    print(f"half of the lanes mean={mean} H={H}", flush=True)
+    V = 3000
+    r = np.random.default_rng(mean + H)
+    deg = r.integers(0, mean, V)
+    deg[::7] = r.integers(mean, 2 * mean, deg[::7].size)
+    deg[5::100] = 3 * mean + r.integers(0, 40, deg[5::100].size)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    e16 = f16(3 * r.standard_normal((E, H)))
+    g = csr_of(hgnn, dev, deg)
+    p = hgnn.hgnn_plan_create(g, 256, 64, 8)
+    alpha, out = (torch.full((n, H), 9.0, dtype=torch.float16, device=dev) for n in (E, V))
+    hgnn.hgnn_edge_softmax(g, p, H, up(e16, dev), alpha)
+    ref = oracle.edge_softmax(rowptr, e16.astype(np.float64))
+    assert np.all(np.abs(down(alpha).astype(np.float64) - ref) <= ref * (2.0 ** -11 + 2.0 ** -18) + 2.0 ** -24)
+    hgnn.hgnn_edge_rowsum(g, p, H, up(e16, dev), out)
+    e64 = e16.astype(np.float64)
+    compare("row sums", down(out), oracle.edge_rowsum(rowptr, e64), oracle.edge_rowsum(rowptr, np.abs(e64)))
+    hgnn.hgnn_plan_destroy(p)
+
+
 @pytest.mark.parametrize("H,planned", [(1, False), (4, False), (8, False), (1, True), (2, True)])
 def test_rows_in_order_of_their_lengths(hgnn, dev, H, planned):
     """Vertices in the order of their degrees, longest rows side by side, take no longer than the same rows in any order: sixteen of the longest in
