@@ -53,9 +53,9 @@ __device__ __forceinline__ long long half_bits_to_fixed(unsigned bits) {
 }
 
 // LDS of a workgroup: the slice's table (W scalars of 4 or 8 bytes), then per wave the bookkeeping of the 64 rows
-// it is working on: exclusive prefix of the pieces' lengths (65 ints), their first positions, and for the score the
-// rows' el and lse
-__host__ __device__ inline int slice_wave_bytes(bool colsum) { return (66 + 64 + (colsum ? 0 : 128)) * 4; }
+// it is working on: a bit for each slot of a round, and of every row with a piece its first position less its first slot and, for the
+// score, its el and lse
+__host__ __device__ inline int slice_wave_bytes(bool colsum) { return 2 * kSliceUnroll * 4 + 64 * (colsum ? 4 : 12); }
 __host__ __device__ inline size_t slice_lds_bytes(int W, bool colsum) {
   return size_t(W) * (colsum ? 8 : 4) + size_t(kSliceWaves) * slice_wave_bytes(colsum);
 }
@@ -66,10 +66,10 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   float* s_er = reinterpret_cast<float*>(smem);
   unsigned long long* s_acc = reinterpret_cast<unsigned long long*>(smem);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  int* s_p = reinterpret_cast<int*>(smem + size_t(a.W) * (COLSUM ? 8 : 4) + size_t(wave) * slice_wave_bytes(COLSUM));
-  int* s_d = s_p + 66;
-  float* s_el = reinterpret_cast<float*>(s_d + 64);
-  float* s_lse = s_el + 64;
+  // (W is a multiple of 64)
+  unsigned* s_begins = reinterpret_cast<unsigned*>(smem + size_t(a.W) * (COLSUM ? 8 : 4) + size_t(wave) * slice_wave_bytes(COLSUM));
+  int* s_row = reinterpret_cast<int*>(s_begins + 2 * kSliceUnroll);  // [64], or pairs of it and el
+  float* s_lse = reinterpret_cast<float*>(s_row + 128);
   // workgroup id = slice * nch + chunk, nch a multiple of 8: the slices of one row chunk run on one XCD (workgroups
   // are dealt out to the XCDs in turn), so the cache lines that neighbouring pieces of a row share meet in one L2
   const int s = int(blockIdx.x) / a.nch, c = int(blockIdx.x) % a.nch;
@@ -89,32 +89,46 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   const int* __restrict__ hi = lo + a.nrows;
   const unsigned short* __restrict__ tbits = reinterpret_cast<const unsigned short*>(a.t);
 
-  // A wave takes 64 rows at a time.  The non-zeros of their pieces of this slice are numbered through (slot q belongs
-  // to the row j with p[j] <= q < p[j+1]) and dealt out to the lanes in turn, so that every load instruction moves 64
-  // non-zeros whatever the lengths of the pieces; a lane's slots ascend, so it finds their rows by walking j forward.
-  // The loads run one round ahead of the work: while the non-zeros of a round (8 x 64 slots) are scored or added, the
-  // column ids and values of the next round are on their way; the row bounds of the next 64 rows are requested when a
-  // batch begins.
+  // A wave takes 64 rows at a time.  The non-zeros of their pieces of this slice are numbered through and dealt out to the lanes in
+  // turn, so that every load instruction moves 64 non-zeros whatever the lengths of the pieces.  The loads run one round ahead of the work: while the
+  // non-zeros of a round (8 x 64 slots) are scored or added, the column ids and values of the next round are on their way; the row bounds of the next
+  // 64 rows are requested when a batch begins.
   // Slots beyond the batch's total repeat its last slot (a valid position): for the score that stores the same value
-  // twice, for the sums the repeated value is replaced by zero.  The row of a slot comes from a branch-free binary
-  // search over the 65 prefix values, six LDS reads per slot; the eight searches of a round are independent chains.
-  auto plan_round = [&](pos_t q0, pos_t total, int (&kk)[kSliceUnroll], int (&jj)[kSliceUnroll]) {
-    int q[kSliceUnroll];
+  // twice, for the sums the repeated value is replaced by zero.  The row of a slot, among those that have a piece, is the number of pieces that
+  // begin behind the first slot and not behind this one: their first slots, less one, are set as bits, which a lane counts below its own.  A binary
+  // search over the prefix values, six LDS reads in turn and some 24 vector instructions per slot, was half of the kernel.  us, score; column sums,
+  // with it / now: 114 M log-normal 236; 241 / 224; 209, 24 M of 100 000 log-normal 56; 64 / 42; 52, 20 M power law of 100 000 118; 142 / 88; 114, 8 M of
+  // 30 000 uniform 23.3; 29.6 / 18.9; 26.4.  The largest are bound by the memory's lines now, of which neighbouring pieces share many (3.1 and 3.3 TB/s).
+  auto plan_round = [&](pos_t qb, pos_t total, pos_t begin, bool has, unsigned& before, int (&kk)[kSliceUnroll], int (&jj)[kSliceUnroll]) {
+    if (lane < 2 * kSliceUnroll) s_begins[lane] = 0u;
+    wave_sync();
+    const pos_t at = begin - 1 - qb;  // (the first piece of a batch begins at slot 0 and is not counted)
+    if (has && at < pos_t(kWave * kSliceUnroll)) atomicOr(s_begins + (at >> 5), 1u << (at & 31u));
+    wave_sync();
 #pragma unroll
     for (int u = 0; u < kSliceUnroll; ++u) {
-      q[u] = int(q0 + u * kWave < total ? q0 + u * kWave : total - 1);
-      jj[u] = 0;
+      const uint2 m = *reinterpret_cast<const uint2*>(s_begins + 2 * u);
+      jj[u] = int(__builtin_amdgcn_mbcnt_hi(m.y, __builtin_amdgcn_mbcnt_lo(m.x, before)));
+      before += unsigned(__popc(m.x) + __popc(m.y));
     }
 #pragma unroll
-    for (int step = kWave / 2; step > 0; step >>= 1) {
-#pragma unroll
-      for (int u = 0; u < kSliceUnroll; ++u)
-        if (s_p[jj[u] + step] <= q[u]) jj[u] += step;  // largest j in [0, 63] with p[j] <= q
+    for (int u = 0; u < kSliceUnroll; ++u) {
+      const pos_t q = qb + pos_t(u * kWave + lane);
+      kk[u] = int(q < total ? q : total - 1);
     }
-#pragma unroll
-    for (int u = 0; u < kSliceUnroll; ++u) kk[u] = s_d[jj[u]] + q[u];  // position = slot + (first position - first slot) of the row
   };
-  auto issue = [&](const int (&kk)[kSliceUnroll], int (&cc)[kSliceUnroll], unsigned (&tt)[kSliceUnroll]) {
+  // position = slot + (first position - first slot) of the row; the score takes the row's el (as bits) along
+  auto issue = [&](int (&kk)[kSliceUnroll], const int (&jj)[kSliceUnroll], int (&cc)[kSliceUnroll], unsigned (&tt)[kSliceUnroll]) {
+#pragma unroll
+    for (int u = 0; u < kSliceUnroll; ++u) {
+      if (COLSUM) {
+        kk[u] += s_row[jj[u]];
+      } else {
+        const uint2 r = reinterpret_cast<const uint2*>(s_row)[jj[u]];
+        kk[u] += int(r.x);
+        tt[u] = r.y;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kSliceUnroll; ++u) {
       cc[u] = a.col[kk[u]];  // ordinary loads: the lines that pieces share are met again in the L1 and the L2
@@ -134,7 +148,7 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
           atomicAdd(s_acc + cidx, (unsigned long long)half_bits_to_fixed(tb));
         }
       } else {
-        float v = s_el[jj[u]] + s_er[cidx];
+        float v = __uint_as_float(tt[u]) + s_er[cidx];
         v = v > 0.f ? v : a.slope * v;
         if (a.lse) v = __expf(v - s_lse[jj[u]]);
         a.out[kk[u]] = half_t(v);
@@ -166,25 +180,31 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
       if (lane >= d) inc += t;
     }
     const pos_t total = pos_t(__shfl(inc, kWave - 1));
-    if (lane == 0) s_p[0] = 0;
-    s_p[lane + 1] = inc;
-    s_d[lane] = b - (inc - (e - b));  // first position minus first slot
-    if (!COLSUM) {
-      s_el[lane] = elv;
-      s_lse[lane] = lsev;
+    const pos_t begin = pos_t(inc - (e - b));
+    const bool has = e > b;
+    const unsigned long long pieces = __ballot(has);
+    const int rank = int(__builtin_amdgcn_mbcnt_hi(unsigned(pieces >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(pieces), 0u)));
+    if (has) {
+      if (COLSUM) {
+        s_row[rank] = b - int(begin);
+      } else {
+        reinterpret_cast<int2*>(s_row)[rank] = make_int2(b - int(begin), __float_as_int(elv));
+        if (a.lse) s_lse[rank] = lsev;
+      }
     }
+    unsigned before = 0;
     wave_sync();
     int kA[kSliceUnroll], jA[kSliceUnroll], cA[kSliceUnroll], kB[kSliceUnroll], jB[kSliceUnroll], cB[kSliceUnroll];
     unsigned tA[kSliceUnroll], tB[kSliceUnroll];
     if (total > 0) {
-      plan_round(lane, total, kA, jA);
-      issue(kA, cA, tA);
+      plan_round(0, total, begin, has, before, kA, jA);
+      issue(kA, jA, cA, tA);
     }
     for (pos_t qb = 0; qb < total; qb += kWave * kSliceUnroll) {
       const bool more = qb + kWave * kSliceUnroll < total;
       if (more) {
-        plan_round(lane + qb + kWave * kSliceUnroll, total, kB, jB);
-        issue(kB, cB, tB);
+        plan_round(qb + kWave * kSliceUnroll, total, begin, has, before, kB, jB);
+        issue(kB, jB, cB, tB);
       }
       work(lane + qb, total, kA, jA, cA, tA);
       if (more) {
@@ -309,7 +329,8 @@ hgnn_status build_col_slices(hgnn_plan* p, const hgnn_csr* g, int W, bool asked,
   HGNN_HIP(s.wait());
   // Scores gather through the caches just as well where there are few: us, segments / slices, 1 M non-zeros of 13 292 vertices 8.4 / 14.0, 1.2 M of
   // 4000 8.3 / 11.8, 3 M of 30 000 17.4 / 16.3, 3.5 M of 13 292 14.0 / 16.0, 5.4 M of 20 000 22.0 / 22.2, 6 M of 60 000 32.6 / 23.0 (power law 26.0 / 34.3), 8 M
-  // of 30 000 33.8 / 27.9, 20 M of 16 000 53.4 / 39.7, 24 M of 100 000 103 / 57.  Column sums have no other way.
+  // of 30 000 33.8 / 27.9, 20 M of 16 000 53.4 / 39.7, 24 M of 100 000 103 / 57 (slices by a binary search per non-zero; now 6 M power law 27.5, 8 M of
+  // 30 000 18.9, 24 M of 100 000 42, 1 M of 13 292 10.2).  Column sums have no other way.
   constexpr int64_t kScoreNnz = int64_t(4) << 20;
   p->slice_scores = asked || g->nnz > kScoreNnz;
   p->ns = ns;

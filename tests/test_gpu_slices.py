@@ -203,6 +203,34 @@ def test_slices_of_long_rows(hgnn, dev, V, ncols, E, W):
     assert np.all(np.abs(down(sums)[:, 0] - ref) <= np.abs(ref) * 2.0 ** -11 * (1 + 2.0 ** -10) + 2.0 ** -25)
 
 
+# pieces that begin and end at the words of a round's bits, at its end and a slot to either side; rows without a piece between them
+@pytest.mark.parametrize("lengths", [[1], [31, 1, 32, 0, 33], [64], [63, 0, 0, 65], [511, 1], [512], [513], [1, 0, 511, 0, 512, 2], [0, 3000, 0, 0, 1]])
+def test_slices_rows_of_a_round(hgnn, dev, lengths):
+    print(f"slices rows of a round {lengths}", flush=True)
+    r = np.random.default_rng(sum(lengths))
+    deg = np.array((lengths * 400)[:400])
+    V, ncols, D, E = deg.size, 100, 8, int(deg.sum())
+    rowptr, row = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32), np.repeat(np.arange(V), deg)
+    key = r.integers(0, ncols, E)
+    col = key[np.lexsort((key, row))].astype(np.int32)
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev), ncols=ncols)
+    p = hgnn.hgnn_plan_create(g, 256, 64, 1, col_blocks=1)
+    U, Vt = up(f16(r.standard_normal((V, D))), dev), up(f16(r.standard_normal((ncols, D))), dev)
+    a_l, a_r = (up(f16(r.standard_normal((1, D))), dev) for _ in range(2))
+    e = [torch.full((E, 1), 9.0, dtype=torch.float16, device=dev) for _ in range(2)]
+    hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_GAT_SCORE, 1, D, U, Vt, e[0], a_l, a_r, 0.2)  # by segments
+    hgnn.hgnn_plan_add_slices(p, g, 0)
+    hgnn.hgnn_sddmm(g, p, hgnn.HGNN_SDDMM_GAT_SCORE, 1, D, U, Vt, e[1], a_l, a_r, 0.2)
+    assert torch.equal(e[0], e[1])  # the same sums of the same fp32 values
+    t = f16(r.standard_normal((E, 1)))
+    sums = torch.full((ncols, 1), 9.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_edge_colsum(g, p, 1, up(t, dev), sums)
+    ref = np.zeros(ncols)
+    np.add.at(ref, col, t[:, 0].astype(np.float64))  # exact
+    assert np.all(np.abs(down(sums)[:, 0] - ref) <= np.abs(ref) * 2.0 ** -11 * (1 + 2.0 ** -10) + 2.0 ** -25)
+    hgnn.hgnn_plan_destroy(p)
+
+
 # stretches of rows without non-zeros, longer than the rows that have any by far: in the middle, at the end, at both, one non-zero in the midst
 @pytest.mark.parametrize("where", ["middle", "end", "all around", "lone"])
 @pytest.mark.parametrize("W", [0, 1024])
