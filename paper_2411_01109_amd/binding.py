@@ -1,7 +1,10 @@
-"""ctypes binding of libhgnn.so: the same entry points as include/hgnn.h, taking
+"""Binding of libhgnn.so: the same entry points as include/hgnn.h, taking
 torch CUDA tensors.  Argument marshalling only -- every step of the path runs in
 the library's HIP kernels; torch supplies device memory and the stream.  There is
 no CPU fallback: a missing library or a failing call raises.
+
+The calls of a step go through csrc/calls.cpp where their arguments are of the plain form, else, like all
+others, through ctypes (a layer of 4096 vertices, five calls: 26.2 us of host time with ctypes alone).
 """
 from __future__ import annotations
 
@@ -13,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhgnn.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 
 HGNN_OK, HGNN_EINVAL, HGNN_EUNSUPPORTED, HGNN_ENOMEM, HGNN_EHIP = range(5)
 HGNN_SUM, HGNN_MEAN = 0, 1
@@ -54,16 +58,17 @@ class _CsrStruct(ctypes.Structure):
 
 
 _lib = None
+_calls = None  # the module of csrc/calls.cpp once the library is loaded
 
 
 def load() -> ctypes.CDLL:
     """Load libhgnn.so; raises when it has not been built (no fallback of any kind)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            f"{LIB_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+    for path in (LIB_PATH, CALLS_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     csr = ctypes.POINTER(_CsrStruct)
@@ -140,8 +145,19 @@ def load() -> ctypes.CDLL:
                                           ctypes.c_size_t, vp]
     for name in EXPORTS:
         getattr(lib, name)  # every declared entry point must be exported
+    from . import _calls as calls
+    if _raw_stream is not None and _current_device is not None:
+        calls.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _raw_stream, _current_device)
+        _calls = calls
     _lib = lib
     return lib
+
+
+def _done(status: int) -> bool:
+    """Of a call through csrc/calls.cpp: whether it has been made (then errors are raised); not if an argument was not plain."""
+    if status > 0:
+        _check(status)
+    return status == 0
 
 
 def _check(status: int) -> None:
@@ -325,6 +341,8 @@ def hgnn_spmm(g: Csr, edge_val: Optional[torch.Tensor], H: int, X: torch.Tensor,
               op: int = HGNN_SUM, row_scale: Optional[torch.Tensor] = None, F: Optional[int] = None,
               workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """workspace: device tensor of at least hgnn_spmm_workspace(...) bytes, or None (long rows then take one wave each)."""
+    if _calls is not None and _done(_calls.spmm(g, edge_val, H, X, Y, op, row_scale, F, workspace, stream)):
+        return
     F = X.shape[1] if F is None else F
     _check(load().hgnn_spmm(g.ref, _ptr(edge_val, torch.float16), H, _ptr(X, torch.float16), _ld(X),
                             _ptr(Y, torch.float16), _ld(Y), F, op, _ptr(row_scale, torch.float32),
@@ -347,6 +365,8 @@ def hgnn_spmm_static(g: Csr, edge_val: Optional[torch.Tensor], H: int, X: torch.
 def hgnn_spmm_discretized(p: Plan, g: Csr, edge_val: Optional[torch.Tensor], H: int, X: torch.Tensor, Y: torch.Tensor,
                           op: int = HGNN_SUM, row_scale: Optional[torch.Tensor] = None, F: Optional[int] = None,
                           stream=None) -> None:
+    if _calls is not None and _done(_calls.spmm_discretized(p, g, edge_val, H, X, Y, op, row_scale, F, stream)):
+        return
     F = X.shape[1] if F is None else F
     _check(load().hgnn_spmm_discretized(p.handle, g.ref, _ptr(edge_val, torch.float16), H, _ptr(X, torch.float16),
                                         _ld(X), _ptr(Y, torch.float16), _ld(Y), F, op,
@@ -358,6 +378,8 @@ def hgnn_spmm_discretized_fused(p: Plan, g: Csr, edge_val: Optional[torch.Tensor
                                 col_scale: Optional[torch.Tensor] = None, self_feat: Optional[torch.Tensor] = None,
                                 self_coef: float = 0.0, agg_coef: float = 1.0, F: Optional[int] = None,
                                 scaled_x: Optional[torch.Tensor] = None, stream=None) -> None:
+    if _calls is not None and _done(_calls.spmm_discretized_fused(p, g, edge_val, H, X, Y, op, row_scale, col_scale, self_feat, self_coef, agg_coef, F, scaled_x, stream)):
+        return
     F = X.shape[1] if F is None else F
     fz = _FusionStruct(_ptr(col_scale, torch.float32), _ptr(self_feat, torch.float16),
                        0 if self_feat is None else _ld(self_feat), self_coef, agg_coef, _ptr(scaled_x, torch.float16),
@@ -400,6 +422,8 @@ def hgnn_plan_groups_export(p: Plan, g: Csr):
 def hgnn_gat_forward_fused(g: Csr, p: Plan, H: int, D: int, U: torch.Tensor, Vt: torch.Tensor, a_l: torch.Tensor,
                            a_r: torch.Tensor, out: torch.Tensor, lse: Optional[torch.Tensor] = None,
                            neg_slope: float = 0.2, stream=None) -> None:
+    if _calls is not None and _done(_calls.gat_forward_fused(g, p, H, D, U, Vt, a_l, a_r, out, lse, neg_slope, stream)):
+        return
     _check(load().hgnn_gat_forward_fused(g.ref, p.handle, H, D, _ptr(U, torch.float16), _ld(U), _ptr(Vt, torch.float16),
                                          _ld(Vt), _ptr(a_l, torch.float16), _ptr(a_r, torch.float16), neg_slope,
                                          _ptr(out, torch.float16), _ld(out), _ptr(lse, torch.float32), _stream(stream)))
@@ -420,6 +444,8 @@ def hgnn_gat_backward_fused(g: Csr, p: Plan, gt: Csr, pt: Plan, H: int, D: int, 
 def hgnn_gat_forward_fused_save(g: Csr, p: Plan, H: int, D: int, U: torch.Tensor, Vt: torch.Tensor, a_l: torch.Tensor,
                                 a_r: torch.Tensor, out: torch.Tensor, lse: torch.Tensor, out_masked: torch.Tensor,
                                 csum: torch.Tensor, neg_slope: float = 0.2, stream=None) -> None:
+    if _calls is not None and _done(_calls.gat_forward_fused_save(g, p, H, D, U, Vt, a_l, a_r, out, lse, out_masked, csum, neg_slope, stream)):
+        return
     _check(load().hgnn_gat_forward_fused_save(g.ref, p.handle, H, D, _ptr(U, torch.float16), _ld(U), _ptr(Vt, torch.float16),
                                               _ld(Vt), _ptr(a_l, torch.float16), _ptr(a_r, torch.float16), neg_slope,
                                               _ptr(out, torch.float16), _ld(out), _ptr(lse, torch.float32),
@@ -431,6 +457,8 @@ def hgnn_gat_backward_fused_saved(g: Csr, p: Plan, gt: Csr, pt: Plan, H: int, D:
                                   a_l: torch.Tensor, a_r: torch.Tensor, out: torch.Tensor, lse: torch.Tensor,
                                   out_masked: torch.Tensor, csum: torch.Tensor, dOut: torch.Tensor, dV: torch.Tensor,
                                   d_el: torch.Tensor, d_er: torch.Tensor, neg_slope: float = 0.2, stream=None) -> None:
+    if _calls is not None and _done(_calls.gat_backward_fused_saved(g, p, gt, pt, H, D, U, Vt, a_l, a_r, out, lse, out_masked, csum, dOut, dV, d_el, d_er, neg_slope, stream)):
+        return
     _check(load().hgnn_gat_backward_fused_saved(g.ref, p.handle, gt.ref, pt.handle, H, D, _ptr(U, torch.float16), _ld(U),
                                                 _ptr(Vt, torch.float16), _ld(Vt), _ptr(a_l, torch.float16),
                                                 _ptr(a_r, torch.float16), neg_slope, _ptr(out, torch.float16), _ld(out),
@@ -449,6 +477,8 @@ def hgnn_scale_rows(X: torch.Tensor, scale: torch.Tensor, out: torch.Tensor, F: 
 def hgnn_linear(X: torch.Tensor, W: torch.Tensor, Y: torch.Tensor, trans_w: bool = False, K: Optional[int] = None,
                 F: Optional[int] = None, stream=None) -> None:
     """Y = X.W (W is [K][F]) or X.W^T (trans_w, W is [F][K]).  A W of fewer than K rows: the other columns of X are zero padding."""
+    if _calls is not None and _done(_calls.linear(X, W, Y, trans_w, K, F, stream)):
+        return
     K = X.shape[1] if K is None else K
     F = (W.shape[0] if trans_w else W.shape[1]) if F is None else F
     n, KW = X.shape[0], K if trans_w else W.shape[0]
@@ -467,6 +497,8 @@ def hgnn_linear_wgrad_workspace(K: int, F: int) -> int:
 def hgnn_linear_wgrad(X: torch.Tensor, dY: torch.Tensor, dW: torch.Tensor, workspace: torch.Tensor, K: Optional[int] = None,
                       F: Optional[int] = None, stream=None) -> None:
     """dW (fp32 [K][F]) = X^T.dY; workspace is a device byte/float tensor of hgnn_linear_wgrad_workspace(K, F) bytes."""
+    if _calls is not None and _done(_calls.linear_wgrad(X, dY, dW, workspace, K, F, stream)):
+        return
     K = X.shape[1] if K is None else K
     F = dY.shape[1] if F is None else F
     _check(load().hgnn_linear_wgrad(X.shape[0], K, F, _ptr(X, torch.float16), _ld(X), _ptr(dY, torch.float16), _ld(dY),
@@ -481,6 +513,8 @@ def hgnn_gat_feature_grad_workspace(H: int, D: int) -> int:
 def hgnn_gat_feature_grad(H: int, D: int, dV: torch.Tensor, d_el: torch.Tensor, d_er: torch.Tensor, a_l: torch.Tensor,
                           a_r: torch.Tensor, hfeat: torch.Tensor, dh: torch.Tensor, da_l: torch.Tensor, da_r: torch.Tensor,
                           workspace: torch.Tensor, stream=None) -> None:
+    if _calls is not None and _done(_calls.gat_feature_grad(H, D, dV, d_el, d_er, a_l, a_r, hfeat, dh, da_l, da_r, workspace, stream)):
+        return
     _check(load().hgnn_gat_feature_grad(dV.shape[0], H, D, _ptr(dV, torch.float16), _ld(dV), _ptr(d_el, torch.float16),
                                         _ptr(d_er, torch.float16), _ptr(a_l, torch.float16), _ptr(a_r, torch.float16),
                                         _ptr(hfeat, torch.float16), _ld(hfeat), _ptr(dh, torch.float16), _ld(dh),
@@ -510,30 +544,40 @@ def hgnn_plan_vector_halves(p: Plan) -> int:
 def hgnn_sddmm(g: Csr, p: Optional[Plan], op: int, H: int, D: int, U: torch.Tensor, Vt: torch.Tensor,
                out: torch.Tensor, a_l: Optional[torch.Tensor] = None, a_r: Optional[torch.Tensor] = None,
                neg_slope: float = 0.2, stream=None) -> None:
+    if _calls is not None and _done(_calls.sddmm(g, p, op, H, D, U, Vt, out, a_l, a_r, neg_slope, stream)):
+        return
     _check(load().hgnn_sddmm(g.ref, None if p is None else p.handle, op, H, D, _ptr(U, torch.float16), _ld(U),
                              _ptr(Vt, torch.float16), _ld(Vt), _ptr(a_l, torch.float16), _ptr(a_r, torch.float16),
                              neg_slope, _ptr(out, torch.float16), _stream(stream)))
 
 
 def hgnn_edge_softmax(g: Csr, p: Optional[Plan], H: int, e: torch.Tensor, alpha: torch.Tensor, stream=None) -> None:
+    if _calls is not None and _done(_calls.edge_softmax(g, p, H, e, alpha, stream)):
+        return
     _check(load().hgnn_edge_softmax(g.ref, None if p is None else p.handle, H, _ptr(e, torch.float16),
                                     _ptr(alpha, torch.float16), _stream(stream)))
 
 
 def hgnn_edge_softmax_bwd(g: Csr, p: Optional[Plan], H: int, alpha: torch.Tensor, dalpha: torch.Tensor,
                           de: torch.Tensor, e: Optional[torch.Tensor] = None, neg_slope: float = 0.2, stream=None) -> None:
+    if _calls is not None and _done(_calls.edge_softmax_bwd(g, p, H, alpha, dalpha, de, e, neg_slope, stream)):
+        return
     _check(load().hgnn_edge_softmax_bwd(g.ref, None if p is None else p.handle, H, _ptr(alpha, torch.float16),
                                         _ptr(dalpha, torch.float16), _ptr(e, torch.float16), neg_slope,
                                         _ptr(de, torch.float16), _stream(stream)))
 
 
 def hgnn_edge_rowsum(g: Csr, p: Optional[Plan], H: int, t: torch.Tensor, out: torch.Tensor, stream=None) -> None:
+    if _calls is not None and _done(_calls.edge_rowsum(g, p, H, t, out, stream)):
+        return
     _check(load().hgnn_edge_rowsum(g.ref, None if p is None else p.handle, H, _ptr(t, torch.float16),
                                    _ptr(out, torch.float16), _stream(stream)))
 
 
 def hgnn_edge_colsum(g: Csr, p: Plan, H: int, t: torch.Tensor, out: torch.Tensor, stream=None) -> None:
     """out[j] = sum of t over the non-zeros of column j (needs column slices in the plan)."""
+    if _calls is not None and _done(_calls.edge_colsum(g, p, H, t, out, stream)):
+        return
     _check(load().hgnn_edge_colsum(g.ref, p.handle, H, _ptr(t, torch.float16), _ptr(out, torch.float16), _stream(stream)))
 
 

@@ -1,18 +1,34 @@
-"""Builds libhgnn.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libhgnn.so (HIP, gfx950 only) in-tree with hipcc, and with g++ the module that calls it from torch tensors."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libhgnn.so")
+CALLS_PATH = os.path.join(HERE, "_calls.so")
 SOURCES = ["memory.hip", "plan.hip", "tasks.hip", "blocked.hip", "groups.hip", "spmm.hip", "spmm_static.hip", "slices.hip", "sddmm.hip", "gat.hip", "gat_bwd.hip", "softmax.hip", "transpose.hip", "dense.hip"]
 # packed-fp32 instructions are switched off on purpose (the compiler must not emit v_pk_*_f32)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+def build_calls(verbose: bool = False) -> str:
+    """Compile csrc/calls.cpp (host code: Python arguments to the library's entry points)."""
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(base, "include"), "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return CALLS_PATH
 
 
 def build(verbose: bool = False) -> str:
@@ -31,6 +47,7 @@ def build(verbose: bool = False) -> str:
 
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
         objs = list(ex.map(one, SOURCES))
+    build_calls(verbose)
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs, "-L/opt/rocm/lib", "-lhsa-runtime64"])
     return LIB_PATH
 
