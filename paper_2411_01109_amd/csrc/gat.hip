@@ -355,7 +355,7 @@ constexpr int kShortPieces = 8;
 template <int L, bool SAVE>
 __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
 #pragma clang fp contract(off)
-  constexpr int G = kWave / L;
+  constexpr int G = kWave / L, kMany = kManyPieces * G;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
@@ -364,9 +364,16 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (i0 >= n_split) return;
+  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  __shared__ int4_t s_row[kWavesPerBlock * G];
+  __shared__ __align__(4) unsigned char s_bytes[kWavesPerBlock * L * sizeof(Soft<SAVE>)];
+  Soft<SAVE>* const s_soft = reinterpret_cast<Soft<SAVE>*>(s_bytes);
+  __shared__ int s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
+  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   const int alone = per_wave > 1 ? kShortPieces : 0;
   // merges the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](Soft<SAVE>& t, pos_t first, pos_t end, pos_t stride) {
@@ -388,19 +395,7 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
         if (k0 + u * stride < end) soft_merge_normalised<SAVE>(t, m[u], z[u], cp[u], o[u], om[u]);
     }
   };
-  if (q[2] > 0 && q[2] <= alone) {
-    Soft<SAVE> t;
-    take(t, q[1], q[1] + q[2], 1);
-    GatArgs b = a;
-    b.enter_block(q[3]);
-    if (active) row_store<SAVE>(b, q[0], f0, head, leader, t);
-  }
-  for (int j = 0; j < per_wave; ++j) {
-    const int n = __shfl(q[2], j * L);
-    if (n <= alone) continue;
-    const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
-    Soft<SAVE> t;
-    take(t, first + g, first + n, G);
+  auto across = [&](Soft<SAVE>& t) {  // merges those of the lane groups
     const float M = across_groups_max<L>(t.m);
     t.scale(M == -INFINITY ? 1.f : __expf(t.m - M));  // exp(-inf) = 0 drops a lane group without a piece
     t.m = M;
@@ -412,9 +407,42 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
 #pragma unroll
       for (int i = 0; i < 8; ++i) t.accm[i] = across_groups_sum<L>(t.accm[i]);
     }
+  };
+  if (q[2] > 0 && q[2] <= alone) {
+    Soft<SAVE> t;
+    take(t, q[1], q[1] + q[2], 1);
+    GatArgs b = a;
+    b.enter_block(q[3]);
+    if (active) row_store<SAVE>(b, q[0], f0, head, leader, t);
+  }
+  for (int j = 0; j < per_wave; ++j) {
+    const int n = __shfl(q[2], j * L);
+    if (n <= alone || n > kMany) continue;
+    const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
+    Soft<SAVE> t;
+    take(t, first + g, first + n, G);
+    across(t);
     GatArgs b = a;
     b.enter_block(bj);
     if (g == 0 && active) row_store<SAVE>(b, rj, f0, head, leader, t);
+  }
+  __syncthreads();
+  for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order), by all waves
+    const int4_t r = s_row[j];
+    Soft<SAVE> t;
+    take(t, pos_t(r[1]) + wave * G + g, pos_t(r[1]) + r[2], kWavesPerBlock * G);
+    across(t);
+    if (g == 0) s_soft[wave * L + l] = t;
+    __syncthreads();
+    if (wave == j % kWavesPerBlock && g == 0 && active) {
+      t = s_soft[l];
+#pragma unroll
+      for (int w = 1; w < kWavesPerBlock; ++w) soft_merge<SAVE>(t, s_soft[w * L + l]);
+      GatArgs b = a;
+      b.enter_block(r[3]);
+      row_store<SAVE>(b, r[0], f0, head, leader, t);
+    }
+    __syncthreads();
   }
 }
 

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
 // Follow-up kernel: sums the staged pieces of every row that has several, in order.
 template <int L, bool VEC>
 __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
-  constexpr int G = kWave / L;
+  constexpr int G = kWave / L, kMany = kManyPieces * G;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / L, l = lane % L;
   const int f0 = 8 * l;
@@ -220,9 +220,15 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   const int head = f0c / a.D;
   const bool leader = active && (f0 % a.D) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (i0 >= n_split) return;
+  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  __shared__ int4_t s_row[kWavesPerBlock * G];
+  __shared__ float s_sum[kWavesPerBlock][L][9];
+  __shared__ int s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
+  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   const int alone = per_wave > 1 ? 8 : 0;  // pieces that a lane group adds by itself
   // adds the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](float (&acc)[8], float& ds, pos_t first, pos_t end, pos_t stride) {
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   }
   for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= alone) continue;
+    if (n <= alone || n > kMany) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
@@ -272,6 +278,33 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
     GatBwdArgs b = a;
     b.enter_block(bj);
     if (g == 0 && active) bwd_row_store<VEC>(b, rj, f0, head, leader, acc, ds);
+  }
+  __syncthreads();
+  for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order), by all waves
+    const int4_t r = s_row[j];
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float ds = 0.f;
+    take(acc, ds, pos_t(r[1]) + wave * G + g, pos_t(r[1]) + r[2], kWavesPerBlock * G);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      const float v = across_groups_sum<L>(i < 8 ? acc[i] : ds);
+      if (g == 0) s_sum[wave][l][i] = v;
+    }
+    __syncthreads();
+    if (wave == j % kWavesPerBlock && g == 0 && active) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) v += s_sum[w][l][i];
+        if (i < 8) acc[i] = v;
+        else ds = v;
+      }
+      GatBwdArgs b = a;
+      b.enter_block(r[3]);
+      bwd_row_store<VEC>(b, r[0], f0, head, leader, acc, ds);
+    }
+    __syncthreads();
   }
 }
 

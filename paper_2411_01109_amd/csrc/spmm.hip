@@ -504,11 +504,10 @@ __global__ __launch_bounds__(kBlock) void spmm_scalar_kernel(SpmmArgs a) {
 
 constexpr int kFinishShort = 8;  // rows of at most this many pieces are summed by one lane group, longer ones by a wave
 
-// acc += staging rows k = first, first + STRIDE, ... <= last
-template <int STRIDE>
+// acc += staging rows k = first, first + STRIDE, ... <= last, U of them in flight at a time
+template <int STRIDE, int U = 4>
 __device__ __forceinline__ void pieces_accumulate(const SpmmArgs& a, int64_t first, int64_t last, int f0,
                                                   float (&acc)[8]) {
-  constexpr int U = 4;
   for (int64_t k = first; k <= last; k += STRIDE * U) {
     half8_t t[U];
 #pragma unroll
@@ -725,10 +724,9 @@ __global__ __launch_bounds__(kWave, L < 8 ? 5 : (LOOP ? 6 : (WM == 0 ? 8 : 7))) 
 // Pass 2 (section 5.2.3): adds the staged fp16 pieces of every row that has several (fp32, in order) and stores the row
 // once.  A wave owns one row, or G: then rows of at most kFinishShort pieces are summed by their own lane group, longer ones
 // by the whole wave (finish_rows_per_wave).
-template <int STRIDE>
+template <int STRIDE, int U = 4>
 __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t first, int64_t last, int f0, float (&acc)[8]) {
   const float* p = reinterpret_cast<const float*>(a.staging) + f0;
-  constexpr int U = 4;
   for (int64_t k = first; k <= last; k += STRIDE * U) {
     float4 lo[U], hi[U];
 #pragma unroll
@@ -752,7 +750,7 @@ __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t f
 template <int L, bool F32>
 __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split, int per_wave,
                                                                   const TaskTotals* __restrict__ totals) {
-  constexpr int G = kWave / L;
+  constexpr int G = kWave / L, kMany = kManyPieces * G;
   if (F32) {
     n_split = totals->n_split;
     per_wave = finish_rows_per_wave(n_split, totals->n_slots, G);
@@ -763,11 +761,17 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (i0 >= n_split) return;
+  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  __shared__ int4_t s_row[kWavesPerBlock * G];
+  __shared__ float s_sum[kWavesPerBlock][L][8];
+  __shared__ int s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   int4_t q = {0, 0, 0, 0};
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
   const int alone = per_wave > 1 ? kFinishShort : 0;
   half_t* const Y = a.Y;
+  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   if (q[2] > 0 && q[2] <= alone) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
@@ -777,7 +781,7 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   }
   for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= alone) continue;
+    if (n <= alone || n > kMany) continue;
     const int r = __shfl(q[0], j * L), first = __shfl(q[1], j * L), b = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
@@ -786,6 +790,31 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
     for (int i = 0; i < 8; ++i) acc[i] = across_groups_sum<L>(acc[i]);
     a.Y = Y + int64_t(b) * a.block_y_stride;
     if (g == 0 && active) store_row(a, r, f0, acc, 1.f);
+  }
+  __syncthreads();
+  for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order)
+    const int4_t m = s_row[j];
+    const int64_t first = m[1] + wave * G + g, last = int64_t(m[1]) + m[2] - 1;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (F32) pieces_accumulate32<kWavesPerBlock * G>(a, first, last, f0c, acc);
+    else pieces_accumulate<kWavesPerBlock * G, 8>(a, first, last, f0c, acc);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc[i] = across_groups_sum<L>(acc[i]);
+      if (g == 0) s_sum[wave][l][i] = acc[i];
+    }
+    __syncthreads();
+    if (wave == j % kWavesPerBlock && g == 0 && active) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) acc[i] += s_sum[w][l][i];
+      }
+      a.Y = Y + int64_t(m[3]) * a.block_y_stride;
+      store_row(a, m[0], f0, acc, 1.f);
+    }
+    __syncthreads();
   }
 }
 

@@ -220,6 +220,11 @@ __host__ __device__ inline int finish_rows_per_wave(int n_split, int n_slots, in
   return n_split <= 8192 || (n_split <= kFinishAlone && n_slots / many >= n_split) ? 1 : G;
 }
 
+// A row of more than this many pieces for each lane group of a wave is added by all waves of a workgroup of the follow-up kernels: the longest row
+// of a power law was most of a launch (62 M non-zeros x 128, 770 pieces: SpMM 43.8 -> 25 us; whole calls, 20 M x 128 326 -> 319.5, attention
+// forward 514 -> 505, backward 643 -> 633, 31 M x 64 296 -> 292.5, 456 -> 447, 678 -> 674; smaller ones the same).
+constexpr int kManyPieces = 32;
+
 // waves of work behind a view (G lane groups per wave)
 template <int G>
 __device__ __forceinline__ int task_waves(const TaskView& v) {

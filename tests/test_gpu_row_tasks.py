@@ -517,3 +517,54 @@ def test_many_rows_of_several_pieces(hgnn, dev, V, least, most, fewer, D):
         got.append([down(t).astype(np.float64) for t in (dV, d_el, d_er)])
     for a, b in zip(*got):  # one rounding of a row against one of each of its pieces beside it
         assert np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(a)
+
+
+# rows of about 32 pieces for each lane group of a wave, one more and several times as many, side by side: beyond them all waves of a workgroup add the
+# pieces; with a row for each wave and for each lane group; in the pass over the graph or over its transpose; a piece is one non-zero
+@pytest.mark.parametrize("flip", [False, True])
+@pytest.mark.parametrize("V,D", [(700, 8), (700, 32), (700, 64), (300, 256), (9000, 32)])
+def test_rows_of_many_pieces(hgnn, dev, V, D, flip):
+    print(f"rows of many pieces V={V} D={D} flip={flip}", flush=True)
+    H, r = 2, np.random.default_rng(V + D)
+    F = H * D
+    many = 32 * 64 * 8 // F
+    deg = r.integers(2, 4, size=V)
+    deg[40:47] = (many - 1, many, many + 1, 2 * many, 5 * many + 3, 4 * many, many + 1)
+    deg[200], deg[V - 1] = many + 5, 9 * many
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, V, size=d)) for d in deg]).astype(np.int32)
+    if flip:
+        rowptr, col = oracle.transpose(rowptr, col, V)[:2]
+    X, dO = f16(r.standard_normal((V, F))), f16(r.standard_normal((V, F)))
+    w = f16(r.standard_normal((col.size, H)))
+    a_l, a_r = f16(0.3 * r.standard_normal(F) / np.sqrt(D)), f16(0.3 * r.standard_normal(F) / np.sqrt(D))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    gt = hgnn.hgnn_transpose(g)
+    p, pt, pt1 = (hgnn.hgnn_plan_create(x, s, F, H, col_blocks=1) for x, s in ((g, 1), (gt, 256), (gt, 1)))
+    half = lambda *s: torch.full(s, 7.0, dtype=torch.float16, device=dev)  # noqa: E731
+    f32 = lambda *s: torch.full(s, 7.0, dtype=torch.float32, device=dev)  # noqa: E731
+    Xd, ald, ard, dOd = up(X, dev), up(a_l, dev), up(a_r, dev), up(dO, dev)
+    bits = []
+    for _ in range(2):  # the same bits on a second run
+        Y, out, outm, lse, csum, out0 = half(V, F), half(V, F), half(V, F), f32(V, H), f32(V, H), half(V, F)
+        hgnn.hgnn_spmm_discretized(p, g, up(w, dev), H, Xd, Y)
+        hgnn.hgnn_gat_forward_fused_save(g, p, H, D, Xd, Xd, ald, ard, out, lse, outm, csum)
+        hgnn.hgnn_gat_forward_fused(g, p, H, D, Xd, Xd, ald, ard, out0)
+        bits.append([down(t) for t in (Y, out, outm, lse, csum)])
+        assert np.array_equal(down(out0).view(np.uint16), bits[-1][1].view(np.uint16))
+    assert all(np.array_equal(a, b) for a, b in zip(*bits))
+    ref, sabs = oracle.spmm(rowptr, col, X, w=w, H=H, want_sabs=True)
+    compare("sum", down(Y), ref, sabs)
+    oref, lref, oabs, mref, cref = oracle.gat_forward(rowptr, col, X, X, a_l, a_r, H, slope=0.2, want_saved=True)
+    compare("out", down(out), oref, oabs)
+    compare("out_masked", down(outm), mref, oabs)
+    assert np.abs(down(csum) - cref).max() <= 2e-3 and np.abs(down(lse) - lref).max() <= 2e-3 + 1e-3 * np.abs(lref).max()
+    got = []
+    for q in (pt, pt1):
+        dV, d_el, d_er = half(V, F), half(V, H), half(V, H)
+        hgnn.hgnn_gat_backward_fused_saved(g, p, gt, q, H, D, Xd, Xd, ald, ard, out, lse, outm, csum, dOd, dV, d_el, d_er)
+        got.append([down(t).astype(np.float64) for t in (dV, d_el, d_er)])
+    for a, b in zip(*got):  # one rounding of a row against one of each of its pieces beside it
+        assert np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(a)
+    for q in (p, pt, pt1):
+        hgnn.hgnn_plan_destroy(q)
