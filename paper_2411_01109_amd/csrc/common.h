@@ -180,6 +180,10 @@ __device__ __forceinline__ int wave_sum(int v) {
   return int(r[0] + r[1]);
 }
 
+// The head of lane l of a row, LH lanes to a head, LH a power of two.  (A division is some 25 vector instructions, and a wave of the kernels over row
+// tasks has a few hundred in all.)
+__device__ __forceinline__ int head_of_lane(int l, int LH) { return l >> (31 - __builtin_clz(unsigned(LH))); }
+
 // All-reduce (sum) over the LH consecutive, LH-aligned lanes of a head; LH is a power of two.  After the
 // quads are summed, a mirror inside 8 (16) lanes pairs every lane with one of the other quad (half), whose
 // partial sum is the same on all its lanes; beyond a row of 16 lanes the exchange goes through ds_bpermute.

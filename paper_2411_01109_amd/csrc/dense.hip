@@ -34,8 +34,10 @@ struct LinearArgs {
   int KC;     // columns of X (rows of W) held in LDS at a time; a multiple of 32, and of the 128 columns of a group when K > KC
   int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
   int wvec;   // W may be read in 16-byte pieces, a workgroup's part at 32-bit offsets
+  uint32_t per_line;  // 2^31 / items on a line of the weight, rounded up
   int step_f, step_k;  // transposed: the waves of a workgroup / and % pieces of 64 columns
   int KW;     // rows of W that exist (not transposed): the others count as zero
+  int64_t nrb;  // blocks of rows, 16 * RT for each wave of a workgroup
 };
 
 // The weight tile W[kc .. kc+KC)[fc0 .. fc0+FC) into LDS in the order in which the products read it: fragment
@@ -57,12 +59,15 @@ __device__ __forceinline__ int linear_batch() { return TRANS ? linear_waves() * 
 template <bool TRANS>
 __device__ __forceinline__ int linear_w_items(const LinearArgs& a) { return a.FC / 8 * (TRANS ? (a.KC + 63) / 64 : a.KC / 8); }
 
+// item / items on a line of the weight (a division is a chain of some thirty instructions ahead of the first load)
+__device__ __forceinline__ int linear_line(const LinearArgs& a, int item) { return int(__umulhi(uint32_t(item) << 1, a.per_line)); }
+
 // W^T: f(u, features / 8, columns / 64), all scalar, for the u-th item of the wave in a batch
 template <class Fn>
 __device__ __forceinline__ void linear_each_item(const LinearArgs& a, int first, Fn&& f) {
   const int across = (a.KC + 63) / 64;
   const int item = __builtin_amdgcn_readfirstlane(first + int(threadIdx.x) / kWave);
-  int g = __builtin_amdgcn_readfirstlane(int(unsigned(item) / unsigned(across))), c = item - g * across;
+  int g = linear_line(a, item), c = item - g * across;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     if (8 * g >= a.FC) break;
@@ -97,7 +102,7 @@ __device__ __forceinline__ void linear_fetch_w(const LinearArgs& a, WeightBatch&
     });
   } else {
     const int F8 = a.FC / 8, idx = first + int(threadIdx.x);
-    w.k8 = int(unsigned(idx) / unsigned(F8)), w.f = 8 * (idx - w.k8 * F8);
+    w.k8 = linear_line(a, idx), w.f = 8 * (idx - w.k8 * F8);
     if (__builtin_amdgcn_readfirstlane(w.k8) >= a.KC / 8) return;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -209,7 +214,6 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
   const int nchunks = CHUNKED ? (a.K + a.KC - 1) / a.KC : 1;
   const int npass = CHUNKED ? 1 : (min(a.FC, a.F - fc0) + 16 * NT - 1) / (16 * NT);
   const bool keep = RT > 1 || a.K <= GK;  // one group holds the whole row: it serves all passes
-  const int64_t nrb = (a.n + int64_t(16 * RT) * wpw - 1) / (int64_t(16 * RT) * wpw);
   const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
   half8_t next[4];
   auto load_group = [&](int64_t rb, int k0) {
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
     linear_load_w<TRANS>(a, Wf, linear_batch<TRANS>(), 0, fc0);
     __syncthreads();
   }
-  for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
+  for (int64_t rb = blockIdx.x; rb < a.nrb; rb += gridDim.x) {
     half8_t cur[4];
     for (int pass = 0; pass < npass; ++pass) {
       float4_t acc[RT][NT];
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
           // what comes after this group: more of the row, the row again for the next pass, or the next row block
           if (kc + k0 + GK < a.K) load_group(rb, kc + k0 + GK);
           else if (pass + 1 < npass) { if (!keep) load_group(rb, 0); }
-          else if (rb + gridDim.x < nrb) load_group(rb + gridDim.x, 0);
+          else if (rb + gridDim.x < a.nrb) load_group(rb + gridDim.x, 0);
 #pragma unroll
           for (int u = 0; u < GS; ++u) {
             if (k0 + 32 * u < kn) {  // uniform
@@ -719,7 +723,7 @@ __global__ __launch_bounds__(kBlock) void gat_feature_grad_kernel(FeatGradArgs a
 constexpr int kLinearLds = 152 * 1024;  // most bytes of W a workgroup keeps (of the 160 KB of a compute unit)
 
 template <void (*KERNEL)(LinearArgs)>
-static hgnn_status launch_linear_kernel(LinearArgs a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+static hgnn_status launch_linear_kernel(LinearArgs a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
   // beyond 64 KB of dynamic LDS the runtime wants to be told, once per kernel and device
   static bool told[64] = {};
   if (lds > 65536) {
@@ -730,8 +734,11 @@ static hgnn_status launch_linear_kernel(LinearArgs a, dim3 grid, int threads, si
       if (dev >= 0 && dev < 64) told[dev] = true;
     }
   }
-  a.step_f = threads / kWave / ((a.KC + 63) / 64);
-  a.step_k = threads / kWave % ((a.KC + 63) / 64);
+  const int across = (a.KC + 63) / 64;
+  a.step_f = threads / kWave / across;
+  a.step_k = threads / kWave % across;
+  const uint32_t line = uint32_t(trans ? across : a.FC / 8);
+  a.per_line = ((uint32_t(1) << 31) + line - 1) / line;
   KERNEL<<<grid, threads, lds, s>>>(a);
   HGNN_LAUNCH_CHECK("linear_kernel");
   return HGNN_OK;
@@ -739,14 +746,14 @@ static hgnn_status launch_linear_kernel(LinearArgs a, dim3 grid, int threads, si
 
 template <int NT, int RT, bool CHUNKED>
 static hgnn_status launch_linear(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (trans) return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true>>(a, grid, threads, lds, s);
-  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false>>(a, grid, threads, lds, s);
+  if (trans) return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true>>(a, true, grid, threads, lds, s);
+  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false>>(a, false, grid, threads, lds, s);
 }
 
 template <int NT, int KP>
 static hgnn_status launch_linear_split(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (trans) return launch_linear_kernel<linear_split_kernel<NT, KP, true>>(a, grid, threads, lds, s);
-  return launch_linear_kernel<linear_split_kernel<NT, KP, false>>(a, grid, threads, lds, s);
+  if (trans) return launch_linear_kernel<linear_split_kernel<NT, KP, true>>(a, true, grid, threads, lds, s);
+  return launch_linear_kernel<linear_split_kernel<NT, KP, false>>(a, false, grid, threads, lds, s);
 }
 
 template <int KP>
@@ -783,7 +790,7 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   HGNN_REQUIRE(K % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y), HGNN_EUNSUPPORTED,
                "%s: needs K %% 8 == 0, ldx %% 8 == 0, ldy %% 8 == 0 and 16-byte aligned X, Y (pad with zeros)", who);
   LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw,
-               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, 0, 0, KW};
+               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, 0, 0, 0, KW, 0};
   const int k32 = (K + 31) / 32 * 32, f32 = (F + 31) / 32 * 32;
   // short rows: several row tiles per wave, where that still leaves four waves for every compute unit
   const int RT = n < int64_t(32) * 4 * kCus || K > 64 ? 1 : (K > 32 || n < int64_t(64) * 4 * kCus ? 2 : 4);
@@ -842,6 +849,7 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   }
   const int fy = int(ceil_div(F, a.FC));
   const int64_t nrb = ceil_div(tiles, wpw);
+  a.nrb = nrb;
   // persistent workgroups, as many as fit the chip at once, each with the same number of row blocks (to one)
   const int64_t resident = int64_t(kCus) * std::max<int64_t>(1, std::min<int64_t>(waves / wpw, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
   const int64_t per = ceil_div(nrb, std::max<int64_t>(1, resident / fy));

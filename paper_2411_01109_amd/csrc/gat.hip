@@ -209,9 +209,9 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int head = f0c / a.D;
-  const bool leader = active && (f0 % a.D) == 0;  // the lane that writes its head's scalars
-  const int LH = a.D / 8;                         // lanes per head, a power of two
+  const int LH = a.D / 8;  // lanes per head, a power of two
+  const int head = head_of_lane(active ? l : 0, LH);
+  const bool leader = active && (l & (LH - 1)) == 0;  // the lane that writes its head's scalars
   const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   a.enter_block(w.block);
   if (w.z1 > w.z0) {
@@ -361,8 +361,8 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int head = f0c / a.D;
-  const bool leader = active && (f0 % a.D) == 0;
+  const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
+  const bool leader = active && (l & (LH - 1)) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
   if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
   __shared__ int4_t s_row[kWavesPerBlock * G];
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kBlock) void gat_block_merge_kernel(GatArgs a, GatB
   const int f0 = 8 * l;
   const int64_t r = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G + g;
   if (r >= a.nrows || f0 >= a.F) return;
-  const int head = f0 / a.D;
+  const int LH = a.D / 8, head = head_of_lane(l, LH);
   Soft<SAVE> t;
   for (int b = 0; b < q.nb; ++b) {
     const int64_t pr = int64_t(b) * a.nrows + r;
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kBlock) void gat_block_merge_kernel(GatArgs a, GatB
     const float* mz = q.mz + b * q.mz_stride + (r * a.H + head) * 2;
     soft_merge_normalised<SAVE>(t, mz[0], mz[1], cp, o, om);
   }
-  row_store<SAVE>(a, r, f0, head, (f0 % a.D) == 0, t);
+  row_store<SAVE>(a, r, f0, head, (l & (LH - 1)) == 0, t);
 }
 
 template <int L, bool NEAR, bool SAVE>

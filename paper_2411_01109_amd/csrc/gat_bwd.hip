@@ -94,9 +94,8 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int head = f0c / a.D;
-  const bool leader = active && (f0 % a.D) == 0;
-  const int LH = a.D / 8;
+  const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
+  const bool leader = active && (l & (LH - 1)) == 0;
   const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   a.enter_block(w.block);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum alpha * x          (VEC)
@@ -217,8 +216,8 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int head = f0c / a.D;
-  const bool leader = active && (f0 % a.D) == 0;
+  const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
+  const bool leader = active && (l & (LH - 1)) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
   if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
   __shared__ int4_t s_row[kWavesPerBlock * G];
@@ -319,7 +318,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_block_sum_kernel(GatBwdArgs a,
   const int f0 = 8 * l;
   const int64_t r = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * G + g;
   if (r >= a.nrows || f0 >= a.F) return;
-  const int head = f0 / a.D;
+  const int LH = a.D / 8, head = head_of_lane(l, LH);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float ds = 0.f;
   for (int b = 0; b < nb; ++b) {
@@ -330,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_block_sum_kernel(GatBwdArgs a,
     }
     ds += part_ds[b * ds_stride + r * a.H + head];
   }
-  bwd_row_store<VEC>(a, r, f0, head, (f0 % a.D) == 0, acc, ds);
+  bwd_row_store<VEC>(a, r, f0, head, (l & (LH - 1)) == 0, acc, ds);
 }
 
 // Everything the passes need of single vertices, in one launch: er[j,h] = a_r[h].Vt[j,h] for every source vertex, and for every
@@ -371,8 +370,8 @@ __global__ __launch_bounds__(kBlock) void gat_vtab_kernel(VertexArgs a) {
   er = head_sum1(er, LH);
   p = head_sum1(p, LH);
   if (a.outm) pm = head_sum1(pm, LH);
-  if ((l % LH) == 0) {
-    const int64_t k = v * a.H + l / LH;
+  if ((l & (LH - 1)) == 0) {
+    const int64_t k = v * a.H + head_of_lane(l, LH);
     if (src) a.er[k] = er;
     if (dst) {
       a.vtab[k] = make_float4(el, a.lse[k], p, 0.f);

@@ -53,8 +53,8 @@ __global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(Sddm
   const int f0 = VW * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int head = MASK ? 0 : f0c / a.D;
   const int LH = MASK ? L : a.D / VW;       // lanes per head (power of two)
+  const int head = MASK ? 0 : head_of_lane(active ? l : 0, LH);
   const int nvalid = active ? a.F - f0 : 0; // MASK: elements of this lane's vector that exist
   auto masked = [&](hv_t x) -> hv_t {
     if (MASK) {
@@ -232,9 +232,10 @@ __global__ __launch_bounds__(kBlock) void vertex_proj_kernel(ProjSide u, ProjSid
     p += __shfl_xor(p, off);
     q += __shfl_xor(q, off);
   }
-  if (l % LH != 0) return;
-  if (inu) u.proj[v * H + l / LH] = p;
-  if (inw) w.proj[v * H + l / LH] = q;
+  if ((l & (LH - 1)) != 0) return;
+  const int head = head_of_lane(l, LH);
+  if (inu) u.proj[v * H + head] = p;
+  if (inw) w.proj[v * H + head] = q;
 }
 
 // step 2, one plan segment per wave: e[k,h] = LeakyReLU(el[row k, h] + er[col k, h]); row ids

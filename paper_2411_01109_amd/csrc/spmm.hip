@@ -28,6 +28,7 @@ struct SpmmArgs {
   int64_t nnz;
   int nrows;
   int F, H, D;
+  uint32_t per_d;  // 2^32 / D, rounded up: f * per_d >> 32 is the head of feature f < 512
   int reduce;
   float one;  // 1.0f
   int rows_per_wave;  // spmm_row_kernel: rows a wave owns, 1 or 64/L
@@ -585,7 +586,7 @@ __device__ __forceinline__ void spmm_task(SpmmArgs a, const TaskView& v, int nco
     return;
   }
   const int H = HV > 0 ? HV : a.H;
-  const int head = HV == 1 ? 0 : f0c / a.D;
+  const int head = HV == 1 ? 0 : int(__umulhi(uint32_t(f0c), a.per_d));
   int* const s_hnd = reinterpret_cast<int*>(smem) + g * Rd::PITCH;
   factor_t* const s_val = reinterpret_cast<factor_t*>(smem + Lds::kHandles) + g * Lds::pitch(H);
   const RowTable<NEAR> table(a.X, ncols, a.ldx, f0c);
@@ -1085,6 +1086,7 @@ static SpmmArgs make_args(const hgnn_csr* g, const hgnn_half* w, int H, const hg
   a.F = F;
   a.H = w ? H : 1;  // without edge values the head structure is irrelevant
   a.D = F / a.H;
+  a.per_d = a.D > 1 ? uint32_t(((uint64_t(1) << 32) + uint32_t(a.D) - 1) / uint32_t(a.D)) : 0;  // (rows of tasks have D = F or a multiple of 8)
   a.reduce = int(op);
   a.one = 1.0f;
   a.agg_coef = 1.0f;
@@ -1759,6 +1761,7 @@ hgnn_status hgnn_spmm_discretized_fused(const hgnn_plan* p, const hgnn_csr* g, c
     if (a.col_scale && !edge_val) {  // the per-edge factor is the column scale alone; heads are irrelevant
       a.H = 1;
       a.D = F;
+      a.per_d = 0;
     }
   }
   // blocks that the automatic rule chose (for max_F) are used when the table of this call is beyond an L2 too

@@ -35,7 +35,7 @@ struct TaskView {
   // Consecutive workgroups go to the eight XCDs in turn.  The waves of lane-group pieces are numbered so that `chunk`
   // consecutive ones run on the same XCD: the rows of a window share lines of the column array and of edge tensors, and each
   // of eight L2s would fetch them (62 M non-zeros, rows of 26 on average, 128 features: 1.82 -> 1.69 ms with chunks of 128).
-  int chunk;
+  int chunk;  // a power of two
   int first_wave[kMaxTaskBlocks + 1];  // for the lane groups of this launch: waves before each block, then all of them
   // Whole-wave pieces and waves of lane-group pieces go through the rows side by side (comes_back() below): of the groups of eight
   // waves (one per XCD) of a block every 2^32 / mix-th takes the former.  mix = 0: one kind after the other.
@@ -305,9 +305,9 @@ __device__ __forceinline__ TaskWave task_enter(const TaskView& v, int wid, int g
   } else {
     i -= int(before * 8);
     if (i < gw) {
-      const int panel = 8 * v.chunk, full = gw / panel * panel;
+      const int panel = 8 * v.chunk, full = gw & -panel;
       if (i < full) {
-        const int p = i / panel * panel, j = i - p;
+        const int p = i & -panel, j = i - p;
         i = p + (j & 7) * v.chunk + (j >> 3);
       }
       const pos_t k = pos_t(i) * G + g;
