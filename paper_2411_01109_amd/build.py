@@ -22,7 +22,9 @@ def build_calls(verbose: bool = False) -> str:
     import torch
 
     base = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    # NDEBUG: else the headers bring a thread-local counter along, and behind a library with thread-local memory that is loaded late and never uses it
+    # every access to such memory in the runtime takes glibc's slow way (2 us more for a set-up call)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-DNDEBUG", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(base, "include"), "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
            os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:

@@ -152,3 +152,15 @@ def test_nothing_is_called_for_what_is_not_plain(hgnn):
         calls.bind(1)
     with pytest.raises(KeyError):
         calls.bind({}, None, None)
+
+
+def test_no_thread_local_memory():
+    """A library with thread-local memory that is loaded late and does not use it slows every access to such memory in the runtime down (glibc's slow
+    way for modules older than the newest one): set-up calls took 2 us more."""
+    with open(binding.CALLS_PATH, "rb") as fh:
+        head = fh.read(64)
+        assert head[:5] == b"\x7fELF\x02"
+        at, size, n = int.from_bytes(head[32:40], "little"), int.from_bytes(head[54:56], "little"), int.from_bytes(head[56:58], "little")
+        fh.seek(at)
+        kinds = [int.from_bytes(fh.read(size)[:4], "little") for _ in range(n)]
+    assert 1 in kinds and 7 not in kinds  # PT_LOAD, PT_TLS
