@@ -355,9 +355,16 @@ __global__ __launch_bounds__(kBlock) void sort_merge_kernel(SortPass p, int last
 //   100 000 words of 20 000 vertices    79 /  65 /  58;  50 / 43 / 39        700 000 of 50 000    98 /  93 /  98;  59 / 55 / 59
 //   300 000 of 30 000                   88 /  79 /  78;  53 / 49 / 48      1 040 000 of 50 000   108 /  99 / 103;  63 / 59 / 62
 //   520 000 of 50 000                   90 /  89 /  84;  54 / 53 / 51      1 200 000 of 100 000  109 / 111 / 119;  66 / 66 / 73
+// Six where they give a compute unit one, or, of those that have some two either way, no more than two: their workgroups are in flight together.
+// eight / six / four:
+//   1.1 M of 100 000   109 / 105 / 112;  65 /  63 /  67     2.3 M of 300 000   175 / 157 / 167; 118 / 109 / 116     2 M of 200 000     124 / 127 / 118;  75 /  79 /  75
+//   1.3 M of 300 000   134 / 128 / 137;  93 /  90 /  96     2.9 M of 200 000   147 / 135 / 147;  88 /  82 /  91     4 M of 262 144     155 / 165 / 173;  95 / 104 / 108
+//   1.57 M of 100 000  121 / 114 / 120;  71 /  68 /  72     3.14 M of 100 000  148 / 136 / 154;  88 /  83 /  92     5.5 M of 262 144   194 / 208 / 220; 119 / 126 / 135
 inline int sort_items(int64_t n) {
   constexpr int64_t kTiles = 256;  // compute units
-  return n <= kTiles * 2 * kSortThreads ? 2 : (n <= kTiles * 4 * kSortThreads ? 4 : kSortPer);
+  if (n <= kTiles * 2 * kSortThreads) return 2;
+  if (n <= kTiles * 4 * kSortThreads) return 4;
+  return n <= kTiles * 6 * kSortThreads || (n > kTiles * 8 * kSortThreads && n <= kTiles * 12 * kSortThreads) ? 6 : kSortPer;
 }
 
 inline size_t sort_scratch_bytes(int64_t n) {
@@ -418,6 +425,7 @@ static uint64_t* sort_words(const Source& src, int64_t n, int first, int last, u
   const int per = sort_items(n);
   if (per == 2) passes(std::integral_constant<int, 2>());
   else if (per == 4) passes(std::integral_constant<int, 4>());
+  else if (per == 6) passes(std::integral_constant<int, 6>());
   else passes(std::integral_constant<int, kSortPer>());
   return in;
 }

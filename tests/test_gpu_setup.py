@@ -63,6 +63,12 @@ def test_sort_items_of_a_thread(hgnn, dev, V, E):
     test_sort_tiles(hgnn, dev, V, E)
 
 
+@pytest.mark.parametrize("V,E", [(70000, 256 * 6144), (70000, 256 * 6144 + 1), (511, 256 * 8192), (511, 256 * 8192 + 1), (70000, 512 * 6144),
+                                 (300000, 512 * 6144 - 6143), (20, 512 * 6144 + 1)])
+def test_sort_six_items_of_a_thread(hgnn, dev, V, E):
+    test_sort_tiles(hgnn, dev, V, E)
+
+
 @pytest.mark.parametrize("E", [3072 * 8192, 3072 * 8192 + 1])
 def test_many_tiles(hgnn, dev, E):
     """The counts of up to 3072 tiles are scanned in one, of more in shares."""
