@@ -78,9 +78,12 @@ __device__ __forceinline__ void linear_each_item(const LinearArgs& a, int first,
   }
 }
 
-// where lane 16q + i of a read finds its 16 bytes in the kilobyte of a fragment: such that the writes of either form, 16 lanes of four features and
-// four q at a time, go to different banks, too
-__device__ __forceinline__ int linear_slot(int i, int q) { return 16 * q + (((i + 4 * q) & 15) ^ q); }
+// Where lane 16q + i of a read finds its 16 bytes in the kilobyte of a fragment: such that the writes of either form, 16 lanes of four features and
+// four q at a time, go to different banks, and so do the lanes of a read, which takes i of 0-3 and 12-15 of an even q together with 4-11 of the odd one
+// behind it (with all lanes of a q turned alike reads met on a bank about once each: 19 717 rows of 504 -> 64 6.8 -> 6.3 us, 140 000 of 1280 -> 128 128.4 ->
+// 126.8).  Places that differ by tile and step as well take the rest of the writes' conflicts away, but each needs an address register of its own:
+// 131 072 of 128 -> 128 14.8 -> 16.1.
+__device__ __forceinline__ int linear_slot(int i, int q) { return 16 * q + (i ^ (13 * q & 15)); }
 
 // Whether 16-byte pieces can be read at 32-bit offsets; else linear_put_w reads all of the weight element by element with the first batch.
 template <bool TRANS>
