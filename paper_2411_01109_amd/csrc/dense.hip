@@ -33,7 +33,7 @@ struct LinearArgs {
   int64_t ldy;
   int KC;     // columns of X (rows of W) held in LDS at a time; a multiple of 32, and of the 128 columns of a group when K > KC
   int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
-  int wvec;   // W may be read in 16-byte pieces, a workgroup's part at 32-bit offsets
+  int near;   // ANY: a workgroup's part of W lies within 32-bit offsets
   uint32_t per_line;  // 2^31 / items on a line of the weight, rounded up
   int step_f, step_k;  // transposed: the waves of a workgroup / and % pieces of 64 columns
   int KW;     // rows of W that exist (not transposed): the others count as zero
@@ -85,55 +85,64 @@ __device__ __forceinline__ void linear_each_item(const LinearArgs& a, int first,
 // 131 072 of 128 -> 128 14.8 -> 16.1.
 __device__ __forceinline__ int linear_slot(int i, int q) { return 16 * q + (i ^ (13 * q & 15)); }
 
-// Whether 16-byte pieces can be read at 32-bit offsets; else linear_put_w reads all of the weight element by element with the first batch.
-template <bool TRANS>
-__device__ __forceinline__ bool linear_batched(const LinearArgs& a, int kc, int fc0) {
-  return a.wvec && (TRANS || (min(a.FC, a.F - fc0) % 8 == 0 && a.KW > kc));
+// ANY = false: lines of whole pieces on 16-byte boundaries, at 32-bit offsets.  ANY: pieces that begin at any element, and of W [K][F] the last one of a line is
+// its last eight features, some of which the piece before it holds, too.  Such a weight read by elements, all of it, cost up to two thirds of a call; us, by
+// elements / so: 4096 rows of 64 -> 42, lines of 48 10.4 / 3.7, 3000 of 2504 -> 41, lines of 48 105 / 33, 70 000 of 2504 -> 100, lines of 104 300 / 141, 4096 of 64 ->
+// 41 by W^T, lines of 67 8.6 / 4.0.  Kernels of their own, because the code costs the others registers (140 000 of 1280 -> 128 by W^T 121 / 140).
+// Offsets beyond 32 bits, or fewer than eight features: all by elements, with the first batch (1000 of 128 -> 7 3.5).
+template <bool TRANS, bool ANY>
+__device__ __forceinline__ bool linear_batched(const LinearArgs& a, int fc0) {
+  return !ANY || (a.near && (TRANS || min(a.FC, a.F - fc0) >= 8));
 }
 
-// Positions outside the weight are read inside it, without branches between the loads; linear_put_w puts zeros in their place.
-template <bool TRANS>
+// Positions outside the weight are read inside it, without branches between the loads; linear_put_w puts zeros in the place of rows (columns of W^T) that
+// do not exist.  What stands in the place of features that do not exist, if anything, meets only results that are not stored.
+template <bool TRANS, bool ANY>
 __device__ __forceinline__ void linear_fetch_w(const LinearArgs& a, WeightBatch& w, int first, int kc, int fc0) {
   const int kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0), lane = threadIdx.x & (kWave - 1);
   const char* const W = reinterpret_cast<const char*>(a.W + fc0 * (TRANS ? a.ldw : 1) + kc * (TRANS ? 1 : a.ldw));
   const uint32_t pitch = uint32_t(a.ldw) * 2u;
-  if (!linear_batched<TRANS>(a, kc, fc0)) return;
+  if (!linear_batched<TRANS, ANY>(a, fc0)) return;
   if constexpr (TRANS) {
     linear_each_item(a, first, [&](int u, int g, int c) {
       const uint32_t at = uint32_t(min(8 * g + (lane >> 3), fn - 1)) * pitch + uint32_t(min(64 * c + 8 * (lane & 7), kn - 8)) * 2u;
-      __builtin_memcpy(w.v + 4 * u, __builtin_assume_aligned(W + at, 16), 16);
+      __builtin_memcpy(w.v + 4 * u, __builtin_assume_aligned(W + at, ANY ? 2 : 16), 16);
     });
   } else {
     const int F8 = a.FC / 8, idx = first + int(threadIdx.x);
     w.k8 = linear_line(a, idx), w.f = 8 * (idx - w.k8 * F8);
-    if (__builtin_amdgcn_readfirstlane(w.k8) >= a.KC / 8) return;
+    if (__builtin_amdgcn_readfirstlane(w.k8) >= a.KC / 8 || a.KW <= kc) return;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t at = uint32_t(min(8 * w.k8 + j, a.KW - kc - 1)) * pitch + uint32_t(min(w.f, fn - 8)) * 2u;
-      __builtin_memcpy(w.v + 4 * j, __builtin_assume_aligned(W + at, 16), 16);
+      __builtin_memcpy(w.v + 4 * j, __builtin_assume_aligned(W + at, ANY ? 2 : 16), 16);
     }
   }
 }
 
-template <bool TRANS>
+template <bool TRANS, bool ANY>
 __device__ __forceinline__ void linear_put_w(const LinearArgs& a, const WeightBatch& w, int first, int kc, int fc0, half_t* __restrict__ Wf) {
   typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
   const int KS = a.KC / 32, kn = min(a.KC, a.K - kc), fn = min(a.FC, a.F - fc0), lane = threadIdx.x & (kWave - 1);
   uint4_t* const out = reinterpret_cast<uint4_t*>(Wf);
   const auto place = [&](int f, int k8) { return out + ((2 * (f >> 5) + ((f >> 2) & 1)) * KS + (k8 >> 2)) * kWave + linear_slot(4 * ((f >> 3) & 3) + (f & 3), k8 & 3); };
-  if (!linear_batched<TRANS>(a, kc, fc0)) {
+  if (!linear_batched<TRANS, ANY>(a, fc0)) {
     const int64_t sf = TRANS ? a.ldw : 1, sk = TRANS ? 1 : a.ldw;
     const int rows = TRANS ? kn : min(kn, a.KW - kc);
-    if (first == 0)
-      for (int idx = threadIdx.x; idx < a.FC * (a.KC / 8); idx += blockDim.x) {
-        const int k8 = int(unsigned(idx) / unsigned(a.FC)), f = idx - k8 * a.FC;
+    if (first != 0) return;
+    for (int idx = threadIdx.x; idx < fn * (a.KC / 8); idx += blockDim.x) {
+      const int k8 = int(unsigned(idx) / unsigned(fn)), f = idx - k8 * fn;
+      half8_t v = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (8 * k8 < rows) {
         const half_t* const src = a.W + (fc0 + f) * sf + (kc + 8 * k8) * sk;
-        half8_t v = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = src[min(j, rows - 1 - 8 * k8) * sk];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          if (f < fn && 8 * k8 + j < rows) v[j] = src[j * sk];
-        *place(f, k8) = __builtin_bit_cast(uint4_t, v);
+          if (8 * k8 + j >= rows) v[j] = half_t(0);
       }
+      *place(f, k8) = __builtin_bit_cast(uint4_t, v);
+    }
     return;
   }
   if constexpr (TRANS) {
@@ -149,26 +158,33 @@ __device__ __forceinline__ void linear_put_w(const LinearArgs& a, const WeightBa
     const int f = w.f, k8 = w.k8;
     if (8 * k8 >= a.KC) return;
     const int rows = f < fn ? min(kn, a.KW - kc) - 8 * k8 : 0;
+    auto put = [&](int f) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      uint4_t v;
+      for (int c = 0; c < 8; ++c) {
+        uint4_t v;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t even = 2 * j < rows ? w.v[8 * j + c / 2] : 0, odd = 2 * j + 1 < rows ? w.v[8 * j + 4 + c / 2] : 0;
-        v[j] = __builtin_amdgcn_perm(odd, even, c & 1 ? 0x07060302u : 0x05040100u);
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t even = 2 * j < rows ? w.v[8 * j + c / 2] : 0, odd = 2 * j + 1 < rows ? w.v[8 * j + 4 + c / 2] : 0;
+          v[j] = __builtin_amdgcn_perm(odd, even, c & 1 ? 0x07060302u : 0x05040100u);
+        }
+        *place(f + c, k8) = v;
       }
-      *place(f + c, k8) = v;
+    };
+    if (!ANY) {
+      put(f);
+    } else {
+      if (f < fn) put(min(f, fn - 8));
     }
   }
 }
 
 // all items from `first` on
-template <bool TRANS>
+template <bool TRANS, bool ANY>
 __device__ __forceinline__ void linear_load_w(const LinearArgs& a, half_t* __restrict__ Wf, int first, int kc, int fc0) {
   for (; first < linear_w_items<TRANS>(a); first += linear_batch<TRANS>()) {
     WeightBatch w;
-    linear_fetch_w<TRANS>(a, w, first, kc, fc0);
-    linear_put_w<TRANS>(a, w, first, kc, fc0, Wf);
+    linear_fetch_w<TRANS, ANY>(a, w, first, kc, fc0);
+    linear_put_w<TRANS, ANY>(a, w, first, kc, fc0, Wf);
   }
 }
 
@@ -204,7 +220,7 @@ __device__ __forceinline__ void linear_store(const LinearArgs& a, int64_t row, i
 // registers are better spent on the loads in flight.  RT > 1 is for rows that do not fill a group: with K <= 64 (32) a group
 // takes two (four) row tiles, so that as many bytes are in flight as with long rows.
 // CHUNKED: the weights of 128 features do not fit; the columns come in chunks, a chunk of W once per row block.
-template <int NT, int RT, bool CHUNKED, bool TRANS>
+template <int NT, int RT, bool CHUNKED, bool TRANS, bool ANY>
 __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
   constexpr int GS = 4 / RT;    // 32-column steps in a group of X loads
   constexpr int GK = 32 * GS;   // columns of a group
@@ -234,10 +250,10 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
     load_group(blockIdx.x, 0);
   } else {
     WeightBatch w;
-    linear_fetch_w<TRANS>(a, w, 0, 0, fc0);
+    linear_fetch_w<TRANS, ANY>(a, w, 0, 0, fc0);
     load_group(blockIdx.x, 0);
-    linear_put_w<TRANS>(a, w, 0, 0, fc0, Wf);
-    linear_load_w<TRANS>(a, Wf, linear_batch<TRANS>(), 0, fc0);
+    linear_put_w<TRANS, ANY>(a, w, 0, 0, fc0, Wf);
+    linear_load_w<TRANS, ANY>(a, Wf, linear_batch<TRANS>(), 0, fc0);
     __syncthreads();
   }
   for (int64_t rb = blockIdx.x; rb < a.nrb; rb += gridDim.x) {
@@ -253,7 +269,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
         const int kn = CHUNKED ? min(a.KC, a.K - kc) : a.K;
         if (CHUNKED) {  // trip counts are uniform over the workgroup
           __syncthreads();
-          linear_load_w<TRANS>(a, Wf, 0, kc, fc0);
+          linear_load_w<TRANS, ANY>(a, Wf, 0, kc, fc0);
           __syncthreads();
         }
         for (int k0 = 0; k0 < kn; k0 += GK) {
@@ -319,7 +335,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
 // weight asked for ahead of X, calls in a row from a graph, 6.6 -> 6.3 and 5.4 -> 4.6, 12 000 x 504 -> 128 by W^T 8.5 -> 9.1.
 constexpr int kSplitSteps = 10;
 
-template <int NT, int KP, bool TRANS>
+template <int NT, int KP, bool TRANS, bool ANY>
 __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   half_t* Wf = reinterpret_cast<half_t*>(lds_raw);
@@ -330,7 +346,7 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
   const int64_t row = (int64_t(blockIdx.x) * tiles + tile) * 16 + i;
   const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
   WeightBatch w0;
-  linear_fetch_w<TRANS>(a, w0, 0, 0, 0);
+  linear_fetch_w<TRANS, ANY>(a, w0, 0, 0, 0);
   half8_t x[kSplitSteps];
 #pragma unroll
   for (int u = 0; u < kSplitSteps; ++u) {
@@ -338,8 +354,8 @@ __global__ __launch_bounds__(1024) void linear_split_kernel(LinearArgs a) {
     const int k = 32 * (s0 + u) + 8 * q;
     if (u < sn && row < a.n && k < a.K) x[u] = *reinterpret_cast<const half8_t*>(a.X + row * a.ldx + k);
   }
-  linear_put_w<TRANS>(a, w0, 0, 0, 0, Wf);
-  linear_load_w<TRANS>(a, Wf, linear_batch<TRANS>(), 0, 0);
+  linear_put_w<TRANS, ANY>(a, w0, 0, 0, 0, Wf);
+  linear_load_w<TRANS, ANY>(a, Wf, linear_batch<TRANS>(), 0, 0);
   __syncthreads();
   float4_t acc[NT];
 #pragma unroll
@@ -747,23 +763,33 @@ static hgnn_status launch_linear_kernel(LinearArgs a, bool trans, dim3 grid, int
   return HGNN_OK;
 }
 
+enum WeightForm { kWhole, kAny, kWholeT, kAnyT };  // linear_batched
+
 template <int NT, int RT, bool CHUNKED>
-static hgnn_status launch_linear(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (trans) return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true>>(a, true, grid, threads, lds, s);
-  return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false>>(a, false, grid, threads, lds, s);
+static hgnn_status launch_linear(const LinearArgs& a, WeightForm form, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  switch (form) {
+    case kWhole: return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false, false>>(a, false, grid, threads, lds, s);
+    case kAny: return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, false, true>>(a, false, grid, threads, lds, s);
+    case kWholeT: return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true, false>>(a, true, grid, threads, lds, s);
+    default: return launch_linear_kernel<linear_kernel<NT, RT, CHUNKED, true, true>>(a, true, grid, threads, lds, s);
+  }
 }
 
 template <int NT, int KP>
-static hgnn_status launch_linear_split(const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (trans) return launch_linear_kernel<linear_split_kernel<NT, KP, true>>(a, true, grid, threads, lds, s);
-  return launch_linear_kernel<linear_split_kernel<NT, KP, false>>(a, false, grid, threads, lds, s);
+static hgnn_status launch_linear_split(const LinearArgs& a, WeightForm form, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  switch (form) {
+    case kWhole: return launch_linear_kernel<linear_split_kernel<NT, KP, false, false>>(a, false, grid, threads, lds, s);
+    case kAny: return launch_linear_kernel<linear_split_kernel<NT, KP, false, true>>(a, false, grid, threads, lds, s);
+    case kWholeT: return launch_linear_kernel<linear_split_kernel<NT, KP, true, false>>(a, true, grid, threads, lds, s);
+    default: return launch_linear_kernel<linear_split_kernel<NT, KP, true, true>>(a, true, grid, threads, lds, s);
+  }
 }
 
 template <int KP>
-static hgnn_status launch_linear_split(int nt, const LinearArgs& a, bool trans, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (nt == 2) return launch_linear_split<2, KP>(a, trans, grid, threads, lds, s);
-  if (nt == 4) return launch_linear_split<4, KP>(a, trans, grid, threads, lds, s);
-  return launch_linear_split<8, KP>(a, trans, grid, threads, lds, s);
+static hgnn_status launch_linear_split(int nt, const LinearArgs& a, WeightForm form, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (nt == 2) return launch_linear_split<2, KP>(a, form, grid, threads, lds, s);
+  if (nt == 4) return launch_linear_split<4, KP>(a, form, grid, threads, lds, s);
+  return launch_linear_split<8, KP>(a, form, grid, threads, lds, s);
 }
 
 static int wgrad_parts(int K, int F) {
@@ -814,7 +840,9 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
       a.KC = kLinearLds / (a.FC * 2) / 128 * 128;
     }
   }
-  a.wvec = ldw % 8 == 0 && aligned16(W) && ldw < (int64_t(1) << 30) / (trans_w ? a.FC : a.KC) ? 1 : 0;
+  a.near = ldw < (int64_t(1) << 30) / (trans_w ? a.FC : a.KC) ? 1 : 0;
+  const bool whole = a.near && ldw % 8 == 0 && aligned16(W) && (trans_w || F % 8 == 0);
+  const WeightForm form = trans_w ? (whole ? kWholeT : kAnyT) : (whole ? kWhole : kAny);
   const size_t lds = size_t(a.KC) * size_t(a.FC) * sizeof(half_t);
   const int64_t tiles = ceil_div(n, int64_t(16) * RT);
   // Waves per compute unit: 16, or 32 where at least as much is written as read and that often.  us, 16 / 32: 233 000 rows of 64 -> 608 78 / 67,
@@ -847,8 +875,8 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
     const size_t need = std::max(lds, size_t(KP - 1) * size_t(T) * size_t(nt) * kWave * sizeof(float4_t));
     const dim3 grid{unsigned(ceil_div(tiles, T)), 1u, 1u};
     const int threads = T * KP * kWave;
-    return KP == 4 ? launch_linear_split<4>(nt, a, trans_w != 0, grid, threads, need, s)
-                   : (KP == 3 ? launch_linear_split<3>(nt, a, trans_w != 0, grid, threads, need, s) : launch_linear_split<2>(nt, a, trans_w != 0, grid, threads, need, s));
+    return KP == 4 ? launch_linear_split<4>(nt, a, form, grid, threads, need, s)
+                   : (KP == 3 ? launch_linear_split<3>(nt, a, form, grid, threads, need, s) : launch_linear_split<2>(nt, a, form, grid, threads, need, s));
   }
   const int fy = int(ceil_div(F, a.FC));
   const int64_t nrb = ceil_div(tiles, wpw);
@@ -861,17 +889,17 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   const dim3 grid{unsigned(want), unsigned(fy), 1u};
   const int threads = wpw * kWave;
   if (a.KC < K) {
-    if (nt == 2) return launch_linear<2, 1, true>(a, trans_w != 0, grid, threads, lds, s);
-    if (nt == 4) return launch_linear<4, 1, true>(a, trans_w != 0, grid, threads, lds, s);
-    return launch_linear<8, 1, true>(a, trans_w != 0, grid, threads, lds, s);
+    if (nt == 2) return launch_linear<2, 1, true>(a, form, grid, threads, lds, s);
+    if (nt == 4) return launch_linear<4, 1, true>(a, form, grid, threads, lds, s);
+    return launch_linear<8, 1, true>(a, form, grid, threads, lds, s);
   }
   if (nt == 2) {
-    if (RT == 4) return launch_linear<2, 4, false>(a, trans_w != 0, grid, threads, lds, s);
-    return RT == 2 ? launch_linear<2, 2, false>(a, trans_w != 0, grid, threads, lds, s) : launch_linear<2, 1, false>(a, trans_w != 0, grid, threads, lds, s);
+    if (RT == 4) return launch_linear<2, 4, false>(a, form, grid, threads, lds, s);
+    return RT == 2 ? launch_linear<2, 2, false>(a, form, grid, threads, lds, s) : launch_linear<2, 1, false>(a, form, grid, threads, lds, s);
   }
-  if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, trans_w != 0, grid, threads, lds, s);
-  if (nt == 4) return launch_linear<4, 1, false>(a, trans_w != 0, grid, threads, lds, s);
-  return launch_linear<8, 1, false>(a, trans_w != 0, grid, threads, lds, s);
+  if (nt == 4 && RT == 2) return launch_linear<4, 2, false>(a, form, grid, threads, lds, s);
+  if (nt == 4) return launch_linear<4, 1, false>(a, form, grid, threads, lds, s);
+  return launch_linear<8, 1, false>(a, form, grid, threads, lds, s);
 }
 
 extern "C" {

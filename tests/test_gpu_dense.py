@@ -315,3 +315,64 @@ def test_linear_weight_of_fewer_rows(hgnn, dev, K, KW, F):
     hgnn.hgnn_linear(up(Xh, dev), buf[:KW], Y)
     ref, sabs = oracle.linear(np.ascontiguousarray(Xh[:, :KW]), Wh, want_sabs=True)
     compare("linear, W of fewer rows", down(Y), ref, sabs)
+
+
+# W that begins at any element, lines of any pitch, the last piece of a line whole, ragged or all there is (fewer than eight features), columns in chunks,
+# columns shared by waves, fewer rows than columns of X; NaN between the lines and around them
+@pytest.mark.parametrize("n,K,KW,F,trans,ldw,first", [
+    (100, 64, 64, 8, False, 9, 1), (100, 64, 64, 9, False, 9, 0), (300, 64, 64, 42, False, 48, 0), (300, 64, 64, 42, False, 43, 3), (33, 40, 40, 15, False, 16, 8),
+    (300, 24, 24, 7, False, 8, 0), (300, 72, 70, 1, False, 3, 5), (300, 72, 65, 3, False, 8, 0), (1000, 504, 504, 47, False, 47, 2), (400, 128, 121, 100, False, 104, 0),
+    (2000, 608, 608, 300, False, 301, 1), (90, 2504, 2500, 41, False, 48, 0), (90, 2504, 2504, 41, False, 41, 7), (40, 1304, 1304, 130, False, 131, 1),
+    (300, 64, 64, 42, True, 67, 0), (300, 24, 24, 5, True, 25, 3), (1000, 504, 504, 100, True, 505, 1), (90, 2504, 2504, 41, True, 2507, 5)])
+def test_linear_weight_from_any_element(hgnn, dev, n, K, KW, F, trans, ldw, first):
+    print(f"linear any n={n} K={K} KW={KW} F={F} trans={trans} ldw={ldw} first={first}", flush=True)
+    r = np.random.default_rng(n + K + F + ldw)
+    X = f16(r.standard_normal((n, K)))
+    X[:, KW:] = 0
+    W = f16(r.standard_normal((F, K) if trans else (KW, F)) / np.sqrt(K))
+    flat = torch.full((first + W.shape[0] * ldw + 64,), float("nan"), dtype=torch.float16, device=dev)
+    Wd = flat.as_strided(W.shape, (ldw, 1), first)
+    Wd.copy_(up(W, dev))
+    Y = torch.full((n + 1, (F + 7) // 8 * 8), 7.0, dtype=torch.float16, device=dev)
+    hgnn.hgnn_linear(up(X, dev), Wd, Y[:n, :F], trans_w=trans)
+    got = down(Y)
+    assert np.all(got[n] == 7.0) and np.all(got[:, F:] == 7.0)
+    ref, sabs = oracle.linear(np.ascontiguousarray(X[:, :KW]), W, trans=trans, want_sabs=True)
+    compare("linear", got[:n, :F], ref, sabs)
+    pad = torch.zeros((W.shape[0], (W.shape[1] + 7) // 8 * 8), dtype=torch.float16, device=dev)  # the same from aligned lines: the same bits
+    pad[:, :W.shape[1]] = up(W, dev)
+    Y2 = torch.full_like(Y, 7.0)
+    hgnn.hgnn_linear(up(X, dev), pad[:, :W.shape[1]], Y2[:n, :F], trans_w=trans)
+    assert np.array_equal(down(Y2).view(np.uint16), got.view(np.uint16))
+
+
+@pytest.mark.parametrize("n,K,F,ldw,trans", [(4096, 64, 42, 48, False), (4096, 64, 42, 42, False), (3000, 2504, 41, 48, False), (4096, 64, 41, 67, True),
+                                             (60000, 608, 52, 56, False)])
+def test_linear_ragged_weight_costs_as_much_as_a_whole_one(hgnn, dev, n, K, F, ldw, trans):
+    """A weight with a ragged end or lines that begin anywhere takes no time of another order: at most 1.5 times that of the same with the features
+    filled up (read by elements it was 1.8 to 2.6 times)."""
+    X = torch.randn((n, K), device=dev).half()
+    up8 = (F + 7) // 8 * 8
+    Y = torch.empty((n, up8), dtype=torch.float16, device=dev)
+
+    def time_of(W, f):
+        hgnn.hgnn_linear(X, W, Y[:, :f], trans_w=trans)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(20):
+                hgnn.hgnn_linear(X, W, Y[:, :f], trans_w=trans)
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    rows, cols = (F, K) if trans else (K, F)
+    ragged = torch.randn((rows, ldw), device=dev).half()[:, :cols]
+    whole = torch.randn((up8, K) if trans else (K, up8), device=dev).half()
+    assert time_of(ragged, F) <= 1.5 * time_of(whole, up8)
