@@ -35,7 +35,8 @@ struct LinearArgs {
   int FC;     // features a workgroup owns (blockIdx.y picks them); a multiple of 32
   int near;   // ANY: a workgroup's part of W lies within 32-bit offsets
   uint32_t per_line;  // 2^31 / items on a line of the weight, rounded up
-  int step_f, step_k;  // transposed: the waves of a workgroup / and % pieces of 64 columns
+  int step_f, step_k;  // transposed: the waves of a workgroup / and % items on a line of the weight
+  int kshift;          // transposed: an item is 2^kshift pieces of 2^(6 - kshift) features
   int KW;     // rows of W that exist (not transposed): the others count as zero
   int64_t nrb;  // blocks of rows, 16 * RT for each wave of a workgroup
 };
@@ -44,7 +45,8 @@ struct LinearArgs {
 // (tile t of 16 features, step ks of 32 columns) is 64 lanes x 16 bytes, so every read of it is one conflict-free
 // kilobyte.  The features of a pair of tiles are dealt out so that a lane's 2 x 4 result values are 8 consecutive
 // features: tile 2b+o, row i of the tile <-> feature 32b + 8(i/4) + 4o + i%4.
-// W [F][K]: an item is 64 columns of eight features, a wave's 16-byte pieces of eight lines.  W [K][F]: an item is a block of eight features of
+// W [F][K]: an item is 64 columns of eight features, a wave's 16-byte pieces of eight lines; of up to 32 columns 16 features, or half of the lanes have none of
+// their own (us: 2000 rows of 16 -> 256 8.2 / 5.7, 30 000 of 16 -> 128 5.3 / 4.8, 60 000 7.4 / 6.9, 30 000 of 32 -> 64 4.0 / 3.8).  W [K][F]: an item is a block of eight features of
 // eight rows, a thread's, transposed by byte permutations.  A batch of items is fetched in one go and put into LDS later, so that the rows of
 // X can be asked for in between: behind them, by loads under conditions and with bank conflicts, the weight was up to a third of a call.
 // 100 003 rows of 64 -> 48 9.7 -> 6.8 us, 131 072 of 128 -> 64 13.5 -> 10.5, 262 144 of 64 -> 64 15.4 -> 12.4, 60 000 of 608 -> 128 28 -> 22 (without
@@ -56,22 +58,24 @@ struct WeightBatch {
 __device__ __forceinline__ int linear_waves() { return __builtin_amdgcn_readfirstlane(int(blockDim.x) / kWave); }
 template <bool TRANS>
 __device__ __forceinline__ int linear_batch() { return TRANS ? linear_waves() * 8 : int(blockDim.x); }
+// W^T: items on a line
+__host__ __device__ __forceinline__ int linear_across(const LinearArgs& a) { return (a.KC + (8 << a.kshift) - 1) >> (3 + a.kshift); }
 template <bool TRANS>
-__device__ __forceinline__ int linear_w_items(const LinearArgs& a) { return a.FC / 8 * (TRANS ? (a.KC + 63) / 64 : a.KC / 8); }
+__device__ __forceinline__ int linear_w_items(const LinearArgs& a) { return TRANS ? (a.FC >> (6 - a.kshift)) * linear_across(a) : a.FC / 8 * (a.KC / 8); }
 
 // item / items on a line of the weight (a division is a chain of some thirty instructions ahead of the first load)
 __device__ __forceinline__ int linear_line(const LinearArgs& a, int item) { return int(__umulhi(uint32_t(item) << 1, a.per_line)); }
 
-// W^T: f(u, features / 8, columns / 64), all scalar, for the u-th item of the wave in a batch
+// W^T: f(u, first feature, first piece), all scalar, for the u-th item of the wave in a batch
 template <class Fn>
 __device__ __forceinline__ void linear_each_item(const LinearArgs& a, int first, Fn&& f) {
-  const int across = (a.KC + 63) / 64;
+  const int across = linear_across(a);
   const int item = __builtin_amdgcn_readfirstlane(first + int(threadIdx.x) / kWave);
   int g = linear_line(a, item), c = item - g * across;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    if (8 * g >= a.FC) break;
-    f(u, g, c);
+    if (g << (6 - a.kshift) >= a.FC) break;
+    f(u, g << (6 - a.kshift), c << a.kshift);
     g += a.step_f, c += a.step_k;
     const int over = c >= across;
     g += over, c -= over ? across : 0;
@@ -104,8 +108,9 @@ __device__ __forceinline__ void linear_fetch_w(const LinearArgs& a, WeightBatch&
   const uint32_t pitch = uint32_t(a.ldw) * 2u;
   if (!linear_batched<TRANS, ANY>(a, fc0)) return;
   if constexpr (TRANS) {
-    linear_each_item(a, first, [&](int u, int g, int c) {
-      const uint32_t at = uint32_t(min(8 * g + (lane >> 3), fn - 1)) * pitch + uint32_t(min(64 * c + 8 * (lane & 7), kn - 8)) * 2u;
+    const int fl = lane >> a.kshift, kl = lane & ((1 << a.kshift) - 1);
+    linear_each_item(a, first, [&](int u, int f0, int k0) {
+      const uint32_t at = uint32_t(min(f0 + fl, fn - 1)) * pitch + uint32_t(min(8 * (k0 + kl), kn - 8)) * 2u;
       __builtin_memcpy(w.v + 4 * u, __builtin_assume_aligned(W + at, ANY ? 2 : 16), 16);
     });
   } else {
@@ -146,8 +151,9 @@ __device__ __forceinline__ void linear_put_w(const LinearArgs& a, const WeightBa
     return;
   }
   if constexpr (TRANS) {
-    linear_each_item(a, first, [&](int u, int g, int c) {
-      const int f = 8 * g + (lane >> 3), k8 = 8 * c + (lane & 7);
+    const int fl = lane >> a.kshift, kl = lane & ((1 << a.kshift) - 1);
+    linear_each_item(a, first, [&](int u, int f0, int k0) {
+      const int f = f0 + fl, k8 = k0 + kl;
       const bool in = f < fn && 8 * k8 < kn;
       uint4_t v;
 #pragma unroll
@@ -753,7 +759,8 @@ static hgnn_status launch_linear_kernel(LinearArgs a, bool trans, dim3 grid, int
       if (dev >= 0 && dev < 64) told[dev] = true;
     }
   }
-  const int across = (a.KC + 63) / 64;
+  a.kshift = a.KC == 32 ? 2 : 3;
+  const int across = linear_across(a);
   a.step_f = threads / kWave / across;
   a.step_k = threads / kWave % across;
   const uint32_t line = uint32_t(trans ? across : a.FC / 8);
@@ -819,7 +826,7 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   HGNN_REQUIRE(K % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y), HGNN_EUNSUPPORTED,
                "%s: needs K %% 8 == 0, ldx %% 8 == 0, ldy %% 8 == 0 and 16-byte aligned X, Y (pad with zeros)", who);
   LinearArgs a{n, K, F, reinterpret_cast<const half_t*>(X), ldx, reinterpret_cast<const half_t*>(W), ldw,
-               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, 0, 0, 0, KW, 0};
+               reinterpret_cast<half_t*>(Y), ldy, 0, 0, 0, 0, 0, 0, 0, KW, 0};
   const int k32 = (K + 31) / 32 * 32, f32 = (F + 31) / 32 * 32;
   // short rows: several row tiles per wave, where that still leaves four waves for every compute unit
   const int RT = n < int64_t(32) * 4 * kCus || K > 64 ? 1 : (K > 32 || n < int64_t(64) * 4 * kCus ? 2 : 4);

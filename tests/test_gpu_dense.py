@@ -346,6 +346,12 @@ def test_linear_weight_from_any_element(hgnn, dev, n, K, KW, F, trans, ldw, firs
     assert np.array_equal(down(Y2).view(np.uint16), got.view(np.uint16))
 
 
+# W^T of up to 32 columns: 16 features of four pieces at a time; one to twenty of them for one to sixteen waves
+@pytest.mark.parametrize("n,K,F", [(40, 8, 1), (300, 32, 17), (4100, 24, 33), (20000, 16, 128), (70, 8, 256), (500, 32, 602), (70000, 8, 100)])
+def test_linear_transposed_weight_of_few_columns(hgnn, dev, n, K, F):
+    test_linear_stays_inside(hgnn, dev, n, K, F, True)
+
+
 @pytest.mark.parametrize("n,K,F,ldw,trans", [(4096, 64, 42, 48, False), (4096, 64, 42, 42, False), (3000, 2504, 41, 48, False), (4096, 64, 41, 67, True),
                                              (60000, 608, 52, 56, False)])
 def test_linear_ragged_weight_costs_as_much_as_a_whole_one(hgnn, dev, n, K, F, ldw, trans):
