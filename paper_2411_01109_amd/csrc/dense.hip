@@ -852,13 +852,29 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   const WeightForm form = trans_w ? (whole ? kWholeT : kAnyT) : (whole ? kWhole : kAny);
   const size_t lds = size_t(a.KC) * size_t(a.FC) * sizeof(half_t);
   const int64_t tiles = ceil_div(n, int64_t(16) * RT);
-  // Waves per compute unit: 16, or 32 where at least as much is written as read and that often.  us, 16 / 32: 233 000 rows of 64 -> 608 78 / 67,
-  // 10^6 of 128 -> 128 107 / 104; 131 072 of 128 -> 128 14.6 / 17.7, 262 144 of 64 -> 64 12.3 / 15.4, 500 000 of 256 -> 64 58 / 59, 233 000 of 608 -> 64 61 / 65
-  const int waves = F >= K && tiles * ceil_div(F, int64_t(16) * nt) >= 32768 ? 32 : 16;
-  // waves per workgroup: the more LDS a workgroup holds, the more waves share it; twice as many from two row tiles per wave on, when the weight is
-  // brought in half as often (four / eight: 500 000 rows of 256 -> 64 61.6 / 58.0, 131 072 of 128 -> 128 by W^T 15.6 / 14.3; 70 000 10.7 / 11.8);
+  // A compute unit holds 16 waves (the registers of four for each SIMD), fewer where their workgroups' weights do not fit beside each other.  Workgroups are
+  // persistent: as many as the chip holds at once, each with the same number of row blocks (to one).
+  const int fy = int(ceil_div(F, a.FC));
+  auto blocks_each = [&](int w, int rounds) {  // for workgroups of w waves, as many as the chip holds `rounds` times
+    const int64_t held = std::max<int64_t>(1, std::min<int64_t>(16 / w, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
+    return ceil_div(ceil_div(tiles, w), std::max<int64_t>(1, int64_t(kCus) * held * rounds / fy));
+  };
+  // Twice as many, one after the other, where at least as much is written as read, often, and that leaves no compute unit with more blocks than before: us, X
+  // and Y out of the caches, one / two rounds: 1.2 M rows of 64 -> 64 66.4 / 65.8, 2.4 M of 128 -> 128 247 / 243, 400 000 of 64 -> 256 72.6 / 64.9, 2.4 M of 16 -> 128 243 /
+  // 228; 233 000 of 64 -> 608 90.0 / 84.5 (workgroups of eight / 16 waves), 400 000 172 / 163; but 800 000 of 128 -> 128 (13 blocks each / twice 7) 85.7 / 89.0,
+  // 288 000 of 64 -> 256 (3 / twice 2) 47 / 52, of 64 -> 608 (3 / twice 2) 125 / 132; of 128 -> 256, 524 288 90.0 / 91.9.  Small weights of many features gain with more blocks,
+  // too, from some 40 000 passes on: 800 000 of 64 -> 256 (7 / twice 4) 135 / 130, 1.2 M of 16 -> 128 (5 / twice 3) 118 / 110.
+  const bool small = lds <= 40 * 1024, many = F >= 4 * int64_t(K);
+  const int64_t passes = tiles * ceil_div(F, int64_t(16) * nt);
+  const bool twice = passes >= 32768 && lds <= 80 * 1024 && (small ? F >= K : many) && 25 * 2 * blocks_each(8, 2) <= 26 * blocks_each(8, 1);
+  const int rounds = twice || (passes >= 40000 && small && many) ? 2 : 1;
+  // waves per workgroup: the more LDS a workgroup holds, the more waves share it; of small weights eight from two row tiles per wave on, when the weight is
+  // brought in half as often, if workgroups of eight take four fifths of the places (else compute units hold unequal numbers): us, four / eight, 131 072 rows of
+  // 128 -> 128 18.4 / 16.6, W^T 18.3 / 16.3, 288 000 37.5 / 35.5, 400 000 50.0 / 47.4, 70 000 10.7 / 11.8; with three quarters of the places taken 144 000 of 128 -> 128 20.2 /
+  // 22.6, 288 000 of 64 -> 64 by W^T 19.0 / 22.4, 288 000 of 64 -> 128 27.4 / 32.3, 400 000 of 64 -> 64 27.1 / 28.0;
   // fewer, so that every compute unit has work, while bringing the weight in stays short
-  int wpw = lds <= 40 * 1024 ? (tiles >= 2 * 16 * kCus ? 8 : 4) : (lds <= 80 * 1024 ? waves / 2 : 16);
+  const bool full = 5 * ceil_div(ceil_div(tiles, 8), blocks_each(8, 1)) * fy >= 4 * 2 * kCus;
+  int wpw = small ? (rounds > 1 || (tiles >= 2 * 16 * kCus && full) ? 8 : 4) : (lds <= 80 * 1024 ? 8 * rounds : 16);
   const int least = lds <= 16 * 1024 ? 1 : (lds <= 32 * 1024 ? 2 : 4);
   while (wpw > least && ceil_div(tiles, wpw) < kCus) wpw /= 2;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -885,13 +901,8 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
     return KP == 4 ? launch_linear_split<4>(nt, a, form, grid, threads, need, s)
                    : (KP == 3 ? launch_linear_split<3>(nt, a, form, grid, threads, need, s) : launch_linear_split<2>(nt, a, form, grid, threads, need, s));
   }
-  const int fy = int(ceil_div(F, a.FC));
-  const int64_t nrb = ceil_div(tiles, wpw);
-  a.nrb = nrb;
-  // persistent workgroups, as many as fit the chip at once, each with the same number of row blocks (to one)
-  const int64_t resident = int64_t(kCus) * std::max<int64_t>(1, std::min<int64_t>(waves / wpw, int64_t(160 * 1024) / std::max<size_t>(lds, 1)));
-  const int64_t per = ceil_div(nrb, std::max<int64_t>(1, resident / fy));
-  const int64_t want = ceil_div(nrb, per);
+  a.nrb = ceil_div(tiles, wpw);
+  const int64_t want = ceil_div(a.nrb, blocks_each(wpw, rounds));
   HGNN_REQUIRE(want <= 0x7fffffff && fy <= 65535, HGNN_EUNSUPPORTED, "%s: grid too large", who);
   const dim3 grid{unsigned(want), unsigned(fy), 1u};
   const int threads = wpw * kWave;

@@ -29,6 +29,7 @@ bool capturing = false, spoiled = false;
 std::string library;
 dim3 push_grid, push_block;
 size_t push_shmem;
+int last_grid = 0, last_block = 0;
 hipStream_t push_stream;
 
 // the test makes streams of device d as 0x1000 * (d + 1) + anything
@@ -47,6 +48,8 @@ bool refused(bool always = false) {
 
 extern "C" {
 // ---- what the test asks
+int fake_last_grid() { return last_grid; }
+int fake_last_block() { return last_block; }
 void fake_reset(const char* lib) {
   library = lib;
   launched.clear();
@@ -132,8 +135,9 @@ hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
   work(st);
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, hipStream_t s) {
   work(s);
+  last_grid = int(grid.x), last_block = int(block.x);
   launched.push_back(names.count(f) ? names[f] : "?");
   return hipSuccess;
 }

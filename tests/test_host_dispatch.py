@@ -184,7 +184,26 @@ def rounds(h):
         assert st == 0 and len(kernel) == 1 and f"Li{most}EEE" in kernel[0], (f, nnz, mean, names)
 
 
-SCENARIOS = [smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns, rounds]
+def waves_of_a_projection(h):
+    """Workgroups of eight waves for small weights where they take most places, else of four; of larger weights eight, or 16 and more of them than the
+    chip holds at once where that leaves nobody with more blocks of rows; all with the same number of blocks, to one."""
+    x = vp(h.data)
+    for n, K, F, trans, waves, most in (
+            (288000, 64, 64, 1, 4, 1024), (144000, 128, 128, 0, 4, 1024), (131072, 128, 128, 0, 8, 512), (288000, 128, 128, 1, 8, 512), (800000, 128, 128, 0, 8, 512),
+            (2400000, 128, 128, 0, 8, 1024), (288000, 64, 256, 0, 4, 1024), (400000, 64, 256, 0, 8, 1024), (800000, 64, 256, 1, 8, 1024), (288000, 128, 256, 0, 8, 512),
+            (400000, 128, 256, 1, 8, 512), (131072, 64, 608, 1, 8, 512), (288000, 64, 608, 1, 8, 512), (233000, 64, 608, 1, 16, 512), (233000, 608, 64, 0, 8, 512),
+            (1200000, 128, 256, 0, 8, 512), (70000, 64, 64, 0, 4, 1024)):
+        st, names = launches(h, lambda: h.lib.hgnn_linear(i64(n), K, F, x, i64(K), x, i64(K if trans else F), trans, x, i64(F), vp(A)))
+        assert st == 0 and len(names) == 1, (n, K, F, names)
+        got, grid = h.fake.fake_last_block() // 64, h.fake.fake_last_grid()
+        assert got == waves and grid <= most, (n, K, F, trans, got, grid)
+        rows = 16 * (1 if K > 64 else (2 if K > 32 else 4))
+        blocks = -(-n // (rows * waves))
+        each = -(-blocks // most)
+        assert grid == -(-blocks // each), (n, K, F, grid, blocks)
+
+
+SCENARIOS = [waves_of_a_projection, smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns, rounds]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
