@@ -682,6 +682,28 @@ static void launch_rows_h(int LR, dim3 grid, hipStream_t s, const EdgeRowArgs& a
 // 103 / 95; 300 000 of 1000 rows, H = 8 56 / 40; 46 / 29.
 static bool list_teams_pay(int H, int n_list) { return H <= 2 || (H == 4 && n_list >= 16384); }
 
+// Whether half of LR lanes take a row, forward and for row sums.  What a team spends is the exchange between its lanes, twice per head forward; but half of the
+// lanes leave half of the waves, need two vectors on each to hold the row, and what they do not hold is read again, or goes to the tier of the longer rows.  So
+// the half have to hold a quarter more than the mean, and the waves of all lanes have to be many: 16 a compute unit where the half hold half more than the
+// mean and the rows are much alike (of those that the plan does not list few are beyond the half; or most are listed, and no longer than the rest), else 60,
+// and 96 where rows differ.  us, all / half:
+//   forward, uniform: 40 non-zeros a row, four heads, 1000, 8000, 64 000 rows 3.1 / 3.1, 5.5 / 4.7, 21 / 15; 20, eight heads, 2000, 16 000, 300 000 3.4 / 3.5, 8.3 / 5.7, 95 / 51;
+//     6, eight heads, 4000, 32 000, 300 000 3.3 / 4.2, 5.1 / 5.1, 25 / 20; a quarter more: 50, one head, 8000, 64 000 2.9 / 3.4, 6.5 / 7.2, four, 4000, 32 000 3.8 / 4.1, 13 / 10
+//   log-normal: 70, two heads, 4000, 16 000, 64 000 4.4 / 5.3, 6.8 / 7.8, 21 / 19; 14, four heads, 1000, 16 000, 300 000 3.2 / 4.2, 4.8 / 5.3, 27 / 26;
+//     6, eight heads, 4000, 32 000, 300 000 4.2 / 6.6, 7.6 / 8.6, 33 / 33; 50, 16 000, 64 000 16 / 19, 51 / 49
+//   sums, uniform: 20, eight heads, 4000, 32 000 2.6 / 2.6, 4.6 / 3.6; log-normal: 14, four heads, 1000, 16 000, 128 000 2.6 / 2.8, 3.0 / 3.2, 7.4 / 6.4
+// With eight heads and a whole wave for a row sums gain nothing (uniform, 50, 64 000 15.7 / 17.6); the backward, with three tensors in registers, neither (6 M
+// non-zeros, log-normal, four heads 17.6 / 19.7).
+static bool half_of_lanes(const hgnn_plan* p, bool sum, int H, int LR, double mean_len) {
+  constexpr int64_t kCus = 256;
+  const double held = LR / 2 * 8 * kKeepVec / H;  // by the half
+  if (LR <= 4 || held < 1.25 * mean_len || (sum && H == 8 && LR == kWave)) return false;
+  const int64_t listed = int64_t(p->n_mid) + p->n_big, waves = int64_t(p->nrows) * LR / kWave;
+  const bool alike = listed < p->nrows / 2 ? listed <= p->nrows / 256 || (held >= p->mid_deg && listed <= p->nrows / 8)
+                                           : double(p->listed_nnz) <= 1.1 * mean_len * double(listed);
+  return waves >= kCus * (!alike ? 96 : (held >= 1.5 * mean_len ? 16 : 60));
+}
+
 // Launches the row kernel (and the follow-up of the chunks when a plan lists long rows) for H in {1,2,4,8}.
 template <int OP>
 static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeRowArgs a, hipStream_t s) {
@@ -705,12 +727,7 @@ static hgnn_status launch_edge_rows(const hgnn_csr* g, const hgnn_plan* p, EdgeR
   const double per_row = mean_len * ((OP == kSum && a.eid) ? 1.0 : H / 8.0);
   int LR = 4;
   while (LR < kWave && LR < per_row) LR <<= 1;
-  // Half of the lanes where two vectors on each still hold a quarter more than the mean row: what a team spends is the exchange between its lanes,
-  // twice per head forward.  us, all / half of them: forward, 3 M of 300 000 uniform rows, four heads 19.1 / 14.4, eight 43 / 28; 3.5 M of 100 000, one
-  // head 7.6 / 7.2, two 13.1 / 10.6, four 28.4 / 19.2, eight 75 / 46; 6 M of 60 000 log-normal, four 48 / 36; sums 8.8 / 6.6, 15.8 / 12.3, 5.1 / 4.8, 6.9 / 6.3,
-  // 13.1 / 9.9, 21.5 / 20.2, 20.6 / 16.8.  With less to spare rows leave for the tier of the longer ones (6 M of 100 000, one head 9.8 / 13.5, sums
-  // 6.2 / 7.6); the backward, with three tensors in registers, gains nothing (log-normal, four heads 17.6 / 19.7).
-  if (p && OP != kBwd && !(OP == kSum && a.eid) && LR > 4 && LR >= 1.25 * per_row) LR >>= 1;
+  if (p && OP != kBwd && !(OP == kSum && a.eid) && half_of_lanes(p, OP == kSum, H, LR, mean_len)) LR >>= 1;
   const int big = (p && p->n_big > 0) ? p->big_deg : 0;
   a.big_row = p ? p->big_row : nullptr;
   // tier 1: sub-wave teams take the rows they can hold in registers; tier 2: a whole wave per row

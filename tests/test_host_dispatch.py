@@ -203,7 +203,30 @@ def waves_of_a_projection(h):
         assert grid == -(-blocks // each), (n, K, F, grid, blocks)
 
 
-SCENARIOS = [waves_of_a_projection, smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns, rounds]
+def lanes_of_a_row(h):
+    """Softmax and row sums: half of the lanes that the mean row fills only if its registers hold a quarter more than the mean and waves are many, by how
+    much more they hold; never without a plan, for the backward and for sums of eight heads by whole waves.  (The runtime's graphs list no rows.)"""
+    x = vp(h.data)
+    for nrows, mean, H, lanes in ((1000, 20, 4, 16), (8000, 20, 4, 16), (20000, 20, 4, 8), (300000, 10, 4, 4), (2000, 6, 8, 8), (25000, 6, 8, 8), (60000, 6, 8, 8),
+                                  (130000, 6, 8, 4), (1000, 40, 4, 32), (10000, 40, 4, 16), (30000, 50, 4, 32), (31000, 50, 4, 16), (100000, 50, 1, 8), (130000, 50, 1, 4),
+                                  (200000, 28, 8, 32), (3000, 70, 4, 64), (5000, 70, 4, 32), (300000, 14, 1, 4), (60000, 100, 8, 64)):
+        g = graph(h, nrows, nrows, nrows * mean)
+        p = vp()
+        assert h.lib.hgnn_plan_create(ctypes.byref(g), 256, 64, 8, 1, ctypes.byref(p), vp(A)) == 0
+        full = 4
+        while full < 64 and full < mean * H / 8:
+            full *= 2
+        for plan in (p, None):
+            for what, args in (("Li0", (x, x)), ("Li1", (x, x, None, ctypes.c_float(0.2), x)), ("Li2", (x, x))):
+                f = {"Li0": h.lib.hgnn_edge_softmax, "Li1": h.lib.hgnn_edge_softmax_bwd, "Li2": h.lib.hgnn_edge_rowsum}[what]
+                st, names = launches(h, lambda: f(ctypes.byref(g), plan, H, *args, vp(A)))
+                want = lanes if plan and what != "Li1" and not (what == "Li2" and H == 8 and full == 64) else full
+                kernel = [n for n in names if "edge_rows_kernel" in n]
+                assert st == 0 and len(kernel) == 1 and f"I{what}ELi{want}ELi{H}E" in kernel[0], (nrows, mean, H, what, plan, want, names)
+        h.lib.hgnn_plan_destroy(p)
+
+
+SCENARIOS = [lanes_of_a_row, waves_of_a_projection, smaller_workspaces, static_form, narrow_features, column_ranges, room_for_column_ranges, many_windows, weight_gradient, shared_columns, rounds]
 
 
 @pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
