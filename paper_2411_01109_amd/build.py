@@ -17,8 +17,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-tar
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def build_calls(verbose: bool = False) -> str:
-    """Compile csrc/calls.cpp (host code: Python arguments to the library's entry points)."""
+def compile_calls(source: str, out: str, flags=(), verbose: bool = False) -> None:
+    """Compile host code that takes torch tensors and Python arguments."""
     import torch
 
     base = os.path.dirname(torch.__file__)
@@ -26,10 +26,15 @@ def build_calls(verbose: bool = False) -> str:
     # every access to such memory in the runtime takes glibc's slow way (2 us more for a set-up call)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-DNDEBUG", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(base, "include"), "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
-           os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+           *flags, source, "-o", out, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+
+
+def build_calls(verbose: bool = False) -> str:
+    """Compile csrc/calls.cpp (Python arguments to the library's entry points)."""
+    compile_calls(os.path.join(CSRC, "calls.cpp"), CALLS_PATH, verbose=verbose)
     return CALLS_PATH
 
 

@@ -12,6 +12,10 @@
 
 #include <climits>
 #include <cstdint>
+#include <cstring>
+#include <exception>
+#include <new>
+#include <optional>
 
 #include "hgnn.h"
 
@@ -145,23 +149,39 @@ struct Reader {
   }
 };
 
-// f(reader, arguments) reads them and returns what calls the entry point; that runs without the interpreter's lock
+// f(reader, arguments) reads them and returns what calls the entry point; that runs without the interpreter's lock.  An exception of the library's becomes
+// one of Python's once the lock is held again: the call has been made and is not repeated.  Nothing is caught around taking the lock, where a thread that
+// outlives the interpreter is unwound.
 template <class F>
 PyObject* run(PyObject* const* a, Py_ssize_t n, Py_ssize_t want, F&& f) {
   long status = kOther;
   if (n == want && g_raw_stream) {
+    Reader r;
+    std::optional<decltype(f(r, a))> call;
     try {
-      Reader r;
-      const auto call = f(r, a);
-      if (r.ok && !PyErr_Occurred()) {
-        Py_BEGIN_ALLOW_THREADS
-        status = long(call());
-        Py_END_ALLOW_THREADS
-      }
-    } catch (...) {  // a tensor without memory of its own: the wrapper raises what torch says of it
-      status = kOther;
+      call.emplace(f(r, a));
+    } catch (const std::exception&) {  // a tensor without memory of its own: the wrapper raises what torch says of it
     }
+    const bool plain = call && r.ok && !PyErr_Occurred();
     PyErr_Clear();
+    if (plain) {
+      PyObject* failed = nullptr;
+      char what[256] = "";
+      Py_BEGIN_ALLOW_THREADS
+      try {
+        status = long((*call)());
+      } catch (const std::bad_alloc&) {
+        failed = PyExc_MemoryError;
+      } catch (const std::exception& e) {
+        failed = PyExc_RuntimeError;
+        std::strncpy(what, e.what(), sizeof(what) - 1);
+      }
+      Py_END_ALLOW_THREADS
+      if (failed) {
+        PyErr_SetString(failed, what);
+        return nullptr;
+      }
+    }
   }
   return PyLong_FromLong(status);
 }
