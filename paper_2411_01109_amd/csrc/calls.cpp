@@ -109,18 +109,19 @@ struct Reader {
     if (!PyBool_Check(o)) ok = false;
     return o == Py_True;
   }
-  const hgnn_csr* graph(PyObject* o) {  // the structure inside a Csr
+  hgnn_csr graph(PyObject* o) {  // a copy of the structure inside a Csr, which is anybody's while the lock is not held
+    hgnn_csr g{};
     PyObject* const s = PyObject_GetAttr(o, g_struct);
     Py_buffer b;
     if (!s || PyObject_GetBuffer(s, &b, PyBUF_SIMPLE) != 0) {
       Py_XDECREF(s);
       ok = false;
-      return nullptr;
+      return g;
     }
-    const hgnn_csr* const g = size_t(b.len) == sizeof(hgnn_csr) ? static_cast<const hgnn_csr*>(b.buf) : nullptr;
-    if (!g) ok = false;
+    if (size_t(b.len) == sizeof(g)) std::memcpy(&g, b.buf, sizeof(g));
+    else ok = false;
     PyBuffer_Release(&b);
-    Py_DECREF(s);  // (the Csr, which the caller holds, keeps it)
+    Py_DECREF(s);
     return g;
   }
   hgnn_plan* plan(PyObject* o) {  // of a Plan that has not been destroyed
@@ -218,7 +219,7 @@ HGNN_CALL(linear_wgrad, 7) {
 } HGNN_END
 
 HGNN_CALL(spmm, 10) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_half* const w = r.half_or_null(a[1]);
   const int H = r.integer(a[2]);
   const Table X = r.table(a[3]), Y = r.table(a[4]);
@@ -228,12 +229,12 @@ HGNN_CALL(spmm, 10) {
   size_t bytes = 0;
   void* const ws = a[8] == Py_None ? nullptr : r.workspace(a[8], &bytes);
   void* const s = r.stream(a[9]);
-  return [=] { return f_spmm(g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, ws, bytes, s); };
+  return [=] { return f_spmm(&g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, ws, bytes, s); };
 } HGNN_END
 
 HGNN_CALL(spmm_discretized, 10) {
   const hgnn_plan* const p = r.plan(a[0]);
-  const hgnn_csr* const g = r.graph(a[1]);
+  const hgnn_csr g = r.graph(a[1]);
   const hgnn_half* const w = r.half_or_null(a[2]);
   const int H = r.integer(a[3]);
   const Table X = r.table(a[4]), Y = r.table(a[5]);
@@ -241,12 +242,12 @@ HGNN_CALL(spmm_discretized, 10) {
   const float* const scale = r.single_or_null(a[7]);
   const int F = r.integer_or(a[8], X.cols);
   void* const s = r.stream(a[9]);
-  return [=] { return f_spmm_discretized(p, g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, s); };
+  return [=] { return f_spmm_discretized(p, &g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, s); };
 } HGNN_END
 
 HGNN_CALL(spmm_discretized_fused, 15) {
   const hgnn_plan* const p = r.plan(a[0]);
-  const hgnn_csr* const g = r.graph(a[1]);
+  const hgnn_csr g = r.graph(a[1]);
   const hgnn_half* const w = r.half_or_null(a[2]);
   const int H = r.integer(a[3]);
   const Table X = r.table(a[4]), Y = r.table(a[5]);
@@ -259,11 +260,11 @@ HGNN_CALL(spmm_discretized_fused, 15) {
   const Table scaled = r.table_or_null(a[13]);
   void* const s = r.stream(a[14]);
   const hgnn_spmm_fusion fz{col_scale, self.half(), self.ld, self_coef, agg_coef, scaled.half(), scaled.ld};
-  return [=] { return f_spmm_discretized_fused(p, g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, &fz, s); };
+  return [=] { return f_spmm_discretized_fused(p, &g, w, H, X.half(), X.ld, Y.half(), Y.ld, F, op, scale, &fz, s); };
 } HGNN_END
 
 HGNN_CALL(sddmm, 12) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan_or_null(a[1]);
   const auto op = hgnn_sddmm_op(r.integer(a[2]));
   const int H = r.integer(a[3]), D = r.integer(a[4]);
@@ -272,48 +273,48 @@ HGNN_CALL(sddmm, 12) {
   const hgnn_half *const al = r.half_or_null(a[8]), *const ar = r.half_or_null(a[9]);
   const float slope = r.real(a[10]);
   void* const s = r.stream(a[11]);
-  return [=] { return f_sddmm(g, p, op, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out, s); };
+  return [=] { return f_sddmm(&g, p, op, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out, s); };
 } HGNN_END
 
 HGNN_CALL(edge_softmax, 6) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan_or_null(a[1]);
   const int H = r.integer(a[2]);
   hgnn_half *const e = r.half(a[3]), *const alpha = r.half(a[4]);
   void* const s = r.stream(a[5]);
-  return [=] { return f_edge_softmax(g, p, H, e, alpha, s); };
+  return [=] { return f_edge_softmax(&g, p, H, e, alpha, s); };
 } HGNN_END
 
 HGNN_CALL(edge_softmax_bwd, 9) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan_or_null(a[1]);
   const int H = r.integer(a[2]);
   hgnn_half *const alpha = r.half(a[3]), *const dalpha = r.half(a[4]), *const de = r.half(a[5]), *const e = r.half_or_null(a[6]);
   const float slope = r.real(a[7]);
   void* const s = r.stream(a[8]);
-  return [=] { return f_edge_softmax_bwd(g, p, H, alpha, dalpha, e, slope, de, s); };
+  return [=] { return f_edge_softmax_bwd(&g, p, H, alpha, dalpha, e, slope, de, s); };
 } HGNN_END
 
 HGNN_CALL(edge_rowsum, 6) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan_or_null(a[1]);
   const int H = r.integer(a[2]);
   hgnn_half *const t = r.half(a[3]), *const out = r.half(a[4]);
   void* const s = r.stream(a[5]);
-  return [=] { return f_edge_rowsum(g, p, H, t, out, s); };
+  return [=] { return f_edge_rowsum(&g, p, H, t, out, s); };
 } HGNN_END
 
 HGNN_CALL(edge_colsum, 6) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan(a[1]);
   const int H = r.integer(a[2]);
   hgnn_half *const t = r.half(a[3]), *const out = r.half(a[4]);
   void* const s = r.stream(a[5]);
-  return [=] { return f_edge_colsum(g, p, H, t, out, s); };
+  return [=] { return f_edge_colsum(&g, p, H, t, out, s); };
 } HGNN_END
 
 HGNN_CALL(gat_forward_fused, 12) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan(a[1]);
   const int H = r.integer(a[2]), D = r.integer(a[3]);
   const Table U = r.table(a[4]), V = r.table(a[5]);
@@ -322,11 +323,11 @@ HGNN_CALL(gat_forward_fused, 12) {
   float* const lse = r.single_or_null(a[9]);
   const float slope = r.real(a[10]);
   void* const s = r.stream(a[11]);
-  return [=] { return f_gat_forward_fused(g, p, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, s); };
+  return [=] { return f_gat_forward_fused(&g, p, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, s); };
 } HGNN_END
 
 HGNN_CALL(gat_forward_fused_save, 14) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan(a[1]);
   const int H = r.integer(a[2]), D = r.integer(a[3]);
   const Table U = r.table(a[4]), V = r.table(a[5]);
@@ -338,14 +339,14 @@ HGNN_CALL(gat_forward_fused_save, 14) {
   const float slope = r.real(a[12]);
   void* const s = r.stream(a[13]);
   return [=] {
-    return f_gat_forward_fused_save(g, p, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, masked.half(), masked.ld, csum, s);
+    return f_gat_forward_fused_save(&g, p, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, masked.half(), masked.ld, csum, s);
   };
 } HGNN_END
 
 HGNN_CALL(gat_backward_fused_saved, 20) {
-  const hgnn_csr* const g = r.graph(a[0]);
+  const hgnn_csr g = r.graph(a[0]);
   const hgnn_plan* const p = r.plan(a[1]);
-  const hgnn_csr* const gt = r.graph(a[2]);
+  const hgnn_csr gt = r.graph(a[2]);
   const hgnn_plan* const pt = r.plan(a[3]);
   const int H = r.integer(a[4]), D = r.integer(a[5]);
   const Table U = r.table(a[6]), V = r.table(a[7]);
@@ -359,7 +360,7 @@ HGNN_CALL(gat_backward_fused_saved, 20) {
   const float slope = r.real(a[18]);
   void* const s = r.stream(a[19]);
   return [=] {
-    return f_gat_backward_fused_saved(g, p, gt, pt, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, masked.half(),
+    return f_gat_backward_fused_saved(&g, p, &gt, pt, H, D, U.half(), U.ld, V.half(), V.ld, al, ar, slope, out.half(), out.ld, lse, masked.half(),
                                       masked.ld, csum, dOut.half(), dOut.ld, dV.half(), dV.ld, d_el, d_er, s);
   };
 } HGNN_END

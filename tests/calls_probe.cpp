@@ -1,4 +1,5 @@
-// The way of a call through csrc/calls.cpp with entry points of the test's own: probe(what) calls one that throws, or that takes its time.
+// The way of a call through csrc/calls.cpp with entry points of the test's own: probe(what) calls one that throws, or that takes its time,
+// rows_later(graph) one that looks at the graph after half a second.
 #include "calls.cpp"
 
 #include <chrono>
@@ -17,7 +18,16 @@ HGNN_CALL(probe, 1) {
   };
 } HGNN_END
 
-PyMethodDef probe_methods[] = {HGNN_METHOD(probe), {nullptr, nullptr, 0, nullptr}};
+
+HGNN_CALL(rows_later, 1) {
+  const hgnn_csr g = r.graph(a[0]);
+  return [=] {
+    std::this_thread::sleep_for(std::chrono::milliseconds(500));
+    return hgnn_status(g.nrows);
+  };
+} HGNN_END
+
+PyMethodDef probe_methods[] = {HGNN_METHOD(probe), HGNN_METHOD(rows_later), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef probe_module = {PyModuleDef_HEAD_INIT, "calls_probe", nullptr, -1, probe_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

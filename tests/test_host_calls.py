@@ -20,7 +20,7 @@ def probe(tmp_path_factory):
 
 def run(folder, text):
     return subprocess.run([sys.executable, "-c", "import sys, threading, time, torch\nsys.path.insert(0, %r)\nfrom calls_probe import probe\n%s" % (folder, text)],
-                          capture_output=True, text=True, timeout=120)
+                          capture_output=True, text=True, timeout=120, cwd=os.path.dirname(HERE))
 
 
 def test_exceptions_of_an_entry_point(probe):
@@ -56,3 +56,25 @@ sys.modules["__main__"].last = Last()
 print("done", flush=True)
 """)
     assert r.returncode == 0 and r.stdout == "done\n" and not r.stderr, r
+
+
+def test_a_graph_that_is_given_another_structure_meanwhile(probe):
+    """A call goes on with the graph that it was given, whatever another thread does to the object."""
+    r = run(probe, """
+from calls_probe import rows_later
+from paper_2411_01109_amd.binding import _CsrStruct
+class Graph:
+    struct = None
+g = Graph()
+g.struct = _CsrStruct(7, 7, 0, None, None, None, None)
+got = []
+t = threading.Thread(target=lambda: got.append(rows_later(g)))
+t.start()
+time.sleep(0.2)
+g.struct = None
+others = [_CsrStruct(9, 9, 0, None, None, None, None) for _ in range(1000)]
+t.join()
+assert got == [7], got
+print("done")
+""")
+    assert r.returncode == 0 and r.stdout == "done\n", r
