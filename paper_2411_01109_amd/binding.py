@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -58,7 +59,7 @@ class _CsrStruct(ctypes.Structure):
 
 
 _lib = None
-_calls = None  # the module of csrc/calls.cpp once the library is loaded
+_calls = None  # the module of csrc/calls.cpp once the library is loaded (_load_calls)
 
 
 def load() -> ctypes.CDLL:
@@ -66,9 +67,9 @@ def load() -> ctypes.CDLL:
     global _lib, _calls
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, CALLS_PATH):
-        if not os.path.exists(path):
-            raise FileNotFoundError(f"{path} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(
+            f"{LIB_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     csr = ctypes.POINTER(_CsrStruct)
@@ -145,12 +146,23 @@ def load() -> ctypes.CDLL:
                                           ctypes.c_size_t, vp]
     for name in EXPORTS:
         getattr(lib, name)  # every declared entry point must be exported
-    from . import _calls as calls
-    if _raw_stream is not None and _current_device is not None:
-        calls.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _raw_stream, _current_device)
-        _calls = calls
+    _calls = _load_calls(lib)
     _lib = lib
     return lib
+
+
+def _load_calls(lib: ctypes.CDLL):
+    """The module of csrc/calls.cpp, bound to the library; None where there is none (the library built alone, another Python or torch than the
+    module was built for, a torch without the functions that name the current stream): every call then goes through ctypes."""
+    if _raw_stream is None or _current_device is None or not os.path.exists(CALLS_PATH):
+        return None
+    try:
+        from . import _calls as calls
+    except ImportError as e:
+        warnings.warn(f"{CALLS_PATH} does not load ({e}): calls cost 2 us more of host time each until it is built again", RuntimeWarning, stacklevel=3)
+        return None
+    calls.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _raw_stream, _current_device)
+    return calls
 
 
 def _done(status: int) -> bool:

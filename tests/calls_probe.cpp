@@ -18,7 +18,6 @@ HGNN_CALL(probe, 1) {
   };
 } HGNN_END
 
-
 HGNN_CALL(rows_later, 1) {
   const hgnn_csr g = r.graph(a[0]);
   return [=] {

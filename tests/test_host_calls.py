@@ -1,4 +1,5 @@
-"""The native route's dealings with the interpreter (csrc/calls.cpp), on the CPU: entry points that throw, threads that outlive the interpreter."""
+"""The native route's dealings with the interpreter (csrc/calls.cpp), on the CPU: entry points that throw, threads that outlive the interpreter;
+and the package without the module."""
 import os
 import subprocess
 import sys
@@ -78,3 +79,36 @@ assert got == [7], got
 print("done")
 """)
     assert r.returncode == 0 and r.stdout == "done\n", r
+
+
+@pytest.mark.parametrize("how", ["missing", "for another interpreter", "there"])
+def test_the_library_serves_without_the_module(hgnn, tmp_path, how):
+    """The package with the library and without a module of native calls that loads: every call goes through ctypes, as it does for arguments that are not plain."""
+    pkg = tmp_path / "paper_2411_01109_amd"
+    pkg.mkdir()
+    here = os.path.dirname(hip_build.LIB_PATH)
+    for name in ("__init__.py", "binding.py", "libhgnn.so", "_calls.so"):
+        if name != "_calls.so" or how == "there":
+            os.symlink(os.path.join(here, name), str(pkg / name))
+    if how == "for another interpreter":
+        (pkg / "_calls.so").write_bytes(b"not of this world")
+    text = """
+import warnings
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    from paper_2411_01109_amd import binding
+    lib = binding.load()
+    assert binding.load() is lib
+assert binding.hgnn_linear_wgrad_workspace(64, 64) > 0
+print((binding._calls is not None), [str(x.category.__name__) for x in w if "_calls" in str(x.message)])
+try:
+    binding.hgnn_linear(torch.zeros(4, 8).half(), torch.zeros(8, 8).half(), torch.zeros(4, 8).half())
+except TypeError as e:
+    assert "CUDA (HIP)" in str(e)
+else:
+    raise AssertionError("a tensor on the CPU was taken")
+"""
+    r = subprocess.run([sys.executable, "-c", "import sys, torch\nsys.path.insert(0, %r)\n%s" % (str(tmp_path), text)], capture_output=True, text=True,
+                       timeout=120, cwd=str(tmp_path))
+    want = {"missing": "False []", "for another interpreter": "False ['RuntimeWarning']", "there": "True []"}[how]
+    assert r.returncode == 0 and r.stdout.strip() == want, r
