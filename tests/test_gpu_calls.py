@@ -164,3 +164,52 @@ def test_no_thread_local_memory():
         fh.seek(at)
         kinds = [int.from_bytes(fh.read(size)[:4], "little") for _ in range(n)]
     assert 1 in kinds and 7 not in kinds  # PT_LOAD, PT_TLS
+
+
+@pytest.fixture
+def taken(hgnn, monkeypatch):
+    """-> the list of calls as (route, entry, values), the stand-ins of either route noting theirs"""
+    lib, native, log = hgnn.load(), binding._calls, []
+    assert native is not None
+    keep, addresses = [], {}
+    for name in hgnn.EXPORTS:
+        fn = getattr(lib, name)
+        if fn.argtypes and fn.restype in (None, ctypes.c_int):
+            kind = ctypes.CFUNCTYPE(ctypes.c_int, *fn.argtypes)
+            keep.append(kind(lambda *a, name=name: log.append(("native", name, tuple(plain(v) for v in a))) or 0))
+            addresses[name] = ctypes.cast(keep[-1], ctypes.c_void_p).value
+
+    class Ctypes(StandIn):
+        def __getattr__(self, name):
+            if not name.startswith("hgnn_") or name in ("hgnn_status_str", "hgnn_last_error"):
+                return getattr(self.lib, name)
+            return lambda *a: log.append(("ctypes", name, tuple(plain(v) for v in a))) or 0
+
+    native.bind(addresses, binding._raw_stream, binding._current_device)
+    monkeypatch.setattr(binding, "load", lambda: Ctypes(lib, log))
+    yield log
+    native.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in hgnn.EXPORTS}, binding._raw_stream, binding._current_device)
+
+
+def both_ways(hgnn, log, monkeypatch, name, args, kw):
+    """-> (route, values) of a call with the native module, after the same without it, whose values must be the same"""
+    native = binding._calls
+    got = []
+    for module in (native, None):
+        del log[:]
+        monkeypatch.setattr(binding, "_calls", module)
+        getattr(hgnn, name)(*args, **kw)
+        assert len(log) == 1, (name, kw, log)
+        got += log
+    monkeypatch.setattr(binding, "_calls", native)
+    assert got[1][0] == "ctypes" and got[0][1:] == got[1][1:], (name, kw, got)
+    return got[0][0]
+
+
+@pytest.mark.gpu
+def test_plain_calls_are_made_natively(hgnn, dev, taken, monkeypatch):
+    g, gt, p, pt, calls = arguments(dev)
+    for name, forms in calls.items():
+        for args, kw in forms:
+            assert both_ways(hgnn, taken, monkeypatch, name, args, kw) == "native", (name, kw)
+    p.handle = pt.handle = None  # (not the library's)
