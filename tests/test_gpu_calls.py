@@ -213,3 +213,31 @@ def test_plain_calls_are_made_natively(hgnn, dev, taken, monkeypatch):
         for args, kw in forms:
             assert both_ways(hgnn, taken, monkeypatch, name, args, kw) == "native", (name, kw)
     p.handle = pt.handle = None  # (not the library's)
+
+
+@pytest.mark.gpu
+def test_streams_and_whole_numbers_are_plain(hgnn, dev, taken, monkeypatch):
+    """A stream object, as torch hands it out, and an int where a float is meant cost no second way."""
+    g, gt, p, pt, calls = arguments(dev)
+    stream = torch.cuda.Stream()
+
+    class Holder:
+        cuda_stream = 0x4560
+
+    for name, forms in calls.items():
+        args, kw = forms[-1]
+        for s in (stream, torch.cuda.current_stream(), torch.cuda.ExternalStream(stream.cuda_stream), Holder(), 0, 0x7f0000001230):
+            assert both_ways(hgnn, taken, monkeypatch, name, args, dict(kw, stream=s)) == "native", (name, s)
+            assert taken[0][2][-1] == getattr(s, "cuda_stream", s)
+        if "neg_slope" in kw:
+            assert both_ways(hgnn, taken, monkeypatch, name, args, dict(kw, neg_slope=0)) == "native"
+    X, W, Y = calls["hgnn_linear"][0][0]
+
+    class Sub(torch.Tensor):
+        pass
+
+    for args, kw in [((X.as_subclass(Sub), W, Y), {}), ((X, W, Y, None), {}), ((X, W, Y), {"stream": "7"}), ((X, W, Y), {"stream": 7.0})]:  # as ever by ctypes
+        assert both_ways(hgnn, taken, monkeypatch, "hgnn_linear", args, kw) == "ctypes", (args, kw)
+    for args, kw in [((X, W, Y), {"K": True}), ((X, W, Y, 1), {}), ((X, W, Y, 0), {}), ((X, W, Y, 1 << 70), {})]:
+        assert both_ways(hgnn, taken, monkeypatch, "hgnn_linear", args, kw) == "native", (args, kw)
+    p.handle = pt.handle = None
