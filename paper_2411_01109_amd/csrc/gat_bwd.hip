@@ -94,7 +94,9 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
   const int f0 = 8 * l;
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
-  const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
+  const int LH = a.D / 8;
+  int head = head_of_lane(active ? l : 0, LH);
+  if (RS == 8) asm("" : "+v"(head));  // (else the compiler holds what follows from it in registers that it does not have: 12 bytes spilled, 2 to 9 %)
   const bool leader = active && (l & (LH - 1)) == 0;
   const TaskWave w = task_enter<L, Rd::R>(v, blockIdx.x, g);
   a.enter_block(w.block);
