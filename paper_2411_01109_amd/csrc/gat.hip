@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kWave, 5 - (SAVE && RS == 1)) void gat_task_kernel(
 // wave with a final merge across the groups.
 constexpr int kShortPieces = 8;
 
-template <int L, bool SAVE>
+template <int L, bool SAVE, bool MANY>
 __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
 #pragma clang fp contract(off)
   constexpr int G = kWave / L, kMany = kManyPieces * G;
@@ -364,16 +364,18 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
   const bool leader = active && (l & (LH - 1)) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  if ((MANY ? int64_t(blockIdx.x) * kWavesPerBlock * per_wave : i0) >= n_split) return;  // MANY: the whole workgroup
   __shared__ int4_t s_row[kWavesPerBlock * G];
   __shared__ __align__(4) unsigned char s_bytes[kWavesPerBlock * L * sizeof(Soft<SAVE>)];
   Soft<SAVE>* const s_soft = reinterpret_cast<Soft<SAVE>*>(s_bytes);
   __shared__ int s_n;
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
+  if (MANY) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+  }
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
-  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
+  if (MANY && q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   const int alone = per_wave > 1 ? kShortPieces : 0;
   // merges the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](Soft<SAVE>& t, pos_t first, pos_t end, pos_t stride) {
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
   }
   for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= alone || n > kMany) continue;
+    if (n <= alone || (MANY && n > kMany)) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     Soft<SAVE> t;
     take(t, first + g, first + n, G);
@@ -426,6 +428,7 @@ __global__ __launch_bounds__(kBlock) void gat_finish_kernel(GatArgs a, const int
     b.enter_block(bj);
     if (g == 0 && active) row_store<SAVE>(b, rj, f0, head, leader, t);
   }
+  if (!MANY) return;
   __syncthreads();
   for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order), by all waves
     const int4_t r = s_row[j];
@@ -509,8 +512,13 @@ static void launch_gat_tasks(int L, int lh, unsigned waves, hipStream_t s, const
 
 template <int L>
 static void launch_gat_finish_l(bool save, dim3 grid, int per_wave, hipStream_t s, const GatArgs& a, const TaskView& v) {
-  if (save) gat_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
-  else gat_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+  if (many_pieces(v, kWave / L)) {
+    if (save) gat_finish_kernel<L, true, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+    else gat_finish_kernel<L, false, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+  } else {
+    if (save) gat_finish_kernel<L, true, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+    else gat_finish_kernel<L, false, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+  }
 }
 
 static void launch_gat_finish(int L, bool save, hipStream_t s, const GatArgs& a, const TaskView& v) {

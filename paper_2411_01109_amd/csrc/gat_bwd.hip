@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kWave, (VEC ? 5 : 6) - (RS <= 2)) void gat_bwd_task
 }
 
 // Follow-up kernel: sums the staged pieces of every row that has several, in order.
-template <int L, bool VEC>
+template <int L, bool VEC, bool MANY>
 __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, const int4_t* __restrict__ split, int n_split, int per_wave) {
   constexpr int G = kWave / L, kMany = kManyPieces * G;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -221,15 +221,17 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   const int LH = a.D / 8, head = head_of_lane(active ? l : 0, LH);
   const bool leader = active && (l & (LH - 1)) == 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  if ((MANY ? int64_t(blockIdx.x) * kWavesPerBlock * per_wave : i0) >= n_split) return;  // MANY: the whole workgroup
   __shared__ int4_t s_row[kWavesPerBlock * G];
   __shared__ float s_sum[kWavesPerBlock][L][9];
   __shared__ int s_n;
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
+  if (MANY) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+  }
   int4_t q = {0, 0, 0, 0};  // row, first slot, pieces, block
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
-  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
+  if (MANY && q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   const int alone = per_wave > 1 ? 8 : 0;  // pieces that a lane group adds by itself
   // adds the pieces first, first + stride, ... < end, four of them in flight at a time
   auto take = [&](float (&acc)[8], float& ds, pos_t first, pos_t end, pos_t stride) {
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
   }
   for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= alone || n > kMany) continue;
+    if (n <= alone || (MANY && n > kMany)) continue;
     const int rj = __shfl(q[0], j * L), first = __shfl(q[1], j * L), bj = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float ds = 0.f;
@@ -280,6 +282,7 @@ __global__ __launch_bounds__(kBlock) void gat_bwd_finish_kernel(GatBwdArgs a, co
     b.enter_block(bj);
     if (g == 0 && active) bwd_row_store<VEC>(b, rj, f0, head, leader, acc, ds);
   }
+  if (!MANY) return;
   __syncthreads();
   for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order), by all waves
     const int4_t r = s_row[j];
@@ -406,18 +409,24 @@ static void launch_bwd_tasks(int L, int lh, unsigned waves, hipStream_t s, const
   }
 }
 
+template <int L, bool VEC>
+static void launch_bwd_finish_l(dim3 grid, int per_wave, hipStream_t s, const GatBwdArgs& a, const TaskView& v) {
+  if (many_pieces(v, kWave / L)) gat_bwd_finish_kernel<L, VEC, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+  else gat_bwd_finish_kernel<L, VEC, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave);
+}
+
 template <bool VEC>
 static void launch_bwd_finish(int L, hipStream_t s, const GatBwdArgs& a, const TaskView& v) {
   const int per_wave = finish_rows_per_wave(v.n_split, v.n_slots, kWave / L);
   const dim3 grid(unsigned(ceil_div(v.n_split, int64_t(kWavesPerBlock) * per_wave)));
   switch (L) {
-    case 1: gat_bwd_finish_kernel<1, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    case 2: gat_bwd_finish_kernel<2, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    case 4: gat_bwd_finish_kernel<4, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    case 8: gat_bwd_finish_kernel<8, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    case 16: gat_bwd_finish_kernel<16, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    case 32: gat_bwd_finish_kernel<32, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
-    default: gat_bwd_finish_kernel<64, VEC><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave); break;
+    case 1: launch_bwd_finish_l<1, VEC>(grid, per_wave, s, a, v); break;
+    case 2: launch_bwd_finish_l<2, VEC>(grid, per_wave, s, a, v); break;
+    case 4: launch_bwd_finish_l<4, VEC>(grid, per_wave, s, a, v); break;
+    case 8: launch_bwd_finish_l<8, VEC>(grid, per_wave, s, a, v); break;
+    case 16: launch_bwd_finish_l<16, VEC>(grid, per_wave, s, a, v); break;
+    case 32: launch_bwd_finish_l<32, VEC>(grid, per_wave, s, a, v); break;
+    default: launch_bwd_finish_l<64, VEC>(grid, per_wave, s, a, v); break;
   }
 }
 

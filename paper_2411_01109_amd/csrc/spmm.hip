@@ -748,7 +748,7 @@ __device__ __forceinline__ void pieces_accumulate32(const SpmmArgs& a, int64_t f
 }
 
 // F32: pieces staged in fp32, n_split is a bound and the number is in *totals
-template <int L, bool F32>
+template <int L, bool F32, bool MANY>
 __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, const int4_t* __restrict__ split, int n_split, int per_wave,
                                                                   const TaskTotals* __restrict__ totals) {
   constexpr int G = kWave / L, kMany = kManyPieces * G;
@@ -762,17 +762,19 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   const bool active = f0 < a.F;
   const int f0c = active ? f0 : 0;
   const int64_t i0 = (int64_t(blockIdx.x) * kWavesPerBlock + wave) * per_wave;
-  if (int64_t(blockIdx.x) * kWavesPerBlock * per_wave >= n_split) return;  // (the whole workgroup)
+  if ((MANY ? int64_t(blockIdx.x) * kWavesPerBlock * per_wave : i0) >= n_split) return;  // MANY: the whole workgroup
   __shared__ int4_t s_row[kWavesPerBlock * G];
   __shared__ float s_sum[kWavesPerBlock][L][8];
   __shared__ int s_n;
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
+  if (MANY) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+  }
   int4_t q = {0, 0, 0, 0};
   if (g < per_wave && i0 + g < n_split) q = split[i0 + g];
   const int alone = per_wave > 1 ? kFinishShort : 0;
   half_t* const Y = a.Y;
-  if (q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
+  if (MANY && q[2] > kMany && l == 0) s_row[atomicAdd(&s_n, 1)] = q;
   if (q[2] > 0 && q[2] <= alone) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<1>(a, q[1], int64_t(q[1]) + q[2] - 1, f0c, acc);
@@ -782,7 +784,7 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
   }
   for (int j = 0; j < per_wave; ++j) {
     const int n = __shfl(q[2], j * L);
-    if (n <= alone || n > kMany) continue;
+    if (n <= alone || (MANY && n > kMany)) continue;
     const int r = __shfl(q[0], j * L), first = __shfl(q[1], j * L), b = __shfl(q[3], j * L);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F32) pieces_accumulate32<G>(a, int64_t(first) + g, int64_t(first) + n - 1, f0c, acc);
@@ -792,6 +794,7 @@ __global__ __launch_bounds__(kBlock) void spmm_task_finish_kernel(SpmmArgs a, co
     a.Y = Y + int64_t(b) * a.block_y_stride;
     if (g == 0 && active) store_row(a, r, f0, acc, 1.f);
   }
+  if (!MANY) return;
   __syncthreads();
   for (int j = 0; j < s_n; ++j) {  // the rows of many pieces, one after the other (in whatever order)
     const int4_t m = s_row[j];
@@ -1498,8 +1501,9 @@ static void launch_zero_split(int L, hipStream_t s, const SpmmArgs& a, const Tas
 
 template <int L>
 static void launch_task_finish_l(dim3 grid, int per_wave, hipStream_t s, const SpmmArgs& a, const TaskView& v) {
-  if (a.stage32) spmm_task_finish_kernel<L, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, v.totals);
-  else spmm_task_finish_kernel<L, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, nullptr);
+  if (a.stage32) spmm_task_finish_kernel<L, true, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, v.totals);
+  else if (many_pieces(v, kWave / L)) spmm_task_finish_kernel<L, false, true><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, nullptr);
+  else spmm_task_finish_kernel<L, false, false><<<grid, kBlock, 0, s>>>(a, v.split, v.n_split, per_wave, nullptr);
 }
 
 static void launch_task_finish(int L, hipStream_t s, const SpmmArgs& a, const TaskView& v) {

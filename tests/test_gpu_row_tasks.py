@@ -568,3 +568,46 @@ def test_rows_of_many_pieces(hgnn, dev, V, D, flip):
         assert np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(a)
     for q in (p, pt, pt1):
         hgnn.hgnn_plan_destroy(q)
+
+
+# one row of 32 pieces for each lane group of a wave, alone or beside one of two pieces, and one piece more: up to there no row can have more, and the
+# follow-up kernels look for none; a piece is one non-zero
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("beside", [0, 1])
+@pytest.mark.parametrize("D", [8, 64, 256])
+def test_as_many_pieces_as_a_wave_adds(hgnn, dev, D, beside, more):
+    print(f"as many pieces D={D} beside={beside} more={more}", flush=True)
+    V, H, r = 90, 2, np.random.default_rng(D + 2 * beside + more)
+    F = H * D
+    deg = np.ones(V, dtype=np.int64)
+    deg[41] = 32 * 64 * 8 // F + more
+    deg[70] += beside
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(r.integers(0, V, size=d)) for d in deg]).astype(np.int32)
+    X, w = f16(r.standard_normal((V, F))), f16(r.standard_normal((col.size, H)))
+    a_l, a_r = f16(0.3 * r.standard_normal(F) / np.sqrt(D)), f16(0.3 * r.standard_normal(F) / np.sqrt(D))
+    g = hgnn.Csr(up(rowptr, dev), up(col, dev))
+    turned = hgnn.hgnn_transpose(g)
+    gt = hgnn.Csr(turned.rowptr, turned.col, ncols=V)
+    p, pt, back = hgnn.hgnn_plan_create(g, 1, F, H, col_blocks=1), hgnn.hgnn_plan_create(gt, 256, F, H, col_blocks=1), hgnn.hgnn_transpose(gt)
+    half = lambda *s: torch.full(s, 7.0, dtype=torch.float16, device=dev)  # noqa: E731
+    f32 = lambda *s: torch.full(s, 7.0, dtype=torch.float32, device=dev)  # noqa: E731
+    Xd, ald, ard = up(X, dev), up(a_l, dev), up(a_r, dev)
+    Y, out, outm, lse, csum = half(V, F), half(V, F), half(V, F), f32(V, H), f32(V, H)
+    hgnn.hgnn_spmm_discretized(p, g, up(w, dev), H, Xd, Y)
+    ref, sabs = oracle.spmm(rowptr, col, X, w=w, H=H, want_sabs=True)
+    compare("sum", down(Y), ref, sabs)
+    hgnn.hgnn_gat_forward_fused_save(g, p, H, D, Xd, Xd, ald, ard, out, lse, outm, csum)
+    oref, lref, oabs, mref, cref = oracle.gat_forward(rowptr, col, X, X, a_l, a_r, H, slope=0.2, want_saved=True)
+    compare("out", down(out), oref, oabs)
+    compare("out_masked", down(outm), mref, oabs)
+    # the pass over the transpose has the long row where the graph itself is the transpose
+    o2, m2, l2, c2 = half(V, F), half(V, F), f32(V, H), f32(V, H)
+    hgnn.hgnn_gat_forward_fused_save(gt, pt, H, D, Xd, Xd, ald, ard, o2, l2, m2, c2)
+    got = []
+    for q in (hgnn.hgnn_plan_create(back, 1, F, H, col_blocks=1), hgnn.hgnn_plan_create(back, 256, F, H, col_blocks=1)):
+        dV, d_el, d_er = half(V, F), half(V, H), half(V, H)
+        hgnn.hgnn_gat_backward_fused_saved(gt, pt, back, q, H, D, Xd, Xd, ald, ard, o2, l2, m2, c2, Xd, dV, d_el, d_er)
+        got.append([down(t).astype(np.float64) for t in (dV, d_el, d_er)])
+    for a, b in zip(*got):  # one rounding of a row against one of each of its pieces beside it
+        assert np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(a)
