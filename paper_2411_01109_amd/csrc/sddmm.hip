@@ -40,8 +40,10 @@ constexpr int kTile = 256;  // non-zeros per wave in the kernels that run withou
 // head of 64 in blocks: 1.06 -> 0.92 ms; 5.5 M, four heads of 16: the same (58 us); on power-law graphs of 20 to 31 M, where the
 // gathers miss the L2s and the results of a row no longer fill lines with their neighbours', 1 to 6 % slower (31 M: one head of
 // 64 338 -> 350 us, four of 16 391 -> 393).
+// Rows of 32 bytes keep to five waves a SIMD: with six, which their registers allow, tables beyond an L2 are fetched more often: uniform, 200 000 vertices, 1 M
+// non-zeros 17.4 / 19.6 us, 2.4 M 31.6 / 35.9 (power law, where most gathers hit, 26.3 / 25.8).
 template <int L, bool NEAR, bool MASK, int RS, int VW, int MOST>
-__global__ __launch_bounds__(kWave, RS <= 2 ? 5 : 6) void sddmm_task_kernel(SddmmArgs a, TaskView v) {
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(RS <= 2 ? 5 : 6, NEAR && !MASK && L == 2 && RS == 2 && VW == 8 ? 5 : 8))) void sddmm_task_kernel(SddmmArgs a, TaskView v) {
   constexpr int G = kWave / L;
   typedef _Float16 hv_t __attribute__((ext_vector_type(VW)));
   typedef Round<L, MOST> Rd;

@@ -39,3 +39,9 @@ def test_backward_of_attention_spills_nothing(hgnn):
     assert len(ours) > 20
     spilled = {n: k[".private_segment_fixed_size"] for n, k in ours.items() if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
     assert not spilled
+
+
+def test_dot_products_of_short_rows_keep_to_five_waves(hgnn):
+    """Rows of 32 bytes: a SIMD's 512 registers hold five waves of 81 to 96."""
+    ours = {n: k[".vgpr_count"] for n, k in kernels().items() if "sddmm_task_kernelILi2ELb1ELb0ELi2ELi8E" in n}
+    assert ours and all(80 < v <= 96 for v in ours.values()), ours
