@@ -10,7 +10,7 @@ msgpack = pytest.importorskip("msgpack")
 
 
 def kernels():
-    """-> {kernel: what its code object says of it} of the library"""
+    """-> {kernel: what its code object says of it} of the library; "registers": what a wave is given of a SIMD's 512, in steps of eight"""
     with open(hip_build.LIB_PATH, "rb") as fh:
         lib = fh.read()
     out, at = {}, lib.find(b"\x7fELF", 1)
@@ -18,17 +18,27 @@ def kernels():
         if lib[at + 4:at + 6] == b"\x02\x01" and struct.unpack_from("<H", lib, at + 18)[0] == 224:  # AMDGPU
             shoff = struct.unpack_from("<Q", lib, at + 40)[0]
             size, n = struct.unpack_from("<HH", lib, at + 58)
-            for i in range(n):
-                kind, _, _, offset, length = struct.unpack_from("<IQQQQ", lib, at + shoff + i * size + 4)
-                if kind != 7:  # SHT_NOTE
-                    continue
-                p, end = at + offset, at + offset + length
-                while p < end:
-                    namesz, descsz, what = struct.unpack_from("<III", lib, p)
-                    desc = p + 12 + (namesz + 3) // 4 * 4
-                    if what == 32:
-                        out.update((k[".name"], k) for k in msgpack.unpackb(lib[desc:desc + descsz])["amdhsa.kernels"])
-                    p = desc + (descsz + 3) // 4 * 4
+            sections = [struct.unpack_from("<IIQQQQII", lib, at + shoff + i * size) for i in range(n)]  # name, type, flags, address, offset, size, link, info
+            ours, given = {}, {}
+            for _, kind, _, _, offset, length, link, _ in sections:
+                if kind == 7:  # SHT_NOTE
+                    p, end = at + offset, at + offset + length
+                    while p < end:
+                        namesz, descsz, what = struct.unpack_from("<III", lib, p)
+                        desc = p + 12 + (namesz + 3) // 4 * 4
+                        if what == 32:
+                            ours.update((k[".name"], k) for k in msgpack.unpackb(lib[desc:desc + descsz])["amdhsa.kernels"])
+                        p = desc + (descsz + 3) // 4 * 4
+                if kind == 11:  # SHT_DYNSYM: the kernels' descriptors, whose word at 48 begins with the registers
+                    for p in range(at + offset, at + offset + length, 24):
+                        name, _, _, index, value, _ = struct.unpack_from("<IBBHQQ", lib, p)
+                        name = at + sections[link][4] + name
+                        name = lib[name:lib.index(b"\0", name)].decode()
+                        if name.endswith(".kd"):
+                            where = at + value - sections[index][3] + sections[index][4]
+                            given[name[:-3]] = 8 * ((struct.unpack_from("<I", lib, where + 48)[0] & 63) + 1)
+            for name, k in ours.items():
+                out[name] = dict(k, registers=given[name])
         at = lib.find(b"\x7fELF", at + 4)
     return out
 
@@ -42,6 +52,6 @@ def test_backward_of_attention_spills_nothing(hgnn):
 
 
 def test_dot_products_of_short_rows_keep_to_five_waves(hgnn):
-    """Rows of 32 bytes: a SIMD's 512 registers hold five waves of 81 to 96."""
-    ours = {n: k[".vgpr_count"] for n, k in kernels().items() if "sddmm_task_kernelILi2ELb1ELb0ELi2ELi8E" in n}
-    assert ours and all(80 < v <= 96 for v in ours.values()), ours
+    """Rows of 32 bytes: a SIMD's 512 registers hold five waves of 88 or 96."""
+    ours = {n: k["registers"] for n, k in kernels().items() if "sddmm_task_kernelILi2ELb1ELb0ELi2ELi8E" in n}
+    assert ours and all(v in (88, 96) for v in ours.values()), ours
