@@ -338,7 +338,7 @@ __global__ __launch_bounds__(1024) void linear_kernel(LinearArgs a) {
 // each takes at most kSplitSteps steps of 32 columns, whose loads all go out before the weight is brought in, and the partial
 // results are added through LDS in the order of the parts.  One row block per workgroup.  Bound by the latencies of a launch, of the
 // rows and of the weight, which more lanes bring in: 19 717 x 504 -> 64 12.9 -> 10.0 us (its bytes take 4.6), 4096 x 504 -> 64 9.0 -> 6.0; with the
-// weight asked for ahead of X, calls in a row from a graph, 6.6 -> 6.3 and 5.4 -> 4.6, 12 000 x 504 -> 128 by W^T 8.5 -> 9.1.
+// weight asked for ahead of X, calls in a row from a graph, 7.2 -> 6.1 and 5.9 -> 4.7, 12 000 x 504 -> 128 by W^T 9.0 -> 8.8.
 constexpr int kSplitSteps = 10;
 
 template <int NT, int KP, bool TRANS, bool ANY>
@@ -880,18 +880,20 @@ static hgnn_status linear_impl(const char* who, int64_t n, int32_t K, int32_t KW
   hipStream_t s = static_cast<hipStream_t>(stream);
   // Few rows with many columns: as many row tiles per workgroup as give every compute unit one, and waves beside them up to 16 that
   // share a tile's columns.  us, a chain of loads per wave / shared (inputs out of the caches):
-  //   K, F               1000        4096        8192       12000       19717       25000       32768 rows
-  //   128, 64          5.9 / 5.0   5.6 / 4.7   4.8 / 4.8   5.2 / 5.0   6.1 / 5.7   6.5 / 6.4   7.2 / 7.1
-  //   128, 128, W^T    7.2 / 5.0   7.1 / 4.7   7.5 / 5.0   8.2 / 5.4   7.4 / 6.5   8.2 / 7.9   9.1 / 8.8
-  //   256, 64          6.4 / 5.0   6.7 / 5.4   6.9 / 5.7   7.8 / 6.1   8.0 / 7.0   8.5 / 8.1   9.0 / 9.1
-  //   504, 64          8.6 / 5.5   9.0 / 6.0   9.2 / 6.6  10.9 / 8.1  12.9 / 10.0 14.0 / 12.1 13.5 / 13.3
-  //   504, 128, W^T   13.2 / 8.1  13.3 / 8.8  13.6 / 9.4  16.1 / 10.5 24.3 / 13.6 24.4 / 16.5 17.8 / 17.8
-  //   1024, 64        16.3 / 8.6  16.4 / 9.0  21.7 / 11.7 22.1 / 12.2
-  // (before the weight was asked for ahead of X, which took 0.3 to 1 us off both sides)
-  // at 40 000 rows (two rounds of workgroups) 10 to 40 % slower.
-  // Behind the kernel that wrote X, in the caches, a chain of few steps ends sooner: 256, 64 at 32 768 rows 7.9 / 8.6, 256, 128 10.5 / 11.3; 128, 64
-  // at 8192 5.2 / 5.5, at 5000 6.6 / 5.4, W^T 5.6 / 4.6 and 7.1 / 4.5; 128, 128 at 8192, 20 000, 27 000 7.2 / 6.5, 7.5 / 7.3, 7.8 / 8.1; 128, 32 at 2000
-  // 4.5 / 4.6.
+  //   K, F               1000        4096        8192       12000       16384       19717       25000       32768 rows
+  //   128, 64          3.6 / 3.5   4.0 / 3.8   4.0 / 3.9   4.6 / 4.2   4.5 / 4.6   5.2 / 5.1   5.4 / 5.6   5.8 / 6.3
+  //   128, 128         4.2 / 4.2   4.3 / 4.4   5.0 / 4.8   5.8 / 5.5   5.5 / 6.1   6.3 / 6.4   6.7 / 7.3   7.9 / 8.9
+  //   128, 128, W^T    5.6 / 4.6   5.8 / 4.7   6.4 / 5.2   7.7 / 5.6   5.9 / 6.4   6.9 / 6.5   7.3 / 7.7   8.4 / 9.0
+  //   256, 64          4.4 / 4.1   5.2 / 4.8   5.4 / 5.1   6.1 / 5.7   6.1 / 6.2   7.0 / 6.4   7.6 / 7.4   8.0 / 8.1
+  //   256, 128         5.9 / 5.2   6.6 / 5.7   6.8 / 6.1   7.1 / 6.9   7.7 / 8.0   9.6 / 8.7  10.0 / 9.9  10.4 / 11.1
+  //   504, 64          7.1 / 4.9   7.3 / 5.3   7.6 / 5.8   9.0 / 7.2   9.7 / 8.8  11.9 / 9.5  12.3 / 11.1 12.2 / 12.7
+  //   504, 128, W^T   11.6 / 7.8  12.0 / 8.3  12.4 / 9.1  14.1 / 10.8 15.0 / 12.6 19.9 / 13.6 20.3 / 15.7 15.6 / 16.7
+  //   1024, 64        11.9 / 7.1  12.1 / 7.4  14.8 / 9.0  15.2 / 10.8 15.7 / 12.9
+  // (at 16 384 and 32 768 rows a chain's workgroups of four waves are one or two for every compute unit).  At 40 000 rows (two rounds of workgroups) sharing was
+  // 10 to 40 % slower when it was last tried.
+  // Behind the kernel that wrote X, in the caches, a chain of few steps ends sooner: 256, 64 at 16 384, 25 000, 32 768 rows 5.0 / 5.4, 5.9 / 5.7, 6.2 / 6.4, 256, 128 6.7 /
+  // 7.4, 8.3 / 8.0, 8.4 / 9.0; 128, 64 at 5000, 8192, 25 000 3.9 / 3.7, 3.6 / 3.8, 4.7 / 5.0, 128, 128 at 8192, 12 000, 19 717 4.5 / 4.6, 5.4 / 5.2, 5.7 / 5.8, W^T 6.0 / 5.0, 7.2 /
+  // 5.5, 6.3 / 6.2; 128, 32 at 2000, 12 000, 28 000 3.0 / 3.2, 3.7 / 3.6, 4.4 / 4.3 (out of the caches 3.0 / 3.3, 4.1 / 3.7, 5.0 / 5.0).
   const int T = int(std::max<int64_t>(2, ceil_div(tiles, kCus))), KP = T <= 4 ? 4 : (T == 5 ? 3 : 2);
   const bool shared = K > 256 ? T <= 8 : (K > 128 ? T <= 7 : K == 128 && T <= 5 && (trans_w || F > 64 || (F > 32 && n < 8192)));
   if (RT == 1 && shared && k32 <= KP * kSplitSteps * 32 && F <= 128 && a.KC == k32 && a.FC == 16 * nt) {

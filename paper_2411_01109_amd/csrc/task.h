@@ -222,7 +222,8 @@ __host__ __device__ inline int finish_rows_per_wave(int n_split, int n_slots, in
 
 // A row of more than this many pieces for each lane group of a wave is added by all waves of a workgroup of the follow-up kernels: the longest row
 // of a power law was most of a launch (62 M non-zeros x 128, 770 pieces: SpMM 43.8 -> 25 us; whole calls, 20 M x 128 326 -> 319.5, attention
-// forward 514 -> 505, backward 643 -> 633, 31 M x 64 296 -> 292.5, 456 -> 447, 678 -> 674; smaller ones the same).
+// forward 514 -> 505, backward 643 -> 633, 31 M x 64 296 -> 292.5, 456 -> 447, 678 -> 674; smaller ones the same).  Never, 128, 64, 32, 16, 8 pieces: 2 M of
+// 20 000 vertices x 128, attention forward 64.1, 63.7, 63.4, 60.1, 60.0, 59.4, backward 49.5, 48.8, 48.9, 46.4, 46.9, 46.4; 31 M x 64 409.7, 407.0, 408.4, 404.3, 403.0, 403.6.
 constexpr int kManyPieces = 32;
 
 // Whether a row may have so many, by the pieces that there are in all (a row of the list has one at least).  Else the follow-up kernels do without the list of

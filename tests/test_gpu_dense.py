@@ -71,8 +71,8 @@ def test_linear_shared_columns(hgnn, dev, n, K, F, trans):
     test_linear_shapes(hgnn, dev, n, K, F, trans, 0, 0)
 
 
-# whole and partial 16-byte pieces of the weight, twice as many waves per workgroup (8192 tiles of rows), 32 waves (few columns, many
-# features); what lies beside and behind the operands must not be looked at
+# whole and partial 16-byte pieces of the weight, twice as many waves per workgroup (8192 tiles of rows), twice as many workgroups as fit (few columns,
+# many features); what lies beside and behind the operands must not be looked at
 @pytest.mark.parametrize("trans", [False, True])
 @pytest.mark.parametrize("n,K,F", [(3, 8, 8), (250, 72, 40), (33000, 40, 52), (131090, 72, 8), (110001, 8, 608), (20000, 168, 100), (70, 2504, 24)])
 def test_linear_stays_inside(hgnn, dev, n, K, F, trans):

@@ -137,6 +137,33 @@ def test_half_of_the_lanes(hgnn, dev, mean, H):
     hgnn.hgnn_plan_destroy(p)
 
 
+# so many rows that half of the lanes take them (16, 60 or 96 waves of all lanes a compute unit), or just not; some rows at and beyond what the half hold
+@pytest.mark.parametrize("V,mean,H,alike", [(17000, 20, 4, True), (9000, 20, 8, True), (8100, 20, 8, True), (33000, 40, 1, True), (4200, 140, 2, True), (124000, 50, 1, True),
+                                            (200000, 6, 8, False), (60000, 6, 8, True), (200000, 6, 4, False)])
+def test_half_of_the_lanes_of_many_rows(hgnn, dev, V, mean, H, alike):
+    print(f"half of the lanes, many rows V={V} mean={mean} H={H} alike={alike}", flush=True)
+    r = np.random.default_rng(V + mean + H)
+    deg = r.integers(mean - 1, mean + 2, V) if alike else r.integers(0, 2 * mean, V)
+    held = 1
+    while held < mean:
+        held *= 2
+    for k, d in enumerate((held - 1, held, held + 1, 2 * held, 2 * held + 1, 33, 300, 0)):
+        deg[11 + k::V // 9] = d
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowptr[-1])
+    e16 = f16(3 * r.standard_normal((E, H)))
+    g = csr_of(hgnn, dev, deg)
+    p = hgnn.hgnn_plan_create(g, 256, 64, 8)
+    alpha, out = (torch.full((n, H), 9.0, dtype=torch.float16, device=dev) for n in (E, V))
+    hgnn.hgnn_edge_softmax(g, p, H, up(e16, dev), alpha)
+    e64 = e16.astype(np.float64)
+    ref = oracle.edge_softmax(rowptr, e64)
+    assert np.all(np.abs(down(alpha).astype(np.float64) - ref) <= ref * (2.0 ** -11 + 2.0 ** -18) + 2.0 ** -24)
+    hgnn.hgnn_edge_rowsum(g, p, H, up(e16, dev), out)
+    compare("row sums", down(out), oracle.edge_rowsum(rowptr, e64), oracle.edge_rowsum(rowptr, np.abs(e64)))
+    hgnn.hgnn_plan_destroy(p)
+
+
 @pytest.mark.parametrize("H,planned", [(1, False), (4, False), (8, False), (1, True), (2, True)])
 def test_rows_in_order_of_their_lengths(hgnn, dev, H, planned):
     """Vertices in the order of their degrees, longest rows side by side, take no longer than the same rows in any order: sixteen of the longest in
