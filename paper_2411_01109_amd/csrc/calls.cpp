@@ -1,6 +1,6 @@
 // The calls of a training or inference step, from Python tensors to the C entry points.  On small graphs a step's time is the host's:
-// a GCN layer of 4096 vertices is five calls and six launches that the GPU ends in 20.7 us; each call spent 2 us in Python and ctypes
-// beside some 2.7 us a launch, 26.2 us in all, and spends 0.5 here.
+// a GCN layer of 4096 vertices is five calls and six launches that the GPU ends in 20.4 us; each call spent 1.9 us in Python and ctypes
+// beside some 2.7 us a launch, 26.2 us in all, and spends 0.28 here, 18.8 in all (0.2 more with a stream object).
 //
 // A function takes what its Python wrapper takes, in the wrapper's order, and returns the call's status, or -1 (kOther) without having
 // called anything when an argument is not of the plain form (a tensor of the expected type on the GPU, an int, a float, a stream, None where

@@ -97,8 +97,8 @@ __global__ __launch_bounds__(kSliceThreads) void edge_slice_kernel(SliceArgs a) 
   // twice, for the sums the repeated value is replaced by zero.  The row of a slot, among those that have a piece, is the number of pieces that
   // begin behind the first slot and not behind this one: their first slots, less one, are set as bits, which a lane counts below its own.  A binary
   // search over the prefix values, six LDS reads in turn and some 24 vector instructions per slot, was half of the kernel.  us, score; column sums,
-  // with it / now: 114 M log-normal 236; 241 / 224; 209, 24 M of 100 000 log-normal 56; 64 / 42; 52, 20 M power law of 100 000 118; 142 / 88; 114, 8 M of
-  // 30 000 uniform 23.3; 29.6 / 18.9; 26.4.  The largest are bound by the memory's lines now, of which neighbouring pieces share many (3.1 and 3.3 TB/s).
+  // with it / now, on one machine: 114 M log-normal 236; 241 / 224; 209, 24 M of 100 000 log-normal 56; 64 / 42; 52, 20 M power law of 100 000 118; 142 / 88; 114, 8 M of
+  // 30 000 uniform 23.3; 29.6 / 18.9; 26.4.  The largest are bound by the memory's lines now, of which neighbouring pieces share many (3.2 and 3.3 TB/s; on another machine 218; 203).
   auto plan_round = [&](pos_t qb, pos_t total, pos_t begin, bool has, unsigned& before, int (&kk)[kSliceUnroll], int (&jj)[kSliceUnroll]) {
     if (lane < 2 * kSliceUnroll) s_begins[lane] = 0u;
     wave_sync();
